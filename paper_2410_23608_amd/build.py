@@ -1,7 +1,8 @@
-"""Builds libspa.so (gfx950 only) from csrc/*.hip with hipcc.
+"""Builds libspa.so (gfx950 only) from csrc/*.hip with hipcc, and the CPython module _launcher from
+csrc/launcher.cpp (the host path of a step; no device code).
 
 Usage: python -m paper_2410_23608_amd.build [--sanitize-host]
-The shared library is written next to this file so that it travels with the source tree.
+Both are written next to this file so that they travel with the source tree.
 --sanitize-host builds libspa_asan.so in <tmp>/spa_build_asan instead: the HOST side of every source under
 AddressSanitizer and UndefinedBehaviorSanitizer (device code unchanged), for the host-only checks
 of tests/test_host_sanitizers.py; it is never loaded by the binding.
@@ -12,6 +13,7 @@ import concurrent.futures
 import os
 import subprocess
 import sys
+import sysconfig
 import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -19,6 +21,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libspa.so")
+LAUNCHER_PATH = os.path.join(HERE, "_launcher.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -63,6 +66,16 @@ def _compile(src: str, sanitize: bool = False) -> str:
     return obj
 
 
+def build_launcher() -> str:
+    cmd = [HIPCC, "-O2", "-std=c++17", "-fPIC", "-shared", "-x", "c++", "-I", sysconfig.get_paths()["include"],
+           "-I", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"), "-D__HIP_PLATFORM_AMD__",
+           "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "launcher.cpp"), "-o", LAUNCHER_PATH]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"hipcc failed for launcher.cpp:\n{r.stdout}\n{r.stderr}")
+    return LAUNCHER_PATH
+
+
 def build(verbose: bool = True, sanitize: bool = False) -> str:
     os.makedirs(SAN_DIR if sanitize else OBJ_DIR, exist_ok=True)
     srcs = sources()
@@ -71,7 +84,10 @@ def build(verbose: bool = True, sanitize: bool = False) -> str:
         print(f"[build] compiling {len(srcs)} HIP sources for gfx950" + (" (host side sanitized)" if sanitize else ""),
               flush=True)
     with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
+        launcher = None if sanitize else ex.submit(build_launcher)
         objs = list(ex.map(lambda s_: _compile(s_, sanitize), srcs))
+        if launcher is not None:
+            launcher.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib, *objs]
     if sanitize:   # (a link line has no -Xarch_ option: the device side is kept out explicitly)
         cmd += ["-fsanitize=address", "-fsanitize=undefined", "-fno-gpu-sanitize"]

@@ -20,7 +20,47 @@ def _td(dtype: str):
     return torch.bfloat16 if dtype == "bf16" else torch.float32
 
 
-class ForwardPass:
+class _Pass:
+    """run(): the step on the caller's tensors, without marshalling them call by call.
+
+    The second run on inputs of the same shapes and dtypes records the step once (`spa.record`); from
+    then on a run is one native call that checks the inputs and issues the launches on the current
+    stream.  Inputs the recording does not cover (other shapes, a wrong device or layout) take the
+    stages one by one, checks and errors included.  Assigning an attribute of any pass (a bias, a
+    buffer) drops the recordings made before."""
+    _epoch = 0
+
+    def __setattr__(self, name, value):
+        if name in self.__dict__ and name[:5] != "_plan":
+            _Pass._epoch += 1
+        object.__setattr__(self, name, value)
+
+    _plan, _plans, _plan_epoch, _plan_seen = None, (), -1, None
+
+    def _issue(self, stages, *inputs):
+        plan = self._plan
+        if plan is None or self._plan_epoch != _Pass._epoch or not plan(*inputs):
+            self._issue_new(stages, inputs)
+
+    def _issue_new(self, stages, inputs):
+        if self._plan_epoch != _Pass._epoch:
+            self._plan, self._plans, self._plan_epoch, self._plan_seen = None, (), _Pass._epoch, None
+        for plan in self._plans:
+            if plan(*inputs):
+                self._plan = plan
+                return
+        seen = [None if t is None else (t.shape, t.dtype) for t in inputs]
+        if seen == self._plan_seen:
+            plan = spa.record(stages, inputs)
+            if plan(*inputs):
+                self._plan, self._plans = plan, (plan, *self._plans[:3])
+                return
+        self._plan_seen = seen
+        for _, fn in stages(*inputs):
+            fn()
+
+
+class ForwardPass(_Pass):
     """gate_select(x) -> pack(qkv) -> packed_attention -> unpack.
 
     fused_unpack=True (default) issues the last two steps as ONE launch
@@ -115,12 +155,11 @@ class ForwardPass:
         ]
 
     def run(self, x, w, qkv, s_up=None, base=None):
-        for _, fn in self.stages(x, w, qkv, s_up, base):
-            fn()
+        self._issue(self.stages, x, w, qkv, s_up, base)
         return self.y
 
 
-class TrainPass:
+class TrainPass(_Pass):
     """Forward + backward of one SPA block with the selection loss (Section 3.3).
 
     q | k are supplied ([B, N, 2C], stand-ins for projected tokens); v is the packed gated
@@ -178,7 +217,8 @@ class TrainPass:
         if s_fine is not None:
             if noise is not None:
                 raise ValueError("s_fine and noise together are not wired up")
-            self.s_up = torch.empty(self.B, self.N, dtype=torch.float32, device="cuda")
+            if not hasattr(self, "s_up"):
+                self.s_up = torch.empty(self.B, self.N, dtype=torch.float32, device="cuda")
             st[0] = ("gate_select_pooled", spa.spa_gate_select_pooled(
                 x, w, self.bias, s_fine, grid[0], grid[1], self.tau, self.scores, self.mask, None, self.s_up,
                 prepare=True))
@@ -233,12 +273,11 @@ class TrainPass:
         ]
 
     def run(self, x, w, qk, labels, dy):
-        for _, fn in self.stages(x, w, qk, labels, dy):
-            fn()
+        self._issue(self.stages, x, w, qk, labels, dy)
         return self.loss
 
 
-class BlockPass:
+class BlockPass(_Pass):
     """One SPA attention block with its projections (Section 3.2), six launches:
 
       gate_select(x) -> pack (indices only) -> QKV projection of the selected, gated tokens
@@ -290,12 +329,11 @@ class BlockPass:
         ])
 
     def run(self, x, w, W_qkv, b_qkv, W_o, b_o):
-        for _, fn in self.stages(x, w, W_qkv, b_qkv, W_o, b_o):
-            fn()
+        self._issue(self.stages, x, w, W_qkv, b_qkv, W_o, b_o)
         return x if self.in_place else self.y
 
 
-class BlockTrainPass:
+class BlockTrainPass(_Pass):
     """Forward + backward of one SPA attention block WITH its projections (Section 3.2) and the
     selection loss (Section 3.3), twelve launches:
 
@@ -367,19 +405,12 @@ class BlockTrainPass:
         if self.overlap:
             with torch.cuda.stream(self.side):             # the prepared calls keep the stream they were made on
                 w_o, w_qkv = weight_side()
-            events = [torch.cuda.Event() for _ in range(3)]
+            events = [spa.Event() for _ in range(3)]
 
-            def on_side(ev, call):
-                def go():
-                    ev.record(main)                        # inputs of the GEMM are complete on the main stream
-                    self.side.wait_event(ev)
-                    call()
-                return go
+            def on_side(ev, call):      # inputs of the GEMM are complete on the main stream
+                return spa.chain(ev.record(main), ev.wait(self.side), call)
 
-            def join():
-                events[2].record(self.side)
-                main.wait_event(events[2])
-
+            join = spa.chain(events[2].record(self.side), events[2].wait(main))
             w_o, w_qkv = on_side(events[0], w_o), on_side(events[1], w_qkv)
         else:
             w_o, w_qkv = weight_side()
@@ -410,12 +441,11 @@ class BlockTrainPass:
         ] + ([("join_streams", join)] if self.overlap else [])
 
     def run(self, x, w, W_qkv, b_qkv, W_o, b_o, labels, dy):
-        for _, fn in self.stages(x, w, W_qkv, b_qkv, W_o, b_o, labels, dy):
-            fn()
+        self._issue(self.stages, x, w, W_qkv, b_qkv, W_o, b_o, labels, dy)
         return self.loss
 
 
-class ContainerForwardPass:
+class ContainerForwardPass(_Pass):
     """The forward pass with the paper's container mask (Section 3.2 "Token Packing"): the
     packed stream is cut into containers of length L and a token attends to the tokens of its
     own image inside its own container; shift = (sh, sw) packs the cyclically shifted map.
@@ -467,8 +497,7 @@ class ContainerForwardPass:
         ])
 
     def run(self, x, w, qkv, base=None):
-        for _, fn in self.stages(x, w, qkv, base):
-            fn()
+        self._issue(self.stages, x, w, qkv, base)
         return self.y
 
 
@@ -482,44 +511,29 @@ def _on_streams(per_stage, streams, stream_of):
     gain over one stream).  The first entry forks the streams off the stream that is current when
     the list is built, the last one joins them back."""
     main = torch.cuda.current_stream()
-    start = torch.cuda.Event()
-    done = [torch.cuda.Event() for _ in streams]
+    start = spa.Event()
+    done = [spa.Event() for _ in streams]
     n = len(per_stage)
     crossing = [i + 1 < n and stream_of[i + 1] != stream_of[i] for i in range(n)]
-    handed = [torch.cuda.Event() if c else None for c in crossing]
-
-    def fork():
-        start.record(main)
-        for st in streams:
-            st.wait_event(start)
-
-    def join():
-        for ev, st in zip(done, streams):
-            ev.record(st)
-            main.wait_event(ev)
-
+    handed = [spa.Event() if c else None for c in crossing]
+    fork = spa.chain(start.record(main), *(start.wait(st) for st in streams))
+    join = spa.chain(*(op for ev, st in zip(done, streams) for op in (ev.record(st), ev.wait(main))))
     queues = [[] for _ in streams]
-    for i, chain in enumerate(per_stage):
-        for j, (name, call) in enumerate(chain):
-            st = streams[stream_of[i]]
-            if j == 0 and (crossing[i] or (i > 0 and crossing[i - 1])):
-                def go(call=call, st=st, wait=handed[i - 1] if i > 0 and crossing[i - 1] else None,
-                       signal=handed[i] if crossing[i] else None):
-                    if wait is not None:
-                        st.wait_event(wait)
-                    call()
-                    if signal is not None:
-                        signal.record(st)
-                queues[stream_of[i]].append((name, go))
-            else:
-                queues[stream_of[i]].append((name, call))
+    for i, calls in enumerate(per_stage):
+        st = streams[stream_of[i]]
+        for j, (name, call) in enumerate(calls):
+            if j == 0 and i > 0 and crossing[i - 1]:
+                call = spa.chain(handed[i - 1].wait(st), call)
+            if j == 0 and crossing[i]:
+                call = spa.chain(call, handed[i].record(st))
+            queues[stream_of[i]].append((name, call))
     out = [("fork_streams", fork)]
     for q in queues:
         out += q
     return out + [("join_streams", join)]
 
 
-class HierarchyPass:
+class HierarchyPass(_Pass):
     """A multi-stage hierarchy (Section 3.1, Section 3.2 on multi-scale scores): every stage
     runs gate -> pack -> attention + scatter, and from the second stage on the gate takes the
     previous (2x finer) stage's score map, max-pooled inside the gate kernel, as s_up.
@@ -560,12 +574,13 @@ class HierarchyPass:
         return out
 
     def run(self, xs, ws, qkvs, bases=None):
-        for _, fn in self.stages(xs, ws, qkvs, bases):
-            fn()
+        n = len(self.cfg)
+        self._issue(lambda *t: self.stages(t[:n], t[n:2 * n], t[2 * n:3 * n], t[3 * n:] or None), *xs[:n], *ws[:n],
+                    *qkvs[:n], *(() if bases is None else bases[:n]))
         return [fp.y for fp in self.passes]
 
 
-class HierarchyTrainPass:
+class HierarchyTrainPass(_Pass):
     """Forward + backward of every stage of a hierarchy (TrainPass per stage); from the second
     stage on the gate takes the finer stage's score map (pooled in the gate kernel).  All
     forwards run first (a stage's gate needs the finer stage's scores), then all backwards.
@@ -596,6 +611,7 @@ class HierarchyTrainPass:
         return _on_streams(chains, self.streams, self.stream_of) if self.concurrent else fwd + bwd
 
     def run(self, xs, ws, qks, labels, dys):
-        for _, fn in self.stages(xs, ws, qks, labels, dys):
-            fn()
+        n = len(self.cfg)
+        self._issue(lambda *t: self.stages(*(t[i * n:(i + 1) * n] for i in range(5))), *xs[:n], *ws[:n], *qks[:n],
+                    *labels[:n], *dys[:n])
         return [tp.loss for tp in self.passes]

@@ -3,11 +3,16 @@
 Argument marshalling only — torch tensors supply device memory and the current stream;
 every step of the path runs in the library's HIP kernels.  There is no fallback: if the
 shared library is missing, importing this module raises.
+
+A call made with prepare=True comes back as a native object (`_launcher.Call`, csrc/launcher.cpp)
+that issues the call again with no marshalling; `record` turns a whole step into one such object
+whose inputs and stream are filled in per run.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import threading
 from ctypes import c_char_p, c_double, c_float, c_int, c_int64, c_size_t, c_void_p
 from typing import Optional
 
@@ -22,6 +27,8 @@ if not os.path.exists(LIB_PATH):
         "(the SPA path has no CPU or PyTorch fallback)")
 
 lib = ctypes.CDLL(LIB_PATH)
+
+from . import _launcher  # noqa: E402  (built beside libspa.so; resolves its symbols by address)
 
 SPA_OK, SPA_F32, SPA_BF16 = 0, 0, 1
 
@@ -101,41 +108,92 @@ def _check(rc: int) -> None:
         raise SpaError(rc, lib.spa_last_error().decode())
 
 
-class Prepared:
-    """A C-ABI call with its arguments already marshalled (pointers, sizes and the stream that
-    was current at preparation).  Calling it enqueues the work again with no per-call
-    conversion cost; the tensors it refers to are kept alive by the object."""
-    __slots__ = ("_fn", "_args", "_keep")
+def _raise(rc: int) -> None:
+    raise SpaError(rc, lib.spa_last_error().decode())
 
-    def __init__(self, fn, args, keep):
-        self._fn = fn
-        self._args = tuple(a if not isinstance(a, int) or t is not _P else _P(a)
-                           for a, t in zip(args, fn.argtypes))
-        self._keep = keep
 
-    def __call__(self):
-        rc = self._fn(*self._args)
-        if rc != SPA_OK:
-            raise SpaError(rc, lib.spa_last_error().decode())
+_launcher.setup(_raise, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+_ADDRESS = {name: ctypes.cast(getattr(lib, name), c_void_p).value for name in _SIGNATURES}
+
+# A C-ABI call with its arguments already marshalled (pointers, sizes and the stream that was
+# current at preparation).  Calling it enqueues the work again with no per-call conversion cost;
+# the tensors it refers to are kept alive by the object.
+Prepared = _launcher.Call
 
 
 def _dispatch(fn, args, keep, prepare):
     if prepare:
-        return Prepared(fn, args, keep)
+        return Prepared(fn.__name__, _ADDRESS[fn.__name__], args, keep)
     _check(fn(*args))
     return None
+
+
+class _Recording(threading.local):
+    """The step being recorded on this thread: its inputs (meta tensors, by storage) and the stream
+    that stands for the current one."""
+    slots = None
+    stream = None
+
+
+_recording = _Recording()
 
 
 def _ptr(t: Optional[torch.Tensor]):
     if t is None:
         return None
     if not t.is_cuda:
+        if _recording.slots is not None and t.is_meta:
+            slot = _recording.slots.get(t.untyped_storage()._cdata)
+            if slot is not None:
+                return (slot, t.storage_offset() * t.element_size())
         raise ValueError("libspa takes device tensors")
     return t.data_ptr()
 
 
-def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+def _stream_ref(stream):
+    """A stream as an argument of a prepared call: its handle, or the place of the current stream in a
+    recorded step."""
+    raw = stream.cuda_stream
+    return (-1, 0) if raw == _recording.stream else raw
+
+
+def _stream():
+    return _stream_ref(torch.cuda.current_stream())
+
+
+class Event:
+    """Orders prepared work on different streams: `record(stream)` and `wait(stream)` are prepared
+    operations, issued when called or in their place in a `chain` / recorded step."""
+    __slots__ = ("_ev",)
+
+    def __init__(self):
+        self._ev = _launcher.Event()
+
+    def record(self, stream):
+        return _launcher.event_op(self._ev, _stream_ref(stream), False, stream)
+
+    def wait(self, stream):
+        return _launcher.event_op(self._ev, _stream_ref(stream), True, stream)
+
+
+def chain(*calls):
+    """Prepared calls as one that issues them in order."""
+    return _launcher.Program(calls, ())
+
+
+def record(stages, inputs):
+    """The step that `stages(*inputs)` lists, as a program: `program(*inputs)` issues it on the stream
+    that is current then, for any contiguous device tensors of the same shapes and dtypes (None where an
+    input was None), and returns True; for anything else it issues nothing and returns False."""
+    meta = [None if t is None else torch.empty(t.shape, dtype=t.dtype, device="meta") for t in inputs]
+    saved = _recording.slots, _recording.stream
+    _recording.slots = {t.untyped_storage()._cdata: i for i, t in enumerate(meta) if t is not None}
+    _recording.stream = torch.cuda.current_stream().cuda_stream
+    try:
+        calls = tuple(call for _, call in stages(*meta))
+    finally:
+        _recording.slots, _recording.stream = saved
+    return _launcher.Program(calls, tuple(None if t is None else (t.dtype, t.shape) for t in meta))
 
 
 def dtype_code(t: torch.Tensor) -> int:
