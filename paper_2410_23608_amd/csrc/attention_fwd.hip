@@ -126,19 +126,19 @@ __device__ __forceinline__ void scatter_fill_rows(const Scatter& sc, long r0, lo
 }
 
 // ------------------------------------------------------------------------- bf16 / MFMA
-// Per-wave state of the online softmax: O^T accumulators (rows = head dim, cols = this
-// wave's 32 queries), running max m (log2 domain, scale folded in) and running sum l (the
-// two halves of the wave keep partial sums that are added at the end).
+// Per-wave state of the softmax: O^T accumulators (rows = head dim, cols = this wave's 32
+// queries), reference m of the exponentials (log2 domain, scale folded in; see fwd_exp) and running
+// sum l (the two halves of the wave keep partial sums that are added at the end).
 template <int DH>
 struct FwdAcc {
   floatx16 o[DH / 32];
   float m, l;
-  __device__ __forceinline__ void init() {
+  __device__ __forceinline__ void init(float m0 = 0.f) {
 #pragma unroll
     for (int d = 0; d < DH / 32; ++d)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[d][r] = 0.f;
-    m = -INFINITY;
+    m = m0;
     l = 0.f;
   }
 };
@@ -171,56 +171,94 @@ __device__ __forceinline__ void fwd_scores(const __bf16* kbuf, int key0, int rem
   }
 }
 
-// One online-softmax update (max, rescale, exp, sum) over a group of GSB*32 keys, then
-// O^T += V^T P^T for the group.  V^T at vbuf (row stride TS), the group's keys at column vcol; TS == 0:
-// V rows as they lie in memory (row stride DH + 8, the group's keys from row vcol), the V^T fragments
-// then come from the transposing LDS read.
-template <int DH, int TS, int GSB, bool FULL>
-__device__ __forceinline__ void fwd_softmax_pv(const floatx16 (&s)[GSB], const __bf16* vbuf, int vcol, int key0,
-                                               int rem, FwdAcc<DH>& acc, float scale_log2, int l32, int hh) {
-  constexpr int DB = DH / 32;
-  float mx = s[0][0];
+// Softmax without a running maximum.  P = exp2(S scale - m) needs a reference m only to stay inside the
+// range of fp32; P, the row sums and the O accumulators are floating point, so their relative precision
+// does not depend on it.  m starts at 0 and is left alone while the lane's row sum stays in
+// [2^-20 after the first keys, 2^40): no maximum over the scores, no exchange between the halves, no
+// rescale of O per group, 56 instead of ~72 vector instructions per 32 x 32 score block, and the
+// exponentials no longer wait for the last score.  When some lane's sum leaves the range (large scores,
+// all first scores far below 0, inf or NaN) the wave takes the group again with the true maximum: the
+// scores are recomputed from the K rows in LDS (they are not kept, to save the registers) and O and l
+// are rescaled, as the online softmax does for every group.
+constexpr float kRowSumMin = 9.5367431640625e-07f;     // 2^-20
+constexpr float kRowSumMax = 1.099511627776e+12f;      // 2^40
+template <int DH, int RS, int GSB, bool FULL>
+__device__ __forceinline__ void fwd_exp(const floatx16 (&s)[GSB], const __bf16* kbuf, int key0, int rem, bool first,
+                                        const bf16x8 (&qf)[DH / 16], FwdAcc<DH>& acc, float scale_log2,
+                                        bf16x8 (&pb)[GSB][2], int l32, int hh) {
+  auto take = [&](const floatx16& t, int sb, float& sum) {
+    float p[16];
 #pragma unroll
-  for (int sb = 0; sb < GSB; ++sb)
+    for (int r = 0; r < 16; ++r) {
+      p[r] = __builtin_amdgcn_exp2f(fmaf(t[r], scale_log2, -acc.m));
+      sum += p[r];
+    }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sb][r]);
-  mx = max_across_halves(mx);
-  const float m_new = fmaxf(acc.m, mx * scale_log2);
-  if (__ballot(m_new != acc.m) != 0) {       // some query's running max moved: rescale
-    const float alpha = __builtin_amdgcn_exp2f(acc.m - m_new);
-    acc.l *= alpha;
+    for (int mf = 0; mf < 2; ++mf) {
+      floatx8 pf;
 #pragma unroll
-    for (int d = 0; d < DB; ++d)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc.o[d][r] *= alpha;
-    acc.m = m_new;
-  }
+      for (int j = 0; j < 8; ++j) pf[j] = p[8 * mf + j];
+      pb[sb][mf] = float_to_bf16x8(pf);
+    }
+  };
   float psum = 0.f;
 #pragma unroll
-  for (int sb = 0; sb < GSB; ++sb) {
-    if (FULL || key0 + sb * 32 < rem) {
-      float p[16];
+  for (int sb = 0; sb < GSB; ++sb)
+    if (FULL || key0 + sb * 32 < rem) take(s[sb], sb, psum);
+  const float l_new = acc.l + psum;
+  if (__builtin_expect(__ballot(!(l_new >= (first ? kRowSumMin : 0.f) && l_new < kRowSumMax)) != 0, 0)) {
+    float mx = -INFINITY;
+    floatx16 t[1];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        p[r] = __builtin_amdgcn_exp2f(fmaf(s[sb][r], scale_log2, -m_new));
-        psum += p[r];
+    for (int sb = 0; sb < GSB; ++sb)
+      if (FULL || key0 + sb * 32 < rem) {
+        fwd_scores<DH, RS, 1, FULL>(kbuf, key0 + sb * 32, rem, qf, t, l32, hh);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, t[0][r]);
       }
+    mx = max_across_halves(mx) * scale_log2;
+    const bool begun = sum_across_halves(acc.l) > 0.f;            // O holds something
+    const float m_new = begun ? fmaxf(acc.m, mx) : mx;
+    const float alpha = begun ? __builtin_amdgcn_exp2f(acc.m - m_new) : 0.f;
+    acc.m = m_new;
+    acc.l *= alpha;
 #pragma unroll
-      for (int mf = 0; mf < 2; ++mf) {
-        floatx8 pf;
+    for (int d = 0; d < DH / 32; ++d)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) pf[j] = p[8 * mf + j];
-        const bf16x8 pb = float_to_bf16x8(pf);
+      for (int r = 0; r < 16; ++r) acc.o[d][r] *= alpha;
+    psum = 0.f;
+#pragma unroll
+    for (int sb = 0; sb < GSB; ++sb)
+      if (FULL || key0 + sb * 32 < rem) {
+        fwd_scores<DH, RS, 1, FULL>(kbuf, key0 + sb * 32, rem, qf, t, l32, hh);
+        take(t[0], sb, psum);
+      }
+  }
+  acc.l += psum;
+}
+
+// The probabilities of a group of GSB*32 keys, then O^T += V^T P^T.  V^T at vbuf (row stride TS), the
+// group's keys at column vcol; TS == 0: V rows as they lie in memory (row stride DH + 8, the group's keys
+// from row vcol), the V^T fragments then come from the transposing LDS read.
+template <int DH, int RS, int TS, int GSB, bool FULL>
+__device__ __forceinline__ void fwd_softmax_pv(const floatx16 (&s)[GSB], const __bf16* kbuf, const __bf16* vbuf, int vcol,
+                                               int key0, int rem, bool first, const bf16x8 (&qf)[DH / 16],
+                                               FwdAcc<DH>& acc, float scale_log2, int l32, int hh) {
+  constexpr int DB = DH / 32;
+  bf16x8 pb[GSB][2];
+  fwd_exp<DH, RS, GSB, FULL>(s, kbuf, key0, rem, first, qf, acc, scale_log2, pb, l32, hh);
+#pragma unroll
+  for (int sb = 0; sb < GSB; ++sb)
+    if (FULL || key0 + sb * 32 < rem) {
+#pragma unroll
+      for (int mf = 0; mf < 2; ++mf)
 #pragma unroll
         for (int d = 0; d < DB; ++d) {
           const bf16x8 a = TS == 0 ? transposed_frag_rowmajor<DH + 8>(vbuf, d, vcol + sb * 32, mf, l32 + 32 * hh)
                                    : transposed_frag<TS == 0 ? 1 : TS>(vbuf, d * 32 + l32, vcol + sb * 32, mf, hh);
-          acc.o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb, acc.o[d], 0, 0, 0);
+          acc.o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[sb][mf], acc.o[d], 0, 0, 0);
         }
-      }
     }
-  }
-  acc.l += psum;
 }
 
 // One tile of NSB*32 keys held in LDS (K rows at kbuf, row stride RS; V^T at vbuf, row
@@ -230,7 +268,7 @@ __device__ __forceinline__ void fwd_softmax_pv(const floatx16 (&s)[GSB], const _
 // the matrix pipe and the vector ALU overlap inside one wave.  rem = valid keys in the tile;
 // FULL = every key valid (no masking code).
 template <int DH, int RS, int TS, int NSB, bool FULL>
-__device__ __forceinline__ void fwd_process_tile(const __bf16* kbuf, const __bf16* vbuf, int vcol0, int rem,
+__device__ __forceinline__ void fwd_process_tile(const __bf16* kbuf, const __bf16* vbuf, int vcol0, int rem, bool first,
                                                  const bf16x8 (&qf)[DH / 16], FwdAcc<DH>& acc,
                                                  float scale_log2, int l32, int hh) {
   constexpr int GSB = NSB >= 4 ? 2 : 1;     // sub-tiles per softmax group
@@ -243,7 +281,8 @@ __device__ __forceinline__ void fwd_process_tile(const __bf16* kbuf, const __bf1
     if (!FULL && key0 >= rem) break;
     if (g + 1 < NG && (FULL || key0 + GSB * 32 < rem))
       fwd_scores<DH, RS, GSB, FULL>(kbuf, key0 + GSB * 32, rem, qf, s[(g + 1) & 1], l32, hh);
-    fwd_softmax_pv<DH, TS, GSB, FULL>(s[g & 1], vbuf, vcol0 + key0, key0, rem, acc, scale_log2, l32, hh);
+    fwd_softmax_pv<DH, RS, TS, GSB, FULL>(s[g & 1], kbuf, vbuf, vcol0 + key0, key0, rem, first && g == 0, qf, acc,
+                                          scale_log2, l32, hh);
   }
 }
 
@@ -559,8 +598,8 @@ tiled_attention(TiledLds<DH, BN>& lds, const Segment seg, int h, int q0, const _
     }
     if (wave_live) {
       const int rem = seg.nk - kt;               // valid keys from this tile on (may exceed BN)
-      if (rem >= BN) fwd_process_tile<DH, RS, TS, NSB, true>(Ks[buf], Vs[buf], 0, BN, qf, acc, scale_log2, l32, hh);
-      else fwd_process_tile<DH, RS, TS, NSB, false>(Ks[buf], Vs[buf], 0, rem, qf, acc, scale_log2, l32, hh);
+      if (rem >= BN) fwd_process_tile<DH, RS, TS, NSB, true>(Ks[buf], Vs[buf], 0, BN, t == 0, qf, acc, scale_log2, l32, hh);
+      else fwd_process_tile<DH, RS, TS, NSB, false>(Ks[buf], Vs[buf], 0, rem, t == 0, qf, acc, scale_log2, l32, hh);
     }
     if (t + 1 < nt) store(buf ^ 1);
     __syncthreads();
@@ -742,7 +781,7 @@ tiled2_wave(Tiled2Lds<DH, BN>& lds, KvRowStage<DH, 64 * NW, BN, GATHER>& stage, 
   FwdAcc<DH> acc[NCA];
 #pragma unroll
   for (int c = 0; c < NCA; ++c) {
-    acc[c].init();
+    acc[c].init(-INFINITY);
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) q[c][kk] = qf[c][kk];
   }
@@ -799,8 +838,8 @@ tiled2_attention(Tiled2Lds<DH, BN>& lds, const Segment seg, int h, int q0, const
 #pragma unroll
   for (int c = 0; c < 2; ++c) load_q_frags<DH>(q + q_src[c] * qs + h * DH, q_ok[c], hh, qf[c]);
   FwdAcc<DH> acc[2];
-  acc[0].init();
-  acc[1].init();
+  acc[0].init(-INFINITY);
+  acc[1].init(-INFINITY);
   stage.store(lds.Ks[0], lds.Vs[0]);
   __syncthreads();
   if (nc == 2) tiled2_wave<DH, NW, BN, 2, GATHER>(lds, stage, seg, gi, kh, vh, ks, vs, qf, acc, scale_log2, lane);
@@ -934,47 +973,7 @@ wave_attention(__bf16* Ks, __bf16* Vs, const Segment seg, int h, int q0, const _
     // scores of the step: S^T = K Q^T, NSB 32-key sub-tiles, one softmax update for all
     floatx16 s[NSB];
     fwd_scores<DH, RS, NSB, false>(Ks, 0, rem, qf, s, l32, hh);
-    float mx = s[0][0];
-#pragma unroll
-    for (int sb = 0; sb < NSB; ++sb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sb][r]);
-    mx = max_across_halves(mx);
-    const float m_new = fmaxf(acc.m, mx * scale_log2);
-    if (__ballot(m_new != acc.m) != 0) {
-      const float alpha = __builtin_amdgcn_exp2f(acc.m - m_new);
-      acc.l *= alpha;
-#pragma unroll
-      for (int d = 0; d < DB; ++d)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc.o[d][r] *= alpha;
-      acc.m = m_new;
-    }
-    float psum = 0.f;
-#pragma unroll
-    for (int sb = 0; sb < NSB; ++sb) {
-      if (sb * 32 < rem) {
-        float p[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          p[r] = __builtin_amdgcn_exp2f(fmaf(s[sb][r], scale_log2, -m_new));
-          psum += p[r];
-        }
-#pragma unroll
-        for (int mf = 0; mf < 2; ++mf) {
-          floatx8 pf;
-#pragma unroll
-          for (int j = 0; j < 8; ++j) pf[j] = p[8 * mf + j];
-          const bf16x8 pb = float_to_bf16x8(pf);
-#pragma unroll
-          for (int d = 0; d < DB; ++d) {
-            const bf16x8 a = transposed_frag_rowmajor<RS>(Vs, d, sb * 32, mf, lane);
-            acc.o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb, acc.o[d], 0, 0, 0);
-          }
-        }
-      }
-    }
-    acc.l += psum;
+    fwd_softmax_pv<DH, RS, 0, NSB, false>(s, Ks, Vs, 0, 0, rem, kt == 0, qf, acc, scale_log2, l32, hh);
   }
 
   // output: park the 32 x DH tile in the (now free) K tile, then write whole rows
@@ -1221,8 +1220,8 @@ attn_fwd_bf16_whole_kernel(const __bf16* __restrict__ q, const __bf16* __restric
   if (wave_live) {
     for (int kt = 0; kt < seg.nk; kt += TILE) {
       const int rem = seg.nk - kt;
-      if (rem >= TILE) fwd_process_tile<DH, RS, TS, NSB, true>(Ks + kt * RS, Vt, kt, TILE, qf, acc, scale_log2, l32, hh);
-      else fwd_process_tile<DH, RS, TS, NSB, false>(Ks + kt * RS, Vt, kt, rem, qf, acc, scale_log2, l32, hh);
+      if (rem >= TILE) fwd_process_tile<DH, RS, TS, NSB, true>(Ks + kt * RS, Vt, kt, TILE, kt == 0, qf, acc, scale_log2, l32, hh);
+      else fwd_process_tile<DH, RS, TS, NSB, false>(Ks + kt * RS, Vt, kt, rem, kt == 0, qf, acc, scale_log2, l32, hh);
     }
   }
   __syncthreads();                       // all waves are done reading K: its rows become the output tile
