@@ -10,8 +10,7 @@
 // in the B-operand layout of the second product O^T = V^T P^T — no trip through LDS.
 // K tiles sit in LDS row-major (A operand: 16-byte reads), V tiles are stored transposed.
 //
-// fp32 path (reference-grade, used by the small fp32 workload): eight lanes per query,
-// K/V tiles read from LDS, plain fp32 FMA.
+// fp32 path (small fp32 workload): the same transposed tiles on the fp32 MFMA, in registers only.
 #include <cmath>
 
 #include <cstdio>
@@ -1236,155 +1235,161 @@ attn_fwd_bf16_whole_kernel(const __bf16* __restrict__ q, const __bf16* __restric
 }
 
 // ------------------------------------------------------------------------------- fp32
-// G lanes share one query: lane g takes the keys j = g (mod G) of every tile with its own
-// online-softmax state, the G partial states are merged with a butterfly of shuffles at the
-// end, and every lane writes DH / G of the query's output elements.
+// One wave per (image, head, 32 queries) on v_mfma_f32_32x32x2_f32 (fp32 products and sums, twice the
+// rate of the vector ALU), everything in registers: no LDS tile, no barrier.  The contraction order is
+// free, so a lane (row l32 of the operand, half hh) simply holds the elements hh DH/2 .. of its K or Q
+// row, S^T = K Q^T leaves 16 keys of one query in a lane, and these probabilities are the B operand of
+// O^T += V^T P^T, register r against V row acc_row(r, hh), of which the 32 lanes of a half read 128
+// consecutive bytes.  The rows of the next 32 keys are in flight during the math.  Bound by latency at
+// the sizes it is used at (2 x 196 tokens: 5 us; eight lanes per query with K / V tiles in LDS: 12.5 us).
 template <int DH>
-__global__ void __launch_bounds__(128)
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 attn_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
                     const float* __restrict__ v, long qs, long ks, long vs, const int32_t* __restrict__ cu,
                     const int32_t* __restrict__ key_lens, int n_pad, int H, float scale,
-                    float* __restrict__ out, float* __restrict__ lse, long lse_stride, Scatter sc) {
-  constexpr int THREADS = 128, G = 8, BM = THREADS / G, BN = 32, JPL = BN / G, EPL = DH / G;
-  static_assert(EPL % 4 == 0, "every lane writes whole 16-byte pieces");
-  __shared__ __attribute__((aligned(16))) float Ks[BN * DH];
-  __shared__ __attribute__((aligned(16))) float Vs[BN * DH];
-
-  const int h = blockIdx.y;
+                    float* __restrict__ out, float* __restrict__ lse, long lse_stride, Scatter sc, int B, int nqb) {
+  constexpr int HD = DH / 2, DB = DH / 32;
+  const TileId tile_id = xcd_tile(nqb, H, B);
+  if (!tile_id.valid) return;
+  const int h = tile_id.h, img = tile_id.rank, lane = threadIdx.x, l32 = lane & 31, hh = lane >> 5;
   const long C = (long)H * DH;
-  // cu == key_lens == nullptr: no packing index exists; the first wave derives the image's packing
-  // order from its n_pad <= 256 mask bytes (see attn_fwd_bf16_wave_mask_kernel) and the workgroup
-  // works on that list as on gathered rows
+  // cu == key_lens == nullptr: no packing index exists; the wave derives the image's packing order from
+  // its n_pad <= 256 mask bytes (see attn_fwd_bf16_wave_mask_kernel) and works on that list as on gathered rows
   __shared__ int32_t list[256];
-  __shared__ int s_n;
-  const bool from_mask = cu == nullptr && key_lens == nullptr;
   Segment seg;
-  if (from_mask) {
-    if (threadIdx.x < kWave) {
-      const long tok0 = (long)blockIdx.z * n_pad;
-      int n = 0;
+  if (cu == nullptr && key_lens == nullptr) {
+    const long tok0 = (long)img * n_pad;
+    int n = 0;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int t = (int)threadIdx.x + 64 * i;
-        const bool sel = t < n_pad && sc.mask[tok0 + t] != 0;
-        const uint64_t bal = __ballot(sel);
-        if (sel) list[n + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u))] = (int32_t)(tok0 + t);
-        n += __popcll(bal);
-      }
-      if (threadIdx.x == 0) s_n = n;
+    for (int i = 0; i < 4; ++i) {
+      const int t = lane + 64 * i;
+      const bool sel = t < n_pad && sc.mask[tok0 + t] != 0;
+      const uint64_t bal = __ballot(sel);
+      if (sel) list[n + rank_in_ballot(bal)] = (int32_t)(tok0 + t);
+      n += __popcll(bal);
     }
     __syncthreads();
-    seg = {0, s_n, s_n};
+    seg = {0, n, n};
     sc.gather_idx = list;
   } else {
-    seg = segment_of(blockIdx.z, cu, key_lens, n_pad);
+    seg = segment_of(img, cu, key_lens, n_pad);
   }
-  if (sc.y != nullptr) {
-    const FillRange fr = fill_range(sc, blockIdx.z, gridDim.z, blockIdx.x, gridDim.x);
-    scatter_fill<float, DH>(sc, fr.b, fr.t0, fr.t1, h, C, threadIdx.x, THREADS);
-  }
-  const int q0 = blockIdx.x * BM;
-  if (q0 >= seg.nq) return;
-  const int tid = threadIdx.x, g = tid % G;
-  const int qi = q0 + tid / G;
-  const bool q_ok = qi < seg.nq;
-
-  float qr[DH], o[DH];
+  const FillRange fr = fill_range(sc, img, B, tile_id.qb, nqb);
+  const int q0 = tile_id.qb * 32;
+  if (q0 < seg.nq) {
+    const int qi = q0 + l32;
+    const bool q_ok = qi < seg.nq;
+    const int32_t* gi = sc.gathered ? sc.gather_idx + seg.row0 : nullptr;
+    const float* kh = k + h * DH + hh * HD;
+    const float* vh = v + h * DH + l32;
+    // key rows: lane l32 fetches key kt + l32 (past the segment: its last key, masked below)
+    float kf[HD], vf[16][DB], kn[HD], vn[16][DB];
+    auto key_row = [&](int kt) { return (int)source_row(gi, seg.row0, min(kt + l32, seg.nk - 1)); };
+    auto fetch = [&](int row, float (&kd)[HD], float (&vd)[16][DB]) {
+      const float* kp = kh + (long)row * ks;
 #pragma unroll
-  for (int d = 0; d < DH; ++d) { qr[d] = 0.f; o[d] = 0.f; }
-  const int32_t* gi = sc.gathered ? sc.gather_idx + seg.row0 : nullptr;
-  if (q_ok) {
-    const float* qp = q + source_row(gi, seg.row0, qi) * qs + h * DH;
-#pragma unroll
-    for (int d = 0; d < DH; d += 4) {
-      const floatx4 t = *reinterpret_cast<const floatx4*>(qp + d);
-      qr[d] = t[0] * scale; qr[d + 1] = t[1] * scale; qr[d + 2] = t[2] * scale; qr[d + 3] = t[3] * scale;
-    }
-  }
-  float m = -INFINITY, l = 0.f;
-
-  for (int kt = 0; kt < seg.nk; kt += BN) {
-    __syncthreads();
-    for (int i = tid; i < BN * DH / 4; i += THREADS) {
-      const int r = i / (DH / 4), c = i % (DH / 4);
-      floatx4 kv = {0.f, 0.f, 0.f, 0.f}, vv = kv;
-      if (kt + r < seg.nk) {
-        const long src = source_row(gi, seg.row0, kt + r);
-        kv = *reinterpret_cast<const floatx4*>(k + src * ks + h * DH + c * 4);
-        vv = *reinterpret_cast<const floatx4*>(v + src * vs + h * DH + c * 4);
+      for (int i = 0; i < HD; i += 4) {
+        const floatx4 t = *reinterpret_cast<const floatx4*>(kp + i);
+        kd[i] = t[0]; kd[i + 1] = t[1]; kd[i + 2] = t[2]; kd[i + 3] = t[3];
       }
-      *reinterpret_cast<floatx4*>(&Ks[r * DH + c * 4]) = kv;
-      *reinterpret_cast<floatx4*>(&Vs[r * DH + c * 4]) = vv;
-    }
-    __syncthreads();
-    const int kn = min(BN, seg.nk - kt);
-    float s[JPL];
-    float mx = -INFINITY;
 #pragma unroll
-    for (int jj = 0; jj < JPL; ++jj) {
-      const int j = jj * G + g;
-      float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+      for (int r = 0; r < 16; ++r) {
+        const float* vp = vh + (long)__shfl(row, acc_row(r, hh), kWave) * vs;
 #pragma unroll
-      for (int d = 0; d < DH; d += 4) {
-        const floatx4 kv = *reinterpret_cast<const floatx4*>(&Ks[j * DH + d]);
-        a0 = fmaf(qr[d], kv[0], a0);
-        a1 = fmaf(qr[d + 1], kv[1], a1);
-        a2 = fmaf(qr[d + 2], kv[2], a2);
-        a3 = fmaf(qr[d + 3], kv[3], a3);
+        for (int d = 0; d < DB; ++d) vd[r][d] = vp[d * 32];
       }
-      s[jj] = j < kn ? (a0 + a1) + (a2 + a3) : -INFINITY;
-      mx = fmaxf(mx, s[jj]);
+    };
+    float qf[HD];
+#pragma unroll
+    for (int i = 0; i < HD; ++i) qf[i] = 0.f;
+    const long q_src = source_row(gi, seg.row0, q_ok ? qi : 0);
+    int row = seg.nk > 0 ? key_row(0) : 0;
+    if (q_ok) {
+      const float* qp = q + q_src * qs + h * DH + hh * HD;
+#pragma unroll
+      for (int i = 0; i < HD; i += 4) {
+        const floatx4 t = *reinterpret_cast<const floatx4*>(qp + i) * scale;
+        qf[i] = t[0]; qf[i + 1] = t[1]; qf[i + 2] = t[2]; qf[i + 3] = t[3];
+      }
     }
-    const float m_new = fmaxf(m, mx);
-    if (m_new > -INFINITY) {          // this lane has seen at least one key
+    floatx16 o[DB];
+#pragma unroll
+    for (int d = 0; d < DB; ++d)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[d][r] = 0.f;
+    float m = -INFINITY, l = 0.f;
+    if (seg.nk > 0) {
+      fetch(row, kf, vf);
+      row = key_row(32);
+    }
+    for (int kt = 0; kt < seg.nk; kt += 32) {
+      const int rem = seg.nk - kt;
+      if (rem > 32) {
+        fetch(row, kn, vn);
+        row = key_row(kt + 64);
+      }
+      floatx16 s;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+      for (int i = 0; i < HD; ++i) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[i], qf[i], s, 0, 0, 0);
+      if (rem < 32) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (acc_row(r, hh) >= rem) {
+            s[r] = -INFINITY;
+#pragma unroll
+            for (int d = 0; d < DB; ++d) vf[r][d] = 0.f;
+          }
+      }
+      float mx = s[0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+      const float m_new = fmaxf(m, max_across_halves(mx));
       const float alpha = expf(m - m_new);
+      m = m_new;
       l *= alpha;
 #pragma unroll
-      for (int d = 0; d < DH; ++d) o[d] *= alpha;
+      for (int d = 0; d < DB; ++d)
 #pragma unroll
-      for (int jj = 0; jj < JPL; ++jj) {
-        const int j = jj * G + g;
-        const float p = expf(s[jj] - m_new);
-        l += p;
+        for (int r = 0; r < 16; ++r) o[d][r] *= alpha;
 #pragma unroll
-        for (int d = 0; d < DH; d += 4) {
-          const floatx4 vv = *reinterpret_cast<const floatx4*>(&Vs[j * DH + d]);
-          o[d] = fmaf(p, vv[0], o[d]);
-          o[d + 1] = fmaf(p, vv[1], o[d + 1]);
-          o[d + 2] = fmaf(p, vv[2], o[d + 2]);
-          o[d + 3] = fmaf(p, vv[3], o[d + 3]);
-        }
+      for (int r = 0; r < 16; ++r) {
+        s[r] = expf(s[r] - m_new);
+        l += s[r];
       }
-      m = m_new;
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int d = 0; d < DB; ++d) o[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[r][d], s[r], o[d], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < HD; ++i) kf[i] = kn[i];
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int d = 0; d < DB; ++d) vf[r][d] = vn[r][d];
+    }
+    const float l_tot = sum_across_halves(l);
+    if (q_ok) {
+      const float inv = seg.nk > 0 ? 1.0f / l_tot : 0.f;
+      float* op = out != nullptr ? out + (seg.row0 + qi) * C + h * DH + 4 * hh : nullptr;
+      const long yoff = sc.y != nullptr ? (long)sc.gather_idx[seg.row0 + qi] * C + h * DH + 4 * hh : 0;
+#pragma unroll
+      for (int d = 0; d < DB; ++d)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int at = d * 32 + 8 * g;
+          floatx4 t = {o[d][4 * g] * inv, o[d][4 * g + 1] * inv, o[d][4 * g + 2] * inv, o[d][4 * g + 3] * inv};
+          if (op != nullptr) *reinterpret_cast<floatx4*>(op + at) = t;
+          if (sc.y != nullptr) {
+            if (sc.base != nullptr) t += *reinterpret_cast<const floatx4*>(static_cast<const float*>(sc.base) + yoff + at);
+            __builtin_nontemporal_store(t, reinterpret_cast<floatx4*>(static_cast<float*>(sc.y) + yoff + at));
+          }
+        }
+      if (lse != nullptr && hh == 0) lse[h * lse_stride + seg.row0 + qi] = seg.nk > 0 ? m + logf(l_tot) : -INFINITY;
     }
   }
-  // merge the G partial states of the query (all G lanes end with the merged state)
-#pragma unroll
-  for (int off = G / 2; off > 0; off >>= 1) {
-    const float m_o = __shfl_xor(m, off, kWave), l_o = __shfl_xor(l, off, kWave);
-    const float m_new = fmaxf(m, m_o);
-    const float a = m > -INFINITY ? expf(m - m_new) : 0.f;
-    const float b = m_o > -INFINITY ? expf(m_o - m_new) : 0.f;
-    l = l * a + l_o * b;
-#pragma unroll
-    for (int d = 0; d < DH; ++d) o[d] = o[d] * a + __shfl_xor(o[d], off, kWave) * b;
-    m = m_new;
-  }
-  if (!q_ok) return;
-  const float inv = seg.nk > 0 ? 1.0f / l : 0.f;
-  float* op = out != nullptr ? out + (seg.row0 + qi) * C + h * DH : nullptr;
-  const long yoff = sc.y != nullptr ? (long)sc.gather_idx[seg.row0 + qi] * C + h * DH : 0;
-#pragma unroll
-  for (int d0 = 0; d0 < DH; d0 += 4) {
-    if (d0 / EPL != g) continue;      // this lane's share of the row
-    floatx4 t = {o[d0] * inv, o[d0 + 1] * inv, o[d0 + 2] * inv, o[d0 + 3] * inv};
-    if (op != nullptr) *reinterpret_cast<floatx4*>(op + d0) = t;
-    if (sc.y != nullptr) {
-      if (sc.base != nullptr) t += *reinterpret_cast<const floatx4*>(static_cast<const float*>(sc.base) + yoff + d0);
-      __builtin_nontemporal_store(t, reinterpret_cast<floatx4*>(static_cast<float*>(sc.y) + yoff + d0));
-    }
-  }
-  if (lse != nullptr && g == 0) lse[h * lse_stride + seg.row0 + qi] = seg.nk > 0 ? m + logf(l) : -INFINITY;
+  if (sc.y != nullptr) scatter_fill<float, DH>(sc, fr.b, fr.t0, fr.t1, h, C, lane, kWave);
 }
 
 // ------------------------------------------------------------------------------- host
@@ -1415,11 +1420,12 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
   const long lse_stride = (long)B * n_max;
   hipStream_t st = as_stream(stream);
   if (dtype == SPA_F32) {
-    const dim3 grid((n_max + 15) / 16, H, B), block(128);   // 16 queries per workgroup, 8 lanes each
+    const int nqb = (n_max + 31) / 32;
+    const dim3 grid(xcd_grid(nqb, H, B)), block(64);
 #define SPA_F32_LAUNCH(D)                                                                                \
   hipLaunchKernelGGL((attn_fwd_f32_kernel<D>), grid, block, 0, st, (const float*)q, (const float*)k,    \
                      (const float*)v, (long)q_stride, (long)k_stride, (long)v_stride, cu, key_lens, n_max, H, scale, (float*)out, lse, \
-                     lse_stride, sc)
+                     lse_stride, sc, B, nqb)
     if (Dh == 32) SPA_F32_LAUNCH(32); else SPA_F32_LAUNCH(64);
 #undef SPA_F32_LAUNCH
   } else {
@@ -1573,22 +1579,21 @@ extern "C" int spa_selected_attention_unpack(const void* q, const void* k, const
   const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / std::sqrt((float)Dh);
   const float scale_log2 = scale * 1.4426950408889634f;
   const Scatter sc = {nullptr, nullptr, base, y, N, 0, 1, mask};
+  const int nqb = (N + 31) / 32;
+  const dim3 grid(xcd_grid(nqb, H, B)), block(64);
   if (dtype == SPA_F32) {
-    const dim3 grid((N + 15) / 16, H, B), block(128);   // 16 queries per workgroup, 8 lanes each
     if (Dh == 32)
       hipLaunchKernelGGL((attn_fwd_f32_kernel<32>), grid, block, 0, as_stream(stream), (const float*)q, (const float*)k,
                          (const float*)v, (long)q_row_stride, (long)k_row_stride, (long)v_row_stride, nullptr, nullptr, N,
-                         H, scale, (float*)nullptr, (float*)nullptr, 0L, sc);
+                         H, scale, (float*)nullptr, (float*)nullptr, 0L, sc, B, nqb);
     else
       hipLaunchKernelGGL((attn_fwd_f32_kernel<64>), grid, block, 0, as_stream(stream), (const float*)q, (const float*)k,
                          (const float*)v, (long)q_row_stride, (long)k_row_stride, (long)v_row_stride, nullptr, nullptr, N,
-                         H, scale, (float*)nullptr, (float*)nullptr, 0L, sc);
+                         H, scale, (float*)nullptr, (float*)nullptr, 0L, sc, B, nqb);
     return check_launch(fn);
   }
-  const int nqb = (N + 31) / 32;
-  const dim3 grid(xcd_grid(nqb, H, B));
 #define SPA_SEL(D)                                                                                              \
-  hipLaunchKernelGGL((attn_fwd_bf16_wave_mask_kernel<D, 32>), grid, dim3(64), 0, as_stream(stream), (const __bf16*)q, \
+  hipLaunchKernelGGL((attn_fwd_bf16_wave_mask_kernel<D, 32>), grid, block, 0, as_stream(stream), (const __bf16*)q, \
                      (const __bf16*)k, (const __bf16*)v, (long)q_row_stride, (long)k_row_stride, (long)v_row_stride,    \
                      mask, N, H, scale_log2, sc, B, nqb)
   if (Dh == 32) SPA_SEL(32); else SPA_SEL(64);
