@@ -304,10 +304,15 @@ __global__ void maxpool2x2_kernel(const float* __restrict__ s, int B, int h, int
 
 // ---------------------------------------------------------------------- gate backward
 // Selection loss (binary cross-entropy on sigmoid(s)) + gradient of r_g = sigmoid(s) . r.
-// A group of G lanes owns a token; the row's chunks live in registers (IT per lane), so x
-// and d_rg are read once.  dw / db / loss are reduced without atomics: lanes accumulate
-// over their tokens, groups are folded in a fixed order into LDS, every workgroup writes one
-// partial row, and a second kernel adds the partial rows in order.
+// G lanes own a token (IT chunks of its row each), so x and d_rg are read once; every workgroup has a
+// contiguous share of the tokens and a group takes U of them at a time, all their loads in flight
+// together.  A row is spread over as many lanes as it has chunks (up to a wave): the dw accumulators
+// are then IT * 8 registers and the fold of a workgroup is one row per wave.  With 16 lanes per token at
+// every width it was 16 rows of C, 49 KB of LDS at C 768, and took as long as the token loop: 12544
+// tokens of 768: 17.9 -> 15.4 us (58 MB); 50176 of 96: 13.2 -> 10.2; 784 of 768: 10.4 -> 8.0.
+// dw / db / loss are reduced without atomics, in a fixed order: lanes over their tokens, the groups of a
+// wave by exchanges, waves through LDS, every workgroup writes one partial row, and a second kernel adds
+// the partial rows.
 // Straight-through estimator of the hard selection: selected tokens differentiate the relaxed
 // weight sigmoid((s + noise) / T) in place of the 0/1 mask.  mask == nullptr: off.
 struct StraightThrough {
@@ -316,153 +321,187 @@ struct StraightThrough {
   float inv_temperature;
 };
 
-template <typename T, int G, int IT>
+template <typename T> struct Raw16;
+template <> struct Raw16<float> { using type = floatx4; };
+template <> struct Raw16<__bf16> { using type = bf16x8; };
+__device__ __forceinline__ void widen(floatx4 v, float (&f)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) f[i] = v[i];
+}
+__device__ __forceinline__ void widen(bf16x8 v, float (&f)[8]) {
+  const floatx8 w = bf16x8_to_float(v);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) f[i] = w[i];
+}
+
+template <typename T, int G, int IT, int U>
 __global__ void __launch_bounds__(kGateThreads)
 gate_bwd_kernel(const T* __restrict__ x, const T* __restrict__ w, float bias,
                 const float* __restrict__ scores, const float* __restrict__ s_up,
                 const uint8_t* __restrict__ labels, const T* __restrict__ d_rg, int gate_scaled,
                 float loss_scale, StraightThrough st, int ntok, int C, T* __restrict__ dx,
-                float* __restrict__ partial, int fold_parallel) {
-  constexpr int VE = Vec16<T>::kElems;
-  constexpr int kGroups = kGateThreads / G;
-  extern __shared__ float lds[];
-  float* w_lds = lds;            // [C]
-  float* sdw = lds + C;          // [C]
-  __shared__ float s_loss[kGroups], s_db[kGroups];
-  for (int c = threadIdx.x; c < C; c += kGateThreads) { w_lds[c] = static_cast<float>(w[c]); sdw[c] = 0.f; }
-  __syncthreads();
+                float* __restrict__ partial) {
+  constexpr int VE = Vec16<T>::kElems, kGroups = kGateThreads / G, kWaves = kGateThreads / kWave;
+  using Raw = typename Raw16<T>::type;
+  extern __shared__ float lds[];                       // [kWaves][C]
+  __shared__ float s_loss[kWaves], s_db[kWaves];
 
   const int grp = threadIdx.x / G, gl = threadIdx.x % G;
   const int chunks = C / VE;
   const bool scaled = gate_scaled != 0 && d_rg != nullptr;
-  float dwa[IT][VE];
+  float wv[IT][VE], dwa[IT][VE];
 #pragma unroll
-  for (int it = 0; it < IT; ++it)
+  for (int it = 0; it < IT; ++it) {
+    const int ch = gl + it * G;
+    Raw r = {};
+    if (ch < chunks) r = *reinterpret_cast<const Raw*>(w + ch * VE);
+    widen(r, wv[it]);
 #pragma unroll
     for (int e = 0; e < VE; ++e) dwa[it][e] = 0.f;
+  }
   float loss_acc = 0.f, db_acc = 0.f;
 
-  for (long tok = (long)blockIdx.x * kGroups + grp; tok < ntok; tok += (long)gridDim.x * kGroups) {
-    float xr[IT][VE], dr[IT][VE];
-    float dot = 0.f, g = 0.f;
+  const long per = ((long)ntok + gridDim.x - 1) / gridDim.x;
+  const long t0 = blockIdx.x * per, t1 = min((long)ntok, t0 + per);
+  for (long base = t0 + grp; base < t1; base += kGroups * U) {
+    Raw xr[U][IT], dr[U][IT];
+    float s[U], up[U], nz[U];
+    uint8_t lab[U], sel[U];
 #pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int ch = gl + it * G;
+    for (int u = 0; u < U; ++u) {
+      const long tok = min(base + u * kGroups, t1 - 1);      // past the share: a valid token, its results unused
 #pragma unroll
-      for (int e = 0; e < VE; ++e) { xr[it][e] = 0.f; dr[it][e] = 0.f; }
-      if (ch < chunks) {
-        Vec16<T>::load(x + tok * (long)C + ch * VE, xr[it]);
-        if (scaled) Vec16<T>::load(d_rg + tok * (long)C + ch * VE, dr[it]);
-#pragma unroll
-        for (int e = 0; e < VE; ++e) {
-          dot = fmaf(dr[it][e], xr[it][e], dot);
-          g = fmaf(xr[it][e], w_lds[ch * VE + e], g);
+      for (int it = 0; it < IT; ++it) {
+        const int ch = gl + it * G;
+        xr[u][it] = {};
+        dr[u][it] = {};
+        if (ch < chunks) {
+          xr[u][it] = *reinterpret_cast<const Raw*>(x + tok * C + ch * VE);
+          if (scaled) dr[u][it] = *reinterpret_cast<const Raw*>(d_rg + tok * C + ch * VE);
         }
       }
+      s[u] = scores[tok];
+      lab[u] = labels[tok];
+      up[u] = s_up != nullptr ? s_up[tok] : 0.f;
+      sel[u] = st.mask != nullptr ? st.mask[tok] : 0;
+      nz[u] = st.noise != nullptr ? st.noise[tok] : 0.f;
     }
-    dot = group_sum<G>(dot);
-    const float s = scores[tok];
-    bool own = true;
-    if (s_up != nullptr) {
-      g = group_sum<G>(g) + bias;
-      own = g >= s_up[tok];                 // the up-scale score won the max: no gradient to (w, b)
-    }
-    const float p = sigmoidf_dev(s);
-    const float y = labels[tok] != 0 ? 1.f : 0.f;
-    float ds = loss_scale * (p - y);
-    if (scaled) {
-      float coef = p * (1.f - p);                      // through r_g = sigmoid(s) . r
-      if (st.mask != nullptr && st.mask[tok] != 0) {   // through the relaxed selection weight: <d_rg, r_g> = p dot
-        const float pt = sigmoidf_dev((s + (st.noise != nullptr ? st.noise[tok] : 0.f)) * st.inv_temperature);
-        coef = fmaf(pt * (1.f - pt) * st.inv_temperature, p, coef);
-      }
-      ds = fmaf(coef, dot, ds);
-    }
-    const float dsg = own ? ds : 0.f;
-    const float pg = scaled ? p : 0.f;
+    float s_mine = 0.f, y_mine = 0.f, d_mine = 0.f;          // lane u of the group keeps the loss of its token u
 #pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int ch = gl + it * G;
-      if (ch < chunks) {
+    for (int u = 0; u < U; ++u) {
+      const long tok = base + u * kGroups;
+      float xf[IT][VE], df[IT][VE];
+      float dot = 0.f, g = 0.f;
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        widen(xr[u][it], xf[it]);
+        widen(dr[u][it], df[it]);
+#pragma unroll
+        for (int e = 0; e < VE; ++e) {
+          dot = fmaf(df[it][e], xf[it][e], dot);
+          g = fmaf(xf[it][e], wv[it][e], g);
+        }
+      }
+      dot = group_sum<G>(dot);
+      bool own = tok < t1;
+      if (s_up != nullptr) own = own && group_sum<G>(g) + bias >= up[u];   // else the up-scale score won the max
+      const float p = sigmoidf_dev(s[u]);
+      const float y = lab[u] != 0 ? 1.f : 0.f;
+      float ds = loss_scale * (p - y);
+      if (scaled) {
+        float coef = p * (1.f - p);                      // through r_g = sigmoid(s) . r
+        if (sel[u] != 0) {                               // through the relaxed selection weight: <d_rg, r_g> = p dot
+          const float pt = sigmoidf_dev((s[u] + nz[u]) * st.inv_temperature);
+          coef = fmaf(pt * (1.f - pt) * st.inv_temperature, p, coef);
+        }
+        ds = fmaf(coef, dot, ds);
+      }
+      const float dsg = own ? ds : 0.f;                  // (w, b) get no gradient where the up-scale score won
+      const float pg = scaled ? p : 0.f;
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int ch = gl + it * G;
         float o[VE];
 #pragma unroll
         for (int e = 0; e < VE; ++e) {
-          o[e] = fmaf(dsg, w_lds[ch * VE + e], pg * dr[it][e]);
-          dwa[it][e] = fmaf(dsg, xr[it][e], dwa[it][e]);
+          o[e] = fmaf(dsg, wv[it][e], pg * df[it][e]);
+          dwa[it][e] = fmaf(dsg, xf[it][e], dwa[it][e]);
         }
-        Vec16<T>::store(dx + tok * (long)C + ch * VE, o);
+        if (ch < chunks && tok < t1) Vec16<T>::store(dx + tok * C + ch * VE, o);
       }
+      if (gl == u) { s_mine = s[u]; y_mine = y; d_mine = dsg; }
     }
-    if (gl == 0) {
-      loss_acc += fmaxf(s, 0.f) - y * s + log1pf(__expf(-fabsf(s)));
-      db_acc += dsg;
+    if (gl < U && base + gl * kGroups < t1) {
+      loss_acc += fmaxf(s_mine, 0.f) - y_mine * s_mine + log1pf(__expf(-fabsf(s_mine)));
+      db_acc += d_mine;
     }
   }
 
-  // fold the groups in a fixed order (group 0, 1, ...).  When the per-group partials fit in
-  // LDS every group parks its partial row and each thread adds a column top to bottom; else
-  // the groups take turns adding into one LDS row.
-  if (fold_parallel) {
-    float* grows = sdw + C;                       // [kGroups][C]
+  // fold: the groups of a wave by exchanges, then one row per wave
+#pragma unroll
+  for (int o = G; o < kWave; o <<= 1)
+#pragma unroll
+    for (int it = 0; it < IT; ++it)
+#pragma unroll
+      for (int e = 0; e < VE; ++e) dwa[it][e] += __shfl_xor(dwa[it][e], o, kWave);
+  loss_acc = wave_sum(loss_acc);
+  db_acc = wave_sum(db_acc);
+  const int wv_id = threadIdx.x / kWave;
+  if ((threadIdx.x & (kWave - 1)) < G) {
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
       const int ch = gl + it * G;
       if (ch < chunks) {
 #pragma unroll
-        for (int e = 0; e < VE; ++e) grows[grp * C + ch * VE + e] = dwa[it][e];
-      }
-    }
-    __syncthreads();
-    for (int c = threadIdx.x; c < C; c += kGateThreads) {
-      float a = 0.f;
-#pragma unroll
-      for (int g2 = 0; g2 < kGroups; ++g2) a += grows[g2 * C + c];
-      sdw[c] = a;
-    }
-    __syncthreads();
-  } else {
-    for (int gsel = 0; gsel < kGroups; ++gsel) {
-      if (grp == gsel) {
-#pragma unroll
-        for (int it = 0; it < IT; ++it) {
-          const int ch = gl + it * G;
-          if (ch < chunks) {
-#pragma unroll
-            for (int e = 0; e < VE; ++e) sdw[ch * VE + e] += dwa[it][e];
-          }
+        for (int e = 0; e < VE; e += 4) {
+          const floatx4 f = {dwa[it][e], dwa[it][e + 1], dwa[it][e + 2], dwa[it][e + 3]};
+          *reinterpret_cast<floatx4*>(&lds[wv_id * C + ch * VE + e]) = f;
         }
       }
-      __syncthreads();
     }
   }
-  if (gl == 0) { s_loss[grp] = loss_acc; s_db[grp] = db_acc; }
+  if ((threadIdx.x & (kWave - 1)) == 0) { s_loss[wv_id] = loss_acc; s_db[wv_id] = db_acc; }
   __syncthreads();
   float* prow = partial + (long)blockIdx.x * (C + 2);
-  for (int c = threadIdx.x; c < C; c += kGateThreads) prow[c] = sdw[c];
+  for (int c = threadIdx.x; c < C; c += kGateThreads) {
+    float a = 0.f;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) a += lds[i * C + c];
+    prow[c] = a;
+  }
   if (threadIdx.x == 0) {
     float a = 0.f, b = 0.f;
-    for (int i = 0; i < kGroups; ++i) { a += s_loss[i]; b += s_db[i]; }
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) { a += s_loss[i]; b += s_db[i]; }
     prow[C] = a;
     prow[C + 1] = b;
   }
 }
 
-// Adds the partial rows in a fixed order: a block owns 16 columns; 16 row slices run in
-// parallel (slice s adds rows s, s+16, ...), then the slices are added 0..15.
-__global__ void __launch_bounds__(256)
+// Adds the partial rows in a fixed order: a block owns 16 columns; 64 row slices run in parallel
+// (slice s adds rows s, s+64, ..., at most 8 of them, whose loads are all in flight at once), then the
+// slices of a wave are added by exchanges and the waves in order.
+constexpr int kGateBwdMaxParts = 512;
+__global__ void __launch_bounds__(1024)
 gate_bwd_reduce_kernel(const float* __restrict__ partial, int nparts, int C, float loss_scale,
                        float* __restrict__ loss, float* __restrict__ dw, float* __restrict__ db) {
   __shared__ float red[16][17];
   const int cl = threadIdx.x & 15, sl = threadIdx.x >> 4;
   const int c = blockIdx.x * 16 + cl;
-  float a = 0.f;
-  if (c < C + 2) {
-#pragma unroll 8
-    for (int i = sl; i < nparts; i += 16) a += partial[(long)i * (C + 2) + c];
+  float v[kGateBwdMaxParts / 64];
+#pragma unroll
+  for (int i = 0; i < kGateBwdMaxParts / 64; ++i) {
+    const int r = sl + 64 * i;
+    v[i] = r < nparts && c < C + 2 ? partial[(long)r * (C + 2) + c] : 0.f;
   }
-  red[sl][cl] = a;
+  float a = 0.f;
+#pragma unroll
+  for (int i = 0; i < kGateBwdMaxParts / 64; ++i) a += v[i];
+  a += __shfl_xor(a, 16, kWave);
+  a += __shfl_xor(a, 32, kWave);
+  if ((threadIdx.x & 63) < 16) red[threadIdx.x >> 6][cl] = a;
   __syncthreads();
-  if (sl == 0 && c < C + 2) {
+  if (threadIdx.x < 16 && c < C + 2) {
     float t = 0.f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) t += red[i][cl];
@@ -472,7 +511,6 @@ gate_bwd_reduce_kernel(const float* __restrict__ partial, int nparts, int C, flo
   }
 }
 
-constexpr int kGateBwdMaxParts = 512;
 
 static int gate_bwd_parts(long ntok) {
   long p = (ntok + 15) / 16;
@@ -613,24 +651,21 @@ static int launch_gate_bwd(const void* x, const void* w, float bias, const float
   constexpr int VE = Vec16<T>::kElems;
   const int chunks = C / VE;
   const int parts = gate_bwd_parts(ntok);
-  // LDS: w [C] + dw row [C] (+ one partial row per group when that fits in 64 KB)
-  const int groups = chunks <= 128 ? 16 : 4;
-  const int fold_parallel = (size_t)(2 + groups) * C * sizeof(float) <= 65536 ? 1 : 0;
-  const size_t lds = (size_t)(fold_parallel ? 2 + groups : 2) * C * sizeof(float);
-#define SPA_GB(G, IT)                                                                                         \
-  hipLaunchKernelGGL((gate_bwd_kernel<T, G, IT>), dim3(parts), dim3(kGateThreads), lds, st,                  \
+  const size_t lds = (size_t)(kGateThreads / kWave) * C * sizeof(float);      // at most 64 KB (C <= 4096)
+#define SPA_GB(G, IT, U)                                                                                      \
+  hipLaunchKernelGGL((gate_bwd_kernel<T, G, IT, U>), dim3(parts), dim3(kGateThreads), lds, st,               \
                      static_cast<const T*>(x), static_cast<const T*>(w), bias, scores, s_up, labels,         \
                      static_cast<const T*>(d_rg), gate_scaled, loss_scale, stt, (int)ntok, C,                \
-                     static_cast<T*>(dx), partial, fold_parallel)
-  if (chunks <= 16) SPA_GB(16, 1);
-  else if (chunks <= 32) SPA_GB(16, 2);
-  else if (chunks <= 64) SPA_GB(16, 4);
-  else if (chunks <= 128) SPA_GB(16, 8);
-  else if (chunks <= 256) SPA_GB(64, 4);
-  else if (chunks <= 512) SPA_GB(64, 8);
+                     static_cast<T*>(dx), partial)
+  if (chunks <= 16) SPA_GB(16, 1, 4);
+  else if (chunks <= 32) SPA_GB(32, 1, 4);
+  else if (chunks <= 64) SPA_GB(64, 1, 4);
+  else if (chunks <= 128) SPA_GB(64, 2, 4);
+  else if (chunks <= 256) SPA_GB(64, 4, 2);
+  else if (chunks <= 512) SPA_GB(64, 8, 1);
   else return fail(SPA_ERR_UNSUPPORTED, "spa_gate_bwd: C = %d too large (at most %d)", C, 512 * VE);
 #undef SPA_GB
-  hipLaunchKernelGGL(gate_bwd_reduce_kernel, dim3((C + 2 + 15) / 16), dim3(256), 0, st, partial, parts, C,
+  hipLaunchKernelGGL(gate_bwd_reduce_kernel, dim3((C + 2 + 15) / 16), dim3(1024), 0, st, partial, parts, C,
                      loss_scale, loss, dw, db);
   return check_launch("spa_gate_bwd");
 }
