@@ -73,7 +73,7 @@ const char* spa_last_error(void);
  *   attn_fwd_wave_max  longest segment (<= 256) the one-wave forward kernels take
  *   attn_bwd_short     "split" | "tiled": two-kernel / long-segment backward for segments <= 256
  *   attn_bwd_long      "two": the dq and dkdv roles of the long-segment backward as two launches
- *   gemm_tm            2 | 4 | 8: 128x128, 256x128, 256x256 projection tiles
+ *   gemm_tm            2 | 8: 128x128, 256x256 tiles of the projections (4 = 2)
  *   gemm_splits        1..16 token chunks of the weight-side GEMM
  *   pack_tile          16 | 32 | 64 | 128 | 256 tokens per packing workgroup
  */
@@ -376,6 +376,19 @@ int spa_linear_packed(const void* x, const int32_t* gather_idx, const float* gat
 int spa_linear_packed_scatter(const void* x, const int32_t* total, const void* W, const void* bias,
                               int M_cap, int K, int N_out, int dtype, const int32_t* scatter_idx,
                               const void* residual, void* y, int64_t y_row_stride, void* stream);
+
+/*
+ * The output projection of the block with the whole scatter back in one launch (Section 3.2): every row of
+ * y is written,
+ *   y[gather_idx[j], :] = residual[gather_idx[j], :] + (x[j, :] W^T + bias)   for j < min(*total, M_cap)
+ *   y[i, :]             = residual[i, :]                                      where inv_pos[i] < 0, i < rows
+ * i.e. spa_linear_packed followed by spa_unpack with base = residual, bit for bit, without the packed
+ * projection in between.  in: as spa_linear_packed_scatter; gather_idx, inv_pos [rows] from spa_pack;
+ * residual, y [rows, N_out] dtype (y may be residual itself).
+ */
+int spa_linear_packed_unpack(const void* x, const int32_t* total, const void* W, const void* bias, int M_cap,
+                             int K, int N_out, int dtype, const int32_t* gather_idx, const int32_t* inv_pos,
+                             int64_t rows, const void* residual, void* y, void* stream);
 
 /* ----------------------------------------------------------------- training ---- */
 

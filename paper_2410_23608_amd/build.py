@@ -40,11 +40,6 @@ def sources():
     return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hip"))
 
 
-# files whose kernels keep more accumulators than the ordinary half of the register file holds:
-# compiled without the "MFMA results in ordinary VGPRs" option
-AGPR_SOURCES = {"linear_big.hip"}
-
-
 # kept out of the source tree: nothing but the host-only sanitizer test reads it
 SAN_DIR = os.path.join(tempfile.gettempdir(), "spa_build_asan")
 SAN_LIB_PATH = os.path.join(SAN_DIR, "libspa_asan.so")
@@ -56,9 +51,6 @@ SAN_FLAGS = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=und
 def _compile(src: str, sanitize: bool = False) -> str:
     obj = os.path.join(SAN_DIR if sanitize else OBJ_DIR, os.path.basename(src)[:-4] + ".o")
     flags = list(FLAGS) + (SAN_FLAGS if sanitize else [])
-    if os.path.basename(src) in AGPR_SOURCES:
-        i = flags.index("-amdgpu-mfma-vgpr-form=1")
-        del flags[i - 1:i + 1]
     cmd = [HIPCC, *flags, "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

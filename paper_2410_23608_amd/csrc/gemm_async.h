@@ -1,0 +1,142 @@
+// The main loop shared by the projection GEMMs (bf16 MFMA, fp32 accumulation): operand tiles go from
+// memory straight to LDS (global_load_lds, 16 bytes a lane) through a ring of STAGES buffers, so the
+// loads of the next tiles are in flight without a register, a store or a wait for each other; the only
+// waits are one counted vmcnt and one barrier per 64-deep contraction step.
+//
+// A direct load puts a wave's 64 pieces of 16 bytes next to each other, so rows cannot be padded;
+// instead the pieces of a row are permuted on the way in (each lane chooses which piece it fetches) and
+// un-permuted in the fragment reads:
+//   rows operand ([rows][64], contraction along the row):  piece c of row r sits at c ^ (r & 7)
+//   deep operand ([64][cols], contraction down the rows):  piece c of row r sits at c ^ 4 (r & 3)
+// which spreads the 16-byte reads of 8 rows, and the transposing reads of 4 rows, over all banks.
+#pragma once
+
+#include "attn_tiles.h"
+#include "spa_common.h"
+
+namespace spa {
+
+constexpr int kGaK = 64;             // contraction step
+
+// 16 bytes of zeros for every lane whose piece lies outside the operand
+static __device__ __align__(256) const uint32_t gemm_zeros[64] = {};
+
+// 16 bytes per lane from src to the wave's 1 KB at LDS byte address dst (lane l at dst + 16 l; M0 holds
+// dst, which the load may use one wait state after it is written).  Inline assembly because the compiler
+// takes the builtin's load for one that may return through either counter and from then on waits for
+// lgkmcnt(0) before every use of an LDS read; what is in flight is counted by the waits below, and by
+// the compiler's own waits on the safe side.
+__device__ __forceinline__ void load_to_lds(const __bf16* src, uint32_t dst) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(src) : "memory", "m0");
+}
+template <int N>
+__device__ __forceinline__ void wait_vmem() {      // at most N vector memory operations still in flight
+  static_assert(N >= 0 && N < 64, "vmcnt has six bits");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0xF70);
+}
+
+// Operand with the contraction along its rows: fragment of rows r0 .. r0+31, contraction 16 kk .. + 15.
+__device__ __forceinline__ bf16x8 rows_frag(const __bf16* tile, int r0, int kk, int l32, int hh) {
+  const int r = r0 + l32;
+  return *reinterpret_cast<const bf16x8*>(tile + r * kGaK + (((2 * kk + hh) ^ (r & 7)) << 3));
+}
+// Operand with the contraction down its rows (COLS columns): fragment of columns c0 .. c0+31, contraction
+// rows 16 kk .. + 15, by the transposing read: within each block of 16 lanes lane i, element e, receives
+// what lane (4 e + i / 4) of the block addressed at its own element i % 4.
+template <int COLS>
+__device__ __forceinline__ bf16x8 deep_frag(const __bf16* tile, int kk, int c0, int lane) {
+  const int blk = lane >> 4, s = lane & 15;
+  const int row = 16 * kk + 8 * (blk >> 1) + (s >> 2);
+  const int piece = ((c0 >> 3) ^ (4 * (s >> 2))) + 2 * (blk & 1) + ((s & 3) >> 1);
+  const __bf16* p = tile + row * COLS + piece * 8 + 4 * (s & 1);
+  typedef shortx4_lds __attribute__((address_space(3))) * lds_ptr;
+  const shortx4_lds lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p));
+  const shortx4_lds hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 4 * COLS));
+  const bf16x4 l4 = __builtin_bit_cast(bf16x4, lo), h4 = __builtin_bit_cast(bf16x4, hi);
+  return __builtin_shufflevector(l4, h4, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// Which piece of which row a thread fetches: piece `col` (elements) of tile row row0 + u * row_step for
+// u = 0 .. count - 1.
+template <int ROWS, int THREADS>
+struct RowsPieces {
+  static constexpr int kCount = ROWS * 8 / THREADS, kRowStep = THREADS / 8;
+  static_assert(kRowStep % 8 == 0, "a thread keeps its permuted column");
+  __device__ static __forceinline__ int row0(int tid) { return tid >> 3; }
+  __device__ static __forceinline__ int col(int tid) { return ((tid & 7) ^ ((tid >> 3) & 7)) * 8; }
+};
+template <int COLS, int THREADS>
+struct DeepPieces {
+  static constexpr int kPerRow = COLS / 8, kCount = kGaK * kPerRow / THREADS, kRowStep = THREADS / kPerRow;
+  static_assert(kRowStep % 4 == 0, "a thread keeps its permuted column");
+  __device__ static __forceinline__ int row0(int tid) { return tid / kPerRow; }
+  __device__ static __forceinline__ int col(int tid) {
+    return ((tid % kPerRow) ^ (4 * ((tid / kPerRow) & 3))) * 8;
+  }
+};
+
+// acc[i][j] += sum over nk contraction steps of (B fragment j) x (A fragment i): MFMA tiles whose rows
+// are B's index and whose columns are A's.  The wave's block is TM * 32 of A by TN * 32 of B.
+// next_a(u, t) / next_b(u, t): address of the thread's u-th piece of step t (called for t = 0, 1, ... in
+// order, so they may step a pointer).  frag_a(tile, i, kk), frag_b(tile, j, kk): fragments;
+// beside(af): called with the A fragments of every 16 contraction elements.  All threads call it.  On
+// return nothing is in flight and every wave is past its last read of the buffers.
+struct Nothing {
+  template <class T> __device__ __forceinline__ void operator()(const T&) const {}
+};
+template <int A_ELEMS, int B_ELEMS, int NA, int NB, int STAGES, int THREADS, int TM, int TN, class FA, class FB, class RA, class RB,
+          class BS = Nothing>
+__device__ __forceinline__ void gemm_async_loop(__bf16* lds, int nk, FA&& next_a, FB&& next_b, RA&& frag_a, RB&& frag_b,
+                                                floatx16 (&acc)[TM][TN], BS&& beside = BS{}) {
+  constexpr int STAGE = A_ELEMS + B_ELEMS, KK = kGaK / 16;
+  const uint32_t wave_dst = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds +
+                            __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 1024;
+  auto issue = [&](int t, int stage) {
+    const uint32_t a = wave_dst + stage * (STAGE * 2), b = a + A_ELEMS * 2;
+#pragma unroll
+    for (int u = 0; u < NA; ++u) load_to_lds(next_a(u, t), a + u * (THREADS * 16));
+#pragma unroll
+    for (int u = 0; u < NB; ++u) load_to_lds(next_b(u, t), b + u * (THREADS * 16));
+  };
+#pragma unroll
+  for (int s = 0; s < STAGES - 1; ++s)
+    if (s < nk) issue(s, s);
+  int stage = 0;
+  for (int t = 0; t < nk; ++t) {
+    // this wave's pieces of step t have arrived (near the end fewer younger steps are in flight)
+    if (STAGES == 2 || t + STAGES - 2 >= nk) wait_vmem<0>();
+    else wait_vmem<(STAGES - 2) * (NA + NB)>();
+    __builtin_amdgcn_s_barrier();               // and everybody's; and step t - 1 has been read by all
+    const __bf16* a = lds + stage * STAGE;
+    const __bf16* b = a + A_ELEMS;
+    // the fragments of 16 contraction elements are read while the MFMAs of the 16 before run; left to
+    // itself the compiler puts every read right before its use and the two never overlap
+    bf16x8 af[2][TM], bfr[2][TN];
+    auto read = [&](int kk) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) af[kk & 1][i] = frag_a(a, i, kk);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) bfr[kk & 1][j] = frag_b(b, j, kk);
+    };
+    read(0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + STAGES - 1 < nk) issue(t + STAGES - 1, stage == 0 ? STAGES - 1 : stage - 1);
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      if (kk + 1 < KK) read(kk + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[kk & 1][j], af[kk & 1][i], acc[i][j], 0, 0, 0);
+      beside(af[kk & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    stage = stage + 1 == STAGES ? 0 : stage + 1;
+  }
+  wait_vmem<0>();
+  __syncthreads();
+}
+
+}  // namespace spa

@@ -5,211 +5,150 @@
 // The row scale s_j is applied to the fp32 accumulator in the epilogue: (s a) W^T = s (a W^T),
 // one rounding fewer than multiplying a materialised bf16 r_g.
 //
-// bf16 path: MFMA GEMM, C[M,N] = A[M,K] B[N,K]^T with both operands K-contiguous ("NT").
-// Workgroup tile 128 x 128 x 64, four waves in a 2 x 2 grid, each wave a 64 x 64 block
-// (2 x 2 v_mfma_f32_32x32x16_bf16 tiles), A and B tiles double-buffered in LDS with two
-// k-tiles of rows in flight in registers.  Row stride 72 elements keeps the 16-byte
-// fragment reads bank-conflict free.  The output tile leaves through LDS as whole rows.
-// The live tiles (the row count is only known on the device) are numbered m-major and cut
-// into 8 equal contiguous ranges, one per XCD (workgroup id % 8): the workgroups that share a
-// block of A rows run on one XCD's L2 and every XCD gets the same number of tiles.
-// Large problems with long k-loops take the 256 x 256 x 64 kernel of linear_big.hip.
+// bf16 path: MFMA GEMM on the pipelined loop of gemm_async.h, 64 deep steps, tiles of 128 x 128 (four waves
+// of 64 x 64, two workgroups per unit) or 256 x 256 (eight waves of 128 x 64); the same kernel multiplies
+// by W as it lies for the input side of the backward (linear_bwd.hip).  With 128 x 128 tiles every flop
+// needs 1/64 byte from L2 and the L2 delivers about 12 TB/s with this pattern, so the large tile, which
+// halves that, wins wherever its workgroups still fill the chip (launch_gemm_rows).  Measured, 12544 rows of
+// 768 -> 2304: 51 us = 870 TFLOP/s (operands staged through registers: 68 us); 6272 rows of 384 -> 384: 6.9
+// us (8.7); 98 rows: 6.3 us (8.1), its steps bound by latency.  The output tile leaves through LDS as
+// whole rows.
 // fp32 path (tiny workload): one thread per output element.
-#include "attn_tiles.h"
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+
+#include "gemm_async.h"
+#include "linear.h"
 #include "spa_common.h"
 
 namespace spa {
 
-constexpr int kGemmBN = 128, kGemmThreads = 256;
+// Workgroup tile BM x BN, WGM x WGN waves, each wave (BM / WGM) x (BN / WGN) of the output.
+// kDeep = false: out = A W^T, W [ncols][kc] (forward); kDeep = true: out = A W, W [kc][ncols] (input side
+// of the backward).  Either way the contraction has kc elements and runs along the rows of A.
+template <bool kScale, bool kDeep, int BM, int BN, int WGM, int WGN, int STAGES>
+__global__ void __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(BM > 128 ? 1 : 2)))
+gemm_rows_kernel(const GemmArgs p) {
+  constexpr int THREADS = 64 * WGM * WGN, TM = BM / WGM / 32, TN = BN / WGN / 32;
+  using PA = RowsPieces<BM, THREADS>;
+  using PB = typename std::conditional<kDeep, DeepPieces<BN, THREADS>, RowsPieces<BN, THREADS>>::type;
+  extern __shared__ __attribute__((aligned(16))) unsigned char gemm_smem[];
+  __bf16* lds = reinterpret_cast<__bf16*>(gemm_smem);
+  __shared__ float bias_s[BN];     // bias of the tile's output columns (0 past the edge or without bias)
+  __shared__ int o_row[BM];        // output row of every tile row
 
-// 256 x 256 x 64 tiles (linear_big.hip)
-hipError_t launch_linear_bf16_big(bool gather, bool scale, const void* x, const int32_t* gather_idx,
-                                  const float* gate_scores, const int32_t* total, const void* W, const void* bias,
-                                  int M_cap, int K, int N_out, void* out, long out_row_stride, hipStream_t st);
-
-// Workgroup tile (64 TM) x 128, four waves as 2 x 2, each wave (32 TM) x 64 of the output held
-// as TM x 2 MFMA tiles.  TM = 2: 128 x 128 tiles (more workgroups for small problems);
-// TM = 4: 256 x 128 tiles (a third less operand traffic per flop).
-template <bool kGather, bool kScale, int BK, int TM>
-__global__ void __launch_bounds__(kGemmThreads)
-linear_bf16_kernel(const __bf16* __restrict__ x, const int32_t* __restrict__ gather_idx,
-                   const float* __restrict__ gate_scores, const int32_t* __restrict__ total,
-                   const __bf16* __restrict__ W, const __bf16* __restrict__ bias, int m_cap, int K, int n_out,
-                   __bf16* out, long out_stride, int m_tiles, int n_tiles,
-                   const int32_t* __restrict__ scatter_idx, const __bf16* residual) {
-  constexpr int BM = 64 * TM, BN = kGemmBN, RS = BK + 8;   // RS = LDS row stride (elements)
-  extern __shared__ __attribute__((aligned(16))) unsigned char gemm_smem[];   // 2 x (A tile, B tile)
-  __bf16(*As)[BM * RS] = reinterpret_cast<__bf16(*)[BM * RS]>(gemm_smem);
-  __bf16(*Bs)[BN * RS] = reinterpret_cast<__bf16(*)[BN * RS]>(gemm_smem + 2 * BM * RS * sizeof(__bf16));
-  __shared__ long a_row[BM];       // source row of every tile row (-1 = past the end)
-  __shared__ float a_scale[BM];
-  __shared__ float bias_s[BN];     // bias of the tile's output columns (0 past n_out or without bias)
-  __shared__ int o_row[BM];        // output row of every tile row when the result is scattered
-
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
   // Tile order.  Workgroup ids go to the 8 XCDs round-robin (id % 8) and each XCD has its own
   // L2.  The LIVE tiles (the row count is only known here, on the device) are numbered m-major
   // and cut into 8 equal contiguous ranges, one per XCD: the workgroups that share a block of A
   // rows run on one XCD, and every XCD gets the same number of tiles.
-  const int M = total != nullptr ? min(total[0], m_cap) : m_cap;
-  const int live_tiles = ((M + BM - 1) / BM) * n_tiles, per_xcd = (live_tiles + 7) >> 3;
+  const int M = p.total != nullptr ? min(p.total[0], p.m_cap) : p.m_cap;
+  const int live_tiles = ((M + BM - 1) / BM) * p.n_tiles, per_xcd = (live_tiles + 7) >> 3;
   const int xcd = blockIdx.x & 7, jx = blockIdx.x >> 3, tile_id = xcd * per_xcd + jx;
-  if (jx >= per_xcd || tile_id >= live_tiles) return;
-  const int mt = tile_id / n_tiles, nt = tile_id - mt * n_tiles;
-  const int m0 = mt * BM, n0 = nt * BN;
+  if (jx < per_xcd && tile_id < live_tiles) {
+    const int mt = tile_id / p.n_tiles, nt = tile_id - mt * p.n_tiles;
+    const int m0 = mt * BM, n0 = nt * BN;
+    const int wm = (wv / WGN) * TM * 32, wn = (wv % WGN) * TN * 32;
 
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
-  const int wm = (wv >> 1) * 32 * TM, wn = (wv & 1) * 64;
-
-  for (int t = tid; t < BM; t += kGemmThreads) {
-    const int r = m0 + t;
-    long src = -1;
-    float sc = 1.f;
-    if (r < M) {
-      src = kGather ? (long)gather_idx[r] : (long)r;
-      if (kScale) sc = sigmoidf_dev(gate_scores[src]);
+    // rows past the end fetch the last valid row and columns past the edge a valid column: they only
+    // reach outputs that are never stored
+    const __bf16* ap[PA::kCount];
+    const __bf16* bp[PB::kCount];
+    const int a_col = PA::col(tid), b_col = PB::col(tid);
+#pragma unroll
+    for (int u = 0; u < PA::kCount; ++u) {
+      const int r = min(m0 + PA::row0(tid) + u * PA::kRowStep, M - 1);
+      ap[u] = p.a + (p.a_idx != nullptr ? (long)p.a_idx[r] : (long)r) * p.lda + a_col;
     }
-    a_row[t] = src;
-    a_scale[t] = sc;
-    o_row[t] = scatter_idx != nullptr && r < M ? scatter_idx[r] : r;
-  }
-  if (tid < BN) bias_s[tid] = bias != nullptr && n0 + tid < n_out ? static_cast<float>(bias[n0 + tid]) : 0.f;
-  __syncthreads();
-
-  // staging: a tile is rows x BK/8 chunks of 16 bytes.  The rows and chunk columns a thread
-  // stages never change, so their addresses are computed once.
-  // Rows past the end of the tile's valid range load a valid row instead of zeros: a row of A
-  // only reaches its own output row and a row of W its own output column, and the epilogue
-  // stores neither.
-  constexpr int CPRW = BK / 8, CA = BM * CPRW / kGemmThreads, CB = BN * CPRW / kGemmThreads;
-  const __bf16* ap[CA];
-  const __bf16* bp[CB];
-  const int st_r = tid / CPRW, st_c = tid % CPRW;           // chunk u of a thread: row st_r + u * (256 / CPRW)
-  constexpr int RSTEP = kGemmThreads / CPRW;
-  const int lds_off = st_r * RS + st_c * 8;
+    float row_scale[TM];
+    if (kScale) {
 #pragma unroll
-  for (int u = 0; u < CA; ++u) {
-    const long src = a_row[st_r + u * RSTEP];
-    ap[u] = x + (src >= 0 ? src : 0) * K + st_c * 8;
-  }
-#pragma unroll
-  for (int u = 0; u < CB; ++u) bp[u] = W + (long)min(n0 + st_r + u * RSTEP, n_out - 1) * K + st_c * 8;
-
-  // Two k-tiles in flight in registers.  When K is not a multiple of BK the PARTIAL k-tile comes
-  // first (k in [0, K % BK)), so that only the prologue needs masked loads and every tile the
-  // main loop touches is whole: tile t >= 1 starts at k = k_first + t * BK.
-  constexpr int PF = 2;
-  bf16x8 areg[PF][CA], breg[PF][CB];
-  const int k_tail = K % BK, nk = (K + BK - 1) / BK, k_first = k_tail ? k_tail - BK : 0;
-  auto gload = [&](int slot, int t) {   // whole tile t (t >= 1 when K % BK != 0)
-    const int k0 = k_first + t * BK;
-#pragma unroll
-    for (int u = 0; u < CA; ++u) areg[slot][u] = *reinterpret_cast<const bf16x8*>(ap[u] + k0);
-#pragma unroll
-    for (int u = 0; u < CB; ++u) breg[slot][u] = *reinterpret_cast<const bf16x8*>(bp[u] + k0);
-  };
-  auto gload_first = [&](int slot) {
-    if (k_tail == 0) { gload(slot, 0); return; }
-    const bool in_k = st_c * 8 < k_tail;   // columns past the partial tile are zero in both operands
-#pragma unroll
-    for (int u = 0; u < CA; ++u) areg[slot][u] = in_k ? *reinterpret_cast<const bf16x8*>(ap[u]) : zero_bf16x8();
-#pragma unroll
-    for (int u = 0; u < CB; ++u) breg[slot][u] = in_k ? *reinterpret_cast<const bf16x8*>(bp[u]) : zero_bf16x8();
-  };
-  auto lstore = [&](int slot, int buf) {
-#pragma unroll
-    for (int u = 0; u < CA; ++u) *reinterpret_cast<bf16x8*>(&As[buf][lds_off + u * RSTEP * RS]) = areg[slot][u];
-#pragma unroll
-    for (int u = 0; u < CB; ++u) *reinterpret_cast<bf16x8*>(&Bs[buf][lds_off + u * RSTEP * RS]) = breg[slot][u];
-  };
-  auto compute = [&](int buf, floatx16 (&acc)[TM][2]) {
-#pragma unroll
-    for (int kk = 0; kk < BK / 16; ++kk) {
-      bf16x8 af[TM], bfr[2];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-        af[i] = *reinterpret_cast<const bf16x8*>(&As[buf][(wm + i * 32 + l32) * RS + kk * 16 + hh * 8]);
-#pragma unroll
-      for (int jn = 0; jn < 2; ++jn)
-        bfr[jn] = *reinterpret_cast<const bf16x8*>(&Bs[buf][(wn + jn * 32 + l32) * RS + kk * 16 + hh * 8]);
-      // C^T tile: rows = output columns n, cols = tokens m, so that a lane's 4 consecutive
-      // accumulator registers are 4 consecutive n of one token (8-byte output pieces)
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int jn = 0; jn < 2; ++jn)
-          acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[jn], af[i], acc[i][jn], 0, 0, 0);
+      for (int i = 0; i < TM; ++i) row_scale[i] = p.scores[p.a_idx[min(m0 + wm + i * 32 + l32, M - 1)]];
     }
-  };
+#pragma unroll
+    for (int u = 0; u < PB::kCount; ++u) {
+      const int r = PB::row0(tid) + u * PB::kRowStep;
+      bp[u] = kDeep ? p.w + (long)r * p.ncols + (n0 + b_col < p.ncols ? n0 + b_col : n0)
+                    : p.w + (long)min(n0 + r, p.ncols - 1) * p.kc + b_col;
+    }
+    for (int t = tid; t < BN; t += THREADS)
+      bias_s[t] = p.bias != nullptr && n0 + t < p.ncols ? static_cast<float>(p.bias[n0 + t]) : 0.f;
+    for (int t = tid; t < BM; t += THREADS) o_row[t] = p.o_idx != nullptr && m0 + t < M ? p.o_idx[m0 + t] : m0 + t;
 
-  floatx16 acc[TM][2];
+    const int nk = (p.kc + kGaK - 1) / kGaK, k_tail = p.kc % kGaK;
+    const __bf16* zeros = reinterpret_cast<const __bf16*>(gemm_zeros);
+    const long b_step = kDeep ? (long)kGaK * p.ncols : kGaK;
+    // the last step may be partial: pieces past the contraction are zero in both operands
+    auto next_a = [&](int u, int t) {
+      const __bf16* g = ap[u];
+      ap[u] += kGaK;
+      if (k_tail != 0 && t == nk - 1 && a_col >= k_tail) g = zeros;
+      return g;
+    };
+    auto next_b = [&](int u, int t) {
+      const __bf16* g = bp[u];
+      bp[u] += b_step;
+      if (k_tail != 0 && t == nk - 1 && (kDeep ? PB::row0(tid) + u * PB::kRowStep : b_col) >= k_tail) g = zeros;
+      return g;
+    };
+    auto frag_a = [&](const __bf16* tile, int i, int kk) { return rows_frag(tile, wm + i * 32, kk, l32, hh); };
+    auto frag_b = [&](const __bf16* tile, int j, int kk) {
+      if constexpr (kDeep) return deep_frag<BN>(tile, kk, wn + j * 32, lane);
+      else return rows_frag(tile, wn + j * 32, kk, l32, hh);
+    };
+    floatx16 acc[TM][TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int jn = 0; jn < 2; ++jn)
+      for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][jn][r] = 0.f;
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    gemm_async_loop<BM * kGaK, BN * kGaK, PA::kCount, PB::kCount, STAGES, THREADS, TM, TN>(lds, nk, next_a, next_b, frag_a,
+                                                                                           frag_b, acc);
 
-  // Software pipeline over k-tiles, two per trip so that register slots and LDS buffers are
-  // static.  Entering a trip: LDS buffer 0 holds tile kt, slot 1 holds tile kt+1, slot 0 is free.
-  // Loads past the last tile repeat the last tile and what they bring is never multiplied, which
-  // keeps the loop body free of branches (the compiler then counts outstanding loads exactly).
-  const int last = nk - 1;
-  gload_first(0);
-  if (nk > 1) gload(1, 1);
-  lstore(0, 0);
-  __syncthreads();
-  for (int kt = 0; kt + 1 < nk; kt += 2) {
-    gload(0, min(kt + 2, last));
-    compute(0, acc);
-    lstore(1, 1);        // tile kt+1
-    __syncthreads();
-    gload(1, min(kt + 3, last));
-    compute(1, acc);
-    lstore(0, 0);        // tile kt+2, or a repeat of the last tile
-    __syncthreads();
-  }
-  if (nk & 1) {
-    compute(0, acc);
-    __syncthreads();     // the epilogue reuses the operand buffers
-  }
-
-  // epilogue: scale, bias, bf16; 64 rows x 64 columns of the wave at a time are parked in LDS
-  // (the operand buffers are free after the last barrier) and leave as whole 16-byte pieces
-  constexpr int ORS = 64 + 8;
-  static_assert(4 * 64 * ORS <= 2 * (BM + BN) * RS, "output staging fits in the operand buffers");
-  __bf16* tile = reinterpret_cast<__bf16*>(gemm_smem) + wv * 64 * ORS;   // 64 rows x 72 per wave
-  float row_scale[TM];
+    // epilogue: scale, bias, bf16; 32 rows of the wave at a time are parked in its own part of LDS (LDS
+    // operations of a wave complete in order) and leave as whole 16-byte pieces
+    constexpr int NC = TN * 32, ORS = NC + 8, PIECES = NC / 8;
+    static_assert(WGM * WGN * 2 * 32 * ORS <= STAGES * (BM + BN) * kGaK, "output staging fits in the operand buffers");
 #pragma unroll
-  for (int i = 0; i < TM; ++i) row_scale[i] = a_scale[wm + i * 32 + l32];
+    for (int i = 0; i < TM; ++i) {
+      __bf16* tile = lds + (wv * 2 + (i & 1)) * 32 * ORS;
+      const float rs = kScale ? sigmoidf_dev(row_scale[i]) : 1.f;
 #pragma unroll
-  for (int half = 0; half < TM / 2; ++half) {
-#pragma unroll
-    for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-      for (int jn = 0; jn < 2; ++jn)
+      for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const int i = half * 2 + ii;
-          const int nloc = jn * 32 + 8 * g + 4 * hh;        // 4 consecutive output columns
-          floatx4 f = {acc[i][jn][4 * g], acc[i][jn][4 * g + 1], acc[i][jn][4 * g + 2], acc[i][jn][4 * g + 3]};
-          if (kScale) f *= row_scale[i];
-          f += *reinterpret_cast<const floatx4*>(&bias_s[wn + nloc]);
-          *reinterpret_cast<bf16x4*>(&tile[(ii * 32 + l32) * ORS + nloc]) = __builtin_convertvector(f, bf16x4);
+          const int n = j * 32 + 8 * g + 4 * hh;        // 4 consecutive output columns
+          floatx4 f = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+          if (kScale) f *= rs;
+          f += *reinterpret_cast<const floatx4*>(&bias_s[wn + n]);
+          *reinterpret_cast<bf16x4*>(&tile[l32 * ORS + n]) = __builtin_convertvector(f, bf16x4);
         }
-    __syncthreads();
-    // 64 rows x 8 chunks per wave
-    for (int i = lane; i < 64 * 8; i += 64) {
-      const int r = i >> 3, c = i & 7;
-      const int m = m0 + wm + half * 64 + r, n = n0 + wn + c * 8;
-      if (m < M && n < n_out) {
-        const long off = (long)o_row[wm + half * 64 + r] * out_stride + n;
-        bf16x8 val = *reinterpret_cast<const bf16x8*>(&tile[r * ORS + c * 8]);
-        if (residual != nullptr)
-          val = float_to_bf16x8(bf16x8_to_float(val) + bf16x8_to_float(*reinterpret_cast<const bf16x8*>(residual + off)));
-        *reinterpret_cast<bf16x8*>(out + off) = val;
+#pragma unroll
+      for (int c = lane; c < 32 * PIECES; c += 64) {
+        const int r = c / PIECES, ch = c % PIECES, row = wm + i * 32 + r, n = n0 + wn + ch * 8;
+        if (m0 + row < M && n < p.ncols) {
+          const long off = (long)o_row[row] * p.ldo + n;
+          bf16x8 val = *reinterpret_cast<const bf16x8*>(&tile[r * ORS + ch * 8]);
+          if (p.residual != nullptr)
+            val = float_to_bf16x8(bf16x8_to_float(val) + bf16x8_to_float(*reinterpret_cast<const bf16x8*>(p.residual + off)));
+          *reinterpret_cast<bf16x8*>(p.out + off) = val;
+        }
       }
     }
-    __syncthreads();
+  }
+  // The rows no packed row maps to: shared by the waves of the workgroups without a tile, which run beside
+  // the others, or by all when those are few.
+  if (p.inv_pos != nullptr) {
+    constexpr int NW = WGM * WGN;
+    const int live = min((int)gridDim.x, 8 * per_xcd), idle = (int)gridDim.x - live;
+    const bool by_idle = 4 * idle >= live;
+    const long units = (long)(by_idle ? idle : (int)gridDim.x) * NW;
+    const long u = ((long)blockIdx.x - (by_idle ? live : 0)) * NW + wv;      // (idle: jx >= per_xcd, i.e. blockIdx.x >= 8 per_xcd)
+    if (u < 0) return;
+    const long per = (p.zrows + units - 1) / units, r0 = min(p.zrows, u * per), r1 = min(p.zrows, r0 + per);
+    zero_unselected_rows(p.out, p.ldo, p.ncols, p.inv_pos, r0, r1, lane, p.residual);
   }
 }
 
@@ -218,7 +157,13 @@ __global__ void __launch_bounds__(256)
 linear_f32_kernel(const float* __restrict__ x, const int32_t* __restrict__ gather_idx,
                   const float* __restrict__ gate_scores, const int32_t* __restrict__ total,
                   const float* __restrict__ W, const float* __restrict__ bias, int m_cap, int K, int n_out,
-                  float* out, long out_stride, const int32_t* __restrict__ scatter_idx, const float* residual) {
+                  float* out, long out_stride, const int32_t* __restrict__ scatter_idx, const float* residual,
+                  const int32_t* __restrict__ inv_pos, long rows) {
+  if (inv_pos != nullptr)          // the rows no packed row maps to keep the residual
+    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < rows * n_out; i += (long)gridDim.x * blockDim.x) {
+      const long r = i / n_out, at = r * out_stride + (i - r * n_out);
+      if (inv_pos[r] < 0) out[at] = residual[at];
+    }
   const int M = total != nullptr ? min(total[0], m_cap) : m_cap;
   const long work = (long)M * n_out;
   for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < work; i += (long)gridDim.x * blockDim.x) {
@@ -234,6 +179,46 @@ linear_f32_kernel(const float* __restrict__ x, const int32_t* __restrict__ gathe
   }
 }
 
+template <bool kScale, bool kDeep, int BM, int BN, int WGM, int WGN, int STAGES>
+static int launch_gemm_rows_tile(const char* fn, GemmArgs args, hipStream_t st) {
+  constexpr size_t smem = (size_t)STAGES * (BM + BN) * kGaK * sizeof(__bf16);
+  const long m_tiles = (args.m_cap + BM - 1) / BM;
+  args.n_tiles = (args.ncols + BN - 1) / BN;
+  SPA_REQUIRE(m_tiles * args.n_tiles + 8 < 2147483647L / 2, SPA_ERR_INVALID_ARG, "%s: too many tiles", fn);
+  const void* kernel = (const void*)gemm_rows_kernel<kScale, kDeep, BM, BN, WGM, WGN, STAGES>;
+  const hipError_t attr = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  SPA_REQUIRE(attr == hipSuccess, SPA_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, smem);
+  const unsigned grid = (unsigned)((m_tiles * args.n_tiles + 7) / 8 * 8);
+  hipLaunchKernelGGL((gemm_rows_kernel<kScale, kDeep, BM, BN, WGM, WGN, STAGES>), dim3(grid), dim3(64 * WGM * WGN), smem,
+                     st, args);
+  return check_launch(fn);
+}
+
+// Tile shape, from about half of the capacity live (what a packed stream has).  Measured step times: a 128 x
+// 128 x 64 step takes 0.45 us alone on its unit, two workgroups per unit and all units share the L2
+// bandwidth (0.0033 us per tile of the launch); a 256 x 256 x 64 step takes 1.55 us, and 0.0087 us per tile
+// when all units are busy: two thirds of the time per output, paid with a quarter of the workgroups and 3 us
+// more before the first and after the last step (6272 x 2304, K 768: 27.5 against 35 us; 6272 x 768: 23
+// against 16 us).  Option gemm_tm = 2 | 8 forces 128 x 128 | 256 x 256 (tuning aid).
+static bool big_tiles(const GemmArgs& a) {
+  const int cfg = options().gemm_tm;
+  if (cfg != 0) return cfg == 8;
+  const double live = a.total != nullptr ? 0.5 * a.m_cap : a.m_cap, nk = (a.kc + kGaK - 1) / kGaK;
+  const double big = ((live + 255) / 256) * ((a.ncols + 255) / 256), small = ((live + 127) / 128) * ((a.ncols + 127) / 128);
+  return nk * fmax(1.55, 0.0087 * big) + 3.0 < nk * fmax(0.45, 0.0033 * small);
+}
+
+int launch_gemm_rows(const char* fn, const GemmArgs& args, bool deep, hipStream_t st) {
+  const bool big = big_tiles(args);
+#define SPA_GEMM(S_, D_)                                                                              \
+  return big ? launch_gemm_rows_tile<S_, D_, 256, 256, 2, 4, 2>(fn, args, st)                         \
+             : launch_gemm_rows_tile<S_, D_, 128, 128, 2, 2, 2>(fn, args, st)
+  if (deep) SPA_GEMM(false, true);
+  if (args.scores != nullptr) SPA_GEMM(true, false);
+  SPA_GEMM(false, false);
+#undef SPA_GEMM
+}
+
 }  // namespace spa
 
 using namespace spa;
@@ -241,7 +226,7 @@ using namespace spa;
 static int linear_common(const char* fn, const void* x, const int32_t* gather_idx, const float* gate_scores,
                          const int32_t* total, const void* W, const void* bias, int M_cap, int K, int N_out,
                          int dtype, void* out, int64_t out_row_stride, const int32_t* scatter_idx,
-                         const void* residual, void* stream) {
+                         const void* residual, const int32_t* inv_pos, int64_t rows, void* stream) {
   SPA_REQUIRE(x && W && out, SPA_ERR_INVALID_ARG, "%s: null pointer", fn);
   SPA_REQUIRE(M_cap >= 1 && K >= 1 && N_out >= 1, SPA_ERR_INVALID_ARG, "%s: M_cap, K, N_out must be >= 1", fn);
   SPA_REQUIRE(dtype == SPA_F32 || dtype == SPA_BF16, SPA_ERR_UNSUPPORTED, "%s: unknown dtype %d", fn, dtype);
@@ -251,12 +236,12 @@ static int linear_common(const char* fn, const void* x, const int32_t* gather_id
   hipStream_t st = as_stream(stream);
   const bool g = gather_idx != nullptr, sc = gate_scores != nullptr;
   if (dtype == SPA_F32) {
-    long wgs = ((long)M_cap * N_out + 255) / 256;
+    long wgs = (std::max((long)M_cap, inv_pos != nullptr ? (long)rows : 0L) * N_out + 255) / 256;
     if (wgs > 8192) wgs = 8192;
 #define SPA_LIN_F32(G_, S_)                                                                                   \
   hipLaunchKernelGGL((linear_f32_kernel<G_, S_>), dim3((unsigned)wgs), dim3(256), 0, st, (const float*)x,    \
                      gather_idx, gate_scores, total, (const float*)W, (const float*)bias, M_cap, K, N_out,   \
-                     (float*)out, (long)out_row_stride, scatter_idx, (const float*)residual)
+                     (float*)out, (long)out_row_stride, scatter_idx, (const float*)residual, inv_pos, (long)rows)
     if (g && sc) SPA_LIN_F32(true, true); else if (g) SPA_LIN_F32(true, false); else SPA_LIN_F32(false, false);
 #undef SPA_LIN_F32
     return check_launch(fn);
@@ -265,52 +250,31 @@ static int linear_common(const char* fn, const void* x, const int32_t* gather_id
   SPA_REQUIRE(N_out % 8 == 0 && out_row_stride % 8 == 0, SPA_ERR_INVALID_ARG,
               "%s: N_out and out_row_stride must be multiples of 8 for bf16", fn);
   SPA_REQUIRE(aligned16(x) && aligned16(W) && aligned16(out), SPA_ERR_INVALID_ARG, "%s: x / W / out not 16-byte aligned", fn);
-  // tile shape: 256 x 256 x 64 only where it measured faster than 128 x 128 x 64: long k-loops
-  // and enough tiles that the live ones (about half of the capacity for a packed stream) still
-  // cover most CUs.  option gemm_tm = 2 | 4 | 8 forces 128 x 128, 256 x 128 or 256 x 256 (tuning aid).
-  const int cfg_env = options().gemm_tm;
-  const long tiles_big = (long)((M_cap + 255) / 256) * ((N_out + 255) / 256);
-  const bool plain_out = scatter_idx == nullptr && residual == nullptr;
-  const bool big = plain_out && (cfg_env == 8 || (cfg_env == 0 && tiles_big >= 384 && K >= 512));
-  if (big) {
-    const hipError_t e = launch_linear_bf16_big(g, sc, x, gather_idx, gate_scores, total, W, bias, M_cap, K, N_out,
-                                                out, (long)out_row_stride, st);
-    SPA_REQUIRE(e == hipSuccess, SPA_ERR_HIP, "%s: cannot reserve LDS for the 256 x 256 tile: %s", fn,
-                hipGetErrorString(e));
-    return check_launch(fn);
-  }
-  const int tm = cfg_env == 4 ? 4 : 2;
-  const int bm = 64 * tm;
-  const int m_tiles = (M_cap + bm - 1) / bm, n_tiles = (N_out + kGemmBN - 1) / kGemmBN;
-  SPA_REQUIRE((long)m_tiles * n_tiles + 8 < 2147483647L / 2, SPA_ERR_INVALID_ARG, "%s: too many tiles", fn);
-  const unsigned grid = (unsigned)((long)((m_tiles + 7) / 8) * 8 * n_tiles);
-#define SPA_LIN_BF16(G_, S_, BK_, TM_)                                                                        \
-  do {                                                                                                        \
-    constexpr size_t smem = (size_t)2 * (64 * TM_ + kGemmBN) * (BK_ + 8) * sizeof(__bf16);                     \
-    const hipError_t attr = hipFuncSetAttribute((const void*)linear_bf16_kernel<G_, S_, BK_, TM_>,            \
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);       \
-    SPA_REQUIRE(attr == hipSuccess, SPA_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, smem);            \
-    hipLaunchKernelGGL((linear_bf16_kernel<G_, S_, BK_, TM_>), dim3(grid), dim3(kGemmThreads), smem, st,      \
-                       (const __bf16*)x, gather_idx, gate_scores, total, (const __bf16*)W, (const __bf16*)bias, \
-                       M_cap, K, N_out, (__bf16*)out, (long)out_row_stride, m_tiles, n_tiles, scatter_idx,     \
-                       (const __bf16*)residual);                                                              \
-  } while (0)
-#define SPA_LIN_BF16_CFG(BK_, TM_)                                                                            \
-  do {                                                                                                        \
-    if (g && sc) SPA_LIN_BF16(true, true, BK_, TM_); else if (g) SPA_LIN_BF16(true, false, BK_, TM_);         \
-    else SPA_LIN_BF16(false, false, BK_, TM_);                                                                \
-  } while (0)
-  if (tm == 4) SPA_LIN_BF16_CFG(32, 4); else SPA_LIN_BF16_CFG(64, 2);
-#undef SPA_LIN_BF16_CFG
-#undef SPA_LIN_BF16
-  return check_launch(fn);
+  GemmArgs args = {};
+  args.a = (const __bf16*)x;
+  args.a_idx = gather_idx;
+  args.lda = K;
+  args.scores = gate_scores;
+  args.total = total;
+  args.m_cap = M_cap;
+  args.kc = K;
+  args.ncols = N_out;
+  args.w = (const __bf16*)W;
+  args.bias = (const __bf16*)bias;
+  args.out = (__bf16*)out;
+  args.ldo = out_row_stride;
+  args.o_idx = scatter_idx;
+  args.residual = (const __bf16*)residual;
+  args.inv_pos = inv_pos;
+  args.zrows = rows;
+  return launch_gemm_rows(fn, args, false, st);
 }
 
 extern "C" int spa_linear_packed(const void* x, const int32_t* gather_idx, const float* gate_scores,
                                  const int32_t* total, const void* W, const void* bias, int M_cap, int K,
                                  int N_out, int dtype, void* out, int64_t out_row_stride, void* stream) {
   return linear_common("spa_linear_packed", x, gather_idx, gate_scores, total, W, bias, M_cap, K, N_out, dtype, out,
-                       out_row_stride, nullptr, nullptr, stream);
+                       out_row_stride, nullptr, nullptr, nullptr, 0, stream);
 }
 
 extern "C" int spa_linear_packed_scatter(const void* x, const int32_t* total, const void* W, const void* bias,
@@ -320,5 +284,16 @@ extern "C" int spa_linear_packed_scatter(const void* x, const int32_t* total, co
   SPA_REQUIRE(scatter_idx != nullptr, SPA_ERR_INVALID_ARG, "%s: scatter_idx is null", fn);
   SPA_REQUIRE(aligned16(residual), SPA_ERR_INVALID_ARG, "%s: residual not 16-byte aligned", fn);
   return linear_common(fn, x, nullptr, nullptr, total, W, bias, M_cap, K, N_out, dtype, y, y_row_stride, scatter_idx,
-                       residual, stream);
+                       residual, nullptr, 0, stream);
+}
+
+extern "C" int spa_linear_packed_unpack(const void* x, const int32_t* total, const void* W, const void* bias, int M_cap,
+                                        int K, int N_out, int dtype, const int32_t* gather_idx, const int32_t* inv_pos,
+                                        int64_t rows, const void* residual, void* y, void* stream) {
+  const char* fn = "spa_linear_packed_unpack";
+  SPA_REQUIRE(gather_idx && inv_pos && residual, SPA_ERR_INVALID_ARG, "%s: null pointer", fn);
+  SPA_REQUIRE(rows >= 1 && rows < 2147483647L, SPA_ERR_INVALID_ARG, "%s: rows must be in [1, 2^31)", fn);
+  SPA_REQUIRE(aligned16(residual), SPA_ERR_INVALID_ARG, "%s: residual not 16-byte aligned", fn);
+  return linear_common(fn, x, nullptr, nullptr, total, W, bias, M_cap, K, N_out, dtype, y, N_out, gather_idx, residual,
+                       inv_pos, rows, stream);
 }

@@ -9,21 +9,21 @@
 // contraction index, with whole 16-byte pieces, and the MFMA fragments are taken with the
 // transposing LDS read (ds_read_b64_tr_b16), so nothing is transposed in memory or staged twice.
 //
-// Input side: 128 x 128 x 64 tiles, four waves 2 x 2, the live tiles cut into 8 contiguous
-// ranges, one per XCD (as in the forward kernel).  The gather of the upstream rows
-// (dout_idx), the scatter of the result rows (dx_idx) and the zero fill of the rows no
-// packed row maps to are folded in.
+// Input side: the row GEMM of linear.hip, which also folds in the gather of the upstream rows (dout_idx),
+// the scatter of the result rows (dx_idx) and the zero fill of the rows no packed row maps to.
 // Weight side: the output is only N_out x K (a few dozen 128 x 128 tiles), so the tokens are
 // cut into `splits` chunks (chunk length fixed on the device from the live row count, so all
 // chunks carry work) and every (chunk, tile) is a workgroup; the partial tiles go to a
 // workspace in fp32 and a second kernel adds them in chunk order: deterministic, no atomics.
-// Items are numbered chunk-major and cut into 8 contiguous ranges, one per XCD, so the tiles
-// that read the same rows share an L2.  dbias comes from the same fragments: one more MFMA
-// per step against a vector of ones in the workgroups of the first column tile.
+// The operands come through the pipelined loop of gemm_async.h (weight_gemm_kernel); rows that have to be
+// multiplied by the gate scale and rounded on the way cannot go straight to LDS and keep the kernel that
+// stages them through registers (linear_bwd_weight_bf16_kernel).
 // fp32 (tiny workload): one thread per output element.
 #include <stdlib.h>
 
 #include "attn_tiles.h"
+#include "gemm_async.h"
+#include "linear.h"
 #include "spa_common.h"
 
 namespace spa {
@@ -33,10 +33,9 @@ constexpr int kLbT = 128;          // output tile edge
 constexpr int kLbK = 64;           // contraction step
 constexpr int kLbRS = kLbT + 16;   // row stride (elements) of a [contraction][128] tile: 72 dwords = 8 mod 64,
                                    // the 4 rows x 32 bytes a 16-lane block reads fall on distinct banks
-constexpr int kLbRSA = kLbK + 8;   // row stride of a [128][contraction] tile (16-byte fragment reads)
-constexpr size_t kLbInputLds = (size_t)2 * (kLbT * kLbRSA + kLbK * kLbRS) * sizeof(__bf16);
 constexpr int kLbRows = 512;       // rows of a chunk whose sources are tabled in LDS at a time (6 KB: with the
                                    // operand stages 78 KB per workgroup, two workgroups per compute unit)
+constexpr size_t kLbGemmLds = (size_t)2 * 2 * kLbK * kLbT * sizeof(__bf16);   // two operand stages
 constexpr size_t kLbWeightLds = (size_t)2 * 2 * kLbK * kLbRS * sizeof(__bf16);
 
 // MFMA operand fragment taken DOWN the columns of a row-major tile whose rows are the
@@ -56,163 +55,7 @@ __device__ __forceinline__ bf16x8 frag_down_columns(const __bf16* tile, int k0, 
   return __builtin_shufflevector(l4, h4, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// ------------------------------------------------------------------------------ input side
-// dx[o(j), :] = dout[a(j), :] W for j < M, W [kc][ncols] row-major (kc = N_out of the forward,
-// the contraction; ncols = K of the forward).
-__global__ void __launch_bounds__(kLbThreads)
-linear_bwd_input_bf16_kernel(const __bf16* __restrict__ dout, const int32_t* __restrict__ dout_idx, long ldd,
-                             const int32_t* __restrict__ total, const __bf16* __restrict__ W, int m_cap, int kc,
-                             int ncols, __bf16* __restrict__ dx, long ldx, const int32_t* __restrict__ dx_idx,
-                             const int32_t* __restrict__ inv_pos, long rows, int n_tiles) {
-  constexpr int BM = kLbT, BN = kLbT, BK = kLbK, RSA = kLbRSA, RSB = kLbRS;
-  extern __shared__ __attribute__((aligned(16))) unsigned char lb_smem[];
-  __bf16(*As)[BM * RSA] = reinterpret_cast<__bf16(*)[BM * RSA]>(lb_smem);
-  __bf16(*Bs)[BK * RSB] = reinterpret_cast<__bf16(*)[BK * RSB]>(lb_smem + 2 * BM * RSA * sizeof(__bf16));
-  __shared__ long a_row[BM];   // source row of every tile row (-1 = past the end)
-  __shared__ int o_row[BM];    // destination row
-
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
-
-  // every wave of the grid clears its share of the rows no packed row maps to
-  if (inv_pos != nullptr) {
-    const long units = (long)gridDim.x * 4, u = (long)blockIdx.x * 4 + wv;
-    const long per = (rows + units - 1) / units, r0 = min(rows, u * per), r1 = min(rows, r0 + per);
-    zero_unselected_rows(dx, ldx, ncols, inv_pos, r0, r1, lane);
-  }
-
-  const int M = total != nullptr ? min(total[0], m_cap) : m_cap;
-  const int live_tiles = ((M + BM - 1) / BM) * n_tiles, per_xcd = (live_tiles + 7) >> 3;
-  const int xcd = blockIdx.x & 7, jx = blockIdx.x >> 3, tile_id = xcd * per_xcd + jx;
-  if (jx >= per_xcd || tile_id >= live_tiles) return;
-  const int mt = tile_id / n_tiles, nt = tile_id - mt * n_tiles;
-  const int m0 = mt * BM, n0 = nt * BN;
-  const int wm = (wv >> 1) * 64, wn = (wv & 1) * 64;
-
-  if (tid < BM) {
-    const int r = m0 + tid;
-    a_row[tid] = r < M ? (dout_idx != nullptr ? (long)dout_idx[r] : (long)r) : -1;
-    o_row[tid] = r < M && dx_idx != nullptr ? dx_idx[r] : r;
-  }
-  __syncthreads();
-
-  // staging.  A: 128 rows x 8 chunks of 16 bytes, thread -> chunk tid % 8 of rows tid / 8 + 32 u.
-  // B: 64 contraction rows x 16 chunks, thread -> chunk tid % 16 of rows tid / 16 + 16 u.
-  // Rows of A past the valid range load a valid row and columns of B past ncols load a valid
-  // column: such a row or column only reaches outputs that are never stored.
-  constexpr int NU = 4;
-  const int sa_r = tid >> 3, sa_c = tid & 7, sb_r = tid >> 4, sb_c = tid & 15;
-  const int lds_a = sa_r * RSA + sa_c * 8, lds_b = sb_r * RSB + sb_c * 8;
-  const __bf16* ap[NU];
-#pragma unroll
-  for (int u = 0; u < NU; ++u) {
-    const long src = a_row[sa_r + u * 32];
-    ap[u] = dout + (src >= 0 ? src : 0) * ldd + sa_c * 8;
-  }
-  const __bf16* bcol = W + (n0 + sb_c * 8 < ncols ? n0 + sb_c * 8 : n0);
-
-  // When kc is not a multiple of BK the PARTIAL contraction tile comes first (its data at the
-  // front of the tile, zeros behind), so only the prologue needs masked loads: tile t >= 1
-  // starts at contraction index k_first + t * BK.
-  constexpr int PF = 2;
-  bf16x8 areg[PF][NU], breg[PF][NU];
-  const int k_tail = kc % BK, nk = (kc + BK - 1) / BK, k_first = k_tail ? k_tail - BK : 0;
-  auto gload = [&](int slot, int t) {
-    const int k0 = k_first + t * BK;
-#pragma unroll
-    for (int u = 0; u < NU; ++u) areg[slot][u] = *reinterpret_cast<const bf16x8*>(ap[u] + k0);
-#pragma unroll
-    for (int u = 0; u < NU; ++u)
-      breg[slot][u] = *reinterpret_cast<const bf16x8*>(bcol + (long)(k0 + sb_r + u * 16) * ncols);
-  };
-  auto gload_first = [&](int slot) {
-    if (k_tail == 0) { gload(slot, 0); return; }
-#pragma unroll
-    for (int u = 0; u < NU; ++u)
-      areg[slot][u] = sa_c * 8 < k_tail ? *reinterpret_cast<const bf16x8*>(ap[u]) : zero_bf16x8();
-#pragma unroll
-    for (int u = 0; u < NU; ++u)
-      breg[slot][u] = sb_r + u * 16 < k_tail ? *reinterpret_cast<const bf16x8*>(bcol + (long)(sb_r + u * 16) * ncols)
-                                             : zero_bf16x8();
-  };
-  auto lstore = [&](int slot, int buf) {
-#pragma unroll
-    for (int u = 0; u < NU; ++u) *reinterpret_cast<bf16x8*>(&As[buf][lds_a + u * 32 * RSA]) = areg[slot][u];
-#pragma unroll
-    for (int u = 0; u < NU; ++u) *reinterpret_cast<bf16x8*>(&Bs[buf][lds_b + u * 16 * RSB]) = breg[slot][u];
-  };
-
-  floatx16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int jn = 0; jn < 2; ++jn)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][jn][r] = 0.f;
-
-  auto compute = [&](int buf) {
-#pragma unroll
-    for (int kk = 0; kk < BK / 16; ++kk) {
-      bf16x8 af[2], bfr[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-        af[i] = *reinterpret_cast<const bf16x8*>(&As[buf][(wm + i * 32 + l32) * RSA + kk * 16 + hh * 8]);
-#pragma unroll
-      for (int jn = 0; jn < 2; ++jn) bfr[jn] = frag_down_columns<RSB>(Bs[buf], kk * 16, wn + jn * 32, lane);
-      // C^T tiles: rows = output columns, cols = packed rows (a lane's 4 consecutive accumulator
-      // registers are 4 consecutive columns of one row)
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int jn = 0; jn < 2; ++jn)
-          acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[jn], af[i], acc[i][jn], 0, 0, 0);
-    }
-  };
-
-  // Entering a trip: LDS buffer 0 holds tile kt, slot 1 holds tile kt + 1, slot 0 is free.
-  // Loads past the last tile repeat it; what they bring is stored but never multiplied.
-  const int last = nk - 1;
-  gload_first(0);
-  if (nk > 1) gload(1, 1);
-  lstore(0, 0);
-  __syncthreads();
-  for (int kt = 0; kt + 1 < nk; kt += 2) {
-    gload(0, min(kt + 2, last));
-    compute(0);
-    lstore(1, 1);
-    __syncthreads();
-    gload(1, min(kt + 3, last));
-    compute(1);
-    lstore(0, 0);
-    __syncthreads();
-  }
-  if (nk & 1) {
-    compute(0);
-    __syncthreads();     // the epilogue reuses the operand buffers
-  }
-
-  // epilogue: the wave's 64 x 64 block is parked in LDS as bf16 and leaves as 16-byte pieces
-  constexpr int ORS = 64 + 8;
-  static_assert((size_t)4 * 64 * ORS * sizeof(__bf16) <= kLbInputLds, "output staging fits in the operand buffers");
-  __bf16* tile = reinterpret_cast<__bf16*>(lb_smem) + wv * 64 * ORS;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int jn = 0; jn < 2; ++jn)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const floatx4 f = {acc[i][jn][4 * g], acc[i][jn][4 * g + 1], acc[i][jn][4 * g + 2], acc[i][jn][4 * g + 3]};
-        *reinterpret_cast<bf16x4*>(&tile[(i * 32 + l32) * ORS + jn * 32 + 8 * g + 4 * hh]) =
-            __builtin_convertvector(f, bf16x4);
-      }
-  __syncthreads();
-  for (int c = lane; c < 64 * 8; c += 64) {
-    const int r = c >> 3, ch = c & 7;
-    const int m = m0 + wm + r, n = n0 + wn + ch * 8;
-    if (m < M && n < ncols)
-      *reinterpret_cast<bf16x8*>(dx + (long)o_row[wm + r] * ldx + n) = *reinterpret_cast<const bf16x8*>(&tile[r * ORS + ch * 8]);
-  }
-}
-
+// ------------------------------------------------------------------------------ input side (fp32)
 __global__ void __launch_bounds__(256)
 linear_bwd_input_f32_kernel(const float* __restrict__ dout, const int32_t* __restrict__ dout_idx, long ldd,
                             const int32_t* __restrict__ total, const float* __restrict__ W, int m_cap, int kc, int ncols,
@@ -246,8 +89,137 @@ __device__ __forceinline__ TokenSplit token_split(int M, int splits) {
   return s;
 }
 
+// The chunk of tokens and the tile of dW a workgroup takes.  Items are numbered chunk-major and cut into 8
+// contiguous ranges, one per XCD, so the tiles that read the same rows share an L2.  At least one chunk
+// (of no rows) exists: with no live rows the result is zero.
+struct WeightItem {
+  int split, n0, k0, m_begin, m_end;
+  bool valid;
+};
+__device__ __forceinline__ WeightItem weight_item(int M, int splits, int n_tiles, int k_tiles, int live_min) {
+  const TokenSplit ts = token_split(M, splits);
+  const int tiles = n_tiles * k_tiles, items = max(ts.live, live_min) * tiles, per_xcd = (items + 7) >> 3;
+  const int xcd = blockIdx.x & 7, jx = blockIdx.x >> 3, item = xcd * per_xcd + jx;
+  WeightItem w = {};
+  w.valid = jx < per_xcd && item < items;
+  w.split = item / tiles;
+  const int tile_id = item - w.split * tiles, nt = tile_id / k_tiles;
+  w.n0 = nt * kLbT;
+  w.k0 = (tile_id - nt * k_tiles) * kLbT;
+  w.m_begin = w.split * ts.chunk;
+  w.m_end = min(M, w.m_begin + ts.chunk);
+  return w;
+}
+
+// The wave's 64 (n) x 64 (k) block leaves as 16-byte pieces of 256-byte row segments, 32 n at a time
+// through its own part of LDS; acc[i][j]: n block i, rows of the tile = k block j.
+__device__ __forceinline__ void store_weight_block(const floatx16 (&acc)[2][2], float* lds_of_wave, float* dst, int n_first,
+                                                   int k_first, int n_out, int K, int lane) {
+  constexpr int ORS = 64 + 4;
+  const int l32 = lane & 31, hh = lane >> 5;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    float* tile = lds_of_wave;                         // (LDS operations of a wave complete in order)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const floatx4 f = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+        *reinterpret_cast<floatx4*>(&tile[l32 * ORS + j * 32 + 8 * g + 4 * hh]) = f;
+      }
+#pragma unroll
+    for (int c = lane; c < 32 * 16; c += 64) {
+      const int r = c >> 4, ch = c & 15, n = n_first + i * 32 + r, k = k_first + ch * 4;
+      if (n < n_out && k < K)
+        *reinterpret_cast<floatx4*>(dst + (long)n * K + k) = *reinterpret_cast<const floatx4*>(&tile[r * ORS + ch * 4]);
+    }
+  }
+}
+
+// part_w[split][n][k] = sum over the chunk's rows j of g_j[n] x_j[k]; part_b[split][n] = sum g_j[n] (one
+// more MFMA per 16 rows against a vector of ones, in the workgroups of the first k tile).  Both operands
+// have the contraction (the tokens) down their rows and come through the ring of gemm_async.h, rows of
+// zeros past the chunk's end.  kGather: rows of g / x are named by index arrays (null: in order), read one
+// step ahead of the loads that use them.  12544 rows, 2304 x 768, with the
+// reduction: gathered 97 -> 80 us, in order 68 us; 98 rows of 384 x 1152: 9.8 -> 6.2 us.
+template <bool kGather>
+__global__ void __launch_bounds__(kLbThreads) __attribute__((amdgpu_waves_per_eu(2)))
+weight_gemm_kernel(const __bf16* __restrict__ dout, const int32_t* __restrict__ dout_idx, long ldd,
+                   const __bf16* __restrict__ x, const int32_t* __restrict__ x_idx, const int32_t* __restrict__ total,
+                   int m_cap, int K, int n_out, int splits, int n_tiles, int k_tiles, float* __restrict__ part_w,
+                   float* __restrict__ part_b) {
+  constexpr int STAGES = 2;
+  using P = DeepPieces<kLbT, kLbThreads>;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lb_smem[];
+  __bf16* lds = reinterpret_cast<__bf16*>(lb_smem);
+  const int M = total != nullptr ? min(total[0], m_cap) : m_cap;
+  const WeightItem w = weight_item(M, splits, n_tiles, k_tiles, 1);
+  if (!w.valid) return;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
+  const int wn = (wv >> 1) * 64, wk = (wv & 1) * 64;
+  const bool do_bias = part_b != nullptr && w.k0 == 0 && wk == 0;
+  const __bf16* zeros = reinterpret_cast<const __bf16*>(gemm_zeros);
+
+  // columns past the matrix edge fetch a valid column (never stored)
+  const int col = P::col(tid);
+  const __bf16* gcol = dout + (w.n0 + col < n_out ? w.n0 + col : w.n0);
+  const __bf16* xcol = x + (w.k0 + col < K ? w.k0 + col : w.k0);
+  int gi[P::kCount], xi[P::kCount];                  // row indices of the next step to be issued
+  auto index = [&](int t) {
+    if (!kGather) return;
+#pragma unroll
+    for (int u = 0; u < P::kCount; ++u) {
+      const int m = min(w.m_begin + t * kGaK + P::row0(tid) + u * P::kRowStep, w.m_end - 1);
+      gi[u] = dout_idx != nullptr ? dout_idx[m] : m;
+      xi[u] = x_idx != nullptr ? x_idx[m] : m;
+    }
+  };
+  const int rows = w.m_end - w.m_begin, nk = rows > 0 ? (rows + kGaK - 1) / kGaK : 0;
+  auto next_g = [&](int u, int t) {
+    const int r = t * kGaK + P::row0(tid) + u * P::kRowStep;
+    const __bf16* p = gcol + (long)(kGather ? gi[u] : w.m_begin + r) * ldd;
+    return r < rows ? p : zeros;
+  };
+  auto next_x = [&](int u, int t) {
+    const int r = t * kGaK + P::row0(tid) + u * P::kRowStep;
+    const __bf16* p = xcol + (long)(kGather ? xi[u] : w.m_begin + r) * K;
+    if (u == P::kCount - 1 && t + 1 < nk) index(t + 1);      // (the last address of step t has been formed)
+    return r < rows ? p : zeros;
+  };
+  floatx16 acc[2][2], accb[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      accb[i][r] = 0.f;
+      acc[i][0][r] = 0.f;
+      acc[i][1][r] = 0.f;
+    }
+  const __bf16 one = static_cast<__bf16>(1.0f);
+  const bf16x8 ones = {one, one, one, one, one, one, one, one};
+  if (nk > 0) index(0);
+  gemm_async_loop<kLbT * kGaK, kLbT * kGaK, P::kCount, P::kCount, STAGES, kLbThreads, 2, 2>(
+      lds, nk, next_g, next_x, [&](const __bf16* tile, int i, int kk) { return deep_frag<kLbT>(tile, kk, wn + i * 32, lane); },
+      [&](const __bf16* tile, int j, int kk) { return deep_frag<kLbT>(tile, kk, wk + j * 32, lane); }, acc,
+      [&](const bf16x8 (&g)[2]) {
+        if (do_bias) {
+          accb[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, g[0], accb[0], 0, 0, 0);
+          accb[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, g[1], accb[1], 0, 0, 0);
+        }
+      });
+  static_assert((size_t)4 * 32 * 68 * sizeof(float) <= kLbGemmLds, "output staging fits in the operand stages");
+  store_weight_block(acc, reinterpret_cast<float*>(lb_smem) + wv * 32 * 68, part_w + (long)w.split * n_out * K, w.n0 + wn,
+                     w.k0 + wk, n_out, K, lane);
+  if (do_bias && hh == 0) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int n = w.n0 + wn + i * 32 + l32;
+      if (n < n_out) part_b[(long)w.split * n_out + n] = accb[i][0];   // every row of the tile holds the column sums
+    }
+  }
+}
+
 // part_w[split][n][k] = sum over the chunk's rows j of g_j[n] r_j[k]; part_b[split][n] = sum g_j[n]
-template <bool kScale>
 __global__ void __launch_bounds__(kLbThreads)
 linear_bwd_weight_bf16_kernel(const __bf16* __restrict__ dout, const int32_t* __restrict__ dout_idx, long ldd,
                               const __bf16* __restrict__ x, const int32_t* __restrict__ x_idx,
@@ -304,7 +276,7 @@ linear_bwd_weight_bf16_kernel(const __bf16* __restrict__ dout, const int32_t* __
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
       bf16x8 xv = d.x[u];
-      if (kScale) xv = float_to_bf16x8(bf16x8_to_float(xv) * d.sc[u]);   // the gated row, rounded to bf16
+      xv = float_to_bf16x8(bf16x8_to_float(xv) * d.sc[u]);   // the gated row, rounded to bf16
       *reinterpret_cast<bf16x8*>(&Gs[buf][lds_off + u * 16 * RS]) = d.ok[u] ? d.g[u] : zero_bf16x8();
       *reinterpret_cast<bf16x8*>(&Xs[buf][lds_off + u * 16 * RS]) = d.ok[u] ? xv : zero_bf16x8();
     }
@@ -363,7 +335,7 @@ linear_bwd_weight_bf16_kernel(const __bf16* __restrict__ dout, const int32_t* __
       xi[u] = x_idx != nullptr ? x_idx[m] : m;
     }
 #pragma unroll
-    for (int u = 0; u < NF; ++u) sv[u] = kScale ? gate_scores[xi[u]] : 0.f;
+    for (int u = 0; u < NF; ++u) sv[u] = gate_scores[xi[u]];
 #pragma unroll
     for (int u = 0; u < NF; ++u) {
       const int r = tid + u * kLbThreads;
@@ -371,7 +343,7 @@ linear_bwd_weight_bf16_kernel(const __bf16* __restrict__ dout, const int32_t* __
       if (r < steps * BK) {
         g_src[r] = valid ? gi[u] : -1;
         x_src[r] = valid ? xi[u] : 0;
-        x_scale[r] = valid ? (kScale ? sigmoidf_dev(sv[u]) : 1.f) : 0.f;
+        x_scale[r] = valid ? sigmoidf_dev(sv[u]) : 0.f;
       }
     }
     __syncthreads();
@@ -477,15 +449,17 @@ linear_bwd_weight_f32_kernel(const float* __restrict__ dout, const int32_t* __re
   }
 }
 
-// Number of token chunks of the weight-side kernel: (chunk, tile) workgroups for about three per
-// compute unit (two are resident at a time), at most 16 chunks (the partial tiles are written
-// and read once per chunk), chunks of at least 256 rows at full capacity.  The option gemm_splits
-// overrides it (tuning aid).
+// Number of token chunks of the weight-side kernel: (chunk, tile) workgroups for two per compute unit (what
+// is resident at a time), at most 16 chunks (every chunk's partial tiles are written and read once), chunks
+// of at least 256 rows at full capacity, and one chunk (no partial tiles, no second launch) up to 2048
+// rows: at half of them live its 16 steps take as long as 3 steps and the second launch.  The option
+// gemm_splits overrides it (tuning aid).
 static int weight_splits(int M_cap, int K, int N_out) {
   const int env = options().gemm_splits;
   if (env > 0) return env;
   const long tiles = (long)((N_out + kLbT - 1) / kLbT) * ((K + kLbT - 1) / kLbT);
-  long s = (768 + tiles - 1) / tiles;
+  if (M_cap <= 2048) return 1;
+  long s = 512 / tiles;
   const long by_rows = M_cap / 256 > 0 ? M_cap / 256 : 1;
   if (s > by_rows) s = by_rows;
   if (s > 16) s = 16;
@@ -523,16 +497,21 @@ extern "C" int spa_linear_packed_bwd_input(const void* dout, const int32_t* dout
               "%s: K, N_out and the row strides must be multiples of 8 for bf16", fn);
   SPA_REQUIRE(aligned16(dout) && aligned16(W) && aligned16(dx), SPA_ERR_INVALID_ARG,
               "%s: dout / W / dx not 16-byte aligned", fn);
-  const int m_tiles = (M_cap + kLbT - 1) / kLbT, n_tiles = (K + kLbT - 1) / kLbT;
-  SPA_REQUIRE((long)m_tiles * n_tiles + 8 < 2147483647L / 2, SPA_ERR_INVALID_ARG, "%s: too many tiles", fn);
-  const unsigned grid = (unsigned)((long)((m_tiles + 7) / 8) * 8 * n_tiles);
-  const hipError_t attr = hipFuncSetAttribute((const void*)linear_bwd_input_bf16_kernel,
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLbInputLds);
-  SPA_REQUIRE(attr == hipSuccess, SPA_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, kLbInputLds);
-  hipLaunchKernelGGL(linear_bwd_input_bf16_kernel, dim3(grid), dim3(kLbThreads), kLbInputLds, st, (const __bf16*)dout,
-                     dout_idx, (long)dout_row_stride, total, (const __bf16*)W, M_cap, N_out, K, (__bf16*)dx,
-                     (long)dx_row_stride, dx_idx, inv_pos, (long)rows, n_tiles);
-  return check_launch(fn);
+  GemmArgs args = {};
+  args.a = (const __bf16*)dout;
+  args.a_idx = dout_idx;
+  args.lda = dout_row_stride;
+  args.total = total;
+  args.m_cap = M_cap;
+  args.kc = N_out;
+  args.ncols = K;
+  args.w = (const __bf16*)W;
+  args.out = (__bf16*)dx;
+  args.ldo = dx_row_stride;
+  args.o_idx = dx_idx;
+  args.inv_pos = inv_pos;
+  args.zrows = rows;
+  return launch_gemm_rows(fn, args, true, st);
 }
 
 extern "C" size_t spa_linear_bwd_weight_workspace_bytes(int M_cap, int K, int N_out, int dtype) {
@@ -576,17 +555,29 @@ extern "C" int spa_linear_packed_bwd_weight(const void* dout, const int32_t* dou
   const unsigned grid = (unsigned)(((items + 7) / 8) * 8);
   float* part_w = static_cast<float*>(workspace);
   float* part_b = part_w + (size_t)splits * N_out * K;
-#define SPA_LBW(S_)                                                                                              \
-  do {                                                                                                           \
-    const hipError_t attr = hipFuncSetAttribute((const void*)linear_bwd_weight_bf16_kernel<S_>,                  \
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLbWeightLds);  \
-    SPA_REQUIRE(attr == hipSuccess, SPA_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, kLbWeightLds);       \
-    hipLaunchKernelGGL((linear_bwd_weight_bf16_kernel<S_>), dim3(grid), dim3(kLbThreads), kLbWeightLds, st,      \
-                       (const __bf16*)dout, dout_idx, (long)dout_row_stride, (const __bf16*)x, x_idx, gate_scores, \
-                       total, M_cap, K, N_out, splits, n_tiles, k_tiles, part_w, part_b);                        \
-  } while (0)
-  if (gate_scores != nullptr) SPA_LBW(true); else SPA_LBW(false);
-#undef SPA_LBW
+  if (gate_scores != nullptr) {
+    const hipError_t attr = hipFuncSetAttribute((const void*)linear_bwd_weight_bf16_kernel,
+                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLbWeightLds);
+    SPA_REQUIRE(attr == hipSuccess, SPA_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, kLbWeightLds);
+    hipLaunchKernelGGL(linear_bwd_weight_bf16_kernel, dim3(grid), dim3(kLbThreads), kLbWeightLds, st, (const __bf16*)dout,
+                       dout_idx, (long)dout_row_stride, (const __bf16*)x, x_idx, gate_scores, total, M_cap, K, N_out, splits,
+                       n_tiles, k_tiles, part_w, part_b);
+  } else {
+    // one chunk: the tiles are the result; more: partial tiles that the second kernel adds
+    float* pw = splits == 1 ? dW : part_w;
+    float* pb = splits == 1 ? dbias : part_b;
+    const bool gather = dout_idx != nullptr || x_idx != nullptr;
+    const void* kernel = gather ? (const void*)weight_gemm_kernel<true> : (const void*)weight_gemm_kernel<false>;
+    const hipError_t attr = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLbGemmLds);
+    SPA_REQUIRE(attr == hipSuccess, SPA_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, kLbGemmLds);
+#define SPA_WG(G_)                                                                                               \
+  hipLaunchKernelGGL((weight_gemm_kernel<G_>), dim3(grid), dim3(kLbThreads), kLbGemmLds, st, (const __bf16*)dout, \
+                     dout_idx, (long)dout_row_stride, (const __bf16*)x, x_idx, total, M_cap, K, N_out, splits, n_tiles, \
+                     k_tiles, pw, pb)
+    if (gather) SPA_WG(true); else SPA_WG(false);
+#undef SPA_WG
+    if (splits == 1) return check_launch(fn);
+  }
   const int rc = check_launch(fn);
   if (rc != SPA_OK) return rc;
   const long nk = (long)N_out * K;

@@ -278,17 +278,16 @@ class TrainPass(_Pass):
 
 
 class BlockPass(_Pass):
-    """One SPA attention block with its projections (Section 3.2), six launches:
+    """One SPA attention block with its projections (Section 3.2), five launches:
 
       gate_select(x) -> pack (indices only) -> QKV projection of the selected, gated tokens
-      (gather and Sigmoid(s) scaling folded into the GEMM's operand load) -> packed attention
-      -> output projection on the packed rows -> scatter back as a residual on x (unselected tokens keep x unchanged).
+      (gather and Sigmoid(s) scaling folded into the GEMM) -> packed attention -> output projection
+      on the packed rows, scattered back as a residual on x (unselected tokens keep x unchanged).
 
     Only selected tokens are ever projected, which is where the method saves its FLOPs.
 
-    in_place=True: five launches.  The output projection scatters its rows straight into the
-    residual stream x (x[token] += projection), so there is no scatter launch and no copy of the
-    bypassing tokens; run() then returns x itself."""
+    in_place=True: the output projection adds its rows into the residual stream x itself
+    (x[token] += projection), with no copy of the bypassing tokens; run() then returns x."""
 
     def __init__(self, B: int, N: int, C: int, H: int, dtype: str, tau: float = 0.5, bias: float = 0.0,
                  in_place: bool = False):
@@ -304,7 +303,6 @@ class BlockPass(_Pass):
         self.total = torch.zeros(1, dtype=torch.int32, **dv)
         self.packed_qkv = torch.zeros(cap, 3 * C, dtype=td, **dv)
         self.attn = torch.zeros(cap, C, dtype=td, **dv)
-        self.proj = torch.zeros(cap, C, dtype=td, **dv)
         self.y = torch.empty(B, N, C, dtype=td, **dv)
 
     def stages(self, x, w, W_qkv, b_qkv, W_o, b_o) -> List[Tuple[str, Callable[[], None]]]:
@@ -323,9 +321,8 @@ class BlockPass(_Pass):
             ("out_projection_scatter", spa.spa_linear_packed_scatter(self.attn, self.total, W_o, b_o, self.gather_idx,
                                                                      x, x, prepare=True)),
         ] if self.in_place else [
-            ("out_projection", spa.spa_linear_packed(self.attn, None, None, self.total, W_o, b_o, self.proj,
-                                                     prepare=True)),
-            ("unpack", spa.spa_unpack(self.proj, self.inv_pos, x, self.y, prepare=True)),
+            ("out_projection_unpack", spa.spa_linear_packed_unpack(self.attn, self.total, W_o, b_o, self.gather_idx,
+                                                                   self.inv_pos, x, self.y, prepare=True)),
         ])
 
     def run(self, x, w, W_qkv, b_qkv, W_o, b_o):
@@ -335,17 +332,17 @@ class BlockPass(_Pass):
 
 class BlockTrainPass(_Pass):
     """Forward + backward of one SPA attention block WITH its projections (Section 3.2) and the
-    selection loss (Section 3.3), twelve launches:
+    selection loss (Section 3.3), eleven calls:
 
-      fwd: gate_select(x) -> pack (indices only) -> QKV projection of the selected, gated tokens
-           -> packed attention -> output projection of the packed rows -> scatter back as a
-           residual on x (y[token] = x[token] + projection, bypassing tokens y = x; x stays
-           intact for the backward pass)
+      fwd: gate_select(x) -> pack (indices and the gated rows, which the weight side of the backward
+           reads) -> QKV projection of the selected, gated tokens -> packed attention -> output
+           projection of the packed rows, scattered back as a residual on x (y[token] = x[token] +
+           projection, bypassing tokens y = x; x stays intact for the backward pass)
       bwd: (dy at token positions) -> input side and weight side of the output projection (dy
            gathered inside the GEMMs) -> attention backward on the packed rows -> input side of
            the QKV projection, scattering d_rg to token positions with the unselected rows
-           cleared, and its weight side (x gathered and gate-scaled inside the GEMM) -> gate
-           backward with the selection loss.
+           cleared, and its weight side (on the packed gated rows) -> gate backward with the
+           selection loss.
     Results: dW_qkv, db_qkv, dW_o, db_o, dw, db (fp32), loss, and dx = the gradient that reaches x
     through the gate and the gated representation; the residual path adds dy itself to it, which
     is left to the caller (it is the upstream gradient, unchanged).
@@ -372,10 +369,10 @@ class BlockTrainPass(_Pass):
         self.gather_idx = torch.zeros(cap, dtype=torch.int32, **dv)
         self.inv_pos = torch.zeros(cap, dtype=torch.int32, **dv)
         self.total = torch.zeros(1, dtype=torch.int32, **dv)
+        self.packed_rg = torch.zeros(cap, C, dtype=td, **dv)
         self.packed_qkv = torch.zeros(cap, 3 * C, dtype=td, **dv)
         self.attn = torch.zeros(cap, C, dtype=td, **dv)
         self.lse = torch.zeros(H, cap, **f32)
-        self.proj = torch.zeros(cap, C, dtype=td, **dv)
         self.y = torch.empty(B, N, C, dtype=td, **dv)
         self.d_attn = torch.zeros(cap, C, dtype=td, **dv)
         self.d_qkv = torch.zeros(cap, 3 * C, dtype=td, **dv)
@@ -399,7 +396,7 @@ class BlockTrainPass(_Pass):
         def weight_side():
             return (spa.spa_linear_packed_bwd_weight(dy2, self.gather_idx, self.attn, None, None, self.total, cap,
                                                      self.dW_o, self.db_o, self.ws_o, prepare=True),
-                    spa.spa_linear_packed_bwd_weight(dp, None, x, self.gather_idx, self.scores, self.total, cap,
+                    spa.spa_linear_packed_bwd_weight(dp, None, self.packed_rg, None, None, self.total, cap,
                                                      self.dW_qkv, self.db_qkv, self.ws_qkv, prepare=True))
 
         if self.overlap:
@@ -417,15 +414,14 @@ class BlockTrainPass(_Pass):
         return [
             ("gate_select", spa.spa_gate_select(x, w, self.bias, None, self.tau, self.scores, self.mask, None,
                                                 prepare=True)),
-            ("pack_indices", spa.spa_pack(None, self.mask, None, None, 0, None, self.cu_seqlens, self.gather_idx,
-                                          self.inv_pos, self.total, prepare=True)),
+            ("pack_rg", spa.spa_pack(x, self.mask, None, self.scores, 0, self.packed_rg, self.cu_seqlens,
+                                     self.gather_idx, self.inv_pos, self.total, prepare=True)),
             ("qkv_projection", spa.spa_linear_packed(x, self.gather_idx, self.scores, self.total, W_qkv, b_qkv, p,
                                                      prepare=True)),
             ("packed_attention", spa.spa_packed_attention(p[:, :C], p[:, C:2 * C], p[:, 2 * C:], self.cu_seqlens, B, N,
                                                           H, Dh, self.attn, self.lse, prepare=True)),
-            ("out_projection", spa.spa_linear_packed(self.attn, None, None, self.total, W_o, b_o, self.proj,
-                                                     prepare=True)),
-            ("unpack", spa.spa_unpack(self.proj, self.inv_pos, x, self.y, prepare=True)),
+            ("out_projection_unpack", spa.spa_linear_packed_unpack(self.attn, self.total, W_o, b_o, self.gather_idx,
+                                                                   self.inv_pos, x, self.y, prepare=True)),
             ("out_projection_bwd_weight", w_o),
             ("out_projection_bwd_input", spa.spa_linear_packed_bwd_input(dy2, self.gather_idx, self.total, W_o, cap,
                                                                          None, None, self.d_attn, prepare=True)),

@@ -67,6 +67,7 @@ _SIGNATURES = {
     "spa_ceiling_mfma": (c_double, [_P, c_int, c_int, _P]),
     "spa_linear_packed": (c_int, [_P, _P, _P, _P, _P, _P, c_int, c_int, c_int, c_int, _P, c_int64, _P]),
     "spa_linear_packed_scatter": (c_int, [_P, _P, _P, _P, c_int, c_int, c_int, c_int, _P, _P, _P, c_int64, _P]),
+    "spa_linear_packed_unpack": (c_int, [_P, _P, _P, _P, c_int, c_int, c_int, c_int, _P, _P, c_int64, _P, _P, _P]),
     "spa_linear_packed_bwd_input": (c_int, [_P, _P, c_int64, _P, _P, c_int, c_int, c_int, c_int, _P, _P, c_int64, _P,
                                             c_int64, _P]),
     "spa_linear_bwd_weight_workspace_bytes": (c_size_t, [c_int, c_int, c_int, c_int]),
@@ -563,6 +564,26 @@ def spa_linear_packed_scatter(x, total, W, bias, scatter_idx, residual, y, prepa
     return _dispatch(lib.spa_linear_packed_scatter,
                      (_ptr(x), _ptr(total), _ptr(W), _ptr(bias), x.shape[0], K, N_out, code, _ptr(scatter_idx),
                       _ptr(residual), _ptr(y), N_out, _stream(),), _keep, prepare)
+
+
+def spa_linear_packed_unpack(x, total, W, bias, gather_idx, inv_pos, residual, y, prepare=False):
+    """y = residual + (projection of the packed rows x, scattered through gather_idx); rows without a packed
+    row (inv_pos < 0) copy the residual.  residual, y [*, N_out] of one shape."""
+    fn = "spa_linear_packed_unpack"
+    K, N_out = x.shape[-1], W.shape[0]
+    rows = y.numel() // N_out
+    if y.shape[-1] != N_out or residual.shape != y.shape:
+        raise ValueError("y and residual must be [..., N_out]")
+    code = _features(fn, x=x, W=W, bias=bias, residual=residual, y=y)
+    _typed(fn, torch.int32, gather_idx=gather_idx, inv_pos=inv_pos, total=total)
+    if W.shape[1] != K:
+        raise ValueError(f"{fn}: W must be [N_out, K = {K}], got {tuple(W.shape)}")
+    _holds(fn, bias=(bias, N_out), gather_idx=(gather_idx, min(x.shape[0], rows)), inv_pos=(inv_pos, rows), total=(total, 1))
+    _keep = (x, total, W, bias, gather_idx, inv_pos, residual, y,)
+    _contig(*_keep)
+    return _dispatch(lib.spa_linear_packed_unpack,
+                     (_ptr(x), _ptr(total), _ptr(W), _ptr(bias), x.shape[0], K, N_out, code, _ptr(gather_idx),
+                      _ptr(inv_pos), rows, _ptr(residual), _ptr(y), _stream(),), _keep, prepare)
 
 
 def spa_linear_packed_bwd_input(dout, dout_idx, total, W, M_cap, dx_idx, inv_pos, dx, prepare=False):
