@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <type_traits>
 
 #include "attn_tiles.h"
 #include "spa_common.h"
@@ -486,61 +487,86 @@ attn_bwd_dvec_kernel(const __bf16* __restrict__ out, const __bf16* __restrict__ 
 }
 
 // ------------------------------------------------- dQ, dK, dV in one kernel (short segments)
-// One workgroup per (image, head); wave j owns the segment's keys 32j .. 32j+31 (K_j, V_j as
-// register operands, dK_j / dV_j in its accumulators).  Q and dO of the whole segment sit in
-// LDS, so every operand is read from memory once and S, dP are computed once (5 GEMM shapes).
-// In round r wave j works on query tile t = (j + r) mod nw: S = Q_t K_j^T, dP = dO_t V_j^T,
-// P, dS; dV_j^T += dO_t^T P, dK_j^T += Q_t^T dS; dS goes through a wave-private LDS tile to
-// come back transposed as the B operand of dQ_t^T += K_j^T dS^T, whose fp32 accumulator tile
-// lives in LDS and is read-modify-written by exactly one wave per round (a barrier between
-// rounds).  Tile t therefore receives its nw contributions in the fixed order j = t, t-1, ...:
-// no atomics, run-to-run bit-stable.
-// Dynamic LDS, rows = 32 * nw:  Q [rows][DH+8] | dO [rows][DH+8] | dQ accumulators [nw] tiles
-// of DH*32 fp32 in register layout | dS tiles [nw][32][40] bf16 | lse*log2(e) [rows] | D [rows].
+// One workgroup per (image, head), one wave per 32 tokens of the longest segment; wave j owns the
+// segment's tokens 32j .. 32j+31, first as keys, then as queries.
+//   keys:    Q and dO of the segment in LDS; S = Q_t K_j^T (a lane holds 16 queries of ONE key), then
+//            dV_j^T += dO_t^T P and, with dP = dO_t V_j^T, dK_j^T += Q_t^T dS over the query tiles t;
+//   queries: K and V of the segment in the same LDS; S^T = K_t Q_j^T, dP^T = V_t dO_j^T (16 keys of one
+//            query in a lane), dQ_j^T += K_t^T dS^T over the key tiles t.
+// S (and at head dim 64 P, see kOnePass) is computed again instead of exchanged: no dS tiles, no dQ
+// accumulators in LDS, no barrier inside either half, so the waves of a workgroup drift apart, and with
+// 65 instead of 141 KB at 196 tokens and at most 128 registers two workgroups share a unit: one loads
+// while the other multiplies.  No atomics, every sum in a fixed order: run-to-run bit-stable.
+// Measured on the ViT-B-shaped batch (64 x 196 tokens, 12 heads of 64): %MEASURED%.
+// Operand rows: packed (row0 + j), or GATED: q, k, v at token positions (row gather_idx[j]), the v row
+// multiplied by Sigmoid(score) and rounded to bf16 (r_g = Sigmoid(s) . r, as a packed r_g holds it).
+// Dynamic LDS, rows = 32 * nw:  A [rows][DH+8] (Q, then K) | B [rows][DH+8] (dO, then V) |
+// lse*log2(e) [rows] | D [rows].
 template <int DH>
-__host__ __device__ constexpr size_t bwd_fused_lds_bytes(int nw) {
-  return (size_t)nw * (2 * 32 * (DH + 8) * 2 + DH * 32 * 4 + 32 * 40 * 2 + 2 * 32 * 4);
+__host__ __device__ constexpr size_t bwd_short_lds_bytes(int nw) {
+  return (size_t)nw * (2 * 32 * (DH + 8) * 2 + 2 * 32 * 4);
 }
 
+// 8 bf16 multiplied by a row scale, rounded again
+__device__ __forceinline__ bf16x8 scale_row(bf16x8 v, float s) { return float_to_bf16x8(bf16x8_to_float(v) * s); }
+
+// The wave's transposed accumulator tile (rows = head dim, a lane = one token) as bf16 rows: the two halves
+// of the wave exchange quads so that a lane holds 8 consecutive columns of its token, 16-byte stores.
 template <int DH>
-__global__ void __launch_bounds__(512)
-attn_bwd_fused_bf16_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
-                           const __bf16* __restrict__ v, long qs, long ks, long vs,
-                           const __bf16* __restrict__ out, const __bf16* __restrict__ dout,
-                           const float* __restrict__ lse, long lse_stride, const int32_t* __restrict__ cu, int H,
-                           float scale, __bf16* __restrict__ dq, long dqs, __bf16* __restrict__ dk, long dks,
-                           __bf16* __restrict__ dv, long dvs, int B, TokenIO tok) {
-  constexpr int RS = DH + 8, KK = DH / 16, DB = DH / 32, CPR = DH / 8, SS = 40, PER = CPR / 2;
-  constexpr int ACC = DH * 32;                       // floats of one dQ accumulator tile
+__device__ __forceinline__ void store_rows(const floatx16 (&acc)[DH / 32], float scale, __bf16* row, bool ok, int hh) {
+#pragma unroll
+  for (int d = 0; d < DH / 32; ++d)
+#pragma unroll
+    for (int g = 0; g < 4; g += 2) {
+      uint32_t w[2][2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const floatx4 f = {acc[d][4 * (g + u)] * scale, acc[d][4 * (g + u) + 1] * scale, acc[d][4 * (g + u) + 2] * scale,
+                           acc[d][4 * (g + u) + 3] * scale};
+        const uintx2 p = __builtin_bit_cast(uintx2, __builtin_convertvector(f, bf16x4));
+        w[u][0] = p[0];
+        w[u][1] = p[1];
+      }
+      // lanes 32.. of the first quad <-> lanes ..31 of the second
+      const auto x0 = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
+      const auto x1 = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+      const uintx4 v = {x0[0], x1[0], x0[1], x1[1]};
+      if (ok) *reinterpret_cast<uintx4*>(row + d * 32 + 8 * g + 8 * hh) = v;
+    }
+}
+
+struct ShortBwd {
+  const __bf16 *q, *k, *v;
+  long qs, ks, vs;
+  const float* v_scores;         // GATED: score of every token
+  const __bf16 *out, *dout;      // out: packed rows
+  const float* lse;
+  long lse_stride;
+  const int32_t* cu;
+  int H, B;
+  float scale;
+  __bf16 *dq, *dk, *dv;
+  long dqs, dks, dvs;
+  TokenIO tok;
+};
+
+template <int DH, bool GATED>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
+attn_bwd_short_bf16_kernel(const ShortBwd p) {
+  constexpr int RS = DH + 8, KK = DH / 16, DB = DH / 32, CPR = DH / 8, PER = CPR / 2;
+  constexpr bool kOnePass = DH == 32;                // dV and dK in one walk (at 64 their accumulators and operands need 150 registers)
   extern __shared__ __attribute__((aligned(16))) unsigned char bwd_smem[];
   __shared__ int s_pick;
   const int threads = blockDim.x, nw = threads >> 6, rows_cap = 32 * nw;
-  __bf16* Qs = reinterpret_cast<__bf16*>(bwd_smem);
-  __bf16* Gs = Qs + rows_cap * RS;
-  float* dqacc = reinterpret_cast<float*>(Gs + rows_cap * RS);
-  __bf16* scr = reinterpret_cast<__bf16*>(dqacc + nw * ACC);
-  float* lse2s = reinterpret_cast<float*>(scr + nw * 32 * SS);
+  __bf16* As = reinterpret_cast<__bf16*>(bwd_smem);
+  __bf16* Bs = As + rows_cap * RS;
+  float* lse2s = reinterpret_cast<float*>(Bs + rows_cap * RS);
   float* Ds = lse2s + rows_cap;
 
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
-  const int h = blockIdx.x % H, rank = blockIdx.x / H;
-  const bool at_tokens = tok.gather_idx != nullptr;
-  // zero this head's columns of the unselected rows of this workgroup's share; every thread
-  // runs it as its last step, so nothing it computes with waits behind these stores
-  auto zero_unselected = [&]() {
-    if (!at_tokens) return;
-    const long per = (tok.rows + B - 1) / B, i0 = rank * per, i1 = min(tok.rows, i0 + per);
-    const bf16x8 z = zero_bf16x8();
-    for (long i = i0 * CPR + tid; i < i1 * CPR; i += threads) {
-      const long row = i / CPR;
-      const int c = (int)(i % CPR);
-      if (tok.inv_pos[row] < 0) {
-        *reinterpret_cast<bf16x8*>(dq + row * dqs + h * DH + c * 8) = z;
-        *reinterpret_cast<bf16x8*>(dk + row * dks + h * DH + c * 8) = z;
-        *reinterpret_cast<bf16x8*>(dv + row * dvs + h * DH + c * 8) = z;
-      }
-    }
-  };
+  const int H = p.H, B = p.B, h = blockIdx.x % H, rank = blockIdx.x / H;
+  const int32_t* cu = p.cu;
+  const bool at_tokens = p.tok.gather_idx != nullptr;
   // heaviest image first (work per segment grows like n^2)
   int img = rank, start = 0, len = 0;
   if (B > 1 && B <= kWave) {                         // every wave ranks on its own: no LDS, no barrier
@@ -549,8 +575,8 @@ attn_bwd_fused_bf16_kernel(const __bf16* __restrict__ q, const __bf16* __restric
     start = rs.row0;
     len = rs.len;
   } else {
-    if (B > 1 && B <= 512 && B * (int)sizeof(int) <= nw * 32 * SS * 2) {     // the ranking borrows the dS tiles
-      int* s_len = reinterpret_cast<int*>(scr);
+    if (B > 1 && B <= 512) {                         // the ranking borrows the operand rows
+      int* s_len = reinterpret_cast<int*>(bwd_smem);
       for (int b = tid; b < B; b += threads) s_len[b] = cu[b + 1] - cu[b];
       __syncthreads();
       for (int b = tid; b < B; b += threads) {
@@ -571,196 +597,212 @@ attn_bwd_fused_bf16_kernel(const __bf16* __restrict__ q, const __bf16* __restric
   }
   const long row0 = start;
   const int n = min(len, rows_cap);
-  if (n <= 0) {
-    zero_unselected();
-    return;
-  }
-  const int nws = (n + 31) >> 5;                     // waves with keys = query tiles = rounds
-  const long C = (long)H * DH;
-  const float scale_log2 = scale * kLog2e;
+  if (n > 0) {
+    const int nws = (n + 31) >> 5;                   // waves with tokens = tiles
+    const long C = (long)H * DH;
+    const float scale_log2 = p.scale * kLog2e;
+    const int32_t* gi = at_tokens ? p.tok.gather_idx + row0 : nullptr;
+    auto token_row = [&](int r) { return at_tokens ? (long)gi[r] : row0 + r; };   // where dO and the gradients live
+    auto src_row = [&](int r) { return GATED ? (long)gi[r] : row0 + r; };         // where q, k, v live
 
-  // ---- stage Q, dO (every thread PER chunks of each), D_i = <dO_i, O_i>, lse_i; wave j: K_j, V_j
-  bf16x8 qreg[PER], greg[PER], oreg[PER], kreg[PER], vf[KK];
-  float lreg[PER];
+    // ---- Q, dO into LDS (every thread PER chunks of each), D_i = <dO_i, O_i>, lse_i; wave j: K_j, V_j
+    {
+      bf16x8 qreg[PER], greg[PER], oreg[PER];
+      float lreg[PER];
 #pragma unroll
-  for (int t = 0; t < PER; ++t) {
-    const int i = tid + t * threads, r = i / CPR, c = i % CPR;
-    qreg[t] = zero_bf16x8(); greg[t] = zero_bf16x8(); oreg[t] = zero_bf16x8();
-    lreg[t] = INFINITY;                              // rows past the segment: probability 0
-    if (r < n) {
-      const long grow = at_tokens ? (long)tok.gather_idx[row0 + r] : row0 + r;
-      qreg[t] = *reinterpret_cast<const bf16x8*>(q + (row0 + r) * qs + h * DH + c * 8);
-      greg[t] = *reinterpret_cast<const bf16x8*>(dout + grow * C + h * DH + c * 8);
-      oreg[t] = *reinterpret_cast<const bf16x8*>(out + (row0 + r) * C + h * DH + c * 8);
-      if (c == 0) lreg[t] = lse[h * lse_stride + row0 + r] * kLog2e;
+      for (int t = 0; t < PER; ++t) {
+        const int i = tid + t * threads, r = i / CPR, c = i % CPR;
+        qreg[t] = zero_bf16x8(); greg[t] = zero_bf16x8(); oreg[t] = zero_bf16x8();
+        lreg[t] = INFINITY;                          // rows past the segment: probability 0
+        if (r < n) {
+          qreg[t] = *reinterpret_cast<const bf16x8*>(p.q + src_row(r) * p.qs + h * DH + c * 8);
+          greg[t] = *reinterpret_cast<const bf16x8*>(p.dout + token_row(r) * C + h * DH + c * 8);
+          oreg[t] = *reinterpret_cast<const bf16x8*>(p.out + (row0 + r) * C + h * DH + c * 8);
+          if (c == 0) lreg[t] = p.lse[h * p.lse_stride + row0 + r] * kLog2e;
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < PER; ++t) {
+        const int i = tid + t * threads, r = i / CPR, c = i % CPR;
+        *reinterpret_cast<bf16x8*>(&As[r * RS + c * 8]) = qreg[t];
+        *reinterpret_cast<bf16x8*>(&Bs[r * RS + c * 8]) = greg[t];
+        const floatx8 gf = bf16x8_to_float(greg[t]), of = bf16x8_to_float(oreg[t]);
+        float d = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) d = fmaf(of[e], gf[e], d);
+#pragma unroll
+        for (int o = 1; o < CPR; o <<= 1) d += __shfl_xor(d, o, kWave);     // the CPR chunks of a row: adjacent lanes
+        if (c == 0) {
+          Ds[r] = d;
+          lse2s[r] = lreg[t];
+        }
+      }
     }
-  }
-  const int ki = wv * 32 + l32;
-  const bool k_ok = ki < n;
+    const bool live = wv < nws;
+    const int ti = wv * 32 + l32;                    // this lane's token, as key and as query
+    const bool t_ok = ti < n;
+    const long my_src = t_ok ? src_row(ti) : 0, my_row = t_ok ? token_row(ti) : 0;
+    const float my_gate = GATED && t_ok ? sigmoidf_dev(p.v_scores[my_src]) : 1.f;
+    bf16x8 kf[KK], vf[KK];
 #pragma unroll
-  for (int t = 0; t < PER; ++t) {
-    const int i = lane + t * 64, r = i / CPR, c = i % CPR;
-    kreg[t] = zero_bf16x8();
-    if (wv * 32 + r < n) kreg[t] = *reinterpret_cast<const bf16x8*>(k + (row0 + wv * 32 + r) * ks + h * DH + c * 8);
-  }
-#pragma unroll
-  for (int kk = 0; kk < KK; ++kk) {
-    vf[kk] = zero_bf16x8();
-    if (k_ok) vf[kk] = *reinterpret_cast<const bf16x8*>(v + (row0 + ki) * vs + h * DH + kk * 16 + hh * 8);
-  }
-#pragma unroll
-  for (int t = 0; t < PER; ++t) {
-    const int i = tid + t * threads, r = i / CPR, c = i % CPR;
-    *reinterpret_cast<bf16x8*>(&Qs[r * RS + c * 8]) = qreg[t];
-    *reinterpret_cast<bf16x8*>(&Gs[r * RS + c * 8]) = greg[t];
-    const floatx8 gf = bf16x8_to_float(greg[t]), of = bf16x8_to_float(oreg[t]);
-    float d = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) d = fmaf(of[e], gf[e], d);
-#pragma unroll
-    for (int o = 1; o < CPR; o <<= 1) d += __shfl_xor(d, o, kWave);     // the CPR chunks of a row: adjacent lanes
-    if (c == 0) {
-      Ds[r] = d;
-      lse2s[r] = lreg[t];
+    for (int kk = 0; kk < KK; ++kk) {
+      kf[kk] = zero_bf16x8();
+      vf[kk] = zero_bf16x8();
+      if (t_ok) {
+        const int col = h * DH + kk * 16 + hh * 8;
+        kf[kk] = *reinterpret_cast<const bf16x8*>(p.k + my_src * p.ks + col);
+        vf[kk] = *reinterpret_cast<const bf16x8*>(p.v + my_src * p.vs + col);
+        if (GATED) vf[kk] = scale_row(vf[kk], my_gate);
+      }
     }
-  }
-  // K_j: through this wave's (still unused) dQ accumulator tile to get both operand forms
-  bf16x8 kf[KK], ktf[DB][2];
-  {
-    __bf16* kt = reinterpret_cast<__bf16*>(dqacc + wv * ACC);
-#pragma unroll
-    for (int t = 0; t < PER; ++t) {
-      const int i = lane + t * 64, r = i / CPR, c = i % CPR;
-      *reinterpret_cast<bf16x8*>(&kt[r * RS + c * 8]) = kreg[t];
-    }
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) kf[kk] = *reinterpret_cast<const bf16x8*>(&kt[l32 * RS + kk * 16 + hh * 8]);
-#pragma unroll
-    for (int d = 0; d < DB; ++d)
-#pragma unroll
-      for (int mf = 0; mf < 2; ++mf) ktf[d][mf] = transposed_frag_rowmajor<RS>(kt, d, 0, mf, lane);   // K_j^T
-  }
-  floatx16 dka[DB], dva[DB];
-#pragma unroll
-  for (int d = 0; d < DB; ++d)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { dka[d][r] = 0.f; dva[d][r] = 0.f; }
-  __syncthreads();
+    __syncthreads();
 
-  const bool live = wv < nws;
-  const bool ragged = live && wv == nws - 1 && (n & 31) != 0;      // this wave's key block has empty lanes
-  __bf16* sc = scr + wv * 32 * SS;
-  for (int r = 0; r < nws; ++r) {
+    // ---- as keys
     if (live) {
-      int t = wv + r;
-      if (t >= nws) t -= nws;
-      const __bf16* Qt = Qs + t * 32 * RS;
-      const __bf16* Gt = Gs + t * 32 * RS;
-      floatx16 s, dp;
+      floatx16 dka[DB], dva[DB];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
+      for (int d = 0; d < DB; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { dka[d][r] = 0.f; dva[d][r] = 0.f; }
+      auto walk = [&](auto want_dv, auto want_dk) {
+        constexpr bool kDv = decltype(want_dv)::value, kDk = decltype(want_dk)::value;
+        for (int t = 0; t < nws; ++t) {
+          const __bf16* Qt = As + t * 32 * RS;
+          const __bf16* Gt = Bs + t * 32 * RS;
+          floatx16 s, dp;
+#pragma unroll
+          for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
+#pragma unroll
+          for (int kk = 0; kk < KK; ++kk) {
+            const bf16x8 qa = *reinterpret_cast<const bf16x8*>(&Qt[l32 * RS + kk * 16 + hh * 8]);
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kf[kk], s, 0, 0, 0);
+            if (kDk) {
+              const bf16x8 ga = *reinterpret_cast<const bf16x8*>(&Gt[l32 * RS + kk * 16 + hh * 8]);
+              dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga, vf[kk], dp, 0, 0, 0);
+            }
+          }
+#pragma unroll
+          for (int mf = 0; mf < 2; ++mf) {
+            floatx8 fp, fd;
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+              const int at = t * 32 + 16 * mf + 8 * g + 4 * hh;
+              const floatx4 l4 = *reinterpret_cast<const floatx4*>(&lse2s[at]);
+              const floatx4 d4 = *reinterpret_cast<const floatx4*>(&Ds[at]);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const int i = 8 * mf + 4 * g + e;
+                fp[4 * g + e] = __builtin_amdgcn_exp2f(fmaf(s[i], scale_log2, -l4[e]));
+                if (kDk) fd[4 * g + e] = fp[4 * g + e] * (dp[i] - d4[e]);
+              }
+            }
+            if (kDv) {
+              const bf16x8 pb = float_to_bf16x8(fp);
+#pragma unroll
+              for (int d = 0; d < DB; ++d)
+                dva[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(transposed_frag_rowmajor<RS>(Gt, d, 0, mf, lane), pb, dva[d], 0, 0, 0);
+            }
+            if (kDk) {
+              const bf16x8 dsb = float_to_bf16x8(fd);
+#pragma unroll
+              for (int d = 0; d < DB; ++d)
+                dka[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(transposed_frag_rowmajor<RS>(Qt, d, 0, mf, lane), dsb, dka[d], 0, 0, 0);
+            }
+          }
+        }
+      };
+      if constexpr (kOnePass) {
+        walk(std::true_type{}, std::true_type{});
+        store_rows<DH>(dva, 1.0f, p.dv + my_row * p.dvs + h * DH, t_ok, hh);
+      } else {
+        walk(std::true_type{}, std::false_type{});
+        store_rows<DH>(dva, 1.0f, p.dv + my_row * p.dvs + h * DH, t_ok, hh);
+        walk(std::false_type{}, std::true_type{});
+      }
+      store_rows<DH>(dka, p.scale, p.dk + my_row * p.dks + h * DH, t_ok, hh);
+    }
+
+    // ---- as queries: Q_j, dO_j from LDS to registers, then K and V rows take their place
+    bf16x8 qf[KK], gf[KK], kreg[PER], vreg[PER];
+    float D = 0.f, lse2 = INFINITY;                  // (queries past the segment: probability 0)
+    if (live) {
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) {
-        const bf16x8 qa = *reinterpret_cast<const bf16x8*>(&Qt[l32 * RS + kk * 16 + hh * 8]);
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kf[kk], s, 0, 0, 0);
-        const bf16x8 ga = *reinterpret_cast<const bf16x8*>(&Gt[l32 * RS + kk * 16 + hh * 8]);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga, vf[kk], dp, 0, 0, 0);
+        qf[kk] = *reinterpret_cast<const bf16x8*>(&As[ti * RS + kk * 16 + hh * 8]);
+        gf[kk] = *reinterpret_cast<const bf16x8*>(&Bs[ti * RS + kk * 16 + hh * 8]);
       }
-      float p[16], ds[16];
+      D = Ds[ti];
+      lse2 = lse2s[ti];
+    }
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const floatx4 l4 = *reinterpret_cast<const floatx4*>(&lse2s[t * 32 + 8 * g + 4 * hh]);
-        const floatx4 d4 = *reinterpret_cast<const floatx4*>(&Ds[t * 32 + 8 * g + 4 * hh]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int i = 4 * g + e;
-          p[i] = __builtin_amdgcn_exp2f(fmaf(s[i], scale_log2, -l4[e]));
-          ds[i] = p[i] * (dp[i] - d4[e]);
-        }
+    for (int t = 0; t < PER; ++t) {
+      const int i = tid + t * threads, r = i / CPR, c = i % CPR;
+      kreg[t] = zero_bf16x8();
+      vreg[t] = zero_bf16x8();
+      if (r < n) {
+        const long src = src_row(r);
+        kreg[t] = *reinterpret_cast<const bf16x8*>(p.k + src * p.ks + h * DH + c * 8);
+        vreg[t] = *reinterpret_cast<const bf16x8*>(p.v + src * p.vs + h * DH + c * 8);
+        if (GATED) vreg[t] = scale_row(vreg[t], sigmoidf_dev(p.v_scores[src]));
       }
-      if (ragged) {                                  // keys past the segment must not reach dQ
+    }
+    __syncthreads();                                 // every wave is done with Q and dO
 #pragma unroll
-        for (int i = 0; i < 16; ++i) ds[i] = k_ok ? ds[i] : 0.f;
-      }
-#pragma unroll
-      for (int mf = 0; mf < 2; ++mf) {
-        floatx8 fp, fd;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) { fp[j] = p[8 * mf + j]; fd[j] = ds[8 * mf + j]; }
-        const bf16x8 pb = float_to_bf16x8(fp), dsb = float_to_bf16x8(fd);
-#pragma unroll
-        for (int d = 0; d < DB; ++d) {
-          const bf16x8 ga = transposed_frag_rowmajor<RS>(Gt, d, 0, mf, lane);   // dO_t^T
-          dva[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga, pb, dva[d], 0, 0, 0);
-          const bf16x8 qa = transposed_frag_rowmajor<RS>(Qt, d, 0, mf, lane);   // Q_t^T
-          dka[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, dsb, dka[d], 0, 0, 0);
-        }
-        // dS tile, [key][query]: registers 8mf .. 8mf+7 are queries 16mf + 4hh + {0..3, 8..11}
-        *reinterpret_cast<bf16x4*>(&sc[l32 * SS + 16 * mf + 4 * hh]) = __builtin_shufflevector(dsb, dsb, 0, 1, 2, 3);
-        *reinterpret_cast<bf16x4*>(&sc[l32 * SS + 16 * mf + 8 + 4 * hh]) = __builtin_shufflevector(dsb, dsb, 4, 5, 6, 7);
-      }
-      // dQ_t^T += K_j^T dS^T on the tile's fp32 accumulators in LDS
-      floatx4* at = reinterpret_cast<floatx4*>(dqacc + t * ACC);
+    for (int t = 0; t < PER; ++t) {
+      const int i = tid + t * threads, r = i / CPR, c = i % CPR;
+      *reinterpret_cast<bf16x8*>(&As[r * RS + c * 8]) = kreg[t];
+      *reinterpret_cast<bf16x8*>(&Bs[r * RS + c * 8]) = vreg[t];
+    }
+    __syncthreads();
+    if (live) {
       floatx16 acc[DB];
 #pragma unroll
       for (int d = 0; d < DB; ++d)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          floatx4 a4 = {0.f, 0.f, 0.f, 0.f};
-          if (r > 0) a4 = at[(d * 4 + g) * 64 + lane];
+        for (int r = 0; r < 16; ++r) acc[d][r] = 0.f;
+      for (int t = 0; t < nws; ++t) {
+        const __bf16* Kt = As + t * 32 * RS;
+        const __bf16* Vt = Bs + t * 32 * RS;
+        floatx16 s, dp;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc[d][4 * g + e] = a4[e];
+        for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+          const bf16x8 ka = *reinterpret_cast<const bf16x8*>(&Kt[l32 * RS + kk * 16 + hh * 8]);
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[kk], s, 0, 0, 0);
+          const bf16x8 va = *reinterpret_cast<const bf16x8*>(&Vt[l32 * RS + kk * 16 + hh * 8]);
+          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, gf[kk], dp, 0, 0, 0);
         }
+        // (keys past the segment have zero rows in K, so their dS reaches nothing)
 #pragma unroll
-      for (int mf = 0; mf < 2; ++mf) {
-        const bf16x8 dst = transposed_frag_rowmajor<SS>(sc, 0, 0, mf, lane);     // dS^T: lane = query
+        for (int mf = 0; mf < 2; ++mf) {
+          floatx8 f;
 #pragma unroll
-        for (int d = 0; d < DB; ++d) acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktf[d][mf], dst, acc[d], 0, 0, 0);
+          for (int j = 0; j < 8; ++j)
+            f[j] = __builtin_amdgcn_exp2f(fmaf(s[8 * mf + j], scale_log2, -lse2)) * (dp[8 * mf + j] - D);
+          const bf16x8 dsb = float_to_bf16x8(f);
+#pragma unroll
+          for (int d = 0; d < DB; ++d)
+            acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(transposed_frag_rowmajor<RS>(Kt, d, 0, mf, lane), dsb, acc[d], 0, 0, 0);
+        }
       }
-#pragma unroll
-      for (int d = 0; d < DB; ++d)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const floatx4 a4 = {acc[d][4 * g], acc[d][4 * g + 1], acc[d][4 * g + 2], acc[d][4 * g + 3]};
-          at[(d * 4 + g) * 64 + lane] = a4;
-        }
+      store_rows<DH>(acc, p.scale, p.dq + my_row * p.dqs + h * DH, t_ok, hh);
     }
-    __syncthreads();
   }
-  if (!live) {
-    zero_unselected();
-    return;
-  }
-  // gradients: dK_j, dV_j from the registers, dQ tile j from LDS; parked as bf16 rows, written whole
-  __bf16* ktile = Qs + wv * 32 * RS;
-  __bf16* vtile = Gs + wv * 32 * RS;
-  park_tile<DH, RS>(dka, scale, ktile, l32, hh);
-  park_tile<DH, RS>(dva, 1.0f, vtile, l32, hh);
-  floatx16 acc[DB];
-  const floatx4* at = reinterpret_cast<const floatx4*>(dqacc + wv * ACC);
-#pragma unroll
-  for (int d = 0; d < DB; ++d)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const floatx4 a4 = at[(d * 4 + g) * 64 + lane];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[d][4 * g + e] = a4[e];
-    }
-  __bf16* qtile = reinterpret_cast<__bf16*>(dqacc + wv * ACC);
-  // (LDS operations of one wave complete in order: the reads above precede the stores below)
-  park_tile<DH, RS>(acc, scale, qtile, l32, hh);
-  const int nrows = min(32, n - wv * 32);
+  // this head's columns of the unselected rows of this workgroup's share (last: nothing waits for them)
   if (at_tokens) {
-    const int32_t* ri = tok.gather_idx + row0 + wv * 32;
-    flush_tile_rows<DH, RS>(qtile, dq + h * DH, dqs, nrows, lane, ri);
-    flush_tile_rows<DH, RS>(ktile, dk + h * DH, dks, nrows, lane, ri);
-    flush_tile_rows<DH, RS>(vtile, dv + h * DH, dvs, nrows, lane, ri);
-  } else {
-    flush_tile<DH, RS>(qtile, dq + (row0 + wv * 32) * dqs + h * DH, dqs, nrows, lane);
-    flush_tile<DH, RS>(ktile, dk + (row0 + wv * 32) * dks + h * DH, dks, nrows, lane);
-    flush_tile<DH, RS>(vtile, dv + (row0 + wv * 32) * dvs + h * DH, dvs, nrows, lane);
+    const long per = (p.tok.rows + B - 1) / B, i0 = rank * per, i1 = min(p.tok.rows, i0 + per);
+    const bf16x8 z = zero_bf16x8();
+    for (long i = i0 * CPR + tid; i < i1 * CPR; i += threads) {
+      const long row = i / CPR;
+      const int c = (int)(i % CPR);
+      if (p.tok.inv_pos[row] < 0) {
+        *reinterpret_cast<bf16x8*>(p.dq + row * p.dqs + h * DH + c * 8) = z;
+        *reinterpret_cast<bf16x8*>(p.dk + row * p.dks + h * DH + c * 8) = z;
+        *reinterpret_cast<bf16x8*>(p.dv + row * p.dvs + h * DH + c * 8) = z;
+      }
+    }
   }
-  zero_unselected();
 }
 
 // ------------------------------------------------------------------------------- fp32
@@ -895,7 +937,8 @@ static int attention_bwd_common(const char* fn, const void* q, const void* k, co
                                 const float* lse, const int32_t* cu_seqlens, int B, int max_seqlen, int H, int Dh,
                                 int dtype, float softmax_scale, void* dq, void* dk, void* dv,
                                 int64_t dq_row_stride, int64_t dk_row_stride, int64_t dv_row_stride,
-                                void* workspace, size_t workspace_bytes, TokenIO tok, void* stream) {
+                                void* workspace, size_t workspace_bytes, TokenIO tok, void* stream,
+                                const float* v_scores = nullptr) {
   const bool at_tokens = tok.gather_idx != nullptr;
   SPA_REQUIRE(q && k && v && out && dout && lse && cu_seqlens && dq && dk && dv, SPA_ERR_INVALID_ARG,
               "%s: null pointer", fn);
@@ -951,20 +994,24 @@ static int attention_bwd_common(const char* fn, const void* q, const void* k, co
     if (one_kernel) {
       const int nw = (max_seqlen + 31) / 32;
       SPA_REQUIRE((long)B * H < 2147483647L, SPA_ERR_INVALID_ARG, "%s: B*H must be < 2^31", fn);
-#define SPA_BWD_FUSED(D)                                                                                        \
+      const ShortBwd args = {(const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_row_stride, (long)k_row_stride,
+                             (long)v_row_stride, v_scores, (const __bf16*)out, (const __bf16*)dout, lse, ls, cu_seqlens, H, B,
+                             scale, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, (long)dq_row_stride, (long)dk_row_stride,
+                             (long)dv_row_stride, tok};
+#define SPA_BWD_SHORT(D, G)                                                                                     \
   do {                                                                                                          \
-    const size_t smem = bwd_fused_lds_bytes<D>(nw);                                                             \
-    const hipError_t attr = hipFuncSetAttribute((const void*)attn_bwd_fused_bf16_kernel<D>,                     \
+    const size_t smem = bwd_short_lds_bytes<D>(nw);                                                             \
+    const hipError_t attr = hipFuncSetAttribute((const void*)attn_bwd_short_bf16_kernel<D, G>,                  \
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);         \
     SPA_REQUIRE(attr == hipSuccess, SPA_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, smem);              \
-    hipLaunchKernelGGL((attn_bwd_fused_bf16_kernel<D>), dim3((unsigned)(B * H)), dim3(64 * nw), smem, st,       \
-                       (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_row_stride,                \
-                       (long)k_row_stride, (long)v_row_stride, (const __bf16*)out, (const __bf16*)dout, lse, ls, \
-                       cu_seqlens, H, scale, (__bf16*)dq, (long)dq_row_stride, (__bf16*)dk, (long)dk_row_stride, \
-                       (__bf16*)dv, (long)dv_row_stride, B, tok);                                               \
+    hipLaunchKernelGGL((attn_bwd_short_bf16_kernel<D, G>), dim3((unsigned)(B * H)), dim3(64 * nw), smem, st, args); \
   } while (0)
-      if (Dh == 32) SPA_BWD_FUSED(32); else SPA_BWD_FUSED(64);
-#undef SPA_BWD_FUSED
+      if (v_scores != nullptr) {
+        if (Dh == 32) SPA_BWD_SHORT(32, true); else SPA_BWD_SHORT(64, true);
+      } else {
+        if (Dh == 32) SPA_BWD_SHORT(32, false); else SPA_BWD_SHORT(64, false);
+      }
+#undef SPA_BWD_SHORT
       return check_launch(fn);
     }
     const int rows_per_block = short_seg ? 32 : 128;
