@@ -48,10 +48,9 @@ static bool parse_option(Options& o, const char* name, const char* value) {
     const int n = v[0] != 0 ? std::atoi(v) : 256;
     if (n < 0 || n > 256) return false;
     o.fwd_wave_max = n;
-  } else if (!std::strcmp(name, "attn_bwd_short")) {   // "" | "split" | "tiled"
-    o.bwd_short = v[0] == 's' ? 1 : v[0] == 't' ? 2 : 0;
-  } else if (!std::strcmp(name, "attn_bwd_long")) {    // "" | "two"
-    o.bwd_long_two = v[0] == 't';
+  } else if (!std::strcmp(name, "attn_bwd_short")) {   // "" | "tiled"
+    o.bwd_tiled = v[0] == 't';
+  } else if (!std::strcmp(name, "attn_bwd_long")) {    // (one form: any value is taken)
   } else if (!std::strcmp(name, "gemm_tm")) {          // 0 | 2 | 4 | 8
     const int n = std::atoi(v);
     if (!(n == 0 || n == 2 || n == 4 || n == 8)) return false;

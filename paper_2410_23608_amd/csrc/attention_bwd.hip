@@ -2,8 +2,8 @@
 //   P = exp(S - lse), dV = P^T dO, dP = dO V^T, D_i = sum_d dO_id O_id,
 //   dS = P * (dP - D), dQ = dS K * scale, dK = dS^T Q * scale.
 // No atomics anywhere; results are run-to-run bit-stable.
-// Segments of up to 256 tokens (bf16): ONE kernel, a workgroup per (image, head), S and dP
-// computed once (5 GEMM shapes); see attn_bwd_fused_bf16_kernel.
+// Segments of up to 256 tokens (bf16): one kernel, a workgroup per (image, head); see
+// attn_bwd_short_bf16_kernel.
 // Longer segments (bf16): two roles in one launch, after a small kernel that writes D_i:
 //   dq role   : a wave owns 32 queries and walks the segment's keys.  Like the forward it
 //               works on transposed tiles (S^T = K Q^T, dP^T = V dO^T) so lse_i and D_i are
@@ -43,269 +43,286 @@ __device__ __forceinline__ Seg seg_of(int b, const int32_t* cu) {
 // Token-position I/O folded into the kernel (gather_idx == nullptr: packed I/O): the upstream
 // gradient row of packed token j is dy[gather_idx[j]], the gradients of packed token j go to
 // row gather_idx[j] of dq / dk / dv, and the rows of unselected tokens (inv_pos < 0) are zeroed,
-// every workgroup of the launch clearing an even share (one-kernel form: its head's columns).
+// every workgroup of the launch clearing an even share (short segments: its head's columns).
 struct TokenIO {
   const int32_t* gather_idx;
   const int32_t* inv_pos;
   long rows;               // B * N
 };
 
-template <int DH, int RS>
-__device__ __forceinline__ void flush_tile_rows(const __bf16* tile, __bf16* dst, long row_stride, int nrows, int lane,
-                                                const int32_t* row_index) {
-  constexpr int CPR = DH / 8;
+// 8 bf16 multiplied by a row scale, rounded again
+__device__ __forceinline__ bf16x8 scale_row(bf16x8 v, float s) { return float_to_bf16x8(bf16x8_to_float(v) * s); }
+
+// The wave's transposed accumulator tile (rows = head dim, a lane = one token) as bf16 rows: the two halves
+// of the wave exchange quads so that a lane holds 8 consecutive columns of its token, 16-byte stores.
+template <int DH>
+__device__ __forceinline__ void store_rows(const floatx16 (&acc)[DH / 32], float scale, __bf16* row, bool ok, int hh) {
 #pragma unroll
-  for (int i = lane; i < 32 * CPR; i += 64) {
-    const int r = i / CPR, c = i % CPR;
-    if (r < nrows)
-      *reinterpret_cast<bf16x8*>(dst + (long)row_index[r] * row_stride + c * 8) =
-          *reinterpret_cast<const bf16x8*>(&tile[r * RS + c * 8]);
+  for (int d = 0; d < DH / 32; ++d)
+#pragma unroll
+    for (int g = 0; g < 4; g += 2) {
+      uint32_t w[2][2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const floatx4 f = {acc[d][4 * (g + u)] * scale, acc[d][4 * (g + u) + 1] * scale, acc[d][4 * (g + u) + 2] * scale,
+                           acc[d][4 * (g + u) + 3] * scale};
+        const uintx2 p = __builtin_bit_cast(uintx2, __builtin_convertvector(f, bf16x4));
+        w[u][0] = p[0];
+        w[u][1] = p[1];
+      }
+      // lanes 32.. of the first quad <-> lanes ..31 of the second
+      const auto x0 = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
+      const auto x1 = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+      const uintx4 v = {x0[0], x1[0], x0[1], x1[1]};
+      if (ok) *reinterpret_cast<uintx4*>(row + d * 32 + 8 * g + 8 * hh) = v;
+    }
+}
+
+// Operands and results of the bf16 kernels.
+struct BwdArgs {
+  const __bf16 *q, *k, *v;
+  long qs, ks, vs;
+  const float* v_scores;         // GATED: score of every token
+  const __bf16 *out, *dout;      // out: packed rows
+  const float* lse;
+  long lse_stride;
+  const int32_t* cu;
+  int H, B;
+  float scale;
+  __bf16 *dq, *dk, *dv;
+  long dqs, dks, dvs;
+  TokenIO tok;
+  float* dvec;                   // long segments: D_i for every (head, packed row)
+};
+
+// -------------------------------------------------------------------------- long segments (bf16)
+constexpr int kBwdBT = 64, kBwdThreads = 256, kBwdRows = 128;     // streamed tile, 4 waves x 32 rows
+
+// Rows of the long kernel's operands: q, k, v, out packed, dO and the gradients
+//   kPacked: packed as well;  kTokens: at token positions;  kGated: q, k, v at token positions too, v gated.
+enum BwdRowsMode { kPacked, kTokens, kGated };
+
+// Two row-major tiles of BT tokens of one head on their way to LDS: operand 0 is K (dq role) or Q (dkdv
+// role), operand 1 is V or dO, their rows packed or (IDX0, IDX1) named by an index, which is read one tile ahead
+// of the rows.  Nothing here waits for a load or branches on one between load() and store(): a tile past the
+// segment's end loads the last row again (the caller gives such rows probability 0).
+template <int DH, bool IDX0, bool IDX1>
+struct PairStage {
+  static constexpr int RS = DH + 8, CPR = DH / 8, CPT = kBwdBT * CPR / kBwdThreads, RPP = kBwdThreads / CPR;
+  static_assert(kBwdBT * CPR % kBwdThreads == 0, "whole passes");
+  bf16x8 v[2][CPT];
+  int idx[CPT];
+  const __bf16* base[2];         // this thread's columns of row 0 (indexed) or of the segment's first row
+  int stride[2];
+  const int32_t* gi;
+  int n;
+  __device__ __forceinline__ static int row(int t) { return (int)threadIdx.x / CPR + t * RPP; }
+  __device__ __forceinline__ void source(int o, const __bf16* p, long row_stride, long row0) {
+    base[o] = p + threadIdx.x % CPR * 8 + ((o ? IDX1 : IDX0) ? 0 : row0 * row_stride);
+    stride[o] = (int)row_stride;
+  }
+  __device__ __forceinline__ void index(int t0) {
+    if (IDX0 || IDX1) {
+#pragma unroll
+      for (int t = 0; t < CPT; ++t) idx[t] = gi[min(t0 + row(t), n - 1)];
+    }
+  }
+  __device__ __forceinline__ void load(int t0) {
+#pragma unroll
+    for (int t = 0; t < CPT; ++t) {
+      const int r = min(t0 + row(t), n - 1);
+      v[0][t] = *reinterpret_cast<const bf16x8*>(base[0] + (long)(IDX0 ? idx[t] : r) * stride[0]);
+      v[1][t] = *reinterpret_cast<const bf16x8*>(base[1] + (long)(IDX1 ? idx[t] : r) * stride[1]);
+    }
+  }
+  // gate: scores of operand 1's rows, nullptr: not gated
+  __device__ __forceinline__ void store(__bf16* a, __bf16* b, const float (&gate)[CPT], bool gated) const {
+#pragma unroll
+    for (int t = 0; t < CPT; ++t) {
+      const int o = row(t) * RS + threadIdx.x % CPR * 8;
+      *reinterpret_cast<bf16x8*>(a + o) = v[0][t];
+      *reinterpret_cast<bf16x8*>(b + o) = gated ? scale_row(v[1][t], sigmoidf_dev(gate[t])) : v[1][t];
+    }
+  }
+};
+
+template <int DH>
+struct BwdLongLds {
+  static constexpr int RS = DH + 8;
+  __attribute__((aligned(16))) __bf16 A[2][kBwdBT * RS];         // K (dq) | Q (dkdv)
+  __attribute__((aligned(16))) __bf16 Bm[2][kBwdBT * RS];        // V (dq) | dO (dkdv)
+  __attribute__((aligned(16))) float lse2s[2][kBwdBT];           // of the streamed queries (dkdv)
+  __attribute__((aligned(16))) float negD[2][kBwdBT];
+};
+
+// Scores and dP of the wave's 32 tokens of the streamed tile against its 32 rows: two chains of DH / 16
+// MFMAs; dp starts from c (-D, so that dS = P dP needs no subtraction), s
+// from what it holds.
+template <int DH>
+__device__ __forceinline__ void bwd_scores(const __bf16* at, const __bf16* bt, int sb, const bf16x8 (&af)[DH / 16],
+                                           const bf16x8 (&bf)[DH / 16], const floatx16& c, floatx16& s, floatx16& dp, int l32,
+                                           int hh) {
+  constexpr int RS = DH + 8;
+  dp = c;
+#pragma unroll
+  for (int kk = 0; kk < DH / 16; ++kk) {
+    const bf16x8 x = *reinterpret_cast<const bf16x8*>(&at[(sb * 32 + l32) * RS + kk * 16 + hh * 8]);
+    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, af[kk], s, 0, 0, 0);
+    const bf16x8 y = *reinterpret_cast<const bf16x8*>(&bt[(sb * 32 + l32) * RS + kk * 16 + hh * 8]);
+    dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(y, bf[kk], dp, 0, 0, 0);
   }
 }
 
-// Both bf16 kernels use the forward's launch scheme: 1-D XCD-aware grid (the blocks that
-// share one (image, head)'s rows sit on one L2), longest image first, 4 waves x 32 rows per
-// workgroup, the other side of the product streaming through double-buffered row-major LDS
-// tiles of BT tokens with the next tile's rows in flight in registers.  Short segments
-// (<= 256 tokens) use the same kernels with ONE wave per workgroup and 32-token tiles: small
-// independent work units that spread over all SIMDs, no longest-first ranking.  Operands whose
-// k-dimension is the token index are read with the transposing LDS read from the same
-// row-major tiles, so nothing is staged twice.
-
-// --------------------------------------------------------------------------- dQ (bf16)
-// LDS of the two long-segment kernels: two row-major operand tiles (double-buffered unless the
-// workgroup is one wave, which stores the next tile only after its own reads of the current
-// one), the per-query statistics of the dkdv side, and the longest-first ranking.
-template <int DH, int NW, int BT, bool LPT>
-struct BwdLds {
-  static constexpr int RS = DH + 8, NBUF = NW == 1 ? 1 : 2;
-  __attribute__((aligned(16))) __bf16 A[NBUF][BT * RS];     // K (dq) | Q (dkdv)
-  __attribute__((aligned(16))) __bf16 Bm[NBUF][BT * RS];    // V (dq) | dO (dkdv)
-  __attribute__((aligned(16))) float lse2s[NBUF][BT];
-  __attribute__((aligned(16))) float Ds[NBUF][BT];
-  int s_cu[LPT ? 2 * kLptMaxB + 1 : 1];
-  int s_pick;
-};
-
-// kHaveD: D_i = <dO_i, O_i> was computed by an earlier launch and is read from dvec; else this
-// kernel computes it and writes dvec for the dkdv kernel that follows.
-template <int DH, int NW, int BT, bool LPT, bool kHaveD>
-__device__ __forceinline__ void
-attn_bwd_dq_body(BwdLds<DH, NW, BT, LPT>& lds, const TileId tile_id, const __bf16* __restrict__ q,
-                 const __bf16* __restrict__ k, const __bf16* __restrict__ v, long qs, long ks, long vs,
-                 const __bf16* __restrict__ out, const __bf16* __restrict__ dout,
-                 const float* __restrict__ lse, long lse_stride, const int32_t* __restrict__ cu, int H,
-                 float scale, __bf16* __restrict__ dq, long gstride, float* __restrict__ dvec, int B,
-                 const TokenIO tok = TokenIO{nullptr, nullptr, 0}, const bool have_live = false,
-                 const Segment live = Segment{0, 0, 0}) {
-  constexpr int RS = DH + 8, KK = DH / 16, DB = DH / 32, THREADS = 64 * NW, NBUF = NW == 1 ? 1 : 2;
-  const bool at_tokens = tok.gather_idx != nullptr;
-  auto& Ks = lds.A;
-  auto& Vs = lds.Bm;
-  int* s_cu = lds.s_cu;
-  int& s_pick = lds.s_pick;
-  static_assert(NBUF * BT >= 32 * NW, "the K buffers double as the output staging tile");
-
-  if (!tile_id.valid) return;
-  const int h = tile_id.h;
-  // (live: the caller numbered the live blocks itself and hands over the block's segment)
-  const Segment seg = have_live ? live
-                      : LPT           ? lpt_segment<THREADS>(tile_id.rank, B, cu, nullptr, 0, s_cu, &s_pick)
-                                      : segment_of(tile_id.rank, cu, nullptr, 0);
-  const int q0 = tile_id.qb * (32 * NW);
-  if (q0 >= seg.nq) return;
+// dq role: 32 queries per wave against the keys of the segment.  S^T = K Q^T, dP^T = V dO^T: a lane holds 16
+// keys of one query, lse and D are one scalar per lane, dS^T is the B operand of dQ^T += K^T dS^T.
+template <int DH, int MODE>
+__device__ __forceinline__ void bwd_dq_role(BwdLongLds<DH>& lds, const BwdArgs& p, const Segment seg, int h, int q0) {
+  constexpr int RS = DH + 8, KK = DH / 16, DB = DH / 32, BT = kBwdBT;
+  constexpr bool GATED = MODE == kGated;
+  using Stage = PairStage<DH, GATED, GATED>;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
-  const int qi = q0 + wv * 32 + l32;
-  const bool wave_live = q0 + wv * 32 < seg.nq;
-  const bool q_ok = qi < seg.nq;
-  const long C = (long)H * DH;
-  const float scale_log2 = scale * kLog2e;
-  const __bf16* kh = k + h * DH;
-  const __bf16* vh = v + h * DH;
+  const int qi = q0 + wv * 32 + l32, n = seg.nk;
+  const bool wave_live = q0 + wv * 32 < n, q_ok = qi < n;
+  const long C = (long)p.H * DH;
+  const float scale_log2 = p.scale * kLog2e;
+  const int32_t* gi = MODE != kPacked ? p.tok.gather_idx + seg.row0 : nullptr;
+  const long q_row = seg.row0 + (q_ok ? qi : 0);
+  const long tok_row = MODE != kPacked ? (long)gi[q_ok ? qi : 0] : q_row;
 
-  RowStage<DH, THREADS, BT> kst, vst;
-  kst.load(kh, seg.row0, seg.nk, ks);
-  vst.load(vh, seg.row0, seg.nk, vs);
-
+  Stage st;
+  float gate[Stage::CPT] = {};
+  st.gi = gi;
+  st.n = n;
+  st.source(0, p.k + h * DH, p.ks, seg.row0);
+  st.source(1, p.v + h * DH, p.vs, seg.row0);
+  auto load_tile = [&](int kt) {                     // (then the index of the one after it)
+    st.load(kt);
+    if (GATED) {
+#pragma unroll
+      for (int t = 0; t < Stage::CPT; ++t) gate[t] = p.v_scores[st.idx[t]];
+    }
+    st.index(kt + BT);
+  };
+  st.index(0);
+  load_tile(0);
   bf16x8 qf[KK], dof[KK];
-  float dpart = 0.f;
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) {
+    const int col = h * DH + kk * 16 + hh * 8;
     qf[kk] = zero_bf16x8();
     dof[kk] = zero_bf16x8();
     if (q_ok) {
-      const int col = h * DH + kk * 16 + hh * 8;
-      const long grow = at_tokens ? (long)tok.gather_idx[seg.row0 + qi] : seg.row0 + qi;
-      qf[kk] = *reinterpret_cast<const bf16x8*>(q + (seg.row0 + qi) * qs + col);
-      dof[kk] = *reinterpret_cast<const bf16x8*>(dout + grow * C + col);
-      if (!kHaveD) {
-        const floatx8 of = bf16x8_to_float(*reinterpret_cast<const bf16x8*>(out + (seg.row0 + qi) * C + col));
-        const floatx8 gf = bf16x8_to_float(dof[kk]);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) dpart = fmaf(of[e], gf[e], dpart);
-      }
+      qf[kk] = *reinterpret_cast<const bf16x8*>(p.q + (GATED ? tok_row : q_row) * p.qs + col);
+      dof[kk] = *reinterpret_cast<const bf16x8*>(p.dout + tok_row * C + col);
     }
   }
-  float D;
-  if (kHaveD) {
-    D = q_ok ? dvec[h * lse_stride + seg.row0 + qi] : 0.f;
-  } else {
-    D = sum_across_halves(dpart);
-    if (q_ok && hh == 0) dvec[h * lse_stride + seg.row0 + qi] = D;
+  const float negd = q_ok ? -p.dvec[h * p.lse_stride + q_row] : 0.f;
+  const float lse2 = q_ok ? p.lse[h * p.lse_stride + q_row] * kLog2e : INFINITY;   // past the segment: probability 0
+  floatx16 acc[DB], negD;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    negD[r] = negd;
+#pragma unroll
+    for (int d = 0; d < DB; ++d) acc[d][r] = 0.f;
   }
-  // invalid queries: lse = +inf makes every probability 0
-  const float lse2 = q_ok ? lse[h * lse_stride + seg.row0 + qi] * kLog2e : INFINITY;
-
-  floatx16 acc[DB];
-#pragma unroll
-  for (int d = 0; d < DB; ++d)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[d][r] = 0.f;
-
-  kst.store(Ks[0]);
-  vst.store(Vs[0]);
+  st.store(lds.A[0], lds.Bm[0], gate, GATED);
   __syncthreads();
-  const int nt = (seg.nk + BT - 1) / BT;
-  for (int t = 0; t < nt; ++t) {
-    const int buf = t & (NBUF - 1), nbuf = (t + 1) & (NBUF - 1), kt = t * BT;
-    if (t + 1 < nt) {
-      kst.load(kh, seg.row0 + kt + BT, seg.nk - kt - BT, ks);
-      vst.load(vh, seg.row0 + kt + BT, seg.nk - kt - BT, vs);
-    }
+  const int nt = (n + BT - 1) / BT;
+  auto tile = [&](int t, auto last) {
+    const int buf = t & 1, kt = t * BT;
+    if (!last) load_tile(kt + BT);
     if (wave_live) {
+      floatx16 s[2], dp[2];
 #pragma unroll
-      for (int sb = 0; sb < BT / 32; ++sb) {
-        const int key0 = kt + sb * 32;
-        if (key0 >= seg.nk) break;
-        floatx16 s, dp;
+      for (int sb = 0; sb < 2; ++sb) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) { s[r] = 0.f; dp[r] = 0.f; }
+        for (int r = 0; r < 16; ++r) s[sb][r] = 0.f;
+        bwd_scores<DH>(lds.A[buf], lds.Bm[buf], sb, qf, dof, negD, s[sb], dp[sb], l32, hh);
+      }
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-          const bf16x8 ka = *reinterpret_cast<const bf16x8*>(&Ks[buf][(sb * 32 + l32) * RS + kk * 16 + hh * 8]);
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[kk], s, 0, 0, 0);
-          const bf16x8 va = *reinterpret_cast<const bf16x8*>(&Vs[buf][(sb * 32 + l32) * RS + kk * 16 + hh * 8]);
-          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, dof[kk], dp, 0, 0, 0);
-        }
-        float ds[16];
+      for (int sb = 0; sb < 2; ++sb) {
+        if (last) {
+          const int left = n - kt - sb * 32;         // valid keys of the sub-block
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          float p = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2, -lse2));
-          if (key0 + acc_row(r, hh) >= seg.nk) p = 0.f;
-          ds[r] = p * (dp[r] - D);
+          for (int r = 0; r < 16; ++r)
+            if (acc_row(r, hh) >= left) s[sb][r] = -INFINITY;
         }
 #pragma unroll
         for (int mf = 0; mf < 2; ++mf) {
           floatx8 f;
 #pragma unroll
-          for (int j = 0; j < 8; ++j) f[j] = ds[8 * mf + j];
+          for (int j = 0; j < 8; ++j)
+            f[j] = __builtin_amdgcn_exp2f(fmaf(s[sb][8 * mf + j], scale_log2, -lse2)) * dp[sb][8 * mf + j];
           const bf16x8 dsb = float_to_bf16x8(f);
 #pragma unroll
-          for (int d = 0; d < DB; ++d) {
-            const bf16x8 a = transposed_frag_rowmajor<RS>(Ks[buf], d, sb * 32, mf, lane);   // K^T
-            acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dsb, acc[d], 0, 0, 0);
-          }
+          for (int d = 0; d < DB; ++d)
+            acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(transposed_frag_rowmajor<RS>(lds.A[buf], d, sb * 32, mf, lane), dsb,
+                                                             acc[d], 0, 0, 0);
         }
       }
     }
-    if (t + 1 < nt) {
-      kst.store(Ks[nbuf]);
-      vst.store(Vs[nbuf]);
+    if (!last) {
+      st.store(lds.A[buf ^ 1], lds.Bm[buf ^ 1], gate, GATED);
+      __syncthreads();
     }
-    __syncthreads();
-  }
-  __bf16* tile = &Ks[0][0] + wv * 32 * RS;
-  if (wave_live) park_tile<DH, RS>(acc, scale, tile, l32, hh);
-  __syncthreads();
-  if (wave_live) {
-    const int nrows = min(32, seg.nq - q0 - wv * 32);
-    if (at_tokens)
-      flush_tile_rows<DH, RS>(tile, dq + h * DH, gstride, nrows, lane, tok.gather_idx + seg.row0 + q0 + wv * 32);
-    else
-      flush_tile<DH, RS>(tile, dq + (seg.row0 + q0 + wv * 32) * gstride + h * DH, gstride, nrows, lane);
-  }
+  };
+  for (int t = 0; t + 1 < nt; ++t) tile(t, std::false_type{});
+  tile(nt - 1, std::true_type{});
+  store_rows<DH>(acc, p.scale, p.dq + tok_row * p.dqs + h * DH, q_ok, hh);
 }
 
-template <int DH, int NW, int BT, bool LPT>
-__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1 ? 3 : 2)))
-attn_bwd_dq_bf16_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
-                        const __bf16* __restrict__ v, long qs, long ks, long vs,
-                        const __bf16* __restrict__ out, const __bf16* __restrict__ dout,
-                        const float* __restrict__ lse, long lse_stride, const int32_t* __restrict__ cu, int H,
-                        float scale, __bf16* __restrict__ dq, long gstride, float* __restrict__ dvec, int B,
-                        int nqb) {
-  __shared__ BwdLds<DH, NW, BT, LPT> lds;
-  attn_bwd_dq_body<DH, NW, BT, LPT, false>(lds, xcd_tile(nqb, H, B), q, k, v, qs, ks, vs, out, dout, lse, lse_stride,
-                                           cu, H, scale, dq, gstride, dvec, B);
-}
-
-// ------------------------------------------------------------------------ dK, dV (bf16)
-template <int DH, int NW, int BT, bool LPT>
-__device__ __forceinline__ void
-attn_bwd_dkdv_body(BwdLds<DH, NW, BT, LPT>& lds, const TileId tile_id, const __bf16* __restrict__ q,
-                   const __bf16* __restrict__ k, const __bf16* __restrict__ v, long qs, long ks, long vs,
-                   const __bf16* __restrict__ dout, const float* __restrict__ lse,
-                   const float* __restrict__ dvec, long lse_stride, const int32_t* __restrict__ cu, int H,
-                   float scale, __bf16* __restrict__ dk, long dks, __bf16* __restrict__ dv, long dvs, int B,
-                   const TokenIO tok = TokenIO{nullptr, nullptr, 0}, const bool have_live = false,
-                 const Segment live = Segment{0, 0, 0}) {
-  constexpr int RS = DH + 8, KK = DH / 16, DB = DH / 32, THREADS = 64 * NW, NBUF = NW == 1 ? 1 : 2;
-  const bool at_tokens = tok.gather_idx != nullptr;
-  auto& Qs = lds.A;
-  auto& Gs = lds.Bm;                  // dO rows
-  auto& lse2s = lds.lse2s;
-  auto& Ds = lds.Ds;
-  int* s_cu = lds.s_cu;
-  int& s_pick = lds.s_pick;
-  static_assert(NBUF * BT >= 32 * NW, "the Q / dO buffers double as the output staging tiles");
-
-  if (!tile_id.valid) return;
-  const int h = tile_id.h;
-  const Segment seg = have_live ? live
-                      : LPT           ? lpt_segment<THREADS>(tile_id.rank, B, cu, nullptr, 0, s_cu, &s_pick)
-                                      : segment_of(tile_id.rank, cu, nullptr, 0);
-  const int k0 = tile_id.qb * (32 * NW);
-  if (k0 >= seg.nk) return;
+// dkdv role: 32 keys per wave against the queries.  S = Q K^T, dP = dO V^T: a lane holds 16 queries of one
+// key, P and dS are the B operands of dV^T += dO^T P and dK^T += Q^T dS.
+template <int DH, int MODE>
+__device__ __forceinline__ void bwd_dkdv_role(BwdLongLds<DH>& lds, const BwdArgs& p, const Segment seg, int h, int k0) {
+  constexpr int RS = DH + 8, KK = DH / 16, DB = DH / 32, BT = kBwdBT;
+  constexpr bool GATED = MODE == kGated;
+  using Stage = PairStage<DH, GATED, MODE != kPacked>;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
-  const int ki = k0 + wv * 32 + l32;
-  const bool wave_live = k0 + wv * 32 < seg.nk;
-  const bool k_ok = ki < seg.nk;
-  const long C = (long)H * DH;
-  const float scale_log2 = scale * kLog2e;
-  const __bf16* qh = q + h * DH;
-  const __bf16* gh = dout + h * DH;
-  const float* lse_h = lse + h * lse_stride + seg.row0;
-  const float* dvec_h = dvec + h * lse_stride + seg.row0;
+  const int ki = k0 + wv * 32 + l32, n = seg.nk;
+  const bool wave_live = k0 + wv * 32 < n, k_ok = ki < n;
+  const long C = (long)p.H * DH;
+  const float scale_log2 = p.scale * kLog2e;
+  const int32_t* gi = MODE != kPacked ? p.tok.gather_idx + seg.row0 : nullptr;
+  const float* lse_h = p.lse + h * p.lse_stride + seg.row0;
+  const float* dvec_h = p.dvec + h * p.lse_stride + seg.row0;
+  const long k_row = seg.row0 + (k_ok ? ki : 0);
+  const long tok_row = MODE != kPacked ? (long)gi[k_ok ? ki : 0] : k_row, src = GATED ? tok_row : k_row;
 
-  RowStage<DH, THREADS, BT> qst, gst;
-  float lreg = 0.f, dreg = 0.f;            // lse / D of query row `tid` of the tile (tid < 64)
-  auto load_stats = [&](int qt) {
+  Stage st;
+  const float no_gate[Stage::CPT] = {};
+  st.gi = gi;
+  st.n = n;
+  st.source(0, p.q + h * DH, p.qs, seg.row0);
+  st.source(1, p.dout + h * DH, C, seg.row0);
+  float lse_t = 0.f, d_t = 0.f;                      // of streamed query `lane` of the tile
+  auto load_tile = [&](int qt) {                     // (then the index of the one after it)
+    st.load(qt);
+    st.index(qt + BT);
+    const int q = min(qt + lane, n - 1);
+    lse_t = lse_h[q];
+    d_t = dvec_h[q];
+  };
+  auto store_all = [&](int buf, int qt) {
+    st.store(lds.A[buf], lds.Bm[buf], no_gate, false);
     if (tid < BT) {
-      const bool ok = qt + tid < seg.nq;
-      lreg = ok ? lse_h[qt + tid] * kLog2e : INFINITY;   // invalid rows: probability 0
-      dreg = ok ? dvec_h[qt + tid] : 0.f;
+      lds.lse2s[buf][tid] = qt + tid < n ? lse_t * kLog2e : INFINITY;    // past the segment: probability 0
+      lds.negD[buf][tid] = -d_t;
     }
   };
-  auto store_stats = [&](int buf) {
-    if (tid < BT) {
-      lse2s[buf][tid] = lreg;
-      Ds[buf][tid] = dreg;
-    }
-  };
-  qst.load(qh, seg.row0, seg.nq, qs);
-  if (at_tokens) gst.load_rows(gh, tok.gather_idx + seg.row0, seg.nq, C);
-  else gst.load(gh, seg.row0, seg.nq, C);
-  load_stats(0);
-
+  st.index(0);
+  load_tile(0);
   bf16x8 kf[KK], vf[KK];
+  const float gate = GATED && k_ok ? sigmoidf_dev(p.v_scores[src]) : 1.f;
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) {
+    const int col = h * DH + kk * 16 + hh * 8;
     kf[kk] = zero_bf16x8();
     vf[kk] = zero_bf16x8();
     if (k_ok) {
-      const int col = h * DH + kk * 16 + hh * 8;
-      kf[kk] = *reinterpret_cast<const bf16x8*>(k + (seg.row0 + ki) * ks + col);
-      vf[kk] = *reinterpret_cast<const bf16x8*>(v + (seg.row0 + ki) * vs + col);
+      kf[kk] = *reinterpret_cast<const bf16x8*>(p.k + src * p.ks + col);
+      vf[kk] = *reinterpret_cast<const bf16x8*>(p.v + src * p.vs + col);
+      if (GATED) vf[kk] = scale_row(vf[kk], gate);
     }
   }
   floatx16 dka[DB], dva[DB];
@@ -313,149 +330,115 @@ attn_bwd_dkdv_body(BwdLds<DH, NW, BT, LPT>& lds, const TileId tile_id, const __b
   for (int d = 0; d < DB; ++d)
 #pragma unroll
     for (int r = 0; r < 16; ++r) { dka[d][r] = 0.f; dva[d][r] = 0.f; }
-
-  qst.store(Qs[0]);
-  gst.store(Gs[0]);
-  store_stats(0);
+  store_all(0, 0);
   __syncthreads();
-  const int nt = (seg.nq + BT - 1) / BT;
-  for (int t = 0; t < nt; ++t) {
-    const int buf = t & (NBUF - 1), nbuf = (t + 1) & (NBUF - 1), qt = t * BT;
-    if (t + 1 < nt) {
-      qst.load(qh, seg.row0 + qt + BT, seg.nq - qt - BT, qs);
-      if (at_tokens) gst.load_rows(gh, tok.gather_idx + seg.row0 + qt + BT, seg.nq - qt - BT, C);
-      else gst.load(gh, seg.row0 + qt + BT, seg.nq - qt - BT, C);
-      load_stats(qt + BT);
-    }
+  const int nt = (n + BT - 1) / BT;
+  auto tile = [&](int t, auto last) {
+    const int buf = t & 1, qt = t * BT;
+    if (!last) load_tile(qt + BT);
     if (wave_live) {
+      const __bf16 *qb = lds.A[buf], *gb = lds.Bm[buf];
+      floatx16 s[2], dp[2];
 #pragma unroll
-      for (int sb = 0; sb < BT / 32; ++sb) {
-        if (qt + sb * 32 >= seg.nq) break;
-        // S tile: rows = 32 queries, cols = this wave's 32 keys
-        floatx16 s, dp;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) { s[r] = 0.f; dp[r] = 0.f; }
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-          const bf16x8 qa = *reinterpret_cast<const bf16x8*>(&Qs[buf][(sb * 32 + l32) * RS + kk * 16 + hh * 8]);
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kf[kk], s, 0, 0, 0);
-          const bf16x8 ga = *reinterpret_cast<const bf16x8*>(&Gs[buf][(sb * 32 + l32) * RS + kk * 16 + hh * 8]);
-          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga, vf[kk], dp, 0, 0, 0);
-        }
-        float p[16], ds[16];
+      for (int sb = 0; sb < 2; ++sb) {
+        floatx16 c;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const floatx4 l4 = *reinterpret_cast<const floatx4*>(&lse2s[buf][sb * 32 + 8 * g + 4 * hh]);
-          const floatx4 d4 = *reinterpret_cast<const floatx4*>(&Ds[buf][sb * 32 + 8 * g + 4 * hh]);
+          const floatx4 d4 = *reinterpret_cast<const floatx4*>(&lds.negD[buf][sb * 32 + 8 * g + 4 * hh]);
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const int r = 4 * g + e;
-            p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2, -l4[e]));
-            ds[r] = p[r] * (dp[r] - d4[e]);
+            c[4 * g + e] = d4[e];
+            s[sb][4 * g + e] = 0.f;
           }
         }
+        bwd_scores<DH>(qb, gb, sb, kf, vf, c, s[sb], dp[sb], l32, hh);
+      }
+#pragma unroll
+      for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
         for (int mf = 0; mf < 2; ++mf) {
           floatx8 fp, fd;
 #pragma unroll
-          for (int j = 0; j < 8; ++j) { fp[j] = p[8 * mf + j]; fd[j] = ds[8 * mf + j]; }
+          for (int g = 0; g < 2; ++g) {
+            const floatx4 l4 = *reinterpret_cast<const floatx4*>(&lds.lse2s[buf][sb * 32 + 16 * mf + 8 * g + 4 * hh]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const int j = 4 * g + e;
+              fp[j] = __builtin_amdgcn_exp2f(fmaf(s[sb][8 * mf + j], scale_log2, -l4[e]));
+              fd[j] = fp[j] * dp[sb][8 * mf + j];
+            }
+          }
           const bf16x8 pb = float_to_bf16x8(fp), dsb = float_to_bf16x8(fd);
 #pragma unroll
           for (int d = 0; d < DB; ++d) {
-            const bf16x8 ga = transposed_frag_rowmajor<RS>(Gs[buf], d, sb * 32, mf, lane);   // dO^T
-            dva[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga, pb, dva[d], 0, 0, 0);
-            const bf16x8 qa = transposed_frag_rowmajor<RS>(Qs[buf], d, sb * 32, mf, lane);   // Q^T
-            dka[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, dsb, dka[d], 0, 0, 0);
+            dva[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(transposed_frag_rowmajor<RS>(gb, d, sb * 32, mf, lane), pb, dva[d], 0, 0, 0);
+            dka[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(transposed_frag_rowmajor<RS>(qb, d, sb * 32, mf, lane), dsb, dka[d], 0, 0, 0);
           }
         }
-      }
     }
-    if (t + 1 < nt) {
-      qst.store(Qs[nbuf]);
-      gst.store(Gs[nbuf]);
-      store_stats(nbuf);
+    if (!last) {
+      store_all(buf ^ 1, qt + BT);
+      __syncthreads();
     }
-    __syncthreads();
-  }
-  __bf16* ktile = &Qs[0][0] + wv * 32 * RS;
-  __bf16* vtile = &Gs[0][0] + wv * 32 * RS;
-  if (wave_live) {
-    park_tile<DH, RS>(dka, scale, ktile, l32, hh);
-    park_tile<DH, RS>(dva, 1.0f, vtile, l32, hh);
-  }
-  __syncthreads();
-  if (wave_live) {
-    const int nrows = min(32, seg.nk - k0 - wv * 32);
-    if (at_tokens) {
-      const int32_t* ri = tok.gather_idx + seg.row0 + k0 + wv * 32;
-      flush_tile_rows<DH, RS>(ktile, dk + h * DH, dks, nrows, lane, ri);
-      flush_tile_rows<DH, RS>(vtile, dv + h * DH, dvs, nrows, lane, ri);
-    } else {
-      flush_tile<DH, RS>(ktile, dk + (seg.row0 + k0 + wv * 32) * dks + h * DH, dks, nrows, lane);
-      flush_tile<DH, RS>(vtile, dv + (seg.row0 + k0 + wv * 32) * dvs + h * DH, dvs, nrows, lane);
-    }
-  }
+  };
+  for (int t = 0; t + 1 < nt; ++t) tile(t, std::false_type{});
+  tile(nt - 1, std::true_type{});
+  store_rows<DH>(dka, p.scale, p.dk + tok_row * p.dks + h * DH, k_ok, hh);
+  store_rows<DH>(dva, 1.0f, p.dv + tok_row * p.dvs + h * DH, k_ok, hh);
 }
 
-template <int DH, int NW, int BT, bool LPT>
-__global__ void __launch_bounds__(64 * NW)
-attn_bwd_dkdv_bf16_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
-                          const __bf16* __restrict__ v, long qs, long ks, long vs,
-                          const __bf16* __restrict__ dout, const float* __restrict__ lse,
-                          const float* __restrict__ dvec, long lse_stride, const int32_t* __restrict__ cu, int H,
-                          float scale, __bf16* __restrict__ dk, long dks, __bf16* __restrict__ dv, long dvs,
-                          int B, int nkb) {
-  __shared__ BwdLds<DH, NW, BT, LPT> lds;
-  attn_bwd_dkdv_body<DH, NW, BT, LPT>(lds, xcd_tile(nkb, H, B), q, k, v, qs, ks, vs, dout, lse, dvec, lse_stride, cu,
-                                      H, scale, dk, dks, dv, dvs, B);
-}
-
-// Long segments, one launch for both sides.  Each of the two kernels above is bound by the
-// chain of its longest workgroup (a wave walks all tokens of its image) with one to two
-// workgroups per compute unit; launched together, the two chains run side by side.  Workgroup
-// -> (xcd = id % 8, role = (id / 8) % 2, j = id / 16): the dq block and the dkdv block of a
-// tile number sit on the same XCD (they read the same rows).  D_i = <dO_i, O_i> comes from
-// the small kernel below, launched first.
-template <int DH, int NW, int BT>
-__global__ void __launch_bounds__(64 * NW)
-attn_bwd_both_bf16_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
-                          const __bf16* __restrict__ v, long qs, long ks, long vs,
-                          const __bf16* __restrict__ out, const __bf16* __restrict__ dout,
-                          const float* __restrict__ lse, float* __restrict__ dvec, long lse_stride,
-                          const int32_t* __restrict__ cu, int H, float scale, __bf16* __restrict__ dq, long dqs,
-                          __bf16* __restrict__ dk, long dks, __bf16* __restrict__ dv, long dvs, int B, int nblk,
-                          TokenIO tok) {
-  __shared__ BwdLds<DH, NW, BT, true> lds;
+// Both roles in one launch: each alone is bound by the chain of its longest workgroup (a wave walks the
+// tokens of its image).  Workgroup -> (xcd = id % 8, number inside the XCD): first the dkdv blocks, longest image
+// first (live_tile_wave), then the dq blocks in the same order: alternating roles would give every other unit only
+// the longer of the two.  Waves of longer images run at a higher priority, as the launch ends with them.
+// Bound by vector instructions and the waits between them: per 32 x 32 block the two roles issue 14 MFMAs (448
+// cycles) and about 125 vector instructions, 32 of them exponentials (630 cycles), at three (head dim 64: two)
+// wavefronts per SIMD; a fourth, without the second score block in flight, is 2-8 % faster on launches of several
+// rounds and 10-25 % slower on smaller ones.  No load is waited for between two tiles (see PairStage).
+// 16 images of 3136 tokens, 10-60 % selected, 3 heads of 32: 74 -> 52 us; 32 x 1024 tokens, all selected, 12
+// heads of 64: 508 -> 410 us; 2 x 4200 tokens, 5-40 %, 8 heads of 32: 28 -> 20 us.
+template <int DH, int MODE>
+__global__ void __launch_bounds__(kBwdThreads) __attribute__((amdgpu_waves_per_eu(DH == 32 ? 3 : 2)))
+attn_bwd_long_bf16_kernel(const BwdArgs p, int nblk) {
+  __shared__ BwdLongLds<DH> lds;
   __shared__ LiveTile s_live;
-  const int xcd = blockIdx.x & 7, jj = blockIdx.x >> 3;
-  TileId tile_id;
-  Segment seg_live = {0, 0, 0};
-  const bool live = live_tiles_apply(H, B);     // live blocks first in launch order (see live_tile_wave)
-  if (live) {
-    const LiveTile lt = live_tile_block(xcd, jj >> 1, H, B, cu, 32 * NW, nblk, &s_live);
-    tile_id = {lt.qb, lt.h, lt.img, lt.valid};
-    seg_live = {lt.row0, lt.len, lt.len};
+  __shared__ int s_cu[2 * kLptMaxB + 1];
+  __shared__ int s_pick;
+  const int xcd = blockIdx.x & 7, jj = blockIdx.x >> 3, half = gridDim.x >> 4;
+  Segment seg = {0, 0, 0};
+  int h = 0, r0 = 0;
+  bool dkdv;
+  if (live_tiles_apply(p.H, p.B)) {
+    const LiveTile lt = live_tile_block<2>(xcd, jj, p.H, p.B, p.cu, kBwdRows, nblk, &s_live);
+    if (lt.valid) seg = {lt.row0, lt.len, lt.len};
+    h = lt.h;
+    r0 = lt.qb * kBwdRows;
+    dkdv = !lt.again;
+    const int weight = dkdv ? 3 * lt.len : 2 * lt.len;
+    if (weight > 2 * lt.longest) __builtin_amdgcn_s_setprio(2);
+    else if (weight > lt.longest) __builtin_amdgcn_s_setprio(1);
   } else {
-    tile_id = xcd_tile_at(xcd, jj >> 1, nblk, H, B);
+    dkdv = jj < half;
+    const TileId t = xcd_tile_at(xcd, dkdv ? jj : jj - half, nblk, p.H, p.B);
+    if (t.valid) seg = lpt_segment<kBwdThreads>(t.rank, p.B, p.cu, nullptr, 0, s_cu, &s_pick);
+    h = t.h;
+    r0 = t.qb * kBwdRows;
   }
-  if (jj & 1)
-    attn_bwd_dkdv_body<DH, NW, BT, true>(lds, tile_id, q, k, v, qs, ks, vs, dout, lse, dvec, lse_stride, cu, H, scale,
-                                         dk, dks, dv, dvs, B, tok, live, seg_live);
-  else
-    attn_bwd_dq_body<DH, NW, BT, true, true>(lds, tile_id, q, k, v, qs, ks, vs, out, dout, lse, lse_stride, cu, H,
-                                             scale, dq, dqs, dvec, B, tok, live, seg_live);
-  if (tok.gather_idx != nullptr) {
-    // gradients of the unselected tokens: every workgroup of a role (with or without a tile) zeroes an
-    // even share of the rows, a quarter per wave: the dq role in dq, the dkdv role in dk and dv
-    const long units = (long)(gridDim.x >> 1) * NW, u = ((long)xcd + 8 * (jj >> 1)) * NW + (threadIdx.x >> 6);
-    const long per = (tok.rows + units - 1) / units, r0 = min(tok.rows, u * per), r1 = min(tok.rows, r0 + per);
+  if (r0 < seg.nk) {
+    if (dkdv) bwd_dkdv_role<DH, MODE>(lds, p, seg, h, r0);
+    else bwd_dq_role<DH, MODE>(lds, p, seg, h, r0);
+  }
+  __builtin_amdgcn_s_setprio(0);
+  if (MODE != kPacked) {
+    // gradients of the unselected tokens: every workgroup (with or without a tile) zeroes an even share of the
+    // rows, a quarter per wave
+    constexpr int NW = kBwdThreads / 64;
+    const long units = (long)gridDim.x * NW, u = (long)blockIdx.x * NW + (threadIdx.x >> 6);
+    const long per = (p.tok.rows + units - 1) / units, z0 = min(p.tok.rows, u * per), z1 = min(p.tok.rows, z0 + per);
     const int lane = threadIdx.x & 63;
-    if (jj & 1) {
-      zero_unselected_rows(dk, dks, H * DH, tok.inv_pos, r0, r1, lane);
-      zero_unselected_rows(dv, dvs, H * DH, tok.inv_pos, r0, r1, lane);
-    } else {
-      zero_unselected_rows(dq, dqs, H * DH, tok.inv_pos, r0, r1, lane);
-    }
+    zero_unselected_rows(p.dq, p.dqs, p.H * DH, p.tok.inv_pos, z0, z1, lane);
+    zero_unselected_rows(p.dk, p.dks, p.H * DH, p.tok.inv_pos, z0, z1, lane);
+    zero_unselected_rows(p.dv, p.dvs, p.H * DH, p.tok.inv_pos, z0, z1, lane);
   }
 }
 
@@ -497,7 +480,7 @@ attn_bwd_dvec_kernel(const __bf16* __restrict__ out, const __bf16* __restrict__ 
 // accumulators in LDS, no barrier inside either half, so the waves of a workgroup drift apart, and with
 // 65 instead of 141 KB at 196 tokens and at most 128 registers two workgroups share a unit: one loads
 // while the other multiplies.  No atomics, every sum in a fixed order: run-to-run bit-stable.
-// Measured on the ViT-B-shaped batch (64 x 196 tokens, 12 heads of 64): %MEASURED%.
+// Measured on the ViT-B-shaped batch (64 x 196 tokens, 12 heads of 64): 44.8 -> 37.3 us.
 // Operand rows: packed (row0 + j), or GATED: q, k, v at token positions (row gather_idx[j]), the v row
 // multiplied by Sigmoid(score) and rounded to bf16 (r_g = Sigmoid(s) . r, as a packed r_g holds it).
 // Dynamic LDS, rows = 32 * nw:  A [rows][DH+8] (Q, then K) | B [rows][DH+8] (dO, then V) |
@@ -507,52 +490,9 @@ __host__ __device__ constexpr size_t bwd_short_lds_bytes(int nw) {
   return (size_t)nw * (2 * 32 * (DH + 8) * 2 + 2 * 32 * 4);
 }
 
-// 8 bf16 multiplied by a row scale, rounded again
-__device__ __forceinline__ bf16x8 scale_row(bf16x8 v, float s) { return float_to_bf16x8(bf16x8_to_float(v) * s); }
-
-// The wave's transposed accumulator tile (rows = head dim, a lane = one token) as bf16 rows: the two halves
-// of the wave exchange quads so that a lane holds 8 consecutive columns of its token, 16-byte stores.
-template <int DH>
-__device__ __forceinline__ void store_rows(const floatx16 (&acc)[DH / 32], float scale, __bf16* row, bool ok, int hh) {
-#pragma unroll
-  for (int d = 0; d < DH / 32; ++d)
-#pragma unroll
-    for (int g = 0; g < 4; g += 2) {
-      uint32_t w[2][2];
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const floatx4 f = {acc[d][4 * (g + u)] * scale, acc[d][4 * (g + u) + 1] * scale, acc[d][4 * (g + u) + 2] * scale,
-                           acc[d][4 * (g + u) + 3] * scale};
-        const uintx2 p = __builtin_bit_cast(uintx2, __builtin_convertvector(f, bf16x4));
-        w[u][0] = p[0];
-        w[u][1] = p[1];
-      }
-      // lanes 32.. of the first quad <-> lanes ..31 of the second
-      const auto x0 = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
-      const auto x1 = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
-      const uintx4 v = {x0[0], x1[0], x0[1], x1[1]};
-      if (ok) *reinterpret_cast<uintx4*>(row + d * 32 + 8 * g + 8 * hh) = v;
-    }
-}
-
-struct ShortBwd {
-  const __bf16 *q, *k, *v;
-  long qs, ks, vs;
-  const float* v_scores;         // GATED: score of every token
-  const __bf16 *out, *dout;      // out: packed rows
-  const float* lse;
-  long lse_stride;
-  const int32_t* cu;
-  int H, B;
-  float scale;
-  __bf16 *dq, *dk, *dv;
-  long dqs, dks, dvs;
-  TokenIO tok;
-};
-
 template <int DH, bool GATED>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
-attn_bwd_short_bf16_kernel(const ShortBwd p) {
+attn_bwd_short_bf16_kernel(const BwdArgs p) {
   constexpr int RS = DH + 8, KK = DH / 16, DB = DH / 32, CPR = DH / 8, PER = CPR / 2;
   constexpr bool kOnePass = DH == 32;                // dV and dK in one walk (at 64 their accumulators and operands need 150 registers)
   extern __shared__ __attribute__((aligned(16))) unsigned char bwd_smem[];
@@ -773,7 +713,12 @@ attn_bwd_short_bf16_kernel(const ShortBwd p) {
           const bf16x8 va = *reinterpret_cast<const bf16x8*>(&Vt[l32 * RS + kk * 16 + hh * 8]);
           dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, gf[kk], dp, 0, 0, 0);
         }
-        // (keys past the segment have zero rows in K, so their dS reaches nothing)
+        const int left = n - t * 32;                 // valid keys of the tile
+        if (left < 32) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (acc_row(r, hh) >= left) s[r] = -INFINITY;
+        }
 #pragma unroll
         for (int mf = 0; mf < 2; ++mf) {
           floatx8 f;
@@ -957,11 +902,9 @@ static int attention_bwd_common(const char* fn, const void* q, const void* k, co
               SPA_ERR_INVALID_ARG, "%s: tensors not 16-byte aligned", fn);
   SPA_REQUIRE(softmax_scale >= 0.f && std::isfinite(softmax_scale), SPA_ERR_INVALID_ARG,
               "%s: softmax_scale must be finite and >= 0", fn);
-  // short segments: the one-kernel form.  Option attn_bwd_short = "split" keeps the two one-wave
-  // kernels, "tiled" forces the long-segment kernels.
-  const Options& opt = options();
-  const bool short_seg = max_seqlen <= 256 && opt.bwd_short != 2;
-  const bool one_kernel = dtype == SPA_BF16 && short_seg && (at_tokens || opt.bwd_short != 1);
+  // short segments: the one-kernel form (option attn_bwd_short = "tiled" takes the long-segment kernel)
+  const bool short_seg = max_seqlen <= 256 && !options().bwd_tiled;
+  const bool one_kernel = dtype == SPA_BF16 && short_seg;
   const size_t need = one_kernel ? 0 : spa_attention_bwd_workspace_bytes(B, max_seqlen, H, Dh, dtype);
   SPA_REQUIRE(need == 0 || (workspace != nullptr && workspace_bytes >= need), SPA_ERR_WORKSPACE,
               "%s: workspace of %zu bytes needed, %zu given", fn, need, workspace_bytes);
@@ -983,21 +926,13 @@ static int attention_bwd_common(const char* fn, const void* q, const void* k, co
     if (Dh == 32) { SPA_BWD_F32(32); } else { SPA_BWD_F32(64); }
 #undef SPA_BWD_F32
   } else {
-#define SPA_BWD_ARGS_DQ                                                                                       \
-  (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_row_stride, (long)k_row_stride,               \
-      (long)v_row_stride, (const __bf16*)out, (const __bf16*)dout, lse, ls, cu_seqlens, H, scale, (__bf16*)dq, \
-      (long)dq_row_stride, dvec, B, nblk
-#define SPA_BWD_ARGS_DKDV                                                                                     \
-  (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_row_stride, (long)k_row_stride,               \
-      (long)v_row_stride, (const __bf16*)dout, lse, dvec, ls, cu_seqlens, H, scale, (__bf16*)dk,              \
-      (long)dk_row_stride, (__bf16*)dv, (long)dv_row_stride, B, nblk
+    const BwdArgs args = {(const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_row_stride, (long)k_row_stride,
+                          (long)v_row_stride, v_scores, (const __bf16*)out, (const __bf16*)dout, lse, ls, cu_seqlens, H, B,
+                          scale, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, (long)dq_row_stride, (long)dk_row_stride,
+                          (long)dv_row_stride, tok, dvec};
     if (one_kernel) {
       const int nw = (max_seqlen + 31) / 32;
       SPA_REQUIRE((long)B * H < 2147483647L, SPA_ERR_INVALID_ARG, "%s: B*H must be < 2^31", fn);
-      const ShortBwd args = {(const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_row_stride, (long)k_row_stride,
-                             (long)v_row_stride, v_scores, (const __bf16*)out, (const __bf16*)dout, lse, ls, cu_seqlens, H, B,
-                             scale, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, (long)dq_row_stride, (long)dk_row_stride,
-                             (long)dv_row_stride, tok};
 #define SPA_BWD_SHORT(D, G)                                                                                     \
   do {                                                                                                          \
     const size_t smem = bwd_short_lds_bytes<D>(nw);                                                             \
@@ -1014,43 +949,24 @@ static int attention_bwd_common(const char* fn, const void* q, const void* k, co
 #undef SPA_BWD_SHORT
       return check_launch(fn);
     }
-    const int rows_per_block = short_seg ? 32 : 128;
-    const int nblk = (max_seqlen + rows_per_block - 1) / rows_per_block;
-    SPA_REQUIRE(((long)H * B + 8) * nblk < 2147483647L, SPA_ERR_INVALID_ARG, "%s: B*H*blocks must be < 2^31", fn);
-    const dim3 grid(xcd_grid(nblk, H, B));
-#define SPA_BWD_BF16(D)                                                                                          \
-  do {                                                                                                           \
-    if (short_seg) {                                                                                             \
-      hipLaunchKernelGGL((attn_bwd_dq_bf16_kernel<D, 1, 32, false>), grid, dim3(64), 0, st, SPA_BWD_ARGS_DQ);     \
-      hipLaunchKernelGGL((attn_bwd_dkdv_bf16_kernel<D, 1, 32, false>), grid, dim3(64), 0, st, SPA_BWD_ARGS_DKDV); \
-    } else {                                                                                                     \
-      hipLaunchKernelGGL((attn_bwd_dq_bf16_kernel<D, 4, 64, true>), grid, dim3(256), 0, st, SPA_BWD_ARGS_DQ);     \
-      hipLaunchKernelGGL((attn_bwd_dkdv_bf16_kernel<D, 4, 64, true>), grid, dim3(256), 0, st, SPA_BWD_ARGS_DKDV); \
-    }                                                                                                            \
-  } while (0)
-    // long segments: D first, then both sides in one launch (option attn_bwd_long = "two" keeps two launches)
-    if (!short_seg && (at_tokens || !opt.bwd_long_two)) {
-      SPA_REQUIRE(2L * grid.x < 2147483647L, SPA_ERR_INVALID_ARG, "%s: B*H*blocks must be < 2^30", fn);
-      const long rows_cap = (long)B * max_seqlen;
-      const unsigned dgrid = (unsigned)std::min<long>((rows_cap * H * (Dh / 8) + 255) / 256, 4096L);
-#define SPA_BWD_BOTH(D)                                                                                          \
+    // long segments: D first, then both roles in one launch
+    const int nblk = (max_seqlen + kBwdRows - 1) / kBwdRows;
+    SPA_REQUIRE(2 * ((long)H * B + 8) * nblk < 2147483647L, SPA_ERR_INVALID_ARG, "%s: B*H*blocks must be < 2^30", fn);
+    const unsigned grid = 2 * xcd_grid(nblk, H, B);
+    const unsigned dgrid = (unsigned)std::min<long>(((long)B * max_seqlen * H * (Dh / 8) + 255) / 256, 4096L);
+#define SPA_BWD_LONG(D)                                                                                          \
   do {                                                                                                           \
     hipLaunchKernelGGL((attn_bwd_dvec_kernel<D>), dim3(dgrid), dim3(256), 0, st, (const __bf16*)out,             \
                        (const __bf16*)dout, cu_seqlens, B, H, ls, dvec, tok.gather_idx);                         \
-    hipLaunchKernelGGL((attn_bwd_both_bf16_kernel<D, 4, 64>), dim3(2 * grid.x), dim3(256), 0, st,                \
-                       (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_row_stride,                 \
-                       (long)k_row_stride, (long)v_row_stride, (const __bf16*)out, (const __bf16*)dout, lse,     \
-                       dvec, ls, cu_seqlens, H, scale, (__bf16*)dq, (long)dq_row_stride, (__bf16*)dk,            \
-                       (long)dk_row_stride, (__bf16*)dv, (long)dv_row_stride, B, nblk, tok);                     \
+    if (v_scores != nullptr)                                                                                     \
+      hipLaunchKernelGGL((attn_bwd_long_bf16_kernel<D, kGated>), dim3(grid), dim3(kBwdThreads), 0, st, args, nblk);\
+    else if (at_tokens)                                                                                          \
+      hipLaunchKernelGGL((attn_bwd_long_bf16_kernel<D, kTokens>), dim3(grid), dim3(kBwdThreads), 0, st, args, nblk);\
+    else                                                                                                         \
+      hipLaunchKernelGGL((attn_bwd_long_bf16_kernel<D, kPacked>), dim3(grid), dim3(kBwdThreads), 0, st, args, nblk);\
   } while (0)
-      if (Dh == 32) SPA_BWD_BOTH(32); else SPA_BWD_BOTH(64);
-#undef SPA_BWD_BOTH
-    } else {
-      if (Dh == 32) SPA_BWD_BF16(32); else SPA_BWD_BF16(64);
-    }
-#undef SPA_BWD_BF16
-#undef SPA_BWD_ARGS_DQ
-#undef SPA_BWD_ARGS_DKDV
+    if (Dh == 32) SPA_BWD_LONG(32); else SPA_BWD_LONG(64);
+#undef SPA_BWD_LONG
   }
   return check_launch(fn);
 }

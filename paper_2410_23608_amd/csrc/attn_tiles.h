@@ -205,7 +205,7 @@ __device__ __forceinline__ RankedSegment ranked_segment_wave(int rank, int B, co
 // Compact longest-first numbering of the LIVE (segment, head, block) work units of an XCD, for up
 // to 64 segments and 64 (segment, head) pairs per XCD, computed by every wave on its own (no LDS
 // memory, no barrier).  Pairs are numbered as in xcd_tile_at: pair = rank * H + h with rank 0 the
-// longest segment (ties by index), pair p on XCD p % 8.  Workgroup j of an XCD takes the j-th live
+// longest segment (ties by index), the pairs dealt to the XCDs there and back.  Workgroup j of an XCD takes the j-th live
 // block of that XCD's pairs in pair order, the ceil(len / rows) blocks of a pair next to each
 // other.  The host sizes the grid for the longest possible segment, so most workgroups of a
 // sparse batch have no block: numbered this way they all come after the live ones in launch
@@ -213,14 +213,17 @@ __device__ __forceinline__ RankedSegment ranked_segment_wave(int rank, int B, co
 // 5-40 % of 4200 tokens the launch takes 32 instead of 38 us).  valid = false: no block.
 struct LiveTile {
   int qb, h, img, row0, len;
-  bool valid;
+  bool valid, again;       // again: number of the second pass over the blocks (kPasses == 2)
+  int longest;             // longest segment of the batch
 };
 constexpr int kLiveMaxB = 64, kLiveMaxPairs = 512;
 __device__ __forceinline__ bool live_tiles_apply(int H, int B) { return B <= kLiveMaxB && H * B <= kLiveMaxPairs; }
 __device__ __forceinline__ int lanes_below(uint64_t m) {      // set bits of m below this lane
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
-// nblk: blocks the grid provides per pair (no segment has more).
+// nblk: blocks the grid provides per pair (no segment has more).  kPasses == 2: the numbers after an XCD's
+// last live block go through the same blocks once more.
+template <int kPasses = 1>
 __device__ __forceinline__ LiveTile live_tile_wave(int xcd, int j, int H, int B, const int32_t* __restrict__ cu,
                                                    int rows, int nblk) {
   const int lane = threadIdx.x & 63;
@@ -252,8 +255,9 @@ __device__ __forceinline__ LiveTile live_tile_wave(int xcd, int j, int H, int B,
   const int len_r = __builtin_amdgcn_ds_permute(r << 2, len);
   const int start_r = __builtin_amdgcn_ds_permute(r << 2, start);
   const int img_r = __builtin_amdgcn_ds_permute(r << 2, lane);
-  // lane l as pair number l of this XCD: its blocks, and the blocks up to and including it
-  const int pair = lane * 8 + xcd;
+  // lane l as pair number l of this XCD (there and back over the XCDs, so that no XCD has the longer segment of
+  // every row of 8 pairs): its blocks, and the blocks up to and including it
+  const int pair = lane * 8 + (lane & 1 ? 7 - xcd : xcd);
   const bool ok = pair < H * B;
   const int rank_l = ok ? pair / H : 0;
   const int len_l = __builtin_amdgcn_ds_bpermute(rank_l << 2, len_r);
@@ -264,16 +268,24 @@ __device__ __forceinline__ LiveTile live_tile_wave(int xcd, int j, int H, int B,
     const int up = __shfl_up(incl, o, 64);
     if (lane >= o) incl += up;
   }
-  LiveTile t = {0, 0, 0, 0, 0, false};
+  LiveTile t = {0, 0, 0, 0, 0, false, false, 0};
+  if (kPasses == 2) {
+    const int all = __builtin_amdgcn_readlane(incl, 63);
+    if (j >= all) {
+      j -= all;
+      t.again = true;
+    }
+  }
   const uint64_t past = __ballot(incl > j);
   if (past == 0) return t;
   const int pl = __builtin_ctzll(past);
-  const int p = pl * 8 + xcd, rank = p / H;
+  const int p = pl * 8 + (pl & 1 ? 7 - xcd : xcd), rank = p / H;
   t.qb = j - (__builtin_amdgcn_readlane(incl, pl) - __builtin_amdgcn_readlane(nb, pl));
   t.h = p - rank * H;
   t.img = __builtin_amdgcn_readlane(img_r, rank);
   t.row0 = __builtin_amdgcn_readlane(start_r, rank);
   t.len = __builtin_amdgcn_readlane(len_r, rank);
+  t.longest = __builtin_amdgcn_readlane(len_r, 0);
   t.valid = true;
   return t;
 }
@@ -282,11 +294,12 @@ __device__ __forceinline__ LiveTile live_tile_wave(int xcd, int j, int H, int B,
 // barrier: measured 1 % faster on an 8-image batch with other batches in flight); with many, the
 // first wave numbers and the others read the answer from LDS (one barrier: a uniform batch of 64
 // segments ran 5 % slower with every wave of every workgroup doing the ranking).  All threads call it.
+template <int kPasses = 1>
 __device__ __forceinline__ LiveTile live_tile_block(int xcd, int j, int H, int B, const int32_t* __restrict__ cu,
                                                     int rows, int nblk, LiveTile* slot) {
-  if (B <= 16) return live_tile_wave(xcd, j, H, B, cu, rows, nblk);
+  if (B <= 16) return live_tile_wave<kPasses>(xcd, j, H, B, cu, rows, nblk);
   if (threadIdx.x < 64) {
-    const LiveTile t = live_tile_wave(xcd, j, H, B, cu, rows, nblk);
+    const LiveTile t = live_tile_wave<kPasses>(xcd, j, H, B, cu, rows, nblk);
     if (threadIdx.x == 0) *slot = t;
   }
   __syncthreads();

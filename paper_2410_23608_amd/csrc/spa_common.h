@@ -19,8 +19,7 @@ struct Options {
   bool fwd_long_two;                       // attn_fwd_long = two (two query chains per wave)
   int fwd_nw, fwd_bn;                      // attn_fwd_cfg (0 = automatic)
   int fwd_wave_max;                        // attn_fwd_wave_max
-  int bwd_short;                           // attn_bwd_short: 0 one kernel, 1 split, 2 tiled
-  bool bwd_long_two;                       // attn_bwd_long = two
+  bool bwd_tiled;                          // attn_bwd_short = tiled
   int gemm_tm, gemm_splits, pack_tile;     // 0 = automatic
 };
 const Options& options();

@@ -1,0 +1,63 @@
+"""The bf16 attention backward kernels at the edges of their tiles (32 tokens per wave, 64-token tiles and
+128-row blocks of the long-segment form) and with scores far below zero, where a key past the segment would
+have an unbounded probability; packed and token-position rows, against fp32 autograd."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+LENS = [1, 0, 31, 32, 33, 63, 64, 65, 127, 128, 129, 191, 193]
+
+
+@pytest.mark.parametrize("shift", [0.0, 8.0])
+@pytest.mark.parametrize("Dh,N", [(32, 224), (64, 224), (32, 260), (64, 330)])
+def test_backward_at_tile_edges(Dh, N, shift):
+    from paper_2410_23608_amd import spa
+    H, C, lens = 2, 2 * Dh, LENS + [N]
+    B = len(lens)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Dh + N)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    cu = torch.tensor([0] + lens, dtype=torch.int32).cumsum(0).int().cuda()
+    T, cap = sum(lens), B * N
+    idx = torch.cat([b * N + torch.randperm(N)[:n].sort().values for b, n in enumerate(lens)]).cuda()
+    gather = torch.zeros(cap, dtype=torch.int32, device="cuda")
+    gather[:T] = idx.int()
+    inv = torch.full((cap,), -1, dtype=torch.int32, device="cuda")
+    inv[idx] = torch.arange(T, dtype=torch.int32, device="cuda")
+    qkv = rnd(cap, 3 * C)
+    qkv[:, :C] += shift
+    qkv[:, C:2 * C] -= shift                       # scores around -shift^2 sqrt(Dh)
+    qkv = qkv.bfloat16()
+    q, k, v = qkv[:, :C], qkv[:, C:2 * C], qkv[:, 2 * C:]
+    dy = rnd(cap, C).bfloat16()
+    out = torch.zeros(cap, C, device="cuda", dtype=torch.bfloat16)
+    lse = torch.zeros(H, cap, device="cuda")
+    spa.spa_packed_attention(q, k, v, cu, B, N, H, Dh, out, lse)
+    ws = torch.empty(spa.spa_attention_bwd_workspace_bytes(B, N, H, Dh, spa.dtype_code(out)), dtype=torch.uint8, device="cuda")
+    got = []
+    for tokens in (False, True):
+        d = torch.full((cap, 3 * C), float("nan"), device="cuda", dtype=torch.bfloat16)
+        dq, dk, dv = d[:, :C], d[:, C:2 * C], d[:, 2 * C:]
+        if tokens:
+            spa.spa_packed_attention_bwd_tokens(q, k, v, out, dy, lse, cu, B, N, H, Dh, gather, inv, dq, dk, dv, ws)
+            assert (d[inv < 0] == 0).all()
+            d = d[idx]
+        else:
+            dout = torch.zeros_like(dy)
+            dout[:T] = dy[idx]
+            spa.spa_packed_attention_bwd(q, k, v, out, dout, lse, cu, B, N, H, Dh, dq, dk, dv, ws)
+            assert torch.isnan(d[T:]).all()
+            d = d[:T]
+        got.append(d.float())
+    assert torch.equal(got[0], got[1])
+    for b, n in enumerate(lens):
+        r = slice(int(cu[b]), int(cu[b]) + n)
+        p = qkv[r].float().reshape(n, 3, H, Dh).permute(1, 2, 0, 3).contiguous().requires_grad_()
+        s = (p[0] @ p[1].transpose(1, 2).contiguous()) / Dh ** 0.5
+        o = torch.softmax(s, -1) @ p[2]
+        o.backward(dy[idx[r]].float().reshape(n, H, Dh).transpose(0, 1).contiguous())
+        ref = p.grad.permute(2, 0, 1, 3).reshape(n, 3 * C)
+        if n:
+            err = (got[0][r] - ref).abs().max() / max(1.0, ref.abs().max())
+            assert err < 3e-2, (b, n, err)
