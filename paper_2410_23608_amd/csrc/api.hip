@@ -34,16 +34,11 @@ static bool parse_option(Options& o, const char* name, const char* value) {
     o.fwd_whole = std::strstr(v, "whole") != nullptr;
     o.fwd_step64 = std::strstr(v, "64") != nullptr;
     o.fwd_plain = std::strstr(v, "plain") != nullptr;
-  } else if (!std::strcmp(name, "attn_fwd_long")) {    // "" (one query chain per wave) | "two"
-    o.fwd_long_two = v[0] == 't';
+  } else if (!std::strcmp(name, "attn_fwd_long")) {    // (one form: any value is taken)
   } else if (!std::strcmp(name, "attn_fwd_cfg")) {     // "" | "NW,BN" with NW in {2,4}, BN in {64,128}
     int a = 0, b = 0;
-    o.fwd_nw = o.fwd_bn = 0;
-    if (v[0] != 0) {
-      if (std::sscanf(v, "%d,%d", &a, &b) != 2 || !(a == 2 || a == 4) || !(b == 64 || b == 128)) return false;
-      o.fwd_nw = a;
-      o.fwd_bn = b;
-    }
+    if (v[0] != 0 && (std::sscanf(v, "%d,%d", &a, &b) != 2 || !(a == 2 || a == 4) || !(b == 64 || b == 128))) return false;
+    o.fwd_tiled = v[0] != 0;
   } else if (!std::strcmp(name, "attn_fwd_wave_max")) { // longest segment the one-wave kernels take
     const int n = v[0] != 0 ? std::atoi(v) : 256;
     if (n < 0 || n > 256) return false;

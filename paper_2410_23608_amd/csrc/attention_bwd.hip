@@ -50,9 +50,6 @@ struct TokenIO {
   long rows;               // B * N
 };
 
-// 8 bf16 multiplied by a row scale, rounded again
-__device__ __forceinline__ bf16x8 scale_row(bf16x8 v, float s) { return float_to_bf16x8(bf16x8_to_float(v) * s); }
-
 // The wave's transposed accumulator tile (rows = head dim, a lane = one token) as bf16 rows: the two halves
 // of the wave exchange quads so that a lane holds 8 consecutive columns of its token, 16-byte stores.
 template <int DH>
@@ -102,50 +99,6 @@ constexpr int kBwdBT = 64, kBwdThreads = 256, kBwdRows = 128;     // streamed ti
 //   kPacked: packed as well;  kTokens: at token positions;  kGated: q, k, v at token positions too, v gated.
 enum BwdRowsMode { kPacked, kTokens, kGated };
 
-// Two row-major tiles of BT tokens of one head on their way to LDS: operand 0 is K (dq role) or Q (dkdv
-// role), operand 1 is V or dO, their rows packed or (IDX0, IDX1) named by an index, which is read one tile ahead
-// of the rows.  Nothing here waits for a load or branches on one between load() and store(): a tile past the
-// segment's end loads the last row again (the caller gives such rows probability 0).
-template <int DH, bool IDX0, bool IDX1>
-struct PairStage {
-  static constexpr int RS = DH + 8, CPR = DH / 8, CPT = kBwdBT * CPR / kBwdThreads, RPP = kBwdThreads / CPR;
-  static_assert(kBwdBT * CPR % kBwdThreads == 0, "whole passes");
-  bf16x8 v[2][CPT];
-  int idx[CPT];
-  const __bf16* base[2];         // this thread's columns of row 0 (indexed) or of the segment's first row
-  int stride[2];
-  const int32_t* gi;
-  int n;
-  __device__ __forceinline__ static int row(int t) { return (int)threadIdx.x / CPR + t * RPP; }
-  __device__ __forceinline__ void source(int o, const __bf16* p, long row_stride, long row0) {
-    base[o] = p + threadIdx.x % CPR * 8 + ((o ? IDX1 : IDX0) ? 0 : row0 * row_stride);
-    stride[o] = (int)row_stride;
-  }
-  __device__ __forceinline__ void index(int t0) {
-    if (IDX0 || IDX1) {
-#pragma unroll
-      for (int t = 0; t < CPT; ++t) idx[t] = gi[min(t0 + row(t), n - 1)];
-    }
-  }
-  __device__ __forceinline__ void load(int t0) {
-#pragma unroll
-    for (int t = 0; t < CPT; ++t) {
-      const int r = min(t0 + row(t), n - 1);
-      v[0][t] = *reinterpret_cast<const bf16x8*>(base[0] + (long)(IDX0 ? idx[t] : r) * stride[0]);
-      v[1][t] = *reinterpret_cast<const bf16x8*>(base[1] + (long)(IDX1 ? idx[t] : r) * stride[1]);
-    }
-  }
-  // gate: scores of operand 1's rows, nullptr: not gated
-  __device__ __forceinline__ void store(__bf16* a, __bf16* b, const float (&gate)[CPT], bool gated) const {
-#pragma unroll
-    for (int t = 0; t < CPT; ++t) {
-      const int o = row(t) * RS + threadIdx.x % CPR * 8;
-      *reinterpret_cast<bf16x8*>(a + o) = v[0][t];
-      *reinterpret_cast<bf16x8*>(b + o) = gated ? scale_row(v[1][t], sigmoidf_dev(gate[t])) : v[1][t];
-    }
-  }
-};
-
 template <int DH>
 struct BwdLongLds {
   static constexpr int RS = DH + 8;
@@ -179,7 +132,7 @@ template <int DH, int MODE>
 __device__ __forceinline__ void bwd_dq_role(BwdLongLds<DH>& lds, const BwdArgs& p, const Segment seg, int h, int q0) {
   constexpr int RS = DH + 8, KK = DH / 16, DB = DH / 32, BT = kBwdBT;
   constexpr bool GATED = MODE == kGated;
-  using Stage = PairStage<DH, GATED, GATED>;
+  using Stage = PairStage<DH, kBwdThreads, BT, GATED, GATED>;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
   const int qi = q0 + wv * 32 + l32, n = seg.nk;
   const bool wave_live = q0 + wv * 32 < n, q_ok = qi < n;
@@ -192,7 +145,7 @@ __device__ __forceinline__ void bwd_dq_role(BwdLongLds<DH>& lds, const BwdArgs& 
   Stage st;
   float gate[Stage::CPT] = {};
   st.gi = gi;
-  st.n = n;
+  st.last = n - 1;
   st.source(0, p.k + h * DH, p.ks, seg.row0);
   st.source(1, p.v + h * DH, p.vs, seg.row0);
   auto load_tile = [&](int kt) {                     // (then the index of the one after it)
@@ -225,7 +178,7 @@ __device__ __forceinline__ void bwd_dq_role(BwdLongLds<DH>& lds, const BwdArgs& 
 #pragma unroll
     for (int d = 0; d < DB; ++d) acc[d][r] = 0.f;
   }
-  st.store(lds.A[0], lds.Bm[0], gate, GATED);
+  if (GATED) st.store_gated(lds.A[0], lds.Bm[0], gate); else st.store(lds.A[0], lds.Bm[0]);
   __syncthreads();
   const int nt = (n + BT - 1) / BT;
   auto tile = [&](int t, auto last) {
@@ -262,7 +215,7 @@ __device__ __forceinline__ void bwd_dq_role(BwdLongLds<DH>& lds, const BwdArgs& 
       }
     }
     if (!last) {
-      st.store(lds.A[buf ^ 1], lds.Bm[buf ^ 1], gate, GATED);
+      if (GATED) st.store_gated(lds.A[buf ^ 1], lds.Bm[buf ^ 1], gate); else st.store(lds.A[buf ^ 1], lds.Bm[buf ^ 1]);
       __syncthreads();
     }
   };
@@ -277,7 +230,7 @@ template <int DH, int MODE>
 __device__ __forceinline__ void bwd_dkdv_role(BwdLongLds<DH>& lds, const BwdArgs& p, const Segment seg, int h, int k0) {
   constexpr int RS = DH + 8, KK = DH / 16, DB = DH / 32, BT = kBwdBT;
   constexpr bool GATED = MODE == kGated;
-  using Stage = PairStage<DH, GATED, MODE != kPacked>;
+  using Stage = PairStage<DH, kBwdThreads, BT, GATED, MODE != kPacked>;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
   const int ki = k0 + wv * 32 + l32, n = seg.nk;
   const bool wave_live = k0 + wv * 32 < n, k_ok = ki < n;
@@ -290,9 +243,8 @@ __device__ __forceinline__ void bwd_dkdv_role(BwdLongLds<DH>& lds, const BwdArgs
   const long tok_row = MODE != kPacked ? (long)gi[k_ok ? ki : 0] : k_row, src = GATED ? tok_row : k_row;
 
   Stage st;
-  const float no_gate[Stage::CPT] = {};
   st.gi = gi;
-  st.n = n;
+  st.last = n - 1;
   st.source(0, p.q + h * DH, p.qs, seg.row0);
   st.source(1, p.dout + h * DH, C, seg.row0);
   float lse_t = 0.f, d_t = 0.f;                      // of streamed query `lane` of the tile
@@ -304,7 +256,7 @@ __device__ __forceinline__ void bwd_dkdv_role(BwdLongLds<DH>& lds, const BwdArgs
     d_t = dvec_h[q];
   };
   auto store_all = [&](int buf, int qt) {
-    st.store(lds.A[buf], lds.Bm[buf], no_gate, false);
+    st.store(lds.A[buf], lds.Bm[buf]);
     if (tid < BT) {
       lds.lse2s[buf][tid] = qt + tid < n ? lse_t * kLog2e : INFINITY;    // past the segment: probability 0
       lds.negD[buf][tid] = -d_t;

@@ -106,20 +106,41 @@ __device__ __forceinline__ void scatter_fill(const Scatter& sc, int b, int t0, i
   }
 }
 
-// Fill every column of the bypassing rows among the flat token rows [r0, r1).
+// One wave fills the bypassing rows among rows [r0, r1) of y: the lanes test 64 rows at a time and list those
+// that need it, then the wave goes over their 16-byte chunks, all lanes at work whatever the row length, four
+// steps of loads in flight.
 template <typename T>
-__device__ __forceinline__ void scatter_fill_rows(const Scatter& sc, long r0, long r1, long C, int tid, int nthreads) {
-  constexpr int VE = 16 / sizeof(T);
-  const int cpr = (int)(C / VE);
-  const long work = (r1 - r0) * cpr;
-  for (long i = tid; i < work; i += nthreads) {
-    const long row = r0 + i / cpr;
-    const int c = (int)(i % cpr);
-    if (bypasses(sc, row)) {
-      const long off = row * C + c * VE;
-      uintx4 val = {0u, 0u, 0u, 0u};
-      if (sc.base != nullptr) val = *reinterpret_cast<const uintx4*>(static_cast<const T*>(sc.base) + off);
-      __builtin_nontemporal_store(val, reinterpret_cast<uintx4*>(static_cast<T*>(sc.y) + off));
+__device__ __forceinline__ void scatter_fill_rows(const Scatter& sc, long r0, long r1, long C, int lane) {
+  constexpr int VE = 16 / sizeof(T), U = 4;
+  const int cpr = (int)(C / VE), dr = kWave / cpr, dc = kWave % cpr;
+  for (long rb = r0; rb < r1; rb += kWave) {
+    const long row = rb + lane;
+    const bool mine = row < r1 && bypasses(sc, row);
+    const uint64_t m = __ballot(mine);
+    const int n = __popcll(m), below = lanes_below(m);
+    const int list = __builtin_amdgcn_ds_permute((mine ? below : n + lane - below) << 2, lane);   // lane i: i-th such row
+    int r = lane / cpr, c = lane % cpr;
+    for (int left = n * cpr; left > 0; left -= U * kWave) {
+      uintx4 val[U];
+      T* dst[U];
+      bool ok[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        ok[u] = r < n;
+        const long off = (rb + __builtin_amdgcn_ds_bpermute((r & 63) << 2, list)) * C + c * VE;
+        dst[u] = static_cast<T*>(sc.y) + off;
+        val[u] = uintx4{0u, 0u, 0u, 0u};
+        if (sc.base != nullptr && ok[u]) val[u] = *reinterpret_cast<const uintx4*>(static_cast<const T*>(sc.base) + off);
+        r += dr;
+        c += dc;
+        if (c >= cpr) {
+          c -= cpr;
+          ++r;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (ok[u]) __builtin_nontemporal_store(val[u], reinterpret_cast<uintx4*>(dst[u]));
     }
   }
 }
@@ -447,118 +468,26 @@ __device__ __forceinline__ void load_q_frags(const __bf16* qrow, bool q_ok, int 
   }
 }
 
-// Register staging of BN key and value rows on their way to LDS (both row-major): chunk i =
-// 16-byte piece i % CPR of row i / CPR; index() runs one tile ahead of load() (see KvStage).
-template <int DH, int THREADS, int BN, bool GATHER>
-struct KvRowStage {
-  static constexpr int CPR = DH / 8, CHUNKS = BN * CPR, CPT = (CHUNKS + THREADS - 1) / THREADS;
-  static constexpr int RPP = THREADS / CPR;
-  static_assert(THREADS % CPR == 0, "a thread keeps its chunk column over the passes");
-  bf16x8 kreg[CPT], vreg[CPT];
-  int tok_rows[CPT];                   // gathered rows only: see KvStage
-  long row0_;
-  int kt_, nk_;
-  __device__ __forceinline__ bool valid(int t) const {
-    const int i = threadIdx.x + t * THREADS;
-    return i < CHUNKS && kt_ + i / CPR < nk_;
-  }
-  __device__ __forceinline__ void index(const int32_t* gi, long row0, int kt, int nk) {
-    row0_ = row0;
-    kt_ = kt;
-    nk_ = nk;
-    if (GATHER) {
-      if (CHUNKS % THREADS == 0 && kt + BN <= nk) {                  // a whole tile: no predicates
-#pragma unroll
-        for (int t = 0; t < CPT; ++t) tok_rows[t] = gi[kt + (threadIdx.x + t * THREADS) / CPR];
-      } else {
-#pragma unroll
-        for (int t = 0; t < CPT; ++t)
-          if (valid(t)) tok_rows[t] = gi[kt + (threadIdx.x + t * THREADS) / CPR];
-      }
-    }
-  }
-  __device__ __forceinline__ void load(const __bf16* kh, const __bf16* vh, long ks, long vs) {
-    const int c = threadIdx.x % CPR, lrow = threadIdx.x / CPR;
-    const uint32_t koff = (uint32_t)lrow * (uint32_t)ks + c * 8, voff = (uint32_t)lrow * (uint32_t)vs + c * 8;
-    // a tile that lies wholly inside the segment (all but the last one): no predicates, no zero fill
-    if (CHUNKS % THREADS == 0 && kt_ + BN <= nk_) {
-#pragma unroll
-      for (int t = 0; t < CPT; ++t) {
-        const __bf16 *kp, *vp;
-        if (GATHER) {
-          kp = kh + row_offset(tok_rows[t], ks) + c * 8;
-          vp = vh + row_offset(tok_rows[t], vs) + c * 8;
-        } else {
-          const long r = row0_ + kt_ + t * RPP;           // uniform
-          kp = kh + r * ks + koff;
-          vp = vh + r * vs + voff;
-        }
-        kreg[t] = *reinterpret_cast<const bf16x8*>(kp);
-        vreg[t] = *reinterpret_cast<const bf16x8*>(vp);
-      }
-      return;
-    }
-#pragma unroll
-    for (int t = 0; t < CPT; ++t) {
-      kreg[t] = zero_bf16x8();
-      vreg[t] = zero_bf16x8();
-      if (valid(t)) {
-        const __bf16 *kp, *vp;
-        if (GATHER) {
-          kp = kh + row_offset(tok_rows[t], ks) + c * 8;
-          vp = vh + row_offset(tok_rows[t], vs) + c * 8;
-        } else {
-          const long r = row0_ + kt_ + t * RPP;           // uniform
-          kp = kh + r * ks + koff;
-          vp = vh + r * vs + voff;
-        }
-        kreg[t] = *reinterpret_cast<const bf16x8*>(kp);
-        vreg[t] = *reinterpret_cast<const bf16x8*>(vp);
-      }
-    }
-  }
-  __device__ __forceinline__ void store(__bf16* kbuf, __bf16* vbuf) const {
-#pragma unroll
-    for (int t = 0; t < CPT; ++t) {
-      const int i = threadIdx.x + t * THREADS, r = i / CPR, c = i % CPR;
-      if (i < CHUNKS) {
-        *reinterpret_cast<bf16x8*>(&kbuf[r * (DH + 8) + c * 8]) = kreg[t];
-        *reinterpret_cast<bf16x8*>(&vbuf[r * (DH + 8) + c * 8]) = vreg[t];
-      }
-    }
-  }
-};
-
-// Long segments.  Workgroup = NW waves x 32 queries; the keys of the segment stream through
-// LDS in tiles of BN keys, double-buffered: while a tile is consumed the next one is already
-// in flight from global memory into registers, and is written to the other LDS buffer
-// before the single barrier that ends the iteration.
-// Head dim 32 is compiled for three waves per SIMD (168 registers, no spills): with several
-// batches in flight the third wave fills the softmax stalls of the other two.
-// V in LDS: at head dim 64 as the rows lie in memory (staging is plain 16-byte copies, the V^T fragments
-// come from the transposing LDS read: uniform long segments 521 against 481 TFLOP/s), at head dim 32
-// transposed while staging (the detection batch 42.2 against 43.1 us for the launch; the same rate on
-// uniform segments).
-template <int DH>
-constexpr bool kTiledVRows = DH == 64;
+// Long segments.  Workgroup = NW waves x 32 queries; the keys of the segment stream through LDS in tiles of BN,
+// double-buffered: while a tile is consumed the next one is in flight from global memory into registers
+// (PairStage), and is written to the other LDS buffer before the single barrier that ends the iteration.  K and V
+// lie in LDS as in memory, the V^T fragments come from the transposing LDS read.
 template <int DH, int BN>
 struct TiledLds {
-  static constexpr int RS = DH + 8, TS = transposed_stride(BN);
-  static constexpr int VSIZE = kTiledVRows<DH> ? BN * RS : DH * TS;
+  static constexpr int RS = DH + 8;
   __attribute__((aligned(16))) __bf16 Ks[2][BN * RS];
-  __attribute__((aligned(16))) __bf16 Vs[2][VSIZE];
+  __attribute__((aligned(16))) __bf16 Vs[2][BN * RS];
 };
+constexpr int kTiledBN = 64;
 
 // The workgroup's work on queries [q0, q0 + 32 NW) of head h of segment seg (q0 < seg.nq).
-template <int DH, int NW, int BN, bool GATHER>
+template <int DH, int NW, bool GATHER>
 __device__ __forceinline__ void
-tiled_attention(TiledLds<DH, BN>& lds, const Segment seg, int h, int q0, const __bf16* __restrict__ q,
+tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, const __bf16* __restrict__ q,
                 const __bf16* __restrict__ k, const __bf16* __restrict__ v, long qs, long ks, long vs, int H,
                 float scale_log2, __bf16* __restrict__ out, float* __restrict__ lse, long lse_stride,
                 const Scatter& sc) {
-  constexpr int RS = DH + 8, NSB = BN / 32;
-  constexpr bool VROWS = kTiledVRows<DH>;
-  constexpr int TS = VROWS ? 0 : transposed_stride(BN);    // 0: V rows in LDS (see fwd_softmax_pv)
+  constexpr int RS = DH + 8, BN = kTiledBN, GSB = BN / 32;
   auto& Ks = lds.Ks;
   auto& Vs = lds.Vs;
   static_assert(2 * BN >= 32 * NW, "the K buffers double as the output staging tile");
@@ -567,319 +496,102 @@ tiled_attention(TiledLds<DH, BN>& lds, const Segment seg, int h, int q0, const _
   const int qi = q0 + wv * 32 + l32;
   const bool wave_live = q0 + wv * 32 < seg.nq;
   const bool q_ok = qi < seg.nq;
-  const __bf16* kh = k + h * DH;
-  const __bf16* vh = v + h * DH;
 
   const int32_t* gi = gather_base<GATHER>(sc, seg.row0);
   const long q_src = q_ok ? source_row(gi, seg.row0, qi) : 0;   // (gathered: an index load, issued first)
-  typename std::conditional<VROWS, KvRowStage<DH, 64 * NW, BN, GATHER>,
-                            KvStage<DH, 64 * NW, (BN / 2) * (DH / 8), GATHER>>::type stage;
-  auto store = [&](int buf) {
-    if constexpr (VROWS) stage.store(Ks[buf], Vs[buf]);
-    else stage.template store<RS, transposed_stride(BN)>(Ks[buf], Vs[buf], 0);
-  };
-  stage.index(gi, seg.row0, 0, seg.nk);
-  stage.load(kh, vh, ks, vs);
-  stage.index(gi, seg.row0, BN, seg.nk);
+  PairStage<DH, 64 * NW, BN, GATHER, GATHER> stage;
+  stage.gi = gi;
+  stage.last = max(seg.nk - 1, 0);
+  stage.source(0, k + h * DH, ks, seg.row0);
+  stage.source(1, v + h * DH, vs, seg.row0);
+  stage.index(0);
+  stage.load(0);
+  stage.index(BN);
   bf16x8 qf[DH / 16];
   load_q_frags<DH>(q + q_src * qs + h * DH, q_ok, hh, qf);
   FwdAcc<DH> acc;
   acc.init();
-  store(0);
+  stage.store(Ks[0], Vs[0]);
   __syncthreads();
 
   const int nt = (seg.nk + BN - 1) / BN;
-  for (int t = 0; t < nt; ++t) {
+  auto tile = [&](int t, auto last) {
     const int buf = t & 1, kt = t * BN;
-    if (t + 1 < nt) {
-      stage.load(kh, vh, ks, vs);                           // tile t + 1, whose rows were indexed a tile ago
-      stage.index(gi, seg.row0, kt + 2 * BN, seg.nk);
+    if (!last) {
+      stage.load(kt + BN);                                  // tile t + 1, whose rows were indexed a tile ago
+      stage.index(kt + 2 * BN);
     }
     if (wave_live) {
-      const int rem = seg.nk - kt;               // valid keys from this tile on (may exceed BN)
-      if (rem >= BN) fwd_process_tile<DH, RS, TS, NSB, true>(Ks[buf], Vs[buf], 0, BN, t == 0, qf, acc, scale_log2, l32, hh);
-      else fwd_process_tile<DH, RS, TS, NSB, false>(Ks[buf], Vs[buf], 0, rem, t == 0, qf, acc, scale_log2, l32, hh);
+      floatx16 s[GSB];
+      fwd_scores<DH, RS, GSB, !last>(Ks[buf], 0, seg.nk - kt, qf, s, l32, hh);
+      fwd_softmax_pv<DH, RS, 0, GSB, !last>(s, Ks[buf], Vs[buf], 0, 0, seg.nk - kt, t == 0, qf, acc, scale_log2, l32, hh);
     }
-    if (t + 1 < nt) store(buf ^ 1);
+    if (!last) stage.store(Ks[buf ^ 1], Vs[buf ^ 1]);
     __syncthreads();
-  }
-  // every wave is past its last read of the K buffers (the loop ends with a barrier)
-  __bf16* tile = &Ks[0][0] + wv * 32 * RS;
-  if (wave_live)
-    fwd_park<DH, RS>(acc, q_ok, seg.nk > 0, tile, lse != nullptr ? lse + h * lse_stride + seg.row0 + qi : nullptr,
+  };
+  for (int t = 0; t + 1 < nt; ++t) tile(t, std::false_type{});
+  if (nt > 0) tile(nt - 1, std::true_type{});
+  // every wave is past its last read of the K buffers
+  __bf16* parked = &Ks[0][0] + wv * 32 * RS;
+  if (wave_live) {
+    fwd_park<DH, RS>(acc, q_ok, seg.nk > 0, parked, lse != nullptr ? lse + h * lse_stride + seg.row0 + qi : nullptr,
                      l32, hh);
-  __syncthreads();
-  if (wave_live)
-    fwd_flush<DH, RS>(tile, out, sc, seg.row0 + q0 + wv * 32, h, C, min(32, seg.nq - q0 - wv * 32), lane);
+    __builtin_amdgcn_wave_barrier();
+    fwd_flush<DH, RS>(parked, out, sc, seg.row0 + q0 + wv * 32, h, C, min(32, seg.nq - q0 - wv * 32), lane);
+  }
 }
 
-template <int DH, int NW, int BN, bool GATHER>
+// Workgroups [0, ntile) take query blocks, the rest fill y's bypassing rows while those run.
+//   up to 64 segments and 64 pairs per XCD: live blocks only, longest segment first (live_order); a launch has
+//     at most as many workgroups as are resident together, and number g of an XCD's G takes blocks g,
+//     2 G - 1 - g, 2 G + g, ...: the order is found once per workgroup;
+//   otherwise block qb of every (segment, head) pair in turn.
+template <int DH, int NW, bool GATHER>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH == 32 ? 3 : 2)))
 attn_fwd_bf16_tiled_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                            const __bf16* __restrict__ v, long qs, long ks, long vs,
                            const int32_t* __restrict__ cu, const int32_t* __restrict__ key_lens, int n_pad,
                            int H, float scale_log2, __bf16* __restrict__ out, float* __restrict__ lse,
-                           long lse_stride, Scatter sc, int B, int nqb) {
-  __shared__ TiledLds<DH, BN> lds;
+                           long lse_stride, Scatter sc, int B, int nqb, int ntile) {
+  __shared__ TiledLds<DH, kTiledBN> lds;
   __shared__ int s_cu[2 * kLptMaxB + 1];
   __shared__ int s_pick;
-  __shared__ LiveTile s_live;
 
-  const long C = (long)H * DH;
-  // live blocks first in launch order where the batch allows it (see live_tile_wave); the bypass fill
-  // is then whole rows, an even share of all tokens per workgroup.  Otherwise block qb of every
-  // (segment, head) pair in turn, the pair's share of its image's bypassing tokens per block.  The
-  // fill is done right away by a workgroup without queries, after the main loop by one that has some.
-  const bool live = key_lens == nullptr && live_tiles_apply(H, B);
-  Segment seg = {0, 0, 0};
-  int h = 0, q0 = 0;
-  FillRange fr = {0, 0, 0};
-  if (live) {
-    const LiveTile lt = live_tile_block(blockIdx.x & 7, blockIdx.x >> 3, H, B, cu, 32 * NW, nqb, &s_live);
-    if (lt.valid) {
-      seg = {lt.row0, lt.len, lt.len};
-      h = lt.h;
-      q0 = lt.qb * (32 * NW);
-    }
-  } else {
-    const TileId tile_id = xcd_tile(nqb, H, B);
-    if (!tile_id.valid) return;
-    h = tile_id.h;
-    seg = lpt_segment<64 * NW>(tile_id.rank, B, cu, key_lens, n_pad, s_cu, &s_pick);
-    const int fill_img = key_lens == nullptr && B > 1 && B <= kLptMaxB ? s_pick : tile_id.rank;
-    fr = fill_range(sc, fill_img, B, tile_id.qb, nqb);
-    q0 = tile_id.qb * (32 * NW);
-  }
-  if (q0 < seg.nq)
-    tiled_attention<DH, NW, BN, GATHER>(lds, seg, h, q0, q, k, v, qs, ks, vs, H, scale_log2, out, lse, lse_stride, sc);
-  if (sc.y == nullptr) return;
-  if (live) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  if ((int)blockIdx.x >= ntile) {
     const long rows = sc.flat ? (long)sc.N : (long)B * sc.N;
-    const long per = (rows + gridDim.x - 1) / gridDim.x;
-    const long r0 = min(rows, blockIdx.x * per);
-    scatter_fill_rows<__bf16>(sc, r0, min(rows, r0 + per), C, threadIdx.x, 64 * NW);
-  } else {
-    scatter_fill<__bf16, DH>(sc, fr.b, fr.t0, fr.t1, h, C, threadIdx.x, 64 * NW);
+    const long units = (long)(gridDim.x - ntile) * NW, u = (long)(blockIdx.x - ntile) * NW + wv, per = (rows + units - 1) / units;
+    scatter_fill_rows<__bf16>(sc, min(rows, u * per), min(rows, (u + 1) * per), (long)H * DH, lane);
+    return;
   }
-}
-
-// Long segments, two query sub-tiles per wave.  A wave owns 64 queries as two independent
-// 32-query chains that share every K and V fragment it reads from LDS: half the LDS operand
-// reads per MFMA of the one-chain kernel above, and two independent dependency chains in one
-// instruction stream, so the score and P V MFMAs of one chain run under the softmax vector
-// work of the other even when the wave has its SIMD to itself (the long-segment launches of
-// this path keep one to two waves per SIMD resident, too few to hide a single chain's stalls).
-// K and V tiles sit row-major in LDS; V^T fragments come from the transposing LDS read, so
-// staging is plain 16-byte copies.  One softmax update per 32 keys and chain.
-template <int DH, int BN>
-struct Tiled2Lds {
-  static constexpr int RS = DH + 8;
-  __attribute__((aligned(16))) __bf16 Ks[2][BN * RS];
-  __attribute__((aligned(16))) __bf16 Vs[2][BN * RS];
-};
-
-
-// Online-softmax update of one chain over one 32-key sub-tile whose first key is k0 of the tile
-// (rem = valid keys of the tile): masks keys past the segment, moves the running max, rescales
-// the chain's accumulators when some query's max moved, and leaves the bf16 probabilities in
-// the B-operand layout of the P V product.
-template <int DH, bool FULL>
-__device__ __forceinline__ void chain_softmax(floatx16& s, int k0, int rem, FwdAcc<DH>& acc, float scale_log2,
-                                              bf16x8 (&pb)[2], int hh) {
-  if (!FULL && rem - k0 < 32) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-      if (k0 + acc_row(r, hh) >= rem) s[r] = -INFINITY;
-  }
-  float mx = s[0];
-#pragma unroll
-  for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-  mx = max_across_halves(mx);
-  // The rescale is unconditional (alpha = 1 when no max moved): skipping it takes a branch per
-  // chain and sub-tile, and every branch ends a scheduling region, which is what keeps the two
-  // chains, the fragment reads and the MFMAs from overlapping.  The first sub-tile of a tile always
-  // holds a valid key, so m_new is finite and alpha well defined.
-  const float m_new = fmaxf(acc.m, mx * scale_log2);
-  const float alpha = __builtin_amdgcn_exp2f(acc.m - m_new);
-  acc.m = m_new;
-#pragma unroll
-  for (int d = 0; d < DH / 32; ++d)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc.o[d][r] *= alpha;
-  float p[16], psum = 0.f;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2, -m_new));
-    psum += p[r];
-  }
-  acc.l = fmaf(acc.l, alpha, psum);
-#pragma unroll
-  for (int mf = 0; mf < 2; ++mf) {
-    floatx8 pf;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) pf[j] = p[8 * mf + j];
-    pb[mf] = float_to_bf16x8(pf);
-  }
-}
-
-// One tile of NSB*32 keys in LDS (K rows at kbuf, V rows at vbuf, both row stride RS) against
-// the wave's NC query chains.  The score MFMAs of sub-tile sb + 1 are issued before the softmax of
-// sub-tile sb.  FULL = every key of the tile is valid; otherwise keys >= rem are masked (their K and
-// V rows in LDS are zero): all sub-tiles are computed, there is no control flow in the tile.
-template <int DH, int RS, int NSB, bool FULL, int NC>
-__device__ __forceinline__ void fwd_tile_chains(const __bf16* kbuf, const __bf16* vbuf, int rem,
-                                                const bf16x8 (&qf)[NC][DH / 16], FwdAcc<DH> (&acc)[NC],
-                                                float scale_log2, int lane) {
-  constexpr int KK = DH / 16, DB = DH / 32;
-  const int l32 = lane & 31, hh = lane >> 5;
-  floatx16 s[2][NC];
-  auto scores = [&](int sb, floatx16 (&dst)[NC]) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) dst[c][r] = 0.f;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      const bf16x8 a = *reinterpret_cast<const bf16x8*>(&kbuf[(sb * 32 + l32) * RS + kk * 16 + hh * 8]);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) dst[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[c][kk], dst[c], 0, 0, 0);
+  if (key_lens == nullptr && live_tiles_apply(H, B)) {
+    const int xcd = blockIdx.x & 7, g = blockIdx.x >> 3, G = ntile >> 3;
+    int(*order)[64] = reinterpret_cast<int(*)[64]>(s_cu);
+    static_assert(sizeof(s_cu) >= 5 * 64 * sizeof(int), "holds the order");
+    if (wv == 0) {
+      const LiveOrder o = live_order(xcd, H, B, cu, 32 * NW, nqb);
+      order[0][lane] = o.len;
+      order[1][lane] = o.start;
+      order[2][lane] = o.img;
+      order[3][lane] = o.nb;
+      order[4][lane] = o.incl;
     }
-  };
-  scores(0, s[0]);
-#pragma unroll
-  for (int sb = 0; sb < NSB; ++sb) {
-    const int k0 = sb * 32;
-    if (sb + 1 < NSB) scores(sb + 1, s[(sb + 1) & 1]);
-    bf16x8 vf[2][DB];                                  // V^T fragments of the sub-tile: read before the softmax needs them
-#pragma unroll
-    for (int mf = 0; mf < 2; ++mf)
-#pragma unroll
-      for (int d = 0; d < DB; ++d) vf[mf][d] = transposed_frag_rowmajor<RS>(vbuf, d, k0, mf, lane);
-    bf16x8 pb[NC][2];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) chain_softmax<DH, FULL>(s[sb & 1][c], k0, rem, acc[c], scale_log2, pb[c], hh);
-#pragma unroll
-    for (int mf = 0; mf < 2; ++mf)
-#pragma unroll
-      for (int d = 0; d < DB; ++d)
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-          acc[c].o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[mf][d], pb[c][mf], acc[c].o[d], 0, 0, 0);
-  }
-}
-
-// The key loop of one wave with NC live query chains (NC = 0: a wave without queries, which only
-// helps to stage the tiles).  Every instantiation runs the same sequence of barriers.
-template <int DH, int NW, int BN, int NC, bool GATHER>
-__device__ __forceinline__ void
-tiled2_wave(Tiled2Lds<DH, BN>& lds, KvRowStage<DH, 64 * NW, BN, GATHER>& stage, const Segment& seg, const int32_t* gi,
-            const __bf16* kh, const __bf16* vh, long ks, long vs, const bf16x8 (&qf)[2][DH / 16], FwdAcc<DH> (&acc2)[2],
-            float scale_log2, int lane) {
-  constexpr int RS = DH + 8, NSB = BN / 32, KK = DH / 16, NCA = NC > 0 ? NC : 1;
-  bf16x8 q[NCA][KK];
-  FwdAcc<DH> acc[NCA];
-#pragma unroll
-  for (int c = 0; c < NCA; ++c) {
-    acc[c].init(-INFINITY);
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) q[c][kk] = qf[c][kk];
-  }
-  const int nt = (seg.nk + BN - 1) / BN;
-  for (int t = 0; t + 1 < nt; ++t) {                  // all tiles but the last are full
-    const int buf = t & 1;
-    stage.load(kh, vh, ks, vs);                        // tile t + 1, whose rows were indexed a tile ago
-    stage.index(gi, seg.row0, (t + 2) * BN, seg.nk);
-    if (NC > 0) fwd_tile_chains<DH, RS, NSB, true, NCA>(lds.Ks[buf], lds.Vs[buf], BN, q, acc, scale_log2, lane);
-    stage.store(lds.Ks[buf ^ 1], lds.Vs[buf ^ 1]);
     __syncthreads();
+    for (int round = 0;; ++round) {
+      const LiveOrder o = {order[0][lane], order[1][lane], order[2][lane], order[3][lane], order[4][lane]};
+      const LiveTile lt = live_pick(o, xcd, round * G + (round & 1 ? G - 1 - g : g), H);
+      if (!lt.valid) return;
+      if (round > 0) __syncthreads();                       // the parked rows are written
+      tiled_attention<DH, NW, GATHER>(lds, {lt.row0, lt.len, lt.len}, lt.h, lt.qb * (32 * NW), q, k, v, qs, ks, vs, H,
+                                      scale_log2, out, lse, lse_stride, sc);
+    }
   }
-  if (nt > 0) {
-    const int buf = (nt - 1) & 1;
-    if (NC > 0)
-      fwd_tile_chains<DH, RS, NSB, false, NCA>(lds.Ks[buf], lds.Vs[buf], seg.nk - (nt - 1) * BN, q, acc, scale_log2, lane);
-  }
-  __syncthreads();                                     // every wave is past its last read of the K buffers
-#pragma unroll
-  for (int c = 0; c < NCA; ++c)
-    if (NC > 0) acc2[c] = acc[c];
-}
-
-// The workgroup's work on queries [q0, q0 + 64 NW) of head h of segment seg (q0 < seg.nq).
-template <int DH, int NW, int BN, bool GATHER>
-__device__ __forceinline__ void
-tiled2_attention(Tiled2Lds<DH, BN>& lds, const Segment seg, int h, int q0, const __bf16* __restrict__ q,
-                 const __bf16* __restrict__ k, const __bf16* __restrict__ v, long qs, long ks, long vs, int H,
-                 float scale_log2, __bf16* __restrict__ out, float* __restrict__ lse, long lse_stride,
-                 const Scatter& sc) {
-  constexpr int RS = DH + 8, KK = DH / 16;
-  static_assert(2 * BN >= 64 * NW, "the K buffers double as the output staging tile");
-  const long C = (long)H * DH;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, l32 = lane & 31, hh = lane >> 5;
-  const int qw = q0 + wv * 64;                         // the wave's first query
-  const int nc = qw >= seg.nq ? 0 : (qw + 32 < seg.nq ? 2 : 1);      // live chains of this wave
-  const __bf16* kh = k + h * DH;
-  const __bf16* vh = v + h * DH;
-  const int32_t* gi = gather_base<GATHER>(sc, seg.row0);
-
-  bool q_ok[2];
-  long q_src[2];
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int qi = qw + 32 * c + l32;
-    q_ok[c] = qi < seg.nq;
-    q_src[c] = q_ok[c] ? source_row(gi, seg.row0, qi) : 0;     // (gathered: an index load, issued first)
-  }
-  KvRowStage<DH, 64 * NW, BN, GATHER> stage;
-  stage.index(gi, seg.row0, 0, seg.nk);
-  stage.load(kh, vh, ks, vs);
-  stage.index(gi, seg.row0, BN, seg.nk);
-  bf16x8 qf[2][KK];
-#pragma unroll
-  for (int c = 0; c < 2; ++c) load_q_frags<DH>(q + q_src[c] * qs + h * DH, q_ok[c], hh, qf[c]);
-  FwdAcc<DH> acc[2];
-  acc[0].init(-INFINITY);
-  acc[1].init(-INFINITY);
-  stage.store(lds.Ks[0], lds.Vs[0]);
-  __syncthreads();
-  if (nc == 2) tiled2_wave<DH, NW, BN, 2, GATHER>(lds, stage, seg, gi, kh, vh, ks, vs, qf, acc, scale_log2, lane);
-  else if (nc == 1) tiled2_wave<DH, NW, BN, 1, GATHER>(lds, stage, seg, gi, kh, vh, ks, vs, qf, acc, scale_log2, lane);
-  else tiled2_wave<DH, NW, BN, 0, GATHER>(lds, stage, seg, gi, kh, vh, ks, vs, qf, acc, scale_log2, lane);
-
-  __bf16* tile = &lds.Ks[0][0] + wv * 64 * RS;
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-    if (c < nc)
-      fwd_park<DH, RS>(acc[c], q_ok[c], seg.nk > 0, tile + c * 32 * RS,
-                       lse != nullptr ? lse + h * lse_stride + seg.row0 + qw + 32 * c + l32 : nullptr, l32, hh);
-  __syncthreads();
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-    if (c < nc)
-      fwd_flush<DH, RS>(tile + c * 32 * RS, out, sc, seg.row0 + qw + 32 * c, h, C, min(32, seg.nq - qw - 32 * c), lane);
-}
-
-template <int DH, int NW, int BN, bool GATHER>
-__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2)))
-attn_fwd_bf16_tiled2_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
-                            const __bf16* __restrict__ v, long qs, long ks, long vs,
-                            const int32_t* __restrict__ cu, const int32_t* __restrict__ key_lens, int n_pad,
-                            int H, float scale_log2, __bf16* __restrict__ out, float* __restrict__ lse,
-                            long lse_stride, Scatter sc, int B, int nqb) {
-  __shared__ Tiled2Lds<DH, BN> lds;
-  __shared__ int s_cu[2 * kLptMaxB + 1];
-  __shared__ int s_pick;
-
   const TileId tile_id = xcd_tile(nqb, H, B);
   if (!tile_id.valid) return;
-  const int h = tile_id.h;
   const Segment seg = lpt_segment<64 * NW>(tile_id.rank, B, cu, key_lens, n_pad, s_cu, &s_pick);
-  const long C = (long)H * DH;
-  const int fill_img = key_lens == nullptr && B > 1 && B <= kLptMaxB ? s_pick : tile_id.rank;
-  const FillRange fr = fill_range(sc, fill_img, B, tile_id.qb, nqb);
-  const int q0 = tile_id.qb * (64 * NW);
+  const int q0 = tile_id.qb * (32 * NW);
   if (q0 < seg.nq)
-    tiled2_attention<DH, NW, BN, GATHER>(lds, seg, h, q0, q, k, v, qs, ks, vs, H, scale_log2, out, lse, lse_stride, sc);
-  if (sc.y != nullptr) scatter_fill<__bf16, DH>(sc, fr.b, fr.t0, fr.t1, h, C, threadIdx.x, 64 * NW);
+    tiled_attention<DH, NW, GATHER>(lds, seg, tile_id.h, q0, q, k, v, qs, ks, vs, H, scale_log2, out, lse, lse_stride, sc);
 }
 
 // Short segments, wave-autonomous.  ONE wave per (image, head, 32-query block), no
@@ -1057,27 +769,6 @@ attn_fwd_bf16_wave_mask_kernel(const __bf16* __restrict__ q, const __bf16* __res
 // all blocks of its pairs), the XCD's live query blocks are listed heaviest first, and the
 // m-th workgroup of a unit takes block r = 32 m + (unit, or 31 - unit for odd m).  Workgroups
 // past the live blocks only fill; the bypassing rows of y are shared evenly by all.
-// One wave fills the bypassing rows among rows [r0, r1) of y: the lanes test 64 rows at a time
-// (one load each), then the wave writes the rows that need it, a lane per 16-byte chunk.
-template <typename T>
-__device__ __forceinline__ void scatter_fill_rows(const Scatter& sc, long r0, long r1, long C, int lane) {
-  constexpr int VE = 16 / sizeof(T);
-  const int cpr = (int)(C / VE);
-  for (long rb = r0; rb < r1; rb += kWave) {
-    const long row = rb + lane;
-    uint64_t todo = __ballot(row < r1 && bypasses(sc, row));
-    while (todo != 0) {
-      const long off0 = (rb + __ffsll((unsigned long long)todo) - 1) * C;
-      todo &= todo - 1;
-      for (int c = lane; c < cpr; c += kWave) {
-        uintx4 val = {0u, 0u, 0u, 0u};
-        if (sc.base != nullptr) val = *reinterpret_cast<const uintx4*>(static_cast<const T*>(sc.base) + off0 + c * VE);
-        __builtin_nontemporal_store(val, reinterpret_cast<uintx4*>(static_cast<T*>(sc.y) + off0 + c * VE));
-      }
-    }
-  }
-}
-
 // No tables are needed: with the pairs sorted by
 // class, class c holds the ranked images [A_c, A_c + n_c) (n_c from one ballot), hence the
 // pairs [A_c H, (A_c + n_c) H), of which this XCD owns a count with a closed form; every pair
@@ -1432,6 +1123,7 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
     const float scale_log2 = scale * 1.4426950408889634f;
 #define SPA_ARGS_PLAIN SPA_ARGS
 #define SPA_ARGS_BN SPA_ARGS, B, nqb
+#define SPA_ARGS_TILED SPA_ARGS, B, nqb, (int)ntile
 #define SPA_LAUNCH(KERNEL, GRID, BLOCK, ARGS, ...)                                                            \
   do {                                                                                                        \
     if (sc.gathered) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, true>), GRID, BLOCK, 0, st, ARGS);               \
@@ -1443,10 +1135,10 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
     // options attn_fwd_cfg (forces the tiled kernel with that launch shape), attn_fwd_short and
     // attn_fwd_wave_max select among the kernels below; unset, the measured best is taken
     const Options& opt = options();
-    int NW = opt.fwd_nw, BN = opt.fwd_bn;
+    const bool tiled = opt.fwd_tiled;
     const bool use_whole = opt.fwd_whole;
     const int wave_max = opt.fwd_wave_max;
-    if (NW == 0 && n_max <= wave_max && !use_whole) {
+    if (!tiled && n_max <= wave_max && !use_whole) {
       // short segments: one wave per (image, head, 32 queries)
       const int nqb = (n_max + 31) / 32;
       const dim3 grid(xcd_grid(nqb, H, B));
@@ -1463,7 +1155,7 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
         if (step64) SPA_LAUNCH(attn_fwd_bf16_wave_kernel, grid, dim3(64), SPA_ARGS_BN, 64, 64);
         else SPA_LAUNCH(attn_fwd_bf16_wave_kernel, grid, dim3(64), SPA_ARGS_BN, 64, 32);
       }
-    } else if (NW == 0 && n_max <= 256) {
+    } else if (!tiled && n_max <= 256) {
       // short segments: one workgroup per (image, head), whole segment in LDS
       const dim3 grid(H, B);
 #define SPA_WHOLE(D)                                                                                          \
@@ -1474,29 +1166,21 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
   } while (0)
       if (Dh == 32) SPA_WHOLE(32); else SPA_WHOLE(64);
 #undef SPA_WHOLE
-    } else if (NW == 0 && opt.fwd_long_two) {
-      // long segments: two query chains per wave, 2 waves x 64 queries per workgroup, 64-key tiles
-      const int nqb = (n_max + 127) / 128;
-      const dim3 grid(xcd_grid(nqb, H, B)), block(128);
-      if (Dh == 32) SPA_LAUNCH(attn_fwd_bf16_tiled2_kernel, grid, block, SPA_ARGS_BN, 32, 2, 64);
-      else SPA_LAUNCH(attn_fwd_bf16_tiled2_kernel, grid, block, SPA_ARGS_BN, 64, 2, 64);
     } else {
-      if (NW == 0) { NW = 4; BN = 128; }
-      const int nqb = (n_max + 32 * NW - 1) / (32 * NW);
-      const dim3 grid(xcd_grid(nqb, H, B)), block(64 * NW);
-#define SPA_TILED(D)                                                                                          \
-  do {                                                                                                        \
-    if (NW == 2 && BN == 64) SPA_LAUNCH(attn_fwd_bf16_tiled_kernel, grid, block, SPA_ARGS_BN, D, 2, 64);        \
-    else if (NW == 2) SPA_LAUNCH(attn_fwd_bf16_tiled_kernel, grid, block, SPA_ARGS_BN, D, 2, 128);              \
-    else if (BN == 64) SPA_LAUNCH(attn_fwd_bf16_tiled_kernel, grid, block, SPA_ARGS_BN, D, 4, 64);              \
-    else SPA_LAUNCH(attn_fwd_bf16_tiled_kernel, grid, block, SPA_ARGS_BN, D, 4, 128);           \
-  } while (0)
-      if (Dh == 32) SPA_TILED(32); else SPA_TILED(64);
-#undef SPA_TILED
+      constexpr int kNW = 4;
+      const int nqb = (n_max + 32 * kNW - 1) / (32 * kNW);
+      const bool live = key_lens == nullptr && live_tiles_apply(H, B);
+      // resident together: 3 waves per SIMD at head dim 32, 2 at 64
+      const long all = xcd_grid(nqb, H, B), ntile = live ? std::min<long>(all, (Dh == 32 ? 3 : 2) * 256) : all;
+      const long rows = sc.y == nullptr ? 0 : sc.flat ? (long)sc.N : (long)B * sc.N;
+      const dim3 grid((unsigned)(ntile + std::min<long>((rows + 31) / 32, 1024))), block(64 * kNW);
+      if (Dh == 32) SPA_LAUNCH(attn_fwd_bf16_tiled_kernel, grid, block, SPA_ARGS_TILED, 32, kNW);
+      else SPA_LAUNCH(attn_fwd_bf16_tiled_kernel, grid, block, SPA_ARGS_TILED, 64, kNW);
     }
 #undef SPA_ARGS
 #undef SPA_ARGS_PLAIN
 #undef SPA_ARGS_BN
+#undef SPA_ARGS_TILED
 #undef SPA_LAUNCH
   }
   return check_launch(fn);

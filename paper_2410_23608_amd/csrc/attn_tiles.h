@@ -217,15 +217,17 @@ struct LiveTile {
   int longest;             // longest segment of the batch
 };
 constexpr int kLiveMaxB = 64, kLiveMaxPairs = 512;
-__device__ __forceinline__ bool live_tiles_apply(int H, int B) { return B <= kLiveMaxB && H * B <= kLiveMaxPairs; }
+__host__ __device__ __forceinline__ bool live_tiles_apply(int H, int B) { return B <= kLiveMaxB && H * B <= kLiveMaxPairs; }
 __device__ __forceinline__ int lanes_below(uint64_t m) {      // set bits of m below this lane
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
-// nblk: blocks the grid provides per pair (no segment has more).  kPasses == 2: the numbers after an XCD's
-// last live block go through the same blocks once more.
-template <int kPasses = 1>
-__device__ __forceinline__ LiveTile live_tile_wave(int xcd, int j, int H, int B, const int32_t* __restrict__ cu,
-                                                   int rows, int nblk) {
+// In two steps, for a workgroup that takes several blocks: the order (a lane's share of it), then number j of it.
+struct LiveOrder {
+  int len, start, img;     // lane r: the segment of launch rank r
+  int nb, incl;            // lane l: blocks of pair number l of this XCD, blocks up to and including it
+};
+// nblk: blocks the grid provides per pair (no segment has more).
+__device__ __forceinline__ LiveOrder live_order(int xcd, int H, int B, const int32_t* __restrict__ cu, int rows, int nblk) {
   const int lane = threadIdx.x & 63;
   int start = 0, len = 0;
   if (lane < B) {
@@ -251,43 +253,53 @@ __device__ __forceinline__ LiveTile live_tile_wave(int xcd, int j, int H, int B,
     }
   }
   if (lane >= B) r = lane;            // (keeps the exchange below a permutation of the 64 lanes)
-  // lane r of these = the segment of launch rank r
-  const int len_r = __builtin_amdgcn_ds_permute(r << 2, len);
-  const int start_r = __builtin_amdgcn_ds_permute(r << 2, start);
-  const int img_r = __builtin_amdgcn_ds_permute(r << 2, lane);
+  LiveOrder o;
+  o.len = __builtin_amdgcn_ds_permute(r << 2, len);
+  o.start = __builtin_amdgcn_ds_permute(r << 2, start);
+  o.img = __builtin_amdgcn_ds_permute(r << 2, lane);
   // lane l as pair number l of this XCD (there and back over the XCDs, so that no XCD has the longer segment of
   // every row of 8 pairs): its blocks, and the blocks up to and including it
   const int pair = lane * 8 + (lane & 1 ? 7 - xcd : xcd);
   const bool ok = pair < H * B;
   const int rank_l = ok ? pair / H : 0;
-  const int len_l = __builtin_amdgcn_ds_bpermute(rank_l << 2, len_r);
-  const int nb = ok ? (len_l + rows - 1) / rows : 0;
-  int incl = nb;
+  const int len_l = __builtin_amdgcn_ds_bpermute(rank_l << 2, o.len);
+  o.nb = ok ? (len_l + rows - 1) / rows : 0;
+  o.incl = o.nb;
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int up = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += up;
+  for (int d = 1; d < 64; d <<= 1) {
+    const int up = __shfl_up(o.incl, d, 64);
+    if (lane >= d) o.incl += up;
   }
+  return o;
+}
+// kPasses == 2: the numbers after an XCD's last live block go through the same blocks once more.
+template <int kPasses = 1>
+__device__ __forceinline__ LiveTile live_pick(const LiveOrder& o, int xcd, int j, int H) {
   LiveTile t = {0, 0, 0, 0, 0, false, false, 0};
   if (kPasses == 2) {
-    const int all = __builtin_amdgcn_readlane(incl, 63);
+    const int all = __builtin_amdgcn_readlane(o.incl, 63);
     if (j >= all) {
       j -= all;
       t.again = true;
     }
   }
-  const uint64_t past = __ballot(incl > j);
+  const uint64_t past = __ballot(o.incl > j);
   if (past == 0) return t;
   const int pl = __builtin_ctzll(past);
   const int p = pl * 8 + (pl & 1 ? 7 - xcd : xcd), rank = p / H;
-  t.qb = j - (__builtin_amdgcn_readlane(incl, pl) - __builtin_amdgcn_readlane(nb, pl));
+  t.qb = j - (__builtin_amdgcn_readlane(o.incl, pl) - __builtin_amdgcn_readlane(o.nb, pl));
   t.h = p - rank * H;
-  t.img = __builtin_amdgcn_readlane(img_r, rank);
-  t.row0 = __builtin_amdgcn_readlane(start_r, rank);
-  t.len = __builtin_amdgcn_readlane(len_r, rank);
-  t.longest = __builtin_amdgcn_readlane(len_r, 0);
+  t.img = __builtin_amdgcn_readlane(o.img, rank);
+  t.row0 = __builtin_amdgcn_readlane(o.start, rank);
+  t.len = __builtin_amdgcn_readlane(o.len, rank);
+  t.longest = __builtin_amdgcn_readlane(o.len, 0);
   t.valid = true;
   return t;
+}
+template <int kPasses = 1>
+__device__ __forceinline__ LiveTile live_tile_wave(int xcd, int j, int H, int B, const int32_t* __restrict__ cu,
+                                                   int rows, int nblk) {
+  return live_pick<kPasses>(live_order(xcd, H, B, cu, rows, nblk), xcd, j, H);
 }
 
 // The same for a workgroup of several waves.  With few segments every wave numbers for itself (no
@@ -355,6 +367,62 @@ __device__ __forceinline__ Segment lpt_segment(int rank, int B, const int32_t* c
   }
   return s;
 }
+
+// 8 bf16 multiplied by a row scale, rounded again
+__device__ __forceinline__ bf16x8 scale_row(bf16x8 v, float s) { return float_to_bf16x8(bf16x8_to_float(v) * s); }
+
+// Two row-major tiles of BT tokens of one head on their way to LDS (keys and values, or queries and output
+// gradients), their rows packed or (IDX0, IDX1) named by an index, which is read one tile ahead of the rows.
+// Nothing here waits for a load or branches on one between load() and store(): rows past the segment's end are
+// loaded as its last row (the caller gives such rows probability 0).  With predicated loads and a separate path
+// for whole tiles the compiler waited for all of them in front of the tile they were meant to overlap.
+template <int DH, int THREADS, int BT, bool IDX0, bool IDX1>
+struct PairStage {
+  static constexpr int RS = DH + 8, CPR = DH / 8, CPT = BT * CPR / THREADS, RPP = THREADS / CPR;
+  static_assert(BT * CPR % THREADS == 0, "whole passes");
+  bf16x8 v[2][CPT];
+  int idx[CPT];
+  const __bf16* base[2];         // this thread's columns of row 0 (indexed) or of the segment's first row
+  int stride[2];
+  const int32_t* gi;
+  int last;                      // the segment's last row
+  __device__ __forceinline__ static int row(int t) { return (int)threadIdx.x / CPR + t * RPP; }
+  __device__ __forceinline__ void source(int o, const __bf16* p, long row_stride, long row0) {
+    base[o] = p + threadIdx.x % CPR * 8 + ((o ? IDX1 : IDX0) ? 0 : row0 * row_stride);
+    stride[o] = (int)row_stride;
+  }
+  __device__ __forceinline__ void index(int t0) {
+    if (IDX0 || IDX1) {
+#pragma unroll
+      for (int t = 0; t < CPT; ++t) idx[t] = gi[min(t0 + row(t), last)];
+    }
+  }
+  __device__ __forceinline__ void load(int t0) {
+#pragma unroll
+    for (int t = 0; t < CPT; ++t) {
+      const int r = min(t0 + row(t), last);
+      v[0][t] = *reinterpret_cast<const bf16x8*>(base[0] + (long)(IDX0 ? idx[t] : r) * stride[0]);
+      v[1][t] = *reinterpret_cast<const bf16x8*>(base[1] + (long)(IDX1 ? idx[t] : r) * stride[1]);
+    }
+  }
+  __device__ __forceinline__ void store(__bf16* a, __bf16* b) const {
+#pragma unroll
+    for (int t = 0; t < CPT; ++t) {
+      const int o = row(t) * RS + threadIdx.x % CPR * 8;
+      *reinterpret_cast<bf16x8*>(a + o) = v[0][t];
+      *reinterpret_cast<bf16x8*>(b + o) = v[1][t];
+    }
+  }
+  // the same with operand 1's rows gated by Sigmoid(gate)
+  __device__ __forceinline__ void store_gated(__bf16* a, __bf16* b, const float (&gate)[CPT]) const {
+#pragma unroll
+    for (int t = 0; t < CPT; ++t) {
+      const int o = row(t) * RS + threadIdx.x % CPR * 8;
+      *reinterpret_cast<bf16x8*>(a + o) = v[0][t];
+      *reinterpret_cast<bf16x8*>(b + o) = scale_row(v[1][t], sigmoidf_dev(gate[t]));
+    }
+  }
+};
 
 // Row-major staging of `ROWS` rows of one head slice on their way to LDS: global -> registers
 // (16-byte chunks, consecutive lanes on consecutive chunks of a row) -> LDS rows of stride
