@@ -565,7 +565,7 @@ attn_fwd_bf16_tiled_kernel(const __bf16* __restrict__ q, const __bf16* __restric
     return;
   }
   if (key_lens == nullptr && live_tiles_apply(H, B)) {
-    const int xcd = blockIdx.x & 7, g = blockIdx.x >> 3, G = ntile >> 3;
+    const int xcd = blockIdx.x & 7, G = ntile >> 3, g = there_and_back(blockIdx.x >> 3, G);
     int(*order)[64] = reinterpret_cast<int(*)[64]>(s_cu);
     static_assert(sizeof(s_cu) >= 5 * 64 * sizeof(int), "holds the order");
     if (wv == 0) {

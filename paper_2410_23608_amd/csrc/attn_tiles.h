@@ -221,6 +221,13 @@ __host__ __device__ __forceinline__ bool live_tiles_apply(int H, int B) { return
 __device__ __forceinline__ int lanes_below(uint64_t m) {      // set bits of m below this lane
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
+// Workgroup g of an XCD's G runs on unit g % 32: numbers that go there and back over the units in rounds of 32
+// give the unit with a round's longest block the shortest of the next.
+__device__ __forceinline__ int there_and_back(int g, int G) {
+  const int m = g >> 5, u = g & 31, size = min(32, G - 32 * m);
+  return 32 * m + (m & 1 ? size - 1 - u : u);
+}
+
 // In two steps, for a workgroup that takes several blocks: the order (a lane's share of it), then number j of it.
 struct LiveOrder {
   int len, start, img;     // lane r: the segment of launch rank r
