@@ -516,8 +516,8 @@ def measure_train(args, torch, workloads, TrainPass, traffic_table, streams):
 
 
 def measure_hierarchy(args, torch, workloads, HierarchyPass, HierarchyTrainPass, traffic_table):
-    """Four-stage hierarchy (batch 16, 56^2 .. 7^2 tokens, C 96 .. 768): forward chain (12 launches)
-    and forward + backward chain (20 calls); per-kernel rooflines, dominant = the finest stage's."""
+    """Four-stage hierarchy (batch 16, 56^2 .. 7^2 tokens, C 96 .. 768): forward chain and forward +
+    backward chain, each step of all stages one launch group; per-group rooflines over all stages' work."""
     hb = workloads.generate_hierarchy(args.seed)
     td = torch.bfloat16
     up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda().to(td).contiguous()
@@ -564,7 +564,12 @@ def measure_hierarchy(args, torch, workloads, HierarchyPass, HierarchyTrainPass,
         wl_ = b_["workload"]
         n = np.diff(tp_.cu_seqlens.cpu().numpy()).astype(np.float64)
         sum_n2s.append(float((n * n).sum()))
-        work.update(train_work(wl_.B, wl_.N, wl_.C, wl_.H, htT[i], sum_n2s[-1], prefix=f"s{i + 1}."))
+        stage_work = train_work(wl_.B, wl_.N, wl_.C, wl_.H, htT[i], sum_n2s[-1])
+        if i > 0:
+            stage_work["gate_select"] = stage_work["gate_select_pooled"]
+        for name, (fl, by) in stage_work.items():
+            have = work.get(name, (0.0, 0))
+            work[name] = (have[0] + fl, have[1] + by)
     kernels, roof = kernels_block(times, work, "bf16", "hierarchy", traffic_table, args.seed)
     res.update({"selected_tokens": htT, "sum_n2": sum_n2s, "value": sum(htT) / med, "unit": "selected tokens/s",
                 "ms_per_step": 1e3 * med, "ms_per_step_min": 1e3 * mn, "regions": args.repeats,
@@ -583,8 +588,9 @@ def measure_hierarchy(args, torch, workloads, HierarchyPass, HierarchyTrainPass,
     cmed, cmin = timed_regions(htcstep, args.steps, args.repeats, torch)
     res["stream_per_stage"] = {
         "ms_per_step": 1e3 * cmed, "ms_per_step_min": 1e3 * cmin, "value": sum(htT) / cmed,
-        "gradients_equal_one_stream": bool(all(torch.equal(a_.dx, b_.dx) and torch.equal(a_.dw, b_.dw)
-                                               for a_, b_ in zip(htpc.passes, htp.passes)))}
+        # (the coarse stages' attention backward is another kernel there)
+        "gradients_close_to_one_stream": bool(all(float((a_.dw - b_.dw).abs().max() / b_.dw.abs().max()) < 1e-2
+                                                  for a_, b_ in zip(htpc.passes, htp.passes)))}
     return res
 
 

@@ -80,6 +80,21 @@ const char* spa_last_error(void);
 int spa_set_option(const char* name, const char* value);
 
 /*
+ * Launch groups: calls of several stages of a hierarchy in one launch per step.  Between spa_group_begin and
+ * spa_group_end (same host thread) up to four calls each of spa_gate_select / spa_gate_select_pooled, spa_pack (no
+ * counts needed, no scores), spa_pack_pair (with scores), spa_packed_attention_unpack /
+ * spa_gathered_attention_unpack / spa_selected_attention_unpack, spa_packed_attention_bwd_tokens (which needs its
+ * workspace here whatever max_seqlen) and spa_gate_bwd (C <= 1024) check their arguments and are noted;
+ * spa_group_end launches them on its stream, step by step in that order: a call sees what calls of earlier steps
+ * of the group write, and a pooled gate the scores of the gate called before it.  bf16, head dim 32; for at most 256
+ * tokens per image at most 64 images, and no gathered attention.  Any other call, or one outside these limits,
+ * returns SPA_ERR_UNSUPPORTED; an error of any call ends the group, nothing is launched.  Same results as the calls
+ * one by one, but for the rounding of the attention backward of short segments (the long-segment kernel serves all).
+ */
+int spa_group_begin(void);
+int spa_group_end(void* stream);
+
+/*
  * Bytes of workspace that call `op` needs for a batch of B images x N tokens, width C, H heads
  * (the one query over the per-call ones below; Section 3.2 / 3.3 name the calls).  0 for the
  * calls that need none (all forward calls and the row-moving transposes), and for bad arguments.

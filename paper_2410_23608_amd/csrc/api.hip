@@ -4,21 +4,25 @@
 #include <cstdlib>
 #include <cstring>
 
+#include "group.h"
 #include "spa_common.h"
 
 namespace spa {
 
 static thread_local char g_err[512] = "";
+thread_local bool g_group_open = false;
 
 int fail(int code, const char* fmt, ...) {
   va_list ap;
   va_start(ap, fmt);
   vsnprintf(g_err, sizeof(g_err), fmt, ap);
   va_end(ap);
+  g_group_open = false;                  // an error ends the group: nothing of it is launched
   return code;
 }
 
 int check_launch(const char* what) {
+  if (g_group_open) return fail(SPA_ERR_UNSUPPORTED, "%s: cannot be part of a group", what);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(SPA_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
   return SPA_OK;
@@ -114,4 +118,26 @@ extern "C" size_t spa_workspace_bytes(int op, int B, int N, int C, int H, int dt
       return cap < 2147483647L ? spa_linear_bwd_weight_workspace_bytes((int)cap, C, C, dtype) : 0;
     default: return 0;   // the forward calls and the row-moving transposes need none
   }
+}
+
+extern "C" int spa_group_begin(void) {
+  using namespace spa;
+  group_forget_gates();
+  group_forget_pack();
+  group_forget_attention();
+  group_forget_attention_bwd();
+  g_group_open = true;
+  return SPA_OK;
+}
+
+extern "C" int spa_group_end(void* stream) {
+  using namespace spa;
+  SPA_REQUIRE(g_group_open, SPA_ERR_INVALID_ARG, "spa_group_end: no group is open on this thread");
+  g_group_open = false;
+  hipStream_t st = as_stream(stream);
+  if (int rc = group_flush_gates(st)) return rc;
+  if (int rc = group_flush_pack(st)) return rc;
+  if (int rc = group_flush_attention(st)) return rc;
+  if (int rc = group_flush_attention_bwd(st)) return rc;
+  return group_flush_gates_bwd(st);
 }

@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "attn_tiles.h"
+#include "group.h"
 #include "spa_common.h"
 
 namespace spa {
@@ -90,6 +91,7 @@ struct BwdArgs {
   long dqs, dks, dvs;
   TokenIO tok;
   float* dvec;                   // long segments: D_i for every (head, packed row)
+  int nblk;                      // long segments: blocks of kBwdRows rows of the longest possible one
 };
 
 // -------------------------------------------------------------------------- long segments (bf16)
@@ -350,13 +352,12 @@ __device__ __forceinline__ void bwd_dkdv_role(BwdLongLds<DH>& lds, const BwdArgs
 // 16 images of 3136 tokens, 10-60 % selected, 3 heads of 32: 74 -> 52 us; 32 x 1024 tokens, all selected, 12
 // heads of 64: 508 -> 410 us; 2 x 4200 tokens, 5-40 %, 8 heads of 32: 28 -> 20 us.
 template <int DH, int MODE>
-__global__ void __launch_bounds__(kBwdThreads) __attribute__((amdgpu_waves_per_eu(DH == 32 ? 3 : 2)))
-attn_bwd_long_bf16_kernel(const BwdArgs p, int nblk) {
+__device__ __forceinline__ void bwd_long_block(const BwdArgs& p, unsigned block, unsigned blocks) {
   __shared__ BwdLongLds<DH> lds;
   __shared__ LiveTile s_live;
   __shared__ int s_cu[2 * kLptMaxB + 1];
   __shared__ int s_pick;
-  const int xcd = blockIdx.x & 7, jj = blockIdx.x >> 3, half = gridDim.x >> 4;
+  const int xcd = block & 7, jj = block >> 3, half = blocks >> 4, nblk = p.nblk;
   Segment seg = {0, 0, 0};
   int h = 0, r0 = 0;
   bool dkdv;
@@ -385,7 +386,7 @@ attn_bwd_long_bf16_kernel(const BwdArgs p, int nblk) {
     // gradients of the unselected tokens: every workgroup (with or without a tile) zeroes an even share of the
     // rows, a quarter per wave
     constexpr int NW = kBwdThreads / 64;
-    const long units = (long)gridDim.x * NW, u = (long)blockIdx.x * NW + (threadIdx.x >> 6);
+    const long units = (long)blocks * NW, u = (long)block * NW + (threadIdx.x >> 6);
     const long per = (p.tok.rows + units - 1) / units, z0 = min(p.tok.rows, u * per), z1 = min(p.tok.rows, z0 + per);
     const int lane = threadIdx.x & 63;
     zero_unselected_rows(p.dq, p.dqs, p.H * DH, p.tok.inv_pos, z0, z1, lane);
@@ -394,31 +395,64 @@ attn_bwd_long_bf16_kernel(const BwdArgs p, int nblk) {
   }
 }
 
+template <int DH, int MODE>
+__global__ void __launch_bounds__(kBwdThreads) __attribute__((amdgpu_waves_per_eu(DH == 32 ? 3 : 2)))
+attn_bwd_long_bf16_kernel(const BwdArgs p) {
+  bwd_long_block<DH, MODE>(p, blockIdx.x, gridDim.x);
+}
+
 // D[h][j] = <dO_j, O_j> over head h's columns, for the packed rows j < cu[B]: DH / 8 adjacent
 // lanes share a (row, head).
 template <int DH>
-__global__ void __launch_bounds__(256)
-attn_bwd_dvec_kernel(const __bf16* __restrict__ out, const __bf16* __restrict__ dout, const int32_t* __restrict__ cu,
-                     int B, int H, long lse_stride, float* __restrict__ dvec, const int32_t* __restrict__ gather_idx) {
+__device__ __forceinline__ void bwd_dvec_block(const BwdArgs& p, unsigned block, unsigned blocks) {
   constexpr int CPR = DH / 8;
-  const long C = (long)H * DH, total = (long)cu[B] * H * CPR;
-  for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < ((total + 63) & ~63L); i += (long)gridDim.x * 256) {
+  const int H = p.H;
+  const int32_t* gather_idx = p.tok.gather_idx;
+  const long C = (long)H * DH, total = (long)p.cu[p.B] * H * CPR;
+  for (long i = (long)block * 256 + threadIdx.x; i < ((total + 63) & ~63L); i += (long)blocks * 256) {
     const long rh = i / CPR;
     const int c = (int)(i % CPR);
     const long row = rh / H;
     const int h = (int)(rh % H);
     float d = 0.f;
     if (i < total) {
-      const floatx8 of = bf16x8_to_float(*reinterpret_cast<const bf16x8*>(out + row * C + h * DH + c * 8));
+      const floatx8 of = bf16x8_to_float(*reinterpret_cast<const bf16x8*>(p.out + row * C + h * DH + c * 8));
       const long grow = gather_idx != nullptr ? (long)gather_idx[row] : row;
-      const floatx8 gf = bf16x8_to_float(*reinterpret_cast<const bf16x8*>(dout + grow * C + h * DH + c * 8));
+      const floatx8 gf = bf16x8_to_float(*reinterpret_cast<const bf16x8*>(p.dout + grow * C + h * DH + c * 8));
 #pragma unroll
       for (int e = 0; e < 8; ++e) d = fmaf(of[e], gf[e], d);
     }
 #pragma unroll
     for (int o = 1; o < CPR; o <<= 1) d += __shfl_xor(d, o, kWave);
-    if (i < total && c == 0) dvec[h * lse_stride + row] = d;
+    if (i < total && c == 0) p.dvec[h * p.lse_stride + row] = d;
   }
+}
+template <int DH>
+__global__ void __launch_bounds__(256) attn_bwd_dvec_kernel(const BwdArgs p) {
+  bwd_dvec_block<DH>(p, blockIdx.x, gridDim.x);
+}
+
+// Several calls in one launch (launch groups, head dim 32, gradients at token positions): whatever the segment
+// lengths, the long-segment form (the short one's workgroups have the size of their segments).
+__global__ void __launch_bounds__(256) attn_bwd_dvec_group_kernel(const Members<BwdArgs> m) {
+  const MemberBlock mb = member_of(m, blockIdx.x);
+  bwd_dvec_block<32>(m.a[mb.s], mb.block, mb.blocks);
+}
+__global__ void __launch_bounds__(kBwdThreads) __attribute__((amdgpu_waves_per_eu(3)))
+attn_bwd_group_kernel(const Members<BwdArgs> m) {
+  const MemberBlock mb = member_of(m, blockIdx.x);
+  bwd_long_block<32, kTokens>(m.a[mb.s], mb.block, mb.blocks);
+}
+static thread_local Noted<BwdArgs> g_noted, g_noted_dvec;
+void group_forget_attention_bwd() { g_noted.n = g_noted_dvec.n = 0; }
+int group_flush_attention_bwd(hipStream_t st) {
+  if (g_noted.n == 0) return SPA_OK;
+  Members<BwdArgs> m;
+  const unsigned dblocks = g_noted_dvec.members(m);
+  hipLaunchKernelGGL(attn_bwd_dvec_group_kernel, dim3(dblocks), dim3(256), 0, st, m);
+  const unsigned blocks = g_noted.members(m);
+  hipLaunchKernelGGL(attn_bwd_group_kernel, dim3(blocks), dim3(kBwdThreads), 0, st, m);
+  return check_launch("spa_group_end");
 }
 
 // ------------------------------------------------- dQ, dK, dV in one kernel (short segments)
@@ -855,7 +889,7 @@ static int attention_bwd_common(const char* fn, const void* q, const void* k, co
   SPA_REQUIRE(softmax_scale >= 0.f && std::isfinite(softmax_scale), SPA_ERR_INVALID_ARG,
               "%s: softmax_scale must be finite and >= 0", fn);
   // short segments: the one-kernel form (option attn_bwd_short = "tiled" takes the long-segment kernel)
-  const bool short_seg = max_seqlen <= 256 && !options().bwd_tiled;
+  const bool short_seg = max_seqlen <= 256 && !options().bwd_tiled && !group_open();
   const bool one_kernel = dtype == SPA_BF16 && short_seg;
   const size_t need = one_kernel ? 0 : spa_attention_bwd_workspace_bytes(B, max_seqlen, H, Dh, dtype);
   SPA_REQUIRE(need == 0 || (workspace != nullptr && workspace_bytes >= need), SPA_ERR_WORKSPACE,
@@ -864,6 +898,8 @@ static int attention_bwd_common(const char* fn, const void* q, const void* k, co
   const long ls = (long)B * max_seqlen;
   float* dvec = static_cast<float*>(workspace);
   hipStream_t st = as_stream(stream);
+  SPA_REQUIRE(!group_open() || (dtype == SPA_BF16 && Dh == 32 && at_tokens && v_scores == nullptr), SPA_ERR_UNSUPPORTED,
+              "%s: this form cannot be part of a group", fn);
   if (dtype == SPA_F32) {
     const dim3 grid((max_seqlen + 127) / 128, H, B), block(128);
 #define SPA_BWD_F32(D)                                                                                        \
@@ -881,7 +917,7 @@ static int attention_bwd_common(const char* fn, const void* q, const void* k, co
     const BwdArgs args = {(const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_row_stride, (long)k_row_stride,
                           (long)v_row_stride, v_scores, (const __bf16*)out, (const __bf16*)dout, lse, ls, cu_seqlens, H, B,
                           scale, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, (long)dq_row_stride, (long)dk_row_stride,
-                          (long)dv_row_stride, tok, dvec};
+                          (long)dv_row_stride, tok, dvec, (max_seqlen + kBwdRows - 1) / kBwdRows};
     if (one_kernel) {
       const int nw = (max_seqlen + 31) / 32;
       SPA_REQUIRE((long)B * H < 2147483647L, SPA_ERR_INVALID_ARG, "%s: B*H must be < 2^31", fn);
@@ -902,20 +938,23 @@ static int attention_bwd_common(const char* fn, const void* q, const void* k, co
       return check_launch(fn);
     }
     // long segments: D first, then both roles in one launch
-    const int nblk = (max_seqlen + kBwdRows - 1) / kBwdRows;
+    const int nblk = args.nblk;
     SPA_REQUIRE(2 * ((long)H * B + 8) * nblk < 2147483647L, SPA_ERR_INVALID_ARG, "%s: B*H*blocks must be < 2^30", fn);
     const unsigned grid = 2 * xcd_grid(nblk, H, B);
     const unsigned dgrid = (unsigned)std::min<long>(((long)B * max_seqlen * H * (Dh / 8) + 255) / 256, 4096L);
-#define SPA_BWD_LONG(D)                                                                                          \
-  do {                                                                                                           \
-    hipLaunchKernelGGL((attn_bwd_dvec_kernel<D>), dim3(dgrid), dim3(256), 0, st, (const __bf16*)out,             \
-                       (const __bf16*)dout, cu_seqlens, B, H, ls, dvec, tok.gather_idx);                         \
-    if (v_scores != nullptr)                                                                                     \
-      hipLaunchKernelGGL((attn_bwd_long_bf16_kernel<D, kGated>), dim3(grid), dim3(kBwdThreads), 0, st, args, nblk);\
-    else if (at_tokens)                                                                                          \
-      hipLaunchKernelGGL((attn_bwd_long_bf16_kernel<D, kTokens>), dim3(grid), dim3(kBwdThreads), 0, st, args, nblk);\
-    else                                                                                                         \
-      hipLaunchKernelGGL((attn_bwd_long_bf16_kernel<D, kPacked>), dim3(grid), dim3(kBwdThreads), 0, st, args, nblk);\
+    if (group_open()) {
+      if (int rc = g_noted_dvec.add(fn, args, dgrid)) return rc;
+      return g_noted.add(fn, args, grid);
+    }
+#define SPA_BWD_LONG(D)                                                                                         \
+  do {                                                                                                          \
+    hipLaunchKernelGGL((attn_bwd_dvec_kernel<D>), dim3(dgrid), dim3(256), 0, st, args);                         \
+    if (v_scores != nullptr)                                                                                    \
+      hipLaunchKernelGGL((attn_bwd_long_bf16_kernel<D, kGated>), dim3(grid), dim3(kBwdThreads), 0, st, args);   \
+    else if (at_tokens)                                                                                         \
+      hipLaunchKernelGGL((attn_bwd_long_bf16_kernel<D, kTokens>), dim3(grid), dim3(kBwdThreads), 0, st, args);  \
+    else                                                                                                        \
+      hipLaunchKernelGGL((attn_bwd_long_bf16_kernel<D, kPacked>), dim3(grid), dim3(kBwdThreads), 0, st, args);  \
   } while (0)
     if (Dh == 32) SPA_BWD_LONG(32); else SPA_BWD_LONG(64);
 #undef SPA_BWD_LONG

@@ -19,6 +19,7 @@
 #include <type_traits>
 
 #include "attn_tiles.h"
+#include "group.h"
 #include "spa_common.h"
 
 namespace spa {
@@ -46,6 +47,20 @@ struct Scatter {
 __device__ __forceinline__ bool bypasses(const Scatter& sc, long row) {
   return sc.mask != nullptr ? sc.mask[row] == 0 : sc.inv_pos[row] < 0;
 }
+
+// Operands and results of the bf16 kernels that can share a launch.
+struct FwdArgs {
+  const __bf16 *q, *k, *v;
+  long qs, ks, vs;
+  const int32_t *cu, *key_lens;
+  int n_pad, H;
+  float scale_log2;
+  __bf16* out;
+  float* lse;
+  long lse_stride;
+  Scatter sc;
+  int B, nqb, ntile;
+};
 
 // Row of q / k / v that holds packed position j of a segment starting at packed row row0:
 // gi = gather_idx + row0 when the rows are gathered through the index, else null.
@@ -546,30 +561,32 @@ tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, c
 //     at most as many workgroups as are resident together, and number g of an XCD's G takes blocks g,
 //     2 G - 1 - g, 2 G + g, ...: the order is found once per workgroup;
 //   otherwise block qb of every (segment, head) pair in turn.
+template <int DH>
+struct TiledShared {
+  TiledLds<DH, kTiledBN> lds;
+  int s_cu[2 * kLptMaxB + 1];
+  int s_pick;
+};
 template <int DH, int NW, bool GATHER>
-__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH == 32 ? 3 : 2)))
-attn_fwd_bf16_tiled_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
-                           const __bf16* __restrict__ v, long qs, long ks, long vs,
-                           const int32_t* __restrict__ cu, const int32_t* __restrict__ key_lens, int n_pad,
-                           int H, float scale_log2, __bf16* __restrict__ out, float* __restrict__ lse,
-                           long lse_stride, Scatter sc, int B, int nqb, int ntile) {
-  __shared__ TiledLds<DH, kTiledBN> lds;
-  __shared__ int s_cu[2 * kLptMaxB + 1];
-  __shared__ int s_pick;
-
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  if ((int)blockIdx.x >= ntile) {
+__device__ __forceinline__ void tiled_block(TiledShared<DH>& sh, const FwdArgs& a, unsigned block, unsigned blocks) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, H = a.H, B = a.B;
+  const Scatter& sc = a.sc;
+  auto attend = [&](const Segment& seg, int h, int q0) {
+    tiled_attention<DH, NW, GATHER>(sh.lds, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, H, a.scale_log2, a.out, a.lse,
+                                    a.lse_stride, sc);
+  };
+  if ((int)block >= a.ntile) {
     const long rows = sc.flat ? (long)sc.N : (long)B * sc.N;
-    const long units = (long)(gridDim.x - ntile) * NW, u = (long)(blockIdx.x - ntile) * NW + wv, per = (rows + units - 1) / units;
+    const long units = (long)(blocks - a.ntile) * NW, u = (long)(block - a.ntile) * NW + wv, per = (rows + units - 1) / units;
     scatter_fill_rows<__bf16>(sc, min(rows, u * per), min(rows, (u + 1) * per), (long)H * DH, lane);
     return;
   }
-  if (key_lens == nullptr && live_tiles_apply(H, B)) {
-    const int xcd = blockIdx.x & 7, G = ntile >> 3, g = there_and_back(blockIdx.x >> 3, G);
-    int(*order)[64] = reinterpret_cast<int(*)[64]>(s_cu);
-    static_assert(sizeof(s_cu) >= 5 * 64 * sizeof(int), "holds the order");
+  if (a.key_lens == nullptr && live_tiles_apply(H, B)) {
+    const int xcd = block & 7, G = a.ntile >> 3, g = there_and_back(block >> 3, G);
+    int(*order)[64] = reinterpret_cast<int(*)[64]>(sh.s_cu);
+    static_assert(sizeof(sh.s_cu) >= 5 * 64 * sizeof(int), "holds the order");
     if (wv == 0) {
-      const LiveOrder o = live_order(xcd, H, B, cu, 32 * NW, nqb);
+      const LiveOrder o = live_order(xcd, H, B, a.cu, 32 * NW, a.nqb);
       order[0][lane] = o.len;
       order[1][lane] = o.start;
       order[2][lane] = o.img;
@@ -582,16 +599,21 @@ attn_fwd_bf16_tiled_kernel(const __bf16* __restrict__ q, const __bf16* __restric
       const LiveTile lt = live_pick(o, xcd, round * G + (round & 1 ? G - 1 - g : g), H);
       if (!lt.valid) return;
       if (round > 0) __syncthreads();                       // the parked rows are written
-      tiled_attention<DH, NW, GATHER>(lds, {lt.row0, lt.len, lt.len}, lt.h, lt.qb * (32 * NW), q, k, v, qs, ks, vs, H,
-                                      scale_log2, out, lse, lse_stride, sc);
+      attend({lt.row0, lt.len, lt.len}, lt.h, lt.qb * (32 * NW));
     }
   }
-  const TileId tile_id = xcd_tile(nqb, H, B);
+  const TileId tile_id = xcd_tile_at(block & 7, block >> 3, a.nqb, H, B);
   if (!tile_id.valid) return;
-  const Segment seg = lpt_segment<64 * NW>(tile_id.rank, B, cu, key_lens, n_pad, s_cu, &s_pick);
+  const Segment seg = lpt_segment<64 * NW>(tile_id.rank, B, a.cu, a.key_lens, a.n_pad, sh.s_cu, &sh.s_pick);
   const int q0 = tile_id.qb * (32 * NW);
-  if (q0 < seg.nq)
-    tiled_attention<DH, NW, GATHER>(lds, seg, tile_id.h, q0, q, k, v, qs, ks, vs, H, scale_log2, out, lse, lse_stride, sc);
+  if (q0 < seg.nq) attend(seg, tile_id.h, q0);
+}
+
+template <int DH, int NW, bool GATHER>
+__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH == 32 ? 3 : 2)))
+attn_fwd_bf16_tiled_kernel(const FwdArgs a) {
+  __shared__ TiledShared<DH> sh;
+  tiled_block<DH, NW, GATHER>(sh, a, blockIdx.x, gridDim.x);
 }
 
 // Short segments, wave-autonomous.  ONE wave per (image, head, 32-query block), no
@@ -613,7 +635,7 @@ wave_attention(__bf16* Ks, __bf16* Vs, const Segment seg, int h, int q0, const _
   constexpr int NSB = STEP / 32;                 // 32-key sub-tiles per step (one softmax update)
   constexpr int LPL = STEP * CPR / 64;           // 16-byte loads per lane per tensor per step
   const long C = (long)H * DH;
-  const int lane = threadIdx.x, l32 = lane & 31, hh = lane >> 5;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, hh = lane >> 5;
   const int qi = q0 + l32;
   const bool q_ok = qi < seg.nq;
   const __bf16* kh = k + h * DH;
@@ -724,39 +746,51 @@ attn_fwd_bf16_wave_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
 // q, k, v and of y), and the bypass fill tests the mask byte instead of inv_pos.  Costs four byte
 // loads and four ballots per wave where the other forms cost a kernel launch.
 template <int DH, int STEP>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
-attn_fwd_bf16_wave_mask_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
-                               const __bf16* __restrict__ v, long qs, long ks, long vs,
-                               const uint8_t* __restrict__ mask, int N, int H, float scale_log2, Scatter sc, int B,
-                               int nqb) {
-  constexpr int RS = DH + 8;
-  __shared__ __attribute__((aligned(16))) __bf16 Ks[STEP * RS];
-  __shared__ __attribute__((aligned(16))) __bf16 Vs[STEP * RS];
-  __shared__ int32_t list[256];
-
-  const TileId tile_id = xcd_tile(nqb, H, B);
+struct WaveLds {
+  static constexpr int RS = DH + 8;
+  __attribute__((aligned(16))) __bf16 Ks[STEP * RS];
+  __attribute__((aligned(16))) __bf16 Vs[STEP * RS];
+};
+template <int DH, int STEP>
+struct MaskLds {
+  WaveLds<DH, STEP> kv;
+  int32_t list[256];
+};
+// Unit j of XCD xcd, one wave (N <= 256 tokens per image, mask and fill of y: a.sc)
+template <int DH, int STEP>
+__device__ __forceinline__ void mask_unit(MaskLds<DH, STEP>& lds, const FwdArgs& a, int xcd, int j) {
+  const TileId tile_id = xcd_tile_at(xcd, j, a.nqb, a.H, a.B);
   if (!tile_id.valid) return;
-  const int h = tile_id.h, img = tile_id.rank, lane = threadIdx.x;
+  const int h = tile_id.h, img = tile_id.rank, lane = threadIdx.x & 63, N = a.sc.N;
   const long tok0 = (long)img * N;
   int n = 0;                                       // survivors of the image so far
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int t = lane + 64 * i;
-    const bool sel = t < N && mask[tok0 + t] != 0;
+    const bool sel = t < N && a.sc.mask[tok0 + t] != 0;
     const uint64_t bal = __ballot(sel);
-    if (sel) list[n + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u))] = (int32_t)(tok0 + t);
+    if (sel) lds.list[n + lanes_below(bal)] = (int32_t)(tok0 + t);
     n += __popcll(bal);
   }
-  __syncthreads();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
   const Segment seg = {0, n, n};                   // packed rows numbered inside the image: row j <-> list[j]
-  Scatter scl = sc;
-  scl.gather_idx = list;
-  const long C = (long)H * DH;
-  const FillRange fr = fill_range(sc, img, B, tile_id.qb, nqb);
+  Scatter scl = a.sc;
+  scl.gather_idx = lds.list;
+  const long C = (long)a.H * DH;
+  const FillRange fr = fill_range(a.sc, img, a.B, tile_id.qb, a.nqb);
   const int q0 = tile_id.qb * 32;
   if (q0 < n)
-    wave_attention<DH, STEP, true>(Ks, Vs, seg, h, q0, q, k, v, qs, ks, vs, H, scale_log2, nullptr, nullptr, 0, scl);
-  scatter_fill<__bf16, DH>(sc, fr.b, fr.t0, fr.t1, h, C, lane, 64);
+    wave_attention<DH, STEP, true>(lds.kv.Ks, lds.kv.Vs, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H, a.scale_log2,
+                                   nullptr, nullptr, 0, scl);
+  scatter_fill<__bf16, DH>(a.sc, fr.b, fr.t0, fr.t1, h, C, lane, 64);
+}
+
+template <int DH, int STEP>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
+attn_fwd_bf16_wave_mask_kernel(const FwdArgs a) {
+  __shared__ MaskLds<DH, STEP> lds;
+  mask_unit<DH, STEP>(lds, a, blockIdx.x & 7, blockIdx.x >> 3);
 }
 
 // The same work units, dealt to the compute units by weight (batches of up to 64 images, one
@@ -838,26 +872,58 @@ static unsigned lpt64_grid(int B, int H, int nqb) {
 // Compiled for three waves per SIMD (168 registers at head dim 64, no spills): a ViT-B-shaped
 // batch has ~2800 live waves for 1024 SIMDs and then runs in one round instead of two.
 template <int DH, int STEP, bool GATHER>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
-attn_fwd_bf16_wave_lpt64_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
-                                const __bf16* __restrict__ v, long qs, long ks, long vs,
-                                const int32_t* __restrict__ cu, const int32_t* __restrict__ key_lens, int n_pad,
-                                int H, float scale_log2, __bf16* __restrict__ out, float* __restrict__ lse,
-                                long lse_stride, Scatter sc, int B, int nqb) {
-  constexpr int RS = DH + 8;
-  __shared__ __attribute__((aligned(16))) __bf16 Ks[STEP * RS];
-  __shared__ __attribute__((aligned(16))) __bf16 Vs[STEP * RS];
-  const int x = blockIdx.x & 7, j = blockIdx.x >> 3, unit = j & 31, m = j >> 5;
-  const LptBlock blk = lpt64_block<32>(cu, key_lens, n_pad, B, H, nqb, x, m * 32 + ((m & 1) ? 31 - unit : unit));
+__device__ __forceinline__ void lpt64_unit(WaveLds<DH, STEP>& lds, const FwdArgs& a, int x, int j, int units) {
+  const int unit = j & 31, m = j >> 5;
+  const LptBlock blk = lpt64_block<32>(a.cu, a.key_lens, a.n_pad, a.B, a.H, a.nqb, x, m * 32 + ((m & 1) ? 31 - unit : unit));
   if (blk.live)
-    wave_attention<DH, STEP, GATHER>(Ks, Vs, blk.seg, blk.h, blk.q0, q, k, v, qs, ks, vs, H, scale_log2, out, lse, lse_stride,
-                             sc);
-  if (sc.y != nullptr) {
-    const long rows = sc.flat ? (long)sc.N : (long)B * sc.N, per = (rows + gridDim.x - 1) / gridDim.x;
-    const long r0 = min(rows, blockIdx.x * per), r1 = min(rows, r0 + per);
-    scatter_fill_rows<__bf16>(sc, r0, r1, (long)H * DH, threadIdx.x);
+    wave_attention<DH, STEP, GATHER>(lds.Ks, lds.Vs, blk.seg, blk.h, blk.q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H,
+                                     a.scale_log2, a.out, a.lse, a.lse_stride, a.sc);
+  if (a.sc.y != nullptr) {
+    const long rows = a.sc.flat ? (long)a.sc.N : (long)a.B * a.sc.N, per = (rows + units - 1) / units, u = 8L * j + x;
+    scatter_fill_rows<__bf16>(a.sc, min(rows, u * per), min(rows, (u + 1) * per), (long)a.H * DH, threadIdx.x & 63);
   }
 }
+template <int DH, int STEP, bool GATHER>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
+attn_fwd_bf16_wave_lpt64_kernel(const FwdArgs a) {
+  __shared__ WaveLds<DH, STEP> lds;
+  lpt64_unit<DH, STEP, GATHER>(lds, a, blockIdx.x & 7, blockIdx.x >> 3, gridDim.x);
+}
+
+// Several calls in one launch (launch groups, head dim 32): the tiled blocks of those with more than 256 tokens
+// per image, four of the one-wave units of the others per workgroup.  GATHER: rows at token positions, the
+// small ones by their mask; otherwise packed rows.
+template <bool GATHER>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+attn_fwd_bf16_group_kernel(const Members<FwdArgs> m) {
+  constexpr int DH = 32, STEP = 32;
+  __shared__ union {
+    TiledShared<DH> tiled;
+    MaskLds<DH, STEP> wave[4];
+  } sh;
+  const MemberBlock mb = member_of(m, blockIdx.x);
+  const FwdArgs& a = m.a[mb.s];
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (a.ntile > 0) tiled_block<DH, 4, GATHER>(sh.tiled, a, mb.block, mb.blocks);
+  else if constexpr (GATHER) mask_unit<DH, STEP>(sh.wave[wv], a, mb.block & 7, (mb.block >> 3) * 4 + wv);
+  else lpt64_unit<DH, STEP, false>(sh.wave[wv].kv, a, mb.block & 7, (mb.block >> 3) * 4 + wv, mb.blocks * 4);
+}
+
+static thread_local Noted<FwdArgs> g_noted[2];       // packed, gathered
+void group_forget_attention() { g_noted[0].n = g_noted[1].n = 0; }
+int group_flush_attention(hipStream_t st) {
+  Members<FwdArgs> m;
+  if (g_noted[0].n > 0) {
+    const unsigned blocks = g_noted[0].members(m);
+    hipLaunchKernelGGL((attn_fwd_bf16_group_kernel<false>), dim3(blocks), dim3(256), 0, st, m);
+  }
+  if (g_noted[1].n > 0) {
+    const unsigned blocks = g_noted[1].members(m);
+    hipLaunchKernelGGL((attn_fwd_bf16_group_kernel<true>), dim3(blocks), dim3(256), 0, st, m);
+  }
+  return check_launch("spa_group_end");
+}
+static unsigned wave_groups(unsigned waves) { return (waves / 8 + 3) / 4 * 8; }      // workgroups of four one-wave units
 
 // Short segments (every segment <= NKMAX keys).  ONE workgroup per (image, head): all K / V
 // rows of the segment are staged once (each element is read from memory exactly once per
@@ -1111,6 +1177,7 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
   const long lse_stride = (long)B * n_max;
   hipStream_t st = as_stream(stream);
   if (dtype == SPA_F32) {
+    SPA_REQUIRE(!group_open(), SPA_ERR_UNSUPPORTED, "%s: fp32 calls cannot be part of a group", fn);
     const int nqb = (n_max + 31) / 32;
     const dim3 grid(xcd_grid(nqb, H, B)), block(64);
 #define SPA_F32_LAUNCH(D)                                                                                \
@@ -1121,9 +1188,29 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
 #undef SPA_F32_LAUNCH
   } else {
     const float scale_log2 = scale * 1.4426950408889634f;
+    FwdArgs args = {(const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_stride, (long)k_stride, (long)v_stride, cu,
+                    key_lens, n_max, H, scale_log2, (__bf16*)out, lse, lse_stride, sc, B, 0, 0};
+    const auto live = [&] { return key_lens == nullptr && live_tiles_apply(H, B); };
+    // the tiled kernel's workgroups: resident together 3 waves per SIMD at head dim 32, 2 at 64
+    const auto tiled_grid = [&] {
+      args.nqb = (n_max + 127) / 128;
+      const long all = xcd_grid(args.nqb, H, B);
+      args.ntile = (int)(live() ? std::min<long>(all, (Dh == 32 ? 3 : 2) * 256) : all);
+      const long rows = sc.y == nullptr ? 0 : sc.flat ? (long)sc.N : (long)B * sc.N;
+      return (unsigned)(args.ntile + std::min<long>((rows + 31) / 32, 1024));
+    };
+    if (group_open()) {
+      SPA_REQUIRE(Dh == 32 && key_lens == nullptr && (n_max > 256 || (!sc.gathered && B <= kWave)), SPA_ERR_UNSUPPORTED,
+                  "%s: this form cannot be part of a group", fn);
+      if (n_max > 256) {
+        const unsigned blocks = tiled_grid();
+        return g_noted[sc.gathered].add(fn, args, (blocks + 7) / 8 * 8);
+      }
+      args.nqb = (n_max + 31) / 32;
+      return g_noted[0].add(fn, args, wave_groups(lpt64_grid(B, H, args.nqb)));
+    }
 #define SPA_ARGS_PLAIN SPA_ARGS
 #define SPA_ARGS_BN SPA_ARGS, B, nqb
-#define SPA_ARGS_TILED SPA_ARGS, B, nqb, (int)ntile
 #define SPA_LAUNCH(KERNEL, GRID, BLOCK, ARGS, ...)                                                            \
   do {                                                                                                        \
     if (sc.gathered) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, true>), GRID, BLOCK, 0, st, ARGS);               \
@@ -1146,8 +1233,9 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
       const bool step64 = opt.fwd_step64, plain = opt.fwd_plain;
       if (!step64 && !plain && B <= kWave) {
         const dim3 lgrid(lpt64_grid(B, H, nqb));
-        if (Dh == 32) SPA_LAUNCH(attn_fwd_bf16_wave_lpt64_kernel, lgrid, dim3(64), SPA_ARGS_BN, 32, 32);
-        else SPA_LAUNCH(attn_fwd_bf16_wave_lpt64_kernel, lgrid, dim3(64), SPA_ARGS_BN, 64, 32);
+        args.nqb = nqb;
+        if (Dh == 32) SPA_LAUNCH(attn_fwd_bf16_wave_lpt64_kernel, lgrid, dim3(64), args, 32, 32);
+        else SPA_LAUNCH(attn_fwd_bf16_wave_lpt64_kernel, lgrid, dim3(64), args, 64, 32);
       } else if (Dh == 32) {
         if (step64) SPA_LAUNCH(attn_fwd_bf16_wave_kernel, grid, dim3(64), SPA_ARGS_BN, 32, 64);
         else SPA_LAUNCH(attn_fwd_bf16_wave_kernel, grid, dim3(64), SPA_ARGS_BN, 32, 32);
@@ -1167,20 +1255,13 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
       if (Dh == 32) SPA_WHOLE(32); else SPA_WHOLE(64);
 #undef SPA_WHOLE
     } else {
-      constexpr int kNW = 4;
-      const int nqb = (n_max + 32 * kNW - 1) / (32 * kNW);
-      const bool live = key_lens == nullptr && live_tiles_apply(H, B);
-      // resident together: 3 waves per SIMD at head dim 32, 2 at 64
-      const long all = xcd_grid(nqb, H, B), ntile = live ? std::min<long>(all, (Dh == 32 ? 3 : 2) * 256) : all;
-      const long rows = sc.y == nullptr ? 0 : sc.flat ? (long)sc.N : (long)B * sc.N;
-      const dim3 grid((unsigned)(ntile + std::min<long>((rows + 31) / 32, 1024))), block(64 * kNW);
-      if (Dh == 32) SPA_LAUNCH(attn_fwd_bf16_tiled_kernel, grid, block, SPA_ARGS_TILED, 32, kNW);
-      else SPA_LAUNCH(attn_fwd_bf16_tiled_kernel, grid, block, SPA_ARGS_TILED, 64, kNW);
+      const dim3 grid(tiled_grid());
+      if (Dh == 32) SPA_LAUNCH(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 32, 4);
+      else SPA_LAUNCH(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 64, 4);
     }
 #undef SPA_ARGS
 #undef SPA_ARGS_PLAIN
 #undef SPA_ARGS_BN
-#undef SPA_ARGS_TILED
 #undef SPA_LAUNCH
   }
   return check_launch(fn);
@@ -1266,6 +1347,7 @@ extern "C" int spa_selected_attention_unpack(const void* q, const void* k, const
   const int nqb = (N + 31) / 32;
   const dim3 grid(xcd_grid(nqb, H, B)), block(64);
   if (dtype == SPA_F32) {
+    SPA_REQUIRE(!group_open(), SPA_ERR_UNSUPPORTED, "%s: fp32 calls cannot be part of a group", fn);
     if (Dh == 32)
       hipLaunchKernelGGL((attn_fwd_f32_kernel<32>), grid, block, 0, as_stream(stream), (const float*)q, (const float*)k,
                          (const float*)v, (long)q_row_stride, (long)k_row_stride, (long)v_row_stride, nullptr, nullptr, N,
@@ -1276,12 +1358,14 @@ extern "C" int spa_selected_attention_unpack(const void* q, const void* k, const
                          H, scale, (float*)nullptr, (float*)nullptr, 0L, sc, B, nqb);
     return check_launch(fn);
   }
-#define SPA_SEL(D)                                                                                              \
-  hipLaunchKernelGGL((attn_fwd_bf16_wave_mask_kernel<D, 32>), grid, block, 0, as_stream(stream), (const __bf16*)q, \
-                     (const __bf16*)k, (const __bf16*)v, (long)q_row_stride, (long)k_row_stride, (long)v_row_stride,    \
-                     mask, N, H, scale_log2, sc, B, nqb)
-  if (Dh == 32) SPA_SEL(32); else SPA_SEL(64);
-#undef SPA_SEL
+  const FwdArgs args = {(const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_row_stride, (long)k_row_stride,
+                        (long)v_row_stride, nullptr, nullptr, N, H, scale_log2, nullptr, nullptr, 0L, sc, B, nqb, 0};
+  if (group_open()) {
+    SPA_REQUIRE(Dh == 32, SPA_ERR_UNSUPPORTED, "%s: this form cannot be part of a group", fn);
+    return g_noted[1].add(fn, args, wave_groups(grid.x));
+  }
+  if (Dh == 32) hipLaunchKernelGGL((attn_fwd_bf16_wave_mask_kernel<32, 32>), grid, block, 0, as_stream(stream), args);
+  else hipLaunchKernelGGL((attn_fwd_bf16_wave_mask_kernel<64, 32>), grid, block, 0, as_stream(stream), args);
   return check_launch(fn);
 }
 

@@ -2,9 +2,11 @@
 // that resizes up-scale scores, and the gate backward with the selection loss
 // (Section 3.3).  All kernels are bandwidth-bound: every feature row is read once with
 // 16-byte loads, a group of G lanes per token, fp32 accumulation.
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
+#include "group.h"
 #include "spa_common.h"
 
 namespace spa {
@@ -274,6 +276,144 @@ gate_select_kernel(const T* __restrict__ x, const T* __restrict__ w, float bias,
   }
 }
 
+// ---- the gates of a hierarchy in one launch (launch groups) -----------------------------------
+// Stage i's score is the larger of its own gate and the 2x2 max-pooled scores of stage i - 1 (twice as fine).  A
+// workgroup takes kPyramidTokens / 4^(L-1) neighbouring tokens of the coarsest of the L stages and every token of the
+// finer ones that they cover: the rows of all of them are independent loads and dot products, and the scores a
+// stage hands to the next stay in LDS.  Each token's sum is the one gate_select_kernel forms, lane for lane.
+// Four dependent launches of 4-5 us each for 20 MB of rows before; see spa_group_begin.
+struct GateStage {
+  const __bf16 *x, *w;
+  float bias, theta;
+  int ntok, N, C, gw;              // gw: 0 for the finest stage
+  const float* s_up;
+  float *scores, *s_up_pooled;
+  uint8_t* mask;
+};
+constexpr int kPyramidTokens = 64;                       // of the finest stage, per workgroup
+struct PyramidArgs {
+  GateStage st[kGroupMax];
+  int L;
+};
+// Dot products of tokens 0 .. n-1 (rows named by at(i)) with w into out[], by the groups of G lanes of `threads`
+// threads, this one being number `tid`: U tokens of a group and K chunks of each in flight together.
+template <int G, int U, int K, class At>
+__device__ __forceinline__ void pyramid_dots(const GateStage& s, int n, float* out, int tid, int threads, At at) {
+  constexpr int VE = 8;
+  const int grp = tid / G, gl = tid % G, groups = threads / G, chunks = s.C / VE;
+  for (int i0 = grp; i0 < n; i0 += groups * U) {
+    const __bf16* row[U];
+    float acc[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      row[u] = s.x + (long)at(min(i0 + u * groups, n - 1)) * s.C;
+      acc[u] = 0.f;
+    }
+    for (int c0 = gl; c0 < chunks; c0 += G * K) {
+      bf16x8 f[K][U], wv[K];
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const int ch = min(c0 + k * G, chunks - 1);          // (past the row: a chunk again, not added)
+#pragma unroll
+        for (int u = 0; u < U; ++u) f[k][u] = *reinterpret_cast<const bf16x8*>(row[u] + ch * VE);
+        wv[k] = *reinterpret_cast<const bf16x8*>(s.w + ch * VE);
+      }
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if (k == 0 || c0 + k * G < chunks) {
+          const floatx8 wf = bf16x8_to_float(wv[k]);
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const floatx8 xf = bf16x8_to_float(f[k][u]);
+#pragma unroll
+            for (int e = 0; e < VE; ++e) acc[u] = fmaf(xf[e], wf[e], acc[u]);
+          }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float d = group_sum<G>(acc[u]);
+      if (gl == 0 && i0 + u * groups < n) out[i0 + u * groups] = d;
+    }
+  }
+}
+// Lanes per token: by the row's 16-byte chunks (the same for every launch of the gate)
+__host__ __device__ constexpr int gate_lanes(int chunks) { return chunks <= 8 ? 8 : chunks <= 64 ? 16 : chunks <= 256 ? 32 : 64; }
+
+__global__ void __launch_bounds__(kGateThreads) gate_pyramid_kernel(const PyramidArgs p) {
+  __shared__ float s_score[2 * kPyramidTokens];          // the stages one after the other: 64 + 16 + 4 + 1 tokens, or fewer
+  __shared__ int s_pos[kPyramidTokens / 4][3];           // image, row and column of the coarsest tokens
+  const int L = p.L, R = kPyramidTokens >> (2 * (L - 1));                    // R coarsest tokens
+  const GateStage& c = p.st[L - 1];
+  const unsigned c0 = blockIdx.x * R;
+  const int live = min(R, c.ntok - (int)c0);             // of them inside the batch
+  if ((int)threadIdx.x < live) {
+    const unsigned ct = c0 + threadIdx.x, b = ct / (unsigned)c.N, n = ct - b * c.N, y = n / (unsigned)c.gw;
+    s_pos[threadIdx.x][0] = b;
+    s_pos[threadIdx.x][1] = y;
+    s_pos[threadIdx.x][2] = n - y * c.gw;
+  }
+  __syncthreads();
+  // flat token of stage i that is number k of the workgroup's: k = (coarsest token, row, column inside its square)
+  auto token = [&](int i, int k) {
+    const int sh = L - 1 - i;
+    const int* pos = s_pos[k >> (2 * sh)];
+    const int in = k & ((1 << (2 * sh)) - 1), y = (pos[1] << sh) + (in >> sh), x = (pos[2] << sh) + (in & ((1 << sh) - 1));
+    return pos[0] * p.st[i].N + y * (c.gw << sh) + x;
+  };
+  // the finest stage to two waves, the next to one (two stages: two), the rest to the last
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  int from = 0;
+  for (int i = 0; i < L; ++i) {
+    const GateStage& s = p.st[i];
+    const int n = live << (2 * (L - 1 - i));
+    const int w0 = i == 0 ? 0 : i == 1 ? 2 : 3, nw = i == 0 || L == 2 ? 2 : 1;
+    if (wave >= w0 && wave < w0 + nw) {
+      const int tid = threadIdx.x - w0 * kWave, nt = nw * kWave, chunks = s.C / 8;
+      float* out = s_score + from;
+      auto row = [&](int k) { return token(i, k); };
+      switch (gate_lanes(chunks)) {
+        case 8: pyramid_dots<8, 8, 1>(s, n, out, tid, nt, row); break;
+        case 16:
+          if (chunks <= 16) pyramid_dots<16, 8, 1>(s, n, out, tid, nt, row);
+          else if (chunks <= 32) pyramid_dots<16, 4, 2>(s, n, out, tid, nt, row);
+          else pyramid_dots<16, 2, 4>(s, n, out, tid, nt, row);
+          break;
+        case 32: pyramid_dots<32, 2, 4>(s, n, out, tid, nt, row); break;
+        default: pyramid_dots<64, 2, 4>(s, n, out, tid, nt, row); break;
+      }
+    }
+    from += n;
+  }
+  __syncthreads();
+  const float* finer = s_score;
+  float* mine = s_score;
+  for (int i = 0; i < L; ++i) {
+    const GateStage& s = p.st[i];
+    const int sh = L - 1 - i, n = live << (2 * sh);
+    for (int k = threadIdx.x; k < n; k += kGateThreads) {
+      float v = mine[k] + s.bias;
+      const int tok = token(i, k);
+      if (i > 0) {
+        // children: a square twice as wide, same coarsest token
+        const int in = k & ((1 << (2 * sh)) - 1), y = in >> sh, x = in & ((1 << sh) - 1), wide = 2 << sh;
+        const float* f = finer + ((k >> (2 * sh)) << (2 * sh + 2)) + 2 * y * wide + 2 * x;
+        const float up = fmaxf(fmaxf(f[0], f[1]), fmaxf(f[wide], f[wide + 1]));
+        if (s.s_up_pooled != nullptr) s.s_up_pooled[tok] = up;
+        v = fmaxf(v, up);
+      }
+      s.scores[tok] = v;
+      s.mask[tok] = v > s.theta ? 1 : 0;
+      mine[k] = v;
+    }
+    finer = mine;
+    mine += n;
+    __syncthreads();
+  }
+}
+
+static thread_local Noted<GateStage> g_noted;
+
 // counts[b] = selected tokens of image b: one workgroup per image, no atomics.
 __global__ void __launch_bounds__(256)
 count_selected_kernel(const uint8_t* __restrict__ mask, int N, int32_t* __restrict__ counts) {
@@ -334,17 +474,33 @@ __device__ __forceinline__ void widen(bf16x8 v, float (&f)[8]) {
   for (int i = 0; i < 8; ++i) f[i] = w[i];
 }
 
+template <typename T>
+struct GateBwdArgs {
+  const T *x, *w;
+  float bias;
+  const float *scores, *s_up;
+  const uint8_t* labels;
+  const T* d_rg;
+  int gate_scaled;
+  float loss_scale;
+  StraightThrough st;
+  int ntok, C;
+  T* dx;
+  float* partial;
+};
 template <typename T, int G, int IT, int U>
-__global__ void __launch_bounds__(kGateThreads)
-gate_bwd_kernel(const T* __restrict__ x, const T* __restrict__ w, float bias,
-                const float* __restrict__ scores, const float* __restrict__ s_up,
-                const uint8_t* __restrict__ labels, const T* __restrict__ d_rg, int gate_scaled,
-                float loss_scale, StraightThrough st, int ntok, int C, T* __restrict__ dx,
-                float* __restrict__ partial) {
+__device__ __forceinline__ void gate_bwd_block(const GateBwdArgs<T>& a, unsigned block, unsigned blocks, float* lds) {
   constexpr int VE = Vec16<T>::kElems, kGroups = kGateThreads / G, kWaves = kGateThreads / kWave;
   using Raw = typename Raw16<T>::type;
-  extern __shared__ float lds[];                       // [kWaves][C]
   __shared__ float s_loss[kWaves], s_db[kWaves];
+  const T *x = a.x, *w = a.w, *d_rg = a.d_rg;
+  const float *scores = a.scores, *s_up = a.s_up;
+  const uint8_t* labels = a.labels;
+  const float bias = a.bias, loss_scale = a.loss_scale;
+  const StraightThrough st = a.st;
+  const int ntok = a.ntok, C = a.C, gate_scaled = a.gate_scaled;
+  T* dx = a.dx;
+  float* partial = a.partial;
 
   const int grp = threadIdx.x / G, gl = threadIdx.x % G;
   const int chunks = C / VE;
@@ -361,8 +517,8 @@ gate_bwd_kernel(const T* __restrict__ x, const T* __restrict__ w, float bias,
   }
   float loss_acc = 0.f, db_acc = 0.f;
 
-  const long per = ((long)ntok + gridDim.x - 1) / gridDim.x;
-  const long t0 = blockIdx.x * per, t1 = min((long)ntok, t0 + per);
+  const long per = ((long)ntok + blocks - 1) / blocks;
+  const long t0 = block * per, t1 = min((long)ntok, t0 + per);
   for (long base = t0 + grp; base < t1; base += kGroups * U) {
     Raw xr[U][IT], dr[U][IT];
     float s[U], up[U], nz[U];
@@ -462,7 +618,7 @@ gate_bwd_kernel(const T* __restrict__ x, const T* __restrict__ w, float bias,
   }
   if ((threadIdx.x & (kWave - 1)) == 0) { s_loss[wv_id] = loss_acc; s_db[wv_id] = db_acc; }
   __syncthreads();
-  float* prow = partial + (long)blockIdx.x * (C + 2);
+  float* prow = partial + (long)block * (C + 2);
   for (int c = threadIdx.x; c < C; c += kGateThreads) {
     float a = 0.f;
 #pragma unroll
@@ -478,16 +634,40 @@ gate_bwd_kernel(const T* __restrict__ x, const T* __restrict__ w, float bias,
   }
 }
 
+// LDS: 4 rows of C floats
+template <typename T, int G, int IT, int U>
+__global__ void __launch_bounds__(kGateThreads) gate_bwd_kernel(const GateBwdArgs<T> a) {
+  extern __shared__ float lds[];
+  gate_bwd_block<T, G, IT, U>(a, blockIdx.x, gridDim.x, lds);
+}
+// Several calls in one launch (launch groups): the forms of launch_gate_bwd, up to 1024 columns
+__global__ void __launch_bounds__(kGateThreads) gate_bwd_group_kernel(const Members<GateBwdArgs<__bf16>> m) {
+  extern __shared__ float lds[];
+  const MemberBlock mb = member_of(m, blockIdx.x);
+  const GateBwdArgs<__bf16>& a = m.a[mb.s];
+  const int chunks = a.C / 8;
+  if (chunks <= 16) gate_bwd_block<__bf16, 16, 1, 4>(a, mb.block, mb.blocks, lds);
+  else if (chunks <= 32) gate_bwd_block<__bf16, 32, 1, 4>(a, mb.block, mb.blocks, lds);
+  else if (chunks <= 64) gate_bwd_block<__bf16, 64, 1, 4>(a, mb.block, mb.blocks, lds);
+  else gate_bwd_block<__bf16, 64, 2, 4>(a, mb.block, mb.blocks, lds);
+}
+
 // Adds the partial rows in a fixed order: a block owns 16 columns; 64 row slices run in parallel
 // (slice s adds rows s, s+64, ..., at most 8 of them, whose loads are all in flight at once), then the
 // slices of a wave are added by exchanges and the waves in order.
 constexpr int kGateBwdMaxParts = 512;
-__global__ void __launch_bounds__(1024)
-gate_bwd_reduce_kernel(const float* __restrict__ partial, int nparts, int C, float loss_scale,
-                       float* __restrict__ loss, float* __restrict__ dw, float* __restrict__ db) {
+struct GateReduceArgs {
+  const float* partial;
+  int nparts, C;
+  float loss_scale;
+  float *loss, *dw, *db;
+};
+__device__ __forceinline__ void gate_bwd_reduce_block(const GateReduceArgs& g, int block) {
+  const float* partial = g.partial;
+  const int nparts = g.nparts, C = g.C;
   __shared__ float red[16][17];
   const int cl = threadIdx.x & 15, sl = threadIdx.x >> 4;
-  const int c = blockIdx.x * 16 + cl;
+  const int c = block * 16 + cl;
   float v[kGateBwdMaxParts / 64];
 #pragma unroll
   for (int i = 0; i < kGateBwdMaxParts / 64; ++i) {
@@ -505,12 +685,34 @@ gate_bwd_reduce_kernel(const float* __restrict__ partial, int nparts, int C, flo
     float t = 0.f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) t += red[i][cl];
-    if (c < C) dw[c] = t;
-    else if (c == C) loss[0] = t * loss_scale;
-    else db[0] = t;
+    if (c < C) g.dw[c] = t;
+    else if (c == C) g.loss[0] = t * g.loss_scale;
+    else g.db[0] = t;
   }
 }
+__global__ void __launch_bounds__(1024) gate_bwd_reduce_kernel(const GateReduceArgs g) {
+  gate_bwd_reduce_block(g, blockIdx.x);
+}
+__global__ void __launch_bounds__(1024) gate_bwd_reduce_group_kernel(const Members<GateReduceArgs> m) {
+  const MemberBlock mb = member_of(m, blockIdx.x);
+  gate_bwd_reduce_block(m.a[mb.s], mb.block);
+}
 
+static thread_local Noted<GateBwdArgs<__bf16>> g_noted_bwd;
+static thread_local Noted<GateReduceArgs> g_noted_reduce;
+void group_forget_gates() { g_noted.n = g_noted_bwd.n = g_noted_reduce.n = 0; }
+int group_flush_gates_bwd(hipStream_t st) {
+  if (g_noted_bwd.n == 0) return SPA_OK;
+  int C = 0;
+  for (int i = 0; i < g_noted_bwd.n; ++i) C = std::max(C, g_noted_bwd.a[i].C);
+  Members<GateBwdArgs<__bf16>> m;
+  const unsigned blocks = g_noted_bwd.members(m);
+  hipLaunchKernelGGL(gate_bwd_group_kernel, dim3(blocks), dim3(kGateThreads), (kGateThreads / kWave) * C * sizeof(float), st, m);
+  Members<GateReduceArgs> r;
+  const unsigned rblocks = g_noted_reduce.members(r);
+  hipLaunchKernelGGL(gate_bwd_reduce_group_kernel, dim3(rblocks), dim3(1024), 0, st, r);
+  return check_launch("spa_group_end");
+}
 
 static int gate_bwd_parts(long ntok) {
   long p = (ntok + 15) / 16;
@@ -546,13 +748,41 @@ static int launch_gate(const char* fn, const void* x, const void* w, float bias,
                          static_cast<const T*>(x), static_cast<const T*>(w), bias, s_up, noise, theta,
                          (int)ntok, N, C, pool, scores, mask, idx);
   };
-  if (chunks <= 8) go(std::integral_constant<int, 8>{});
-  else if (chunks <= 64) go(std::integral_constant<int, 16>{});
-  else if (chunks <= 256) go(std::integral_constant<int, 32>{});
-  else go(std::integral_constant<int, 64>{});
+  switch (gate_lanes(chunks)) {
+    case 8: go(std::integral_constant<int, 8>{}); break;
+    case 16: go(std::integral_constant<int, 16>{}); break;
+    case 32: go(std::integral_constant<int, 32>{}); break;
+    default: go(std::integral_constant<int, 64>{}); break;
+  }
   if (counts != nullptr && idx.arrive == nullptr)
     hipLaunchKernelGGL(count_selected_kernel, dim3(B), dim3(256), 0, st, mask, N, counts);
   return check_launch(fn);
+}
+
+// The noted gates: one launch where each takes the scores of the one before it, else one by one, in order.
+int group_flush_gates(hipStream_t st) {
+  const Noted<GateStage>& g = g_noted;
+  bool chain = g.n >= 2 && g.a[0].gw == 0 && g.a[0].s_up == nullptr;
+  for (int i = 1; i < g.n; ++i)
+    chain = chain && g.a[i].gw > 0 && g.a[i].s_up == g.a[i - 1].scores && g.a[i - 1].N == 4 * g.a[i].N && g.a[i - 1].ntok == 4 * g.a[i].ntok &&
+            (i == 1 || g.a[i - 1].gw == 2 * g.a[i].gw);
+  if (chain) {
+    PyramidArgs p;
+    for (int i = 0; i < kGroupMax; ++i) p.st[i] = g.a[i < g.n ? i : g.n - 1];
+    p.L = g.n;
+    const long R = kPyramidTokens >> (2 * (g.n - 1)), wgs = (p.st[g.n - 1].ntok + R - 1) / R;
+    hipLaunchKernelGGL(gate_pyramid_kernel, dim3((unsigned)wgs), dim3(kGateThreads), 0, st, p);
+    return check_launch("spa_group_end");
+  }
+  for (int i = 0; i < g.n; ++i) {
+    const GateStage& s = g.a[i];
+    const bool pooled = s.gw > 0;
+    if (int rc = launch_gate<__bf16>("spa_group_end", s.x, s.w, s.bias, s.s_up, nullptr, s.theta, s.ntok / s.N, s.N, s.C,
+                                     PoolGrid{pooled ? s.N / s.gw : 0, s.gw, s.s_up_pooled}, pooled, s.scores, s.mask,
+                                     nullptr, st))
+      return rc;
+  }
+  return SPA_OK;
 }
 
 }  // namespace spa
@@ -578,6 +808,12 @@ static int gate_select_common(const char* fn, const void* x, const void* w, floa
   // sigmoid((s + e) / T) > tau  <=>  s + e > T * logit(tau)
   const float theta = (float)((double)temperature * std::log((double)tau / (1.0 - (double)tau)));
   hipStream_t st = as_stream(stream);
+  if (group_open()) {
+    SPA_REQUIRE(dtype == SPA_BF16 && noise == nullptr && counts == nullptr && idx.arrive == nullptr, SPA_ERR_UNSUPPORTED,
+                "%s: this form cannot be part of a group", fn);
+    return g_noted.add(fn, GateStage{static_cast<const __bf16*>(x), static_cast<const __bf16*>(w), bias, theta, B * N, N, C,
+                                     pooled ? pool.gw : 0, s_up, scores, pool.s_up_pooled, mask}, 0);
+  }
   if (dtype == SPA_F32)
     return launch_gate<float>(fn, x, w, bias, s_up, noise, theta, B, N, C, pool, pooled, scores, mask, counts, st, idx);
   return launch_gate<__bf16>(fn, x, w, bias, s_up, noise, theta, B, N, C, pool, pooled, scores, mask, counts, st, idx);
@@ -652,11 +888,20 @@ static int launch_gate_bwd(const void* x, const void* w, float bias, const float
   const int chunks = C / VE;
   const int parts = gate_bwd_parts(ntok);
   const size_t lds = (size_t)(kGateThreads / kWave) * C * sizeof(float);      // at most 64 KB (C <= 4096)
-#define SPA_GB(G, IT, U)                                                                                      \
-  hipLaunchKernelGGL((gate_bwd_kernel<T, G, IT, U>), dim3(parts), dim3(kGateThreads), lds, st,               \
-                     static_cast<const T*>(x), static_cast<const T*>(w), bias, scores, s_up, labels,         \
-                     static_cast<const T*>(d_rg), gate_scaled, loss_scale, stt, (int)ntok, C,                \
-                     static_cast<T*>(dx), partial)
+  const GateBwdArgs<T> args = {static_cast<const T*>(x), static_cast<const T*>(w), bias, scores, s_up, labels,
+                               static_cast<const T*>(d_rg), gate_scaled, loss_scale, stt, (int)ntok, C, static_cast<T*>(dx),
+                               partial};
+  const GateReduceArgs rargs = {partial, parts, C, loss_scale, loss, dw, db};
+  const unsigned rblocks = (C + 2 + 15) / 16;
+  if constexpr (sizeof(T) == 2) {
+    if (group_open()) {
+      SPA_REQUIRE(C <= 1024, SPA_ERR_UNSUPPORTED, "spa_gate_bwd: C = %d > 1024 cannot be part of a group", C);
+      if (int rc = g_noted_bwd.add("spa_gate_bwd", args, parts)) return rc;
+      return g_noted_reduce.add("spa_gate_bwd", rargs, rblocks);
+    }
+  }
+  SPA_REQUIRE(!group_open(), SPA_ERR_UNSUPPORTED, "spa_gate_bwd: fp32 calls cannot be part of a group");
+#define SPA_GB(G, IT, U) hipLaunchKernelGGL((gate_bwd_kernel<T, G, IT, U>), dim3(parts), dim3(kGateThreads), lds, st, args)
   if (chunks <= 16) SPA_GB(16, 1, 4);
   else if (chunks <= 32) SPA_GB(32, 1, 4);
   else if (chunks <= 64) SPA_GB(64, 1, 4);
@@ -665,8 +910,7 @@ static int launch_gate_bwd(const void* x, const void* w, float bias, const float
   else if (chunks <= 512) SPA_GB(64, 8, 1);
   else return fail(SPA_ERR_UNSUPPORTED, "spa_gate_bwd: C = %d too large (at most %d)", C, 512 * VE);
 #undef SPA_GB
-  hipLaunchKernelGGL(gate_bwd_reduce_kernel, dim3((C + 2 + 15) / 16), dim3(1024), 0, st, partial, parts, C,
-                     loss_scale, loss, dw, db);
+  hipLaunchKernelGGL(gate_bwd_reduce_kernel, dim3(rblocks), dim3(1024), 0, st, rargs);
   return check_launch("spa_gate_bwd");
 }
 

@@ -59,6 +59,7 @@ struct Entry {
 };
 #define ENTRY(fn) {#fn, Signature<decltype(&fn)>::kinds, &Signature<decltype(&fn)>::call}
 const Entry kEntries[] = {
+    ENTRY(spa_group_begin), ENTRY(spa_group_end),
     ENTRY(spa_gate_select), ENTRY(spa_gate_select_index), ENTRY(spa_gate_select_pooled), ENTRY(spa_gate_select_gumbel),
     ENTRY(spa_gate_bwd_straight_through), ENTRY(spa_maxpool2x2), ENTRY(spa_pack), ENTRY(spa_pack_pair),
     ENTRY(spa_pack_shifted), ENTRY(spa_container_segments), ENTRY(spa_packed_attention),

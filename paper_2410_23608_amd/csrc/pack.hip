@@ -8,6 +8,7 @@
 // wave ballots, and copies its survivors' rows to their final place.
 #include <cstdlib>
 
+#include "group.h"
 #include "spa_common.h"
 
 namespace spa {
@@ -115,22 +116,39 @@ __device__ __forceinline__ void copy_selected_rows(const T* __restrict__ xt, T* 
 // kShift: tokens are ranked in the raster order of the shifted map (Section 1: the feature
 // map is shifted so that the token pairs sharing a container vary); gather_idx / inv_pos keep
 // naming ORIGINAL positions, so the scatter back undoes the shift by itself.
+template <typename T>
+struct PackArgs {
+  const T* x;
+  const uint8_t* mask;
+  const int32_t* counts;
+  const float* gate_scores;
+  int B, N, C, tile, tiles_per_image, container_len;
+  Shift shift;
+  T* packed;
+  int32_t *cu_seqlens, *gather_idx, *inv_pos, *total;
+  const T* x2;
+  int C2;
+  T* packed2;
+};
 template <typename T, bool kScale, bool kShift, bool kPair>
-__global__ void __launch_bounds__(kPackThreads)
-pack_kernel(const T* __restrict__ x, const uint8_t* __restrict__ mask,
-            const int32_t* __restrict__ counts, const float* __restrict__ gate_scores,
-            int B, int N, int C, int tile, int tiles_per_image, int container_len, Shift shift,
-            T* __restrict__ packed, int32_t* __restrict__ cu_seqlens,
-            int32_t* __restrict__ gather_idx, int32_t* __restrict__ inv_pos,
-            int32_t* __restrict__ total, const T* __restrict__ x2, int C2, T* __restrict__ packed2) {
+__device__ __forceinline__ void pack_block(const PackArgs<T>& a, int block) {
   constexpr int VE = 16 / sizeof(T);
   __shared__ int red[kPackWaves];
   __shared__ int wave_cnt[kPackWaves];
   __shared__ int sel_src[kPackThreads];
   __shared__ float sel_scale[kPackThreads];
+  const T *x = a.x, *x2 = a.x2;
+  const uint8_t* mask = a.mask;
+  const int32_t* counts = a.counts;
+  const float* gate_scores = a.gate_scores;
+  const int B = a.B, N = a.N, C = a.C, C2 = a.C2, tile = a.tile, tiles_per_image = a.tiles_per_image;
+  const int container_len = a.container_len;
+  const Shift shift = a.shift;
+  T *packed = a.packed, *packed2 = a.packed2;
+  int32_t *cu_seqlens = a.cu_seqlens, *gather_idx = a.gather_idx, *inv_pos = a.inv_pos, *total = a.total;
 
-  const int b = blockIdx.x / tiles_per_image;
-  const int t = blockIdx.x % tiles_per_image;
+  const int b = block / tiles_per_image;
+  const int t = block % tiles_per_image;
   const int tile_start = t * tile;
   const int tile_n = min(tile, N - tile_start);
   const long img0 = (long)b * N;
@@ -198,6 +216,31 @@ pack_kernel(const T* __restrict__ x, const uint8_t* __restrict__ mask,
     copy_selected_rows<T, kScale && !kPair>(x + img0 * (long)C, packed + (long)base * C, C, nsel, sel_src, sel_scale, tid);
   if (kPair)
     copy_selected_rows<T, kScale>(x2 + img0 * (long)C2, packed2 + (long)base * C2, C2, nsel, sel_src, sel_scale, tid);
+}
+
+template <typename T, bool kScale, bool kShift, bool kPair>
+__global__ void __launch_bounds__(kPackThreads) pack_kernel(const PackArgs<T> a) {
+  pack_block<T, kScale, kShift, kPair>(a, blockIdx.x);
+}
+// Several calls in one launch (launch groups)
+template <bool kScale, bool kPair>
+__global__ void __launch_bounds__(kPackThreads) pack_group_kernel(const Members<PackArgs<__bf16>> m) {
+  const MemberBlock mb = member_of(m, blockIdx.x);
+  pack_block<__bf16, kScale, false, kPair>(m.a[mb.s], mb.block);
+}
+static thread_local Noted<PackArgs<__bf16>> g_noted[2];       // rows or index alone, pairs with a gated second row
+void group_forget_pack() { g_noted[0].n = g_noted[1].n = 0; }
+int group_flush_pack(hipStream_t st) {
+  Members<PackArgs<__bf16>> m;
+  if (g_noted[0].n > 0) {
+    const unsigned blocks = g_noted[0].members(m);
+    hipLaunchKernelGGL((pack_group_kernel<false, false>), dim3(blocks), dim3(kPackThreads), 0, st, m);
+  }
+  if (g_noted[1].n > 0) {
+    const unsigned blocks = g_noted[1].members(m);
+    hipLaunchKernelGGL((pack_group_kernel<true, true>), dim3(blocks), dim3(kPackThreads), 0, st, m);
+  }
+  return check_launch("spa_group_end");
 }
 
 // y[i] = base[i] (+ src[inv[i]]) or src[inv[i]] or 0.  A block owns `rpb` consecutive output
@@ -349,11 +392,17 @@ static int pack_common(const char* fn, const void* x, const uint8_t* mask, const
   SPA_REQUIRE((long)B * tpi < 2147483647L, SPA_ERR_INVALID_ARG, "%s: too many tiles", fn);
   const dim3 grid((unsigned)((long)B * tpi)), block(kPackThreads);
   hipStream_t st = as_stream(stream);
-#define SPA_PACK_LAUNCH(T, S, SH)                                                                        \
-  hipLaunchKernelGGL((pack_kernel<T, S, SH, false>), grid, block, 0, st, static_cast<const T*>(x), mask, counts, \
-                     gate_scores, B, N, C, tile, tpi, container_len, shift, static_cast<T*>(packed),     \
-                     cu_seqlens, gather_idx, inv_pos, total, static_cast<const T*>(nullptr), 0,          \
-                     static_cast<T*>(nullptr))
+#define SPA_PACK_ARGS(T)                                                                                       \
+  PackArgs<T> {                                                                                                \
+    static_cast<const T*>(x), mask, counts, gate_scores, B, N, C, tile, tpi, container_len, shift,             \
+        static_cast<T*>(packed), cu_seqlens, gather_idx, inv_pos, total, nullptr, 0, nullptr                   \
+  }
+  if (group_open()) {
+    SPA_REQUIRE(dtype == SPA_BF16 && !shifted && gate_scores == nullptr, SPA_ERR_UNSUPPORTED,
+                "%s: this form cannot be part of a group", fn);
+    return g_noted[0].add(fn, SPA_PACK_ARGS(__bf16), grid.x);
+  }
+#define SPA_PACK_LAUNCH(T, S, SH) hipLaunchKernelGGL((pack_kernel<T, S, SH, false>), grid, block, 0, st, SPA_PACK_ARGS(T))
 #define SPA_PACK_SCALE(T, SH)                                                                            \
   do {                                                                                                   \
     if (gate_scores) SPA_PACK_LAUNCH(T, true, SH); else SPA_PACK_LAUNCH(T, false, SH);                   \
@@ -365,6 +414,7 @@ static int pack_common(const char* fn, const void* x, const uint8_t* mask, const
   }
 #undef SPA_PACK_SCALE
 #undef SPA_PACK_LAUNCH
+#undef SPA_PACK_ARGS
   return check_launch(fn);
 }
 
@@ -392,16 +442,24 @@ extern "C" int spa_pack_pair(const void* x, int C, const void* x2, int C2, const
   const dim3 grid((unsigned)((long)B * tpi)), block(kPackThreads);
   hipStream_t st = as_stream(stream);
   const Shift shift{1, 1, 0, 0};
-#define SPA_PACK_PAIR(T, S)                                                                                    \
-  hipLaunchKernelGGL((pack_kernel<T, S, false, true>), grid, block, 0, st, static_cast<const T*>(x), mask, counts, \
-                     gate_scores, B, N, C, tile, tpi, 0, shift, static_cast<T*>(packed), cu_seqlens, gather_idx, \
-                     inv_pos, total, static_cast<const T*>(x2), C2, static_cast<T*>(packed2))
+#define SPA_PACK_ARGS(T)                                                                                       \
+  PackArgs<T> {                                                                                                \
+    static_cast<const T*>(x), mask, counts, gate_scores, B, N, C, tile, tpi, 0, shift, static_cast<T*>(packed), \
+        cu_seqlens, gather_idx, inv_pos, total, static_cast<const T*>(x2), C2, static_cast<T*>(packed2)        \
+  }
+  if (group_open()) {
+    SPA_REQUIRE(dtype == SPA_BF16 && gate_scores != nullptr, SPA_ERR_UNSUPPORTED,
+                "%s: this form cannot be part of a group", fn);
+    return g_noted[1].add(fn, SPA_PACK_ARGS(__bf16), grid.x);
+  }
+#define SPA_PACK_PAIR(T, S) hipLaunchKernelGGL((pack_kernel<T, S, false, true>), grid, block, 0, st, SPA_PACK_ARGS(T))
   if (dtype == SPA_F32) {
     if (gate_scores) SPA_PACK_PAIR(float, true); else SPA_PACK_PAIR(float, false);
   } else {
     if (gate_scores) SPA_PACK_PAIR(__bf16, true); else SPA_PACK_PAIR(__bf16, false);
   }
 #undef SPA_PACK_PAIR
+#undef SPA_PACK_ARGS
   return check_launch(fn);
 }
 

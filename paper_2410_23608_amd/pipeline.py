@@ -529,14 +529,17 @@ def _on_streams(per_stage, streams, stream_of):
     return out + [("join_streams", join)]
 
 
+def _groupable(cfg):
+    """Stages whose calls can share launches (spa_group_begin): 2 to 4 of them, bf16, heads of 32, at most 1024 columns and 64 images."""
+    return 2 <= len(cfg) <= 4 and all(c[5] == "bf16" and c[3] == 32 * c[4] and c[3] <= 1024 and c[0] <= 64 for c in cfg)
+
+
 class HierarchyPass(_Pass):
     """A multi-stage hierarchy (Section 3.1, Section 3.2 on multi-scale scores): every stage
     runs gate -> pack -> attention + scatter, and from the second stage on the gate takes the
     previous (2x finer) stage's score map, max-pooled inside the gate kernel, as s_up.
-    Three launches per stage (lean form: two for the coarse stages), no host sync anywhere in the chain.  (Everything on one stream:
-    spreading the stages over two or four streams was measured and is slower for the forward
-    chain, 129 and 166 us against 102 us; the events and the fork / join per chain cost more
-    than the overlap of the small coarse stages brings.)"""
+    The stages' gates, their packing and their attention are one launch each where _groupable says so
+    (three launches per chain), else two or three launches per stage; no host sync anywhere in the chain."""
 
     def __init__(self, stages, lean: bool = False):
         """stages: one (B, grid_h, grid_w, C, H, dtype, tau, bias) tuple per stage, finest
@@ -559,15 +562,20 @@ class HierarchyPass(_Pass):
 
     def stages(self, xs, ws, qkvs, bases=None) -> List[Tuple[str, Callable[[], None]]]:
         """xs, ws, qkvs: one tensor per stage.  Returns the chain as named prepared launches."""
-        out = []
+        per_stage = []
         for i, (fp, cfg) in enumerate(zip(self.passes, self.cfg)):
             st = fp.stages(xs[i], ws[i], qkvs[i], None, None if bases is None else bases[i])
             if i > 0:
                 st[0] = ("gate_select_pooled", spa.spa_gate_select_pooled(
                     xs[i], ws[i], fp.bias, self.passes[i - 1].scores, cfg[1], cfg[2], fp.tau, fp.scores, fp.mask,
                     None, self.s_up[i], prepare=True))
-            out += [(f"s{i + 1}.{name}", fn) for name, fn in st]
-        return out
+            per_stage.append(st)
+        if not _groupable(self.cfg):
+            return [(f"s{i + 1}.{name}", fn) for i, st in enumerate(per_stage) for name, fn in st]
+        packs = [st[1][1] for st in per_stage if len(st) == 3]
+        return [("gate_select", spa.group(*(st[0][1] for st in per_stage))),
+                *([("pack", spa.group(*packs))] if packs else []),
+                ("attention_unpack", spa.group(*(st[-1][1] for st in per_stage)))]
 
     def run(self, xs, ws, qkvs, bases=None):
         n = len(self.cfg)
@@ -578,8 +586,9 @@ class HierarchyPass(_Pass):
 
 class HierarchyTrainPass(_Pass):
     """Forward + backward of every stage of a hierarchy (TrainPass per stage); from the second
-    stage on the gate takes the finer stage's score map (pooled in the gate kernel).  All
-    forwards run first (a stage's gate needs the finer stage's scores), then all backwards.
+    stage on the gate takes the finer stage's score map (pooled in the gate kernel).  The same step of all
+    stages is one launch group where _groupable says so (seven launches per chain); else all forwards run
+    first (a stage's gate needs the finer stage's scores), then all backwards.
     The score map handed down is treated as a constant by the coarser stage's backward.
 
     concurrent=True: every stage runs forward and backward on a HIP stream of its own (default
@@ -595,16 +604,20 @@ class HierarchyTrainPass(_Pass):
         self.passes = [TrainPass(B, gh * gw, C, H, dtype, tau, bias) for (B, gh, gw, C, H, dtype, tau, bias) in self.cfg]
 
     def stages(self, xs, ws, qks, labels, dys) -> List[Tuple[str, Callable[[], None]]]:
-        fwd, bwd, chains = [], [], []
+        chains = []
         for i, (tp, cfg) in enumerate(zip(self.passes, self.cfg)):
             with torch.cuda.stream(self.streams[self.stream_of[i]] if self.concurrent else torch.cuda.current_stream()):
                 st = tp.stages(xs[i], ws[i], qks[i], labels[i], dys[i],
                                s_fine=self.passes[i - 1].scores if i > 0 else None, grid=(cfg[1], cfg[2]))
-            n_fwd = 3 if tp.pack_pair else 4      # gate, pack (one or two launches), attention + scatter
-            fwd += [(f"s{i + 1}.{n}", f) for n, f in st[:n_fwd]]
-            bwd += [(f"s{i + 1}.{n}", f) for n, f in st[n_fwd:]]
-            chains.append([(f"s{i + 1}.{n}", f) for n, f in st])
-        return _on_streams(chains, self.streams, self.stream_of) if self.concurrent else fwd + bwd
+            chains.append(st)
+        if not self.concurrent and _groupable(self.cfg) and all(tp.pack_pair and tp.fused_bwd for tp in self.passes):
+            # gate, pack, attention + scatter, attention backward, gate backward
+            return [(name, spa.group(*(st[j][1] for st in chains))) for j, (name, _) in enumerate(chains[0])]
+        chains = [[(f"s{i + 1}.{n}", f) for n, f in st] for i, st in enumerate(chains)]
+        if self.concurrent:
+            return _on_streams(chains, self.streams, self.stream_of)
+        n_fwd = [3 if tp.pack_pair else 4 for tp in self.passes]      # gate, pack (one or two launches), attention + scatter
+        return [c for st, n in zip(chains, n_fwd) for c in st[:n]] + [c for st, n in zip(chains, n_fwd) for c in st[n:]]
 
     def run(self, xs, ws, qks, labels, dys):
         n = len(self.cfg)

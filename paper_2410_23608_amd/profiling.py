@@ -7,8 +7,8 @@ into profiles/hbm_traffic_table.txt, the table bench.py reads its `roofline.traf
 
 <dir> is the -d directory of a `rocprofv3 ... --output-format csv -d <dir> -o p -- python3 bench.py --only ...`
 run (kernel-trace for `kernels`, one --pmc counter set for the others).  A chain names the calls of one
-step; every libspa kernel of the run is attributed to the call that launches it by its name, and for
-the multi-stage hierarchy to its stage by its grid size (finest stage = largest grid).
+step; every libspa kernel of the run is attributed to the call that launches it by its name (the
+multi-stage hierarchy: one launch per step for all stages).
 """
 from __future__ import annotations
 
@@ -36,7 +36,10 @@ CHAINS = {
     "train": [("gate_select_kernel", "gate_select"), ("pack_kernel", "pack_qk_rg"), ("attn_fwd", "packed_attention_unpack"),
               ("attn_bwd", "packed_attention_bwd_tokens"), ("gate_bwd", "gate_bwd")],
 }
-CHAINS["hierarchy"] = CHAINS["train"]
+CHAINS["hierarchy"] = [("gate_pyramid_kernel", "gate_select"), ("pack_group_kernel", "pack_qk_rg"),
+                       ("attn_fwd_bf16_group_kernel", "packed_attention_unpack"), ("attn_bwd_dvec_group", "packed_attention_bwd_tokens"),
+                       ("attn_bwd_group", "packed_attention_bwd_tokens"), ("gate_bwd_group", "gate_bwd"),
+                       ("gate_bwd_reduce_group", "gate_bwd")]
 # a whole bench.py run (every configuration and the extras): calls named by kind only
 CHAINS["all"] = [("gate_select_kernel", "gate"), ("count_selected", "gate"), ("pack_kernel", "pack"), ("unpack_kernel", "unpack"),
                  ("gather_rows", "unpack / pack backward"), ("attn_fwd", "attention forward"), ("attn_bwd", "attention backward"),
@@ -96,36 +99,15 @@ def grid_of(r) -> int:
 
 
 def call_of(name: str, chain: str):
-    if chain == "hierarchy":       # the run also holds the forward-only chain, whose stages use other attention forms
-        if "attn_fwd_bf16_wave_mask" in name:
-            return "selected_attention_unpack"
-        if re.search(r"attn_fwd_bf16_\w+_kernel(<[^>]*true>|I\w*Lb1EEE)", name):
+    if chain == "hierarchy":       # the run also holds the forward-only chain
+        if "pack_group_kernel<false, false>" in short(name):
+            return "pack_indices"
+        if "attn_fwd_bf16_group_kernel<true>" in short(name):
             return "gathered_attention_unpack"
     for sub, call in CHAINS[chain]:
         if sub in name:
             return call
     return None
-
-
-def stage_labels(groups, chain):
-    """hierarchy: (call, grid) groups -> 's<k>.call' with k by descending grid among the groups whose
-    kernel shares a name; other chains: the call itself."""
-    if chain != "hierarchy":
-        return {g: g[1] for g in groups}
-    by_family = defaultdict(list)                 # instances of one kernel template differ by stage (lanes per token)
-    for g in groups:
-        by_family[(g[1], g[0].split("<")[0])].append(g)
-    labels = {}
-    for (_, family), gs in by_family.items():
-        # a stage = a distinct grid size; the gate backward picks its instance (tokens per workgroup) by the
-        # stage's C and two of them launch the same grid, so there the instance tells the stages apart
-        key = lambda g: (-g[2], g[0] if family == "gate_bwd_kernel" else "")
-        ranks = sorted({key(g) for g in gs})
-        # kernels of the long-segment forms serve the two finest stages, the short forms the two coarsest
-        first = 3 if (("wave" in family or "fused" in family) and len(ranks) <= 2) else 1     # (wave: lpt64 and mask kernels)
-        for g in gs:
-            labels[g] = f"s{first + ranks.index(key(g))}.{g[1]}"
-    return labels
 
 
 def cmd_kernels(a):
@@ -134,7 +116,6 @@ def cmd_kernels(a):
     for r in rows:
         groups[(short(r["Kernel_Name"]), call_of(r["Kernel_Name"], a.chain) or "-", grid_of(r))].append(
             (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3)
-    labels = stage_labels(list(groups), a.chain)
     out = [f"# rocprofv3 kernel trace: {a.title or a.chain + ', ' + a.workload}, one stream (every kernel runs alone)", "",
            "Command (MI355X box):", "", f"    {PRE}{a.command}", "",
            "libspa kernels of that run, by kernel and grid size (the run holds the warm-up, the timed steps, the "
@@ -148,7 +129,7 @@ def cmd_kernels(a):
         out[0] = f"# rocprofv3 kernel trace: {a.title or 'a whole bench.py run'} (the 60 kernel / grid pairs with the most GPU time)"
     for g in sorted(groups, key=lambda g: -sum(groups[g])):
         d = groups[g]
-        out.append(f"| {labels[g]} | {g[0]} | {g[2]} | {len(d)} | {statistics.mean(d):.2f} | {statistics.median(d):.2f} | "
+        out.append(f"| {g[1]} | {g[0]} | {g[2]} | {len(d)} | {statistics.mean(d):.2f} | {statistics.median(d):.2f} | "
                    f"{min(d):.2f} | {max(d):.2f} |")
     if a.note:
         out += ["", a.note]
@@ -183,7 +164,6 @@ def cmd_traffic(a):
         fa = statistics.mean(c["FETCH_SIZE"]) * sf * 1024
         wa = statistics.mean(wv) * sw * 1024
         groups[(short(k), call_of(k, a.chain) or "-", grid)] = (len(c["FETCH_SIZE"]), fa, wa)
-    labels = stage_labels(list(groups), a.chain)
     out = [f"# rocprofv3 HBM traffic counters: {a.title or a.chain + ', ' + a.workload}", "",
            "Commands (MI355X box), one counter per run:", "",
            f"    {PRE}{a.command.replace('COUNTER', 'FETCH_SIZE')}", f"    {PRE}{a.command.replace('COUNTER', 'WRITE_SIZE')}", "",
@@ -193,9 +173,9 @@ def cmd_traffic(a):
     per_call = defaultdict(float)
     for g in sorted(groups, key=lambda g: -(groups[g][1] + groups[g][2])):
         n, fa, wa = groups[g]
-        out.append(f"| {labels[g]} | {g[0]} | {g[2]} | {n} | {fa / 1e6:.2f} | {wa / 1e6:.2f} | {(fa + wa) / 1e6:.2f} |")
+        out.append(f"| {g[1]} | {g[0]} | {g[2]} | {n} | {fa / 1e6:.2f} | {wa / 1e6:.2f} | {(fa + wa) / 1e6:.2f} |")
         if g[1] != "-":
-            per_call[labels[g]] += fa + wa
+            per_call[g[1]] += fa + wa
     write(f"hbm_traffic_{a.workload}.md", out)
     # the table bench.py reads: the rows of this workload are replaced
     keep = []
@@ -225,13 +205,12 @@ def cmd_pipes(a):
     for (k, grid), c in vals.items():
         if is_spa(k) and "GRBM_GUI_ACTIVE" in c:
             groups[(short(k), call_of(k, a.chain) or "-", grid)] = c
-    labels = stage_labels(list(groups), a.chain)
     m = lambda c, n: statistics.mean(c[n]) if c.get(n) else float("nan")
     for g in sorted(groups, key=lambda g: -m(groups[g], "GRBM_GUI_ACTIVE")):
         c = groups[g]
         cyc = m(c, "GRBM_GUI_ACTIVE") / 8
         mf = m(c, "SQ_INSTS_MFMA")
-        out.append(f"| {labels[g]} | {g[0]} | {g[2]} | {len(c['GRBM_GUI_ACTIVE'])} | {cyc:.0f} | "
+        out.append(f"| {g[1]} | {g[0]} | {g[2]} | {len(c['GRBM_GUI_ACTIVE'])} | {cyc:.0f} | "
                    f"{100 * m(c, 'SQ_VALU_MFMA_BUSY_CYCLES') / (cyc * 1024):.1f} % | "
                    f"{100 * 4 * m(c, 'SQ_ACTIVE_INST_VALU') / (cyc * 1024):.1f} % | "
                    f"{100 * m(c, 'SQ_WAIT_INST_ANY') / m(c, 'SQ_WAVE_CYCLES'):.1f} % | "

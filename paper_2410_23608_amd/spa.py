@@ -37,6 +37,8 @@ _SIGNATURES = {
     "spa_version": (c_int, []),
     "spa_last_error": (c_char_p, []),
     "spa_set_option": (c_int, [c_char_p, c_char_p]),
+    "spa_group_begin": (c_int, []),
+    "spa_group_end": (c_int, [_P]),
     "spa_workspace_bytes": (c_size_t, [c_int, c_int, c_int, c_int, c_int, c_int]),
     "spa_gate_select": (c_int, [_P, _P, c_float, _P, c_float, c_int, c_int, c_int, c_int, _P, _P, _P, _P]),
     "spa_gate_select_index": (c_int, [_P, _P, c_float, _P, c_float, c_int, c_int, c_int, c_int, _P, _P, _P, _P, _P, _P, _P,
@@ -268,6 +270,19 @@ SPA_OP_QKV_PROJECTION_BWD_WEIGHT, SPA_OP_OUT_PROJECTION_BWD_WEIGHT = 6, 7
 def spa_set_option(name: str, value: Optional[str] = None) -> None:
     """Process-wide launch option (kernel selection for tests and tuning); None / "" = default."""
     _check(lib.spa_set_option(name.encode(), (value or "").encode()))
+
+
+def group(*calls):
+    """Prepared calls of several stages as one that issues them as a launch group (spa_group_begin / end)."""
+    return chain(spa_group_begin(prepare=True), *calls, spa_group_end(prepare=True))
+
+
+def spa_group_begin(prepare=False):
+    return _dispatch(lib.spa_group_begin, (), (), prepare)
+
+
+def spa_group_end(prepare=False):
+    return _dispatch(lib.spa_group_end, (_stream(),), (), prepare)
 
 
 def spa_workspace_bytes(op: int, B: int, N: int, C: int, H: int, dtype: int) -> int:
