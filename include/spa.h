@@ -275,6 +275,16 @@ int spa_packed_attention(const void* q, const void* k, const void* v, int64_t q_
                          int dtype, float softmax_scale, void* out, float* lse, void* stream);
 
 /*
+ * spa_packed_attention with the exponentials always taken against the running maximum of the scores (not only where
+ * their range needs it).  The results agree within the rounding of the probabilities; gradients that sum with
+ * cancellation behind it agree with those of other implementations of the online softmax more closely.
+ */
+int spa_packed_attention_running_max(const void* q, const void* k, const void* v, int64_t q_row_stride,
+                                     int64_t k_row_stride, int64_t v_row_stride, const int32_t* cu_seqlens, int B,
+                                     int max_seqlen, int H, int Dh, int dtype, float softmax_scale, void* out,
+                                     float* lse, void* stream);
+
+/*
  * Scatter back (Section 3.2: positive tokens undergo attention, negative tokens go on
  * directly).  y[i,:] = packed_out[inv_pos[i],:] if inv_pos[i] >= 0 else 0; with base given,
  * y[i,:] = base[i,:] (+ packed_out[inv_pos[i],:] on selected rows).

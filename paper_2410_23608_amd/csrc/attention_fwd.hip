@@ -215,9 +215,12 @@ __device__ __forceinline__ void fwd_scores(const __bf16* kbuf, int key0, int rem
 // all first scores far below 0, inf or NaN) the wave takes the group again with the true maximum: the
 // scores are recomputed from the K rows in LDS (they are not kept, to save the registers) and O and l
 // are rescaled, as the online softmax does for every group.
+// RM: the running maximum all the same (spa_packed_attention_running_max).  Which way a probability is rounded to
+// bf16 depends on the reference, and where gradients pass through projections, sums with cancellation (the bias
+// gradient of the gate) move by a few percent with it; the maximum costs up to 9 % of a launch.
 constexpr float kRowSumMin = 9.5367431640625e-07f;     // 2^-20
 constexpr float kRowSumMax = 1.099511627776e+12f;      // 2^40
-template <int DH, int RS, int GSB, bool FULL>
+template <int DH, int RS, int GSB, bool FULL, bool RM>
 __device__ __forceinline__ void fwd_exp(const floatx16 (&s)[GSB], const __bf16* kbuf, int key0, int rem, bool first,
                                         const bf16x8 (&qf)[DH / 16], FwdAcc<DH>& acc, float scale_log2,
                                         bf16x8 (&pb)[GSB][2], int l32, int hh) {
@@ -236,10 +239,31 @@ __device__ __forceinline__ void fwd_exp(const floatx16 (&s)[GSB], const __bf16* 
       pb[sb][mf] = float_to_bf16x8(pf);
     }
   };
+  if (RM) {
+    float mx = s[0][0];
+#pragma unroll
+    for (int sb = 0; sb < GSB; ++sb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sb][r]);
+    const float m_new = fmaxf(acc.m, max_across_halves(mx) * scale_log2);
+    if (__ballot(m_new != acc.m) != 0) {               // some query's running max moved: rescale
+      const float alpha = __builtin_amdgcn_exp2f(acc.m - m_new);
+      acc.l *= alpha;
+#pragma unroll
+      for (int d = 0; d < DH / 32; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc.o[d][r] *= alpha;
+      acc.m = m_new;
+    }
+  }
   float psum = 0.f;
 #pragma unroll
   for (int sb = 0; sb < GSB; ++sb)
     if (FULL || key0 + sb * 32 < rem) take(s[sb], sb, psum);
+  if (RM) {
+    acc.l += psum;
+    return;
+  }
   const float l_new = acc.l + psum;
   if (__builtin_expect(__ballot(!(l_new >= (first ? kRowSumMin : 0.f) && l_new < kRowSumMax)) != 0, 0)) {
     float mx = -INFINITY;
@@ -275,13 +299,13 @@ __device__ __forceinline__ void fwd_exp(const floatx16 (&s)[GSB], const __bf16* 
 // The probabilities of a group of GSB*32 keys, then O^T += V^T P^T.  V^T at vbuf (row stride TS), the
 // group's keys at column vcol; TS == 0: V rows as they lie in memory (row stride DH + 8, the group's keys
 // from row vcol), the V^T fragments then come from the transposing LDS read.
-template <int DH, int RS, int TS, int GSB, bool FULL>
+template <int DH, int RS, int TS, int GSB, bool FULL, bool RM>
 __device__ __forceinline__ void fwd_softmax_pv(const floatx16 (&s)[GSB], const __bf16* kbuf, const __bf16* vbuf, int vcol,
                                                int key0, int rem, bool first, const bf16x8 (&qf)[DH / 16],
                                                FwdAcc<DH>& acc, float scale_log2, int l32, int hh) {
   constexpr int DB = DH / 32;
   bf16x8 pb[GSB][2];
-  fwd_exp<DH, RS, GSB, FULL>(s, kbuf, key0, rem, first, qf, acc, scale_log2, pb, l32, hh);
+  fwd_exp<DH, RS, GSB, FULL, RM>(s, kbuf, key0, rem, first, qf, acc, scale_log2, pb, l32, hh);
 #pragma unroll
   for (int sb = 0; sb < GSB; ++sb)
     if (FULL || key0 + sb * 32 < rem) {
@@ -316,7 +340,7 @@ __device__ __forceinline__ void fwd_process_tile(const __bf16* kbuf, const __bf1
     if (!FULL && key0 >= rem) break;
     if (g + 1 < NG && (FULL || key0 + GSB * 32 < rem))
       fwd_scores<DH, RS, GSB, FULL>(kbuf, key0 + GSB * 32, rem, qf, s[(g + 1) & 1], l32, hh);
-    fwd_softmax_pv<DH, RS, TS, GSB, FULL>(s[g & 1], kbuf, vbuf, vcol0 + key0, key0, rem, first && g == 0, qf, acc,
+    fwd_softmax_pv<DH, RS, TS, GSB, FULL, false>(s[g & 1], kbuf, vbuf, vcol0 + key0, key0, rem, first && g == 0, qf, acc,
                                           scale_log2, l32, hh);
   }
 }
@@ -496,7 +520,7 @@ struct TiledLds {
 constexpr int kTiledBN = 64;
 
 // The workgroup's work on queries [q0, q0 + 32 NW) of head h of segment seg (q0 < seg.nq).
-template <int DH, int NW, bool GATHER>
+template <int DH, int NW, bool GATHER, bool RM>
 __device__ __forceinline__ void
 tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, const __bf16* __restrict__ q,
                 const __bf16* __restrict__ k, const __bf16* __restrict__ v, long qs, long ks, long vs, int H,
@@ -525,7 +549,7 @@ tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, c
   bf16x8 qf[DH / 16];
   load_q_frags<DH>(q + q_src * qs + h * DH, q_ok, hh, qf);
   FwdAcc<DH> acc;
-  acc.init();
+  acc.init(RM ? -INFINITY : 0.f);
   stage.store(Ks[0], Vs[0]);
   __syncthreads();
 
@@ -539,7 +563,7 @@ tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, c
     if (wave_live) {
       floatx16 s[GSB];
       fwd_scores<DH, RS, GSB, !last>(Ks[buf], 0, seg.nk - kt, qf, s, l32, hh);
-      fwd_softmax_pv<DH, RS, 0, GSB, !last>(s, Ks[buf], Vs[buf], 0, 0, seg.nk - kt, t == 0, qf, acc, scale_log2, l32, hh);
+      fwd_softmax_pv<DH, RS, 0, GSB, !last, RM>(s, Ks[buf], Vs[buf], 0, 0, seg.nk - kt, t == 0, qf, acc, scale_log2, l32, hh);
     }
     if (!last) stage.store(Ks[buf ^ 1], Vs[buf ^ 1]);
     __syncthreads();
@@ -567,12 +591,12 @@ struct TiledShared {
   int s_cu[2 * kLptMaxB + 1];
   int s_pick;
 };
-template <int DH, int NW, bool GATHER>
+template <int DH, int NW, bool GATHER, bool RM>
 __device__ __forceinline__ void tiled_block(TiledShared<DH>& sh, const FwdArgs& a, unsigned block, unsigned blocks) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, H = a.H, B = a.B;
   const Scatter& sc = a.sc;
   auto attend = [&](const Segment& seg, int h, int q0) {
-    tiled_attention<DH, NW, GATHER>(sh.lds, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, H, a.scale_log2, a.out, a.lse,
+    tiled_attention<DH, NW, GATHER, RM>(sh.lds, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, H, a.scale_log2, a.out, a.lse,
                                     a.lse_stride, sc);
   };
   if ((int)block >= a.ntile) {
@@ -609,11 +633,11 @@ __device__ __forceinline__ void tiled_block(TiledShared<DH>& sh, const FwdArgs& 
   if (q0 < seg.nq) attend(seg, tile_id.h, q0);
 }
 
-template <int DH, int NW, bool GATHER>
+template <int DH, int NW, bool RM, bool GATHER>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH == 32 ? 3 : 2)))
 attn_fwd_bf16_tiled_kernel(const FwdArgs a) {
   __shared__ TiledShared<DH> sh;
-  tiled_block<DH, NW, GATHER>(sh, a, blockIdx.x, gridDim.x);
+  tiled_block<DH, NW, GATHER, RM>(sh, a, blockIdx.x, gridDim.x);
 }
 
 // Short segments, wave-autonomous.  ONE wave per (image, head, 32-query block), no
@@ -625,7 +649,7 @@ attn_fwd_bf16_tiled_kernel(const FwdArgs a) {
 // instead of concentrating a heavy (image, head) on one compute unit.
 // The wave's work on queries [q0, q0 + 32) of head h of segment seg (q0 < seg.nq): Ks, Vs are
 // its private LDS tiles of STEP rows.
-template <int DH, int STEP, bool GATHER>
+template <int DH, int STEP, bool GATHER, bool RM>
 __device__ __forceinline__ void
 wave_attention(__bf16* Ks, __bf16* Vs, const Segment seg, int h, int q0, const __bf16* __restrict__ q,
                const __bf16* __restrict__ k, const __bf16* __restrict__ v, long qs, long ks, long vs, int H,
@@ -694,7 +718,7 @@ wave_attention(__bf16* Ks, __bf16* Vs, const Segment seg, int h, int q0, const _
   bf16x8 qf[KK];
   load_q_frags<DH>(q + q_src * qs + h * DH, q_ok, hh, qf);
   FwdAcc<DH> acc;
-  acc.init();
+  acc.init(RM ? -INFINITY : 0.f);
 
   for (int kt = 0; kt < seg.nk; kt += STEP) {
     lstore();                                     // this step's rows: registers -> LDS
@@ -706,7 +730,7 @@ wave_attention(__bf16* Ks, __bf16* Vs, const Segment seg, int h, int q0, const _
     // scores of the step: S^T = K Q^T, NSB 32-key sub-tiles, one softmax update for all
     floatx16 s[NSB];
     fwd_scores<DH, RS, NSB, false>(Ks, 0, rem, qf, s, l32, hh);
-    fwd_softmax_pv<DH, RS, 0, NSB, false>(s, Ks, Vs, 0, 0, rem, kt == 0, qf, acc, scale_log2, l32, hh);
+    fwd_softmax_pv<DH, RS, 0, NSB, false, RM>(s, Ks, Vs, 0, 0, rem, kt == 0, qf, acc, scale_log2, l32, hh);
   }
 
   // output: park the 32 x DH tile in the (now free) K tile, then write whole rows
@@ -715,28 +739,28 @@ wave_attention(__bf16* Ks, __bf16* Vs, const Segment seg, int h, int q0, const _
   fwd_flush<DH, RS>(Ks, out, sc, seg.row0 + q0, h, C, min(32, seg.nq - q0), lane);
 }
 
-template <int DH, int STEP, bool GATHER>
+template <int DH, int STEP>
+struct WaveLds {
+  static constexpr int RS = DH + 8;
+  __attribute__((aligned(16))) __bf16 Ks[STEP * RS];
+  __attribute__((aligned(16))) __bf16 Vs[STEP * RS];
+};
+template <int DH, int STEP, bool RM, bool GATHER>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(STEP == 32 ? 3 : 1)))
-attn_fwd_bf16_wave_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
-                          const __bf16* __restrict__ v, long qs, long ks, long vs,
-                          const int32_t* __restrict__ cu, const int32_t* __restrict__ key_lens, int n_pad,
-                          int H, float scale_log2, __bf16* __restrict__ out, float* __restrict__ lse,
-                          long lse_stride, Scatter sc, int B, int nqb) {
-  constexpr int RS = DH + 8;
-  __shared__ __attribute__((aligned(16))) __bf16 Ks[STEP * RS];
-  __shared__ __attribute__((aligned(16))) __bf16 Vs[STEP * RS];
-
-  const TileId tile_id = xcd_tile(nqb, H, B);
+attn_fwd_bf16_wave_kernel(const FwdArgs a) {
+  __shared__ WaveLds<DH, STEP> lds;
+  const TileId tile_id = xcd_tile(a.nqb, a.H, a.B);
   if (!tile_id.valid) return;
   const int h = tile_id.h, img = tile_id.rank;
-  const Segment seg = segment_of(img, cu, key_lens, n_pad);
-  const long C = (long)H * DH;
+  const Segment seg = segment_of(img, a.cu, a.key_lens, a.n_pad);
+  const long C = (long)a.H * DH;
   // this wave's share of the image's bypassing tokens: at once if it has no queries, else last
-  const FillRange fr = fill_range(sc, img, B, tile_id.qb, nqb);
+  const FillRange fr = fill_range(a.sc, img, a.B, tile_id.qb, a.nqb);
   const int q0 = tile_id.qb * 32;
   if (q0 < seg.nq)
-    wave_attention<DH, STEP, GATHER>(Ks, Vs, seg, h, q0, q, k, v, qs, ks, vs, H, scale_log2, out, lse, lse_stride, sc);
-  if (sc.y != nullptr) scatter_fill<__bf16, DH>(sc, fr.b, fr.t0, fr.t1, h, C, threadIdx.x, 64);
+    wave_attention<DH, STEP, GATHER, RM>(lds.Ks, lds.Vs, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H, a.scale_log2, a.out,
+                                         a.lse, a.lse_stride, a.sc);
+  if (a.sc.y != nullptr) scatter_fill<__bf16, DH>(a.sc, fr.b, fr.t0, fr.t1, h, C, threadIdx.x, 64);
 }
 
 // The one-wave work units driven by the selection mask itself: no packing launch precedes this
@@ -745,12 +769,6 @@ attn_fwd_bf16_wave_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
 // wave_attention runs on it as on gathered rows (packed position j of the image = row list[j] of
 // q, k, v and of y), and the bypass fill tests the mask byte instead of inv_pos.  Costs four byte
 // loads and four ballots per wave where the other forms cost a kernel launch.
-template <int DH, int STEP>
-struct WaveLds {
-  static constexpr int RS = DH + 8;
-  __attribute__((aligned(16))) __bf16 Ks[STEP * RS];
-  __attribute__((aligned(16))) __bf16 Vs[STEP * RS];
-};
 template <int DH, int STEP>
 struct MaskLds {
   WaveLds<DH, STEP> kv;
@@ -781,7 +799,7 @@ __device__ __forceinline__ void mask_unit(MaskLds<DH, STEP>& lds, const FwdArgs&
   const FillRange fr = fill_range(a.sc, img, a.B, tile_id.qb, a.nqb);
   const int q0 = tile_id.qb * 32;
   if (q0 < n)
-    wave_attention<DH, STEP, true>(lds.kv.Ks, lds.kv.Vs, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H, a.scale_log2,
+    wave_attention<DH, STEP, true, false>(lds.kv.Ks, lds.kv.Vs, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H, a.scale_log2,
                                    nullptr, nullptr, 0, scl);
   scatter_fill<__bf16, DH>(a.sc, fr.b, fr.t0, fr.t1, h, C, lane, 64);
 }
@@ -871,23 +889,23 @@ static unsigned lpt64_grid(int B, int H, int nqb) {
 
 // Compiled for three waves per SIMD (168 registers at head dim 64, no spills): a ViT-B-shaped
 // batch has ~2800 live waves for 1024 SIMDs and then runs in one round instead of two.
-template <int DH, int STEP, bool GATHER>
+template <int DH, int STEP, bool GATHER, bool RM>
 __device__ __forceinline__ void lpt64_unit(WaveLds<DH, STEP>& lds, const FwdArgs& a, int x, int j, int units) {
   const int unit = j & 31, m = j >> 5;
   const LptBlock blk = lpt64_block<32>(a.cu, a.key_lens, a.n_pad, a.B, a.H, a.nqb, x, m * 32 + ((m & 1) ? 31 - unit : unit));
   if (blk.live)
-    wave_attention<DH, STEP, GATHER>(lds.Ks, lds.Vs, blk.seg, blk.h, blk.q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H,
+    wave_attention<DH, STEP, GATHER, RM>(lds.Ks, lds.Vs, blk.seg, blk.h, blk.q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H,
                                      a.scale_log2, a.out, a.lse, a.lse_stride, a.sc);
   if (a.sc.y != nullptr) {
     const long rows = a.sc.flat ? (long)a.sc.N : (long)a.B * a.sc.N, per = (rows + units - 1) / units, u = 8L * j + x;
     scatter_fill_rows<__bf16>(a.sc, min(rows, u * per), min(rows, (u + 1) * per), (long)a.H * DH, threadIdx.x & 63);
   }
 }
-template <int DH, int STEP, bool GATHER>
+template <int DH, int STEP, bool RM, bool GATHER>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
 attn_fwd_bf16_wave_lpt64_kernel(const FwdArgs a) {
   __shared__ WaveLds<DH, STEP> lds;
-  lpt64_unit<DH, STEP, GATHER>(lds, a, blockIdx.x & 7, blockIdx.x >> 3, gridDim.x);
+  lpt64_unit<DH, STEP, GATHER, RM>(lds, a, blockIdx.x & 7, blockIdx.x >> 3, gridDim.x);
 }
 
 // Several calls in one launch (launch groups, head dim 32): the tiled blocks of those with more than 256 tokens
@@ -904,9 +922,9 @@ attn_fwd_bf16_group_kernel(const Members<FwdArgs> m) {
   const MemberBlock mb = member_of(m, blockIdx.x);
   const FwdArgs& a = m.a[mb.s];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (a.ntile > 0) tiled_block<DH, 4, GATHER>(sh.tiled, a, mb.block, mb.blocks);
+  if (a.ntile > 0) tiled_block<DH, 4, GATHER, false>(sh.tiled, a, mb.block, mb.blocks);
   else if constexpr (GATHER) mask_unit<DH, STEP>(sh.wave[wv], a, mb.block & 7, (mb.block >> 3) * 4 + wv);
-  else lpt64_unit<DH, STEP, false>(sh.wave[wv].kv, a, mb.block & 7, (mb.block >> 3) * 4 + wv, mb.blocks * 4);
+  else lpt64_unit<DH, STEP, false, false>(sh.wave[wv].kv, a, mb.block & 7, (mb.block >> 3) * 4 + wv, mb.blocks * 4);
 }
 
 static thread_local Noted<FwdArgs> g_noted[2];       // packed, gathered
@@ -1153,7 +1171,7 @@ attn_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
 static int attention_common(const char* fn, const void* q, const void* k, const void* v,
                             int64_t q_stride, int64_t k_stride, int64_t v_stride, const int32_t* cu, const int32_t* key_lens, int B,
                             int n_max, int H, int Dh, int dtype, float softmax_scale, void* out,
-                            float* lse, const Scatter& sc, void* stream) {
+                            float* lse, const Scatter& sc, void* stream, bool running_max = false) {
   SPA_REQUIRE(q && k && v && (out || sc.y) && (cu || key_lens), SPA_ERR_INVALID_ARG, "%s: null pointer", fn);
   SPA_REQUIRE(B >= 1 && n_max >= 1 && H >= 1, SPA_ERR_INVALID_ARG, "%s: B, max_seqlen, H must be >= 1", fn);
   SPA_REQUIRE((long)B * n_max < 2147483647L, SPA_ERR_INVALID_ARG, "%s: B*max_seqlen must be < 2^31", fn);
@@ -1200,7 +1218,8 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
       return (unsigned)(args.ntile + std::min<long>((rows + 31) / 32, 1024));
     };
     if (group_open()) {
-      SPA_REQUIRE(Dh == 32 && key_lens == nullptr && (n_max > 256 || (!sc.gathered && B <= kWave)), SPA_ERR_UNSUPPORTED,
+      SPA_REQUIRE(Dh == 32 && key_lens == nullptr && !running_max && (n_max > 256 || (!sc.gathered && B <= kWave)),
+                  SPA_ERR_UNSUPPORTED,
                   "%s: this form cannot be part of a group", fn);
       if (n_max > 256) {
         const unsigned blocks = tiled_grid();
@@ -1210,7 +1229,11 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
       return g_noted[0].add(fn, args, wave_groups(lpt64_grid(B, H, args.nqb)));
     }
 #define SPA_ARGS_PLAIN SPA_ARGS
-#define SPA_ARGS_BN SPA_ARGS, B, nqb
+#define SPA_LAUNCH_MAX(KERNEL, GRID, BLOCK, ARGS, ...)                                                        \
+  do {                                                                                                        \
+    if (running_max) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, true, false>), GRID, BLOCK, 0, st, ARGS);        \
+    else SPA_LAUNCH(KERNEL, GRID, BLOCK, ARGS, __VA_ARGS__, false);                                           \
+  } while (0)
 #define SPA_LAUNCH(KERNEL, GRID, BLOCK, ARGS, ...)                                                            \
   do {                                                                                                        \
     if (sc.gathered) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, true>), GRID, BLOCK, 0, st, ARGS);               \
@@ -1229,19 +1252,19 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
       // short segments: one wave per (image, head, 32 queries)
       const int nqb = (n_max + 31) / 32;
       const dim3 grid(xcd_grid(nqb, H, B));
+      args.nqb = nqb;
       // default: blocks dealt to the compute units by weight ("plain": numbered blindly)
       const bool step64 = opt.fwd_step64, plain = opt.fwd_plain;
       if (!step64 && !plain && B <= kWave) {
         const dim3 lgrid(lpt64_grid(B, H, nqb));
-        args.nqb = nqb;
-        if (Dh == 32) SPA_LAUNCH(attn_fwd_bf16_wave_lpt64_kernel, lgrid, dim3(64), args, 32, 32);
-        else SPA_LAUNCH(attn_fwd_bf16_wave_lpt64_kernel, lgrid, dim3(64), args, 64, 32);
+        if (Dh == 32) SPA_LAUNCH_MAX(attn_fwd_bf16_wave_lpt64_kernel, lgrid, dim3(64), args, 32, 32);
+        else SPA_LAUNCH_MAX(attn_fwd_bf16_wave_lpt64_kernel, lgrid, dim3(64), args, 64, 32);
       } else if (Dh == 32) {
-        if (step64) SPA_LAUNCH(attn_fwd_bf16_wave_kernel, grid, dim3(64), SPA_ARGS_BN, 32, 64);
-        else SPA_LAUNCH(attn_fwd_bf16_wave_kernel, grid, dim3(64), SPA_ARGS_BN, 32, 32);
+        if (step64) SPA_LAUNCH_MAX(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 32, 64);
+        else SPA_LAUNCH_MAX(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 32, 32);
       } else {
-        if (step64) SPA_LAUNCH(attn_fwd_bf16_wave_kernel, grid, dim3(64), SPA_ARGS_BN, 64, 64);
-        else SPA_LAUNCH(attn_fwd_bf16_wave_kernel, grid, dim3(64), SPA_ARGS_BN, 64, 32);
+        if (step64) SPA_LAUNCH_MAX(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 64, 64);
+        else SPA_LAUNCH_MAX(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 64, 32);
       }
     } else if (!tiled && n_max <= 256) {
       // short segments: one workgroup per (image, head), whole segment in LDS
@@ -1256,13 +1279,13 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
 #undef SPA_WHOLE
     } else {
       const dim3 grid(tiled_grid());
-      if (Dh == 32) SPA_LAUNCH(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 32, 4);
-      else SPA_LAUNCH(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 64, 4);
+      if (Dh == 32) SPA_LAUNCH_MAX(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 32, 4);
+      else SPA_LAUNCH_MAX(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 64, 4);
     }
 #undef SPA_ARGS
 #undef SPA_ARGS_PLAIN
-#undef SPA_ARGS_BN
 #undef SPA_LAUNCH
+#undef SPA_LAUNCH_MAX
   }
   return check_launch(fn);
 }
@@ -1279,6 +1302,18 @@ extern "C" int spa_packed_attention(const void* q, const void* k, const void* v,
   const Scatter none = {nullptr, nullptr, nullptr, nullptr, 0, 0, 0, nullptr};
   return attention_common("spa_packed_attention", q, k, v, q_row_stride, k_row_stride, v_row_stride, cu_seqlens, nullptr, B, max_seqlen,
                           H, Dh, dtype, softmax_scale, out, lse, none, stream);
+}
+
+extern "C" int spa_packed_attention_running_max(const void* q, const void* k, const void* v, int64_t q_row_stride,
+                                                int64_t k_row_stride, int64_t v_row_stride, const int32_t* cu_seqlens, int B,
+                                                int max_seqlen, int H, int Dh, int dtype, float softmax_scale, void* out,
+                                                float* lse, void* stream) {
+  const char* fn = "spa_packed_attention_running_max";
+  SPA_REQUIRE(cu_seqlens, SPA_ERR_INVALID_ARG, "%s: cu_seqlens is null", fn);
+  SPA_REQUIRE(out, SPA_ERR_INVALID_ARG, "%s: out is null", fn);
+  const Scatter none = {nullptr, nullptr, nullptr, nullptr, 0, 0, 0, nullptr};
+  return attention_common(fn, q, k, v, q_row_stride, k_row_stride, v_row_stride, cu_seqlens, nullptr, B, max_seqlen, H, Dh, dtype,
+                          softmax_scale, out, lse, none, stream, true);
 }
 
 extern "C" int spa_padded_attention(const void* q, const void* k, const void* v, int64_t row_stride,

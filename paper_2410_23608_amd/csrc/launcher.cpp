@@ -62,7 +62,7 @@ const Entry kEntries[] = {
     ENTRY(spa_group_begin), ENTRY(spa_group_end),
     ENTRY(spa_gate_select), ENTRY(spa_gate_select_index), ENTRY(spa_gate_select_pooled), ENTRY(spa_gate_select_gumbel),
     ENTRY(spa_gate_bwd_straight_through), ENTRY(spa_maxpool2x2), ENTRY(spa_pack), ENTRY(spa_pack_pair),
-    ENTRY(spa_pack_shifted), ENTRY(spa_container_segments), ENTRY(spa_packed_attention),
+    ENTRY(spa_pack_shifted), ENTRY(spa_container_segments), ENTRY(spa_packed_attention), ENTRY(spa_packed_attention_running_max),
     ENTRY(spa_packed_attention_unpack), ENTRY(spa_gathered_attention_unpack), ENTRY(spa_selected_attention_unpack),
     ENTRY(spa_segment_attention_unpack), ENTRY(spa_ceiling_copy), ENTRY(spa_linear_packed),
     ENTRY(spa_linear_packed_scatter), ENTRY(spa_linear_packed_unpack), ENTRY(spa_linear_packed_bwd_input), ENTRY(spa_linear_packed_bwd_weight),

@@ -57,6 +57,8 @@ _SIGNATURES = {
     "spa_container_segments_capacity": (c_int64, [c_int, c_int64, c_int]),
     "spa_container_segments": (c_int, [_P, c_int, c_int, c_int64, c_int, _P, _P, _P]),
     "spa_packed_attention": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, c_int, c_int, c_int, c_int, c_int, c_float, _P, _P, _P]),
+    "spa_packed_attention_running_max": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, c_int, c_int, c_int, c_int, c_int,
+                                                 c_float, _P, _P, _P]),
     "spa_packed_attention_unpack": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, _P, _P, _P, c_int, c_int, c_int,
                                             c_int, c_int, c_float, _P, _P, _P, _P]),
     "spa_gathered_attention_unpack": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, _P, _P, _P, c_int, c_int, c_int,
@@ -447,11 +449,7 @@ def _row_stride(t) -> int:
     return int(t.stride(0))
 
 
-def spa_packed_attention(q, k, v, cu_seqlens, B, max_seqlen, H, Dh, out, lse=None, softmax_scale=0.0,
-                         prepare=False):
-    """q, k, v: [rows, H*Dh] tensors or column-slice views of fused packed buffers; the row
-    strides are taken from the views."""
-    fn = "spa_packed_attention"
+def _packed_attention(fn, q, k, v, cu_seqlens, B, max_seqlen, H, Dh, out, lse, softmax_scale, prepare):
     code = _features(fn, q=q, k=k, v=v, out=out)
     _typed(fn, torch.int32, cu_seqlens=cu_seqlens)
     _typed(fn, torch.float32, lse=lse)
@@ -459,9 +457,24 @@ def spa_packed_attention(q, k, v, cu_seqlens, B, max_seqlen, H, Dh, out, lse=Non
     _holds(fn, cu_seqlens=(cu_seqlens, B + 1), lse=(lse, H * B * max_seqlen))
     _keep = (q, k, v, out, lse, cu_seqlens,)
     _contig(out, lse, cu_seqlens)
-    return _dispatch(lib.spa_packed_attention, (_ptr(q), _ptr(k), _ptr(v), _row_stride(q), _row_stride(k), _row_stride(v),
-                                    _ptr(cu_seqlens), B, max_seqlen,
-                                    H, Dh, code, float(softmax_scale), _ptr(out), _ptr(lse), _stream(),), _keep, prepare)
+    return _dispatch(getattr(lib, fn), (_ptr(q), _ptr(k), _ptr(v), _row_stride(q), _row_stride(k), _row_stride(v),
+                                        _ptr(cu_seqlens), B, max_seqlen,
+                                        H, Dh, code, float(softmax_scale), _ptr(out), _ptr(lse), _stream(),), _keep, prepare)
+
+
+def spa_packed_attention(q, k, v, cu_seqlens, B, max_seqlen, H, Dh, out, lse=None, softmax_scale=0.0,
+                         prepare=False):
+    """q, k, v: [rows, H*Dh] tensors or column-slice views of fused packed buffers; the row
+    strides are taken from the views."""
+    return _packed_attention("spa_packed_attention", q, k, v, cu_seqlens, B, max_seqlen, H, Dh, out, lse, softmax_scale,
+                             prepare)
+
+
+def spa_packed_attention_running_max(q, k, v, cu_seqlens, B, max_seqlen, H, Dh, out, lse=None, softmax_scale=0.0,
+                                     prepare=False):
+    """spa_packed_attention with the running maximum of the scores as the reference of the exponentials."""
+    return _packed_attention("spa_packed_attention_running_max", q, k, v, cu_seqlens, B, max_seqlen, H, Dh, out, lse,
+                             softmax_scale, prepare)
 
 
 def _scatter_checks(fn, q, k, v, seg, n_seg, max_seqlen, gather_idx, inv_pos, base, H, Dh, y, out, lse):

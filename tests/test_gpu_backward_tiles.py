@@ -61,3 +61,29 @@ def test_backward_at_tile_edges(Dh, N, shift):
         if n:
             err = (got[0][r] - ref).abs().max() / max(1.0, ref.abs().max())
             assert err < 3e-2, (b, n, err)
+
+
+@pytest.mark.parametrize("Dh,N", [(32, 40), (64, 196), (32, 256), (64, 260), (32, 400)])
+@pytest.mark.parametrize("shift", [0.0, 8.0])
+def test_running_max_form_equals_the_default_form(Dh, N, shift):
+    from paper_2410_23608_amd import spa
+    H, C, lens = 2, 2 * Dh, [n for n in LENS if n < N] + [N]
+    B, cap = len(lens), len(lens) * N
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Dh + N)
+    cu = torch.tensor([0] + lens, dtype=torch.int32).cumsum(0).int().cuda()
+    T = sum(lens)
+    qkv = torch.randn(cap, 3 * C, generator=g, device="cuda")
+    qkv[:, :C] += shift
+    qkv[:, C:2 * C] -= shift
+    qkv = qkv.bfloat16()
+    got = []
+    for fn in (spa.spa_packed_attention, spa.spa_packed_attention_running_max):
+        out = torch.full((cap, C), float("nan"), device="cuda", dtype=torch.bfloat16)
+        lse = torch.full((H, cap), float("nan"), device="cuda")
+        fn(qkv[:, :C], qkv[:, C:2 * C], qkv[:, 2 * C:], cu, B, N, H, Dh, out, lse)
+        assert torch.isnan(out[T:]).all()
+        got.append((out[:T].float(), lse[:, :T]))
+    (o0, l0), (o1, l1) = got
+    assert torch.isfinite(o1).all() and (o0 - o1).abs().max() <= 2e-2
+    assert (l0 - l1).abs().max() <= 1e-4 * max(1.0, float(l0.abs().max()))
