@@ -448,6 +448,12 @@ def train_work(B, N, C, H, T, sum_n2, prefix="", bwd_executed_over_algorithmic=1
         prefix + "gate_select": (0.0, B * N * (C * e + 5)),
         prefix + "gate_select_pooled": (0.0, B * N * (C * e + 5 + 16)),
         prefix + "pack_qk_rg": (0.0, 2 * T * 3 * C * e + 8 * T + 5 * B * N + 4 * (B + 1)),
+        prefix + "pack_indices": (0.0, 4 * T + 5 * B * N + 4 * (B + 1)),
+        # q|k rows and x rows (the values, gated on the way) at token positions
+        prefix + "gated_attention_unpack": (4.0 * C * sum_n2, T * 3 * C * e + B * N * C * e + 8 * T + 4 * B * N
+                                            + 4 * (B + 1) + T * C * e + 4 * H * T),
+        prefix + "gated_attention_bwd_tokens": (10.0 * C * sum_n2, 5 * T * C * e + 3 * B * N * C * e + 4 * H * T
+                                                + 4 * T + 8 * B * N),
         prefix + "packed_attention_unpack": (4.0 * C * sum_n2, T * 3 * C * e + B * N * C * e + 4 * T + 4 * B * N
                                              + 4 * (B + 1) + T * C * e + 4 * H * T),
         # reads q, k, v, out rows and dy at the selected positions; writes dq | dk and d_rg at ALL token positions

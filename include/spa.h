@@ -83,8 +83,9 @@ int spa_set_option(const char* name, const char* value);
  * Launch groups: calls of several stages of a hierarchy in one launch per step.  Between spa_group_begin and
  * spa_group_end (same host thread) up to four calls each of spa_gate_select / spa_gate_select_pooled, spa_pack (no
  * counts needed, no scores), spa_pack_pair (with scores), spa_packed_attention_unpack /
- * spa_gathered_attention_unpack / spa_selected_attention_unpack, spa_packed_attention_bwd_tokens (which needs its
- * workspace here whatever max_seqlen) and spa_gate_bwd (C <= 1024) check their arguments and are noted;
+ * spa_gathered_attention_unpack / spa_selected_attention_unpack / spa_gated_attention_unpack,
+ * spa_packed_attention_bwd_tokens / spa_gated_attention_bwd_tokens (which need their workspace here whatever
+ * max_seqlen) and spa_gate_bwd (C <= 1024) check their arguments and are noted;
  * spa_group_end launches them on its stream, step by step in that order: a call sees what calls of earlier steps
  * of the group write, and a pooled gate the scores of the gate called before it.  bf16, head dim 32; for at most 256
  * tokens per image at most 64 images, and no gathered attention.  Any other call, or one outside these limits,
@@ -331,6 +332,19 @@ int spa_gathered_attention_unpack(const void* q, const void* k, const void* v, i
                                   void* stream);
 
 /*
+ * spa_gathered_attention_unpack whose values are the gated representation of the tokens: the v row of packed
+ * position j is Sigmoid(scores[i]) * x[i], i = gather_idx[j], rounded to bf16 (r_g, Section 3.2), formed on the way
+ * to the matrix units.  Results equal spa_pack_pair of q|k and x followed by spa_packed_attention_unpack, bit for
+ * bit, with no row copied.  bf16 only.
+ * in:  x [B*N, H*Dh] rows at x_row_stride; scores [B*N] fp32; the rest as above.
+ */
+int spa_gated_attention_unpack(const void* q, const void* k, const void* x, int64_t q_row_stride,
+                               int64_t k_row_stride, int64_t x_row_stride, const float* scores,
+                               const int32_t* cu_seqlens, const int32_t* gather_idx, const int32_t* inv_pos,
+                               const void* base, int B, int N, int H, int Dh, int dtype, float softmax_scale,
+                               void* out, float* lse, void* y, void* stream);
+
+/*
  * Packing order, attention and scatter in ONE call, for images of at most 256 tokens (Section 3.2:
  * the positive tokens, in token order, attend to each other inside their image; the negative tokens
  * go on directly): spa_gathered_attention_unpack without a packing index.  Every wave derives its
@@ -521,6 +535,18 @@ int spa_packed_attention_bwd_tokens(const void* q, const void* k, const void* v,
                                     void* dq, void* dk, void* dv, int64_t dq_row_stride,
                                     int64_t dk_row_stride, int64_t dv_row_stride,
                                     void* workspace, size_t workspace_bytes, void* stream);
+
+/*
+ * The backward of spa_gated_attention_unpack: spa_packed_attention_bwd_tokens with q, k and x at token positions and
+ * v = Sigmoid(scores) * x.  d_rg: the gradient of v (gate_scaled = 1 in spa_gate_bwd).  bf16 only.
+ */
+int spa_gated_attention_bwd_tokens(const void* q, const void* k, const void* x, int64_t q_row_stride,
+                                   int64_t k_row_stride, int64_t x_row_stride, const float* scores,
+                                   const void* out, const void* dy, const float* lse, const int32_t* cu_seqlens,
+                                   int B, int max_seqlen, int H, int Dh, int dtype, float softmax_scale,
+                                   const int32_t* gather_idx, const int32_t* inv_pos, int64_t rows, void* dq,
+                                   void* dk, void* d_rg, int64_t dq_row_stride, int64_t dk_row_stride,
+                                   int64_t d_rg_row_stride, void* workspace, size_t workspace_bytes, void* stream);
 
 /* Bytes of workspace spa_gate_bwd needs. Host. */
 size_t spa_gate_bwd_workspace_bytes(int B, int N, int C, int dtype);

@@ -438,20 +438,27 @@ __global__ void __launch_bounds__(256) attn_bwd_dvec_group_kernel(const Members<
   const MemberBlock mb = member_of(m, blockIdx.x);
   bwd_dvec_block<32>(m.a[mb.s], mb.block, mb.blocks);
 }
+template <int MODE>
 __global__ void __launch_bounds__(kBwdThreads) __attribute__((amdgpu_waves_per_eu(3)))
 attn_bwd_group_kernel(const Members<BwdArgs> m) {
   const MemberBlock mb = member_of(m, blockIdx.x);
-  bwd_long_block<32, kTokens>(m.a[mb.s], mb.block, mb.blocks);
+  bwd_long_block<32, MODE>(m.a[mb.s], mb.block, mb.blocks);
 }
-static thread_local Noted<BwdArgs> g_noted, g_noted_dvec;
-void group_forget_attention_bwd() { g_noted.n = g_noted_dvec.n = 0; }
-int group_flush_attention_bwd(hipStream_t st) {
-  if (g_noted.n == 0) return SPA_OK;
+static thread_local Noted<BwdArgs> g_noted[2], g_noted_dvec[2];      // packed, gated operands
+void group_forget_attention_bwd() { g_noted[0].n = g_noted[1].n = g_noted_dvec[0].n = g_noted_dvec[1].n = 0; }
+template <int MODE>
+static void flush_mode(hipStream_t st) {
+  constexpr int g = MODE == kGated;
+  if (g_noted[g].n == 0) return;
   Members<BwdArgs> m;
-  const unsigned dblocks = g_noted_dvec.members(m);
+  const unsigned dblocks = g_noted_dvec[g].members(m);
   hipLaunchKernelGGL(attn_bwd_dvec_group_kernel, dim3(dblocks), dim3(256), 0, st, m);
-  const unsigned blocks = g_noted.members(m);
-  hipLaunchKernelGGL(attn_bwd_group_kernel, dim3(blocks), dim3(kBwdThreads), 0, st, m);
+  const unsigned blocks = g_noted[g].members(m);
+  hipLaunchKernelGGL(attn_bwd_group_kernel<MODE>, dim3(blocks), dim3(kBwdThreads), 0, st, m);
+}
+int group_flush_attention_bwd(hipStream_t st) {
+  flush_mode<kTokens>(st);
+  flush_mode<kGated>(st);
   return check_launch("spa_group_end");
 }
 
@@ -898,7 +905,7 @@ static int attention_bwd_common(const char* fn, const void* q, const void* k, co
   const long ls = (long)B * max_seqlen;
   float* dvec = static_cast<float*>(workspace);
   hipStream_t st = as_stream(stream);
-  SPA_REQUIRE(!group_open() || (dtype == SPA_BF16 && Dh == 32 && at_tokens && v_scores == nullptr), SPA_ERR_UNSUPPORTED,
+  SPA_REQUIRE(!group_open() || (dtype == SPA_BF16 && Dh == 32 && at_tokens), SPA_ERR_UNSUPPORTED,
               "%s: this form cannot be part of a group", fn);
   if (dtype == SPA_F32) {
     const dim3 grid((max_seqlen + 127) / 128, H, B), block(128);
@@ -943,8 +950,8 @@ static int attention_bwd_common(const char* fn, const void* q, const void* k, co
     const unsigned grid = 2 * xcd_grid(nblk, H, B);
     const unsigned dgrid = (unsigned)std::min<long>(((long)B * max_seqlen * H * (Dh / 8) + 255) / 256, 4096L);
     if (group_open()) {
-      if (int rc = g_noted_dvec.add(fn, args, dgrid)) return rc;
-      return g_noted.add(fn, args, grid);
+      if (int rc = g_noted_dvec[v_scores != nullptr].add(fn, args, dgrid)) return rc;
+      return g_noted[v_scores != nullptr].add(fn, args, grid);
     }
 #define SPA_BWD_LONG(D)                                                                                         \
   do {                                                                                                          \
@@ -990,4 +997,21 @@ extern "C" int spa_packed_attention_bwd_tokens(const void* q, const void* k, con
                               max_seqlen, H, Dh, dtype, softmax_scale, dq, dk, dv, dq_row_stride, dk_row_stride,
                               dv_row_stride, workspace, workspace_bytes, TokenIO{gather_idx, inv_pos, (long)rows},
                               stream);
+}
+
+extern "C" int spa_gated_attention_bwd_tokens(const void* q, const void* k, const void* x, int64_t q_row_stride,
+                                              int64_t k_row_stride, int64_t x_row_stride, const float* scores,
+                                              const void* out, const void* dy, const float* lse, const int32_t* cu_seqlens,
+                                              int B, int max_seqlen, int H, int Dh, int dtype, float softmax_scale,
+                                              const int32_t* gather_idx, const int32_t* inv_pos, int64_t rows, void* dq,
+                                              void* dk, void* d_rg, int64_t dq_row_stride, int64_t dk_row_stride,
+                                              int64_t d_rg_row_stride, void* workspace, size_t workspace_bytes, void* stream) {
+  const char* fn = "spa_gated_attention_bwd_tokens";
+  SPA_REQUIRE(scores && gather_idx && inv_pos, SPA_ERR_INVALID_ARG, "%s: null pointer", fn);
+  SPA_REQUIRE(rows >= 1 && rows < 2147483647L, SPA_ERR_INVALID_ARG, "%s: rows must be in [1, 2^31)", fn);
+  SPA_REQUIRE(dtype == SPA_BF16, SPA_ERR_UNSUPPORTED, "%s: bf16 only (use spa_pack_pair + spa_packed_attention_bwd_tokens)", fn);
+  return attention_bwd_common(fn, q, k, x, q_row_stride, k_row_stride, x_row_stride, out, dy, lse, cu_seqlens, B,
+                              max_seqlen, H, Dh, dtype, softmax_scale, dq, dk, d_rg, dq_row_stride, dk_row_stride,
+                              d_rg_row_stride, workspace, workspace_bytes, TokenIO{gather_idx, inv_pos, (long)rows},
+                              stream, scores);
 }

@@ -52,6 +52,7 @@ __device__ __forceinline__ bool bypasses(const Scatter& sc, long row) {
 struct FwdArgs {
   const __bf16 *q, *k, *v;
   long qs, ks, vs;
+  const float* v_scores;       // kFwdGated: score of every token
   const int32_t *cu, *key_lens;
   int n_pad, H;
   float scale_log2;
@@ -64,10 +65,12 @@ struct FwdArgs {
 
 // Row of q / k / v that holds packed position j of a segment starting at packed row row0:
 // gi = gather_idx + row0 when the rows are gathered through the index, else null.
-// GATHER is a compile-time property of every bf16 kernel: with packed rows the index is known to be
+// GATHER is a compile-time property of every bf16 kernel: with packed rows (kFwdPacked) the index is known to be
 // absent and the row addresses stay affine in the loop counters (pointer increments), with gathered
-// rows every row address is a multiply on a loaded index.
-template <bool GATHER>
+// rows every row address is a multiply on a loaded index.  kFwdGated: gathered, and a v row is multiplied by
+// Sigmoid(score of its token) and rounded to bf16 on its way to LDS, as a packed r_g holds it.
+constexpr int kFwdPacked = 0, kFwdGathered = 1, kFwdGated = 2;
+template <int GATHER>
 __device__ __forceinline__ const int32_t* gather_base(const Scatter& sc, long row0) {
   return GATHER ? sc.gather_idx + row0 : nullptr;
 }
@@ -392,7 +395,7 @@ __device__ __forceinline__ void fwd_flush(const __bf16* tile, __bf16* out, const
 
 // Register staging of key/value rows on their way to LDS: task i = 16-byte chunk column
 // c = i % CPR of the row pair (2*(i / CPR), +1); K goes row-major, V transposed.
-template <int DH, int THREADS, int TASKS, bool GATHER>
+template <int DH, int THREADS, int TASKS, int GATHER>
 struct KvStage {
   static constexpr int CPR = DH / 8;
   static constexpr int TPT = (TASKS + THREADS - 1) / THREADS;
@@ -520,12 +523,12 @@ struct TiledLds {
 constexpr int kTiledBN = 64;
 
 // The workgroup's work on queries [q0, q0 + 32 NW) of head h of segment seg (q0 < seg.nq).
-template <int DH, int NW, bool GATHER, bool RM>
+template <int DH, int NW, int GATHER, bool RM>
 __device__ __forceinline__ void
 tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, const __bf16* __restrict__ q,
                 const __bf16* __restrict__ k, const __bf16* __restrict__ v, long qs, long ks, long vs, int H,
-                float scale_log2, __bf16* __restrict__ out, float* __restrict__ lse, long lse_stride,
-                const Scatter& sc) {
+                const float* __restrict__ v_scores, float scale_log2, __bf16* __restrict__ out, float* __restrict__ lse,
+                long lse_stride, const Scatter& sc) {
   constexpr int RS = DH + 8, BN = kTiledBN, GSB = BN / 32;
   auto& Ks = lds.Ks;
   auto& Vs = lds.Vs;
@@ -538,34 +541,43 @@ tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, c
 
   const int32_t* gi = gather_base<GATHER>(sc, seg.row0);
   const long q_src = q_ok ? source_row(gi, seg.row0, qi) : 0;   // (gathered: an index load, issued first)
-  PairStage<DH, 64 * NW, BN, GATHER, GATHER> stage;
+  PairStage<DH, 64 * NW, BN, GATHER != 0, GATHER != 0> stage;
   stage.gi = gi;
   stage.last = max(seg.nk - 1, 0);
   stage.source(0, k + h * DH, ks, seg.row0);
   stage.source(1, v + h * DH, vs, seg.row0);
+  float gate[decltype(stage)::CPT] = {};
+  auto load_tile = [&](int kt) {                                // (then the index of the one after it)
+    stage.load(kt);
+    if (GATHER == kFwdGated) {
+#pragma unroll
+      for (int t = 0; t < decltype(stage)::CPT; ++t) gate[t] = v_scores[stage.idx[t]];
+    }
+    stage.index(kt + BN);
+  };
+  auto store_tile = [&](int buf) {
+    if (GATHER == kFwdGated) stage.store_gated(Ks[buf], Vs[buf], gate);
+    else stage.store(Ks[buf], Vs[buf]);
+  };
   stage.index(0);
-  stage.load(0);
-  stage.index(BN);
+  load_tile(0);
   bf16x8 qf[DH / 16];
   load_q_frags<DH>(q + q_src * qs + h * DH, q_ok, hh, qf);
   FwdAcc<DH> acc;
   acc.init(RM ? -INFINITY : 0.f);
-  stage.store(Ks[0], Vs[0]);
+  store_tile(0);
   __syncthreads();
 
   const int nt = (seg.nk + BN - 1) / BN;
   auto tile = [&](int t, auto last) {
     const int buf = t & 1, kt = t * BN;
-    if (!last) {
-      stage.load(kt + BN);                                  // tile t + 1, whose rows were indexed a tile ago
-      stage.index(kt + 2 * BN);
-    }
+    if (!last) load_tile(kt + BN);
     if (wave_live) {
       floatx16 s[GSB];
       fwd_scores<DH, RS, GSB, !last>(Ks[buf], 0, seg.nk - kt, qf, s, l32, hh);
       fwd_softmax_pv<DH, RS, 0, GSB, !last, RM>(s, Ks[buf], Vs[buf], 0, 0, seg.nk - kt, t == 0, qf, acc, scale_log2, l32, hh);
     }
-    if (!last) stage.store(Ks[buf ^ 1], Vs[buf ^ 1]);
+    if (!last) store_tile(buf ^ 1);
     __syncthreads();
   };
   for (int t = 0; t + 1 < nt; ++t) tile(t, std::false_type{});
@@ -591,13 +603,13 @@ struct TiledShared {
   int s_cu[2 * kLptMaxB + 1];
   int s_pick;
 };
-template <int DH, int NW, bool GATHER, bool RM>
+template <int DH, int NW, int GATHER, bool RM>
 __device__ __forceinline__ void tiled_block(TiledShared<DH>& sh, const FwdArgs& a, unsigned block, unsigned blocks) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, H = a.H, B = a.B;
   const Scatter& sc = a.sc;
   auto attend = [&](const Segment& seg, int h, int q0) {
-    tiled_attention<DH, NW, GATHER, RM>(sh.lds, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, H, a.scale_log2, a.out, a.lse,
-                                    a.lse_stride, sc);
+    tiled_attention<DH, NW, GATHER, RM>(sh.lds, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, H, a.v_scores, a.scale_log2,
+                                        a.out, a.lse, a.lse_stride, sc);
   };
   if ((int)block >= a.ntile) {
     const long rows = sc.flat ? (long)sc.N : (long)B * sc.N;
@@ -633,7 +645,7 @@ __device__ __forceinline__ void tiled_block(TiledShared<DH>& sh, const FwdArgs& 
   if (q0 < seg.nq) attend(seg, tile_id.h, q0);
 }
 
-template <int DH, int NW, bool RM, bool GATHER>
+template <int DH, int NW, bool RM, int GATHER>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH == 32 ? 3 : 2)))
 attn_fwd_bf16_tiled_kernel(const FwdArgs a) {
   __shared__ TiledShared<DH> sh;
@@ -649,11 +661,11 @@ attn_fwd_bf16_tiled_kernel(const FwdArgs a) {
 // instead of concentrating a heavy (image, head) on one compute unit.
 // The wave's work on queries [q0, q0 + 32) of head h of segment seg (q0 < seg.nq): Ks, Vs are
 // its private LDS tiles of STEP rows.
-template <int DH, int STEP, bool GATHER, bool RM>
+template <int DH, int STEP, int GATHER, bool RM>
 __device__ __forceinline__ void
 wave_attention(__bf16* Ks, __bf16* Vs, const Segment seg, int h, int q0, const __bf16* __restrict__ q,
                const __bf16* __restrict__ k, const __bf16* __restrict__ v, long qs, long ks, long vs, int H,
-               float scale_log2, __bf16* __restrict__ out, float* __restrict__ lse, long lse_stride,
+               const float* __restrict__ v_scores, float scale_log2, __bf16* __restrict__ out, float* __restrict__ lse, long lse_stride,
                const Scatter& sc) {
   constexpr int RS = DH + 8, KK = DH / 16, DB = DH / 32, CPR = DH / 8;
   constexpr int NSB = STEP / 32;                 // 32-key sub-tiles per step (one softmax update)
@@ -667,6 +679,7 @@ wave_attention(__bf16* Ks, __bf16* Vs, const Segment seg, int h, int q0, const _
 
   // lane -> (row, chunk) of the step's tile: 8 (Dh 64) or 4 (Dh 32) lanes cover one row
   bf16x8 kreg[LPL], vreg[LPL];
+  float gate[LPL] = {};
   const int32_t* gi = gather_base<GATHER>(sc, seg.row0);
   int tok_rows[LPL];                              // gathered rows only: token rows of the next gload
   int kt_next = 0;                                // first key of the step the next gload fetches
@@ -699,6 +712,7 @@ wave_attention(__bf16* Ks, __bf16* Vs, const Segment seg, int h, int q0, const _
         }
         kreg[t] = *reinterpret_cast<const bf16x8*>(kp);
         vreg[t] = *reinterpret_cast<const bf16x8*>(vp);
+        if (GATHER == kFwdGated) gate[t] = v_scores[tok_rows[t]];
       }
     }
   };
@@ -707,7 +721,8 @@ wave_attention(__bf16* Ks, __bf16* Vs, const Segment seg, int h, int q0, const _
     for (int t = 0; t < LPL; ++t) {
       const int i = lane + 64 * t, r = i / CPR, c = i % CPR;
       *reinterpret_cast<bf16x8*>(&Ks[r * RS + c * 8]) = kreg[t];
-      *reinterpret_cast<bf16x8*>(&Vs[r * RS + c * 8]) = vreg[t];
+      *reinterpret_cast<bf16x8*>(&Vs[r * RS + c * 8]) =
+          GATHER == kFwdGated ? scale_row(vreg[t], sigmoidf_dev(gate[t])) : vreg[t];
     }
   };
 
@@ -745,7 +760,7 @@ struct WaveLds {
   __attribute__((aligned(16))) __bf16 Ks[STEP * RS];
   __attribute__((aligned(16))) __bf16 Vs[STEP * RS];
 };
-template <int DH, int STEP, bool RM, bool GATHER>
+template <int DH, int STEP, bool RM, int GATHER>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(STEP == 32 ? 3 : 1)))
 attn_fwd_bf16_wave_kernel(const FwdArgs a) {
   __shared__ WaveLds<DH, STEP> lds;
@@ -758,7 +773,7 @@ attn_fwd_bf16_wave_kernel(const FwdArgs a) {
   const FillRange fr = fill_range(a.sc, img, a.B, tile_id.qb, a.nqb);
   const int q0 = tile_id.qb * 32;
   if (q0 < seg.nq)
-    wave_attention<DH, STEP, GATHER, RM>(lds.Ks, lds.Vs, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H, a.scale_log2, a.out,
+    wave_attention<DH, STEP, GATHER, RM>(lds.Ks, lds.Vs, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H, a.v_scores, a.scale_log2, a.out,
                                          a.lse, a.lse_stride, a.sc);
   if (a.sc.y != nullptr) scatter_fill<__bf16, DH>(a.sc, fr.b, fr.t0, fr.t1, h, C, threadIdx.x, 64);
 }
@@ -799,7 +814,7 @@ __device__ __forceinline__ void mask_unit(MaskLds<DH, STEP>& lds, const FwdArgs&
   const FillRange fr = fill_range(a.sc, img, a.B, tile_id.qb, a.nqb);
   const int q0 = tile_id.qb * 32;
   if (q0 < n)
-    wave_attention<DH, STEP, true, false>(lds.kv.Ks, lds.kv.Vs, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H, a.scale_log2,
+    wave_attention<DH, STEP, kFwdGathered, false>(lds.kv.Ks, lds.kv.Vs, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H, a.v_scores, a.scale_log2,
                                    nullptr, nullptr, 0, scl);
   scatter_fill<__bf16, DH>(a.sc, fr.b, fr.t0, fr.t1, h, C, lane, 64);
 }
@@ -889,19 +904,19 @@ static unsigned lpt64_grid(int B, int H, int nqb) {
 
 // Compiled for three waves per SIMD (168 registers at head dim 64, no spills): a ViT-B-shaped
 // batch has ~2800 live waves for 1024 SIMDs and then runs in one round instead of two.
-template <int DH, int STEP, bool GATHER, bool RM>
+template <int DH, int STEP, int GATHER, bool RM>
 __device__ __forceinline__ void lpt64_unit(WaveLds<DH, STEP>& lds, const FwdArgs& a, int x, int j, int units) {
   const int unit = j & 31, m = j >> 5;
   const LptBlock blk = lpt64_block<32>(a.cu, a.key_lens, a.n_pad, a.B, a.H, a.nqb, x, m * 32 + ((m & 1) ? 31 - unit : unit));
   if (blk.live)
     wave_attention<DH, STEP, GATHER, RM>(lds.Ks, lds.Vs, blk.seg, blk.h, blk.q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H,
-                                     a.scale_log2, a.out, a.lse, a.lse_stride, a.sc);
+                                     a.v_scores, a.scale_log2, a.out, a.lse, a.lse_stride, a.sc);
   if (a.sc.y != nullptr) {
     const long rows = a.sc.flat ? (long)a.sc.N : (long)a.B * a.sc.N, per = (rows + units - 1) / units, u = 8L * j + x;
     scatter_fill_rows<__bf16>(a.sc, min(rows, u * per), min(rows, (u + 1) * per), (long)a.H * DH, threadIdx.x & 63);
   }
 }
-template <int DH, int STEP, bool RM, bool GATHER>
+template <int DH, int STEP, bool RM, int GATHER>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
 attn_fwd_bf16_wave_lpt64_kernel(const FwdArgs a) {
   __shared__ WaveLds<DH, STEP> lds;
@@ -909,9 +924,8 @@ attn_fwd_bf16_wave_lpt64_kernel(const FwdArgs a) {
 }
 
 // Several calls in one launch (launch groups, head dim 32): the tiled blocks of those with more than 256 tokens
-// per image, four of the one-wave units of the others per workgroup.  GATHER: rows at token positions, the
-// small ones by their mask; otherwise packed rows.
-template <bool GATHER>
+// per image, four of the one-wave units of the others (kFwdGathered: by their mask) per workgroup.
+template <int FORM>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
 attn_fwd_bf16_group_kernel(const Members<FwdArgs> m) {
   constexpr int DH = 32, STEP = 32;
@@ -922,23 +936,24 @@ attn_fwd_bf16_group_kernel(const Members<FwdArgs> m) {
   const MemberBlock mb = member_of(m, blockIdx.x);
   const FwdArgs& a = m.a[mb.s];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (a.ntile > 0) tiled_block<DH, 4, GATHER, false>(sh.tiled, a, mb.block, mb.blocks);
-  else if constexpr (GATHER) mask_unit<DH, STEP>(sh.wave[wv], a, mb.block & 7, (mb.block >> 3) * 4 + wv);
-  else lpt64_unit<DH, STEP, false, false>(sh.wave[wv].kv, a, mb.block & 7, (mb.block >> 3) * 4 + wv, mb.blocks * 4);
+  if (a.ntile > 0) tiled_block<DH, 4, FORM, false>(sh.tiled, a, mb.block, mb.blocks);
+  else if constexpr (FORM == kFwdGathered) mask_unit<DH, STEP>(sh.wave[wv], a, mb.block & 7, (mb.block >> 3) * 4 + wv);
+  else lpt64_unit<DH, STEP, FORM, false>(sh.wave[wv].kv, a, mb.block & 7, (mb.block >> 3) * 4 + wv, mb.blocks * 4);
 }
 
-static thread_local Noted<FwdArgs> g_noted[2];       // packed, gathered
-void group_forget_attention() { g_noted[0].n = g_noted[1].n = 0; }
-int group_flush_attention(hipStream_t st) {
+static thread_local Noted<FwdArgs> g_noted[3];       // by form
+void group_forget_attention() { g_noted[0].n = g_noted[1].n = g_noted[2].n = 0; }
+template <int FORM>
+static void flush_form(hipStream_t st) {
+  if (g_noted[FORM].n == 0) return;
   Members<FwdArgs> m;
-  if (g_noted[0].n > 0) {
-    const unsigned blocks = g_noted[0].members(m);
-    hipLaunchKernelGGL((attn_fwd_bf16_group_kernel<false>), dim3(blocks), dim3(256), 0, st, m);
-  }
-  if (g_noted[1].n > 0) {
-    const unsigned blocks = g_noted[1].members(m);
-    hipLaunchKernelGGL((attn_fwd_bf16_group_kernel<true>), dim3(blocks), dim3(256), 0, st, m);
-  }
+  const unsigned blocks = g_noted[FORM].members(m);
+  hipLaunchKernelGGL((attn_fwd_bf16_group_kernel<FORM>), dim3(blocks), dim3(256), 0, st, m);
+}
+int group_flush_attention(hipStream_t st) {
+  flush_form<kFwdPacked>(st);
+  flush_form<kFwdGathered>(st);
+  flush_form<kFwdGated>(st);
   return check_launch("spa_group_end");
 }
 static unsigned wave_groups(unsigned waves) { return (waves / 8 + 3) / 4 * 8; }      // workgroups of four one-wave units
@@ -947,7 +962,7 @@ static unsigned wave_groups(unsigned waves) { return (waves / 8 + 3) / 4 * 8; } 
 // rows of the segment are staged once (each element is read from memory exactly once per
 // head), one barrier, then wave w owns queries [32w, 32w+32) and walks the keys in LDS with
 // no further synchronisation.  No workgroup is launched for nothing.
-template <int DH, int NKMAX, bool GATHER>
+template <int DH, int NKMAX, int GATHER>
 __global__ void __launch_bounds__(2 * NKMAX)
 attn_fwd_bf16_whole_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                            const __bf16* __restrict__ v, long qs, long ks, long vs,
@@ -1171,7 +1186,8 @@ attn_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
 static int attention_common(const char* fn, const void* q, const void* k, const void* v,
                             int64_t q_stride, int64_t k_stride, int64_t v_stride, const int32_t* cu, const int32_t* key_lens, int B,
                             int n_max, int H, int Dh, int dtype, float softmax_scale, void* out,
-                            float* lse, const Scatter& sc, void* stream, bool running_max = false) {
+                            float* lse, const Scatter& sc, void* stream, bool running_max = false,
+                            const float* v_scores = nullptr) {
   SPA_REQUIRE(q && k && v && (out || sc.y) && (cu || key_lens), SPA_ERR_INVALID_ARG, "%s: null pointer", fn);
   SPA_REQUIRE(B >= 1 && n_max >= 1 && H >= 1, SPA_ERR_INVALID_ARG, "%s: B, max_seqlen, H must be >= 1", fn);
   SPA_REQUIRE((long)B * n_max < 2147483647L, SPA_ERR_INVALID_ARG, "%s: B*max_seqlen must be < 2^31", fn);
@@ -1206,8 +1222,9 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
 #undef SPA_F32_LAUNCH
   } else {
     const float scale_log2 = scale * 1.4426950408889634f;
-    FwdArgs args = {(const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_stride, (long)k_stride, (long)v_stride, cu,
-                    key_lens, n_max, H, scale_log2, (__bf16*)out, lse, lse_stride, sc, B, 0, 0};
+    FwdArgs args = {(const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_stride, (long)k_stride, (long)v_stride, v_scores,
+                    cu, key_lens, n_max, H, scale_log2, (__bf16*)out, lse, lse_stride, sc, B, 0, 0};
+    const int form = v_scores != nullptr ? kFwdGated : sc.gathered ? kFwdGathered : kFwdPacked;
     const auto live = [&] { return key_lens == nullptr && live_tiles_apply(H, B); };
     // the tiled kernel's workgroups: resident together 3 waves per SIMD at head dim 32, 2 at 64
     const auto tiled_grid = [&] {
@@ -1218,26 +1235,27 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
       return (unsigned)(args.ntile + std::min<long>((rows + 31) / 32, 1024));
     };
     if (group_open()) {
-      SPA_REQUIRE(Dh == 32 && key_lens == nullptr && !running_max && (n_max > 256 || (!sc.gathered && B <= kWave)),
+      SPA_REQUIRE(Dh == 32 && key_lens == nullptr && !running_max && (n_max > 256 || (form != kFwdGathered && B <= kWave)),
                   SPA_ERR_UNSUPPORTED,
                   "%s: this form cannot be part of a group", fn);
       if (n_max > 256) {
         const unsigned blocks = tiled_grid();
-        return g_noted[sc.gathered].add(fn, args, (blocks + 7) / 8 * 8);
+        return g_noted[form].add(fn, args, (blocks + 7) / 8 * 8);
       }
       args.nqb = (n_max + 31) / 32;
-      return g_noted[0].add(fn, args, wave_groups(lpt64_grid(B, H, args.nqb)));
+      return g_noted[form].add(fn, args, wave_groups(lpt64_grid(B, H, args.nqb)));
     }
 #define SPA_ARGS_PLAIN SPA_ARGS
 #define SPA_LAUNCH_MAX(KERNEL, GRID, BLOCK, ARGS, ...)                                                        \
   do {                                                                                                        \
-    if (running_max) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, true, false>), GRID, BLOCK, 0, st, ARGS);        \
+    if (running_max) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, true, kFwdPacked>), GRID, BLOCK, 0, st, ARGS);   \
+    else if (form == kFwdGated) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, false, kFwdGated>), GRID, BLOCK, 0, st, ARGS); \
     else SPA_LAUNCH(KERNEL, GRID, BLOCK, ARGS, __VA_ARGS__, false);                                           \
   } while (0)
 #define SPA_LAUNCH(KERNEL, GRID, BLOCK, ARGS, ...)                                                            \
   do {                                                                                                        \
-    if (sc.gathered) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, true>), GRID, BLOCK, 0, st, ARGS);               \
-    else hipLaunchKernelGGL((KERNEL<__VA_ARGS__, false>), GRID, BLOCK, 0, st, ARGS);                          \
+    if (sc.gathered) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFwdGathered>), GRID, BLOCK, 0, st, ARGS);       \
+    else hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFwdPacked>), GRID, BLOCK, 0, st, ARGS);                     \
   } while (0)
 #define SPA_ARGS                                                                                              \
   (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_stride, (long)k_stride, (long)v_stride, cu,   \
@@ -1248,7 +1266,7 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
     const bool tiled = opt.fwd_tiled;
     const bool use_whole = opt.fwd_whole;
     const int wave_max = opt.fwd_wave_max;
-    if (!tiled && n_max <= wave_max && !use_whole) {
+    if (!tiled && n_max <= wave_max && (!use_whole || form == kFwdGated)) {
       // short segments: one wave per (image, head, 32 queries)
       const int nqb = (n_max + 31) / 32;
       const dim3 grid(xcd_grid(nqb, H, B));
@@ -1266,7 +1284,7 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
         if (step64) SPA_LAUNCH_MAX(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 64, 64);
         else SPA_LAUNCH_MAX(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 64, 32);
       }
-    } else if (!tiled && n_max <= 256) {
+    } else if (!tiled && n_max <= 256 && form != kFwdGated) {
       // short segments: one workgroup per (image, head), whole segment in LDS
       const dim3 grid(H, B);
 #define SPA_WHOLE(D)                                                                                          \
@@ -1355,6 +1373,20 @@ extern "C" int spa_gathered_attention_unpack(const void* q, const void* k, const
                           dtype, softmax_scale, out, lse, sc, stream);
 }
 
+extern "C" int spa_gated_attention_unpack(const void* q, const void* k, const void* x, int64_t q_row_stride,
+                                          int64_t k_row_stride, int64_t x_row_stride, const float* scores,
+                                          const int32_t* cu_seqlens, const int32_t* gather_idx, const int32_t* inv_pos,
+                                          const void* base, int B, int N, int H, int Dh, int dtype, float softmax_scale,
+                                          void* out, float* lse, void* y, void* stream) {
+  const char* fn = "spa_gated_attention_unpack";
+  SPA_REQUIRE(scores && cu_seqlens && gather_idx && inv_pos && y, SPA_ERR_INVALID_ARG, "%s: null pointer", fn);
+  SPA_REQUIRE(aligned16(y) && aligned16(base), SPA_ERR_INVALID_ARG, "%s: y / base not 16-byte aligned", fn);
+  SPA_REQUIRE(dtype == SPA_BF16, SPA_ERR_UNSUPPORTED, "%s: bf16 only (use spa_pack_pair + spa_packed_attention_unpack)", fn);
+  const Scatter sc = {gather_idx, inv_pos, base, y, N, 0, 1, nullptr};
+  return attention_common(fn, q, k, x, q_row_stride, k_row_stride, x_row_stride, cu_seqlens, nullptr, B, N, H, Dh, dtype,
+                          softmax_scale, out, lse, sc, stream, false, scores);
+}
+
 extern "C" int spa_selected_attention_unpack(const void* q, const void* k, const void* v, int64_t q_row_stride,
                                              int64_t k_row_stride, int64_t v_row_stride, const uint8_t* mask,
                                              const void* base, int B, int N, int H, int Dh, int dtype,
@@ -1394,7 +1426,7 @@ extern "C" int spa_selected_attention_unpack(const void* q, const void* k, const
     return check_launch(fn);
   }
   const FwdArgs args = {(const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_row_stride, (long)k_row_stride,
-                        (long)v_row_stride, nullptr, nullptr, N, H, scale_log2, nullptr, nullptr, 0L, sc, B, nqb, 0};
+                        (long)v_row_stride, nullptr, nullptr, nullptr, N, H, scale_log2, nullptr, nullptr, 0L, sc, B, nqb, 0};
   if (group_open()) {
     SPA_REQUIRE(Dh == 32, SPA_ERR_UNSUPPORTED, "%s: this form cannot be part of a group", fn);
     return g_noted[1].add(fn, args, wave_groups(grid.x));

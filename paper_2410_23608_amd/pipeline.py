@@ -169,7 +169,8 @@ class TrainPass(_Pass):
     fused_bwd (default): the gather of dy and the scatters of dq, dk, dv run inside the
     attention backward, 6 calls instead of 9.
     pack_pair (default): q|k and the gated x are packed by one launch (the survivors are counted
-    and ranked once), 5 calls.
+    and ranked once), 5 calls; in bf16 with fused_bwd no row is packed at all: packing builds the index and
+    the attention kernels fetch the rows through it and gate v on the way (same results, bit for bit).
     """
 
     def __init__(self, B: int, N: int, C: int, H: int, dtype: str, tau: float = 0.5, bias: float = 0.0,
@@ -177,6 +178,7 @@ class TrainPass(_Pass):
         self.B, self.N, self.C, self.H, self.Dh = B, N, C, H, C // H
         self.fused_bwd = True if fused_bwd is None else fused_bwd
         self.pack_pair = pack_pair
+        self.gated = dtype == "bf16" and pack_pair and self.fused_bwd
         self.tau, self.bias = tau, bias
         self.loss_scale = 0.01 / (B * N) if loss_scale is None else loss_scale
         td, cap = _td(dtype), B * N
@@ -184,8 +186,8 @@ class TrainPass(_Pass):
         dv = dict(device="cuda")
         self.scores = torch.empty(B, N, dtype=torch.float32, **dv)
         self.mask = torch.empty(B, N, dtype=torch.uint8, **dv)
-        self.packed_qk = torch.zeros(cap, 2 * C, dtype=td, **dv)
-        self.packed_v = torch.zeros(cap, C, dtype=td, **dv)
+        self.packed_qk = None if self.gated else torch.zeros(cap, 2 * C, dtype=td, **dv)
+        self.packed_v = None if self.gated else torch.zeros(cap, C, dtype=td, **dv)
         self.cu_seqlens = torch.zeros(B + 1, dtype=torch.int32, **dv)
         self.gather_idx = torch.zeros(cap, dtype=torch.int32, **dv)
         self.inv_pos = torch.zeros(cap, dtype=torch.int32, **dv)
@@ -237,9 +239,26 @@ class TrainPass(_Pass):
 
     def _stages(self, x, w, qk, labels, dy) -> List[Tuple[str, Callable[[], None]]]:
         C = self.C
+        B, N, H, Dh = self.B, self.N, self.H, self.Dh
+        if self.gated:
+            t, xt, dqk_tok = qk.view(B * N, 2 * C), x.view(B * N, C), self.dqk.view(B * N, 2 * C)
+            return [
+                ("gate_select", spa.spa_gate_select(x, w, self.bias, None, self.tau, self.scores, self.mask, None, prepare=True)),
+                ("pack_indices", spa.spa_pack(None, self.mask, None, None, 0, None, self.cu_seqlens, self.gather_idx,
+                                              self.inv_pos, self.total, prepare=True)),
+                ("gated_attention_unpack", spa.spa_gated_attention_unpack(
+                    t[:, :C], t[:, C:], xt, self.scores, self.cu_seqlens, self.gather_idx, self.inv_pos, None, H, Dh,
+                    self.y, self.out, self.lse, prepare=True)),
+                ("gated_attention_bwd_tokens", spa.spa_gated_attention_bwd_tokens(
+                    t[:, :C], t[:, C:], xt, self.scores, self.out, dy, self.lse, self.cu_seqlens, B, N, H, Dh,
+                    self.gather_idx, self.inv_pos, dqk_tok[:, :C], dqk_tok[:, C:], self.d_rg.view(B * N, C), self.ws_attn,
+                    prepare=True)),
+                ("gate_bwd", spa.spa_gate_bwd(x, w, self.bias, self.scores, None, labels, self.d_rg, True,
+                                              self.loss_scale, self.loss, self.dx, self.dw, self.db, self.ws_gate,
+                                              prepare=True)),
+            ]
         pq, pk, pv = self.packed_qk[:, :C], self.packed_qk[:, C:], self.packed_v
         dq, dk = self.dqk_packed[:, :C], self.dqk_packed[:, C:]
-        B, N, H, Dh = self.B, self.N, self.H, self.Dh
         if self.fused_bwd:
             dqk_tok = self.dqk.view(B * N, 2 * C)
             attention_bwd = [("packed_attention_bwd_tokens", spa.spa_packed_attention_bwd_tokens(
@@ -610,7 +629,7 @@ class HierarchyTrainPass(_Pass):
                 st = tp.stages(xs[i], ws[i], qks[i], labels[i], dys[i],
                                s_fine=self.passes[i - 1].scores if i > 0 else None, grid=(cfg[1], cfg[2]))
             chains.append(st)
-        if not self.concurrent and _groupable(self.cfg) and all(tp.pack_pair and tp.fused_bwd for tp in self.passes):
+        if not self.concurrent and _groupable(self.cfg) and all(tp.gated for tp in self.passes):
             # gate, pack, attention + scatter, attention backward, gate backward
             return [(name, spa.group(*(st[j][1] for st in chains))) for j, (name, _) in enumerate(chains[0])]
         chains = [[(f"s{i + 1}.{n}", f) for n, f in st] for i, st in enumerate(chains)]

@@ -33,13 +33,14 @@ CHAINS = {
                          ("attn_fwd", "gathered_attention_unpack")],
     "forward_packed": [("gate_select_kernel", "gate_select"), ("pack_kernel", "pack"),
                        ("attn_fwd", "packed_attention_unpack")],
-    "train": [("gate_select_kernel", "gate_select"), ("pack_kernel", "pack_qk_rg"), ("attn_fwd", "packed_attention_unpack"),
-              ("attn_bwd", "packed_attention_bwd_tokens"), ("gate_bwd", "gate_bwd")],
+    "train": [("gate_select_kernel", "gate_select"), ("pack_kernel", "pack_indices"), ("attn_fwd", "gated_attention_unpack"),
+              ("attn_bwd", "gated_attention_bwd_tokens"), ("gate_bwd", "gate_bwd")],
 }
-CHAINS["hierarchy"] = [("gate_pyramid_kernel", "gate_select"), ("pack_group_kernel", "pack_qk_rg"),
-                       ("attn_fwd_bf16_group_kernel", "packed_attention_unpack"), ("attn_bwd_dvec_group", "packed_attention_bwd_tokens"),
-                       ("attn_bwd_group", "packed_attention_bwd_tokens"), ("gate_bwd_group", "gate_bwd"),
-                       ("gate_bwd_reduce_group", "gate_bwd")]
+CHAINS["hierarchy"] = [("gate_pyramid_kernel", "gate_select"), ("pack_group_kernel", "pack_indices"),
+                       ("attn_fwd_bf16_group_kernel<1>", "gathered_attention_unpack"),      # the forward-only chain
+                       ("attn_fwd_bf16_group_kernel<2>", "gated_attention_unpack"),
+                       ("attn_bwd_dvec_group", "gated_attention_bwd_tokens"), ("attn_bwd_group", "gated_attention_bwd_tokens"),
+                       ("gate_bwd_group", "gate_bwd"), ("gate_bwd_reduce_group", "gate_bwd")]
 # a whole bench.py run (every configuration and the extras): calls named by kind only
 CHAINS["all"] = [("gate_select_kernel", "gate"), ("count_selected", "gate"), ("pack_kernel", "pack"), ("unpack_kernel", "unpack"),
                  ("gather_rows", "unpack / pack backward"), ("attn_fwd", "attention forward"), ("attn_bwd", "attention backward"),
@@ -99,13 +100,8 @@ def grid_of(r) -> int:
 
 
 def call_of(name: str, chain: str):
-    if chain == "hierarchy":       # the run also holds the forward-only chain
-        if "pack_group_kernel<false, false>" in short(name):
-            return "pack_indices"
-        if "attn_fwd_bf16_group_kernel<true>" in short(name):
-            return "gathered_attention_unpack"
     for sub, call in CHAINS[chain]:
-        if sub in name:
+        if sub in name or sub in short(name):
             return call
     return None
 

@@ -63,6 +63,8 @@ _SIGNATURES = {
                                             c_int, c_int, c_float, _P, _P, _P, _P]),
     "spa_gathered_attention_unpack": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, _P, _P, _P, c_int, c_int, c_int,
                                               c_int, c_int, c_float, _P, _P, _P, _P]),
+    "spa_gated_attention_unpack": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, _P, _P, _P, _P, c_int, c_int, c_int,
+                                           c_int, c_int, c_float, _P, _P, _P, _P]),
     "spa_selected_attention_unpack": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, _P, c_int, c_int, c_int, c_int,
                                               c_int, c_float, _P, _P]),
     "spa_segment_attention_unpack": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, c_int, c_int, _P, _P, _P, c_int64,
@@ -87,6 +89,9 @@ _SIGNATURES = {
     "spa_packed_attention_bwd_tokens": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, _P, _P, _P, c_int, c_int,
                                                 c_int, c_int, c_int, c_float, _P, _P, c_int64, _P, _P, _P, c_int64,
                                                 c_int64, c_int64, _P, c_size_t, _P]),
+    "spa_gated_attention_bwd_tokens": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, _P, _P, _P, _P, c_int, c_int,
+                                               c_int, c_int, c_int, c_float, _P, _P, c_int64, _P, _P, _P, c_int64,
+                                               c_int64, c_int64, _P, c_size_t, _P]),
     "spa_gate_bwd_workspace_bytes": (c_size_t, [c_int, c_int, c_int, c_int]),
     "spa_gate_bwd": (c_int, [_P, _P, c_float, _P, _P, _P, _P, c_int, c_float, c_int, c_int, c_int, c_int,
                              _P, _P, _P, _P, _P, c_size_t, _P]),
@@ -521,6 +526,23 @@ def spa_gathered_attention_unpack(q, k, v, cu_seqlens, gather_idx, inv_pos, base
                       _ptr(out), _ptr(lse), _ptr(y), _stream(),), _keep, prepare)
 
 
+def spa_gated_attention_unpack(q, k, x, scores, cu_seqlens, gather_idx, inv_pos, base, H, Dh, y, out=None, lse=None,
+                               softmax_scale=0.0, prepare=False):
+    """spa_gathered_attention_unpack with v = Sigmoid(scores) * x (scores [B,N] f32)."""
+    fn = "spa_gated_attention_unpack"
+    B, N, C = y.shape
+    _, code = _scatter_checks(fn, q, k, x, cu_seqlens, B, N, gather_idx, inv_pos, base, H, Dh, y, out, lse)
+    _typed(fn, torch.float32, scores=scores)
+    _rows(fn, C, q=(q, B * N), k=(k, B * N), x=(x, B * N))
+    _holds(fn, scores=(scores, B * N))
+    _keep = (q, k, x, scores, cu_seqlens, gather_idx, inv_pos, base, y, out, lse,)
+    _contig(scores, cu_seqlens, gather_idx, inv_pos, base, y, out, lse)
+    return _dispatch(lib.spa_gated_attention_unpack,
+                     (_ptr(q), _ptr(k), _ptr(x), _row_stride(q), _row_stride(k), _row_stride(x), _ptr(scores),
+                      _ptr(cu_seqlens), _ptr(gather_idx), _ptr(inv_pos), _ptr(base), B, N, H, Dh, code,
+                      float(softmax_scale), _ptr(out), _ptr(lse), _ptr(y), _stream(),), _keep, prepare)
+
+
 def spa_selected_attention_unpack(q, k, v, mask, base, H, Dh, y, softmax_scale=0.0, prepare=False):
     """Attention over the selected tokens of every image straight from the mask (no packing index), scatter
     and bypass included: q, k, v [B*N, H*Dh] tensors or column-slice views at token positions, mask [B,N]
@@ -758,6 +780,31 @@ def spa_packed_attention_bwd_tokens(q, k, v, out, dy, lse, cu_seqlens, B, max_se
                       _ptr(lse), _ptr(cu_seqlens), B, max_seqlen, H, Dh, code, float(softmax_scale),
                       _ptr(gather_idx), _ptr(inv_pos), rows, _ptr(dq), _ptr(dk), _ptr(dv), _row_stride(dq),
                       _row_stride(dk), _row_stride(dv), _ptr(workspace), ws_bytes, _stream(),), _keep, prepare)
+
+
+def spa_gated_attention_bwd_tokens(q, k, x, scores, out, dy, lse, cu_seqlens, B, max_seqlen, H, Dh, gather_idx, inv_pos,
+                                   dq, dk, d_rg, workspace=None, softmax_scale=0.0, prepare=False):
+    """The backward of spa_gated_attention_unpack, everything but out and lse at token positions
+    (workspace: only for max_seqlen > 256, and in a launch group)."""
+    fn = "spa_gated_attention_bwd_tokens"
+    C = H * Dh
+    rows = dy.numel() // dy.shape[-1]
+    code = _features(fn, q=q, k=k, x=x, out=out, dy=dy, dq=dq, dk=dk, d_rg=d_rg)
+    _typed(fn, torch.int32, cu_seqlens=cu_seqlens, gather_idx=gather_idx, inv_pos=inv_pos)
+    _typed(fn, torch.float32, lse=lse, scores=scores)
+    if dy.shape[-1] != C:
+        raise ValueError(f"{fn}: dy must be [..., H*Dh]")
+    _rows(fn, C, q=(q, rows), k=(k, rows), x=(x, rows), out=(out, 1), dq=(dq, rows), dk=(dk, rows), d_rg=(d_rg, rows))
+    _holds(fn, cu_seqlens=(cu_seqlens, B + 1), lse=(lse, H * B * max_seqlen), gather_idx=(gather_idx, rows),
+           inv_pos=(inv_pos, rows), scores=(scores, rows))
+    _keep = (q, k, x, scores, dq, dk, d_rg, out, dy, lse, cu_seqlens, gather_idx, inv_pos, workspace,)
+    _contig(scores, out, dy, lse, cu_seqlens, gather_idx, inv_pos, workspace)
+    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    return _dispatch(lib.spa_gated_attention_bwd_tokens,
+                     (_ptr(q), _ptr(k), _ptr(x), _row_stride(q), _row_stride(k), _row_stride(x), _ptr(scores), _ptr(out),
+                      _ptr(dy), _ptr(lse), _ptr(cu_seqlens), B, max_seqlen, H, Dh, code, float(softmax_scale),
+                      _ptr(gather_idx), _ptr(inv_pos), rows, _ptr(dq), _ptr(dk), _ptr(d_rg), _row_stride(dq),
+                      _row_stride(dk), _row_stride(d_rg), _ptr(workspace), ws_bytes, _stream(),), _keep, prepare)
 
 
 def spa_gate_bwd_workspace_bytes(B, N, C, dtype) -> int:
