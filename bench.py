@@ -718,7 +718,7 @@ def measure_extras(wl, ctx, args, torch, spa, workloads, pipeline):
     dy_blk = torch.randn(VB, VN, VC, generator=g).cuda().to(torch.bfloat16)
     lab_blk = torch.from_numpy(vb["labels"]).cuda()
     blk_train = {}
-    for key, ov in (("two_streams", True), ("one_stream", False)):
+    for key, ov in (("weight_side_beside", True), ("in_order", False)):
         btp = pipeline.BlockTrainPass(VB, VN, VC, VH, "bf16", vwl.tau, vwl.bias, overlap_weight_grads=ov)
         tst = btp.stages(vx, vw, W_qkv, b_qkv, W_o, b_o, lab_blk, dy_blk)
         tmed = run_chain(tst)

@@ -85,7 +85,9 @@ int spa_set_option(const char* name, const char* value);
  * counts needed, no scores), spa_pack_pair (with scores), spa_packed_attention_unpack /
  * spa_gathered_attention_unpack / spa_selected_attention_unpack / spa_gated_attention_unpack,
  * spa_packed_attention_bwd_tokens / spa_gated_attention_bwd_tokens (which need their workspace here whatever
- * max_seqlen) and spa_gate_bwd (C <= 1024) check their arguments and are noted;
+ * max_seqlen) and spa_gate_bwd (C <= 1024), and one spa_linear_packed_bwd_input with up to two
+ * spa_linear_packed_bwd_weight (without gate_scores; one launch unless the input side takes 256 x 256 tiles), check
+ * their arguments and are noted;
  * spa_group_end launches them on its stream, step by step in that order: a call sees what calls of earlier steps
  * of the group write, and a pooled gate the scores of the gate called before it.  bf16, head dim 32; for at most 256
  * tokens per image at most 64 images, and no gathered attention.  Any other call, or one outside these limits,

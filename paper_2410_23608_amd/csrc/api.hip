@@ -126,6 +126,7 @@ extern "C" int spa_group_begin(void) {
   group_forget_pack();
   group_forget_attention();
   group_forget_attention_bwd();
+  group_forget_linear();
   g_group_open = true;
   return SPA_OK;
 }
@@ -139,5 +140,6 @@ extern "C" int spa_group_end(void* stream) {
   if (int rc = group_flush_pack(st)) return rc;
   if (int rc = group_flush_attention(st)) return rc;
   if (int rc = group_flush_attention_bwd(st)) return rc;
-  return group_flush_gates_bwd(st);
+  if (int rc = group_flush_gates_bwd(st)) return rc;
+  return group_flush_linear(st);
 }

@@ -3,8 +3,8 @@
 // per stage and step.  A dependent launch costs about 4 us however small it is.
 //
 // Between begin and end an entry point only notes its kernel's arguments (thread-local); end launches what was noted
-// step by step: gates, packing, attention, attention backward, gate backward.  A kernel of a group takes the
-// arguments of up to kGroupMax calls, the workgroups of call s being [end[s-1], end[s]).
+// step by step: gates, packing, attention, attention backward, gate backward, projection backward.  A kernel of a
+// group takes the arguments of up to kGroupMax calls, the workgroups of call s being [end[s-1], end[s]).
 #pragma once
 #include "spa_common.h"
 
@@ -65,9 +65,11 @@ int group_flush_pack(hipStream_t st);
 int group_flush_attention(hipStream_t st);
 int group_flush_attention_bwd(hipStream_t st);
 int group_flush_gates_bwd(hipStream_t st);
+int group_flush_linear(hipStream_t st);
 void group_forget_gates();
 void group_forget_pack();
 void group_forget_attention();
 void group_forget_attention_bwd();
+void group_forget_linear();
 
 }  // namespace spa

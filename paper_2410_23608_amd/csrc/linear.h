@@ -25,5 +25,7 @@ struct GemmArgs {
 
 // deep = false: out = A W^T (W [ncols][kc]); true: out = A W (W [kc][ncols]).
 int launch_gemm_rows(const char* fn, const GemmArgs& args, bool deep, hipStream_t st);
+// Inside a launch group (linear_bwd.hip): the row GEMM of a backward input side is noted; big: with 256 x 256 tiles.
+int group_note_rows(const char* fn, const GemmArgs& args, bool big);
 
 }  // namespace spa

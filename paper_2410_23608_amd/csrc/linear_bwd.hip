@@ -19,10 +19,13 @@
 // multiplied by the gate scale and rounded on the way cannot go straight to LDS and keep the kernel that
 // stages them through registers (linear_bwd_weight_bf16_kernel).
 // fp32 (tiny workload): one thread per output element.
-#include <stdlib.h>
+#include <algorithm>
+#include <cstdlib>
 
 #include "attn_tiles.h"
 #include "gemm_async.h"
+#include "gemm_rows.h"
+#include "group.h"
 #include "linear.h"
 #include "spa_common.h"
 
@@ -96,10 +99,10 @@ struct WeightItem {
   int split, n0, k0, m_begin, m_end;
   bool valid;
 };
-__device__ __forceinline__ WeightItem weight_item(int M, int splits, int n_tiles, int k_tiles, int live_min) {
+__device__ __forceinline__ WeightItem weight_item(int M, int splits, int n_tiles, int k_tiles, int live_min, unsigned block) {
   const TokenSplit ts = token_split(M, splits);
   const int tiles = n_tiles * k_tiles, items = max(ts.live, live_min) * tiles, per_xcd = (items + 7) >> 3;
-  const int xcd = blockIdx.x & 7, jx = blockIdx.x >> 3, item = xcd * per_xcd + jx;
+  const int xcd = block & 7, jx = block >> 3, item = xcd * per_xcd + jx;
   WeightItem w = {};
   w.valid = jx < per_xcd && item < items;
   w.split = item / tiles;
@@ -142,18 +145,27 @@ __device__ __forceinline__ void store_weight_block(const floatx16 (&acc)[2][2], 
 // zeros past the chunk's end.  kGather: rows of g / x are named by index arrays (null: in order), read one
 // step ahead of the loads that use them.  12544 rows, 2304 x 768, with the
 // reduction: gathered 97 -> 80 us, in order 68 us; 98 rows of 384 x 1152: 9.8 -> 6.2 us.
+struct WeightArgs {
+  const __bf16* dout;
+  const int32_t* dout_idx;
+  long ldd;
+  const __bf16* x;
+  const int32_t *x_idx, *total;
+  int m_cap, K, n_out, splits, n_tiles, k_tiles;
+  float *part_w, *part_b;
+};
 template <bool kGather>
-__global__ void __launch_bounds__(kLbThreads) __attribute__((amdgpu_waves_per_eu(2)))
-weight_gemm_kernel(const __bf16* __restrict__ dout, const int32_t* __restrict__ dout_idx, long ldd,
-                   const __bf16* __restrict__ x, const int32_t* __restrict__ x_idx, const int32_t* __restrict__ total,
-                   int m_cap, int K, int n_out, int splits, int n_tiles, int k_tiles, float* __restrict__ part_w,
-                   float* __restrict__ part_b) {
+__device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned char* lb_smem, unsigned block) {
   constexpr int STAGES = 2;
   using P = DeepPieces<kLbT, kLbThreads>;
-  extern __shared__ __attribute__((aligned(16))) unsigned char lb_smem[];
   __bf16* lds = reinterpret_cast<__bf16*>(lb_smem);
+  const __bf16 *dout = a.dout, *x = a.x;
+  const int32_t *dout_idx = a.dout_idx, *x_idx = a.x_idx, *total = a.total;
+  const long ldd = a.ldd;
+  const int m_cap = a.m_cap, K = a.K, n_out = a.n_out;
+  float *part_w = a.part_w, *part_b = a.part_b;
   const int M = total != nullptr ? min(total[0], m_cap) : m_cap;
-  const WeightItem w = weight_item(M, splits, n_tiles, k_tiles, 1);
+  const WeightItem w = weight_item(M, a.splits, a.n_tiles, a.k_tiles, 1, block);
   if (!w.valid) return;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
   const int wn = (wv >> 1) * 64, wk = (wv & 1) * 64;
@@ -217,6 +229,34 @@ weight_gemm_kernel(const __bf16* __restrict__ dout, const int32_t* __restrict__ 
       if (n < n_out) part_b[(long)w.split * n_out + n] = accb[i][0];   // every row of the tile holds the column sums
     }
   }
+}
+
+template <bool kGather>
+__global__ void __launch_bounds__(kLbThreads) __attribute__((amdgpu_waves_per_eu(2))) weight_gemm_kernel(const WeightArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lb_smem[];
+  weight_gemm_block<kGather>(a, lb_smem, blockIdx.x);
+}
+
+// A launch group of the projections' backward: an input side with 128 x 128 tiles and up to two weight sides in one
+// launch (and the sums of both weight sides' chunks in one more).  On their own they leave units idle (98 rows, 384
+// columns: 3 to 9 tiles) and wait for each other.  At 3136 rows of 384 columns the training step of a block takes
+// 93 us so, 115 with the GEMMs one after the other and 110 with the weight sides on a second stream.
+struct LinearGroup {
+  GemmArgs rows;
+  WeightArgs w[2];
+  unsigned end[2];               // workgroups of the input side, and of it and the first weight side
+};
+__global__ void __launch_bounds__(kLbThreads) __attribute__((amdgpu_waves_per_eu(2))) linear_bwd_group_kernel(const LinearGroup g) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lb_smem[];
+  const unsigned block = blockIdx.x;
+  if (block < g.end[0]) {
+    gemm_rows_block<false, true, 128, 128, 2, 2, 2>(g.rows, lb_smem, block, g.end[0]);
+    return;
+  }
+  const int s = block >= g.end[1];
+  const WeightArgs& a = g.w[s];
+  if (a.dout_idx != nullptr || a.x_idx != nullptr) weight_gemm_block<true>(a, lb_smem, block - g.end[s]);
+  else weight_gemm_block<false>(a, lb_smem, block - g.end[s]);
 }
 
 // part_w[split][n][k] = sum over the chunk's rows j of g_j[n] r_j[k]; part_b[split][n] = sum g_j[n]
@@ -403,25 +443,37 @@ linear_bwd_weight_bf16_kernel(const __bf16* __restrict__ dout, const int32_t* __
 }
 
 // dW = sum of the partial tiles in chunk order; dbias likewise
-__global__ void __launch_bounds__(256)
-linear_bwd_weight_reduce_kernel(const float* __restrict__ part_w, const float* __restrict__ part_b,
-                                const int32_t* __restrict__ total, int m_cap, int splits, long nk, int n_out,
-                                float* __restrict__ dW, float* __restrict__ dbias) {
-  const int M = total != nullptr ? min(total[0], m_cap) : m_cap;
-  const int live = token_split(M, splits).live;
-  const long quads = nk >> 2, work = quads + (dbias != nullptr ? n_out : 0);
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < work; i += (long)gridDim.x * blockDim.x) {
+struct WeightReduceArgs {
+  const float *part_w, *part_b;
+  const int32_t* total;
+  int m_cap, splits;
+  long nk;
+  int n_out;
+  float *dW, *dbias;
+};
+__device__ __forceinline__ void weight_reduce_block(const WeightReduceArgs& a, unsigned block, unsigned blocks) {
+  const int M = a.total != nullptr ? min(a.total[0], a.m_cap) : a.m_cap;
+  const int live = token_split(M, a.splits).live;
+  const long quads = a.nk >> 2, work = quads + (a.dbias != nullptr ? a.n_out : 0);
+  for (long i = (long)block * blockDim.x + threadIdx.x; i < work; i += (long)blocks * blockDim.x) {
     if (i < quads) {
-      floatx4 a = {0.f, 0.f, 0.f, 0.f};
-      for (int s = 0; s < live; ++s) a += *reinterpret_cast<const floatx4*>(part_w + (long)s * nk + 4 * i);
-      *reinterpret_cast<floatx4*>(dW + 4 * i) = a;
+      floatx4 v = {0.f, 0.f, 0.f, 0.f};
+      for (int s = 0; s < live; ++s) v += *reinterpret_cast<const floatx4*>(a.part_w + (long)s * a.nk + 4 * i);
+      *reinterpret_cast<floatx4*>(a.dW + 4 * i) = v;
     } else {
       const long n = i - quads;
-      float a = 0.f;
-      for (int s = 0; s < live; ++s) a += part_b[(long)s * n_out + n];
-      dbias[n] = a;
+      float v = 0.f;
+      for (int s = 0; s < live; ++s) v += a.part_b[(long)s * a.n_out + n];
+      a.dbias[n] = v;
     }
   }
+}
+__global__ void __launch_bounds__(256) linear_bwd_weight_reduce_kernel(const WeightReduceArgs a) {
+  weight_reduce_block(a, blockIdx.x, gridDim.x);
+}
+__global__ void __launch_bounds__(256) linear_bwd_weight_reduce_group_kernel(const Members<WeightReduceArgs> m) {
+  const MemberBlock mb = member_of(m, blockIdx.x);
+  weight_reduce_block(m.a[mb.s], mb.block, mb.blocks);
 }
 
 __global__ void __launch_bounds__(256)
@@ -447,6 +499,63 @@ linear_bwd_weight_f32_kernel(const float* __restrict__ dout, const int32_t* __re
     }
     if (is_w) dW[i] = a; else dbias[n] = a;
   }
+}
+
+static int reserve_lds(const char* fn, const void* kernel, size_t bytes) {
+  const hipError_t attr = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  return attr == hipSuccess ? SPA_OK : fail(SPA_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, bytes);
+}
+static int launch_weight(const char* fn, const WeightArgs& a, unsigned grid, hipStream_t st) {
+  const bool gather = a.dout_idx != nullptr || a.x_idx != nullptr;
+  if (int rc = reserve_lds(fn, gather ? (const void*)weight_gemm_kernel<true> : (const void*)weight_gemm_kernel<false>, kLbGemmLds))
+    return rc;
+  if (gather) hipLaunchKernelGGL((weight_gemm_kernel<true>), dim3(grid), dim3(kLbThreads), kLbGemmLds, st, a);
+  else hipLaunchKernelGGL((weight_gemm_kernel<false>), dim3(grid), dim3(kLbThreads), kLbGemmLds, st, a);
+  return check_launch(fn);
+}
+
+static thread_local struct {
+  int n_rows, n_weight;
+  bool big;
+  GemmArgs rows;
+  WeightArgs w[2];
+  unsigned wgrid[2];
+  Noted<WeightReduceArgs> reduce;
+} g_noted;
+void group_forget_linear() { g_noted.n_rows = g_noted.n_weight = g_noted.reduce.n = 0; }
+int group_note_rows(const char* fn, const GemmArgs& args, bool big) {
+  SPA_REQUIRE(g_noted.n_rows == 0, SPA_ERR_UNSUPPORTED, "%s: one input side in a group", fn);
+  g_noted.rows = args;
+  g_noted.big = big;
+  g_noted.n_rows = 1;
+  return SPA_OK;
+}
+int group_flush_linear(hipStream_t st) {
+  auto& n = g_noted;
+  if (n.n_rows == 1 && n.n_weight > 0 && !n.big) {
+    LinearGroup g;
+    g.rows = n.rows;
+    g.rows.n_tiles = (n.rows.ncols + 127) / 128;
+    const long tiles = (long)((n.rows.m_cap + 127) / 128) * g.rows.n_tiles;
+    g.end[0] = (unsigned)((tiles + 7) / 8 * 8);
+    g.w[0] = n.w[0];
+    g.w[1] = n.w[n.n_weight - 1];
+    g.end[1] = g.end[0] + n.wgrid[0];
+    const unsigned blocks = g.end[1] + (n.n_weight == 2 ? n.wgrid[1] : 0);
+    if (int rc = reserve_lds("spa_group_end", (const void*)linear_bwd_group_kernel, kLbGemmLds)) return rc;
+    hipLaunchKernelGGL(linear_bwd_group_kernel, dim3(blocks), dim3(kLbThreads), kLbGemmLds, st, g);
+  } else {
+    if (n.n_rows == 1)
+      if (int rc = launch_gemm_rows("spa_group_end", n.rows, true, st)) return rc;
+    for (int i = 0; i < n.n_weight; ++i)
+      if (int rc = launch_weight("spa_group_end", n.w[i], n.wgrid[i], st)) return rc;
+  }
+  if (n.reduce.n > 0) {
+    Members<WeightReduceArgs> m;
+    const unsigned blocks = n.reduce.members(m);
+    hipLaunchKernelGGL(linear_bwd_weight_reduce_group_kernel, dim3(blocks), dim3(256), 0, st, m);
+  }
+  return check_launch("spa_group_end");
 }
 
 // Number of token chunks of the weight-side kernel: (chunk, tile) workgroups for two per compute unit (what
@@ -483,6 +592,7 @@ extern "C" int spa_linear_packed_bwd_input(const void* dout, const int32_t* dout
   SPA_REQUIRE(inv_pos == nullptr || (dx_idx != nullptr && rows >= 0), SPA_ERR_INVALID_ARG,
               "%s: inv_pos (zero fill of the rows no packed row maps to) needs dx_idx and rows >= 0", fn);
   hipStream_t st = as_stream(stream);
+  SPA_REQUIRE(!(group_open() && dtype == SPA_F32), SPA_ERR_UNSUPPORTED, "%s: fp32 calls cannot be part of a group", fn);
   if (dtype == SPA_F32) {
     long work = (long)M_cap * K;
     if (inv_pos != nullptr && rows * K > work) work = rows * K;
@@ -532,6 +642,7 @@ extern "C" int spa_linear_packed_bwd_weight(const void* dout, const int32_t* dou
   SPA_REQUIRE(!(gate_scores != nullptr && x_idx == nullptr), SPA_ERR_INVALID_ARG,
               "%s: gate_scores are indexed by token and need x_idx", fn);
   hipStream_t st = as_stream(stream);
+  SPA_REQUIRE(!(group_open() && dtype == SPA_F32), SPA_ERR_UNSUPPORTED, "%s: fp32 calls cannot be part of a group", fn);
   if (dtype == SPA_F32) {
     long wgs = ((long)N_out * K + N_out + 255) / 256;
     if (wgs > 8192) wgs = 8192;
@@ -555,6 +666,9 @@ extern "C" int spa_linear_packed_bwd_weight(const void* dout, const int32_t* dou
   const unsigned grid = (unsigned)(((items + 7) / 8) * 8);
   float* part_w = static_cast<float*>(workspace);
   float* part_b = part_w + (size_t)splits * N_out * K;
+  const WeightReduceArgs rargs = {part_w, part_b, total, M_cap, splits, (long)N_out * K, N_out, dW, dbias};
+  const unsigned rblocks = (unsigned)std::min<long>(((long)N_out * K / 4 + N_out + 255) / 256, 4096);
+  SPA_REQUIRE(!(group_open() && gate_scores != nullptr), SPA_ERR_UNSUPPORTED, "%s: gated rows cannot be part of a group", fn);
   if (gate_scores != nullptr) {
     const hipError_t attr = hipFuncSetAttribute((const void*)linear_bwd_weight_bf16_kernel,
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLbWeightLds);
@@ -566,25 +680,20 @@ extern "C" int spa_linear_packed_bwd_weight(const void* dout, const int32_t* dou
     // one chunk: the tiles are the result; more: partial tiles that the second kernel adds
     float* pw = splits == 1 ? dW : part_w;
     float* pb = splits == 1 ? dbias : part_b;
-    const bool gather = dout_idx != nullptr || x_idx != nullptr;
-    const void* kernel = gather ? (const void*)weight_gemm_kernel<true> : (const void*)weight_gemm_kernel<false>;
-    const hipError_t attr = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLbGemmLds);
-    SPA_REQUIRE(attr == hipSuccess, SPA_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, kLbGemmLds);
-#define SPA_WG(G_)                                                                                               \
-  hipLaunchKernelGGL((weight_gemm_kernel<G_>), dim3(grid), dim3(kLbThreads), kLbGemmLds, st, (const __bf16*)dout, \
-                     dout_idx, (long)dout_row_stride, (const __bf16*)x, x_idx, total, M_cap, K, N_out, splits, n_tiles, \
-                     k_tiles, pw, pb)
-    if (gather) SPA_WG(true); else SPA_WG(false);
-#undef SPA_WG
-    if (splits == 1) return check_launch(fn);
+    const WeightArgs wargs = {(const __bf16*)dout, dout_idx, (long)dout_row_stride, (const __bf16*)x, x_idx, total, M_cap, K,
+                              N_out, splits, n_tiles, k_tiles, pw, pb};
+    if (group_open()) {
+      SPA_REQUIRE(g_noted.n_weight < 2, SPA_ERR_UNSUPPORTED, "%s: two weight sides in a group", fn);
+      g_noted.w[g_noted.n_weight] = wargs;
+      g_noted.wgrid[g_noted.n_weight++] = grid;
+      return splits == 1 ? SPA_OK : g_noted.reduce.add(fn, rargs, rblocks);
+    }
+    if (int rc = launch_weight(fn, wargs, grid, st)) return rc;
+    if (splits == 1) return SPA_OK;
   }
   const int rc = check_launch(fn);
   if (rc != SPA_OK) return rc;
-  const long nk = (long)N_out * K;
-  long wgs = (nk / 4 + N_out + 255) / 256;
-  if (wgs > 4096) wgs = 4096;
-  hipLaunchKernelGGL(linear_bwd_weight_reduce_kernel, dim3((unsigned)wgs), dim3(256), 0, st, part_w, part_b, total, M_cap,
-                     splits, nk, N_out, dW, dbias);
+  hipLaunchKernelGGL(linear_bwd_weight_reduce_kernel, dim3(rblocks), dim3(256), 0, st, rargs);
   return check_launch(fn);
 }
 

@@ -366,15 +366,20 @@ class BlockTrainPass(_Pass):
     through the gate and the gated representation; the residual path adds dy itself to it, which
     is left to the caller (it is the upstream gradient, unchanged).
 
-    overlap_weight_grads (default): nothing downstream in the step reads dW / dbias, so the two
-    weight-side GEMMs are enqueued on a second HIP stream (default priority) and run beside the
-    attention backward, the input-side GEMM and the gate backward; events order them after
-    their inputs and the step's last stage joins the streams."""
+    overlap_weight_grads (default): nothing downstream in the step reads dW / dbias, so the two weight-side GEMMs run
+    beside other work.  In bf16 with B N C^2 <= 6e9 they share one launch with the input side of the QKV projection
+    (a launch group), and their partial sums one more: these GEMMs leave units idle there and every dependent launch
+    costs about 4 us.  Above that line each of them fills the chip, and they are enqueued on a second HIP stream
+    (default priority) beside the attention backward, the input-side GEMM and the gate backward; events order them
+    after their inputs and the step's last stage joins the streams.  Measured, us a step, one launch / second stream /
+    in order: 32 x 196 x 384 93 / 110 / 115, 128 x 196 x 384 178 / 184 / 200, 32 x 196 x 768 148 / 190 / 168 and
+    64 x 196 x 768 (7.4e9) 222 / 218 / 241, 128 x 196 x 768 421 / 401 / 422."""
 
     def __init__(self, B: int, N: int, C: int, H: int, dtype: str, tau: float = 0.5, bias: float = 0.0,
                  loss_scale: Optional[float] = None, overlap_weight_grads: bool = True):
-        self.overlap = overlap_weight_grads
-        self.side = torch.cuda.Stream() if overlap_weight_grads else None
+        self.grouped = overlap_weight_grads and dtype == "bf16" and B * N * C * C <= 6e9
+        self.overlap = overlap_weight_grads and not self.grouped
+        self.side = torch.cuda.Stream() if self.overlap else None
         self.B, self.N, self.C, self.H, self.Dh = B, N, C, H, C // H
         self.tau, self.bias = tau, bias
         self.loss_scale = 0.01 / (B * N) if loss_scale is None else loss_scale
@@ -430,7 +435,7 @@ class BlockTrainPass(_Pass):
             w_o, w_qkv = on_side(events[0], w_o), on_side(events[1], w_qkv)
         else:
             w_o, w_qkv = weight_side()
-        return [
+        forward = [
             ("gate_select", spa.spa_gate_select(x, w, self.bias, None, self.tau, self.scores, self.mask, None,
                                                 prepare=True)),
             ("pack_rg", spa.spa_pack(x, self.mask, None, self.scores, 0, self.packed_rg, self.cu_seqlens,
@@ -441,18 +446,21 @@ class BlockTrainPass(_Pass):
                 p[:, :C], p[:, C:2 * C], p[:, 2 * C:], self.cu_seqlens, B, N, H, Dh, self.attn, self.lse, prepare=True)),
             ("out_projection_unpack", spa.spa_linear_packed_unpack(self.attn, self.total, W_o, b_o, self.gather_idx,
                                                                    self.inv_pos, x, self.y, prepare=True)),
-            ("out_projection_bwd_weight", w_o),
-            ("out_projection_bwd_input", spa.spa_linear_packed_bwd_input(dy2, self.gather_idx, self.total, W_o, cap,
-                                                                         None, None, self.d_attn, prepare=True)),
-            ("packed_attention_bwd", spa.spa_packed_attention_bwd(
-                p[:, :C], p[:, C:2 * C], p[:, 2 * C:], self.attn, self.d_attn, self.lse, self.cu_seqlens, B, N, H, Dh,
-                dp[:, :C], dp[:, C:2 * C], dp[:, 2 * C:], self.ws_attn, prepare=True)),
-            ("qkv_projection_bwd_weight", w_qkv),
-            ("qkv_projection_bwd_input", spa.spa_linear_packed_bwd_input(dp, None, self.total, W_qkv, cap,
-                                                                         self.gather_idx, self.inv_pos,
-                                                                         self.d_rg.view(cap, C), prepare=True)),
-            ("gate_bwd", spa.spa_gate_bwd(x, w, self.bias, self.scores, None, labels, self.d_rg, True, self.loss_scale,
-                                          self.loss, self.dx, self.dw, self.db, self.ws_gate, prepare=True)),
+        ]
+        in_o = spa.spa_linear_packed_bwd_input(dy2, self.gather_idx, self.total, W_o, cap, None, None, self.d_attn, prepare=True)
+        attention_bwd = spa.spa_packed_attention_bwd(
+            p[:, :C], p[:, C:2 * C], p[:, 2 * C:], self.attn, self.d_attn, self.lse, self.cu_seqlens, B, N, H, Dh,
+            dp[:, :C], dp[:, C:2 * C], dp[:, 2 * C:], self.ws_attn, prepare=True)
+        in_qkv = spa.spa_linear_packed_bwd_input(dp, None, self.total, W_qkv, cap, self.gather_idx, self.inv_pos,
+                                                 self.d_rg.view(cap, C), prepare=True)
+        gate_bwd = ("gate_bwd", spa.spa_gate_bwd(x, w, self.bias, self.scores, None, labels, self.d_rg, True, self.loss_scale,
+                                                 self.loss, self.dx, self.dw, self.db, self.ws_gate, prepare=True))
+        if self.grouped:
+            return forward + [("out_projection_bwd_input", in_o), ("packed_attention_bwd", attention_bwd),
+                              ("projections_bwd", spa.group(in_qkv, w_o, w_qkv)), gate_bwd]
+        return forward + [
+            ("out_projection_bwd_weight", w_o), ("out_projection_bwd_input", in_o), ("packed_attention_bwd", attention_bwd),
+            ("qkv_projection_bwd_weight", w_qkv), ("qkv_projection_bwd_input", in_qkv), gate_bwd,
         ] + ([("join_streams", join)] if self.overlap else [])
 
     def run(self, x, w, W_qkv, b_qkv, W_o, b_o, labels, dy):

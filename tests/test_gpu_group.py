@@ -66,6 +66,39 @@ def test_grouped_equals_one_by_one(mods, monkeypatch, B, h, w, H, stages, form):
             assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("B,N,C,H,tm", [(1, 1, 64, 2, None), (1, 50, 384, 6, None), (3, 129, 192, 3, None), (32, 196, 384, 6, None),
+                                        (8, 400, 256, 8, "8"), (64, 196, 768, 12, None)])
+def test_block_backward_projections_in_one_launch(mods, B, N, C, H, tm):
+    """The weight sides beside other work (a launch group; two streams past its line) against everything in order: one
+    chunk of rows and several, no row at all, 256 x 256 tiles (gemm_tm = 8: a group of separate launches)."""
+    spa, pipeline = mods
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
+    x, w, dy = rnd(B, N, C), rnd(C) / C ** 0.5, rnd(B, N, C)
+    if B > 1 or N == 1:
+        x[0] = 0                                   # (nothing selected there)
+    W = [rnd(3 * C, C) / C ** 0.5, rnd(3 * C), rnd(C, C) / C ** 0.5, rnd(C)]
+    lab = (rnd(B, N) > 0).to(torch.uint8)
+    got = []
+    spa.spa_set_option("gemm_tm", tm)
+    try:
+        for beside in (True, False):
+            p = pipeline.BlockTrainPass(B, N, C, H, "bf16", bias=-0.5, overlap_weight_grads=beside)
+            assert not beside or p.grouped == (B * N * C * C <= 6e9)
+            for t in (p.dW_qkv, p.db_qkv, p.dW_o, p.db_o, p.d_rg):
+                t.fill_(float("nan"))
+            for _ in range(2):
+                p.run(x, w, *W, lab, dy)
+            torch.cuda.synchronize()
+            got.append(p)
+    finally:
+        spa.spa_set_option("gemm_tm")
+    assert (int(got[1].mask[0].sum()) == 0) == (B > 1 or N == 1)
+    for name in ("y", "d_rg", "dx", "dW_qkv", "db_qkv", "dW_o", "db_o", "dw", "db", "loss"):
+        assert torch.equal(getattr(got[0], name), getattr(got[1], name)), name
+
+
 def test_what_a_group_refuses(mods):
     spa, _ = mods
     x, w = torch.randn(1, 40, 64, device="cuda"), torch.randn(64, device="cuda")
