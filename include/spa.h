@@ -260,6 +260,15 @@ int spa_container_segments(const int32_t* cu_seqlens, int B, int container_len, 
                            int32_t* seg_cu_seqlens, int32_t* n_segments, void* stream);
 
 /*
+ * The packing index of the cyclically shifted map and its container segments in one launch (two for B > 1024): same
+ * cu_seqlens, gather_idx, inv_pos and total as spa_pack_shifted without rows, same segment list as
+ * spa_container_segments with max_total = B*N.
+ */
+int spa_pack_containers(const uint8_t* mask, int B, int grid_h, int grid_w, int shift_h, int shift_w, int container_len,
+                        int seg_cap, int32_t* cu_seqlens, int32_t* gather_idx, int32_t* inv_pos, int32_t* total,
+                        int32_t* seg_cu_seqlens, int32_t* n_segments, void* stream);
+
+/*
  * Multi-head self-attention on packed tokens in which a token attends only to tokens of
  * its own image (Section 3.2, last paragraph).  For every image b and head h, over packed
  * rows [cu_seqlens[b], cu_seqlens[b+1]):
@@ -381,6 +390,14 @@ int spa_segment_attention_unpack(const void* q, const void* k, const void* v, in
                                  const int32_t* gather_idx, const int32_t* inv_pos, const void* base,
                                  int64_t rows, int H, int Dh, int dtype, float softmax_scale, void* out,
                                  float* lse, void* y, void* stream);
+
+/* spa_segment_attention_unpack on q, k, v at TOKEN positions: packed row j is fetched from row gather_idx[j]. */
+int spa_gathered_segment_attention_unpack(const void* q, const void* k, const void* v, int64_t q_row_stride,
+                                          int64_t k_row_stride, int64_t v_row_stride,
+                                          const int32_t* seg_cu_seqlens, int n_segments, int max_seqlen,
+                                          const int32_t* gather_idx, const int32_t* inv_pos, const void* base,
+                                          int64_t rows, int H, int Dh, int dtype, float softmax_scale, void* out,
+                                          float* lse, void* y, void* stream);
 
 /*
  * Linear projection of packed tokens (the 3 L C^2 / N C^2 terms of the SPA complexity

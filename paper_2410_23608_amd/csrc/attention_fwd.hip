@@ -1450,3 +1450,18 @@ extern "C" int spa_segment_attention_unpack(const void* q, const void* k, const 
   return attention_common(fn, q, k, v, q_row_stride, k_row_stride, v_row_stride, seg_cu_seqlens, nullptr, n_segments,
                           max_seqlen, H, Dh, dtype, softmax_scale, out, lse, sc, stream);
 }
+
+extern "C" int spa_gathered_segment_attention_unpack(const void* q, const void* k, const void* v, int64_t q_row_stride,
+                                                     int64_t k_row_stride, int64_t v_row_stride,
+                                                     const int32_t* seg_cu_seqlens, int n_segments, int max_seqlen,
+                                                     const int32_t* gather_idx, const int32_t* inv_pos, const void* base,
+                                                     int64_t rows, int H, int Dh, int dtype, float softmax_scale, void* out,
+                                                     float* lse, void* y, void* stream) {
+  const char* fn = "spa_gathered_segment_attention_unpack";
+  SPA_REQUIRE(seg_cu_seqlens && gather_idx && inv_pos && y, SPA_ERR_INVALID_ARG, "%s: null pointer", fn);
+  SPA_REQUIRE(rows >= 1 && rows < 2147483647L, SPA_ERR_INVALID_ARG, "%s: rows must be in [1, 2^31)", fn);
+  SPA_REQUIRE(aligned16(y) && aligned16(base), SPA_ERR_INVALID_ARG, "%s: y / base not 16-byte aligned", fn);
+  const Scatter sc = {gather_idx, inv_pos, base, y, (int)rows, 1, 1, nullptr};
+  return attention_common(fn, q, k, v, q_row_stride, k_row_stride, v_row_stride, seg_cu_seqlens, nullptr, n_segments,
+                          max_seqlen, H, Dh, dtype, softmax_scale, out, lse, sc, stream);
+}

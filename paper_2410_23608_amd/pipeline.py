@@ -473,8 +473,10 @@ class ContainerForwardPass(_Pass):
     packed stream is cut into containers of length L and a token attends to the tokens of its
     own image inside its own container; shift = (sh, sw) packs the cyclically shifted map.
 
-      gate_select(x) -> pack_shifted(qkv) -> container_segments -> attention on the image x
-      container segments + scatter back (one launch; fused_unpack=False: two).  No host sync."""
+      gate_select(x) -> packing index and segment list -> attention on the image x container segments, which
+      fetches the rows through the index, + scatter back: three launches (64 x 196 x 384, L = 49: 18.1 us; with
+      packed rows and the list in a launch of its own 23.4; fused_unpack=False: pack_shifted(qkv) and
+      container_segments, attention and scatter as separate launches).  No host sync."""
 
     def __init__(self, B: int, grid_h: int, grid_w: int, C: int, H: int, dtype: str, container_len: int,
                  shift: Tuple[int, int] = (0, 0), tau: float = 0.5, bias: float = 0.0, fused_unpack: bool = True):
@@ -486,7 +488,7 @@ class ContainerForwardPass(_Pass):
         dv = dict(device="cuda")
         self.scores = torch.empty(B, N, dtype=torch.float32, **dv)
         self.mask = torch.empty(B, N, dtype=torch.uint8, **dv)
-        self.packed_qkv = torch.zeros(cap + container_len - 1, 3 * C, dtype=td, **dv)
+        self.packed_qkv = None if fused_unpack else torch.zeros(cap + container_len - 1, 3 * C, dtype=td, **dv)
         self.cu_seqlens = torch.zeros(B + 1, dtype=torch.int32, **dv)
         self.gather_idx = torch.zeros(cap, dtype=torch.int32, **dv)
         self.inv_pos = torch.zeros(cap, dtype=torch.int32, **dv)
@@ -500,24 +502,29 @@ class ContainerForwardPass(_Pass):
 
     def stages(self, x, w, qkv, base=None) -> List[Tuple[str, Callable[[], None]]]:
         C, p = self.C, self.packed_qkv
-        return [
-            ("gate_select", spa.spa_gate_select(x, w, self.bias, None, self.tau, self.scores, self.mask, None,
-                                                prepare=True)),
+        gate = [("gate_select", spa.spa_gate_select(x, w, self.bias, None, self.tau, self.scores, self.mask, None,
+                                                    prepare=True))]
+        if self.fused_unpack:
+            t = qkv.view(self.B * self.N, 3 * C)
+            return gate + [
+                ("pack_containers", spa.spa_pack_containers(self.mask, *self.grid, *self.shift, self.L, self.cu_seqlens,
+                                                            self.gather_idx, self.inv_pos, self.total,
+                                                            self.seg_cu_seqlens, self.n_segments, prepare=True)),
+                ("segment_attention_unpack", spa.spa_gathered_segment_attention_unpack(
+                    t[:, :C], t[:, C:2 * C], t[:, 2 * C:], self.seg_cu_seqlens, self.max_seqlen, self.gather_idx,
+                    self.inv_pos, base, self.H, self.Dh, self.y, prepare=True)),
+            ]
+        return gate + [
             ("pack_shifted", spa.spa_pack_shifted(qkv, self.mask, None, None, self.grid[0], self.grid[1],
                                                   self.shift[0], self.shift[1], self.L, p, self.cu_seqlens,
                                                   self.gather_idx, self.inv_pos, self.total, prepare=True)),
             ("container_segments", spa.spa_container_segments(self.cu_seqlens, self.L, self.B * self.N,
                                                               self.seg_cu_seqlens, self.n_segments, prepare=True)),
-        ] + ([
-            ("segment_attention_unpack", spa.spa_segment_attention_unpack(
-                p[:, :C], p[:, C:2 * C], p[:, 2 * C:], self.seg_cu_seqlens, self.max_seqlen, self.gather_idx,
-                self.inv_pos, base, self.H, self.Dh, self.y, None, None, prepare=True)),
-        ] if self.fused_unpack else [
             ("packed_attention", spa.spa_packed_attention(p[:, :C], p[:, C:2 * C], p[:, 2 * C:], self.seg_cu_seqlens,
                                                           self.seg_cap, self.max_seqlen, self.H, self.Dh, self.out,
                                                           None, prepare=True)),
             ("unpack", spa.spa_unpack(self.out, self.inv_pos, base, self.y, prepare=True)),
-        ])
+        ]
 
     def run(self, x, w, qkv, base=None):
         self._issue(self.stages, x, w, qkv, base)

@@ -56,6 +56,7 @@ _SIGNATURES = {
                                  _P, _P, _P]),
     "spa_container_segments_capacity": (c_int64, [c_int, c_int64, c_int]),
     "spa_container_segments": (c_int, [_P, c_int, c_int, c_int64, c_int, _P, _P, _P]),
+    "spa_pack_containers": (c_int, [_P, c_int, c_int, c_int, c_int, c_int, c_int, c_int, _P, _P, _P, _P, _P, _P, _P]),
     "spa_packed_attention": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, c_int, c_int, c_int, c_int, c_int, c_float, _P, _P, _P]),
     "spa_packed_attention_running_max": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, c_int, c_int, c_int, c_int, c_int,
                                                  c_float, _P, _P, _P]),
@@ -69,6 +70,8 @@ _SIGNATURES = {
                                               c_int, c_float, _P, _P]),
     "spa_segment_attention_unpack": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, c_int, c_int, _P, _P, _P, c_int64,
                                              c_int, c_int, c_int, c_float, _P, _P, _P, _P]),
+    "spa_gathered_segment_attention_unpack": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, c_int, c_int, _P, _P, _P,
+                                                      c_int64, c_int, c_int, c_int, c_float, _P, _P, _P, _P]),
     "spa_ceiling_copy": (c_int, [_P, _P, c_size_t, _P]),
     "spa_ceiling_mfma": (c_double, [_P, c_int, c_int, _P]),
     "spa_linear_packed": (c_int, [_P, _P, _P, _P, _P, _P, c_int, c_int, c_int, c_int, _P, c_int64, _P]),
@@ -448,6 +451,22 @@ def spa_container_segments(cu_seqlens, container_len, max_total, seg_cu_seqlens,
                       _ptr(seg_cu_seqlens), _ptr(n_segments), _stream(),), _keep, prepare)
 
 
+def spa_pack_containers(mask, grid_h, grid_w, shift_h, shift_w, container_len, cu_seqlens, gather_idx, inv_pos, total,
+                        seg_cu_seqlens, n_segments, prepare=False):
+    """spa_pack_shifted without rows and spa_container_segments in one launch."""
+    fn = "spa_pack_containers"
+    B, N, _, _ = _pack_checks(fn, None, mask, None, None, 0, None, cu_seqlens, gather_idx, inv_pos, total)
+    if N != grid_h * grid_w:
+        raise ValueError("mask.shape[1] != grid_h * grid_w")
+    _typed(fn, torch.int32, seg_cu_seqlens=seg_cu_seqlens, n_segments=n_segments)
+    _keep = (mask, cu_seqlens, gather_idx, inv_pos, total, seg_cu_seqlens, n_segments,)
+    _contig(*_keep)
+    return _dispatch(lib.spa_pack_containers,
+                     (_ptr(mask), B, int(grid_h), int(grid_w), int(shift_h), int(shift_w), int(container_len),
+                      seg_cu_seqlens.numel() - 1, _ptr(cu_seqlens), _ptr(gather_idx), _ptr(inv_pos), _ptr(total),
+                      _ptr(seg_cu_seqlens), _ptr(n_segments), _stream(),), _keep, prepare)
+
+
 def _row_stride(t) -> int:
     if t.dim() != 2 or t.stride(1) != 1:
         raise ValueError("expected a 2-D [rows, H*Dh] tensor or column-slice view with unit inner stride")
@@ -562,19 +581,34 @@ def spa_selected_attention_unpack(q, k, v, mask, base, H, Dh, y, softmax_scale=0
                       B, N, H, Dh, code, float(softmax_scale), _ptr(y), _stream(),), _keep, prepare)
 
 
+def _segment_attention_unpack(fn, gathered, q, k, v, seg_cu_seqlens, max_seqlen, gather_idx, inv_pos, base, H, Dh, y, out,
+                              lse, softmax_scale, prepare):
+    n_segments = seg_cu_seqlens.numel() - 1
+    rows, code = _scatter_checks(fn, q, k, v, seg_cu_seqlens, n_segments, max_seqlen, gather_idx, inv_pos, base, H, Dh, y,
+                                 out, lse)
+    if gathered:
+        _rows(fn, H * Dh, q=(q, rows), k=(k, rows), v=(v, rows))
+    _keep = (q, k, v, seg_cu_seqlens, gather_idx, inv_pos, base, y, out, lse,)
+    _contig(seg_cu_seqlens, gather_idx, inv_pos, base, y, out, lse)
+    return _dispatch(getattr(lib, fn),
+                     (_ptr(q), _ptr(k), _ptr(v), _row_stride(q), _row_stride(k), _row_stride(v), _ptr(seg_cu_seqlens),
+                      n_segments, int(max_seqlen), _ptr(gather_idx), _ptr(inv_pos), _ptr(base), rows, H, Dh,
+                      code, float(softmax_scale), _ptr(out), _ptr(lse), _ptr(y), _stream(),), _keep, prepare)
+
+
 def spa_segment_attention_unpack(q, k, v, seg_cu_seqlens, max_seqlen, gather_idx, inv_pos, base, H, Dh, y, out=None,
                                  lse=None, softmax_scale=0.0, prepare=False):
     """Attention inside the segments of seg_cu_seqlens (not necessarily whole images) + scatter
     back to y [B,N,C] in one launch."""
-    n_segments = seg_cu_seqlens.numel() - 1
-    rows, code = _scatter_checks("spa_segment_attention_unpack", q, k, v, seg_cu_seqlens, n_segments, max_seqlen,
-                                 gather_idx, inv_pos, base, H, Dh, y, out, lse)
-    _keep = (q, k, v, seg_cu_seqlens, gather_idx, inv_pos, base, y, out, lse,)
-    _contig(seg_cu_seqlens, gather_idx, inv_pos, base, y, out, lse)
-    return _dispatch(lib.spa_segment_attention_unpack,
-                     (_ptr(q), _ptr(k), _ptr(v), _row_stride(q), _row_stride(k), _row_stride(v), _ptr(seg_cu_seqlens),
-                      n_segments, int(max_seqlen), _ptr(gather_idx), _ptr(inv_pos), _ptr(base), rows, H, Dh,
-                      code, float(softmax_scale), _ptr(out), _ptr(lse), _ptr(y), _stream(),), _keep, prepare)
+    return _segment_attention_unpack("spa_segment_attention_unpack", False, q, k, v, seg_cu_seqlens, max_seqlen, gather_idx,
+                                     inv_pos, base, H, Dh, y, out, lse, softmax_scale, prepare)
+
+
+def spa_gathered_segment_attention_unpack(q, k, v, seg_cu_seqlens, max_seqlen, gather_idx, inv_pos, base, H, Dh, y,
+                                          out=None, lse=None, softmax_scale=0.0, prepare=False):
+    """spa_segment_attention_unpack on un-packed q, k, v [B*N, H*Dh] at token positions."""
+    return _segment_attention_unpack("spa_gathered_segment_attention_unpack", True, q, k, v, seg_cu_seqlens, max_seqlen,
+                                     gather_idx, inv_pos, base, H, Dh, y, out, lse, softmax_scale, prepare)
 
 
 def spa_linear_packed(x, gather_idx, gate_scores, total, W, bias, out, prepare=False):

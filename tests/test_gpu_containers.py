@@ -245,3 +245,33 @@ def test_segment_attention_unpack_equals_two_calls(spa, dtype, B, gh, gw, C, H, 
     spa.spa_segment_attention_unpack(q, k, v, seg, n_max, g_d, inv_d, base, H, Dh, y3)      # y only
     torch.cuda.synchronize()
     assert torch.equal(y3, y2)
+
+
+@pytest.mark.parametrize("B,gh,gw,L,shift", [(1, 1, 1, 1, (0, 0)), (3, 5, 7, 4, (1, 2)), (64, 14, 14, 49, (3, 3)), (2, 64, 63, 25, (0, 1)),
+                                             (70, 16, 33, 64, (5, 0)), (1024, 1, 3, 2, (0, 0)), (1025, 2, 2, 3, (1, 1)),
+                                             (5, 40, 20, 800, (2, 2))])
+def test_index_and_segments_in_one_launch(spa, B, gh, gw, L, shift):
+    """spa_pack_containers against its two steps, then attention on rows fetched through the index against the packed
+    rows: images without a token and full ones, more images than one launch takes, containers past 256 tokens."""
+    from paper_2410_23608_amd import pipeline
+    N, C, H = gh * gw, 64, 2
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B + N)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
+    x, w, qkv, base = rnd(B, N, C), rnd(C) / 8, rnd(B, N, 3 * C), rnd(B, N, C)
+    if B > 2:
+        x[1] = 0                                          # score 1/2: nothing selected
+        x[B - 1] = w.sign()                               # everything
+    got = []
+    for fused in (True, False):
+        p = pipeline.ContainerForwardPass(B, gh, gw, C, H, "bf16", L, shift, fused_unpack=fused)
+        for t in (p.cu_seqlens, p.seg_cu_seqlens, p.inv_pos, p.n_segments, p.total):
+            t.fill_(-7)
+        p.run(x, w, qkv, base)
+        torch.cuda.synchronize()
+        got.append(p)
+    a, b = got
+    T = int(b.total)
+    for name in ("mask", "cu_seqlens", "inv_pos", "total", "seg_cu_seqlens", "n_segments", "y"):
+        assert torch.equal(getattr(a, name), getattr(b, name)), name
+    assert torch.equal(a.gather_idx[:T], b.gather_idx[:T])
