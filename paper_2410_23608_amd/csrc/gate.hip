@@ -652,9 +652,10 @@ __global__ void __launch_bounds__(kGateThreads) gate_bwd_group_kernel(const Memb
   else gate_bwd_block<__bf16, 64, 2, 4>(a, mb.block, mb.blocks, lds);
 }
 
-// Adds the partial rows in a fixed order: a block owns 16 columns; 64 row slices run in parallel
-// (slice s adds rows s, s+64, ..., at most 8 of them, whose loads are all in flight at once), then the
-// slices of a wave are added by exchanges and the waves in order.
+// Adds the partial rows in a fixed order: a block owns 16 columns; SL row slices run in parallel
+// (slice s adds rows s, s+SL, ..., at most 8 of them, whose loads are all in flight at once), then the
+// slices of a wave are added by exchanges and the waves in order.  64 slices, or 16 where these reach all rows
+// (at most 128): sixteen waves a workgroup start later than four, 0.6 us of the 7.6 of both launches at 50 tokens of 64.
 constexpr int kGateBwdMaxParts = 512;
 struct GateReduceArgs {
   const float* partial;
@@ -662,21 +663,24 @@ struct GateReduceArgs {
   float loss_scale;
   float *loss, *dw, *db;
 };
+template <int SL>
 __device__ __forceinline__ void gate_bwd_reduce_block(const GateReduceArgs& g, int block) {
+  constexpr int kRows = 8, kWaves = SL / 4;
+  static_assert(kGateBwdMaxParts <= 64 * kRows, "64 slices reach every row");
   const float* partial = g.partial;
   const int nparts = g.nparts, C = g.C;
-  __shared__ float red[16][17];
+  __shared__ float red[kWaves][17];
   const int cl = threadIdx.x & 15, sl = threadIdx.x >> 4;
   const int c = block * 16 + cl;
-  float v[kGateBwdMaxParts / 64];
+  float v[kRows];
 #pragma unroll
-  for (int i = 0; i < kGateBwdMaxParts / 64; ++i) {
-    const int r = sl + 64 * i;
+  for (int i = 0; i < kRows; ++i) {
+    const int r = sl + SL * i;
     v[i] = r < nparts && c < C + 2 ? partial[(long)r * (C + 2) + c] : 0.f;
   }
   float a = 0.f;
 #pragma unroll
-  for (int i = 0; i < kGateBwdMaxParts / 64; ++i) a += v[i];
+  for (int i = 0; i < kRows; ++i) a += v[i];
   a += __shfl_xor(a, 16, kWave);
   a += __shfl_xor(a, 32, kWave);
   if ((threadIdx.x & 63) < 16) red[threadIdx.x >> 6][cl] = a;
@@ -684,18 +688,19 @@ __device__ __forceinline__ void gate_bwd_reduce_block(const GateReduceArgs& g, i
   if (threadIdx.x < 16 && c < C + 2) {
     float t = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) t += red[i][cl];
+    for (int i = 0; i < kWaves; ++i) t += red[i][cl];
     if (c < C) g.dw[c] = t;
     else if (c == C) g.loss[0] = t * g.loss_scale;
     else g.db[0] = t;
   }
 }
-__global__ void __launch_bounds__(1024) gate_bwd_reduce_kernel(const GateReduceArgs g) {
-  gate_bwd_reduce_block(g, blockIdx.x);
+template <int SL>
+__global__ void __launch_bounds__(16 * SL) gate_bwd_reduce_kernel(const GateReduceArgs g) {
+  gate_bwd_reduce_block<SL>(g, blockIdx.x);
 }
 __global__ void __launch_bounds__(1024) gate_bwd_reduce_group_kernel(const Members<GateReduceArgs> m) {
   const MemberBlock mb = member_of(m, blockIdx.x);
-  gate_bwd_reduce_block(m.a[mb.s], mb.block);
+  gate_bwd_reduce_block<64>(m.a[mb.s], mb.block);
 }
 
 static thread_local Noted<GateBwdArgs<__bf16>> g_noted_bwd;
@@ -902,7 +907,11 @@ static int launch_gate_bwd(const void* x, const void* w, float bias, const float
   }
   SPA_REQUIRE(!group_open(), SPA_ERR_UNSUPPORTED, "spa_gate_bwd: fp32 calls cannot be part of a group");
 #define SPA_GB(G, IT, U) hipLaunchKernelGGL((gate_bwd_kernel<T, G, IT, U>), dim3(parts), dim3(kGateThreads), lds, st, args)
-  if (chunks <= 16) SPA_GB(16, 1, 4);
+  // (up to 512 shares a share is 16 tokens, one per group of 16 lanes, two per group of 32: no more taken at a time)
+  const bool few = ntok <= 16L * kGateBwdMaxParts;
+  if (chunks <= 16 && few) SPA_GB(16, 1, 1);
+  else if (chunks <= 16) SPA_GB(16, 1, 4);
+  else if (chunks <= 32 && few) SPA_GB(32, 1, 2);
   else if (chunks <= 32) SPA_GB(32, 1, 4);
   else if (chunks <= 64) SPA_GB(64, 1, 4);
   else if (chunks <= 128) SPA_GB(64, 2, 4);
@@ -910,7 +919,8 @@ static int launch_gate_bwd(const void* x, const void* w, float bias, const float
   else if (chunks <= 512) SPA_GB(64, 8, 1);
   else return fail(SPA_ERR_UNSUPPORTED, "spa_gate_bwd: C = %d too large (at most %d)", C, 512 * VE);
 #undef SPA_GB
-  hipLaunchKernelGGL(gate_bwd_reduce_kernel, dim3(rblocks), dim3(1024), 0, st, rargs);
+  if (parts <= 128) hipLaunchKernelGGL(gate_bwd_reduce_kernel<16>, dim3(rblocks), dim3(256), 0, st, rargs);
+  else hipLaunchKernelGGL(gate_bwd_reduce_kernel<64>, dim3(rblocks), dim3(1024), 0, st, rargs);
   return check_launch("spa_gate_bwd");
 }
 

@@ -87,3 +87,30 @@ def test_running_max_form_equals_the_default_form(Dh, N, shift):
     (o0, l0), (o1, l1) = got
     assert torch.isfinite(o1).all() and (o0 - o1).abs().max() <= 2e-2
     assert (l0 - l1).abs().max() <= 1e-4 * max(1.0, float(l0.abs().max()))
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("ntok,C", [(1, 64), (17, 128), (2047, 64), (2048, 256), (2049, 128), (8191, 96), (8192, 136), (8193, 128),
+                                    (8193, 256)])
+def test_gate_backward_at_its_shares(dtype, ntok, C):
+    """The forms of the gate backward: 128 and 512 partial rows, shares of 16 tokens and longer ones, a last short share."""
+    from paper_2410_23608_amd import spa
+    g = torch.Generator(device="cuda")
+    g.manual_seed(ntok + C)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    x, w, d = rnd(1, ntok, C).to(dtype), (rnd(C) / C ** 0.5).to(dtype), rnd(1, ntok, C).to(dtype)
+    scores, lab = rnd(1, ntok), (rnd(1, ntok) > 0).to(torch.uint8)
+    ws = torch.empty(spa.spa_gate_bwd_workspace_bytes(1, ntok, C, spa.dtype_code(x)), dtype=torch.uint8, device="cuda")
+    f = lambda n: torch.full((n,), float("nan"), device="cuda")
+    loss, dw, db, dx = f(1), f(C), f(1), torch.full_like(x, float("nan"))
+    spa.spa_gate_bwd(x, w, 0.0, scores, None, lab, d, True, 0.25, loss, dx, dw, db, ws)
+    torch.cuda.synchronize()
+    xf, df, s, y = x[0].double(), d[0].double(), scores[0].double(), lab[0].double()
+    p = torch.sigmoid(s)
+    ds = 0.25 * (p - y) + p * (1 - p) * (df * xf).sum(1)
+    rel = lambda a, b: float((a.double() - b).norm() / b.norm())
+    assert rel(dx[0], ds[:, None] * w.double() + p[:, None] * df) <= (1e-5 if dtype == torch.float32 else 1e-2)
+    assert rel(dw, (ds[:, None] * xf).sum(0)) <= 1e-4
+    assert abs(float(db) - float(ds.sum())) <= 1e-4 * float(ds.abs().sum())
+    ref = 0.25 * float((torch.nn.functional.softplus(s) - y * s).sum())
+    assert abs(float(loss) - ref) <= 1e-4 * ref
