@@ -533,6 +533,19 @@ int spa_packed_attention_bwd(const void* q, const void* k, const void* v, int64_
                              void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * spa_packed_attention_bwd that may also take the long-segment kernel for short segments (max_seqlen <= 256, bf16)
+ * whose few (image, head) pairs would leave the chip idle; the same gradients but for rounding.
+ */
+int spa_packed_attention_bwd_spread(const void* q, const void* k, const void* v, int64_t q_row_stride,
+                                    int64_t k_row_stride, int64_t v_row_stride,
+                                    const void* out, const void* dout, const float* lse,
+                                    const int32_t* cu_seqlens, int B, int max_seqlen, int H, int Dh,
+                                    int dtype, float softmax_scale,
+                                    void* dq, void* dk, void* dv, int64_t dq_row_stride,
+                                    int64_t dk_row_stride, int64_t dv_row_stride,
+                                    void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * spa_unpack_bwd, spa_packed_attention_bwd and spa_pack_bwd (of dq, dk and dv) in one launch:
  * the upstream gradient is read at the token positions and the gradients are written at the
  * token positions (the transposes of the scatter and gather of Section 3.2 folded into the
@@ -566,6 +579,15 @@ int spa_gated_attention_bwd_tokens(const void* q, const void* k, const void* x, 
                                    const int32_t* gather_idx, const int32_t* inv_pos, int64_t rows, void* dq,
                                    void* dk, void* d_rg, int64_t dq_row_stride, int64_t dk_row_stride,
                                    int64_t d_rg_row_stride, void* workspace, size_t workspace_bytes, void* stream);
+
+/* The same for spa_gated_attention_bwd_tokens, when it is given the workspace. */
+int spa_gated_attention_bwd_tokens_spread(const void* q, const void* k, const void* x, int64_t q_row_stride,
+                                          int64_t k_row_stride, int64_t x_row_stride, const float* scores,
+                                          const void* out, const void* dy, const float* lse, const int32_t* cu_seqlens,
+                                          int B, int max_seqlen, int H, int Dh, int dtype, float softmax_scale,
+                                          const int32_t* gather_idx, const int32_t* inv_pos, int64_t rows, void* dq,
+                                          void* dk, void* d_rg, int64_t dq_row_stride, int64_t dk_row_stride,
+                                          int64_t d_rg_row_stride, void* workspace, size_t workspace_bytes, void* stream);
 
 /* Bytes of workspace spa_gate_bwd needs. Host. */
 size_t spa_gate_bwd_workspace_bytes(int B, int N, int C, int dtype);

@@ -869,14 +869,25 @@ extern "C" size_t spa_attention_bwd_workspace_bytes(int B, int max_seqlen, int H
   return (size_t)H * (size_t)B * (size_t)max_seqlen * sizeof(float);   // D_i for every (head, row)
 }
 
-// tok.gather_idx != nullptr: gradients in and out at token positions (one-kernel form only).
+// Short segments whose (image, head) pairs, one workgroup each in the one-kernel form, leave most of the 256 units
+// idle take the long-segment form, whose roles and 128-row blocks are workgroups of their own.  It costs a launch more
+// (D), which the smallest segments and batches do not earn back: us of the training step, one kernel -> long form,
+// 196 tokens, head dim 64: 12 pairs +0.9, 24 -4.4, 96 -3.7, 252 -3.2, 384 +0.1; 49 tokens: 24 +0.4, 252 -1.0; head dim
+// 32, 196 tokens: 24 +0.7, 48 -0.6, 192 -2.0, 252 -0.6, 384 +2.4; 144 tokens: no gain.
+static bool few_pairs(int B, int H, int Dh, int n_max) {
+  const long pairs = (long)B * H;
+  return B > 1 && B <= kWave && (Dh == 64 ? n_max > 64 && pairs >= 16 && pairs <= 288 : n_max > 160 && pairs >= 32 && pairs <= 256);
+}
+
+// tok.gather_idx != nullptr: gradients in and out at token positions.  spread: few_pairs decides, where the caller
+// gave the workspace.
 static int attention_bwd_common(const char* fn, const void* q, const void* k, const void* v, int64_t q_row_stride,
                                 int64_t k_row_stride, int64_t v_row_stride, const void* out, const void* dout,
                                 const float* lse, const int32_t* cu_seqlens, int B, int max_seqlen, int H, int Dh,
                                 int dtype, float softmax_scale, void* dq, void* dk, void* dv,
                                 int64_t dq_row_stride, int64_t dk_row_stride, int64_t dv_row_stride,
                                 void* workspace, size_t workspace_bytes, TokenIO tok, void* stream,
-                                const float* v_scores = nullptr) {
+                                bool spread, const float* v_scores = nullptr) {
   const bool at_tokens = tok.gather_idx != nullptr;
   SPA_REQUIRE(q && k && v && out && dout && lse && cu_seqlens && dq && dk && dv, SPA_ERR_INVALID_ARG,
               "%s: null pointer", fn);
@@ -895,10 +906,13 @@ static int attention_bwd_common(const char* fn, const void* q, const void* k, co
               SPA_ERR_INVALID_ARG, "%s: tensors not 16-byte aligned", fn);
   SPA_REQUIRE(softmax_scale >= 0.f && std::isfinite(softmax_scale), SPA_ERR_INVALID_ARG,
               "%s: softmax_scale must be finite and >= 0", fn);
-  // short segments: the one-kernel form (option attn_bwd_short = "tiled" takes the long-segment kernel)
-  const bool short_seg = max_seqlen <= 256 && !options().bwd_tiled && !group_open();
+  // short segments: the one-kernel form, which needs no workspace (option attn_bwd_short = "tiled" takes the
+  // long-segment kernel)
+  const size_t dvec_bytes = spa_attention_bwd_workspace_bytes(B, max_seqlen, H, Dh, dtype);
+  const bool short_seg = max_seqlen <= 256 && !options().bwd_tiled && !group_open() &&
+                         !(spread && few_pairs(B, H, Dh, max_seqlen) && workspace != nullptr && workspace_bytes >= dvec_bytes);
   const bool one_kernel = dtype == SPA_BF16 && short_seg;
-  const size_t need = one_kernel ? 0 : spa_attention_bwd_workspace_bytes(B, max_seqlen, H, Dh, dtype);
+  const size_t need = one_kernel ? 0 : dvec_bytes;
   SPA_REQUIRE(need == 0 || (workspace != nullptr && workspace_bytes >= need), SPA_ERR_WORKSPACE,
               "%s: workspace of %zu bytes needed, %zu given", fn, need, workspace_bytes);
   const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / std::sqrt((float)Dh);
@@ -979,7 +993,20 @@ extern "C" int spa_packed_attention_bwd(const void* q, const void* k, const void
   return attention_bwd_common("spa_packed_attention_bwd", q, k, v, q_row_stride, k_row_stride, v_row_stride, out,
                               dout, lse, cu_seqlens, B, max_seqlen, H, Dh, dtype, softmax_scale, dq, dk, dv,
                               dq_row_stride, dk_row_stride, dv_row_stride, workspace, workspace_bytes,
-                              TokenIO{nullptr, nullptr, 0}, stream);
+                              TokenIO{nullptr, nullptr, 0}, stream, false);
+}
+
+extern "C" int spa_packed_attention_bwd_spread(const void* q, const void* k, const void* v, int64_t q_row_stride,
+                                               int64_t k_row_stride, int64_t v_row_stride, const void* out,
+                                               const void* dout, const float* lse, const int32_t* cu_seqlens, int B,
+                                               int max_seqlen, int H, int Dh, int dtype, float softmax_scale,
+                                               void* dq, void* dk, void* dv, int64_t dq_row_stride,
+                                               int64_t dk_row_stride, int64_t dv_row_stride, void* workspace,
+                                               size_t workspace_bytes, void* stream) {
+  return attention_bwd_common("spa_packed_attention_bwd_spread", q, k, v, q_row_stride, k_row_stride, v_row_stride, out,
+                              dout, lse, cu_seqlens, B, max_seqlen, H, Dh, dtype, softmax_scale, dq, dk, dv,
+                              dq_row_stride, dk_row_stride, dv_row_stride, workspace, workspace_bytes,
+                              TokenIO{nullptr, nullptr, 0}, stream, true);
 }
 
 extern "C" int spa_packed_attention_bwd_tokens(const void* q, const void* k, const void* v, int64_t q_row_stride,
@@ -996,7 +1023,7 @@ extern "C" int spa_packed_attention_bwd_tokens(const void* q, const void* k, con
   return attention_bwd_common(fn, q, k, v, q_row_stride, k_row_stride, v_row_stride, out, dy, lse, cu_seqlens, B,
                               max_seqlen, H, Dh, dtype, softmax_scale, dq, dk, dv, dq_row_stride, dk_row_stride,
                               dv_row_stride, workspace, workspace_bytes, TokenIO{gather_idx, inv_pos, (long)rows},
-                              stream);
+                              stream, false);
 }
 
 extern "C" int spa_gated_attention_bwd_tokens(const void* q, const void* k, const void* x, int64_t q_row_stride,
@@ -1013,5 +1040,22 @@ extern "C" int spa_gated_attention_bwd_tokens(const void* q, const void* k, cons
   return attention_bwd_common(fn, q, k, x, q_row_stride, k_row_stride, x_row_stride, out, dy, lse, cu_seqlens, B,
                               max_seqlen, H, Dh, dtype, softmax_scale, dq, dk, d_rg, dq_row_stride, dk_row_stride,
                               d_rg_row_stride, workspace, workspace_bytes, TokenIO{gather_idx, inv_pos, (long)rows},
-                              stream, scores);
+                              stream, false, scores);
+}
+
+extern "C" int spa_gated_attention_bwd_tokens_spread(const void* q, const void* k, const void* x, int64_t q_row_stride,
+                                                     int64_t k_row_stride, int64_t x_row_stride, const float* scores,
+                                                     const void* out, const void* dy, const float* lse, const int32_t* cu_seqlens,
+                                                     int B, int max_seqlen, int H, int Dh, int dtype, float softmax_scale,
+                                                     const int32_t* gather_idx, const int32_t* inv_pos, int64_t rows, void* dq,
+                                                     void* dk, void* d_rg, int64_t dq_row_stride, int64_t dk_row_stride,
+                                                     int64_t d_rg_row_stride, void* workspace, size_t workspace_bytes, void* stream) {
+  const char* fn = "spa_gated_attention_bwd_tokens_spread";
+  SPA_REQUIRE(scores && gather_idx && inv_pos, SPA_ERR_INVALID_ARG, "%s: null pointer", fn);
+  SPA_REQUIRE(rows >= 1 && rows < 2147483647L, SPA_ERR_INVALID_ARG, "%s: rows must be in [1, 2^31)", fn);
+  SPA_REQUIRE(dtype == SPA_BF16, SPA_ERR_UNSUPPORTED, "%s: bf16 only (use spa_pack_pair + spa_packed_attention_bwd_tokens)", fn);
+  return attention_bwd_common(fn, q, k, x, q_row_stride, k_row_stride, x_row_stride, out, dy, lse, cu_seqlens, B,
+                              max_seqlen, H, Dh, dtype, softmax_scale, dq, dk, d_rg, dq_row_stride, dk_row_stride,
+                              d_rg_row_stride, workspace, workspace_bytes, TokenIO{gather_idx, inv_pos, (long)rows},
+                              stream, true, scores);
 }

@@ -169,16 +169,19 @@ class TrainPass(_Pass):
     fused_bwd (default): the gather of dy and the scatters of dq, dk, dv run inside the
     attention backward, 6 calls instead of 9.
     pack_pair (default): q|k and the gated x are packed by one launch (the survivors are counted
-    and ranked once), 5 calls; in bf16 with fused_bwd no row is packed at all: packing builds the index and
-    the attention kernels fetch the rows through it and gate v on the way (same results, bit for bit).
+    and ranked once), 5 calls; in bf16 with fused_bwd and up to 2048 tokens per image no row is packed at all:
+    packing builds the index and the attention kernels fetch the rows through it and gate v on the way (same results).
+    Every tile of a segment's keys is fetched once per 128 queries, so beyond that packing costs less (pack_rows decides otherwise):
+    us a step, index only / packed, 43 x 1160 tokens of 448 248 / 266, 24 x 2112 of 192 160 / 156, 8 x 4131 of 256 196 / 189.
     """
 
     def __init__(self, B: int, N: int, C: int, H: int, dtype: str, tau: float = 0.5, bias: float = 0.0,
-                 loss_scale: Optional[float] = None, fused_bwd: Optional[bool] = None, pack_pair: bool = True):
+                 loss_scale: Optional[float] = None, fused_bwd: Optional[bool] = None, pack_pair: bool = True,
+                 pack_rows: Optional[bool] = None):
         self.B, self.N, self.C, self.H, self.Dh = B, N, C, H, C // H
         self.fused_bwd = True if fused_bwd is None else fused_bwd
         self.pack_pair = pack_pair
-        self.gated = dtype == "bf16" and pack_pair and self.fused_bwd
+        self.gated = dtype == "bf16" and pack_pair and self.fused_bwd and not (N > 2048 if pack_rows is None else pack_rows)
         self.tau, self.bias = tau, bias
         self.loss_scale = 0.01 / (B * N) if loss_scale is None else loss_scale
         td, cap = _td(dtype), B * N
@@ -252,7 +255,7 @@ class TrainPass(_Pass):
                 ("gated_attention_bwd_tokens", spa.spa_gated_attention_bwd_tokens(
                     t[:, :C], t[:, C:], xt, self.scores, self.out, dy, self.lse, self.cu_seqlens, B, N, H, Dh,
                     self.gather_idx, self.inv_pos, dqk_tok[:, :C], dqk_tok[:, C:], self.d_rg.view(B * N, C), self.ws_attn,
-                    prepare=True)),
+                    prepare=True, spread=True)),
                 ("gate_bwd", spa.spa_gate_bwd(x, w, self.bias, self.scores, None, labels, self.d_rg, True,
                                               self.loss_scale, self.loss, self.dx, self.dw, self.db, self.ws_gate,
                                               prepare=True)),
@@ -450,7 +453,7 @@ class BlockTrainPass(_Pass):
         in_o = spa.spa_linear_packed_bwd_input(dy2, self.gather_idx, self.total, W_o, cap, None, None, self.d_attn, prepare=True)
         attention_bwd = spa.spa_packed_attention_bwd(
             p[:, :C], p[:, C:2 * C], p[:, 2 * C:], self.attn, self.d_attn, self.lse, self.cu_seqlens, B, N, H, Dh,
-            dp[:, :C], dp[:, C:2 * C], dp[:, 2 * C:], self.ws_attn, prepare=True)
+            dp[:, :C], dp[:, C:2 * C], dp[:, 2 * C:], self.ws_attn, prepare=True, spread=True)
         in_qkv = spa.spa_linear_packed_bwd_input(dp, None, self.total, W_qkv, cap, self.gather_idx, self.inv_pos,
                                                  self.d_rg.view(cap, C), prepare=True)
         gate_bwd = ("gate_bwd", spa.spa_gate_bwd(x, w, self.bias, self.scores, None, labels, self.d_rg, True, self.loss_scale,
@@ -635,7 +638,10 @@ class HierarchyTrainPass(_Pass):
         self.streams = [torch.cuda.Stream() for _ in stages] if concurrent else None
         self.stream_of = list(range(len(stages)))
         self.cfg = list(stages)
-        self.passes = [TrainPass(B, gh * gw, C, H, dtype, tau, bias) for (B, gh, gw, C, H, dtype, tau, bias) in self.cfg]
+        # in a launch group every stage takes its rows through the index
+        rows = False if not concurrent and _groupable(self.cfg) else None
+        self.passes = [TrainPass(B, gh * gw, C, H, dtype, tau, bias, pack_rows=rows)
+                       for (B, gh, gw, C, H, dtype, tau, bias) in self.cfg]
 
     def stages(self, xs, ws, qks, labels, dys) -> List[Tuple[str, Callable[[], None]]]:
         chains = []

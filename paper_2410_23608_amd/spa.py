@@ -89,12 +89,18 @@ _SIGNATURES = {
     "spa_packed_attention_bwd": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, _P, _P, _P, c_int, c_int, c_int,
                                          c_int, c_int, c_float, _P, _P, _P, c_int64, c_int64, c_int64, _P,
                                          c_size_t, _P]),
+    "spa_packed_attention_bwd_spread": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, _P, _P, _P, c_int, c_int, c_int,
+                                                c_int, c_int, c_float, _P, _P, _P, c_int64, c_int64, c_int64, _P,
+                                                c_size_t, _P]),
     "spa_packed_attention_bwd_tokens": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, _P, _P, _P, c_int, c_int,
                                                 c_int, c_int, c_int, c_float, _P, _P, c_int64, _P, _P, _P, c_int64,
                                                 c_int64, c_int64, _P, c_size_t, _P]),
     "spa_gated_attention_bwd_tokens": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, _P, _P, _P, _P, c_int, c_int,
                                                c_int, c_int, c_int, c_float, _P, _P, c_int64, _P, _P, _P, c_int64,
                                                c_int64, c_int64, _P, c_size_t, _P]),
+    "spa_gated_attention_bwd_tokens_spread": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, _P, _P, _P, _P, c_int, c_int,
+                                                      c_int, c_int, c_int, c_float, _P, _P, c_int64, _P, _P, _P, c_int64,
+                                                      c_int64, c_int64, _P, c_size_t, _P]),
     "spa_gate_bwd_workspace_bytes": (c_size_t, [c_int, c_int, c_int, c_int]),
     "spa_gate_bwd": (c_int, [_P, _P, c_float, _P, _P, _P, _P, c_int, c_float, c_int, c_int, c_int, c_int,
                              _P, _P, _P, _P, _P, c_size_t, _P]),
@@ -773,8 +779,10 @@ def spa_attention_bwd_workspace_bytes(B, max_seqlen, H, Dh, dtype) -> int:
 
 
 def spa_packed_attention_bwd(q, k, v, out, dout, lse, cu_seqlens, B, max_seqlen, H, Dh,
-                             dq, dk, dv, workspace, softmax_scale=0.0, prepare=False):
-    fn = "spa_packed_attention_bwd"
+                             dq, dk, dv, workspace, softmax_scale=0.0, prepare=False, spread=False):
+    """spread: may take the long-segment kernel where few (image, head) pairs idle the chip
+    (spa_packed_attention_bwd_spread)."""
+    fn = "spa_packed_attention_bwd_spread" if spread else "spa_packed_attention_bwd"
     C = H * Dh
     code = _features(fn, q=q, k=k, v=v, out=out, dout=dout, dq=dq, dk=dk, dv=dv)
     _typed(fn, torch.int32, cu_seqlens=cu_seqlens)
@@ -784,7 +792,7 @@ def spa_packed_attention_bwd(q, k, v, out, dout, lse, cu_seqlens, B, max_seqlen,
     _keep = (q, k, v, dq, dk, dv, out, dout, lse, cu_seqlens, workspace,)
     _contig(out, dout, lse, cu_seqlens, workspace)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    return _dispatch(lib.spa_packed_attention_bwd, (_ptr(q), _ptr(k), _ptr(v), _row_stride(q), _row_stride(k), _row_stride(v),
+    return _dispatch(getattr(lib, fn), (_ptr(q), _ptr(k), _ptr(v), _row_stride(q), _row_stride(k), _row_stride(v),
                                         _ptr(out), _ptr(dout), _ptr(lse), _ptr(cu_seqlens), B, max_seqlen, H, Dh,
                                         code, float(softmax_scale), _ptr(dq), _ptr(dk), _ptr(dv),
                                         _row_stride(dq), _row_stride(dk), _row_stride(dv), _ptr(workspace),
@@ -817,10 +825,11 @@ def spa_packed_attention_bwd_tokens(q, k, v, out, dy, lse, cu_seqlens, B, max_se
 
 
 def spa_gated_attention_bwd_tokens(q, k, x, scores, out, dy, lse, cu_seqlens, B, max_seqlen, H, Dh, gather_idx, inv_pos,
-                                   dq, dk, d_rg, workspace=None, softmax_scale=0.0, prepare=False):
+                                   dq, dk, d_rg, workspace=None, softmax_scale=0.0, prepare=False, spread=False):
     """The backward of spa_gated_attention_unpack, everything but out and lse at token positions
-    (workspace: only for max_seqlen > 256, and in a launch group)."""
-    fn = "spa_gated_attention_bwd_tokens"
+    (workspace: only for max_seqlen > 256, and in a launch group).  spread: may take the long-segment kernel, given the
+    workspace, where few (image, head) pairs idle the chip (spa_gated_attention_bwd_tokens_spread)."""
+    fn = "spa_gated_attention_bwd_tokens_spread" if spread else "spa_gated_attention_bwd_tokens"
     C = H * Dh
     rows = dy.numel() // dy.shape[-1]
     code = _features(fn, q=q, k=k, x=x, out=out, dy=dy, dq=dq, dk=dk, d_rg=d_rg)
@@ -834,7 +843,7 @@ def spa_gated_attention_bwd_tokens(q, k, x, scores, out, dy, lse, cu_seqlens, B,
     _keep = (q, k, x, scores, dq, dk, d_rg, out, dy, lse, cu_seqlens, gather_idx, inv_pos, workspace,)
     _contig(scores, out, dy, lse, cu_seqlens, gather_idx, inv_pos, workspace)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    return _dispatch(lib.spa_gated_attention_bwd_tokens,
+    return _dispatch(getattr(lib, fn),
                      (_ptr(q), _ptr(k), _ptr(x), _row_stride(q), _row_stride(k), _row_stride(x), _ptr(scores), _ptr(out),
                       _ptr(dy), _ptr(lse), _ptr(cu_seqlens), B, max_seqlen, H, Dh, code, float(softmax_scale),
                       _ptr(gather_idx), _ptr(inv_pos), rows, _ptr(dq), _ptr(dk), _ptr(d_rg), _row_stride(dq),

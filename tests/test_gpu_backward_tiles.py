@@ -114,3 +114,44 @@ def test_gate_backward_at_its_shares(dtype, ntok, C):
     assert abs(float(db) - float(ds.sum())) <= 1e-4 * float(ds.abs().sum())
     ref = 0.25 * float((torch.nn.functional.softplus(s) - y * s).sum())
     assert abs(float(loss) - ref) <= 1e-4 * ref
+
+
+@pytest.mark.parametrize("B,H,Dh,N", [(4, 4, 64, 97), (2, 8, 64, 256), (9, 32, 64, 130), (17, 17, 64, 130), (2, 16, 32, 161),
+                                      (8, 32, 32, 200)])
+def test_spread_backward_of_few_pairs(B, H, Dh, N):
+    """Short segments with few (image, head) pairs, on both sides of the line: the same gradients but for rounding, packed
+    and gated operands, an image without a token and a full one; without the workspace the one-kernel form."""
+    from paper_2410_23608_amd import spa
+    C, cap = H * Dh, B * N
+    g = torch.Generator(device="cuda")
+    g.manual_seed(cap)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    lens = [0, N] + [(37 * b) % (N + 1) for b in range(2, B)]
+    cu = torch.tensor([0] + lens, dtype=torch.int32).cumsum(0).int().cuda()
+    T = sum(lens)
+    idx = torch.cat([b * N + torch.randperm(N)[:n].sort().values for b, n in enumerate(lens)]).cuda()
+    gather = torch.zeros(cap, dtype=torch.int32, device="cuda")
+    gather[:T] = idx.int()
+    inv = torch.full((cap,), -1, dtype=torch.int32, device="cuda")
+    inv[idx] = torch.arange(T, dtype=torch.int32, device="cuda")
+    q, k, x, dy, scores = rnd(cap, C).bfloat16(), rnd(cap, C).bfloat16(), rnd(cap, C).bfloat16(), rnd(cap, C).bfloat16(), rnd(cap)
+    out, lse = torch.zeros(cap, C, device="cuda", dtype=torch.bfloat16), torch.zeros(H, cap, device="cuda")
+    y = torch.empty(B, N, C, device="cuda", dtype=torch.bfloat16)
+    spa.spa_gated_attention_unpack(q, k, x, scores, cu, gather, inv, None, H, Dh, y, out, lse)
+    ws = torch.empty(spa.spa_attention_bwd_workspace_bytes(B, N, H, Dh, spa.dtype_code(out)), dtype=torch.uint8, device="cuda")
+    rel = lambda a, b: float((a.float() - b.float()).norm() / b.float().norm())
+    new = lambda: [torch.full((cap, C), float("nan"), device="cuda", dtype=torch.bfloat16) for _ in range(3)]
+    runs = []
+    for spread, w in ((False, ws), (True, ws), (True, None)):
+        d = new()
+        spa.spa_gated_attention_bwd_tokens(q, k, x, scores, out, dy, lse, cu, B, N, H, Dh, gather, inv, *d, w, spread=spread)
+        runs.append(d)
+    assert all(torch.equal(a, b) for a, b in zip(runs[0], runs[2]))
+    assert all((b[inv < 0] == 0).all() and rel(b, a) <= 5e-3 for a, b in zip(runs[0], runs[1]))
+    pq, pk, pv, pdo = (torch.zeros(cap, C, device="cuda", dtype=torch.bfloat16) for _ in range(4))
+    pq[:T], pk[:T], pdo[:T] = q[idx], k[idx], dy[idx]
+    pv[:T] = (torch.sigmoid(scores[idx])[:, None] * x[idx].float()).bfloat16()
+    a, b = new(), new()
+    spa.spa_packed_attention_bwd(pq, pk, pv, out, pdo, lse, cu, B, N, H, Dh, *a, ws)
+    spa.spa_packed_attention_bwd(pq, pk, pv, out, pdo, lse, cu, B, N, H, Dh, *b, ws, spread=True)
+    assert all(torch.isnan(v[T:]).all() and rel(v[:T], u[:T]) <= 5e-3 for u, v in zip(a, b))
