@@ -350,19 +350,20 @@ __device__ __forceinline__ void bwd_dkdv_role(BwdLongLds<DH>& lds, const BwdArgs
 // wavefronts per SIMD; a fourth, without the second score block in flight, is 2-8 % faster on launches of several
 // rounds and 10-25 % slower on smaller ones.  No load is waited for between two tiles (see PairStage).
 // 16 images of 3136 tokens, 10-60 % selected, 3 heads of 32: 74 -> 52 us; 32 x 1024 tokens, all selected, 12
-// heads of 64: 508 -> 410 us; 2 x 4200 tokens, 5-40 %, 8 heads of 32: 28 -> 20 us.
+// heads of 64: 508 -> 410 us; 2 x 4200 tokens, 5-40 %, 8 heads of 32: 28 -> 20 us; 122 x 480 tokens, 6-48 %, 11 heads
+// of 64, where every workgroup ranked the segments in LDS and those without a block lay between the others: 267 -> 160.
 template <int DH, int MODE>
 __device__ __forceinline__ void bwd_long_block(const BwdArgs& p, unsigned block, unsigned blocks) {
   __shared__ BwdLongLds<DH> lds;
   __shared__ LiveTile s_live;
-  __shared__ int s_cu[2 * kLptMaxB + 1];
-  __shared__ int s_pick;
   const int xcd = block & 7, jj = block >> 3, half = blocks >> 4, nblk = p.nblk;
   Segment seg = {0, 0, 0};
   int h = 0, r0 = 0;
   bool dkdv;
-  if (live_tiles_apply(p.H, p.B)) {
-    const LiveTile lt = live_tile_block<2>(xcd, jj, p.H, p.B, p.cu, kBwdRows, nblk, &s_live);
+  if (p.B <= kLptMaxB) {
+    const LiveTile lt = live_tiles_apply(p.H, p.B)
+                            ? live_tile_block<2>(xcd, jj, p.H, p.B, p.cu, kBwdRows, nblk, &s_live)
+                            : class_tile_block<2>(xcd, jj, p.H, p.B, p.cu, kBwdRows, nblk, &s_live);
     if (lt.valid) seg = {lt.row0, lt.len, lt.len};
     h = lt.h;
     r0 = lt.qb * kBwdRows;
@@ -373,7 +374,7 @@ __device__ __forceinline__ void bwd_long_block(const BwdArgs& p, unsigned block,
   } else {
     dkdv = jj < half;
     const TileId t = xcd_tile_at(xcd, dkdv ? jj : jj - half, nblk, p.H, p.B);
-    if (t.valid) seg = lpt_segment<kBwdThreads>(t.rank, p.B, p.cu, nullptr, 0, s_cu, &s_pick);
+    if (t.valid) seg = segment_of(t.rank, p.cu, nullptr, 0);
     h = t.h;
     r0 = t.qb * kBwdRows;
   }

@@ -596,7 +596,9 @@ tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, c
 //   up to 64 segments and 64 pairs per XCD: live blocks only, longest segment first (live_order); a launch has
 //     at most as many workgroups as are resident together, and number g of an XCD's G takes blocks g,
 //     2 G - 1 - g, 2 G + g, ...: the order is found once per workgroup;
-//   otherwise block qb of every (segment, head) pair in turn.
+//   up to 256 segments: live blocks first, longest segment first, one per workgroup (class_tile_block; 122 x 480
+//     tokens, 6-48 %, 11 heads of 64: 114 us with block qb of every pair in turn, 55 so);
+//   otherwise (and for padded batches) block qb of every (segment, head) pair in turn.
 template <int DH>
 struct TiledShared {
   TiledLds<DH, kTiledBN> lds;
@@ -637,6 +639,12 @@ __device__ __forceinline__ void tiled_block(TiledShared<DH>& sh, const FwdArgs& 
       if (round > 0) __syncthreads();                       // the parked rows are written
       attend({lt.row0, lt.len, lt.len}, lt.h, lt.qb * (32 * NW));
     }
+  }
+  if (a.key_lens == nullptr && B <= kLptMaxB) {
+    const LiveTile lt = class_tile_block<1>(block & 7, block >> 3, H, B, a.cu, 32 * NW, a.nqb,
+                                            reinterpret_cast<LiveTile*>(sh.s_cu));
+    if (lt.valid) attend({lt.row0, lt.len, lt.len}, lt.h, lt.qb * (32 * NW));
+    return;
   }
   const TileId tile_id = xcd_tile_at(block & 7, block >> 3, a.nqb, H, B);
   if (!tile_id.valid) return;
@@ -842,10 +850,6 @@ attn_fwd_bf16_wave_mask_kernel(const FwdArgs a) {
 // of class c has exactly c live blocks.  Walking the 9 classes with scalar arithmetic finds
 // the class, the pair and the block of number r; the image is the k-th set bit of the class
 // ballot and its bounds come by readlane.
-__device__ __forceinline__ int pairs_below(int X, int x) {        // XCD x's pairs with index < X
-  const int g = X >> 3, s = (g & 1) ? 7 - x : x;
-  return g + (s < (X & 7) ? 1 : 0);
-}
 // Block number r of XCD x -> its segment, head and first query (live = false: past the live
 // blocks).  QB = queries per block; a segment's class is its number of blocks.  Every wave of
 // the workgroup computes the same answer from its own ballots.

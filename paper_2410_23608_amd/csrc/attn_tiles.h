@@ -325,6 +325,83 @@ __device__ __forceinline__ LiveTile live_tile_block(int xcd, int j, int H, int B
   return *slot;
 }
 
+constexpr int kLptMaxB = 256;
+__device__ __forceinline__ int pairs_below(int X, int x) {        // XCD x's pairs with index < X, dealt there and back
+  const int g = X >> 3, s = (g & 1) ? 7 - x : x;
+  return g + (s < (X & 7) ? 1 : 0);
+}
+// The same numbering for up to kLptMaxB segments and any number of pairs, segments of as many blocks in index order:
+// with the segments sorted by blocks, those of c blocks are a range, so are their pairs, and an XCD's part of a range
+// has a closed form; one ballot per 64 segments and possible count finds block number j.
+template <int kPasses>
+__device__ __forceinline__ LiveTile class_tile_wave(int xcd, int j, int H, int B, const int32_t* __restrict__ cu, int rows,
+                                                    int nblk) {
+  constexpr int G = kLptMaxB / 64;
+  const int lane = threadIdx.x & 63;
+  int start[G], len[G], cls[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const int b = lane + 64 * g;
+    start[g] = len[g] = cls[g] = 0;
+    if (b < B) {
+      start[g] = cu[b];
+      len[g] = max(cu[b + 1] - start[g], 0);
+      cls[g] = min((len[g] + rows - 1) / rows, nblk);
+    }
+  }
+  LiveTile t = {0, 0, 0, 0, 0, false, false, 0};
+  for (int pass = 0; pass < kPasses; ++pass) {
+    int ranked = 0, mine = 0;                      // segments of more blocks, this XCD's pairs of them
+    for (int c = nblk; c > 0; --c) {
+      uint64_t same[G];
+      int n_c = 0;
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        same[g] = 64 * g < B ? __ballot(cls[g] == c) : 0;
+        n_c += __popcll(same[g]);
+      }
+      if (n_c == 0) continue;
+      if (ranked == 0) t.longest = c * rows;
+      const int pairs = pairs_below((ranked + n_c) * H, xcd) - pairs_below(ranked * H, xcd);
+      if (j < pairs * c) {
+        const int l = mine + j / c, p = 8 * l + (l & 1 ? 7 - xcd : xcd);
+        int k = p / H - ranked;
+        t.h = p % H;
+        t.qb = j % c;
+        t.again = pass > 0;
+        t.valid = true;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const int cnt = __popcll(same[g]);
+          if (k >= 0 && k < cnt) {
+            const int at = kth_set_bit(same[g], k);
+            t.img = 64 * g + at;
+            t.row0 = __builtin_amdgcn_readlane(start[g], at);
+            t.len = __builtin_amdgcn_readlane(len[g], at);
+          }
+          k -= cnt;
+        }
+        return t;
+      }
+      j -= pairs * c;
+      ranked += n_c;
+      mine += pairs;
+    }
+  }
+  return t;
+}
+// For a workgroup of several waves: the first numbers, the others read the answer from LDS.  All threads call it.
+template <int kPasses>
+__device__ __forceinline__ LiveTile class_tile_block(int xcd, int j, int H, int B, const int32_t* __restrict__ cu, int rows,
+                                                     int nblk, LiveTile* slot) {
+  if (threadIdx.x < 64) {
+    const LiveTile t = class_tile_wave<kPasses>(xcd, j, H, B, cu, rows, nblk);
+    if (threadIdx.x == 0) *slot = t;
+  }
+  __syncthreads();
+  return *slot;
+}
+
 // Longest-segment-first launch order.  Work per segment grows like n^2 and workgroups are
 // handed to compute units in launch order, so the heaviest images should start first.  Maps
 // launch rank -> image by ranking the segment lengths (ties by index) and returns that
@@ -333,7 +410,6 @@ __device__ __forceinline__ LiveTile live_tile_block(int xcd, int j, int H, int B
 // Used by the long-segment kernel only: short-segment workgroups are all resident at once
 // and the ranking would cost more than it gains.
 // s_cu: 2*kLptMaxB + 1 ints of LDS.
-constexpr int kLptMaxB = 256;
 template <int THREADS>
 __device__ __forceinline__ Segment lpt_segment(int rank, int B, const int32_t* cu, const int32_t* key_lens,
                                                int n_pad, int* s_cu, int* s_pick) {

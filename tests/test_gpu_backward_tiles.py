@@ -155,3 +155,36 @@ def test_spread_backward_of_few_pairs(B, H, Dh, N):
     spa.spa_packed_attention_bwd(pq, pk, pv, out, pdo, lse, cu, B, N, H, Dh, *a, ws)
     spa.spa_packed_attention_bwd(pq, pk, pv, out, pdo, lse, cu, B, N, H, Dh, *b, ws, spread=True)
     assert all(torch.isnan(v[T:]).all() and rel(v[:T], u[:T]) <= 5e-3 for u, v in zip(a, b))
+
+
+@pytest.mark.parametrize("B,H,Dh,N", [(65, 2, 32, 260), (40, 16, 32, 300), (130, 1, 64, 513), (256, 3, 64, 257), (257, 2, 32, 290)])
+def test_many_long_segments_equal_few(B, H, Dh, N):
+    """Batches past the order of up to 64 segments and 512 pairs, bit for bit the same as image by image in small ones:
+    more than 64, 128 and 256 segments, more than 512 pairs, images without a token."""
+    from paper_2410_23608_amd import spa
+    C = H * Dh
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B + N)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
+    lens = [(0, N, 1, 129, 64, 200)[b % 6] if b % 5 else (53 * b) % (N + 1) for b in range(B)]
+    starts = [0]
+    for n in lens:
+        starts.append(starts[-1] + n)
+    T = starts[-1]
+    q, k, v, dout = rnd(T, C), rnd(T, C), rnd(T, C), rnd(T, C)
+
+    def run(b0, b1):
+        r, nb = slice(starts[b0], starts[b1]), b1 - b0
+        cu = torch.tensor([s - starts[b0] for s in starts[b0:b1 + 1]], dtype=torch.int32, device="cuda")
+        t = [x[r].contiguous() for x in (q, k, v, dout)]
+        out, lse = torch.zeros_like(t[0]), torch.zeros(H, nb * N, device="cuda")
+        ws = torch.empty(spa.spa_attention_bwd_workspace_bytes(nb, N, H, Dh, spa.SPA_BF16), dtype=torch.uint8, device="cuda")
+        d = [torch.full_like(out, float("nan")) for _ in range(3)]
+        spa.spa_packed_attention(*t[:3], cu, nb, N, H, Dh, out, lse)
+        spa.spa_packed_attention_bwd(*t[:3], out, t[3], lse, cu, nb, N, H, Dh, *d, ws)
+        torch.cuda.synchronize()
+        return [out, *d]
+
+    whole, step = run(0, B), 20
+    parts = [run(b, min(B, b + step)) for b in range(0, B, step)]
+    assert all(torch.equal(a, torch.cat(p)) for a, p in zip(whole, zip(*parts)))
