@@ -474,7 +474,8 @@ int group_flush_attention_bwd(hipStream_t st) {
 // accumulators in LDS, no barrier inside either half, so the waves of a workgroup drift apart, and with
 // 65 instead of 141 KB at 196 tokens and at most 128 registers two workgroups share a unit: one loads
 // while the other multiplies.  No atomics, every sum in a fixed order: run-to-run bit-stable.
-// Measured on the ViT-B-shaped batch (64 x 196 tokens, 12 heads of 64): 44.8 -> 37.3 us.
+// Measured on the ViT-B-shaped batch (64 x 196 tokens, 12 heads of 64): 44.8 -> 37.3 us; 128 images, their order by
+// ballots instead of a ranking in LDS in every workgroup: 82 -> 72.
 // Operand rows: packed (row0 + j), or GATED: q, k, v at token positions (row gather_idx[j]), the v row
 // multiplied by Sigmoid(score) and rounded to bf16 (r_g = Sigmoid(s) . r, as a packed r_g holds it).
 // Dynamic LDS, rows = 32 * nw:  A [rows][DH+8] (Q, then K) | B [rows][DH+8] (dO, then V) |
@@ -490,7 +491,6 @@ attn_bwd_short_bf16_kernel(const BwdArgs p) {
   constexpr int RS = DH + 8, KK = DH / 16, DB = DH / 32, CPR = DH / 8, PER = CPR / 2;
   constexpr bool kOnePass = DH == 32;                // dV and dK in one walk (at 64 their accumulators and operands need 150 registers)
   extern __shared__ __attribute__((aligned(16))) unsigned char bwd_smem[];
-  __shared__ int s_pick;
   const int threads = blockDim.x, nw = threads >> 6, rows_cap = 32 * nw;
   __bf16* As = reinterpret_cast<__bf16*>(bwd_smem);
   __bf16* Bs = As + rows_cap * RS;
@@ -503,29 +503,14 @@ attn_bwd_short_bf16_kernel(const BwdArgs p) {
   const bool at_tokens = p.tok.gather_idx != nullptr;
   // heaviest image first (work per segment grows like n^2)
   int img = rank, start = 0, len = 0;
-  if (B > 1 && B <= kWave) {                         // every wave ranks on its own: no LDS, no barrier
-    const RankedSegment rs = ranked_segment_wave(rank, B, cu, nw);
+  if (B > 1 && B <= 8 * kWave) {                     // every wave ranks on its own: no LDS, no barrier
+    const RankedSegment rs = B <= kWave       ? ranked_segment_wave<1>(rank, B, cu, nw)
+                             : B <= 2 * kWave ? ranked_segment_wave<2>(rank, B, cu, nw)
+                                              : ranked_segment_wave<8>(rank, B, cu, nw);
     img = rs.img;
     start = rs.row0;
     len = rs.len;
-  } else {
-    if (B > 1 && B <= 512) {                         // the ranking borrows the operand rows
-      int* s_len = reinterpret_cast<int*>(bwd_smem);
-      for (int b = tid; b < B; b += threads) s_len[b] = cu[b + 1] - cu[b];
-      __syncthreads();
-      for (int b = tid; b < B; b += threads) {
-        const int nb = s_len[b];
-        int r = 0;
-#pragma unroll 8
-        for (int j = 0; j < B; ++j) {
-          const int nj = s_len[j];
-          r += (nj > nb) | ((nj == nb) & (j < b));
-        }
-        if (r == rank) s_pick = b;
-      }
-      __syncthreads();
-      img = s_pick;
-    }
+  } else {                                           // (more images: in index order)
     start = cu[img];
     len = cu[img + 1] - start;
   }

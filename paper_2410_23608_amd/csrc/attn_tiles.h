@@ -174,32 +174,43 @@ __device__ __forceinline__ int kth_set_bit(uint64_t mask, int kth) {
   return pos;
 }
 
-// Heaviest-class-first launch order for up to 64 segments, computed by every wave on its own (no
-// LDS, no barrier): lane b holds segment b's bounds, a segment's class is its number of 32-row
+// Heaviest-class-first launch order for up to 64 G segments, computed by every wave on its own (no
+// LDS, no barrier): lane b holds the bounds of segments b, b + 64, ...; a segment's class is its number of 32-row
 // tiles (<= ncls), launch rank r is the (r - #heavier)th segment of its class in index order.
 // Returns the segment of launch rank `rank` (< B) with its length.
 struct RankedSegment {
   int img, row0, len;
 };
+template <int G>
 __device__ __forceinline__ RankedSegment ranked_segment_wave(int rank, int B, const int32_t* __restrict__ cu, int ncls) {
   const int lane = threadIdx.x & 63;
-  int start = 0, len = 0, cls = -1;
-  if (lane < B) {
-    start = cu[lane];
-    len = cu[lane + 1] - start;
-    cls = min((max(len, 0) + 31) >> 5, ncls);
-  }
-  int img = 0, ranked = 0;
-  for (int c = ncls; c >= 0; --c) {
-    const uint64_t bal = __ballot(cls == c);
-    const int n_c = __popcll(bal);
-    if (rank < ranked + n_c) {
-      img = kth_set_bit(bal, rank - ranked);
-      break;
+  int start[G], len[G], cls[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const int b = lane + 64 * g;
+    start[g] = len[g] = 0;
+    cls[g] = -1;
+    if (b < B) {
+      start[g] = cu[b];
+      len[g] = cu[b + 1] - start[g];
+      cls[g] = min((max(len[g], 0) + 31) >> 5, ncls);
     }
-    ranked += n_c;
   }
-  return {img, __builtin_amdgcn_readlane(start, img), __builtin_amdgcn_readlane(len, img)};
+  RankedSegment s = {0, 0, 0};
+  for (int c = ncls; c >= 0; --c) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const uint64_t bal = __ballot(cls[g] == c);
+      const int n_c = __popcll(bal);
+      if (rank >= 0 && rank < n_c) {
+        const int at = kth_set_bit(bal, rank);
+        s = {64 * g + at, __builtin_amdgcn_readlane(start[g], at), __builtin_amdgcn_readlane(len[g], at)};
+      }
+      rank -= n_c;
+    }
+    if (rank < 0) break;
+  }
+  return s;
 }
 
 // Compact longest-first numbering of the LIVE (segment, head, block) work units of an XCD, for up

@@ -157,10 +157,11 @@ def test_spread_backward_of_few_pairs(B, H, Dh, N):
     assert all(torch.isnan(v[T:]).all() and rel(v[:T], u[:T]) <= 5e-3 for u, v in zip(a, b))
 
 
-@pytest.mark.parametrize("B,H,Dh,N", [(65, 2, 32, 260), (40, 16, 32, 300), (130, 1, 64, 513), (256, 3, 64, 257), (257, 2, 32, 290)])
-def test_many_long_segments_equal_few(B, H, Dh, N):
+@pytest.mark.parametrize("B,H,Dh,N", [(65, 2, 32, 260), (40, 16, 32, 300), (130, 1, 64, 513), (256, 3, 64, 257), (257, 2, 32, 290),
+                                      (66, 2, 64, 196), (129, 1, 32, 130), (513, 1, 64, 40)])
+def test_many_segments_equal_few(B, H, Dh, N):
     """Batches past the order of up to 64 segments and 512 pairs, bit for bit the same as image by image in small ones:
-    more than 64, 128 and 256 segments, more than 512 pairs, images without a token."""
+    more than 64, 128, 256 and 512 segments, more than 512 pairs, short and long ones, images without a token."""
     from paper_2410_23608_amd import spa
     C = H * Dh
     g = torch.Generator(device="cuda")
