@@ -167,7 +167,7 @@ def test_many_segments_equal_few(B, H, Dh, N):
     g = torch.Generator(device="cuda")
     g.manual_seed(B + N)
     rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
-    lens = [(0, N, 1, 129, 64, 200)[b % 6] if b % 5 else (53 * b) % (N + 1) for b in range(B)]
+    lens = [min(N, (0, N, 1, 129, 64, 200)[b % 6]) if b % 5 else (53 * b) % (N + 1) for b in range(B)]
     starts = [0]
     for n in lens:
         starts.append(starts[-1] + n)
