@@ -494,7 +494,7 @@ def measure_train(args, torch, workloads, TrainPass, traffic_table, streams):
            "ms_per_step": 1e3 * med, "ms_per_step_min": 1e3 * mn, "regions": args.repeats,
            "launch": f"eager, one stream, {len(stages)} calls per step ({' + '.join(n_ for n_, _ in stages)}), warm cache",
            "kernels": kernels, "roofline": roof,
-           "attention_bwd_tflops": kernels["packed_attention_bwd_tokens"].get("tflops")}
+           "attention_bwd_tflops": next(k for n_, k in kernels.items() if n_.endswith("attention_bwd_tokens")).get("tflops")}
     S = len(streams)
     if S > 1:   # the training step with S batches in flight, like the forward headline
         tsets = []
