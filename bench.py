@@ -713,7 +713,7 @@ def measure_extras(wl, ctx, args, torch, spa, workloads, pipeline):
         "workload": "vit_s", "launches": [n_ for n_, _ in bstages], "value": vT / bmed, "unit": "selected tokens/s",
         "ms_per_step": 1e3 * bmed, "stage_us": {k_: round(v_, 2) for k_, v_ in bus.items()},
         "qkv_projection_tflops": round(2.0 * vT * VC * 3 * VC / bus["qkv_projection"] / 1e6, 1),
-        "out_projection_tflops": round(2.0 * vT * VC * VC / bus["out_projection"] / 1e6, 1),
+        "out_projection_tflops": round(2.0 * vT * VC * VC / bus["out_projection_unpack"] / 1e6, 1),
         "dense_projection_flops_saved": round(1.0 - vT / (VB * VN), 3)}
     dy_blk = torch.randn(VB, VN, VC, generator=g).cuda().to(torch.bfloat16)
     lab_blk = torch.from_numpy(vb["labels"]).cuda()
