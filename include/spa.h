@@ -287,9 +287,8 @@ int spa_packed_attention(const void* q, const void* k, const void* v, int64_t q_
                          int dtype, float softmax_scale, void* out, float* lse, void* stream);
 
 /*
- * spa_packed_attention with the exponentials always taken against the running maximum of the scores (not only where
- * their range needs it).  The results agree within the rounding of the probabilities; gradients that sum with
- * cancellation behind it agree with those of other implementations of the online softmax more closely.
+ * spa_packed_attention under a second name, for callers linked against it: every form takes the exponentials against
+ * the running maximum of the scores.
  */
 int spa_packed_attention_running_max(const void* q, const void* k, const void* v, int64_t q_row_stride,
                                      int64_t k_row_stride, int64_t v_row_stride, const int32_t* cu_seqlens, int B,

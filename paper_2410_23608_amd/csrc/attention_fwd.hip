@@ -165,18 +165,18 @@ __device__ __forceinline__ void scatter_fill_rows(const Scatter& sc, long r0, lo
 
 // ------------------------------------------------------------------------- bf16 / MFMA
 // Per-wave state of the softmax: O^T accumulators (rows = head dim, cols = this wave's 32
-// queries), reference m of the exponentials (log2 domain, scale folded in; see fwd_exp) and running
+// queries), running maximum m of the scores (log2 domain, scale folded in; see fwd_exp) and running
 // sum l (the two halves of the wave keep partial sums that are added at the end).
 template <int DH>
 struct FwdAcc {
   floatx16 o[DH / 32];
   float m, l;
-  __device__ __forceinline__ void init(float m0 = 0.f) {
+  __device__ __forceinline__ void init() {
 #pragma unroll
     for (int d = 0; d < DH / 32; ++d)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[d][r] = 0.f;
-    m = m0;
+    m = -INFINITY;
     l = 0.f;
   }
 };
@@ -209,106 +209,62 @@ __device__ __forceinline__ void fwd_scores(const __bf16* kbuf, int key0, int rem
   }
 }
 
-// Softmax without a running maximum.  P = exp2(S scale - m) needs a reference m only to stay inside the
-// range of fp32; P, the row sums and the O accumulators are floating point, so their relative precision
-// does not depend on it.  m starts at 0 and is left alone while the lane's row sum stays in
-// [2^-20 after the first keys, 2^40): no maximum over the scores, no exchange between the halves, no
-// rescale of O per group, 56 instead of ~72 vector instructions per 32 x 32 score block, and the
-// exponentials no longer wait for the last score.  When some lane's sum leaves the range (large scores,
-// all first scores far below 0, inf or NaN) the wave takes the group again with the true maximum: the
-// scores are recomputed from the K rows in LDS (they are not kept, to save the registers) and O and l
-// are rescaled, as the online softmax does for every group.
-// RM: the running maximum all the same (spa_packed_attention_running_max).  Which way a probability is rounded to
-// bf16 depends on the reference, and where gradients pass through projections, sums with cancellation (the bias
-// gradient of the gate) move by a few percent with it; the maximum costs up to 9 % of a launch.
-constexpr float kRowSumMin = 9.5367431640625e-07f;     // 2^-20
-constexpr float kRowSumMax = 1.099511627776e+12f;      // 2^40
-template <int DH, int RS, int GSB, bool FULL, bool RM>
-__device__ __forceinline__ void fwd_exp(const floatx16 (&s)[GSB], const __bf16* kbuf, int key0, int rem, bool first,
-                                        const bf16x8 (&qf)[DH / 16], FwdAcc<DH>& acc, float scale_log2,
-                                        bf16x8 (&pb)[GSB][2], int l32, int hh) {
-  auto take = [&](const floatx16& t, int sb, float& sum) {
-    float p[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      p[r] = __builtin_amdgcn_exp2f(fmaf(t[r], scale_log2, -acc.m));
-      sum += p[r];
-    }
-#pragma unroll
-    for (int mf = 0; mf < 2; ++mf) {
-      floatx8 pf;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) pf[j] = p[8 * mf + j];
-      pb[sb][mf] = float_to_bf16x8(pf);
-    }
-  };
-  if (RM) {
-    float mx = s[0][0];
-#pragma unroll
-    for (int sb = 0; sb < GSB; ++sb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sb][r]);
-    const float m_new = fmaxf(acc.m, max_across_halves(mx) * scale_log2);
-    if (__ballot(m_new != acc.m) != 0) {               // some query's running max moved: rescale
-      const float alpha = __builtin_amdgcn_exp2f(acc.m - m_new);
-      acc.l *= alpha;
-#pragma unroll
-      for (int d = 0; d < DH / 32; ++d)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc.o[d][r] *= alpha;
-      acc.m = m_new;
-    }
-  }
-  float psum = 0.f;
+// The online softmax of a group of GSB*32 keys: P = exp2(S scale - m) with m the running maximum of the row, O and
+// l rescaled where it moved.  The maximum is what keeps the results accurate, not only in range: the largest
+// probability of a row is then exactly 1 and rounds to bf16 without an error, so that a row whose weight lies on one
+// key returns that key's V row and dP - D cancels there in the backward.  Against any other reference it is rounded by
+// up to 2^-9 while l adds the unrounded values: the error of the output against 64 bits grows by 1.1, 1.25 and 1.35
+// for normal q and k of sigma 1, 1.5 and 2, that of dq and dk by up to 1.5.  A fixed reference with a rescue by the
+// maximum was faster (us a step: 8 images of 4200 tokens, 5-40 %, 8 heads of 32, 35.5 against 38.7; 64 x 196 tokens,
+// 6 heads of 64, 15.7 against 16.8) and not kept for that loss.
+template <int DH, int GSB, bool FULL>
+__device__ __forceinline__ void fwd_exp(const floatx16 (&s)[GSB], int key0, int rem, FwdAcc<DH>& acc, float scale_log2,
+                                        bf16x8 (&pb)[GSB][2]) {
+  float mx = s[0][0];
 #pragma unroll
   for (int sb = 0; sb < GSB; ++sb)
-    if (FULL || key0 + sb * 32 < rem) take(s[sb], sb, psum);
-  if (RM) {
-    acc.l += psum;
-    return;
-  }
-  const float l_new = acc.l + psum;
-  if (__builtin_expect(__ballot(!(l_new >= (first ? kRowSumMin : 0.f) && l_new < kRowSumMax)) != 0, 0)) {
-    float mx = -INFINITY;
-    floatx16 t[1];
 #pragma unroll
-    for (int sb = 0; sb < GSB; ++sb)
-      if (FULL || key0 + sb * 32 < rem) {
-        fwd_scores<DH, RS, 1, FULL>(kbuf, key0 + sb * 32, rem, qf, t, l32, hh);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, t[0][r]);
-      }
-    mx = max_across_halves(mx) * scale_log2;
-    const bool begun = sum_across_halves(acc.l) > 0.f;            // O holds something
-    const float m_new = begun ? fmaxf(acc.m, mx) : mx;
-    const float alpha = begun ? __builtin_amdgcn_exp2f(acc.m - m_new) : 0.f;
-    acc.m = m_new;
+    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sb][r]);
+  const float m_new = fmaxf(acc.m, max_across_halves(mx) * scale_log2);
+  if (__ballot(m_new != acc.m) != 0) {                 // some query's running max moved: rescale
+    const float alpha = __builtin_amdgcn_exp2f(acc.m - m_new);
     acc.l *= alpha;
 #pragma unroll
     for (int d = 0; d < DH / 32; ++d)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc.o[d][r] *= alpha;
-    psum = 0.f;
-#pragma unroll
-    for (int sb = 0; sb < GSB; ++sb)
-      if (FULL || key0 + sb * 32 < rem) {
-        fwd_scores<DH, RS, 1, FULL>(kbuf, key0 + sb * 32, rem, qf, t, l32, hh);
-        take(t[0], sb, psum);
-      }
+    acc.m = m_new;
   }
+  float psum = 0.f;
+#pragma unroll
+  for (int sb = 0; sb < GSB; ++sb)
+    if (FULL || key0 + sb * 32 < rem) {
+      float p[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        p[r] = __builtin_amdgcn_exp2f(fmaf(s[sb][r], scale_log2, -m_new));
+        psum += p[r];
+      }
+#pragma unroll
+      for (int mf = 0; mf < 2; ++mf) {
+        floatx8 pf;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) pf[j] = p[8 * mf + j];
+        pb[sb][mf] = float_to_bf16x8(pf);
+      }
+    }
   acc.l += psum;
 }
 
 // The probabilities of a group of GSB*32 keys, then O^T += V^T P^T.  V^T at vbuf (row stride TS), the
 // group's keys at column vcol; TS == 0: V rows as they lie in memory (row stride DH + 8, the group's keys
 // from row vcol), the V^T fragments then come from the transposing LDS read.
-template <int DH, int RS, int TS, int GSB, bool FULL, bool RM>
-__device__ __forceinline__ void fwd_softmax_pv(const floatx16 (&s)[GSB], const __bf16* kbuf, const __bf16* vbuf, int vcol,
-                                               int key0, int rem, bool first, const bf16x8 (&qf)[DH / 16],
+template <int DH, int TS, int GSB, bool FULL>
+__device__ __forceinline__ void fwd_softmax_pv(const floatx16 (&s)[GSB], const __bf16* vbuf, int vcol, int key0, int rem,
                                                FwdAcc<DH>& acc, float scale_log2, int l32, int hh) {
   constexpr int DB = DH / 32;
   bf16x8 pb[GSB][2];
-  fwd_exp<DH, RS, GSB, FULL, RM>(s, kbuf, key0, rem, first, qf, acc, scale_log2, pb, l32, hh);
+  fwd_exp<DH, GSB, FULL>(s, key0, rem, acc, scale_log2, pb);
 #pragma unroll
   for (int sb = 0; sb < GSB; ++sb)
     if (FULL || key0 + sb * 32 < rem) {
@@ -330,7 +286,7 @@ __device__ __forceinline__ void fwd_softmax_pv(const floatx16 (&s)[GSB], const _
 // the matrix pipe and the vector ALU overlap inside one wave.  rem = valid keys in the tile;
 // FULL = every key valid (no masking code).
 template <int DH, int RS, int TS, int NSB, bool FULL>
-__device__ __forceinline__ void fwd_process_tile(const __bf16* kbuf, const __bf16* vbuf, int vcol0, int rem, bool first,
+__device__ __forceinline__ void fwd_process_tile(const __bf16* kbuf, const __bf16* vbuf, int vcol0, int rem,
                                                  const bf16x8 (&qf)[DH / 16], FwdAcc<DH>& acc,
                                                  float scale_log2, int l32, int hh) {
   constexpr int GSB = NSB >= 4 ? 2 : 1;     // sub-tiles per softmax group
@@ -343,8 +299,7 @@ __device__ __forceinline__ void fwd_process_tile(const __bf16* kbuf, const __bf1
     if (!FULL && key0 >= rem) break;
     if (g + 1 < NG && (FULL || key0 + GSB * 32 < rem))
       fwd_scores<DH, RS, GSB, FULL>(kbuf, key0 + GSB * 32, rem, qf, s[(g + 1) & 1], l32, hh);
-    fwd_softmax_pv<DH, RS, TS, GSB, FULL, false>(s[g & 1], kbuf, vbuf, vcol0 + key0, key0, rem, first && g == 0, qf, acc,
-                                          scale_log2, l32, hh);
+    fwd_softmax_pv<DH, TS, GSB, FULL>(s[g & 1], vbuf, vcol0 + key0, key0, rem, acc, scale_log2, l32, hh);
   }
 }
 
@@ -523,7 +478,7 @@ struct TiledLds {
 constexpr int kTiledBN = 64;
 
 // The workgroup's work on queries [q0, q0 + 32 NW) of head h of segment seg (q0 < seg.nq).
-template <int DH, int NW, int GATHER, bool RM>
+template <int DH, int NW, int GATHER>
 __device__ __forceinline__ void
 tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, const __bf16* __restrict__ q,
                 const __bf16* __restrict__ k, const __bf16* __restrict__ v, long qs, long ks, long vs, int H,
@@ -564,7 +519,7 @@ tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, c
   bf16x8 qf[DH / 16];
   load_q_frags<DH>(q + q_src * qs + h * DH, q_ok, hh, qf);
   FwdAcc<DH> acc;
-  acc.init(RM ? -INFINITY : 0.f);
+  acc.init();
   store_tile(0);
   __syncthreads();
 
@@ -575,7 +530,7 @@ tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, c
     if (wave_live) {
       floatx16 s[GSB];
       fwd_scores<DH, RS, GSB, !last>(Ks[buf], 0, seg.nk - kt, qf, s, l32, hh);
-      fwd_softmax_pv<DH, RS, 0, GSB, !last, RM>(s, Ks[buf], Vs[buf], 0, 0, seg.nk - kt, t == 0, qf, acc, scale_log2, l32, hh);
+      fwd_softmax_pv<DH, 0, GSB, !last>(s, Vs[buf], 0, 0, seg.nk - kt, acc, scale_log2, l32, hh);
     }
     if (!last) store_tile(buf ^ 1);
     __syncthreads();
@@ -605,12 +560,12 @@ struct TiledShared {
   int s_cu[2 * kLptMaxB + 1];
   int s_pick;
 };
-template <int DH, int NW, int GATHER, bool RM>
+template <int DH, int NW, int GATHER>
 __device__ __forceinline__ void tiled_block(TiledShared<DH>& sh, const FwdArgs& a, unsigned block, unsigned blocks) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, H = a.H, B = a.B;
   const Scatter& sc = a.sc;
   auto attend = [&](const Segment& seg, int h, int q0) {
-    tiled_attention<DH, NW, GATHER, RM>(sh.lds, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, H, a.v_scores, a.scale_log2,
+    tiled_attention<DH, NW, GATHER>(sh.lds, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, H, a.v_scores, a.scale_log2,
                                         a.out, a.lse, a.lse_stride, sc);
   };
   if ((int)block >= a.ntile) {
@@ -653,11 +608,11 @@ __device__ __forceinline__ void tiled_block(TiledShared<DH>& sh, const FwdArgs& 
   if (q0 < seg.nq) attend(seg, tile_id.h, q0);
 }
 
-template <int DH, int NW, bool RM, int GATHER>
+template <int DH, int NW, int GATHER>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH == 32 ? 3 : 2)))
 attn_fwd_bf16_tiled_kernel(const FwdArgs a) {
   __shared__ TiledShared<DH> sh;
-  tiled_block<DH, NW, GATHER, RM>(sh, a, blockIdx.x, gridDim.x);
+  tiled_block<DH, NW, GATHER>(sh, a, blockIdx.x, gridDim.x);
 }
 
 // Short segments, wave-autonomous.  ONE wave per (image, head, 32-query block), no
@@ -669,7 +624,7 @@ attn_fwd_bf16_tiled_kernel(const FwdArgs a) {
 // instead of concentrating a heavy (image, head) on one compute unit.
 // The wave's work on queries [q0, q0 + 32) of head h of segment seg (q0 < seg.nq): Ks, Vs are
 // its private LDS tiles of STEP rows.
-template <int DH, int STEP, int GATHER, bool RM>
+template <int DH, int STEP, int GATHER>
 __device__ __forceinline__ void
 wave_attention(__bf16* Ks, __bf16* Vs, const Segment seg, int h, int q0, const __bf16* __restrict__ q,
                const __bf16* __restrict__ k, const __bf16* __restrict__ v, long qs, long ks, long vs, int H,
@@ -741,7 +696,7 @@ wave_attention(__bf16* Ks, __bf16* Vs, const Segment seg, int h, int q0, const _
   bf16x8 qf[KK];
   load_q_frags<DH>(q + q_src * qs + h * DH, q_ok, hh, qf);
   FwdAcc<DH> acc;
-  acc.init(RM ? -INFINITY : 0.f);
+  acc.init();
 
   for (int kt = 0; kt < seg.nk; kt += STEP) {
     lstore();                                     // this step's rows: registers -> LDS
@@ -753,7 +708,7 @@ wave_attention(__bf16* Ks, __bf16* Vs, const Segment seg, int h, int q0, const _
     // scores of the step: S^T = K Q^T, NSB 32-key sub-tiles, one softmax update for all
     floatx16 s[NSB];
     fwd_scores<DH, RS, NSB, false>(Ks, 0, rem, qf, s, l32, hh);
-    fwd_softmax_pv<DH, RS, 0, NSB, false, RM>(s, Ks, Vs, 0, 0, rem, kt == 0, qf, acc, scale_log2, l32, hh);
+    fwd_softmax_pv<DH, 0, NSB, false>(s, Vs, 0, 0, rem, acc, scale_log2, l32, hh);
   }
 
   // output: park the 32 x DH tile in the (now free) K tile, then write whole rows
@@ -768,7 +723,7 @@ struct WaveLds {
   __attribute__((aligned(16))) __bf16 Ks[STEP * RS];
   __attribute__((aligned(16))) __bf16 Vs[STEP * RS];
 };
-template <int DH, int STEP, bool RM, int GATHER>
+template <int DH, int STEP, int GATHER>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(STEP == 32 ? 3 : 1)))
 attn_fwd_bf16_wave_kernel(const FwdArgs a) {
   __shared__ WaveLds<DH, STEP> lds;
@@ -781,7 +736,7 @@ attn_fwd_bf16_wave_kernel(const FwdArgs a) {
   const FillRange fr = fill_range(a.sc, img, a.B, tile_id.qb, a.nqb);
   const int q0 = tile_id.qb * 32;
   if (q0 < seg.nq)
-    wave_attention<DH, STEP, GATHER, RM>(lds.Ks, lds.Vs, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H, a.v_scores, a.scale_log2, a.out,
+    wave_attention<DH, STEP, GATHER>(lds.Ks, lds.Vs, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H, a.v_scores, a.scale_log2, a.out,
                                          a.lse, a.lse_stride, a.sc);
   if (a.sc.y != nullptr) scatter_fill<__bf16, DH>(a.sc, fr.b, fr.t0, fr.t1, h, C, threadIdx.x, 64);
 }
@@ -822,7 +777,7 @@ __device__ __forceinline__ void mask_unit(MaskLds<DH, STEP>& lds, const FwdArgs&
   const FillRange fr = fill_range(a.sc, img, a.B, tile_id.qb, a.nqb);
   const int q0 = tile_id.qb * 32;
   if (q0 < n)
-    wave_attention<DH, STEP, kFwdGathered, false>(lds.kv.Ks, lds.kv.Vs, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H, a.v_scores, a.scale_log2,
+    wave_attention<DH, STEP, kFwdGathered>(lds.kv.Ks, lds.kv.Vs, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H, a.v_scores, a.scale_log2,
                                    nullptr, nullptr, 0, scl);
   scatter_fill<__bf16, DH>(a.sc, fr.b, fr.t0, fr.t1, h, C, lane, 64);
 }
@@ -908,23 +863,23 @@ static unsigned lpt64_grid(int B, int H, int nqb) {
 
 // Compiled for three waves per SIMD (168 registers at head dim 64, no spills): a ViT-B-shaped
 // batch has ~2800 live waves for 1024 SIMDs and then runs in one round instead of two.
-template <int DH, int STEP, int GATHER, bool RM>
+template <int DH, int STEP, int GATHER>
 __device__ __forceinline__ void lpt64_unit(WaveLds<DH, STEP>& lds, const FwdArgs& a, int x, int j, int units) {
   const int unit = j & 31, m = j >> 5;
   const LptBlock blk = lpt64_block<32>(a.cu, a.key_lens, a.n_pad, a.B, a.H, a.nqb, x, m * 32 + ((m & 1) ? 31 - unit : unit));
   if (blk.live)
-    wave_attention<DH, STEP, GATHER, RM>(lds.Ks, lds.Vs, blk.seg, blk.h, blk.q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H,
+    wave_attention<DH, STEP, GATHER>(lds.Ks, lds.Vs, blk.seg, blk.h, blk.q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H,
                                      a.v_scores, a.scale_log2, a.out, a.lse, a.lse_stride, a.sc);
   if (a.sc.y != nullptr) {
     const long rows = a.sc.flat ? (long)a.sc.N : (long)a.B * a.sc.N, per = (rows + units - 1) / units, u = 8L * j + x;
     scatter_fill_rows<__bf16>(a.sc, min(rows, u * per), min(rows, (u + 1) * per), (long)a.H * DH, threadIdx.x & 63);
   }
 }
-template <int DH, int STEP, bool RM, int GATHER>
+template <int DH, int STEP, int GATHER>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
 attn_fwd_bf16_wave_lpt64_kernel(const FwdArgs a) {
   __shared__ WaveLds<DH, STEP> lds;
-  lpt64_unit<DH, STEP, GATHER, RM>(lds, a, blockIdx.x & 7, blockIdx.x >> 3, gridDim.x);
+  lpt64_unit<DH, STEP, GATHER>(lds, a, blockIdx.x & 7, blockIdx.x >> 3, gridDim.x);
 }
 
 // Several calls in one launch (launch groups, head dim 32): the tiled blocks of those with more than 256 tokens
@@ -940,9 +895,9 @@ attn_fwd_bf16_group_kernel(const Members<FwdArgs> m) {
   const MemberBlock mb = member_of(m, blockIdx.x);
   const FwdArgs& a = m.a[mb.s];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (a.ntile > 0) tiled_block<DH, 4, FORM, false>(sh.tiled, a, mb.block, mb.blocks);
+  if (a.ntile > 0) tiled_block<DH, 4, FORM>(sh.tiled, a, mb.block, mb.blocks);
   else if constexpr (FORM == kFwdGathered) mask_unit<DH, STEP>(sh.wave[wv], a, mb.block & 7, (mb.block >> 3) * 4 + wv);
-  else lpt64_unit<DH, STEP, FORM, false>(sh.wave[wv].kv, a, mb.block & 7, (mb.block >> 3) * 4 + wv, mb.blocks * 4);
+  else lpt64_unit<DH, STEP, FORM>(sh.wave[wv].kv, a, mb.block & 7, (mb.block >> 3) * 4 + wv, mb.blocks * 4);
 }
 
 static thread_local Noted<FwdArgs> g_noted[3];       // by form
@@ -1013,8 +968,8 @@ attn_fwd_bf16_whole_kernel(const __bf16* __restrict__ q, const __bf16* __restric
   if (wave_live) {
     for (int kt = 0; kt < seg.nk; kt += TILE) {
       const int rem = seg.nk - kt;
-      if (rem >= TILE) fwd_process_tile<DH, RS, TS, NSB, true>(Ks + kt * RS, Vt, kt, TILE, kt == 0, qf, acc, scale_log2, l32, hh);
-      else fwd_process_tile<DH, RS, TS, NSB, false>(Ks + kt * RS, Vt, kt, rem, kt == 0, qf, acc, scale_log2, l32, hh);
+      if (rem >= TILE) fwd_process_tile<DH, RS, TS, NSB, true>(Ks + kt * RS, Vt, kt, TILE, qf, acc, scale_log2, l32, hh);
+      else fwd_process_tile<DH, RS, TS, NSB, false>(Ks + kt * RS, Vt, kt, rem, qf, acc, scale_log2, l32, hh);
     }
   }
   __syncthreads();                       // all waves are done reading K: its rows become the output tile
@@ -1190,8 +1145,7 @@ attn_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
 static int attention_common(const char* fn, const void* q, const void* k, const void* v,
                             int64_t q_stride, int64_t k_stride, int64_t v_stride, const int32_t* cu, const int32_t* key_lens, int B,
                             int n_max, int H, int Dh, int dtype, float softmax_scale, void* out,
-                            float* lse, const Scatter& sc, void* stream, bool running_max = false,
-                            const float* v_scores = nullptr) {
+                            float* lse, const Scatter& sc, void* stream, const float* v_scores = nullptr) {
   SPA_REQUIRE(q && k && v && (out || sc.y) && (cu || key_lens), SPA_ERR_INVALID_ARG, "%s: null pointer", fn);
   SPA_REQUIRE(B >= 1 && n_max >= 1 && H >= 1, SPA_ERR_INVALID_ARG, "%s: B, max_seqlen, H must be >= 1", fn);
   SPA_REQUIRE((long)B * n_max < 2147483647L, SPA_ERR_INVALID_ARG, "%s: B*max_seqlen must be < 2^31", fn);
@@ -1239,7 +1193,7 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
       return (unsigned)(args.ntile + std::min<long>((rows + 31) / 32, 1024));
     };
     if (group_open()) {
-      SPA_REQUIRE(Dh == 32 && key_lens == nullptr && !running_max && (n_max > 256 || (form != kFwdGathered && B <= kWave)),
+      SPA_REQUIRE(Dh == 32 && key_lens == nullptr && (n_max > 256 || (form != kFwdGathered && B <= kWave)),
                   SPA_ERR_UNSUPPORTED,
                   "%s: this form cannot be part of a group", fn);
       if (n_max > 256) {
@@ -1249,17 +1203,15 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
       args.nqb = (n_max + 31) / 32;
       return g_noted[form].add(fn, args, wave_groups(lpt64_grid(B, H, args.nqb)));
     }
-#define SPA_ARGS_PLAIN SPA_ARGS
-#define SPA_LAUNCH_MAX(KERNEL, GRID, BLOCK, ARGS, ...)                                                        \
-  do {                                                                                                        \
-    if (running_max) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, true, kFwdPacked>), GRID, BLOCK, 0, st, ARGS);   \
-    else if (form == kFwdGated) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, false, kFwdGated>), GRID, BLOCK, 0, st, ARGS); \
-    else SPA_LAUNCH(KERNEL, GRID, BLOCK, ARGS, __VA_ARGS__, false);                                           \
-  } while (0)
 #define SPA_LAUNCH(KERNEL, GRID, BLOCK, ARGS, ...)                                                            \
   do {                                                                                                        \
     if (sc.gathered) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFwdGathered>), GRID, BLOCK, 0, st, ARGS);       \
     else hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFwdPacked>), GRID, BLOCK, 0, st, ARGS);                     \
+  } while (0)
+#define SPA_LAUNCH_FORM(KERNEL, GRID, BLOCK, ARGS, ...)                                                       \
+  do {                                                                                                        \
+    if (form == kFwdGated) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFwdGated>), GRID, BLOCK, 0, st, ARGS);    \
+    else SPA_LAUNCH(KERNEL, GRID, BLOCK, ARGS, __VA_ARGS__);                                                  \
   } while (0)
 #define SPA_ARGS                                                                                              \
   (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_stride, (long)k_stride, (long)v_stride, cu,   \
@@ -1279,35 +1231,34 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
       const bool step64 = opt.fwd_step64, plain = opt.fwd_plain;
       if (!step64 && !plain && B <= kWave) {
         const dim3 lgrid(lpt64_grid(B, H, nqb));
-        if (Dh == 32) SPA_LAUNCH_MAX(attn_fwd_bf16_wave_lpt64_kernel, lgrid, dim3(64), args, 32, 32);
-        else SPA_LAUNCH_MAX(attn_fwd_bf16_wave_lpt64_kernel, lgrid, dim3(64), args, 64, 32);
+        if (Dh == 32) SPA_LAUNCH_FORM(attn_fwd_bf16_wave_lpt64_kernel, lgrid, dim3(64), args, 32, 32);
+        else SPA_LAUNCH_FORM(attn_fwd_bf16_wave_lpt64_kernel, lgrid, dim3(64), args, 64, 32);
       } else if (Dh == 32) {
-        if (step64) SPA_LAUNCH_MAX(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 32, 64);
-        else SPA_LAUNCH_MAX(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 32, 32);
+        if (step64) SPA_LAUNCH_FORM(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 32, 64);
+        else SPA_LAUNCH_FORM(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 32, 32);
       } else {
-        if (step64) SPA_LAUNCH_MAX(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 64, 64);
-        else SPA_LAUNCH_MAX(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 64, 32);
+        if (step64) SPA_LAUNCH_FORM(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 64, 64);
+        else SPA_LAUNCH_FORM(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 64, 32);
       }
     } else if (!tiled && n_max <= 256 && form != kFwdGated) {
       // short segments: one workgroup per (image, head), whole segment in LDS
       const dim3 grid(H, B);
 #define SPA_WHOLE(D)                                                                                          \
   do {                                                                                                        \
-    if (n_max <= 64) SPA_LAUNCH(attn_fwd_bf16_whole_kernel, grid, dim3(128), SPA_ARGS_PLAIN, D, 64);       \
-    else if (n_max <= 128) SPA_LAUNCH(attn_fwd_bf16_whole_kernel, grid, dim3(256), SPA_ARGS_PLAIN, D, 128); \
-    else SPA_LAUNCH(attn_fwd_bf16_whole_kernel, grid, dim3(512), SPA_ARGS_PLAIN, D, 256);          \
+    if (n_max <= 64) SPA_LAUNCH(attn_fwd_bf16_whole_kernel, grid, dim3(128), SPA_ARGS, D, 64);       \
+    else if (n_max <= 128) SPA_LAUNCH(attn_fwd_bf16_whole_kernel, grid, dim3(256), SPA_ARGS, D, 128); \
+    else SPA_LAUNCH(attn_fwd_bf16_whole_kernel, grid, dim3(512), SPA_ARGS, D, 256);          \
   } while (0)
       if (Dh == 32) SPA_WHOLE(32); else SPA_WHOLE(64);
 #undef SPA_WHOLE
     } else {
       const dim3 grid(tiled_grid());
-      if (Dh == 32) SPA_LAUNCH_MAX(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 32, 4);
-      else SPA_LAUNCH_MAX(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 64, 4);
+      if (Dh == 32) SPA_LAUNCH_FORM(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 32, 4);
+      else SPA_LAUNCH_FORM(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 64, 4);
     }
 #undef SPA_ARGS
-#undef SPA_ARGS_PLAIN
 #undef SPA_LAUNCH
-#undef SPA_LAUNCH_MAX
+#undef SPA_LAUNCH_FORM
   }
   return check_launch(fn);
 }
@@ -1330,12 +1281,8 @@ extern "C" int spa_packed_attention_running_max(const void* q, const void* k, co
                                                 int64_t k_row_stride, int64_t v_row_stride, const int32_t* cu_seqlens, int B,
                                                 int max_seqlen, int H, int Dh, int dtype, float softmax_scale, void* out,
                                                 float* lse, void* stream) {
-  const char* fn = "spa_packed_attention_running_max";
-  SPA_REQUIRE(cu_seqlens, SPA_ERR_INVALID_ARG, "%s: cu_seqlens is null", fn);
-  SPA_REQUIRE(out, SPA_ERR_INVALID_ARG, "%s: out is null", fn);
-  const Scatter none = {nullptr, nullptr, nullptr, nullptr, 0, 0, 0, nullptr};
-  return attention_common(fn, q, k, v, q_row_stride, k_row_stride, v_row_stride, cu_seqlens, nullptr, B, max_seqlen, H, Dh, dtype,
-                          softmax_scale, out, lse, none, stream, true);
+  return spa_packed_attention(q, k, v, q_row_stride, k_row_stride, v_row_stride, cu_seqlens, B, max_seqlen, H, Dh, dtype,
+                              softmax_scale, out, lse, stream);
 }
 
 extern "C" int spa_padded_attention(const void* q, const void* k, const void* v, int64_t row_stride,
@@ -1388,7 +1335,7 @@ extern "C" int spa_gated_attention_unpack(const void* q, const void* k, const vo
   SPA_REQUIRE(dtype == SPA_BF16, SPA_ERR_UNSUPPORTED, "%s: bf16 only (use spa_pack_pair + spa_packed_attention_unpack)", fn);
   const Scatter sc = {gather_idx, inv_pos, base, y, N, 0, 1, nullptr};
   return attention_common(fn, q, k, x, q_row_stride, k_row_stride, x_row_stride, cu_seqlens, nullptr, B, N, H, Dh, dtype,
-                          softmax_scale, out, lse, sc, stream, false, scores);
+                          softmax_scale, out, lse, sc, stream, scores);
 }
 
 extern "C" int spa_selected_attention_unpack(const void* q, const void* k, const void* v, int64_t q_row_stride,

@@ -445,7 +445,7 @@ class BlockTrainPass(_Pass):
                                      self.gather_idx, self.inv_pos, self.total, prepare=True)),
             ("qkv_projection", spa.spa_linear_packed(x, self.gather_idx, self.scores, self.total, W_qkv, b_qkv, p,
                                                      prepare=True)),
-            ("packed_attention", spa.spa_packed_attention_running_max(
+            ("packed_attention", spa.spa_packed_attention(
                 p[:, :C], p[:, C:2 * C], p[:, 2 * C:], self.cu_seqlens, B, N, H, Dh, self.attn, self.lse, prepare=True)),
             ("out_projection_unpack", spa.spa_linear_packed_unpack(self.attn, self.total, W_o, b_o, self.gather_idx,
                                                                    self.inv_pos, x, self.y, prepare=True)),

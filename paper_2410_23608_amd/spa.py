@@ -502,7 +502,7 @@ def spa_packed_attention(q, k, v, cu_seqlens, B, max_seqlen, H, Dh, out, lse=Non
 
 def spa_packed_attention_running_max(q, k, v, cu_seqlens, B, max_seqlen, H, Dh, out, lse=None, softmax_scale=0.0,
                                      prepare=False):
-    """spa_packed_attention with the running maximum of the scores as the reference of the exponentials."""
+    """spa_packed_attention under a second name."""
     return _packed_attention("spa_packed_attention_running_max", q, k, v, cu_seqlens, B, max_seqlen, H, Dh, out, lse,
                              softmax_scale, prepare)
 
