@@ -180,10 +180,15 @@ __device__ __forceinline__ void bwd_dq_role(BwdLongLds<DH>& lds, const BwdArgs& 
 #pragma unroll
     for (int d = 0; d < DB; ++d) acc[d][r] = 0.f;
   }
-  if (GATED) st.store_gated(lds.A[0], lds.Bm[0], gate); else st.store(lds.A[0], lds.Bm[0]);
+  auto store_tile = [&](int buf, auto clear) {
+    if (GATED) st.template store_gated<clear>(lds.A[buf], lds.Bm[buf], gate);
+    else st.template store<clear>(lds.A[buf], lds.Bm[buf]);
+  };
+  store_tile(0, std::true_type{});
   __syncthreads();
   const int nt = (n + BT - 1) / BT;
-  auto tile = [&](int t, auto last) {
+  walk_tiles(nt, [&](int t, auto at) {
+    constexpr bool last = decltype(at)::value == kTileLast;
     const int buf = t & 1, kt = t * BT;
     if (!last) load_tile(kt + BT);
     if (wave_live) {
@@ -217,12 +222,10 @@ __device__ __forceinline__ void bwd_dq_role(BwdLongLds<DH>& lds, const BwdArgs& 
       }
     }
     if (!last) {
-      if (GATED) st.store_gated(lds.A[buf ^ 1], lds.Bm[buf ^ 1], gate); else st.store(lds.A[buf ^ 1], lds.Bm[buf ^ 1]);
+      store_tile(buf ^ 1, std::bool_constant<decltype(at)::value == kTileBeforeLast>{});
       __syncthreads();
     }
-  };
-  for (int t = 0; t + 1 < nt; ++t) tile(t, std::false_type{});
-  tile(nt - 1, std::true_type{});
+  });
   store_rows<DH>(acc, p.scale, p.dq + tok_row * p.dqs + h * DH, q_ok, hh);
 }
 
@@ -257,8 +260,8 @@ __device__ __forceinline__ void bwd_dkdv_role(BwdLongLds<DH>& lds, const BwdArgs
     lse_t = lse_h[q];
     d_t = dvec_h[q];
   };
-  auto store_all = [&](int buf, int qt) {
-    st.store(lds.A[buf], lds.Bm[buf]);
+  auto store_all = [&](int buf, int qt, auto clear) {
+    st.template store<clear>(lds.A[buf], lds.Bm[buf]);
     if (tid < BT) {
       lds.lse2s[buf][tid] = qt + tid < n ? lse_t * kLog2e : INFINITY;    // past the segment: probability 0
       lds.negD[buf][tid] = -d_t;
@@ -284,10 +287,11 @@ __device__ __forceinline__ void bwd_dkdv_role(BwdLongLds<DH>& lds, const BwdArgs
   for (int d = 0; d < DB; ++d)
 #pragma unroll
     for (int r = 0; r < 16; ++r) { dka[d][r] = 0.f; dva[d][r] = 0.f; }
-  store_all(0, 0);
+  store_all(0, 0, std::true_type{});
   __syncthreads();
   const int nt = (n + BT - 1) / BT;
-  auto tile = [&](int t, auto last) {
+  walk_tiles(nt, [&](int t, auto at) {
+    constexpr bool last = decltype(at)::value == kTileLast;
     const int buf = t & 1, qt = t * BT;
     if (!last) load_tile(qt + BT);
     if (wave_live) {
@@ -331,12 +335,10 @@ __device__ __forceinline__ void bwd_dkdv_role(BwdLongLds<DH>& lds, const BwdArgs
         }
     }
     if (!last) {
-      store_all(buf ^ 1, qt + BT);
+      store_all(buf ^ 1, qt + BT, std::bool_constant<decltype(at)::value == kTileBeforeLast>{});
       __syncthreads();
     }
-  };
-  for (int t = 0; t + 1 < nt; ++t) tile(t, std::false_type{});
-  tile(nt - 1, std::true_type{});
+  });
   store_rows<DH>(dka, p.scale, p.dk + tok_row * p.dks + h * DH, k_ok, hh);
   store_rows<DH>(dva, 1.0f, p.dv + tok_row * p.dvs + h * DH, k_ok, hh);
 }

@@ -510,9 +510,9 @@ tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, c
     }
     stage.index(kt + BN);
   };
-  auto store_tile = [&](int buf) {
-    if (GATHER == kFwdGated) stage.store_gated(Ks[buf], Vs[buf], gate);
-    else stage.store(Ks[buf], Vs[buf]);
+  auto store_tile = [&](int buf, auto clear) {
+    if (GATHER == kFwdGated) stage.template store_gated<clear>(Ks[buf], Vs[buf], gate);
+    else stage.template store<clear>(Ks[buf], Vs[buf]);
   };
   stage.index(0);
   load_tile(0);
@@ -520,11 +520,12 @@ tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, c
   load_q_frags<DH>(q + q_src * qs + h * DH, q_ok, hh, qf);
   FwdAcc<DH> acc;
   acc.init();
-  store_tile(0);
+  store_tile(0, std::true_type{});
   __syncthreads();
 
   const int nt = (seg.nk + BN - 1) / BN;
-  auto tile = [&](int t, auto last) {
+  walk_tiles(nt, [&](int t, auto at) {
+    constexpr bool last = decltype(at)::value == kTileLast;
     const int buf = t & 1, kt = t * BN;
     if (!last) load_tile(kt + BN);
     if (wave_live) {
@@ -532,11 +533,9 @@ tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, c
       fwd_scores<DH, RS, GSB, !last>(Ks[buf], 0, seg.nk - kt, qf, s, l32, hh);
       fwd_softmax_pv<DH, 0, GSB, !last>(s, Vs[buf], 0, 0, seg.nk - kt, acc, scale_log2, l32, hh);
     }
-    if (!last) store_tile(buf ^ 1);
+    if (!last) store_tile(buf ^ 1, std::bool_constant<decltype(at)::value == kTileBeforeLast>{});
     __syncthreads();
-  };
-  for (int t = 0; t + 1 < nt; ++t) tile(t, std::false_type{});
-  if (nt > 0) tile(nt - 1, std::true_type{});
+  });
   // every wave is past its last read of the K buffers
   __bf16* parked = &Ks[0][0] + wv * 32 * RS;
   if (wave_live) {

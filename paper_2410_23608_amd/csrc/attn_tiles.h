@@ -6,6 +6,8 @@
 // the token index (a lane reads 4 consecutive tokens of one head-dim column as 8 bytes).
 #pragma once
 
+#include <type_traits>
+
 #include "spa_common.h"
 
 namespace spa {
@@ -465,10 +467,21 @@ __device__ __forceinline__ Segment lpt_segment(int rank, int B, const int32_t* c
 // 8 bf16 multiplied by a row scale, rounded again
 __device__ __forceinline__ bf16x8 scale_row(bf16x8 v, float s) { return float_to_bf16x8(bf16x8_to_float(v) * s); }
 
+// Where a tile stands in a segment's walk: the code of the last one masks, the one before it stores the last one.
+enum TileAt { kTileInside, kTileBeforeLast, kTileLast };
+template <class F>
+__device__ __forceinline__ void walk_tiles(int nt, F tile) {
+  for (int t = 0; t + 2 < nt; ++t) tile(t, std::integral_constant<int, kTileInside>{});
+  if (nt > 1) tile(nt - 2, std::integral_constant<int, kTileBeforeLast>{});
+  if (nt > 0) tile(nt - 1, std::integral_constant<int, kTileLast>{});
+}
+
 // Two row-major tiles of BT tokens of one head on their way to LDS (keys and values, or queries and output
 // gradients), their rows packed or (IDX0, IDX1) named by an index, which is read one tile ahead of the rows.
 // Nothing here waits for a load or branches on one between load() and store(): rows past the segment's end are
-// loaded as its last row (the caller gives such rows probability 0).  With predicated loads and a separate path
+// loaded as its last row (the caller gives such rows probability 0, and store<true>() clears operand 1's, which that
+// probability multiplies: 0 times an infinity of the last row would be NaN; it is for a tile that may be the last, in
+// every tile its selects cost 1 %).  With predicated loads and a separate path
 // for whole tiles the compiler waited for all of them in front of the tile they were meant to overlap.
 template <int DH, int THREADS, int BT, bool IDX0, bool IDX1>
 struct PairStage {
@@ -480,6 +493,7 @@ struct PairStage {
   int stride[2];
   const int32_t* gi;
   int last;                      // the segment's last row
+  int from;                      // first row of the tile in flight
   __device__ __forceinline__ static int row(int t) { return (int)threadIdx.x / CPR + t * RPP; }
   __device__ __forceinline__ void source(int o, const __bf16* p, long row_stride, long row0) {
     base[o] = p + threadIdx.x % CPR * 8 + ((o ? IDX1 : IDX0) ? 0 : row0 * row_stride);
@@ -492,6 +506,7 @@ struct PairStage {
     }
   }
   __device__ __forceinline__ void load(int t0) {
+    from = t0;
 #pragma unroll
     for (int t = 0; t < CPT; ++t) {
       const int r = min(t0 + row(t), last);
@@ -499,7 +514,14 @@ struct PairStage {
       v[1][t] = *reinterpret_cast<const bf16x8*>(base[1] + (long)(IDX1 ? idx[t] : r) * stride[1]);
     }
   }
-  __device__ __forceinline__ void store(__bf16* a, __bf16* b) const {
+  __device__ __forceinline__ void clear_past() {
+#pragma unroll
+    for (int t = 0; t < CPT; ++t)
+      if (from + row(t) > last) v[1][t] = zero_bf16x8();
+  }
+  template <bool LAST>
+  __device__ __forceinline__ void store(__bf16* a, __bf16* b) {
+    if (LAST) clear_past();
 #pragma unroll
     for (int t = 0; t < CPT; ++t) {
       const int o = row(t) * RS + threadIdx.x % CPR * 8;
@@ -508,7 +530,9 @@ struct PairStage {
     }
   }
   // the same with operand 1's rows gated by Sigmoid(gate)
-  __device__ __forceinline__ void store_gated(__bf16* a, __bf16* b, const float (&gate)[CPT]) const {
+  template <bool LAST>
+  __device__ __forceinline__ void store_gated(__bf16* a, __bf16* b, const float (&gate)[CPT]) {
+    if (LAST) clear_past();
 #pragma unroll
     for (int t = 0; t < CPT; ++t) {
       const int o = row(t) * RS + threadIdx.x % CPR * 8;

@@ -171,8 +171,8 @@ def test_scores_that_rise_or_fall_along_the_segment(form, Dh, N, rise):
 
 @pytest.mark.parametrize("form,Dh,N", _forms(FORMS, [(32, 100), (64, 196), (64, 300)]))
 def test_infinities_and_nan_stay_where_they_belong(form, Dh, N):
-    """A NaN in a K row makes its image's outputs NaN and no other image's; NaN and infinities in a V row pass to that
-    column of its image alone, an infinity as itself."""
+    """A NaN in a K row makes its image's outputs NaN and no other image's; NaN and infinities in a V row (the last
+    one of the segment among them) pass to that column of its image alone, an infinity as itself."""
     g = torch.Generator(device="cuda")
     g.manual_seed(N)
     H, lens = 2, [N - 3, N - 3, N - 3, N - 3]
@@ -180,9 +180,9 @@ def test_infinities_and_nan_stay_where_they_belong(form, Dh, N):
     q, k, v = (torch.randn(4 * n, C, generator=g, device="cuda").bfloat16() for _ in range(3))
     clean = _forward(form, q, k, v, lens, N, H, Dh)[0]
     k[n + 7, 3] = float("nan")
-    v[2 * n + n - 2, 5] = float("inf")
+    v[2 * n + n - 1, 5] = float("inf")
     v[3 * n + 2, 1] = -float("inf")
-    v[3 * n + n - 2, Dh + 1] = float("nan")
+    v[3 * n + n - 1, Dh + 1] = float("nan")
     y = _forward(form, q, k, v, lens, N, H, Dh)[0]
     assert torch.equal(y[:n], clean[:n])
     assert torch.isnan(y[n:2 * n, :Dh]).all() and torch.equal(y[n:2 * n, Dh:], clean[n:2 * n, Dh:])
@@ -191,3 +191,37 @@ def test_infinities_and_nan_stay_where_they_belong(form, Dh, N):
         assert torch.equal(y[r][:, rest], clean[r][:, rest])
         for c, val in cols.items():
             assert torch.isnan(y[r, c]).all() if math.isnan(val) else (y[r, c] == val).all(), (c, val)
+
+
+@pytest.mark.parametrize("gated", [False, True])
+@pytest.mark.parametrize("Dh,N", [(32, 300), (64, 290)])
+def test_an_infinite_gradient_reaches_dv_as_itself(Dh, N, gated):
+    """dO = inf in the last row of a segment: that column of dV is inf, the others are what they are without it."""
+    from paper_2410_23608_amd import spa
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    H, n = 2, N - 3
+    C = H * Dh
+    q, k, v, do = (torch.randn(n, C, generator=g, device="cuda").bfloat16() for _ in range(4))
+    do[n - 1, 5] = float("inf")
+    cu = torch.tensor([0, n], dtype=torch.int32, device="cuda")
+    ident = torch.arange(N, dtype=torch.int32, device="cuda")
+    inv = torch.where(ident < n, ident, -1)
+    ws = torch.empty(spa.spa_attention_bwd_workspace_bytes(1, N, H, Dh, spa.SPA_BF16), dtype=torch.uint8, device="cuda")
+    got = []
+    for clean in (True, False):
+        pad = lambda t: torch.cat([t, torch.zeros(N - n, C, device="cuda", dtype=torch.bfloat16)])
+        d = pad(do if not clean else torch.where(torch.isinf(do), torch.zeros_like(do), do))
+        a = [pad(t) for t in (q, k, v)]
+        out, lse = torch.zeros(N, C, device="cuda", dtype=torch.bfloat16), torch.zeros(H, N, device="cuda")
+        spa.spa_packed_attention(*a, cu, 1, N, H, Dh, out, lse)
+        r = [torch.full((N, C), float("nan"), device="cuda", dtype=torch.bfloat16) for _ in range(3)]
+        if gated:
+            spa.spa_gated_attention_bwd_tokens(*a, torch.full((N,), 100.0, device="cuda"), out, d, lse, cu, 1, N, H, Dh, ident, inv,
+                                               *r, ws)
+        else:
+            spa.spa_packed_attention_bwd(*a, out, d, lse, cu, 1, N, H, Dh, *r, ws)
+        torch.cuda.synchronize()
+        got.append(r[2][:n])
+    rest = [c for c in range(C) if c != 5]
+    assert (got[1][:, 5] == float("inf")).all() and torch.equal(got[0][:, rest], got[1][:, rest])
