@@ -22,7 +22,6 @@ int fail(int code, const char* fmt, ...) {
 }
 
 int check_launch(const char* what) {
-  if (g_group_open) return fail(SPA_ERR_UNSUPPORTED, "%s: cannot be part of a group", what);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(SPA_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
   return SPA_OK;

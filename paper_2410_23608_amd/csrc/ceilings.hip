@@ -40,6 +40,7 @@ ceiling_mfma_kernel(float* __restrict__ sink, int iters) {
 using namespace spa;
 
 extern "C" int spa_ceiling_copy(const void* src, void* dst, size_t bytes, void* stream) {
+  SPA_REFUSE_IN_GROUP("spa_ceiling_copy");
   SPA_REQUIRE(src && dst && bytes >= 16 && bytes % 16 == 0, SPA_ERR_INVALID_ARG,
               "spa_ceiling_copy: null pointer or size not a positive multiple of 16");
   SPA_REQUIRE(aligned16(src) && aligned16(dst), SPA_ERR_INVALID_ARG, "spa_ceiling_copy: buffers not 16-byte aligned");
@@ -52,6 +53,10 @@ extern "C" int spa_ceiling_copy(const void* src, void* dst, size_t bytes, void* 
 }
 
 extern "C" double spa_ceiling_mfma(float* sink, int waves_per_simd, int iters, void* stream) {
+  if (group_open()) {
+    fail(SPA_ERR_UNSUPPORTED, "spa_ceiling_mfma: cannot be part of a group");
+    return -1.0;
+  }
   if (sink == nullptr || waves_per_simd < 1 || waves_per_simd > 8 || iters < 1) {
     fail(SPA_ERR_INVALID_ARG, "spa_ceiling_mfma: bad argument");
     return -1.0;

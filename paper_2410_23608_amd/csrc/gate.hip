@@ -868,6 +868,7 @@ extern "C" int spa_gate_select_pooled(const void* x, const void* w, float bias, 
 }
 
 extern "C" int spa_maxpool2x2(const float* s, int B, int h, int w, float* pooled, void* stream) {
+  SPA_REFUSE_IN_GROUP("spa_maxpool2x2");
   SPA_REQUIRE(s && pooled, SPA_ERR_INVALID_ARG, "spa_maxpool2x2: null pointer");
   SPA_REQUIRE(B >= 1 && h >= 2 && w >= 2 && h % 2 == 0 && w % 2 == 0, SPA_ERR_INVALID_ARG,
               "spa_maxpool2x2: need B >= 1 and even h, w >= 2 (got %d, %d, %d)", B, h, w);

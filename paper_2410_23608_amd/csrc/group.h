@@ -56,9 +56,6 @@ struct Noted {
   }
 };
 
-extern thread_local bool g_group_open;
-inline bool group_open() { return g_group_open; }
-
 // One per source file that takes part: launch what was noted / forget it.
 int group_flush_gates(hipStream_t st);
 int group_flush_pack(hipStream_t st);

@@ -82,10 +82,7 @@ static bool big_tiles(const GemmArgs& a) {
 
 int launch_gemm_rows(const char* fn, const GemmArgs& args, bool deep, hipStream_t st) {
   const bool big = big_tiles(args);
-  if (group_open()) {
-    SPA_REQUIRE(deep, SPA_ERR_UNSUPPORTED, "%s: cannot be part of a group", fn);
-    return group_note_rows(fn, args, big);
-  }
+  if (group_open()) return group_note_rows(fn, args, big);
 #define SPA_GEMM(S_, D_)                                                                              \
   return big ? launch_gemm_rows_tile<S_, D_, 256, 256, 2, 4, 2>(fn, args, st)                         \
              : launch_gemm_rows_tile<S_, D_, 128, 128, 2, 2, 2>(fn, args, st)
@@ -103,6 +100,7 @@ static int linear_common(const char* fn, const void* x, const int32_t* gather_id
                          const int32_t* total, const void* W, const void* bias, int M_cap, int K, int N_out,
                          int dtype, void* out, int64_t out_row_stride, const int32_t* scatter_idx,
                          const void* residual, const int32_t* inv_pos, int64_t rows, void* stream) {
+  SPA_REFUSE_IN_GROUP(fn);
   SPA_REQUIRE(x && W && out, SPA_ERR_INVALID_ARG, "%s: null pointer", fn);
   SPA_REQUIRE(M_cap >= 1 && K >= 1 && N_out >= 1, SPA_ERR_INVALID_ARG, "%s: M_cap, K, N_out must be >= 1", fn);
   SPA_REQUIRE(dtype == SPA_F32 || dtype == SPA_BF16, SPA_ERR_UNSUPPORTED, "%s: unknown dtype %d", fn, dtype);

@@ -624,6 +624,7 @@ extern "C" int64_t spa_container_segments_capacity(int B, int64_t max_total, int
 extern "C" int spa_container_segments(const int32_t* cu_seqlens, int B, int container_len, int64_t max_total,
                                       int seg_cap, int32_t* seg_cu_seqlens, int32_t* n_segments, void* stream) {
   const char* fn = "spa_container_segments";
+  SPA_REFUSE_IN_GROUP(fn);
   SPA_REQUIRE(cu_seqlens && seg_cu_seqlens && n_segments, SPA_ERR_INVALID_ARG, "%s: null pointer", fn);
   SPA_REQUIRE(B >= 1 && container_len >= 1 && max_total >= 0, SPA_ERR_INVALID_ARG,
               "%s: B, container_len must be >= 1 and max_total >= 0", fn);
@@ -648,7 +649,7 @@ extern "C" int spa_pack_containers(const uint8_t* mask, int B, int grid_h, int g
   const int64_t need = spa_container_segments_capacity(B, (int64_t)B * N, container_len);
   SPA_REQUIRE(seg_cap >= need, SPA_ERR_WORKSPACE, "%s: seg_cap = %d, need %lld for B = %d, N = %d, L = %d", fn, seg_cap,
               (long long)need, B, N, container_len);
-  SPA_REQUIRE(!group_open(), SPA_ERR_UNSUPPORTED, "%s: cannot be part of a group", fn);
+  SPA_REFUSE_IN_GROUP(fn);
   if (B > kSegImages) {           // more images than the first workgroup's LDS holds
     if (int rc = spa_pack_shifted(nullptr, mask, nullptr, nullptr, B, grid_h, grid_w, shift_h, shift_w, 8, SPA_BF16, 0, nullptr,
                                   cu_seqlens, gather_idx, inv_pos, total, stream))
@@ -668,6 +669,7 @@ extern "C" int spa_pack_containers(const uint8_t* mask, int B, int grid_h, int g
 
 extern "C" int spa_unpack(const void* packed_out, const int32_t* inv_pos, const void* base,
                           int B, int N, int C, int dtype, void* y, void* stream) {
+  SPA_REFUSE_IN_GROUP("spa_unpack");
   SPA_REQUIRE(packed_out && inv_pos && y, SPA_ERR_INVALID_ARG, "spa_unpack: null pointer");
   if (int rc = check_rows("spa_unpack", B, N, C, dtype)) return rc;
   SPA_REQUIRE(aligned16(packed_out) && aligned16(y) && aligned16(base), SPA_ERR_INVALID_ARG,
@@ -679,6 +681,7 @@ extern "C" int spa_unpack(const void* packed_out, const int32_t* inv_pos, const 
 
 extern "C" int spa_pack_bwd(const void* dpacked, const int32_t* inv_pos, int B, int N, int C,
                             int dtype, void* d_rg, void* stream) {
+  SPA_REFUSE_IN_GROUP("spa_pack_bwd");
   SPA_REQUIRE(dpacked && inv_pos && d_rg, SPA_ERR_INVALID_ARG, "spa_pack_bwd: null pointer");
   if (int rc = check_rows("spa_pack_bwd", B, N, C, dtype)) return rc;
   SPA_REQUIRE(aligned16(dpacked) && aligned16(d_rg), SPA_ERR_INVALID_ARG, "spa_pack_bwd: buffers not 16-byte aligned");
@@ -689,6 +692,7 @@ extern "C" int spa_pack_bwd(const void* dpacked, const int32_t* inv_pos, int B, 
 
 extern "C" int spa_unpack_bwd(const void* dy, const int32_t* gather_idx, const int32_t* total,
                               int B, int N, int C, int dtype, void* dout, void* stream) {
+  SPA_REFUSE_IN_GROUP("spa_unpack_bwd");
   SPA_REQUIRE(dy && gather_idx && total && dout, SPA_ERR_INVALID_ARG, "spa_unpack_bwd: null pointer");
   if (int rc = check_rows("spa_unpack_bwd", B, N, C, dtype)) return rc;
   SPA_REQUIRE(aligned16(dy) && aligned16(dout), SPA_ERR_INVALID_ARG, "spa_unpack_bwd: buffers not 16-byte aligned");

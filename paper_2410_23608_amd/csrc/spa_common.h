@@ -27,10 +27,15 @@ inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s);
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline int elem_size(int dtype) { return dtype == SPA_BF16 ? 2 : 4; }
 
+extern thread_local bool g_group_open;             // a launch group is open on this thread (group.h)
+inline bool group_open() { return g_group_open; }
+
 #define SPA_REQUIRE(cond, code, ...)                 \
   do {                                               \
     if (!(cond)) return ::spa::fail(code, __VA_ARGS__); \
   } while (0)
+// For entry points that launch at once whatever the group: nothing of a group is launched when a call of it fails.
+#define SPA_REFUSE_IN_GROUP(fn) SPA_REQUIRE(!::spa::group_open(), SPA_ERR_UNSUPPORTED, "%s: cannot be part of a group", fn)
 
 // ---- device side -----------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));

@@ -118,3 +118,80 @@ def test_what_a_group_refuses(mods):
     spa.spa_gate_select(x, w, 0.0, None, 0.5, scores, mask)
     torch.cuda.synchronize()
     assert (mask != 7).all()
+
+
+def test_a_refused_call_launches_nothing(mods):
+    """Every call that cannot be part of a group leaves its outputs as they were, and the calls noted before it too."""
+    spa, _ = mods
+    B, N, C, L = 2, 16, 64, 5
+    f32 = lambda *s: torch.ones(*s, device="cuda")
+    i32 = lambda *s: torch.zeros(*s, dtype=torch.int32, device="cuda")
+    x, xb, w, wb = f32(B, N, C), f32(B, N, C).bfloat16(), f32(C, C), f32(C, C).bfloat16()
+    idx, cu, tot = torch.arange(B * N, dtype=torch.int32, device="cuda"), torch.tensor([0, N, 2 * N]).int().cuda(), i32(1) + B * N
+    scores, mask = f32(B, N), torch.full((B, N), 7, dtype=torch.uint8, device="cuda")
+    calls = {
+        "maxpool2x2": lambda o: spa.spa_maxpool2x2(f32(B, N), 4, 4, o(torch.float32, B, N // 4)),
+        "container_segments": lambda o: spa.spa_container_segments(cu, L, B * N, o(torch.int32, B + B * N // L + 1), i32(1)),
+        "pack_containers": lambda o: spa.spa_pack_containers(mask, 4, 4, 0, 0, L, o(torch.int32, B + 1), i32(B * N), i32(B * N),
+                                                             i32(1), i32(B + B * N // L + 1), i32(1)),
+        "unpack": lambda o: spa.spa_unpack(xb.view(-1, C), idx, None, o(torch.bfloat16, B, N, C)),
+        "pack_bwd": lambda o: spa.spa_pack_bwd(xb.view(-1, C), idx, o(torch.bfloat16, B, N, C)),
+        "unpack_bwd": lambda o: spa.spa_unpack_bwd(xb, idx, tot, o(torch.bfloat16, B * N, C)),
+        "linear_packed f32": lambda o: spa.spa_linear_packed(x, idx, None, tot, w, None, o(torch.float32, B * N, C)),
+        "linear_packed": lambda o: spa.spa_linear_packed(xb, idx, None, tot, wb, None, o(torch.bfloat16, B * N, C)),
+        "linear_scatter f32": lambda o: spa.spa_linear_packed_scatter(x.view(-1, C), tot, w, None, idx, None, o(torch.float32, B, N, C)),
+        "linear_unpack f32": lambda o: spa.spa_linear_packed_unpack(x.view(-1, C), tot, w, None, idx, idx, x, o(torch.float32, B, N, C)),
+        "ceiling_copy": lambda o: spa.spa_ceiling_copy(x, o(torch.float32, B, N, C)),
+        "gate f32": lambda o: spa.spa_gate_select(x, w[0], 0.0, None, 0.5, o(torch.float32, B, N), mask),
+        "pack f32": lambda o: spa.spa_pack(x, mask, None, None, 0, o(torch.float32, B * N, C), cu, i32(B * N), i32(B * N), i32(1)),
+        "padded_attention": lambda o: spa.spa_padded_attention(xb.view(-1, C), xb.view(-1, C), xb.view(-1, C), i32(B) + N, B, N, 2, 32,
+                                                               o(torch.bfloat16, B * N, C)),
+    }
+    for name, call in calls.items():
+        made = []
+        out = lambda dtype, *s: made.append(torch.full(s, 99, dtype=dtype, device="cuda")) or made[-1]
+        torch.cuda.synchronize()
+        spa.spa_group_begin()
+        spa.spa_gate_select(xb, wb[0], 0.0, None, 0.5, scores, mask)
+        with pytest.raises(spa.SpaError):
+            call(out)
+        with pytest.raises(spa.SpaError):
+            spa.spa_group_end()
+        torch.cuda.synchronize()
+        assert len(made) == 1 and (made[0] == 99).all() and (mask == 7).all() and (scores == 1).all(), name
+
+
+def test_packed_rows_and_pairs_in_a_group(mods):
+    """The calls of a training pass with packed rows (pairs packed in one launch, gradients at token positions) of two
+    stages, in a group and one by one."""
+    spa, pipeline = mods
+    got = []
+    for grouped in (True, False):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(5)
+        rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+        chains, passes = [], []
+        for N, H in ((300, 2), (50, 3)):
+            B, C = 3, 32 * H
+            p = pipeline.TrainPass(B, N, C, H, "bf16", pack_rows=True)
+            assert not p.gated
+            x, w = rnd(B, N, C).bfloat16(), (2 * rnd(C) / C ** 0.5).bfloat16()
+            x[0] = 0
+            chains.append(p.stages(x, w, rnd(B, N, 2 * C).bfloat16(), (rnd(B, N) > 0).to(torch.uint8), rnd(B, N, C).bfloat16()))
+            passes.append(p)
+        for j in range(len(chains[0])):
+            if grouped:
+                spa.group(*(c[j][1] for c in chains))()
+            else:
+                for c in chains:
+                    c[j][1]()
+        torch.cuda.synchronize()
+        got.append(passes)
+    for a, b in zip(*got):
+        for name in ("scores", "mask", "cu_seqlens", "inv_pos", "y"):
+            assert torch.equal(getattr(a, name), getattr(b, name)), name
+        T = int(b.total)
+        assert T > 0 and torch.equal(a.packed_qk[:T], b.packed_qk[:T]) and torch.equal(a.packed_v[:T], b.packed_v[:T])
+        for name in ("dqk", "d_rg", "dx", "dw", "db", "loss"):
+            u, v = getattr(a, name).float(), getattr(b, name).float()
+            assert (u - v).abs().max() <= 2e-2 * max(1.0, float(v.abs().max())), name
