@@ -42,11 +42,38 @@ template <> struct Vec16<__bf16> {
   }
 };
 
+template <typename T> struct Raw16;
+template <> struct Raw16<float> { using type = floatx4; };
+template <> struct Raw16<__bf16> { using type = bf16x8; };
+__device__ __forceinline__ void widen(floatx4 v, float (&f)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) f[i] = v[i];
+}
+__device__ __forceinline__ void widen(bf16x8 v, float (&f)[8]) {
+  const floatx8 w = bf16x8_to_float(v);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) f[i] = w[i];
+}
+
 template <int G>
 __device__ __forceinline__ float group_sum(float v) {
 #pragma unroll
   for (int o = G / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
   return v;
+}
+
+// Lanes per token: by the row's 16-byte chunks (the same for every launch of the gate)
+__host__ __device__ constexpr int gate_lanes(int chunks) { return chunks <= 8 ? 8 : chunks <= 64 ? 16 : chunks <= 256 ? 32 : 64; }
+// The order of a token's sum.  The gate backward forms the sum again to see which side won the maximum with the
+// up-scale score, on up to 64 lanes where the forward has 16 or 32, and near a tie the last bit decides: a lane of the
+// forward therefore keeps gate_chains(G) partial sums, chunk number k of the lane in chain k % gate_chains(G), and
+// folds them as the wider exchange of the backward does (lane ^ 32, then lane ^ 16).  Both then agree bit for bit.
+__host__ __device__ constexpr int gate_chains(int G) { return G == 16 ? 4 : G == 32 ? 2 : 1; }
+template <int A>
+__device__ __forceinline__ float fold_chains(const float (&acc)[A]) {
+  if constexpr (A == 4) return (acc[0] + acc[2]) + (acc[1] + acc[3]);
+  else if constexpr (A == 2) return acc[0] + acc[1];
+  else return acc[0];
 }
 
 // One group of G lanes per token; the group strides over the row's 16-byte chunks.
@@ -179,8 +206,9 @@ __device__ __forceinline__ void build_pack_index(const uint8_t* mask, int ntok, 
   }
 }
 
+// Held to eight waves per SIMD (left alone the sixteen-lane form takes 74 registers: 6 waves, 1 % of a detection step).
 template <typename T, int G, bool kPool, bool kIndex>
-__global__ void __launch_bounds__(kGateThreads)
+__global__ void __launch_bounds__(kGateThreads) __attribute__((amdgpu_waves_per_eu(kIndex ? 4 : 8)))
 gate_select_kernel(const T* __restrict__ x, const T* __restrict__ w, float bias,
                    const float* __restrict__ s_up, const float* __restrict__ noise, float theta, int ntok, int N, int C,
                    PoolGrid pool, float* __restrict__ scores, uint8_t* __restrict__ mask, IndexOut idx) {
@@ -193,24 +221,40 @@ gate_select_kernel(const T* __restrict__ x, const T* __restrict__ w, float bias,
   __shared__ uint8_t s_sel[kGroups];
   for (long base = (long)blockIdx.x * kGroups; base < ntok; base += (long)gridDim.x * kGroups) {
     const long tok = base + grp;
-    float acc = 0.f;
+    constexpr int A = gate_chains(G);
+    float acc[A] = {};
     if (tok < ntok) {
       // the lane's chunks of w come from memory like its chunks of the row (w is a few KB that every
       // workgroup reads: cache hits), issued together with them: no staging of w in LDS, no barrier
       // between the launch and the first row load
       const T* row = x + tok * (long)C;
-#pragma unroll 4
-      for (int ch = gl; ch < chunks; ch += G) {
-        float f[VE], wv[VE];
-        Vec16<T>::load(row + ch * VE, f);
-        Vec16<T>::load(w + ch * VE, wv);
+#pragma unroll(4 / A)
+      for (int c0 = 0; c0 < chunks; c0 += A * G) {
+        typename Raw16<T>::type xr[A], wr[A];
 #pragma unroll
-        for (int i = 0; i < VE; ++i) acc = fmaf(f[i], wv[i], acc);
+        for (int a = 0; a < A; ++a) {
+          const int ch = c0 + a * G + gl;
+          xr[a] = {};                                      // (past the row: zeros, which change no sum)
+          wr[a] = {};
+          if (ch < chunks) {
+            xr[a] = *reinterpret_cast<const typename Raw16<T>::type*>(row + ch * VE);
+            wr[a] = *reinterpret_cast<const typename Raw16<T>::type*>(w + ch * VE);
+          }
+        }
+#pragma unroll
+        for (int a = 0; a < A; ++a)
+          if (c0 + a * G < chunks) {                       // uniform
+            float f[VE], wv[VE];
+            widen(xr[a], f);
+            widen(wr[a], wv);
+#pragma unroll
+            for (int i = 0; i < VE; ++i) acc[a] = fmaf(f[i], wv[i], acc[a]);
+          }
       }
     }
-    acc = group_sum<G>(acc);
+    const float dot = group_sum<G>(fold_chains(acc));
     if (gl == 0 && tok < ntok) {
-      float s = acc + bias;
+      float s = dot + bias;
       if (kPool) {
         const int b = (int)(tok / N), n = (int)(tok - (long)b * N);
         const int oy = n / pool.gw, ox = n - oy * pool.gw;
@@ -299,16 +343,13 @@ struct PyramidArgs {
 // threads, this one being number `tid`: U tokens of a group and K chunks of each in flight together.
 template <int G, int U, int K, class At>
 __device__ __forceinline__ void pyramid_dots(const GateStage& s, int n, float* out, int tid, int threads, At at) {
-  constexpr int VE = 8;
+  constexpr int VE = 8, A = gate_chains(G) < K ? gate_chains(G) : K;       // (K chunks of a lane are all it has, or a multiple of the chains)
   const int grp = tid / G, gl = tid % G, groups = threads / G, chunks = s.C / VE;
   for (int i0 = grp; i0 < n; i0 += groups * U) {
     const __bf16* row[U];
-    float acc[U];
+    float acc[U][A] = {};
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      row[u] = s.x + (long)at(min(i0 + u * groups, n - 1)) * s.C;
-      acc[u] = 0.f;
-    }
+    for (int u = 0; u < U; ++u) row[u] = s.x + (long)at(min(i0 + u * groups, n - 1)) * s.C;
     for (int c0 = gl; c0 < chunks; c0 += G * K) {
       bf16x8 f[K][U], wv[K];
 #pragma unroll
@@ -326,19 +367,17 @@ __device__ __forceinline__ void pyramid_dots(const GateStage& s, int n, float* o
           for (int u = 0; u < U; ++u) {
             const floatx8 xf = bf16x8_to_float(f[k][u]);
 #pragma unroll
-            for (int e = 0; e < VE; ++e) acc[u] = fmaf(xf[e], wf[e], acc[u]);
+            for (int e = 0; e < VE; ++e) acc[u][k % A] = fmaf(xf[e], wf[e], acc[u][k % A]);
           }
         }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const float d = group_sum<G>(acc[u]);
+      const float d = group_sum<G>(fold_chains(acc[u]));
       if (gl == 0 && i0 + u * groups < n) out[i0 + u * groups] = d;
     }
   }
 }
-// Lanes per token: by the row's 16-byte chunks (the same for every launch of the gate)
-__host__ __device__ constexpr int gate_lanes(int chunks) { return chunks <= 8 ? 8 : chunks <= 64 ? 16 : chunks <= 256 ? 32 : 64; }
 
 __global__ void __launch_bounds__(kGateThreads) gate_pyramid_kernel(const PyramidArgs p) {
   __shared__ float s_score[2 * kPyramidTokens];          // the stages one after the other: 64 + 16 + 4 + 1 tokens, or fewer
@@ -461,19 +500,6 @@ struct StraightThrough {
   float inv_temperature;
 };
 
-template <typename T> struct Raw16;
-template <> struct Raw16<float> { using type = floatx4; };
-template <> struct Raw16<__bf16> { using type = bf16x8; };
-__device__ __forceinline__ void widen(floatx4 v, float (&f)[4]) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) f[i] = v[i];
-}
-__device__ __forceinline__ void widen(bf16x8 v, float (&f)[8]) {
-  const floatx8 w = bf16x8_to_float(v);
-#pragma unroll
-  for (int i = 0; i < 8; ++i) f[i] = w[i];
-}
-
 template <typename T>
 struct GateBwdArgs {
   const T *x, *w;
@@ -560,7 +586,7 @@ __device__ __forceinline__ void gate_bwd_block(const GateBwdArgs<T>& a, unsigned
       }
       dot = group_sum<G>(dot);
       bool own = tok < t1;
-      if (s_up != nullptr) own = own && group_sum<G>(g) + bias >= up[u];   // else the up-scale score won the max
+      if (s_up != nullptr) own = own && group_sum<G>(g) + bias >= up[u];   // else the up-scale score won the max (see gate_chains)
       const float p = sigmoidf_dev(s[u]);
       const float y = lab[u] != 0 ? 1.f : 0.f;
       float ds = loss_scale * (p - y);

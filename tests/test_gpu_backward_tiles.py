@@ -189,3 +189,30 @@ def test_many_segments_equal_few(B, H, Dh, N):
     whole, step = run(0, B), 20
     parts = [run(b, min(B, b + step)) for b in range(0, B, step)]
     assert all(torch.equal(a, torch.cat(p)) for a, p in zip(whole, zip(*parts)))
+
+
+@pytest.mark.parametrize("dtype,C", [(t, k * c) for t, k in ((torch.bfloat16, 8), (torch.float32, 4))
+                                     for c in (8, 16, 17, 25, 32, 33, 48, 64, 65, 96, 128, 129, 256, 257, 512)])
+def test_gate_backward_decides_ties_as_the_forward(dtype, C):
+    """Up-scale scores at the gate's own value (a tie: the gate's), one step of fp32 above (theirs) and one below it, for
+    every way the backward spreads a row over lanes: (w, x) get a gradient exactly where the gate won."""
+    from paper_2410_23608_amd import spa
+    ntok = 600
+    g = torch.Generator(device="cuda")
+    g.manual_seed(C)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    x, w, lab = rnd(1, ntok, C).to(dtype), (rnd(C) / C ** 0.5).to(dtype), (rnd(1, ntok) > 0).to(torch.uint8)
+    own, scores = torch.empty(1, ntok, device="cuda"), torch.empty(1, ntok, device="cuda")
+    mask = torch.empty(1, ntok, dtype=torch.uint8, device="cuda")
+    spa.spa_gate_select(x, w, 0.3, None, 0.5, own, mask)
+    step = torch.arange(ntok, device="cuda")[None] % 3 - 1
+    inf = torch.full_like(own, float("inf"))
+    up = torch.where(step > 0, torch.nextafter(own, inf), torch.where(step < 0, torch.nextafter(own, -inf), own))
+    spa.spa_gate_select(x, w, 0.3, up, 0.5, scores, mask)
+    assert torch.equal(scores, torch.maximum(own, up))
+    ws = torch.empty(spa.spa_gate_bwd_workspace_bytes(1, ntok, C, spa.dtype_code(x)), dtype=torch.uint8, device="cuda")
+    f = lambda n: torch.full((n,), float("nan"), device="cuda")
+    loss, dw, db, dx = f(1), f(C), f(1), torch.full_like(x, float("nan"))
+    spa.spa_gate_bwd(x, w, 0.3, scores, up, lab, None, False, 1.0, loss, dx, dw, db, ws)
+    torch.cuda.synchronize()
+    assert torch.equal((dx != 0).any(-1), step <= 0)
