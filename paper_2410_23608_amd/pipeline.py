@@ -50,7 +50,8 @@ class _Pass:
                 self._plan = plan
                 return
         seen = [None if t is None else (t.shape, t.dtype) for t in inputs]
-        if seen == self._plan_seen:
+        # (a recording takes contiguous device tensors only: rows inside a wider buffer go stage by stage)
+        if seen == self._plan_seen and all(t is None or (t.is_cuda and t.is_contiguous()) for t in inputs):
             plan = spa.record(stages, inputs)
             if plan(*inputs):
                 self._plan, self._plans = plan, (plan, *self._plans[:3])

@@ -84,3 +84,25 @@ def test_recorded_run_with_optional_inputs_and_refusals(pipeline):
     for bad in ((x.float(), w, qkv), (x, w, qkv.cpu()), (x.transpose(0, 1).contiguous().transpose(0, 1), w, qkv)):
         with pytest.raises(ValueError):
             p.run(*bad)
+
+
+@pytest.mark.parametrize("form", [dict(gathered=True), dict(gathered=True, keep_packed_out=False, from_mask=True)])
+def test_rows_inside_a_wider_buffer_are_not_recorded(pipeline, monkeypatch, form):
+    """q | k | v as a column slice is taken stage by stage on every run, with no attempt at a recording of it."""
+    made = []
+    record = pipeline.spa.record
+    monkeypatch.setattr(pipeline.spa, "record", lambda *a: made.append(1) or record(*a))
+    p, ref = (pipeline.ForwardPass(WL.B, WL.N, WL.C, WL.H, "bf16", **form) for _ in range(2))
+    x, w, qkv = _inputs("forward", 3)
+    wide = torch.cat([qkv, torch.full_like(x, float("nan"))], -1)
+    for _ in range(4):
+        p.y.fill_(float("nan"))
+        y = p.run(x, w, wide[..., :3 * WL.C])
+        for _, fn in ref.stages(x, w, qkv):
+            fn()
+        assert torch.equal(y, ref.y)
+    assert not made
+    for _ in range(3):
+        assert torch.equal(p.run(x, w, qkv), ref.y)
+    assert len(made) == 1
+    assert torch.equal(p.run(x, w, wide[..., :3 * WL.C]), ref.y) and len(made) == 1
