@@ -10,6 +10,7 @@ of tests/test_host_sanitizers.py; it is never loaded by the binding.
 from __future__ import annotations
 
 import concurrent.futures
+import importlib.util
 import os
 import subprocess
 import sys
@@ -59,9 +60,12 @@ def _compile(src: str, sanitize: bool = False) -> str:
 
 
 def build_launcher() -> str:
+    torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
     cmd = [HIPCC, "-O2", "-std=c++17", "-fPIC", "-shared", "-x", "c++", "-I", sysconfig.get_paths()["include"],
            "-I", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"), "-D__HIP_PLATFORM_AMD__",
-           "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "launcher.cpp"), "-o", LAUNCHER_PATH]
+           "-isystem", os.path.join(torch_dir, "include"), "-D_GLIBCXX_USE_CXX11_ABI=1",
+           "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "launcher.cpp"), "-o", LAUNCHER_PATH,
+           "-L", os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for launcher.cpp:\n{r.stdout}\n{r.stderr}")

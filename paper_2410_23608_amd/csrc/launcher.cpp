@@ -4,14 +4,17 @@
 // re-checking the tensors of every call costs 5 us per launch for prepared calls and 10-25 us
 // otherwise, against 2.9 us for the launch itself: a step of three launches was bound by the host
 // (42 us for 19 us of kernels at 2 x 196 tokens).  Here the arguments of a call are kept as raw
-// 8-byte values (Call), and a whole step as a list of them (Program) in which the caller's tensors
-// and the current stream are open places that every run fills in: per run, one check of dtype,
-// shape, contiguity and device per input, then the launches, with the interpreter lock released.
+// 8-byte values (Call), and a whole step as a list of them (Program) in which the caller's tensors, the
+// pass's own buffers and the current stream are open places that every run fills in: per run, one check of
+// dtype, shape, contiguity and device per tensor, one comparison per other attribute of the pass, then the
+// launches, with the interpreter lock released.  Tensors are read through torch's C++ interface (a few ns
+// each; five attribute reads through Python objects were 0.3 us).
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <structmember.h>
 
 #include <hip/hip_runtime_api.h>
+#include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
 #include <cstring>
@@ -75,7 +78,6 @@ const Entry kEntries[] = {
 PyObject* g_on_error = nullptr;      // called with the return code of a failing C call; raises
 PyObject* g_device = nullptr;        // () -> current device index
 PyObject* g_raw_stream = nullptr;    // (device index) -> current stream of the device
-PyObject *s_dtype, *s_shape, *s_is_contiguous, *s_is_cuda, *s_data_ptr;
 
 constexpr int kNoSlot = -2, kStreamSlot = -1;
 
@@ -88,10 +90,10 @@ struct Op {
   int nargs = 0;
   bool open = false;                  // some argument is filled in per run
   Value args[kMaxArgs];
-  int8_t slot[kMaxArgs];              // kNoSlot | kStreamSlot | index of an input (args[] then holds the byte offset)
+  int16_t slot[kMaxArgs];             // kNoSlot | kStreamSlot | index of a tensor (args[] then holds the byte offset)
 };
 
-// base[i]: address of input i; stream: what kStreamSlot stands for
+// base[i]: address of tensor i; stream: what kStreamSlot stands for
 int issue(const Op& op, const Value* base, void* stream) {
   Value local[kMaxArgs];
   const Value* v = op.args;
@@ -118,7 +120,7 @@ PyObject* raise_code(int rc) {
   return nullptr;
 }
 
-// An argument as the binding hands it over: None, a number, or (input index, byte offset) for a place
+// An argument as the binding hands it over: None, a number, or (tensor index, byte offset) for a place
 // that is filled in per run ((-1, 0) = the current stream).
 bool parse_arg(PyObject* o, char kind, Op& op, int i) {
   op.args[i].raw = 0;
@@ -127,7 +129,7 @@ bool parse_arg(PyObject* o, char kind, Op& op, int i) {
   if (PyTuple_Check(o)) {
     const long idx = PyLong_AsLong(PyTuple_GET_ITEM(o, 0));
     op.args[i].l = PyLong_AsLongLong(PyTuple_GET_ITEM(o, 1));
-    op.slot[i] = (int8_t)idx;
+    op.slot[i] = (int16_t)idx;
     op.open = true;
   } else if (kind == 'f') {
     op.args[i].f = (float)PyFloat_AsDouble(o);
@@ -255,48 +257,110 @@ PyObject* event_op(PyObject*, PyObject* a) {
 }
 
 // ---- Program: a step --------------------------------------------------------------------------
-struct Input {
-  PyObject* dtype = nullptr;    // nullptr: the input is absent (None)
-  PyObject* shape = nullptr;
+// What a tensor has to be for the recorded launches to hold for it.
+struct TensorSpec {
+  bool absent = false;          // None
+  at::ScalarType dtype = at::kFloat;
+  std::vector<int64_t> shape;
+};
+
+// What a step depends on beside its inputs: the attributes of its owner (object 0) and of the passes inside it
+// (object k, found from object `of`, which comes before it).  `index` >= 0: element of the list `name` holds.
+struct Place {
+  enum What : uint8_t {
+    kObject,      // the next object: of exactly the type `value`
+    kTensor,      // an open place: the next slot
+    kConstant,    // equal to `value`
+    kLength       // a list or tuple of `index` elements
+  } what = kConstant;
+  int of = 0;
+  PyObject* name = nullptr;
+  Py_ssize_t index = -1;
+  PyObject* value = nullptr;
+  TensorSpec tensor;
 };
 
 struct ProgramObject {
   PyObject_HEAD
   vectorcallfunc vectorcall;
   std::vector<const Op*>* ops;
-  std::vector<Input>* inputs;
+  std::vector<TensorSpec>* inputs;
+  std::vector<Place>* places;
   PyObject* keep;               // the Call objects
-  bool open;                    // some op names the current stream or an input
+  long runs;                    // steps issued
+  size_t slots, objects;
+  bool owned;                   // called with the owner of the places in front of the inputs
+  bool open;                    // some op names the current stream or a tensor
+  bool part;                    // of a step being recorded: its calls name tensors of the program it goes into
 };
+constexpr size_t kMaxSlots = 512, kMaxObjects = 16;
 
 PyTypeObject ProgramType = {PyVarObject_HEAD_INIT(nullptr, 0)};
 
-// 1: as recorded, address in *out; 0: something else; -1: error
-int match(const Input& in, PyObject* t, Value* out) {
+// true: as recorded, address in *out.  Exactly torch's own tensor types: what a subclass makes of its
+// attributes is not read here (such a step goes call by call).
+bool match(const TensorSpec& spec, PyObject* o, Value* out) {
   out->raw = 0;
-  if (in.dtype == nullptr) return t == Py_None;
-  if (t == Py_None) return 0;
-  PyObject* o = PyObject_GetAttr(t, s_dtype);
-  if (o == nullptr) return -1;
-  bool ok = o == in.dtype;
-  Py_DECREF(o);
-  if (!ok) return 0;
-  if ((o = PyObject_GetAttr(t, s_shape)) == nullptr) return -1;
-  const int eq = PyObject_RichCompareBool(o, in.shape, Py_EQ);
-  Py_DECREF(o);
-  if (eq <= 0) return eq;
-  if ((o = PyObject_GetAttr(t, s_is_cuda)) == nullptr) return -1;
-  ok = o == Py_True;
-  Py_DECREF(o);
-  if (!ok) return 0;
-  if ((o = PyObject_CallMethodNoArgs(t, s_is_contiguous)) == nullptr) return -1;
-  ok = o == Py_True;
-  Py_DECREF(o);
-  if (!ok) return 0;
-  if ((o = PyObject_CallMethodNoArgs(t, s_data_ptr)) == nullptr) return -1;
-  out->z = PyLong_AsSize_t(o);
-  Py_DECREF(o);
-  return PyErr_Occurred() ? -1 : 1;
+  if (spec.absent) return o == Py_None;
+  if (!THPVariable_CheckExact(o)) return false;
+  try {
+    const at::Tensor& t = THPVariable_Unpack(o);
+    if (!t.is_cuda() || t.scalar_type() != spec.dtype || t.sizes() != at::IntArrayRef(spec.shape) || !t.is_contiguous()) return false;
+    out->p = t.data_ptr();
+    return true;
+  } catch (...) {               // a tensor without memory of its own: the call-by-call path says so
+    return false;
+  }
+}
+
+// The attribute (or list element) a place names, borrowed; nullptr when it is not there.
+PyObject* look_up(const Place& p, PyObject* const* dicts) {
+  PyObject* v = PyDict_GetItemWithError(dicts[p.of], p.name);
+  if (v == nullptr || p.index < 0 || p.what == Place::kLength) return v;
+  if (PyList_CheckExact(v)) return p.index < PyList_GET_SIZE(v) ? PyList_GET_ITEM(v, p.index) : nullptr;
+  if (PyTuple_CheckExact(v)) return p.index < PyTuple_GET_SIZE(v) ? PyTuple_GET_ITEM(v, p.index) : nullptr;
+  return nullptr;
+}
+
+// The owner's state against the recording; fills the slots from `slot` on, whose tensors `held` then holds.
+bool match_places(const ProgramObject* self, PyObject* owner, Value* base, size_t slot, std::vector<PyObject*>& held) {
+  PyObject* dicts[kMaxObjects];
+  size_t n = 0;
+  auto enter = [&](PyObject* o) {                    // (the object keeps its dict alive, its holder the object)
+    PyObject* d = PyObject_GenericGetDict(o, nullptr);
+    if (d == nullptr) return false;
+    dicts[n++] = d;
+    Py_DECREF(d);
+    return true;
+  };
+  if (!enter(owner)) return false;
+  for (const Place& p : *self->places) {
+    PyObject* v = look_up(p, dicts);
+    if (v == nullptr) return false;
+    switch (p.what) {
+      case Place::kObject:
+        if ((PyObject*)Py_TYPE(v) != p.value || !enter(v)) return false;
+        break;
+      case Place::kTensor:
+        if (!match(p.tensor, v, &base[slot++])) return false;
+        Py_INCREF(v);                                // a program's thread may replace it while the launches go out
+        held.push_back(v);
+        break;
+      case Place::kConstant:
+        if (v != p.value) {
+          Py_INCREF(v);
+          const int eq = PyObject_RichCompareBool(v, p.value, Py_EQ);
+          Py_DECREF(v);
+          if (eq != 1) return false;
+        }
+        break;
+      case Place::kLength:
+        if (!(PyList_CheckExact(v) && PyList_GET_SIZE(v) == p.index) && !(PyTuple_CheckExact(v) && PyTuple_GET_SIZE(v) == p.index))
+          return false;
+        break;
+    }
+  }
+  return true;
 }
 
 void* current_stream() {
@@ -310,26 +374,40 @@ void* current_stream() {
   return p;
 }
 
-// program(*inputs) -> True when the step was issued, False when the inputs are not those it was recorded for
+// program([owner,] *inputs) -> True when the step was issued, False when the inputs or the owner's attributes are
+// not those it was recorded for
 PyObject* program_vectorcall(PyObject* o, PyObject* const* args, size_t nargsf, PyObject* kwnames) {
   ProgramObject* self = (ProgramObject*)o;
-  const size_t n = (size_t)PyVectorcall_NARGS(nargsf);
-  constexpr size_t kMaxInputs = 64;
+  const size_t n = (size_t)PyVectorcall_NARGS(nargsf), first = self->owned ? 1 : 0;
   if (kwnames != nullptr && PyTuple_GET_SIZE(kwnames) != 0) {
     PyErr_SetString(PyExc_TypeError, "a program takes positional inputs");
     return nullptr;
   }
-  if (n != self->inputs->size() || n > kMaxInputs) Py_RETURN_FALSE;
-  Value base[kMaxInputs];
-  for (size_t i = 0; i < n; ++i) {
-    const int m = match((*self->inputs)[i], args[i], &base[i]);
-    if (m < 0) return nullptr;
-    if (m == 0) Py_RETURN_FALSE;
+  if (self->part) {
+    PyErr_SetString(PyExc_RuntimeError, "a part of a recorded step runs inside its program only");
+    return nullptr;
+  }
+  if (n != self->inputs->size() + first) Py_RETURN_FALSE;
+  Value base[kMaxSlots];
+  for (size_t i = first; i < n; ++i)
+    if (!match((*self->inputs)[i - first], args[i], &base[i - first])) Py_RETURN_FALSE;
+  std::vector<PyObject*> held;
+  auto release = [&] { for (PyObject* t : held) Py_DECREF(t); };
+  if (self->owned) {
+    held.reserve(self->places->size());
+    if (!match_places(self, args[0], base, n - first, held)) {
+      release();
+      PyErr_Clear();            // an attribute that cannot be compared is one that is not as recorded
+      Py_RETURN_FALSE;
+    }
   }
   void* stream = nullptr;
   if (self->open) {
     stream = current_stream();
-    if (PyErr_Occurred()) return nullptr;
+    if (PyErr_Occurred()) {
+      release();
+      return nullptr;
+    }
   }
   int rc = SPA_OK;
   Py_BEGIN_ALLOW_THREADS
@@ -338,63 +416,125 @@ PyObject* program_vectorcall(PyObject* o, PyObject* const* args, size_t nargsf, 
     if (rc != SPA_OK) break;
   }
   Py_END_ALLOW_THREADS
+  ++self->runs;
+  release();
   if (rc != SPA_OK) return raise_code(rc);
   Py_RETURN_TRUE;
 }
 
-// Program(calls, inputs): calls = Calls and input-less Programs; inputs = (dtype, shape) or None per input
+// None | an example of the tensor (dtype and shape are taken from it)
+bool parse_tensor(PyObject* o, TensorSpec* out) {
+  if (o == Py_None) {
+    out->absent = true;
+    return true;
+  }
+  if (!THPVariable_Check(o)) {
+    PyErr_SetString(PyExc_TypeError, "an input is described by None or a tensor");
+    return false;
+  }
+  try {
+    const at::Tensor& t = THPVariable_Unpack(o);
+    out->dtype = t.scalar_type();
+    out->shape = t.sizes().vec();
+    return true;
+  } catch (...) {
+    PyErr_SetString(PyExc_TypeError, "an input needs a dtype and a shape");
+    return false;
+  }
+}
+
+// (what, object, name, index, value)
+bool parse_place(PyObject* o, Place* out, size_t objects) {
+  const char* what;
+  if (!PyArg_ParseTuple(o, "siUnO", &what, &out->of, &out->name, &out->index, &out->value)) {
+    out->name = out->value = nullptr;
+    return false;
+  }
+  Py_INCREF(out->name);
+  Py_INCREF(out->value);
+  out->what = what[0] == 'o' ? Place::kObject : what[0] == 't' ? Place::kTensor : what[0] == 'l' ? Place::kLength : Place::kConstant;
+  if (out->of < 0 || (size_t)out->of >= objects) {
+    PyErr_SetString(PyExc_ValueError, "a place names an object that comes after it");
+    return false;
+  }
+  return out->what != Place::kTensor || parse_tensor(out->value, &out->tensor);
+}
+
+// Program(calls, inputs, places = None): calls = Calls and input-less Programs; inputs = None or an example tensor per
+// input; places = what the step reads of its owner (None: it has none)
 PyObject* program_new(PyTypeObject* type, PyObject* a, PyObject*) {
-  PyObject *calls, *inputs;
-  if (!PyArg_ParseTuple(a, "O!O!", &PyTuple_Type, &calls, &PyTuple_Type, &inputs)) return nullptr;
+  PyObject *calls, *inputs, *places = Py_None;
+  if (!PyArg_ParseTuple(a, "O!O!|O", &PyTuple_Type, &calls, &PyTuple_Type, &inputs, &places)) return nullptr;
+  if (places != Py_None && !PyTuple_CheckExact(places)) {
+    PyErr_SetString(PyExc_TypeError, "places are a tuple");
+    return nullptr;
+  }
   ProgramObject* self = (ProgramObject*)type->tp_alloc(type, 0);
   if (self == nullptr) return nullptr;
   self->vectorcall = program_vectorcall;
   self->ops = new std::vector<const Op*>;
-  self->inputs = new std::vector<Input>;
+  self->inputs = new std::vector<TensorSpec>;
+  self->places = new std::vector<Place>;
   Py_INCREF(calls);
   self->keep = calls;
+  auto fail = [&]() -> PyObject* {
+    Py_DECREF(self);
+    return nullptr;
+  };
   for (Py_ssize_t i = 0; i < PyTuple_GET_SIZE(calls); ++i) {
     PyObject* c = PyTuple_GET_ITEM(calls, i);
     if (Py_TYPE(c) == &CallType) {
       self->ops->push_back(((CallObject*)c)->op);
-    } else if (Py_TYPE(c) == &ProgramType && ((ProgramObject*)c)->inputs->empty()) {
+    } else if (Py_TYPE(c) == &ProgramType && ((ProgramObject*)c)->inputs->empty() && !((ProgramObject*)c)->owned) {
       for (const Op* op : *((ProgramObject*)c)->ops) self->ops->push_back(op);
     } else {
       PyErr_SetString(PyExc_TypeError, "a program is made of calls");
-      Py_DECREF(self);
-      return nullptr;
+      return fail();
     }
   }
   for (const Op* op : *self->ops) self->open = self->open || op->open;
   for (Py_ssize_t i = 0; i < PyTuple_GET_SIZE(inputs); ++i) {
-    PyObject* s = PyTuple_GET_ITEM(inputs, i);
-    Input in;
-    if (s != Py_None) {
-      in.dtype = PyTuple_GetItem(s, 0);
-      in.shape = in.dtype != nullptr ? PyTuple_GetItem(s, 1) : nullptr;
-      if (in.shape == nullptr) {
-        Py_DECREF(self);
-        return nullptr;
-      }
-      Py_INCREF(in.dtype);
-      Py_INCREF(in.shape);
+    self->inputs->emplace_back();
+    if (!parse_tensor(PyTuple_GET_ITEM(inputs, i), &self->inputs->back())) return fail();
+  }
+  self->slots = self->inputs->size();
+  self->objects = 1;
+  if (places != Py_None) {
+    self->owned = true;
+    for (Py_ssize_t i = 0; i < PyTuple_GET_SIZE(places); ++i) {
+      self->places->emplace_back();
+      if (!parse_place(PyTuple_GET_ITEM(places, i), &self->places->back(), self->objects)) return fail();
+      self->slots += self->places->back().what == Place::kTensor;
+      self->objects += self->places->back().what == Place::kObject;
     }
-    self->inputs->push_back(in);
+  }
+  if (self->slots > kMaxSlots || self->objects > kMaxObjects) {
+    PyErr_SetString(PyExc_ValueError, "too many tensors or passes in a program");
+    return fail();
+  }
+  for (const Op* op : *self->ops)
+    for (int i = 0; i < op->nargs; ++i) self->part = self->part || op->slot[i] >= (int)self->slots;
+  if (self->part && self->slots > 0) {
+    PyErr_SetString(PyExc_ValueError, "a call names a tensor the program does not have");
+    return fail();
   }
   return (PyObject*)self;
 }
 
 void program_dealloc(PyObject* o) {
   ProgramObject* self = (ProgramObject*)o;
-  for (Input& in : *self->inputs) {
-    Py_XDECREF(in.dtype);
-    Py_XDECREF(in.shape);
+  for (Place& p : *self->places) {
+    Py_XDECREF(p.name);
+    Py_XDECREF(p.value);
   }
+  delete self->places;
   delete self->inputs;
   delete self->ops;
   Py_XDECREF(self->keep);
   Py_TYPE(o)->tp_free(o);
 }
+
+PyMemberDef kProgramMembers[] = {{"runs", T_LONG, offsetof(ProgramObject, runs), READONLY, "steps issued"}, {nullptr, 0, 0, 0, nullptr}};
 
 // setup(on_error, current_device, raw_stream)
 PyObject* setup(PyObject*, PyObject* a) {
@@ -430,11 +570,7 @@ bool ready(PyTypeObject& t, const char* name, size_t size, newfunc make, destruc
 }  // namespace
 
 PyMODINIT_FUNC PyInit__launcher(void) {
-  s_dtype = PyUnicode_InternFromString("dtype");
-  s_shape = PyUnicode_InternFromString("shape");
-  s_is_contiguous = PyUnicode_InternFromString("is_contiguous");
-  s_is_cuda = PyUnicode_InternFromString("is_cuda");
-  s_data_ptr = PyUnicode_InternFromString("data_ptr");
+  ProgramType.tp_members = kProgramMembers;
   if (!ready(EventType, "_launcher.Event", sizeof(EventObject), event_new, event_dealloc, 0) ||
       !ready(CallType, "_launcher.Call", sizeof(CallObject), call_new, call_dealloc, offsetof(CallObject, vectorcall)) ||
       !ready(ProgramType, "_launcher.Program", sizeof(ProgramObject), program_new, program_dealloc,

@@ -24,41 +24,51 @@ class _Pass:
     """run(): the step on the caller's tensors, without marshalling them call by call.
 
     The second run on inputs of the same shapes and dtypes records the step once (`spa.record`); from
-    then on a run is one native call that checks the inputs and issues the launches on the current
-    stream.  Inputs the recording does not cover (other shapes, a wrong device or layout) take the
-    stages one by one, checks and errors included.  Assigning an attribute of any pass (a bias, a
-    buffer) drops the recordings made before."""
-    _epoch = 0
+    then on a run is one native call that checks the inputs and the attributes of the pass (and of the
+    passes inside it) and issues the launches on the current stream.  Buffers are taken from the
+    attributes anew on every run.  What the recording does not cover (other shapes, a wrong device or
+    layout, an attribute that changed) takes the stages one by one, checks and errors included."""
+    _plan, _plans, _plan_seen = None, (), None
+    _plan_pause, _plan_pauses = 0, 0                # runs without a try at recording: left, after the next useless one
 
-    def __setattr__(self, name, value):
-        if name in self.__dict__ and name[:5] != "_plan":
-            _Pass._epoch += 1
-        object.__setattr__(self, name, value)
+    def __getstate__(self):                         # copies and pickles of a pass are without its recordings
+        return {name: v for name, v in vars(self).items() if not name.startswith("_plan")}
 
-    _plan, _plans, _plan_epoch, _plan_seen = None, (), -1, None
+    def _steps(self, *inputs):
+        return self.stages(*inputs)
 
-    def _issue(self, stages, *inputs):
+    def _issue(self, *inputs):
         plan = self._plan
-        if plan is None or self._plan_epoch != _Pass._epoch or not plan(*inputs):
-            self._issue_new(stages, inputs)
+        if plan is None or not plan(self, *inputs):
+            self._issue_new(inputs)
 
-    def _issue_new(self, stages, inputs):
-        if self._plan_epoch != _Pass._epoch:
-            self._plan, self._plans, self._plan_epoch, self._plan_seen = None, (), _Pass._epoch, None
+    def _issue_new(self, inputs):
         for plan in self._plans:
-            if plan(*inputs):
+            if plan is not self._plan and plan(self, *inputs):
                 self._plan = plan
                 return
         seen = [None if t is None else (t.shape, t.dtype) for t in inputs]
         # (a recording takes contiguous device tensors only: rows inside a wider buffer go stage by stage)
         if seen == self._plan_seen and all(t is None or (t.is_cuda and t.is_contiguous()) for t in inputs):
-            plan = spa.record(stages, inputs)
-            if plan(*inputs):
-                self._plan, self._plans = plan, (plan, *self._plans[:3])
+            if self._plan_pause > 0:
+                self._plan_pause -= 1
+            elif self._record(inputs):
                 return
         self._plan_seen = seen
-        for _, fn in stages(*inputs):
+        for _, fn in self._steps(*inputs):
             fn()
+
+    def _record(self, inputs):
+        # a recording that served no run but its own: what it depends on changes from run to run, and recording
+        # costs as much as the stages; fewer and fewer tries then
+        useless = bool(self._plans) and self._plans[0].runs < 2
+        plan = spa.record(self, inputs, _Pass)
+        issued = plan is not None and plan(self, *inputs)
+        self._plan_pauses = min(64, 2 * self._plan_pauses + 1) if useless or not issued else 0
+        self._plan_pause = self._plan_pauses
+        if issued:
+            self._plan, self._plans = plan, (plan, *self._plans[:3])
+        return issued
 
 
 class ForwardPass(_Pass):
@@ -156,7 +166,7 @@ class ForwardPass(_Pass):
         ]
 
     def run(self, x, w, qkv, s_up=None, base=None):
-        self._issue(self.stages, x, w, qkv, s_up, base)
+        self._issue(x, w, qkv, s_up, base)
         return self.y
 
 
@@ -296,7 +306,7 @@ class TrainPass(_Pass):
         ]
 
     def run(self, x, w, qk, labels, dy):
-        self._issue(self.stages, x, w, qk, labels, dy)
+        self._issue(x, w, qk, labels, dy)
         return self.loss
 
 
@@ -349,7 +359,7 @@ class BlockPass(_Pass):
         ])
 
     def run(self, x, w, W_qkv, b_qkv, W_o, b_o):
-        self._issue(self.stages, x, w, W_qkv, b_qkv, W_o, b_o)
+        self._issue(x, w, W_qkv, b_qkv, W_o, b_o)
         return x if self.in_place else self.y
 
 
@@ -468,7 +478,7 @@ class BlockTrainPass(_Pass):
         ] + ([("join_streams", join)] if self.overlap else [])
 
     def run(self, x, w, W_qkv, b_qkv, W_o, b_o, labels, dy):
-        self._issue(self.stages, x, w, W_qkv, b_qkv, W_o, b_o, labels, dy)
+        self._issue(x, w, W_qkv, b_qkv, W_o, b_o, labels, dy)
         return self.loss
 
 
@@ -531,7 +541,7 @@ class ContainerForwardPass(_Pass):
         ]
 
     def run(self, x, w, qkv, base=None):
-        self._issue(self.stages, x, w, qkv, base)
+        self._issue(x, w, qkv, base)
         return self.y
 
 
@@ -615,10 +625,13 @@ class HierarchyPass(_Pass):
                 *([("pack", spa.group(*packs))] if packs else []),
                 ("attention_unpack", spa.group(*(st[-1][1] for st in per_stage)))]
 
+    def _steps(self, *t):
+        n = len(self.cfg)
+        return self.stages(t[:n], t[n:2 * n], t[2 * n:3 * n], t[3 * n:] or None)
+
     def run(self, xs, ws, qkvs, bases=None):
         n = len(self.cfg)
-        self._issue(lambda *t: self.stages(t[:n], t[n:2 * n], t[2 * n:3 * n], t[3 * n:] or None), *xs[:n], *ws[:n],
-                    *qkvs[:n], *(() if bases is None else bases[:n]))
+        self._issue(*xs[:n], *ws[:n], *qkvs[:n], *(() if bases is None else bases[:n]))
         return [fp.y for fp in self.passes]
 
 
@@ -660,8 +673,11 @@ class HierarchyTrainPass(_Pass):
         n_fwd = [3 if tp.pack_pair else 4 for tp in self.passes]      # gate, pack (one or two launches), attention + scatter
         return [c for st, n in zip(chains, n_fwd) for c in st[:n]] + [c for st, n in zip(chains, n_fwd) for c in st[n:]]
 
+    def _steps(self, *t):
+        n = len(self.cfg)
+        return self.stages(*(t[i * n:(i + 1) * n] for i in range(5)))
+
     def run(self, xs, ws, qks, labels, dys):
         n = len(self.cfg)
-        self._issue(lambda *t: self.stages(*(t[i * n:(i + 1) * n] for i in range(5))), *xs[:n], *ws[:n], *qks[:n],
-                    *labels[:n], *dys[:n])
+        self._issue(*xs[:n], *ws[:n], *qks[:n], *labels[:n], *dys[:n])
         return [tp.loss for tp in self.passes]

@@ -6,10 +6,11 @@ shared library is missing, importing this module raises.
 
 A call made with prepare=True comes back as a native object (`_launcher.Call`, csrc/launcher.cpp)
 that issues the call again with no marshalling; `record` turns a whole step into one such object
-whose inputs and stream are filled in per run.
+whose inputs, buffers and stream are filled in per run.
 """
 from __future__ import annotations
 
+import copy
 import ctypes
 import os
 import threading
@@ -148,7 +149,7 @@ def _dispatch(fn, args, keep, prepare):
 
 
 class _Recording(threading.local):
-    """The step being recorded on this thread: its inputs (meta tensors, by storage) and the stream
+    """The step being recorded on this thread: its tensors (meta tensors, by storage) and the stream
     that stands for the current one."""
     slots = None
     stream = None
@@ -200,19 +201,65 @@ def chain(*calls):
     return _launcher.Program(calls, ())
 
 
-def record(stages, inputs):
-    """The step that `stages(*inputs)` lists, as a program: `program(*inputs)` issues it on the stream
-    that is current then, for any contiguous device tensors of the same shapes and dtypes (None where an
-    input was None), and returns True; for anything else it issues nothing and returns False."""
-    meta = [None if t is None else torch.empty(t.shape, dtype=t.dtype, device="meta") for t in inputs]
+class _StandIns:
+    """Stand-ins of a pass and of the passes inside it: the same attributes, with a meta tensor for every tensor.
+    `places` lists what was read of them, in the order the program reads it again on every run."""
+
+    def __init__(self, nested):
+        self.nested, self.places, self.made, self.tensors = nested, [], [], []
+
+    def tensor(self, t):
+        self.tensors.append(None if t is None else torch.empty(t.shape, dtype=t.dtype, device="meta"))
+        return self.tensors[-1]
+
+    def make(self, obj):
+        number, new = len(self.made), object.__new__(type(obj))
+        self.made.append((new, obj))
+        for name, v in list(vars(obj).items()):
+            if not name.startswith("_plan"):
+                new.__dict__[name] = self._value(v, number, name)
+        return new
+
+    def _value(self, v, number, name, index=-1):
+        if isinstance(v, torch.Tensor):
+            if not (v.is_cuda and v.is_contiguous()):
+                raise ValueError(f"{name} is not a contiguous device tensor")
+            meta = self.tensor(v)
+            self.places.append(("tensor", number, name, index, meta))
+            return meta
+        if isinstance(v, self.nested):
+            self.places.append(("object", number, name, index, type(v)))
+            return self.make(v)
+        if type(v) in (list, tuple) and index < 0 and any(isinstance(e, (torch.Tensor, self.nested)) for e in v):
+            self.places.append(("length", number, name, len(v), None))
+            return type(v)([self._value(e, number, name, i) for i, e in enumerate(v)])
+        self.places.append(("constant", number, name, index, copy.copy(v) if type(v) in (list, dict, set) else v))
+        return v
+
+    def as_made(self):
+        """No attribute was added by the steps (a buffer made on first use belongs to the pass itself)."""
+        return all(set(vars(new)) == {n for n in vars(obj) if not n.startswith("_plan")} for new, obj in self.made)
+
+
+def record(owner, inputs, nested):
+    """The step that `owner._steps(*inputs)` lists, as a program: `program(owner, *inputs)` issues it on the stream
+    that is current then and returns True, for any contiguous device tensors of the same shapes and dtypes (None where
+    an input was None).  What the step reads of its owner and of the passes inside it (instances of `nested`) is read
+    again on every run: tensors by address, everything else compared.  For anything else it issues nothing and returns
+    False.  None when the step cannot be recorded."""
+    st = _StandIns(nested)
+    meta = [st.tensor(t) for t in inputs]
     saved = _recording.slots, _recording.stream
-    _recording.slots = {t.untyped_storage()._cdata: i for i, t in enumerate(meta) if t is not None}
-    _recording.stream = torch.cuda.current_stream().cuda_stream
     try:
-        calls = tuple(call for _, call in stages(*meta))
+        stand_in = st.make(owner)
+        _recording.slots = {t.untyped_storage()._cdata: i for i, t in enumerate(st.tensors) if t is not None}
+        _recording.stream = torch.cuda.current_stream().cuda_stream
+        calls = tuple(call for _, call in stand_in._steps(*meta))
+        return _launcher.Program(calls, tuple(meta), tuple(st.places)) if st.as_made() else None
+    except Exception:           # whatever is wrong with it: issued call by call, the step says so itself
+        return None
     finally:
         _recording.slots, _recording.stream = saved
-    return _launcher.Program(calls, tuple(None if t is None else (t.dtype, t.shape) for t in meta))
 
 
 def dtype_code(t: torch.Tensor) -> int:

@@ -1,7 +1,10 @@
 """run() replays a recorded step from the second run on: every run on new tensors, on another
 stream, after an attribute changed or with other optional inputs must give what the stages issued
 one by one give, bit for bit, and refuse what they refuse."""
+import copy
 import dataclasses
+import gc
+import weakref
 
 import pytest
 import torch
@@ -106,3 +109,142 @@ def test_rows_inside_a_wider_buffer_are_not_recorded(pipeline, monkeypatch, form
         assert torch.equal(p.run(x, w, qkv), ref.y)
     assert len(made) == 1
     assert torch.equal(p.run(x, w, wide[..., :3 * WL.C]), ref.y) and len(made) == 1
+
+
+@pytest.fixture
+def recordings(pipeline, monkeypatch):
+    """The recordings made while the test runs."""
+    made, record = [], pipeline.spa.record
+    monkeypatch.setattr(pipeline.spa, "record", lambda *a: made.append(record(*a)) or made[-1])
+    return made
+
+
+def _hierarchy(pipeline, train):
+    """Two stages and their inputs per seed."""
+    cfg = [(2, 8, 12, 64, 2, "bf16", 0.5, 0.0), (2, 4, 6, 128, 4, "bf16", 0.5, 0.1)]
+
+    def inputs(seed):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(seed)
+        rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
+        cols = []
+        for B, h, w, C, H, *_ in cfg:
+            N = h * w
+            col = (rnd(B, N, C), rnd(C) / C ** 0.5, rnd(B, N, (2 if train else 3) * C))
+            cols.append(col + ((rnd(B, N) > 0).to(torch.uint8), rnd(B, N, C)) if train else col)
+        return [list(c) for c in zip(*cols)]
+    make = (lambda: pipeline.HierarchyTrainPass(cfg)) if train else (lambda: pipeline.HierarchyPass(cfg))
+    return make, inputs
+
+
+def test_attributes_of_one_pass_leave_the_others_recorded(pipeline, recordings):
+    a, b = _make(pipeline, "forward"), _make(pipeline, "forward")
+    ins = _inputs("forward", 1)
+    for _ in range(2):
+        a.run(*ins)
+        b.run(*ins)
+    assert len(recordings) == 2
+    for i in range(4):
+        b.note = i
+        b.lse = torch.zeros_like(b.lse)
+        a.run(*ins)
+    assert len(recordings) == 2 and recordings[0].runs == 5
+
+
+@pytest.mark.parametrize("how", ["attribute", "data", "set_"])
+def test_a_replaced_buffer_is_written(pipeline, recordings, how):
+    """y under another name, in other memory: the attribute assigned, its data assigned, its storage set."""
+    p, ref = _make(pipeline, "forward"), _make(pipeline, "forward")
+    for i in range(6):
+        ins = _inputs("forward", 60 + i)
+        if i == 3:
+            old, new = p.y.detach(), torch.empty_like(p.y)
+            kept = old.clone()
+            if how == "attribute":
+                p.y = new
+            elif how == "data":
+                old = p.y.data
+                p.y.data = new
+            else:
+                p.y.set_(new.untyped_storage(), 0, new.shape, new.stride())
+            assert p.y.data_ptr() == new.data_ptr()
+        y = p.run(*ins)
+        for _, fn in ref.stages(*ins):
+            fn()
+        torch.cuda.synchronize()
+        assert y is p.y and torch.equal(y, ref.y)
+    assert torch.equal(old, kept) and len(recordings) == 1      # other memory is no reason to record again
+
+
+def test_a_buffer_of_another_shape_takes_the_stages(pipeline):
+    p = _make(pipeline, "forward")
+    ins = _inputs("forward", 2)
+    for _ in range(3):
+        y = p.run(*ins).clone()
+    p.y = torch.empty(1, dtype=torch.bfloat16, device="cuda")
+    for _ in range(2):
+        with pytest.raises((ValueError, TypeError)):
+            p.run(*ins)
+    p.y = torch.empty_like(y)
+    assert torch.equal(p.run(*ins), y)
+
+
+@pytest.mark.parametrize("train", [False, True])
+def test_a_replaced_stage_of_a_hierarchy_is_run(pipeline, recordings, train):
+    make, inputs = _hierarchy(pipeline, train)
+    p, ref = make(), make()
+    for i in range(8):
+        ins = inputs(i)
+        if i == 3:
+            old = p.passes[1]
+            p.passes[1] = make().passes[1]
+            before = old.y.clone()
+        if i == 5 and not train:
+            p.s_up[1] = torch.full_like(p.s_up[1], float("nan"))
+        if i == 6:
+            p.passes[0].scores = torch.empty_like(p.passes[0].scores)
+            p.passes[1].container_len = 0
+        got = p.run(*ins)
+        for _, fn in ref.stages(*ins):
+            fn()
+        torch.cuda.synchronize()
+        assert all(a is (q.loss if train else q.y) for a, q in zip(got, p.passes))
+        for q, r in zip(p.passes, ref.passes):
+            for name in ("y", "scores", "mask", "cu_seqlens") + (("dx", "dqk", "dw", "db", "loss") if train else ()):
+                assert torch.equal(getattr(q, name), getattr(r, name)), (i, name)
+        if not train:
+            assert torch.equal(p.s_up[1], ref.s_up[1])
+        if i >= 3:
+            assert torch.equal(old.y, before)
+    assert recordings[0].runs >= 4
+
+
+def test_what_changes_on_every_run_is_not_recorded_on_every_run(pipeline, recordings):
+    p = _make(pipeline, "forward")
+    ins = _inputs("forward", 4)
+    want = p.run(*ins).clone()
+    for i in range(40):
+        p.note = object()
+        p.y.zero_()
+        assert torch.equal(p.run(*ins), want)
+    assert len(recordings) <= 6
+    for _ in range(80):                                  # and once it stays as it is the step is recorded
+        p.run(*ins)
+    assert recordings[-1].runs >= 2
+
+
+def test_recordings_hold_nothing_alive(pipeline):
+    make, inputs = _hierarchy(pipeline, True)
+    p, q = make(), _make(pipeline, "forward")
+    for _ in range(3):
+        p.run(*inputs(0))
+        q.run(*_inputs("forward", 0))
+    refs = [weakref.ref(o) for o in (p, p.passes[1], p.passes[1].y, q, q.y)]
+    dup = copy.deepcopy(q)                               # (a copy starts without recordings)
+    assert dup._plan is None and torch.equal(dup.run(*_inputs("forward", 0)), q.y)
+    gc.disable()
+    try:
+        del p, q
+        assert all(r() is None for r in refs)
+    finally:
+        gc.enable()
