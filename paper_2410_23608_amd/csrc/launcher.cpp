@@ -90,10 +90,10 @@ struct Op {
   int nargs = 0;
   bool open = false;                  // some argument is filled in per run
   Value args[kMaxArgs];
-  int16_t slot[kMaxArgs];             // kNoSlot | kStreamSlot | index of a tensor (args[] then holds the byte offset)
+  int16_t slot[kMaxArgs];             // kNoSlot | kStreamSlot | index of an open place (args[] then holds the byte offset)
 };
 
-// base[i]: address of tensor i; stream: what kStreamSlot stands for
+// base[i]: address (or value) of open place i; stream: what kStreamSlot stands for
 int issue(const Op& op, const Value* base, void* stream) {
   Value local[kMaxArgs];
   const Value* v = op.args;
@@ -120,8 +120,8 @@ PyObject* raise_code(int rc) {
   return nullptr;
 }
 
-// An argument as the binding hands it over: None, a number, or (tensor index, byte offset) for a place
-// that is filled in per run ((-1, 0) = the current stream).
+// An argument as the binding hands it over: None, a number, or (index, byte offset) for a place
+// that is filled in per run ((-1, 0) = the current stream; a number of the pass: (index, 0))
 bool parse_arg(PyObject* o, char kind, Op& op, int i) {
   op.args[i].raw = 0;
   op.slot[i] = kNoSlot;
@@ -270,6 +270,7 @@ struct Place {
   enum What : uint8_t {
     kObject,      // the next object: of exactly the type `value`
     kTensor,      // an open place: the next slot
+    kNumber,      // likewise, a float argument of the calls
     kConstant,    // equal to `value`
     kLength       // a list or tuple of `index` elements
   } what = kConstant;
@@ -346,6 +347,14 @@ bool match_places(const ProgramObject* self, PyObject* owner, Value* base, size_
         Py_INCREF(v);                                // a program's thread may replace it while the launches go out
         held.push_back(v);
         break;
+      case Place::kNumber: {
+        if (!PyFloat_CheckExact(v) && !PyLong_CheckExact(v)) return false;
+        const double d = PyFloat_AsDouble(v);
+        if (d == -1.0 && PyErr_Occurred()) return false;
+        base[slot].raw = 0;
+        base[slot++].f = (float)d;
+        break;
+      }
       case Place::kConstant:
         if (v != p.value) {
           Py_INCREF(v);
@@ -452,7 +461,7 @@ bool parse_place(PyObject* o, Place* out, size_t objects) {
   }
   Py_INCREF(out->name);
   Py_INCREF(out->value);
-  out->what = what[0] == 'o' ? Place::kObject : what[0] == 't' ? Place::kTensor : what[0] == 'l' ? Place::kLength : Place::kConstant;
+  out->what = what[0] == 'o' ? Place::kObject : what[0] == 't' ? Place::kTensor : what[0] == 'n' ? Place::kNumber : what[0] == 'l' ? Place::kLength : Place::kConstant;
   if (out->of < 0 || (size_t)out->of >= objects) {
     PyErr_SetString(PyExc_ValueError, "a place names an object that comes after it");
     return false;
@@ -504,7 +513,7 @@ PyObject* program_new(PyTypeObject* type, PyObject* a, PyObject*) {
     for (Py_ssize_t i = 0; i < PyTuple_GET_SIZE(places); ++i) {
       self->places->emplace_back();
       if (!parse_place(PyTuple_GET_ITEM(places, i), &self->places->back(), self->objects)) return fail();
-      self->slots += self->places->back().what == Place::kTensor;
+      self->slots += self->places->back().what == Place::kTensor || self->places->back().what == Place::kNumber;
       self->objects += self->places->back().what == Place::kObject;
     }
   }

@@ -25,9 +25,11 @@ class _Pass:
 
     The second run on inputs of the same shapes and dtypes records the step once (`spa.record`); from
     then on a run is one native call that checks the inputs and the attributes of the pass (and of the
-    passes inside it) and issues the launches on the current stream.  Buffers are taken from the
-    attributes anew on every run.  What the recording does not cover (other shapes, a wrong device or
+    passes inside it) and issues the launches on the current stream.  Buffers and the numbers of
+    _numbers are taken from the attributes anew on every run (a learned bias changes with every step of a
+    training program).  What the recording does not cover (other shapes, a wrong device or
     layout, an attribute that changed) takes the stages one by one, checks and errors included."""
+    _numbers = ("tau", "bias", "loss_scale")
     _plan, _plans, _plan_seen = None, (), None
     _plan_pause, _plan_pauses = 0, 0                # runs without a try at recording: left, after the next useless one
 
@@ -62,7 +64,7 @@ class _Pass:
         # a recording that served no run but its own: what it depends on changes from run to run, and recording
         # costs as much as the stages; fewer and fewer tries then
         useless = bool(self._plans) and self._plans[0].runs < 2
-        plan = spa.record(self, inputs, _Pass)
+        plan = spa.record(self, inputs, _Pass, self._numbers)
         issued = plan is not None and plan(self, *inputs)
         self._plan_pauses = min(64, 2 * self._plan_pauses + 1) if useless or not issued else 0
         self._plan_pause = self._plan_pauses

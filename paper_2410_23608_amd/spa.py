@@ -181,6 +181,17 @@ def _stream():
     return _stream_ref(torch.cuda.current_stream())
 
 
+class _Number:
+    """A number of the pass whose step is being recorded: an open place of the calls it is given to."""
+
+    def __init__(self, slot):
+        self.slot = slot
+
+
+def _num(v):
+    return (v.slot, 0) if type(v) is _Number else float(v)
+
+
 class Event:
     """Orders prepared work on different streams: `record(stream)` and `wait(stream)` are prepared
     operations, issued when called or in their place in a `chain` / recorded step."""
@@ -205,12 +216,12 @@ class _StandIns:
     """Stand-ins of a pass and of the passes inside it: the same attributes, with a meta tensor for every tensor.
     `places` lists what was read of them, in the order the program reads it again on every run."""
 
-    def __init__(self, nested):
-        self.nested, self.places, self.made, self.tensors = nested, [], [], []
+    def __init__(self, nested, numbers):
+        self.nested, self.numbers, self.places, self.made, self.slots = nested, numbers, [], [], []
 
     def tensor(self, t):
-        self.tensors.append(None if t is None else torch.empty(t.shape, dtype=t.dtype, device="meta"))
-        return self.tensors[-1]
+        self.slots.append(None if t is None else torch.empty(t.shape, dtype=t.dtype, device="meta"))
+        return self.slots[-1]
 
     def make(self, obj):
         number, new = len(self.made), object.__new__(type(obj))
@@ -227,6 +238,10 @@ class _StandIns:
             meta = self.tensor(v)
             self.places.append(("tensor", number, name, index, meta))
             return meta
+        if name in self.numbers and type(v) in (int, float):
+            self.slots.append(None)
+            self.places.append(("number", number, name, index, None))
+            return _Number(len(self.slots) - 1)
         if isinstance(v, self.nested):
             self.places.append(("object", number, name, index, type(v)))
             return self.make(v)
@@ -241,18 +256,19 @@ class _StandIns:
         return all(set(vars(new)) == {n for n in vars(obj) if not n.startswith("_plan")} for new, obj in self.made)
 
 
-def record(owner, inputs, nested):
+def record(owner, inputs, nested, numbers=()):
     """The step that `owner._steps(*inputs)` lists, as a program: `program(owner, *inputs)` issues it on the stream
     that is current then and returns True, for any contiguous device tensors of the same shapes and dtypes (None where
     an input was None).  What the step reads of its owner and of the passes inside it (instances of `nested`) is read
-    again on every run: tensors by address, everything else compared.  For anything else it issues nothing and returns
-    False.  None when the step cannot be recorded."""
-    st = _StandIns(nested)
+    again on every run: tensors by address, the attributes named in `numbers` (floats that only reach the calls) by value,
+    everything else compared.  For anything else it issues nothing and returns False.  None when the step cannot be
+    recorded."""
+    st = _StandIns(nested, numbers)
     meta = [st.tensor(t) for t in inputs]
     saved = _recording.slots, _recording.stream
     try:
         stand_in = st.make(owner)
-        _recording.slots = {t.untyped_storage()._cdata: i for i, t in enumerate(st.tensors) if t is not None}
+        _recording.slots = {t.untyped_storage()._cdata: i for i, t in enumerate(st.slots) if t is not None}
         _recording.stream = torch.cuda.current_stream().cuda_stream
         calls = tuple(call for _, call in stand_in._steps(*meta))
         return _launcher.Program(calls, tuple(meta), tuple(st.places)) if st.as_made() else None
@@ -368,7 +384,7 @@ def spa_gate_select(x, w, bias, s_up, tau, scores, mask, counts=None, prepare=Fa
     B, N, C, code = _gate_select_checks("spa_gate_select", x, w, s_up, None, scores, mask, counts)
     _keep = (x, w, s_up, scores, mask, counts,)
     _contig(*_keep)
-    return _dispatch(lib.spa_gate_select, (_ptr(x), _ptr(w), float(bias), _ptr(s_up), float(tau), B, N, C, code,
+    return _dispatch(lib.spa_gate_select, (_ptr(x), _ptr(w), _num(bias), _ptr(s_up), _num(tau), B, N, C, code,
                                _ptr(scores), _ptr(mask), _ptr(counts), _stream(),), _keep, prepare)
 
 
@@ -384,7 +400,7 @@ def spa_gate_select_index(x, w, bias, s_up, tau, scores, mask, counts, cu_seqlen
     _contig(*_keep)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     return _dispatch(lib.spa_gate_select_index,
-                     (_ptr(x), _ptr(w), float(bias), _ptr(s_up), float(tau), B, N, C, code, _ptr(scores), _ptr(mask),
+                     (_ptr(x), _ptr(w), _num(bias), _ptr(s_up), _num(tau), B, N, C, code, _ptr(scores), _ptr(mask),
                       _ptr(counts), _ptr(cu_seqlens), _ptr(gather_idx), _ptr(inv_pos), _ptr(total), _ptr(workspace),
                       ws_bytes, _stream(),), _keep, prepare)
 
@@ -396,7 +412,7 @@ def spa_gate_select_gumbel(x, w, bias, s_up, noise, temperature, tau, scores, ma
     _keep = (x, w, s_up, noise, scores, mask, counts,)
     _contig(*_keep)
     return _dispatch(lib.spa_gate_select_gumbel,
-                     (_ptr(x), _ptr(w), float(bias), _ptr(s_up), _ptr(noise), float(temperature), float(tau), B, N, C,
+                     (_ptr(x), _ptr(w), _num(bias), _ptr(s_up), _ptr(noise), _num(temperature), _num(tau), B, N, C,
                       code, _ptr(scores), _ptr(mask), _ptr(counts), _stream(),), _keep, prepare)
 
 
@@ -413,7 +429,7 @@ def spa_gate_select_pooled(x, w, bias, s_fine, grid_h, grid_w, tau, scores, mask
     _keep = (x, w, s_fine, scores, mask, counts, s_up_pooled,)
     _contig(*_keep)
     return _dispatch(lib.spa_gate_select_pooled,
-                     (_ptr(x), _ptr(w), float(bias), _ptr(s_fine), float(tau), B, int(grid_h), int(grid_w), C,
+                     (_ptr(x), _ptr(w), _num(bias), _ptr(s_fine), _num(tau), B, int(grid_h), int(grid_w), C,
                       code, _ptr(scores), _ptr(mask), _ptr(counts), _ptr(s_up_pooled), _stream(),), _keep, prepare)
 
 
@@ -536,7 +552,7 @@ def _packed_attention(fn, q, k, v, cu_seqlens, B, max_seqlen, H, Dh, out, lse, s
     _contig(out, lse, cu_seqlens)
     return _dispatch(getattr(lib, fn), (_ptr(q), _ptr(k), _ptr(v), _row_stride(q), _row_stride(k), _row_stride(v),
                                         _ptr(cu_seqlens), B, max_seqlen,
-                                        H, Dh, code, float(softmax_scale), _ptr(out), _ptr(lse), _stream(),), _keep, prepare)
+                                        H, Dh, code, _num(softmax_scale), _ptr(out), _ptr(lse), _stream(),), _keep, prepare)
 
 
 def spa_packed_attention(q, k, v, cu_seqlens, B, max_seqlen, H, Dh, out, lse=None, softmax_scale=0.0,
@@ -578,7 +594,7 @@ def spa_packed_attention_unpack(q, k, v, cu_seqlens, gather_idx, inv_pos, base, 
     _contig(cu_seqlens, gather_idx, inv_pos, base, y, out, lse)
     return _dispatch(lib.spa_packed_attention_unpack,
                      (_ptr(q), _ptr(k), _ptr(v), _row_stride(q), _row_stride(k), _row_stride(v), _ptr(cu_seqlens),
-                      _ptr(gather_idx), _ptr(inv_pos), _ptr(base), B, N, H, Dh, code, float(softmax_scale),
+                      _ptr(gather_idx), _ptr(inv_pos), _ptr(base), B, N, H, Dh, code, _num(softmax_scale),
                       _ptr(out), _ptr(lse), _ptr(y), _stream(),), _keep, prepare)
 
 
@@ -594,7 +610,7 @@ def spa_gathered_attention_unpack(q, k, v, cu_seqlens, gather_idx, inv_pos, base
     _contig(cu_seqlens, gather_idx, inv_pos, base, y, out, lse)
     return _dispatch(lib.spa_gathered_attention_unpack,
                      (_ptr(q), _ptr(k), _ptr(v), _row_stride(q), _row_stride(k), _row_stride(v), _ptr(cu_seqlens),
-                      _ptr(gather_idx), _ptr(inv_pos), _ptr(base), B, N, H, Dh, code, float(softmax_scale),
+                      _ptr(gather_idx), _ptr(inv_pos), _ptr(base), B, N, H, Dh, code, _num(softmax_scale),
                       _ptr(out), _ptr(lse), _ptr(y), _stream(),), _keep, prepare)
 
 
@@ -612,7 +628,7 @@ def spa_gated_attention_unpack(q, k, x, scores, cu_seqlens, gather_idx, inv_pos,
     return _dispatch(lib.spa_gated_attention_unpack,
                      (_ptr(q), _ptr(k), _ptr(x), _row_stride(q), _row_stride(k), _row_stride(x), _ptr(scores),
                       _ptr(cu_seqlens), _ptr(gather_idx), _ptr(inv_pos), _ptr(base), B, N, H, Dh, code,
-                      float(softmax_scale), _ptr(out), _ptr(lse), _ptr(y), _stream(),), _keep, prepare)
+                      _num(softmax_scale), _ptr(out), _ptr(lse), _ptr(y), _stream(),), _keep, prepare)
 
 
 def spa_selected_attention_unpack(q, k, v, mask, base, H, Dh, y, softmax_scale=0.0, prepare=False):
@@ -631,7 +647,7 @@ def spa_selected_attention_unpack(q, k, v, mask, base, H, Dh, y, softmax_scale=0
     _contig(mask, base, y)
     return _dispatch(lib.spa_selected_attention_unpack,
                      (_ptr(q), _ptr(k), _ptr(v), _row_stride(q), _row_stride(k), _row_stride(v), _ptr(mask), _ptr(base),
-                      B, N, H, Dh, code, float(softmax_scale), _ptr(y), _stream(),), _keep, prepare)
+                      B, N, H, Dh, code, _num(softmax_scale), _ptr(y), _stream(),), _keep, prepare)
 
 
 def _segment_attention_unpack(fn, gathered, q, k, v, seg_cu_seqlens, max_seqlen, gather_idx, inv_pos, base, H, Dh, y, out,
@@ -646,7 +662,7 @@ def _segment_attention_unpack(fn, gathered, q, k, v, seg_cu_seqlens, max_seqlen,
     return _dispatch(getattr(lib, fn),
                      (_ptr(q), _ptr(k), _ptr(v), _row_stride(q), _row_stride(k), _row_stride(v), _ptr(seg_cu_seqlens),
                       n_segments, int(max_seqlen), _ptr(gather_idx), _ptr(inv_pos), _ptr(base), rows, H, Dh,
-                      code, float(softmax_scale), _ptr(out), _ptr(lse), _ptr(y), _stream(),), _keep, prepare)
+                      code, _num(softmax_scale), _ptr(out), _ptr(lse), _ptr(y), _stream(),), _keep, prepare)
 
 
 def spa_segment_attention_unpack(q, k, v, seg_cu_seqlens, max_seqlen, gather_idx, inv_pos, base, H, Dh, y, out=None,
@@ -841,7 +857,7 @@ def spa_packed_attention_bwd(q, k, v, out, dout, lse, cu_seqlens, B, max_seqlen,
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     return _dispatch(getattr(lib, fn), (_ptr(q), _ptr(k), _ptr(v), _row_stride(q), _row_stride(k), _row_stride(v),
                                         _ptr(out), _ptr(dout), _ptr(lse), _ptr(cu_seqlens), B, max_seqlen, H, Dh,
-                                        code, float(softmax_scale), _ptr(dq), _ptr(dk), _ptr(dv),
+                                        code, _num(softmax_scale), _ptr(dq), _ptr(dk), _ptr(dv),
                                         _row_stride(dq), _row_stride(dk), _row_stride(dv), _ptr(workspace),
                                         ws_bytes, _stream(),), _keep, prepare)
 
@@ -866,7 +882,7 @@ def spa_packed_attention_bwd_tokens(q, k, v, out, dy, lse, cu_seqlens, B, max_se
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     return _dispatch(lib.spa_packed_attention_bwd_tokens,
                      (_ptr(q), _ptr(k), _ptr(v), _row_stride(q), _row_stride(k), _row_stride(v), _ptr(out), _ptr(dy),
-                      _ptr(lse), _ptr(cu_seqlens), B, max_seqlen, H, Dh, code, float(softmax_scale),
+                      _ptr(lse), _ptr(cu_seqlens), B, max_seqlen, H, Dh, code, _num(softmax_scale),
                       _ptr(gather_idx), _ptr(inv_pos), rows, _ptr(dq), _ptr(dk), _ptr(dv), _row_stride(dq),
                       _row_stride(dk), _row_stride(dv), _ptr(workspace), ws_bytes, _stream(),), _keep, prepare)
 
@@ -892,7 +908,7 @@ def spa_gated_attention_bwd_tokens(q, k, x, scores, out, dy, lse, cu_seqlens, B,
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     return _dispatch(getattr(lib, fn),
                      (_ptr(q), _ptr(k), _ptr(x), _row_stride(q), _row_stride(k), _row_stride(x), _ptr(scores), _ptr(out),
-                      _ptr(dy), _ptr(lse), _ptr(cu_seqlens), B, max_seqlen, H, Dh, code, float(softmax_scale),
+                      _ptr(dy), _ptr(lse), _ptr(cu_seqlens), B, max_seqlen, H, Dh, code, _num(softmax_scale),
                       _ptr(gather_idx), _ptr(inv_pos), rows, _ptr(dq), _ptr(dk), _ptr(d_rg), _row_stride(dq),
                       _row_stride(dk), _row_stride(d_rg), _ptr(workspace), ws_bytes, _stream(),), _keep, prepare)
 
@@ -918,8 +934,8 @@ def spa_gate_bwd(x, w, bias, scores, s_up, labels, d_rg, gate_scaled, loss_scale
     _keep = (x, w, scores, s_up, labels, d_rg, loss, dx, dw, db, workspace,)
     _contig(*_keep)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    return _dispatch(lib.spa_gate_bwd, (_ptr(x), _ptr(w), float(bias), _ptr(scores), _ptr(s_up), _ptr(labels), _ptr(d_rg),
-                            int(bool(gate_scaled)), float(loss_scale), B, N, C, code, _ptr(loss), _ptr(dx),
+    return _dispatch(lib.spa_gate_bwd, (_ptr(x), _ptr(w), _num(bias), _ptr(scores), _ptr(s_up), _ptr(labels), _ptr(d_rg),
+                            int(bool(gate_scaled)), _num(loss_scale), B, N, C, code, _ptr(loss), _ptr(dx),
                             _ptr(dw), _ptr(db), _ptr(workspace), ws_bytes, _stream(),), _keep, prepare)
 
 
@@ -932,8 +948,8 @@ def spa_gate_bwd_static(x, w, bias, scores, s_up, labels, d_rg, gate_scaled, los
     _keep = (x, w, scores, s_up, labels, d_rg, loss, dx, dw, db,)
     _contig(*_keep)
     return _dispatch(lib.spa_gate_bwd_static,
-                     (_ptr(x), _ptr(w), float(bias), _ptr(scores), _ptr(s_up), _ptr(labels), _ptr(d_rg),
-                      int(bool(gate_scaled)), float(loss_scale), B, N, C, code, _ptr(loss), _ptr(dx), _ptr(dw),
+                     (_ptr(x), _ptr(w), _num(bias), _ptr(scores), _ptr(s_up), _ptr(labels), _ptr(d_rg),
+                      int(bool(gate_scaled)), _num(loss_scale), B, N, C, code, _ptr(loss), _ptr(dx), _ptr(dw),
                       _ptr(db), _stream(),), _keep, prepare)
 
 
@@ -945,8 +961,8 @@ def spa_gate_bwd_straight_through(x, w, bias, scores, s_up, labels, d_rg, loss_s
     _contig(*_keep)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     return _dispatch(lib.spa_gate_bwd_straight_through,
-                     (_ptr(x), _ptr(w), float(bias), _ptr(scores), _ptr(s_up), _ptr(labels), _ptr(d_rg),
-                      float(loss_scale), _ptr(mask), _ptr(noise), float(temperature), B, N, C, code,
+                     (_ptr(x), _ptr(w), _num(bias), _ptr(scores), _ptr(s_up), _ptr(labels), _ptr(d_rg),
+                      _num(loss_scale), _ptr(mask), _ptr(noise), _num(temperature), B, N, C, code,
                       _ptr(loss), _ptr(dx), _ptr(dw), _ptr(db), _ptr(workspace), ws_bytes, _stream(),), _keep, prepare)
 
 
@@ -961,4 +977,4 @@ def spa_padded_attention(q, k, v, seqlens, B, n_pad, H, Dh, out, softmax_scale=0
     if not (_row_stride(q) == _row_stride(k) == _row_stride(v)):
         raise ValueError("spa_padded_attention takes one row stride for q, k, v")
     return _dispatch(lib.spa_padded_attention, (_ptr(q), _ptr(k), _ptr(v), _row_stride(q), _ptr(seqlens), B, n_pad, H, Dh,
-                                    code, float(softmax_scale), _ptr(out), _stream(),), _keep, prepare)
+                                    code, _num(softmax_scale), _ptr(out), _stream(),), _keep, prepare)

@@ -56,7 +56,7 @@ def test_recorded_runs_equal_stages(pipeline, kind):
     other = torch.cuda.Stream()
     for i in range(6):
         if i == 4:
-            p.bias = ref.bias = 0.75                    # drops the recording
+            p.bias = ref.bias = 0.75
         ins = _inputs(kind, 40 + i)                     # new tensors every time
         torch.cuda.synchronize()
         if i == 3:
@@ -248,3 +248,47 @@ def test_recordings_hold_nothing_alive(pipeline):
         assert all(r() is None for r in refs)
     finally:
         gc.enable()
+
+
+@pytest.mark.parametrize("kind", ["forward", "train", "block", "block_train", "container", "hierarchy", "hierarchy_train"])
+def test_a_bias_that_is_learned_keeps_the_recording(pipeline, recordings, kind):
+    """A new bias before every step, as a training program assigns it, and other thresholds and loss scales: one
+    recording, and what the stages give."""
+    if kind.startswith("hierarchy"):
+        make, inputs = _hierarchy(pipeline, kind == "hierarchy_train")
+    else:
+        make, inputs = lambda: _make(pipeline, kind), lambda seed: _inputs(kind, seed)
+    p, ref = make(), make()
+    for i in range(7):
+        ins = inputs(i)
+        for o in (p, ref):
+            for n, q in enumerate(getattr(o, "passes", [o])):
+                q.bias = [0.0, -0.25, 0.5, 1, -1.0, 0.125, 0][i] + 0.01 * n      # (whole numbers too)
+                q.tau = 0.5 if i < 4 else 0.4
+                if hasattr(q, "loss_scale") and i == 5:
+                    q.loss_scale = 0.02
+        p.run(*ins)
+        for _, fn in ref.stages(*ins):
+            fn()
+        torch.cuda.synchronize()
+        for q, r in zip(getattr(p, "passes", [p]), getattr(ref, "passes", [ref])):
+            assert all(torch.equal(a, b) for a, b in zip(_results(q), _results(r))), i
+    assert len(recordings) == 1 and recordings[0].runs == 6
+
+
+def test_numbers_a_step_refuses(pipeline, recordings):
+    p = _make(pipeline, "forward")
+    ins = _inputs("forward", 1)
+    for _ in range(3):
+        want = p.run(*ins).clone()
+    p.tau = 1.5
+    for _ in range(2):
+        with pytest.raises(pipeline.spa.SpaError):
+            p.run(*ins)
+    p.tau, p.bias = 0.5, None
+    with pytest.raises(TypeError):
+        p.run(*ins)
+    p.bias = torch.zeros((), device="cuda")              # what float() takes, stage by stage
+    assert torch.equal(p.run(*ins), want)
+    p.bias = 0.0
+    assert torch.equal(p.run(*ins), want)
