@@ -12,8 +12,10 @@ means something.
 Prints ONE JSON line: whole-path throughput in selected tokens/s (median over R repeats of the
 timed K-step region), the roofline of the dominant kernel (durations measured live with events
 on the launch stream), the CPU oracle timed on this machine's host cores, and a `configs` block
-with the same measurements for every configuration: ViT-S-shaped forward, detection-shaped
-forward, ViT-B-shaped forward + backward, four-stage hierarchy forward + backward.
+with throughput, step time and dominant kernel of every configuration: ViT-S-shaped forward,
+detection-shaped forward, ViT-B-shaped forward + backward, four-stage hierarchy forward + backward.
+Everything else that was measured (every kernel of every configuration, other forms of the step,
+the padded baseline) goes to the file named by --details.
 """
 from __future__ import annotations
 
@@ -58,6 +60,8 @@ def parse_args():
     ap.add_argument("--no-extras", action="store_true",
                     help="skip the four-call form, graph replay, padded baseline, widened rows")
     ap.add_argument("--cpu-seconds", type=float, default=10.0)
+    ap.add_argument("--details", default=os.path.join(ROOT, "bench_details.json"),
+                    help="file for the full result (\"\" = none); the printed line is its summary")
     ap.add_argument("--kernel-launches", type=int, default=200,
                     help="launches per kernel of the per-kernel timing passes (independent of --steps)")
     ap.add_argument("--calibration-copy", action="store_true",
@@ -833,7 +837,39 @@ def main():
     if not args.no_cpu_baseline:
         result["cpu_baseline"] = cpu_oracle_baseline(wl, ctx["bun"], args.cpu_seconds)
         result["cpu_baseline"]["gpu_over_cpu"] = round(head["value"] / result["cpu_baseline"]["value"], 1)
-    print(json.dumps(result))
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(result, f, indent=1)
+    print(json.dumps(summary(result)))
+
+
+ROOFLINE_FIELDS = ("kernel", "bound", "achieved", "peak", "unit", "frac", "avg_launch_us", "traffic", "frac_of_measured_ceiling")
+
+
+def _brief(res):
+    roof = res.get("roofline", {})
+    return {"value": round(res["value"], 1), "us": round(res["ms_per_step"] * 1e3, 2), "kernel_us": roof.get("avg_launch_us"),
+            "frac": roof.get("frac")}
+
+
+def summary(result):
+    """The line that is printed: the headline with its roofline and, for every configuration, selected tokens/s, us a
+    step, and the launch time and roofline fraction of its dominant kernel.  Short: the records of a run keep the last
+    2000 characters of its output."""
+    line = {k: v for k, v in result.items()
+            if k not in ("kernels", "configs", "extras", "roofline", "ceilings", "single_stream", "cpu_baseline",
+                         "ms_per_step_until_last_event")}
+    line["config"] = {k: v for k, v in result["config"].items() if k != "launch"}
+    line["roofline"] = {k: result["roofline"][k] for k in ROOFLINE_FIELDS if k in result["roofline"]}
+    line["configs"] = {name: _brief(res) for name, res in result["configs"].items()}
+    if "forward" in result["configs"].get("hierarchy", {}):
+        line["configs"]["hierarchy_forward"] = _brief(result["configs"]["hierarchy"]["forward"])
+    padded = result.get("extras", {}).get("padded_baseline")
+    if padded is not None:
+        line["padded_baseline"] = {k: padded[k] for k in ("packed_attention_us", "padded_dense_us", "padded_skipping_masked_keys_us")}
+    if "cpu_baseline" in result:
+        line["cpu_baseline"] = {k: v for k, v in result["cpu_baseline"].items() if k != "sample"}
+    return line
 
 
 if __name__ == "__main__":
