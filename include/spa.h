@@ -82,8 +82,10 @@ int spa_set_option(const char* name, const char* value);
 /*
  * Launch groups: calls of several stages of a hierarchy in one launch per step.  Between spa_group_begin and
  * spa_group_end (same host thread) up to four calls each of spa_gate_select / spa_gate_select_pooled, spa_pack (no
- * counts needed, no scores), spa_pack_pair (with scores), spa_packed_attention_unpack /
- * spa_gathered_attention_unpack / spa_selected_attention_unpack / spa_gated_attention_unpack,
+ * counts needed, no scores), spa_pack_pair (with scores), of each operand form of the attention (packed:
+ * spa_packed_attention, spa_packed_attention_unpack, spa_segment_attention_unpack; gathered:
+ * spa_gathered_attention_unpack, spa_gathered_segment_attention_unpack, spa_selected_attention_unpack; gated:
+ * spa_gated_attention_unpack),
  * spa_packed_attention_bwd_tokens / spa_gated_attention_bwd_tokens (which need their workspace here whatever
  * max_seqlen) and spa_gate_bwd (C <= 1024), and one spa_linear_packed_bwd_input with up to two
  * spa_linear_packed_bwd_weight (without gate_scores; one launch unless the input side takes 256 x 256 tiles), check
@@ -91,7 +93,8 @@ int spa_set_option(const char* name, const char* value);
  * spa_group_end launches them on its stream, step by step in that order: a call sees what calls of earlier steps
  * of the group write, and a pooled gate the scores of the gate called before it.  bf16, head dim 32; for at most 256
  * tokens per image at most 64 images, and no gathered attention.  Any other call, or one outside these limits,
- * returns SPA_ERR_UNSUPPORTED; an error of any call ends the group, nothing is launched.  Same results as the calls
+ * returns SPA_ERR_UNSUPPORTED; an error of any call ends the group, nothing is launched, neither of the group nor by
+ * the call itself.  Same results as the calls
  * one by one, but for the rounding of the attention backward of short segments (the long-segment kernel serves all).
  */
 int spa_group_begin(void);
@@ -533,7 +536,8 @@ int spa_packed_attention_bwd(const void* q, const void* k, const void* v, int64_
 
 /*
  * spa_packed_attention_bwd that may also take the long-segment kernel for short segments (max_seqlen <= 256, bf16)
- * whose few (image, head) pairs would leave the chip idle; the same gradients but for rounding.
+ * whose few (image, head) pairs would leave the chip idle; the same gradients but for rounding.  A call of its own
+ * because the choice depends on the whole batch: spa_packed_attention_bwd gives an image the same bits in any batch.
  */
 int spa_packed_attention_bwd_spread(const void* q, const void* k, const void* v, int64_t q_row_stride,
                                     int64_t k_row_stride, int64_t v_row_stride,

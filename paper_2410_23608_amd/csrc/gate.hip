@@ -12,15 +12,11 @@
 namespace spa {
 
 constexpr int kGateThreads = 256;
-constexpr int kMaxGateC = 8192;   // (the gate backward stages w in LDS as fp32)
+constexpr int kMaxGateC = 8192;
 
 template <typename T> struct Vec16;
 template <> struct Vec16<float> {
   static constexpr int kElems = 4;
-  __device__ static __forceinline__ void load(const float* p, float (&f)[4]) {
-    floatx4 v = *reinterpret_cast<const floatx4*>(p);
-    f[0] = v[0]; f[1] = v[1]; f[2] = v[2]; f[3] = v[3];
-  }
   // dx is the last thing the backward pass writes and nothing here reads it again: non-temporal
   __device__ static __forceinline__ void store(float* p, const float (&f)[4]) {
     floatx4 v = {f[0], f[1], f[2], f[3]};
@@ -29,11 +25,6 @@ template <> struct Vec16<float> {
 };
 template <> struct Vec16<__bf16> {
   static constexpr int kElems = 8;
-  __device__ static __forceinline__ void load(const __bf16* p, float (&f)[8]) {
-    floatx8 v = bf16x8_to_float(*reinterpret_cast<const bf16x8*>(p));
-#pragma unroll
-    for (int i = 0; i < 8; ++i) f[i] = v[i];
-  }
   __device__ static __forceinline__ void store(__bf16* p, const float (&f)[8]) {
     floatx8 v;
 #pragma unroll

@@ -1,6 +1,7 @@
 // Launch groups (spa_group_begin / spa_group_end): the calls of the stages of a hierarchy, which are small and do
 // not depend on each other except through the gates' score maps, in one launch per step of the path instead of one
-// per stage and step.  A dependent launch costs about 4 us however small it is.
+// per stage and step.  However small it is, a launch costs the host 3.6 us and the stream 1.6 us (200 dependent
+// launches of one workgroup, issued one by one and queued ahead), and a small kernel 2-3 us more of trips to memory.
 //
 // Between begin and end an entry point only notes its kernel's arguments (thread-local); end launches what was noted
 // step by step: gates, packing, attention, attention backward, gate backward, projection backward.  A kernel of a

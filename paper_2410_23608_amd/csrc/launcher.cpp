@@ -2,7 +2,7 @@
 //
 // A step is a handful of C-ABI calls with ~20 arguments each.  Marshalling them through ctypes and
 // re-checking the tensors of every call costs 5 us per launch for prepared calls and 10-25 us
-// otherwise, against 2.9 us for the launch itself: a step of three launches was bound by the host
+// otherwise, against 3.6 us with the launch itself from here: a step of three launches was bound by the host
 // (42 us for 19 us of kernels at 2 x 196 tokens).  Here the arguments of a call are kept as raw
 // 8-byte values (Call), and a whole step as a list of them (Program) in which the caller's tensors, the
 // pass's own buffers and the current stream are open places that every run fills in: per run, one check of

@@ -385,7 +385,7 @@ class BlockTrainPass(_Pass):
     overlap_weight_grads (default): nothing downstream in the step reads dW / dbias, so the two weight-side GEMMs run
     beside other work.  In bf16 with B N C^2 <= 6e9 they share one launch with the input side of the QKV projection
     (a launch group), and their partial sums one more: these GEMMs leave units idle there and every dependent launch
-    costs about 4 us.  Above that line each of them fills the chip, and they are enqueued on a second HIP stream
+    costs 4 us, most of it before its first product.  Above that line each of them fills the chip, and they are enqueued on a second HIP stream
     (default priority) beside the attention backward, the input-side GEMM and the gate backward; events order them
     after their inputs and the step's last stage joins the streams.  Measured, us a step, one launch / second stream /
     in order: 32 x 196 x 384 93 / 110 / 115, 128 x 196 x 384 178 / 184 / 200, 32 x 196 x 768 148 / 190 / 168 and
@@ -513,7 +513,7 @@ class ContainerForwardPass(_Pass):
         self.max_seqlen = min(container_len, N)
         self.seg_cu_seqlens = torch.zeros(self.seg_cap + 1, dtype=torch.int32, **dv)
         self.n_segments = torch.zeros(1, dtype=torch.int32, **dv)
-        self.out = torch.zeros(cap, C, dtype=td, **dv)
+        self.out = None if fused_unpack else torch.zeros(cap, C, dtype=td, **dv)      # (the fused form writes y only)
         self.y = torch.empty(B, N, C, dtype=td, **dv)
 
     def stages(self, x, w, qkv, base=None) -> List[Tuple[str, Callable[[], None]]]:
@@ -580,7 +580,11 @@ def _on_streams(per_stage, streams, stream_of):
 
 
 def _groupable(cfg):
-    """Stages whose calls can share launches (spa_group_begin): 2 to 4 of them, bf16, heads of 32, at most 1024 columns and 64 images."""
+    """Stages whose calls can share launches (spa_group_begin).  The limits are those of the grouped kernels: four
+    calls a launch; bf16; heads of 32, the one head dim their attention is built for (two of them in one kernel would
+    hold the registers and the LDS of the wider: at head dim 64 the tiled form runs two wavefronts per SIMD, at 32
+    three); 1024 columns (the gate backward holds a row in registers); 64 images (one per lane where the one-wave
+    attention numbers its blocks)."""
     return 2 <= len(cfg) <= 4 and all(c[5] == "bf16" and c[3] == 32 * c[4] and c[3] <= 1024 and c[0] <= 64 for c in cfg)
 
 
