@@ -323,8 +323,21 @@ PyObject* look_up(const Place& p, PyObject* const* dicts) {
   return nullptr;
 }
 
+// Tensors of the owner's state, held while the launches go out: a program's other threads may replace them.
+struct Held {
+  PyObject* t[kMaxSlots];
+  size_t n = 0;
+  void add(PyObject* o) {
+    Py_INCREF(o);
+    t[n++] = o;
+  }
+  ~Held() {
+    while (n > 0) Py_DECREF(t[--n]);
+  }
+};
+
 // The owner's state against the recording; fills the slots from `slot` on, whose tensors `held` then holds.
-bool match_places(const ProgramObject* self, PyObject* owner, Value* base, size_t slot, std::vector<PyObject*>& held) {
+bool match_places(const ProgramObject* self, PyObject* owner, Value* base, size_t slot, Held& held) {
   PyObject* dicts[kMaxObjects];
   size_t n = 0;
   auto enter = [&](PyObject* o) {                    // (the object keeps its dict alive, its holder the object)
@@ -344,8 +357,7 @@ bool match_places(const ProgramObject* self, PyObject* owner, Value* base, size_
         break;
       case Place::kTensor:
         if (!match(p.tensor, v, &base[slot++])) return false;
-        Py_INCREF(v);                                // a program's thread may replace it while the launches go out
-        held.push_back(v);
+        held.add(v);
         break;
       case Place::kNumber: {
         if (!PyFloat_CheckExact(v) && !PyLong_CheckExact(v)) return false;
@@ -400,23 +412,15 @@ PyObject* program_vectorcall(PyObject* o, PyObject* const* args, size_t nargsf, 
   Value base[kMaxSlots];
   for (size_t i = first; i < n; ++i)
     if (!match((*self->inputs)[i - first], args[i], &base[i - first])) Py_RETURN_FALSE;
-  std::vector<PyObject*> held;
-  auto release = [&] { for (PyObject* t : held) Py_DECREF(t); };
-  if (self->owned) {
-    held.reserve(self->places->size());
-    if (!match_places(self, args[0], base, n - first, held)) {
-      release();
-      PyErr_Clear();            // an attribute that cannot be compared is one that is not as recorded
-      Py_RETURN_FALSE;
-    }
+  Held held;
+  if (self->owned && !match_places(self, args[0], base, n - first, held)) {
+    PyErr_Clear();              // an attribute that cannot be compared is one that is not as recorded
+    Py_RETURN_FALSE;
   }
   void* stream = nullptr;
   if (self->open) {
     stream = current_stream();
-    if (PyErr_Occurred()) {
-      release();
-      return nullptr;
-    }
+    if (PyErr_Occurred()) return nullptr;
   }
   int rc = SPA_OK;
   Py_BEGIN_ALLOW_THREADS
@@ -426,7 +430,6 @@ PyObject* program_vectorcall(PyObject* o, PyObject* const* args, size_t nargsf, 
   }
   Py_END_ALLOW_THREADS
   ++self->runs;
-  release();
   if (rc != SPA_OK) return raise_code(rc);
   Py_RETURN_TRUE;
 }
@@ -455,6 +458,10 @@ bool parse_tensor(PyObject* o, TensorSpec* out) {
 // (what, object, name, index, value)
 bool parse_place(PyObject* o, Place* out, size_t objects) {
   const char* what;
+  if (!PyTuple_Check(o)) {
+    PyErr_SetString(PyExc_TypeError, "a place is a tuple");
+    return false;
+  }
   if (!PyArg_ParseTuple(o, "siUnO", &what, &out->of, &out->name, &out->index, &out->value)) {
     out->name = out->value = nullptr;
     return false;

@@ -292,3 +292,17 @@ def test_numbers_a_step_refuses(pipeline, recordings):
     assert torch.equal(p.run(*ins), want)
     p.bias = 0.0
     assert torch.equal(p.run(*ins), want)
+
+
+def test_parameters_are_recorded_and_subclasses_are_not(pipeline, recordings):
+    class Marked(torch.Tensor):
+        pass
+    p = _make(pipeline, "forward")
+    x, w, qkv = _inputs("forward", 5)
+    want = p.run(x, w, qkv).clone()
+    for _ in range(3):
+        assert torch.equal(p.run(x, torch.nn.Parameter(w, requires_grad=False), qkv), want)
+    assert len(recordings) == 1 and recordings[0].runs == 3
+    for _ in range(2):
+        assert torch.equal(p.run(x, w.as_subclass(Marked), qkv), want)
+    assert recordings[0].runs == 3
