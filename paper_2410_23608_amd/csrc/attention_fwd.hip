@@ -61,6 +61,7 @@ struct FwdArgs {
   long lse_stride;
   Scatter sc;
   int B, nqb, ntile;
+  int waves;                   // launch groups: waves a unit of the short form (1 or 2)
 };
 
 // Row of q / k / v that holds packed position j of a segment starting at packed row row0:
@@ -325,19 +326,19 @@ __device__ __forceinline__ void fwd_park(FwdAcc<DH>& acc, bool q_ok, bool have_k
 
 // Output stage, phase 2 (after a barrier): the wave copies its parked tile to global memory,
 // consecutive lanes writing consecutive 16-byte chunks of a row.  nrows = valid rows (<= 32);
-// prow0 = packed row of the tile's first row.  out may be null when only y is wanted.
+// prow0 = packed row of the tile's first row, y_row = row of y of lane % 32's row.  out may be null when only y is wanted.
 template <int DH, int RS>
-__device__ __forceinline__ void fwd_flush(const __bf16* tile, __bf16* out, const Scatter& sc, long prow0, int h,
+__device__ __forceinline__ void fwd_flush(const __bf16* tile, __bf16* out, const Scatter& sc, int y_row, long prow0, int h,
                                           long C, int nrows, int lane) {
   constexpr int CPR = DH / 8;
 #pragma unroll
   for (int i = lane; i < 32 * CPR; i += 64) {
-    const int r = i / CPR, c = i % CPR;
+    const int r = i / CPR, c = i % CPR, token = __builtin_amdgcn_ds_bpermute(r << 2, y_row);
     if (r < nrows) {
       bf16x8 val = *reinterpret_cast<const bf16x8*>(&tile[r * RS + c * 8]);
       if (out != nullptr) *reinterpret_cast<bf16x8*>(out + (prow0 + r) * C + h * DH + c * 8) = val;
       if (sc.y != nullptr) {
-        const long off = (long)sc.gather_idx[prow0 + r] * C + h * DH + c * 8;
+        const long off = (long)token * C + h * DH + c * 8;
         if (sc.base != nullptr) {
           const floatx8 bv = bf16x8_to_float(*reinterpret_cast<const bf16x8*>(static_cast<const __bf16*>(sc.base) + off));
           val = float_to_bf16x8(bf16x8_to_float(val) + bv);
@@ -496,6 +497,7 @@ tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, c
 
   const int32_t* gi = gather_base<GATHER>(sc, seg.row0);
   const long q_src = q_ok ? source_row(gi, seg.row0, qi) : 0;   // (gathered: an index load, issued first)
+  const int y_row = GATHER ? (int)q_src : sc.y != nullptr && q_ok ? sc.gather_idx[seg.row0 + qi] : 0;
   PairStage<DH, 64 * NW, BN, GATHER != 0, GATHER != 0> stage;
   stage.gi = gi;
   stage.last = max(seg.nk - 1, 0);
@@ -542,7 +544,7 @@ tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, c
     fwd_park<DH, RS>(acc, q_ok, seg.nk > 0, parked, lse != nullptr ? lse + h * lse_stride + seg.row0 + qi : nullptr,
                      l32, hh);
     __builtin_amdgcn_wave_barrier();
-    fwd_flush<DH, RS>(parked, out, sc, seg.row0 + q0 + wv * 32, h, C, min(32, seg.nq - q0 - wv * 32), lane);
+    fwd_flush<DH, RS>(parked, out, sc, y_row, seg.row0 + q0 + wv * 32, h, C, min(32, seg.nq - q0 - wv * 32), lane);
   }
 }
 
@@ -614,24 +616,75 @@ attn_fwd_bf16_tiled_kernel(const FwdArgs a) {
   tiled_block<DH, NW, GATHER>(sh, a, blockIdx.x, gridDim.x);
 }
 
-// Short segments, wave-autonomous.  ONE wave per (image, head, 32-query block), no
-// workgroup barriers, no shared state between waves: the wave streams its segment's K and V
-// rows in steps of STEP keys through a private LDS tile (coalesced 16-byte row loads, the next
-// step's rows already in flight in registers), reads K fragments back as MFMA A operands
-// and V fragments through the transposing LDS read, and keeps the online softmax state in
-// registers.  Work units are small (<= n/32 steps each), so the load spreads over all SIMDs
-// instead of concentrating a heavy (image, head) on one compute unit.
-// The wave's work on queries [q0, q0 + 32) of head h of segment seg (q0 < seg.nq): Ks, Vs are
-// its private LDS tiles of STEP rows.
-template <int DH, int STEP, int GATHER>
+// Short segments.  A work unit is 32 queries of one (image, head); SPLIT waves share it, each taking every SPLIT-th step of
+// STEP keys.  A wave streams its keys' K and V rows through a private LDS tile (coalesced 16-byte row loads, its next step's
+// rows already in flight in registers), reads K fragments back as MFMA A operands and V fragments through the transposing
+// LDS read, and keeps the online softmax state in registers; no barrier until the waves of a unit merge at the end.  Work
+// units are small (<= n/32 steps each), so the load spreads over all SIMDs instead of concentrating a heavy (image,
+// head) on one compute unit.
+template <int DH, int STEP>
+struct WaveLds {
+  static constexpr int RS = DH + 8;
+  __attribute__((aligned(16))) __bf16 Ks[STEP * RS];
+  __attribute__((aligned(16))) __bf16 Vs[STEP * RS];
+};
+
+// The sums of waves 1 .. SPLIT - 1 of a unit go to the first one through LDS (room: 64 (DH / 2 + 2) floats a wave at
+// lds + part * stride).  All waves call it; true for the first.  A wave that had no keys counts with weight 0.
+template <int DH, int SPLIT>
+__device__ __forceinline__ bool merge_parts(FwdAcc<DH>& acc, int part, bool have_keys, void* lds, int stride, int lane) {
+  if (part > 0) {
+    floatx4* o = reinterpret_cast<floatx4*>(static_cast<char*>(lds) + part * stride);
+    float* ml = reinterpret_cast<float*>(o + DH / 8 * kWave);
+#pragma unroll
+    for (int g = 0; g < DH / 8; ++g)
+      o[g * kWave + lane] = floatx4{acc.o[g / 4][4 * (g % 4)], acc.o[g / 4][4 * (g % 4) + 1], acc.o[g / 4][4 * (g % 4) + 2],
+                                    acc.o[g / 4][4 * (g % 4) + 3]};
+    ml[lane] = acc.m;
+    ml[kWave + lane] = acc.l;
+  }
+  __syncthreads();
+  if (part > 0) return false;
+  if (!have_keys) return true;
+  float m[SPLIT], m_all = acc.m;
+#pragma unroll
+  for (int i = 1; i < SPLIT; ++i) {
+    m[i] = reinterpret_cast<const float*>(static_cast<const char*>(lds) + i * stride)[DH / 8 * kWave * 4 + lane];
+    m_all = fmaxf(m_all, m[i]);
+  }
+  const float a = __builtin_amdgcn_exp2f(acc.m - m_all);
+  acc.m = m_all;
+  acc.l *= a;
+#pragma unroll
+  for (int d = 0; d < DH / 32; ++d)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc.o[d][r] *= a;
+#pragma unroll
+  for (int i = 1; i < SPLIT; ++i) {
+    const floatx4* o = reinterpret_cast<const floatx4*>(static_cast<const char*>(lds) + i * stride);
+    const float w = __builtin_amdgcn_exp2f(m[i] - m_all);
+    acc.l = fmaf(reinterpret_cast<const float*>(o + DH / 8 * kWave)[kWave + lane], w, acc.l);
+#pragma unroll
+    for (int g = 0; g < DH / 8; ++g) {
+      const floatx4 f = o[g * kWave + lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc.o[g / 4][4 * (g % 4) + e] = fmaf(f[e], w, acc.o[g / 4][4 * (g % 4) + e]);
+    }
+  }
+  return true;
+}
+
+// The work of wave `part` on queries [q0, q0 + 32) of head h of segment seg (q0 < seg.nq); lds: the unit's tiles, one a wave.
+template <int DH, int STEP, int GATHER, int SPLIT>
 __device__ __forceinline__ void
-wave_attention(__bf16* Ks, __bf16* Vs, const Segment seg, int h, int q0, const __bf16* __restrict__ q,
+wave_attention(WaveLds<DH, STEP>* lds, int part, const Segment seg, int h, int q0, const __bf16* __restrict__ q,
                const __bf16* __restrict__ k, const __bf16* __restrict__ v, long qs, long ks, long vs, int H,
                const float* __restrict__ v_scores, float scale_log2, __bf16* __restrict__ out, float* __restrict__ lse, long lse_stride,
                const Scatter& sc) {
-  constexpr int RS = DH + 8, KK = DH / 16, DB = DH / 32, CPR = DH / 8;
+  constexpr int RS = DH + 8, KK = DH / 16, CPR = DH / 8;
   constexpr int NSB = STEP / 32;                 // 32-key sub-tiles per step (one softmax update)
   constexpr int LPL = STEP * CPR / 64;           // 16-byte loads per lane per tensor per step
+  __bf16 *Ks = lds[part].Ks, *Vs = lds[part].Vs;
   const long C = (long)H * DH;
   const int lane = threadIdx.x & 63, l32 = lane & 31, hh = lane >> 5;
   const int qi = q0 + l32;
@@ -688,20 +741,23 @@ wave_attention(__bf16* Ks, __bf16* Vs, const Segment seg, int h, int q0, const _
     }
   };
 
+  const int first = part * STEP;
   const long q_src = q_ok ? source_row(gi, seg.row0, qi) : 0;   // (gathered: an index load, issued first, so that
-  iload(0);                                                      // its wait is the one the first row loads need anyway)
+  iload(first);                                                  // its wait is the one the first row loads need anyway)
   gload();
-  iload(STEP);
+  iload(first + SPLIT * STEP);
   bf16x8 qf[KK];
   load_q_frags<DH>(q + q_src * qs + h * DH, q_ok, hh, qf);
+  // the row of y of this lane's query: the row it was read from, or fetched now, when nothing waits for it yet
+  const int y_row = GATHER ? (int)q_src : sc.y != nullptr && q_ok ? sc.gather_idx[seg.row0 + qi] : 0;
   FwdAcc<DH> acc;
   acc.init();
 
-  for (int kt = 0; kt < seg.nk; kt += STEP) {
+  for (int kt = first; kt < seg.nk; kt += SPLIT * STEP) {
     lstore();                                     // this step's rows: registers -> LDS
-    if (kt + STEP < seg.nk) {
+    if (kt + SPLIT * STEP < seg.nk) {
       gload();                                    // next step's rows: in flight during the math
-      iload(kt + 2 * STEP);
+      iload(kt + 2 * SPLIT * STEP);
     }
     const int rem = seg.nk - kt;
     // scores of the step: S^T = K Q^T, NSB 32-key sub-tiles, one softmax update for all
@@ -710,52 +766,58 @@ wave_attention(__bf16* Ks, __bf16* Vs, const Segment seg, int h, int q0, const _
     fwd_softmax_pv<DH, 0, NSB, false>(s, Vs, 0, 0, rem, acc, scale_log2, l32, hh);
   }
 
+  if constexpr (SPLIT > 1)
+    if (!merge_parts<DH, SPLIT>(acc, part, seg.nk > 0, lds, sizeof(WaveLds<DH, STEP>), lane)) return;
   // output: park the 32 x DH tile in the (now free) K tile, then write whole rows
   fwd_park<DH, RS>(acc, q_ok, seg.nk > 0, Ks, lse != nullptr ? lse + h * lse_stride + seg.row0 + qi : nullptr, l32,
                    hh);
-  fwd_flush<DH, RS>(Ks, out, sc, seg.row0 + q0, h, C, min(32, seg.nq - q0), lane);
+  fwd_flush<DH, RS>(Ks, out, sc, y_row, seg.row0 + q0, h, C, min(32, seg.nq - q0), lane);
 }
 
-template <int DH, int STEP>
-struct WaveLds {
-  static constexpr int RS = DH + 8;
-  __attribute__((aligned(16))) __bf16 Ks[STEP * RS];
-  __attribute__((aligned(16))) __bf16 Vs[STEP * RS];
-};
-template <int DH, int STEP, int GATHER>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(STEP == 32 ? 3 : 1)))
+// Waves a unit.  One wave a unit lives 2 us + 0.8 us for every 32 keys + 1.5 us; where the units do not fill the chip (half
+// of them have queries) that chain is the launch, so two waves share it, the merge costing 0.3 us.  With more units the
+// waves of those without queries take the others' slots.  us a step, 196 tokens an image, 6 heads of 64, two launches,
+// 1 / 2 / 4 waves: 8 images (336 units) 11.2 / 9.3 / 9.7, 16 images 12.0 / 10.0 / 10.5, 32 images (1344) 13.0 / 11.8 / 14.3,
+// 64 images 15.9 / 16.5 / 20.5.  Segments of up to 3 steps are not worth a merge.
+static int unit_waves(int nqb, long units) { return nqb >= 4 && units <= 1536 ? 2 : 1; }
+
+template <int SPLIT, int DH, int STEP, int GATHER>
+__global__ void __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(STEP == 32 ? 3 : 1)))
 attn_fwd_bf16_wave_kernel(const FwdArgs a) {
-  __shared__ WaveLds<DH, STEP> lds;
+  __shared__ WaveLds<DH, STEP> lds[SPLIT];
   const TileId tile_id = xcd_tile(a.nqb, a.H, a.B);
   if (!tile_id.valid) return;
   const int h = tile_id.h, img = tile_id.rank;
   const Segment seg = segment_of(img, a.cu, a.key_lens, a.n_pad);
   const long C = (long)a.H * DH;
-  // this wave's share of the image's bypassing tokens: at once if it has no queries, else last
+  // this unit's share of the image's bypassing tokens: at once if it has no queries, else last
   const FillRange fr = fill_range(a.sc, img, a.B, tile_id.qb, a.nqb);
   const int q0 = tile_id.qb * 32;
   if (q0 < seg.nq)
-    wave_attention<DH, STEP, GATHER>(lds.Ks, lds.Vs, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H, a.v_scores, a.scale_log2, a.out,
-                                         a.lse, a.lse_stride, a.sc);
-  if (a.sc.y != nullptr) scatter_fill<__bf16, DH>(a.sc, fr.b, fr.t0, fr.t1, h, C, threadIdx.x, 64);
+    wave_attention<DH, STEP, GATHER, SPLIT>(lds, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H, a.v_scores,
+                                            a.scale_log2, a.out, a.lse, a.lse_stride, a.sc);
+  if (a.sc.y != nullptr) scatter_fill<__bf16, DH>(a.sc, fr.b, fr.t0, fr.t1, h, C, threadIdx.x, 64 * SPLIT);
 }
 
-// The one-wave work units driven by the selection mask itself: no packing launch precedes this
-// kernel.  The wave reads its image's N <= 256 mask bytes, ranks the survivors with ballots and
+// The work units driven by the selection mask itself: no packing launch precedes this
+// kernel.  Every wave reads its image's N <= 256 mask bytes, ranks the survivors with ballots and
 // writes their token rows, in order, to a list in LDS: exactly the image's part of gather_idx, so
 // wave_attention runs on it as on gathered rows (packed position j of the image = row list[j] of
 // q, k, v and of y), and the bypass fill tests the mask byte instead of inv_pos.  Costs four byte
 // loads and four ballots per wave where the other forms cost a kernel launch.
-template <int DH, int STEP>
+template <int DH, int STEP, int SPLIT>
 struct MaskLds {
-  WaveLds<DH, STEP> kv;
+  WaveLds<DH, STEP> kv[SPLIT];
   int32_t list[256];
 };
-// Unit j of XCD xcd, one wave (N <= 256 tokens per image, mask and fill of y: a.sc)
-template <int DH, int STEP>
-__device__ __forceinline__ void mask_unit(MaskLds<DH, STEP>& lds, const FwdArgs& a, int xcd, int j) {
+// Unit j of XCD xcd (N <= 256 tokens per image, mask and fill of y: a.sc), wave `part` of it
+template <int DH, int STEP, int SPLIT>
+__device__ __forceinline__ void mask_unit(MaskLds<DH, STEP, SPLIT>& lds, const FwdArgs& a, int xcd, int j, int part) {
   const TileId tile_id = xcd_tile_at(xcd, j, a.nqb, a.H, a.B);
-  if (!tile_id.valid) return;
+  if (!tile_id.valid) {
+    if (SPLIT > 1) __syncthreads();
+    return;
+  }
   const int h = tile_id.h, img = tile_id.rank, lane = threadIdx.x & 63, N = a.sc.N;
   const long tok0 = (long)img * N;
   int n = 0;                                       // survivors of the image so far
@@ -764,7 +826,7 @@ __device__ __forceinline__ void mask_unit(MaskLds<DH, STEP>& lds, const FwdArgs&
     const int t = lane + 64 * i;
     const bool sel = t < N && a.sc.mask[tok0 + t] != 0;
     const uint64_t bal = __ballot(sel);
-    if (sel) lds.list[n + lanes_below(bal)] = (int32_t)(tok0 + t);
+    if (sel) lds.list[n + lanes_below(bal)] = (int32_t)(tok0 + t);      // (every wave of the unit writes the same list)
     n += __popcll(bal);
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -776,16 +838,17 @@ __device__ __forceinline__ void mask_unit(MaskLds<DH, STEP>& lds, const FwdArgs&
   const FillRange fr = fill_range(a.sc, img, a.B, tile_id.qb, a.nqb);
   const int q0 = tile_id.qb * 32;
   if (q0 < n)
-    wave_attention<DH, STEP, kFwdGathered>(lds.kv.Ks, lds.kv.Vs, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H, a.v_scores, a.scale_log2,
-                                   nullptr, nullptr, 0, scl);
-  scatter_fill<__bf16, DH>(a.sc, fr.b, fr.t0, fr.t1, h, C, lane, 64);
+    wave_attention<DH, STEP, kFwdGathered, SPLIT>(lds.kv, part, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H, a.v_scores,
+                                                  a.scale_log2, nullptr, nullptr, 0, scl);
+  else if (SPLIT > 1) __syncthreads();             // (the workgroup's other unit merges)
+  scatter_fill<__bf16, DH>(a.sc, fr.b, fr.t0, fr.t1, h, C, lane + 64 * part, 64 * SPLIT);
 }
 
-template <int DH, int STEP>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
+template <int DH, int STEP, int SPLIT>
+__global__ void __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(3)))
 attn_fwd_bf16_wave_mask_kernel(const FwdArgs a) {
-  __shared__ MaskLds<DH, STEP> lds;
-  mask_unit<DH, STEP>(lds, a, blockIdx.x & 7, blockIdx.x >> 3);
+  __shared__ MaskLds<DH, STEP, SPLIT> lds;
+  mask_unit<DH, STEP, SPLIT>(lds, a, blockIdx.x & 7, blockIdx.x >> 3, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
 }
 
 // The same work units, dealt to the compute units by weight (batches of up to 64 images, one
@@ -862,23 +925,25 @@ static unsigned lpt64_grid(int B, int H, int nqb) {
 
 // Compiled for three waves per SIMD (168 registers at head dim 64, no spills): a ViT-B-shaped
 // batch has ~2800 live waves for 1024 SIMDs and then runs in one round instead of two.
-template <int DH, int STEP, int GATHER>
-__device__ __forceinline__ void lpt64_unit(WaveLds<DH, STEP>& lds, const FwdArgs& a, int x, int j, int units) {
+template <int DH, int STEP, int GATHER, int SPLIT>
+__device__ __forceinline__ void lpt64_unit(WaveLds<DH, STEP>* lds, const FwdArgs& a, int x, int j, int units, int part) {
   const int unit = j & 31, m = j >> 5;
   const LptBlock blk = lpt64_block<32>(a.cu, a.key_lens, a.n_pad, a.B, a.H, a.nqb, x, m * 32 + ((m & 1) ? 31 - unit : unit));
   if (blk.live)
-    wave_attention<DH, STEP, GATHER>(lds.Ks, lds.Vs, blk.seg, blk.h, blk.q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H,
-                                     a.v_scores, a.scale_log2, a.out, a.lse, a.lse_stride, a.sc);
+    wave_attention<DH, STEP, GATHER, SPLIT>(lds, part, blk.seg, blk.h, blk.q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, a.H,
+                                            a.v_scores, a.scale_log2, a.out, a.lse, a.lse_stride, a.sc);
+  else if (SPLIT > 1) __syncthreads();           // (the workgroup's other unit merges)
   if (a.sc.y != nullptr) {
-    const long rows = a.sc.flat ? (long)a.sc.N : (long)a.B * a.sc.N, per = (rows + units - 1) / units, u = 8L * j + x;
+    const long rows = a.sc.flat ? (long)a.sc.N : (long)a.B * a.sc.N, waves = (long)units * SPLIT, per = (rows + waves - 1) / waves,
+               u = (8L * j + x) * SPLIT + part;
     scatter_fill_rows<__bf16>(a.sc, min(rows, u * per), min(rows, (u + 1) * per), (long)a.H * DH, threadIdx.x & 63);
   }
 }
-template <int DH, int STEP, int GATHER>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
+template <int SPLIT, int DH, int STEP, int GATHER>
+__global__ void __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(3)))
 attn_fwd_bf16_wave_lpt64_kernel(const FwdArgs a) {
-  __shared__ WaveLds<DH, STEP> lds;
-  lpt64_unit<DH, STEP, GATHER>(lds, a, blockIdx.x & 7, blockIdx.x >> 3, gridDim.x);
+  __shared__ WaveLds<DH, STEP> lds[SPLIT];
+  lpt64_unit<DH, STEP, GATHER, SPLIT>(lds, a, blockIdx.x & 7, blockIdx.x >> 3, gridDim.x, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
 }
 
 // Several calls in one launch (launch groups, head dim 32): the tiled blocks of those with more than 256 tokens
@@ -889,14 +954,22 @@ attn_fwd_bf16_group_kernel(const Members<FwdArgs> m) {
   constexpr int DH = 32, STEP = 32;
   __shared__ union {
     TiledShared<DH> tiled;
-    MaskLds<DH, STEP> wave[4];
+    MaskLds<DH, STEP, 1> wave[4];
+    MaskLds<DH, STEP, 2> pair[2];
   } sh;
   const MemberBlock mb = member_of(m, blockIdx.x);
   const FwdArgs& a = m.a[mb.s];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (a.ntile > 0) tiled_block<DH, 4, FORM>(sh.tiled, a, mb.block, mb.blocks);
-  else if constexpr (FORM == kFwdGathered) mask_unit<DH, STEP>(sh.wave[wv], a, mb.block & 7, (mb.block >> 3) * 4 + wv);
-  else lpt64_unit<DH, STEP, FORM>(sh.wave[wv].kv, a, mb.block & 7, (mb.block >> 3) * 4 + wv, mb.blocks * 4);
+  else if (a.waves == 2) {
+    const int j = (mb.block >> 3) * 2 + (wv >> 1);
+    if constexpr (FORM == kFwdGathered) mask_unit<DH, STEP, 2>(sh.pair[wv >> 1], a, mb.block & 7, j, wv & 1);
+    else lpt64_unit<DH, STEP, FORM, 2>(sh.pair[wv >> 1].kv, a, mb.block & 7, j, mb.blocks * 2, wv & 1);
+  } else {
+    const int j = (mb.block >> 3) * 4 + wv;
+    if constexpr (FORM == kFwdGathered) mask_unit<DH, STEP, 1>(sh.wave[wv], a, mb.block & 7, j, 0);
+    else lpt64_unit<DH, STEP, FORM, 1>(sh.wave[wv].kv, a, mb.block & 7, j, mb.blocks * 4, 0);
+  }
 }
 
 static thread_local Noted<FwdArgs> g_noted[3];       // by form
@@ -914,7 +987,8 @@ int group_flush_attention(hipStream_t st) {
   flush_form<kFwdGated>(st);
   return check_launch("spa_group_end");
 }
-static unsigned wave_groups(unsigned waves) { return (waves / 8 + 3) / 4 * 8; }      // workgroups of four one-wave units
+// workgroups of four waves for so many units (8 XCDs)
+static unsigned wave_groups(unsigned units, int waves) { return (units / 8 * waves + 3) / 4 * 8; }
 
 // Short segments (every segment <= NKMAX keys).  ONE workgroup per (image, head): all K / V
 // rows of the segment are staged once (each element is read from memory exactly once per
@@ -950,6 +1024,7 @@ attn_fwd_bf16_whole_kernel(const __bf16* __restrict__ q, const __bf16* __restric
   const bool q_ok = qi < seg.nq;
 
   const int32_t* gi = gather_base<GATHER>(sc, seg.row0);
+  const int y_row = sc.y != nullptr && q_ok ? sc.gather_idx[seg.row0 + qi] : 0;
   KvStage<DH, THREADS, (NKMAX / 2) * (DH / 8), GATHER> stage;
   stage.index(gi, seg.row0, 0, seg.nk);
   stage.load(k + h * DH, v + h * DH, ks, vs);
@@ -977,7 +1052,7 @@ attn_fwd_bf16_whole_kernel(const __bf16* __restrict__ q, const __bf16* __restric
     fwd_park<DH, RS>(acc, q_ok, seg.nk > 0, tile, lse != nullptr ? lse + h * lse_stride + seg.row0 + qi : nullptr,
                      l32, hh);
   __syncthreads();
-  if (wave_live) fwd_flush<DH, RS>(tile, out, sc, seg.row0 + wv * 32, h, C, min(32, seg.nq - wv * 32), lane);
+  if (wave_live) fwd_flush<DH, RS>(tile, out, sc, y_row, seg.row0 + wv * 32, h, C, min(32, seg.nq - wv * 32), lane);
   if (sc.y != nullptr && live_threads >= THREADS)
     scatter_fill<__bf16, DH>(sc, fr.b, fr.t0, fr.t1, h, C, threadIdx.x, THREADS);
 }
@@ -990,8 +1065,8 @@ attn_fwd_bf16_whole_kernel(const __bf16* __restrict__ q, const __bf16* __restric
 // O^T += V^T P^T, register r against V row acc_row(r, hh), of which the 32 lanes of a half read 128
 // consecutive bytes.  The rows of the next 32 keys are in flight during the math.  Bound by latency at
 // the sizes it is used at (2 x 196 tokens: 5 us; eight lanes per query with K / V tiles in LDS: 12.5 us).
-template <int DH>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+template <int DH, int SPLIT>
+__global__ void __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
 attn_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
                     const float* __restrict__ v, long qs, long ks, long vs, const int32_t* __restrict__ cu,
                     const int32_t* __restrict__ key_lens, int n_pad, int H, float scale,
@@ -999,7 +1074,8 @@ attn_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
   constexpr int HD = DH / 2, DB = DH / 32;
   const TileId tile_id = xcd_tile(nqb, H, B);
   if (!tile_id.valid) return;
-  const int h = tile_id.h, img = tile_id.rank, lane = threadIdx.x, l32 = lane & 31, hh = lane >> 5;
+  const int h = tile_id.h, img = tile_id.rank, lane = threadIdx.x & 63, l32 = lane & 31, hh = lane >> 5;
+  const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const long C = (long)H * DH;
   // cu == key_lens == nullptr: no packing index exists; the wave derives the image's packing order from
   // its n_pad <= 256 mask bytes (see attn_fwd_bf16_wave_mask_kernel) and works on that list as on gathered rows
@@ -1013,7 +1089,7 @@ attn_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
       const int t = lane + 64 * i;
       const bool sel = t < n_pad && sc.mask[tok0 + t] != 0;
       const uint64_t bal = __ballot(sel);
-      if (sel) list[n + rank_in_ballot(bal)] = (int32_t)(tok0 + t);
+      if (sel) list[n + rank_in_ballot(bal)] = (int32_t)(tok0 + t);      // (every wave of the unit writes the same list)
       n += __popcll(bal);
     }
     __syncthreads();
@@ -1051,7 +1127,8 @@ attn_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
 #pragma unroll
     for (int i = 0; i < HD; ++i) qf[i] = 0.f;
     const long q_src = source_row(gi, seg.row0, q_ok ? qi : 0);
-    int row = seg.nk > 0 ? key_row(0) : 0;
+    const int first = 32 * part;                         // keys first .. + 31, then every SPLIT-th 32
+    int row = first < seg.nk ? key_row(first) : 0;
     if (q_ok) {
       const float* qp = q + q_src * qs + h * DH + hh * HD;
 #pragma unroll
@@ -1066,15 +1143,15 @@ attn_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[d][r] = 0.f;
     float m = -INFINITY, l = 0.f;
-    if (seg.nk > 0) {
+    if (first < seg.nk) {
       fetch(row, kf, vf);
-      row = key_row(32);
+      row = key_row(first + 32 * SPLIT);
     }
-    for (int kt = 0; kt < seg.nk; kt += 32) {
+    for (int kt = first; kt < seg.nk; kt += 32 * SPLIT) {
       const int rem = seg.nk - kt;
-      if (rem > 32) {
+      if (rem > 32 * SPLIT) {
         fetch(row, kn, vn);
-        row = key_row(kt + 64);
+        row = key_row(kt + 64 * SPLIT);
       }
       floatx16 s;
 #pragma unroll
@@ -1117,8 +1194,49 @@ attn_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
 #pragma unroll
         for (int d = 0; d < DB; ++d) vf[r][d] = vn[r][d];
     }
+    // the sums of waves 1 .. go to the first one (a wave that had no keys counts with weight 0)
+    if constexpr (SPLIT > 1) {
+      __shared__ float4 part_o[SPLIT - 1][DB * 4][kWave];
+      __shared__ float part_ml[SPLIT - 1][2][kWave];
+      if (part > 0) {
+#pragma unroll
+        for (int d = 0; d < DB; ++d)
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+            part_o[part - 1][d * 4 + g][lane] = float4{o[d][4 * g], o[d][4 * g + 1], o[d][4 * g + 2], o[d][4 * g + 3]};
+        part_ml[part - 1][0][lane] = m;
+        part_ml[part - 1][1][lane] = l;
+      }
+      __syncthreads();
+      if (part == 0) {
+        float m_all = m;
+#pragma unroll
+        for (int i = 0; i < SPLIT - 1; ++i) m_all = fmaxf(m_all, part_ml[i][0][lane]);
+        const float a = seg.nk > 0 ? expf(m - m_all) : 1.f;
+        l *= a;
+#pragma unroll
+        for (int d = 0; d < DB; ++d)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[d][r] *= a;
+        for (int i = 0; i < SPLIT - 1; ++i) {
+          const float w = seg.nk > 0 ? expf(part_ml[i][0][lane] - m_all) : 0.f;
+          l = fmaf(part_ml[i][1][lane], w, l);
+#pragma unroll
+          for (int d = 0; d < DB; ++d)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              const float4 f = part_o[i][d * 4 + g][lane];
+              o[d][4 * g] = fmaf(f.x, w, o[d][4 * g]);
+              o[d][4 * g + 1] = fmaf(f.y, w, o[d][4 * g + 1]);
+              o[d][4 * g + 2] = fmaf(f.z, w, o[d][4 * g + 2]);
+              o[d][4 * g + 3] = fmaf(f.w, w, o[d][4 * g + 3]);
+            }
+        }
+        m = m_all;
+      }
+    }
     const float l_tot = sum_across_halves(l);
-    if (q_ok) {
+    if (q_ok && part == 0) {
       const float inv = seg.nk > 0 ? 1.0f / l_tot : 0.f;
       float* op = out != nullptr ? out + (seg.row0 + qi) * C + h * DH + 4 * hh : nullptr;
       const long yoff = sc.y != nullptr ? (long)sc.gather_idx[seg.row0 + qi] * C + h * DH + 4 * hh : 0;
@@ -1137,10 +1255,24 @@ attn_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
       if (lse != nullptr && hh == 0) lse[h * lse_stride + seg.row0 + qi] = seg.nk > 0 ? m + logf(l_tot) : -INFINITY;
     }
   }
-  if (sc.y != nullptr) scatter_fill<float, DH>(sc, fr.b, fr.t0, fr.t1, h, C, lane, kWave);
+  if (sc.y != nullptr) scatter_fill<float, DH>(sc, fr.b, fr.t0, fr.t1, h, C, threadIdx.x, 64 * SPLIT);
 }
 
 // ------------------------------------------------------------------------------- host
+// fp32: four waves a unit where the units leave the chip idle and there are keys to split (2 x 196 tokens, 2 heads of 32: the
+// launch 8.3 -> 4.9 us)
+template <class... Args>
+static void launch_f32(int Dh, int B, int H, int nqb, hipStream_t st, Args... args) {
+  const dim3 grid(xcd_grid(nqb, H, B));
+  const bool split = nqb >= 4 && grid.x <= 768;
+#define SPA_LAUNCH_F32(D, W) hipLaunchKernelGGL((attn_fwd_f32_kernel<D, W>), grid, dim3(64 * W), 0, st, args...)
+  if (Dh == 32) {
+    if (split) SPA_LAUNCH_F32(32, 4); else SPA_LAUNCH_F32(32, 1);
+  } else {
+    if (split) SPA_LAUNCH_F32(64, 4); else SPA_LAUNCH_F32(64, 1);
+  }
+#undef SPA_LAUNCH_F32
+}
 static int attention_common(const char* fn, const void* q, const void* k, const void* v,
                             int64_t q_stride, int64_t k_stride, int64_t v_stride, const int32_t* cu, const int32_t* key_lens, int B,
                             int n_max, int H, int Dh, int dtype, float softmax_scale, void* out,
@@ -1170,17 +1302,12 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
   if (dtype == SPA_F32) {
     SPA_REQUIRE(!group_open(), SPA_ERR_UNSUPPORTED, "%s: fp32 calls cannot be part of a group", fn);
     const int nqb = (n_max + 31) / 32;
-    const dim3 grid(xcd_grid(nqb, H, B)), block(64);
-#define SPA_F32_LAUNCH(D)                                                                                \
-  hipLaunchKernelGGL((attn_fwd_f32_kernel<D>), grid, block, 0, st, (const float*)q, (const float*)k,    \
-                     (const float*)v, (long)q_stride, (long)k_stride, (long)v_stride, cu, key_lens, n_max, H, scale, (float*)out, lse, \
-                     lse_stride, sc, B, nqb)
-    if (Dh == 32) SPA_F32_LAUNCH(32); else SPA_F32_LAUNCH(64);
-#undef SPA_F32_LAUNCH
+    launch_f32(Dh, B, H, nqb, st, (const float*)q, (const float*)k, (const float*)v, (long)q_stride, (long)k_stride, (long)v_stride,
+               cu, key_lens, n_max, H, scale, (float*)out, lse, lse_stride, sc, B, nqb);
   } else {
     const float scale_log2 = scale * 1.4426950408889634f;
     FwdArgs args = {(const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_stride, (long)k_stride, (long)v_stride, v_scores,
-                    cu, key_lens, n_max, H, scale_log2, (__bf16*)out, lse, lse_stride, sc, B, 0, 0};
+                    cu, key_lens, n_max, H, scale_log2, (__bf16*)out, lse, lse_stride, sc, B, 0, 0, 1};
     const int form = v_scores != nullptr ? kFwdGated : sc.gathered ? kFwdGathered : kFwdPacked;
     const auto live = [&] { return key_lens == nullptr && live_tiles_apply(H, B); };
     // the tiled kernel's workgroups: resident together 3 waves per SIMD at head dim 32, 2 at 64
@@ -1200,7 +1327,8 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
         return g_noted[form].add(fn, args, (blocks + 7) / 8 * 8);
       }
       args.nqb = (n_max + 31) / 32;
-      return g_noted[form].add(fn, args, wave_groups(lpt64_grid(B, H, args.nqb)));
+      args.waves = unit_waves(args.nqb, xcd_grid(args.nqb, H, B));
+      return g_noted[form].add(fn, args, wave_groups(lpt64_grid(B, H, args.nqb), args.waves));
     }
 #define SPA_LAUNCH(KERNEL, GRID, BLOCK, ARGS, ...)                                                            \
   do {                                                                                                        \
@@ -1228,17 +1356,24 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
       args.nqb = nqb;
       // default: blocks dealt to the compute units by weight ("plain": numbered blindly)
       const bool step64 = opt.fwd_step64, plain = opt.fwd_plain;
-      if (!step64 && !plain && B <= kWave) {
-        const dim3 lgrid(lpt64_grid(B, H, nqb));
-        if (Dh == 32) SPA_LAUNCH_FORM(attn_fwd_bf16_wave_lpt64_kernel, lgrid, dim3(64), args, 32, 32);
-        else SPA_LAUNCH_FORM(attn_fwd_bf16_wave_lpt64_kernel, lgrid, dim3(64), args, 64, 32);
-      } else if (Dh == 32) {
-        if (step64) SPA_LAUNCH_FORM(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 32, 64);
-        else SPA_LAUNCH_FORM(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 32, 32);
+      const int waves = step64 ? 1 : unit_waves(nqb, grid.x);
+      const dim3 lgrid(lpt64_grid(B, H, nqb)), block(64 * waves);
+#define SPA_WAVE(KERNEL, GRID, D)                                                       \
+  do {                                                                                  \
+    if (waves == 2) SPA_LAUNCH_FORM(KERNEL, GRID, block, args, 2, D, 32);          \
+    else SPA_LAUNCH_FORM(KERNEL, GRID, block, args, 1, D, 32);                          \
+  } while (0)
+      if (step64) {
+        if (Dh == 32) SPA_LAUNCH_FORM(attn_fwd_bf16_wave_kernel, grid, block, args, 1, 32, 64);
+        else SPA_LAUNCH_FORM(attn_fwd_bf16_wave_kernel, grid, block, args, 1, 64, 64);
+      } else if (!plain && B <= kWave) {
+        if (Dh == 32) SPA_WAVE(attn_fwd_bf16_wave_lpt64_kernel, lgrid, 32);
+        else SPA_WAVE(attn_fwd_bf16_wave_lpt64_kernel, lgrid, 64);
       } else {
-        if (step64) SPA_LAUNCH_FORM(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 64, 64);
-        else SPA_LAUNCH_FORM(attn_fwd_bf16_wave_kernel, grid, dim3(64), args, 64, 32);
+        if (Dh == 32) SPA_WAVE(attn_fwd_bf16_wave_kernel, grid, 32);
+        else SPA_WAVE(attn_fwd_bf16_wave_kernel, grid, 64);
       }
+#undef SPA_WAVE
     } else if (!tiled && n_max <= 256 && form != kFwdGated) {
       // short segments: one workgroup per (image, head), whole segment in LDS
       const dim3 grid(H, B);
@@ -1362,27 +1497,31 @@ extern "C" int spa_selected_attention_unpack(const void* q, const void* k, const
   const float scale_log2 = scale * 1.4426950408889634f;
   const Scatter sc = {nullptr, nullptr, base, y, N, 0, 1, mask};
   const int nqb = (N + 31) / 32;
-  const dim3 grid(xcd_grid(nqb, H, B)), block(64);
+  const dim3 grid(xcd_grid(nqb, H, B));
   if (dtype == SPA_F32) {
     SPA_REQUIRE(!group_open(), SPA_ERR_UNSUPPORTED, "%s: fp32 calls cannot be part of a group", fn);
-    if (Dh == 32)
-      hipLaunchKernelGGL((attn_fwd_f32_kernel<32>), grid, block, 0, as_stream(stream), (const float*)q, (const float*)k,
-                         (const float*)v, (long)q_row_stride, (long)k_row_stride, (long)v_row_stride, nullptr, nullptr, N,
-                         H, scale, (float*)nullptr, (float*)nullptr, 0L, sc, B, nqb);
-    else
-      hipLaunchKernelGGL((attn_fwd_f32_kernel<64>), grid, block, 0, as_stream(stream), (const float*)q, (const float*)k,
-                         (const float*)v, (long)q_row_stride, (long)k_row_stride, (long)v_row_stride, nullptr, nullptr, N,
-                         H, scale, (float*)nullptr, (float*)nullptr, 0L, sc, B, nqb);
+    launch_f32(Dh, B, H, nqb, as_stream(stream), (const float*)q, (const float*)k, (const float*)v, (long)q_row_stride,
+               (long)k_row_stride, (long)v_row_stride, (const int32_t*)nullptr, (const int32_t*)nullptr, N, H, scale, (float*)nullptr,
+               (float*)nullptr, 0L, sc, B, nqb);
     return check_launch(fn);
   }
-  const FwdArgs args = {(const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_row_stride, (long)k_row_stride,
-                        (long)v_row_stride, nullptr, nullptr, nullptr, N, H, scale_log2, nullptr, nullptr, 0L, sc, B, nqb, 0};
+  FwdArgs args = {(const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_row_stride, (long)k_row_stride,
+                        (long)v_row_stride, nullptr, nullptr, nullptr, N, H, scale_log2, nullptr, nullptr, 0L, sc, B, nqb, 0, 1};
   if (group_open()) {
     SPA_REQUIRE(Dh == 32, SPA_ERR_UNSUPPORTED, "%s: this form cannot be part of a group", fn);
-    return g_noted[1].add(fn, args, wave_groups(grid.x));
+    args.waves = unit_waves(nqb, grid.x);
+    return g_noted[1].add(fn, args, wave_groups(grid.x, args.waves));
   }
-  if (Dh == 32) hipLaunchKernelGGL((attn_fwd_bf16_wave_mask_kernel<32, 32>), grid, block, 0, as_stream(stream), args);
-  else hipLaunchKernelGGL((attn_fwd_bf16_wave_mask_kernel<64, 32>), grid, block, 0, as_stream(stream), args);
+  const int waves = unit_waves(nqb, grid.x);
+#define SPA_MASK(D, W) hipLaunchKernelGGL((attn_fwd_bf16_wave_mask_kernel<D, 32, W>), grid, dim3(64 * W), 0, as_stream(stream), args)
+#define SPA_MASK_WAVES(D)                 \
+  do {                                    \
+    if (waves == 2) SPA_MASK(D, 2);  \
+    else SPA_MASK(D, 1);                  \
+  } while (0)
+  if (Dh == 32) SPA_MASK_WAVES(32); else SPA_MASK_WAVES(64);
+#undef SPA_MASK
+#undef SPA_MASK_WAVES
   return check_launch(fn);
 }
 

@@ -1,0 +1,65 @@
+"""Short-segment forward with the keys of a unit shared by several waves (small launches): lengths at the edges of the
+waves' steps of 32 keys, down to units whose second wave has no keys, images without and with all tokens selected."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+LENS = [0, 1, 31, 32, 33, 63, 64, 65, 95, 97, 128, 129, 160, 193]
+
+
+def _reference(q, k, v, lens, H, Dh):
+    """softmax(q k^T / sqrt(Dh)) v and its log-sum-exp of every segment, in float64."""
+    out, lse, at = torch.zeros_like(q), torch.zeros(H, q.shape[0], dtype=torch.float64), 0
+    for n in lens:
+        if n == 0:
+            continue
+        h = lambda t: t[at:at + n].view(n, H, Dh).transpose(0, 1)
+        s = (h(q) @ h(k).transpose(1, 2).contiguous()) / Dh ** 0.5
+        out[at:at + n] = (torch.softmax(s, 2) @ h(v).contiguous()).transpose(0, 1).reshape(n, H * Dh)
+        lse[:, at:at + n] = torch.logsumexp(s, 2)
+        at += n
+    return out, lse
+
+
+@pytest.mark.parametrize("form", ["packed", "gathered", "selected"])
+@pytest.mark.parametrize("dtype,H,Dh,N", [("bf16", 2, 64, 193), ("bf16", 3, 32, 256), ("bf16", 1, 32, 97), ("f32", 2, 32, 196),
+                                          ("f32", 1, 64, 193), ("f32", 2, 32, 300)])
+def test_units_of_several_waves(form, dtype, H, Dh, N):
+    from paper_2410_23608_amd import spa
+    if form == "selected" and N > 256:
+        pytest.skip("the mask form takes images of up to 256 tokens")
+    lens = [n for n in LENS if n <= N] + [N]
+    B, C, T, td = len(lens), H * Dh, sum(lens), torch.bfloat16 if dtype == "bf16" else torch.float32
+    assert N > 96 and B * H * ((N + 31) // 32) <= 768               # what makes several waves share a unit
+    g = torch.Generator().manual_seed(N + Dh)
+    rows = torch.cat([b * N + torch.randperm(N, generator=g)[:n].sort().values for b, n in enumerate(lens)])
+    mask = torch.zeros(B * N, dtype=torch.uint8)
+    mask[rows] = 1
+    mask = mask.cuda().view(B, N)
+    qkv = (1.5 * torch.randn(B * N, 3 * C, generator=g)).to(td)
+    ref, ref_lse = _reference(*(qkv[rows].double()[:, i * C:(i + 1) * C] for i in range(3)), lens, H, Dh)
+    t = qkv.cuda()
+    ints = lambda n: torch.zeros(n, dtype=torch.int32, device="cuda")
+    cu, gather, inv = ints(B + 1), ints(B * N), ints(B * N)
+    spa.spa_pack(None, mask, None, None, 0, None, cu, gather, inv, None)
+    y = torch.full((B, N, C), float("nan"), dtype=td, device="cuda")
+    out, lse = torch.zeros(B * N, C, dtype=td, device="cuda"), torch.zeros(H, B * N, device="cuda")
+    cols = lambda m: (m[:, :C], m[:, C:2 * C], m[:, 2 * C:])
+    if form == "selected":
+        spa.spa_selected_attention_unpack(*cols(t), mask, None, H, Dh, y)
+    elif form == "gathered":
+        spa.spa_gathered_attention_unpack(*cols(t), cu, gather, inv, None, H, Dh, y, out, lse)
+    else:
+        packed = torch.zeros_like(t)
+        packed[:T] = t[gather[:T].long()]
+        spa.spa_packed_attention_unpack(*cols(packed), cu, gather, inv, None, H, Dh, y, out, lse)
+    torch.cuda.synchronize()
+    got = y.view(B * N, C).cpu().double()
+    assert (got[mask.view(-1).cpu() == 0] == 0).all()
+    # bf16: probabilities and the result rounded once each (2^-9 of values up to 4 sigma = 6); fp32: sums of up to 300
+    # products of rounding 2^-24 on each, values up to 6
+    assert (got[rows] - ref).abs().max() <= (3e-2 if dtype == "bf16" else 1e-5)
+    if form != "selected":
+        assert (out[:T].cpu().double() - got[rows]).abs().max() == 0
+        assert (lse[:, :T].cpu().double() - ref_lse).abs().max() <= 1e-5
