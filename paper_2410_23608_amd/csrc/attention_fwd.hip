@@ -498,7 +498,7 @@ tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, c
   const int32_t* gi = gather_base<GATHER>(sc, seg.row0);
   const long q_src = q_ok ? source_row(gi, seg.row0, qi) : 0;   // (gathered: an index load, issued first)
   const int y_row = GATHER ? (int)q_src : sc.y != nullptr && q_ok ? sc.gather_idx[seg.row0 + qi] : 0;
-  PairStage<DH, 64 * NW, BN, GATHER != 0, GATHER != 0> stage;
+  PairStage<DH, 64 * NW, BN, GATHER != 0, GATHER != 0> stage(threadIdx.x);
   stage.gi = gi;
   stage.last = max(seg.nk - 1, 0);
   stage.source(0, k + h * DH, ks, seg.row0);
@@ -778,8 +778,10 @@ wave_attention(WaveLds<DH, STEP>* lds, int part, const Segment seg, int h, int q
 // of them have queries) that chain is the launch, so two waves share it, the merge costing 0.3 us.  With more units the
 // waves of those without queries take the others' slots.  us a step, 196 tokens an image, 6 heads of 64, two launches,
 // 1 / 2 / 4 waves: 8 images (336 units) 11.2 / 9.3 / 9.7, 16 images 12.0 / 10.0 / 10.5, 32 images (1344) 13.0 / 11.8 / 14.3,
-// 64 images 15.9 / 16.5 / 20.5.  Segments of up to 3 steps are not worth a merge.
-static int unit_waves(int nqb, long units) { return nqb >= 4 && units <= 1536 ? 2 : 1; }
+// 64 images 15.9 / 16.5 / 20.5; 32 x 256 tokens, 6 heads of 64 (1536) 15.9 / 14.1.  Head dim 32, 6 heads: 18 x 256 tokens (864)
+// 11.6 / 10.9, 32 x 256 (1536) 12.7 / 12.5, and beside other calls of a launch group, training, 100.0 / 101.4.
+// Segments of up to 3 steps are not worth a merge.
+static int unit_waves(int Dh, int nqb, long units) { return nqb >= 4 && units <= (Dh == 64 ? 1536 : 1024) ? 2 : 1; }
 
 template <int SPLIT, int DH, int STEP, int GATHER>
 __global__ void __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(STEP == 32 ? 3 : 1)))
@@ -1327,7 +1329,7 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
         return g_noted[form].add(fn, args, (blocks + 7) / 8 * 8);
       }
       args.nqb = (n_max + 31) / 32;
-      args.waves = unit_waves(args.nqb, xcd_grid(args.nqb, H, B));
+      args.waves = unit_waves(Dh, args.nqb, xcd_grid(args.nqb, H, B));
       return g_noted[form].add(fn, args, wave_groups(lpt64_grid(B, H, args.nqb), args.waves));
     }
 #define SPA_LAUNCH(KERNEL, GRID, BLOCK, ARGS, ...)                                                            \
@@ -1356,7 +1358,7 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
       args.nqb = nqb;
       // default: blocks dealt to the compute units by weight ("plain": numbered blindly)
       const bool step64 = opt.fwd_step64, plain = opt.fwd_plain;
-      const int waves = step64 ? 1 : unit_waves(nqb, grid.x);
+      const int waves = step64 ? 1 : unit_waves(Dh, nqb, grid.x);
       const dim3 lgrid(lpt64_grid(B, H, nqb)), block(64 * waves);
 #define SPA_WAVE(KERNEL, GRID, D)                                                       \
   do {                                                                                  \
@@ -1509,10 +1511,10 @@ extern "C" int spa_selected_attention_unpack(const void* q, const void* k, const
                         (long)v_row_stride, nullptr, nullptr, nullptr, N, H, scale_log2, nullptr, nullptr, 0L, sc, B, nqb, 0, 1};
   if (group_open()) {
     SPA_REQUIRE(Dh == 32, SPA_ERR_UNSUPPORTED, "%s: this form cannot be part of a group", fn);
-    args.waves = unit_waves(nqb, grid.x);
+    args.waves = unit_waves(Dh, nqb, grid.x);
     return g_noted[1].add(fn, args, wave_groups(grid.x, args.waves));
   }
-  const int waves = unit_waves(nqb, grid.x);
+  const int waves = unit_waves(Dh, nqb, grid.x);
 #define SPA_MASK(D, W) hipLaunchKernelGGL((attn_fwd_bf16_wave_mask_kernel<D, 32, W>), grid, dim3(64 * W), 0, as_stream(stream), args)
 #define SPA_MASK_WAVES(D)                 \
   do {                                    \
