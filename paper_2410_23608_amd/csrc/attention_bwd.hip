@@ -128,14 +128,15 @@ __device__ __forceinline__ void bwd_scores(const __bf16* at, const __bf16* bt, i
   }
 }
 
+// (LOOP: the role is called in a loop over blocks.)
 // dq role: 32 queries per wave against the keys of the segment.  S^T = K Q^T, dP^T = V dO^T: a lane holds 16
 // keys of one query, lse and D are one scalar per lane, dS^T is the B operand of dQ^T += K^T dS^T.
-template <int DH, int MODE>
+template <int DH, int MODE, bool LOOP>
 __device__ __forceinline__ void bwd_dq_role(BwdLongLds<DH>& lds, const BwdArgs& p, const Segment seg, int h, int q0) {
   constexpr int RS = DH + 8, KK = DH / 16, DB = DH / 32, BT = kBwdBT;
   constexpr bool GATED = MODE == kGated;
   using Stage = PairStage<DH, kBwdThreads, BT, GATED, GATED>;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
+  const int tid = LOOP ? fresh_thread_id() : threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
   const int qi = q0 + wv * 32 + l32, n = seg.nk;
   const bool wave_live = q0 + wv * 32 < n, q_ok = qi < n;
   const long C = (long)p.H * DH;
@@ -144,7 +145,7 @@ __device__ __forceinline__ void bwd_dq_role(BwdLongLds<DH>& lds, const BwdArgs& 
   const long q_row = seg.row0 + (q_ok ? qi : 0);
   const long tok_row = MODE != kPacked ? (long)gi[q_ok ? qi : 0] : q_row;
 
-  Stage st;
+  Stage st(tid);
   float gate[Stage::CPT] = {};
   st.gi = gi;
   st.last = n - 1;
@@ -231,12 +232,12 @@ __device__ __forceinline__ void bwd_dq_role(BwdLongLds<DH>& lds, const BwdArgs& 
 
 // dkdv role: 32 keys per wave against the queries.  S = Q K^T, dP = dO V^T: a lane holds 16 queries of one
 // key, P and dS are the B operands of dV^T += dO^T P and dK^T += Q^T dS.
-template <int DH, int MODE>
+template <int DH, int MODE, bool LOOP>
 __device__ __forceinline__ void bwd_dkdv_role(BwdLongLds<DH>& lds, const BwdArgs& p, const Segment seg, int h, int k0) {
   constexpr int RS = DH + 8, KK = DH / 16, DB = DH / 32, BT = kBwdBT;
   constexpr bool GATED = MODE == kGated;
   using Stage = PairStage<DH, kBwdThreads, BT, GATED, MODE != kPacked>;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
+  const int tid = LOOP ? fresh_thread_id() : threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
   const int ki = k0 + wv * 32 + l32, n = seg.nk;
   const bool wave_live = k0 + wv * 32 < n, k_ok = ki < n;
   const long C = (long)p.H * DH;
@@ -247,7 +248,7 @@ __device__ __forceinline__ void bwd_dkdv_role(BwdLongLds<DH>& lds, const BwdArgs
   const long k_row = seg.row0 + (k_ok ? ki : 0);
   const long tok_row = MODE != kPacked ? (long)gi[k_ok ? ki : 0] : k_row, src = GATED ? tok_row : k_row;
 
-  Stage st;
+  Stage st(tid);
   st.gi = gi;
   st.last = n - 1;
   st.source(0, p.q + h * DH, p.qs, seg.row0);
@@ -345,7 +346,7 @@ __device__ __forceinline__ void bwd_dkdv_role(BwdLongLds<DH>& lds, const BwdArgs
 
 // Both roles in one launch: each alone is bound by the chain of its longest workgroup (a wave walks the
 // tokens of its image).  Workgroup -> (xcd = id % 8, number inside the XCD): first the dkdv blocks, longest image
-// first (live_tile_wave), then the dq blocks in the same order: alternating roles would give every other unit only
+// first (live_order), then the dq blocks in the same order: alternating roles would give every other unit only
 // the longer of the two.  Waves of longer images run at a higher priority, as the launch ends with them.
 // Bound by vector instructions and the waits between them: per 32 x 32 block the two roles issue 14 MFMAs (448
 // cycles) and about 125 vector instructions, 32 of them exponentials (630 cycles), at three (head dim 64: two)
@@ -381,8 +382,8 @@ __device__ __forceinline__ void bwd_long_block(const BwdArgs& p, unsigned block,
     r0 = t.qb * kBwdRows;
   }
   if (r0 < seg.nk) {
-    if (dkdv) bwd_dkdv_role<DH, MODE>(lds, p, seg, h, r0);
-    else bwd_dq_role<DH, MODE>(lds, p, seg, h, r0);
+    if (dkdv) bwd_dkdv_role<DH, MODE, false>(lds, p, seg, h, r0);
+    else bwd_dq_role<DH, MODE, false>(lds, p, seg, h, r0);
   }
   __builtin_amdgcn_s_setprio(0);
   if (MODE != kPacked) {
@@ -398,10 +399,62 @@ __device__ __forceinline__ void bwd_long_block(const BwdArgs& p, unsigned block,
   }
 }
 
+// The same for calls of up to 64 segments and 512 (segment, head) pairs in a launch group, or with segments of up to 4
+// blocks: at most as many workgroups as are resident together, of which number g of an XCD's G takes blocks g, 2 G - 1 - g,
+// 2 G + g, ... of the order.  A grid with a workgroup for each block of the longest possible segments puts
+// thousands without a block, 3.5 us of a slot each, in front of the next call's (four stages of 16 images, 3136 to
+// 49 tokens: 2868 of 5280; the step 163 -> 156 us; 64 x 400 tokens, 6 heads of 64: 115 -> 112).  Long segments in a
+// launch of their own end with them, and are better dealt as slots become free (4 x 4200 tokens, 8 heads of 32: 91.6 against 93.0
+// us; 32 x 3136: 340 against 347).
+constexpr int bwd_long_slots(int DH) { return (DH == 32 ? 3 : 2) * 256; }
+template <int DH, int MODE>
+__device__ __forceinline__ void bwd_resident_block(const BwdArgs& p, unsigned block, unsigned blocks) {
+  __shared__ BwdLongLds<DH> lds;
+  __shared__ int s_order[5][64];
+  const int xcd = block & 7, G = blocks >> 3, g = there_and_back(block >> 3, G), lane = threadIdx.x & 63;
+  if (threadIdx.x < 64) {
+    const LiveOrder o = live_order(xcd, p.H, p.B, p.cu, kBwdRows, p.nblk);
+    s_order[0][lane] = o.len;
+    s_order[1][lane] = o.start;
+    s_order[2][lane] = o.img;
+    s_order[3][lane] = o.nb;
+    s_order[4][lane] = o.incl;
+  }
+  __syncthreads();
+  for (int round = 0;; ++round) {
+    const LiveOrder o = {s_order[0][lane], s_order[1][lane], s_order[2][lane], s_order[3][lane], s_order[4][lane]};
+    const LiveTile lt = live_pick<2>(o, xcd, round * G + (round & 1 ? G - 1 - g : g), p.H);
+    if (!lt.valid) break;
+    if (round > 0) __syncthreads();                  // every wave is past its last read of the tiles
+    const Segment seg = {lt.row0, lt.len, lt.len};
+    if (!lt.again) bwd_dkdv_role<DH, MODE, true>(lds, p, seg, lt.h, lt.qb * kBwdRows);
+    else bwd_dq_role<DH, MODE, true>(lds, p, seg, lt.h, lt.qb * kBwdRows);
+  }
+  if (MODE != kPacked) {
+    // gradients of the unselected tokens: zeroed by the workgroups without a block, which run beside the others, or by
+    // all where those are few; an even share of the XCD's eighth of the rows each, a quarter per wave
+    constexpr int NW = kBwdThreads / 64;
+    const int busy = min(G, 2 * __builtin_amdgcn_readfirstlane(s_order[4][63])), idle = G - busy;
+    const bool by_idle = 4 * idle >= G;
+    if (by_idle && g < busy) return;
+    const long from = p.tok.rows * xcd / 8, to = p.tok.rows * (xcd + 1) / 8;
+    const long units = (long)(by_idle ? idle : G) * NW, u = (long)(by_idle ? g - busy : g) * NW + (threadIdx.x >> 6);
+    const long per = (to - from + units - 1) / units, z0 = min(to, from + u * per), z1 = min(to, z0 + per);
+    zero_unselected_rows(p.dq, p.dqs, p.H * DH, p.tok.inv_pos, z0, z1, lane);
+    zero_unselected_rows(p.dk, p.dks, p.H * DH, p.tok.inv_pos, z0, z1, lane);
+    zero_unselected_rows(p.dv, p.dvs, p.H * DH, p.tok.inv_pos, z0, z1, lane);
+  }
+}
+
 template <int DH, int MODE>
 __global__ void __launch_bounds__(kBwdThreads) __attribute__((amdgpu_waves_per_eu(DH == 32 ? 3 : 2)))
 attn_bwd_long_bf16_kernel(const BwdArgs p) {
   bwd_long_block<DH, MODE>(p, blockIdx.x, gridDim.x);
+}
+template <int DH, int MODE>
+__global__ void __launch_bounds__(kBwdThreads) __attribute__((amdgpu_waves_per_eu(DH == 32 ? 3 : 2)))
+attn_bwd_resident_bf16_kernel(const BwdArgs p) {
+  bwd_resident_block<DH, MODE>(p, blockIdx.x, gridDim.x);
 }
 
 // D[h][j] = <dO_j, O_j> over head h's columns, for the packed rows j < cu[B]: DH / 8 adjacent
@@ -441,11 +494,14 @@ __global__ void __launch_bounds__(256) attn_bwd_dvec_group_kernel(const Members<
   const MemberBlock mb = member_of(m, blockIdx.x);
   bwd_dvec_block<32>(m.a[mb.s], mb.block, mb.blocks);
 }
-template <int MODE>
+template <int MODE, bool RESIDENT>
 __global__ void __launch_bounds__(kBwdThreads) __attribute__((amdgpu_waves_per_eu(3)))
 attn_bwd_group_kernel(const Members<BwdArgs> m) {
   const MemberBlock mb = member_of(m, blockIdx.x);
-  bwd_long_block<32, MODE>(m.a[mb.s], mb.block, mb.blocks);
+  if (RESIDENT) {
+    const BwdArgs a = m.a[mb.s];
+    bwd_resident_block<32, MODE>(a, mb.block, mb.blocks);
+  } else bwd_long_block<32, MODE>(m.a[mb.s], mb.block, mb.blocks);
 }
 static thread_local Noted<BwdArgs> g_noted[2], g_noted_dvec[2];      // packed, gated operands
 void group_forget_attention_bwd() { g_noted[0].n = g_noted[1].n = g_noted_dvec[0].n = g_noted_dvec[1].n = 0; }
@@ -456,8 +512,13 @@ static void flush_mode(hipStream_t st) {
   Members<BwdArgs> m;
   const unsigned dblocks = g_noted_dvec[g].members(m);
   hipLaunchKernelGGL(attn_bwd_dvec_group_kernel, dim3(dblocks), dim3(256), 0, st, m);
+  bool resident = true;
+  for (int i = 0; i < g_noted[g].n; ++i) resident = resident && live_tiles_apply(g_noted[g].a[i].H, g_noted[g].a[i].B);
+  for (int i = 0; resident && i < g_noted[g].n; ++i)
+    g_noted[g].blocks[i] = std::min(g_noted[g].blocks[i], (unsigned)bwd_long_slots(32));
   const unsigned blocks = g_noted[g].members(m);
-  hipLaunchKernelGGL(attn_bwd_group_kernel<MODE>, dim3(blocks), dim3(kBwdThreads), 0, st, m);
+  if (resident) hipLaunchKernelGGL((attn_bwd_group_kernel<MODE, true>), dim3(blocks), dim3(kBwdThreads), 0, st, m);
+  else hipLaunchKernelGGL((attn_bwd_group_kernel<MODE, false>), dim3(blocks), dim3(kBwdThreads), 0, st, m);
 }
 int group_flush_attention_bwd(hipStream_t st) {
   flush_mode<kTokens>(st);
@@ -949,24 +1010,28 @@ static int attention_bwd_common(const char* fn, const void* q, const void* k, co
     // long segments: D first, then both roles in one launch
     const int nblk = args.nblk;
     SPA_REQUIRE(2 * ((long)H * B + 8) * nblk < 2147483647L, SPA_ERR_INVALID_ARG, "%s: B*H*blocks must be < 2^30", fn);
-    const unsigned grid = 2 * xcd_grid(nblk, H, B);
+    const bool resident = nblk <= 4 && live_tiles_apply(H, B);
+    const unsigned all = 2 * xcd_grid(nblk, H, B), grid = resident && !group_open() ? std::min(all, (unsigned)bwd_long_slots(Dh)) : all;
     const unsigned dgrid = (unsigned)std::min<long>(((long)B * max_seqlen * H * (Dh / 8) + 255) / 256, 4096L);
     if (group_open()) {
       if (int rc = g_noted_dvec[v_scores != nullptr].add(fn, args, dgrid)) return rc;
       return g_noted[v_scores != nullptr].add(fn, args, grid);
     }
+#define SPA_BWD_MODE(KERNEL, D)                                                                                 \
+  do {                                                                                                          \
+    if (v_scores != nullptr) hipLaunchKernelGGL((KERNEL<D, kGated>), dim3(grid), dim3(kBwdThreads), 0, st, args); \
+    else if (at_tokens) hipLaunchKernelGGL((KERNEL<D, kTokens>), dim3(grid), dim3(kBwdThreads), 0, st, args);   \
+    else hipLaunchKernelGGL((KERNEL<D, kPacked>), dim3(grid), dim3(kBwdThreads), 0, st, args);                  \
+  } while (0)
 #define SPA_BWD_LONG(D)                                                                                         \
   do {                                                                                                          \
     hipLaunchKernelGGL((attn_bwd_dvec_kernel<D>), dim3(dgrid), dim3(256), 0, st, args);                         \
-    if (v_scores != nullptr)                                                                                    \
-      hipLaunchKernelGGL((attn_bwd_long_bf16_kernel<D, kGated>), dim3(grid), dim3(kBwdThreads), 0, st, args);   \
-    else if (at_tokens)                                                                                         \
-      hipLaunchKernelGGL((attn_bwd_long_bf16_kernel<D, kTokens>), dim3(grid), dim3(kBwdThreads), 0, st, args);  \
-    else                                                                                                        \
-      hipLaunchKernelGGL((attn_bwd_long_bf16_kernel<D, kPacked>), dim3(grid), dim3(kBwdThreads), 0, st, args);  \
+    if (resident) SPA_BWD_MODE(attn_bwd_resident_bf16_kernel, D);                                               \
+    else SPA_BWD_MODE(attn_bwd_long_bf16_kernel, D);                                                            \
   } while (0)
     if (Dh == 32) SPA_BWD_LONG(32); else SPA_BWD_LONG(64);
 #undef SPA_BWD_LONG
+#undef SPA_BWD_MODE
   }
   return check_launch(fn);
 }

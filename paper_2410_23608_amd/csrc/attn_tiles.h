@@ -467,6 +467,14 @@ __device__ __forceinline__ Segment lpt_segment(int rank, int B, const int32_t* c
 // 8 bf16 multiplied by a row scale, rounded again
 __device__ __forceinline__ bf16x8 scale_row(bf16x8 v, float s) { return float_to_bf16x8(bf16x8_to_float(v) * s); }
 
+// The thread's number, for code inside a loop over work units: what depends on it is computed anew for every unit instead
+// of being kept in registers from one to the next (the loop of the attention backward spilled 15 registers so).
+__device__ __forceinline__ int fresh_thread_id() {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  return tid;
+}
+
 // Where a tile stands in a segment's walk: the code of the last one masks, the one before it stores the last one.
 enum TileAt { kTileInside, kTileBeforeLast, kTileLast };
 template <class F>
@@ -487,6 +495,7 @@ template <int DH, int THREADS, int BT, bool IDX0, bool IDX1>
 struct PairStage {
   static constexpr int RS = DH + 8, CPR = DH / 8, CPT = BT * CPR / THREADS, RPP = THREADS / CPR;
   static_assert(BT * CPR % THREADS == 0, "whole passes");
+  const int tid;                 // this thread's number
   bf16x8 v[2][CPT];
   int idx[CPT];
   const __bf16* base[2];         // this thread's columns of row 0 (indexed) or of the segment's first row
@@ -494,9 +503,10 @@ struct PairStage {
   const int32_t* gi;
   int last;                      // the segment's last row
   int from;                      // first row of the tile in flight
-  __device__ __forceinline__ static int row(int t) { return (int)threadIdx.x / CPR + t * RPP; }
+  __device__ __forceinline__ explicit PairStage(int tid_) : tid(tid_) {}
+  __device__ __forceinline__ int row(int t) const { return tid / CPR + t * RPP; }
   __device__ __forceinline__ void source(int o, const __bf16* p, long row_stride, long row0) {
-    base[o] = p + threadIdx.x % CPR * 8 + ((o ? IDX1 : IDX0) ? 0 : row0 * row_stride);
+    base[o] = p + tid % CPR * 8 + ((o ? IDX1 : IDX0) ? 0 : row0 * row_stride);
     stride[o] = (int)row_stride;
   }
   __device__ __forceinline__ void index(int t0) {
@@ -524,7 +534,7 @@ struct PairStage {
     if (LAST) clear_past();
 #pragma unroll
     for (int t = 0; t < CPT; ++t) {
-      const int o = row(t) * RS + threadIdx.x % CPR * 8;
+      const int o = row(t) * RS + tid % CPR * 8;
       *reinterpret_cast<bf16x8*>(a + o) = v[0][t];
       *reinterpret_cast<bf16x8*>(b + o) = v[1][t];
     }
@@ -535,7 +545,7 @@ struct PairStage {
     if (LAST) clear_past();
 #pragma unroll
     for (int t = 0; t < CPT; ++t) {
-      const int o = row(t) * RS + threadIdx.x % CPR * 8;
+      const int o = row(t) * RS + tid % CPR * 8;
       *reinterpret_cast<bf16x8*>(a + o) = v[0][t];
       *reinterpret_cast<bf16x8*>(b + o) = scale_row(v[1][t], sigmoidf_dev(gate[t]));
     }
