@@ -46,11 +46,36 @@ __device__ __forceinline__ void widen(bf16x8 v, float (&f)[8]) {
   for (int i = 0; i < 8; ++i) f[i] = w[i];
 }
 
+// Sum over groups of G neighbouring lanes, in every lane, in the order of exchanges with lane ^ G/2, ^ G/4, ... ^ 1, in the
+// vector ALU: the two halves and the two 16-lane rows of a half by the lane swaps, ^ 8 as a rotation of the row by 8, ^ 4 as
+// one by 4 once both halves of a row hold the same (groups of 8: as two shifts), ^ 2 and ^ 1 inside a quad.  An
+// exchange through LDS takes 85 cycles, one of these 8 to 16, and the dot products wait for each of them.
+template <int CTRL, int BANKS = 0xF>
+__device__ __forceinline__ float dpp_move(float v, float other = 0.f) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, other), __builtin_bit_cast(int, v), CTRL, 0xF, BANKS, false));
+}
+__device__ __forceinline__ float add_lane_xor32(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  const unsigned a = r[0], b = r[1];
+  return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
+}
+__device__ __forceinline__ float add_lane_xor16(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned a = r[0], b = r[1];
+  return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
+}
 template <int G>
 __device__ __forceinline__ float group_sum(float v) {
-#pragma unroll
-  for (int o = G / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+  constexpr int kRor = 0x120, kShl = 0x100, kShr = 0x110;
+  if (G > 32) v = add_lane_xor32(v);
+  if (G > 16) v = add_lane_xor16(v);
+  if (G > 8) v += dpp_move<kRor + 8>(v);
+  if (G > 8) v += dpp_move<kRor + 4>(v);
+  else v += dpp_move<kShr + 4, 0xA>(v, dpp_move<kShl + 4, 0x5>(v));
+  v += dpp_move<0x4E>(v);                                  // quad_perm [2, 3, 0, 1]
+  return v + dpp_move<0xB1>(v);                            // quad_perm [1, 0, 3, 2]
 }
 
 // Lanes per token: by the row's 16-byte chunks (the same for every launch of the gate)
@@ -564,20 +589,24 @@ __device__ __forceinline__ void gate_bwd_block(const GateBwdArgs<T>& a, unsigned
     for (int u = 0; u < U; ++u) {
       const long tok = base + u * kGroups;
       float xf[IT][VE], df[IT][VE];
-      float dot = 0.f, g = 0.f;
+      float dot = 0.f;
 #pragma unroll
       for (int it = 0; it < IT; ++it) {
         widen(xr[u][it], xf[it]);
         widen(dr[u][it], df[it]);
 #pragma unroll
-        for (int e = 0; e < VE; ++e) {
-          dot = fmaf(df[it][e], xf[it][e], dot);
-          g = fmaf(xf[it][e], wv[it][e], g);
-        }
+        for (int e = 0; e < VE; ++e) dot = fmaf(df[it][e], xf[it][e], dot);
       }
       dot = group_sum<G>(dot);
       bool own = tok < t1;
-      if (s_up != nullptr) own = own && group_sum<G>(g) + bias >= up[u];   // else the up-scale score won the max (see gate_chains)
+      if (s_up != nullptr) {                             // (uniform) did the up-scale score win the max? (see gate_chains)
+        float g = 0.f;
+#pragma unroll
+        for (int it = 0; it < IT; ++it)
+#pragma unroll
+          for (int e = 0; e < VE; ++e) g = fmaf(xf[it][e], wv[it][e], g);
+        own = own && group_sum<G>(g) + bias >= up[u];
+      }
       const float p = sigmoidf_dev(s[u]);
       const float y = lab[u] != 0 ? 1.f : 0.f;
       float ds = loss_scale * (p - y);
@@ -612,13 +641,14 @@ __device__ __forceinline__ void gate_bwd_block(const GateBwdArgs<T>& a, unsigned
 
   // fold: the groups of a wave by exchanges, then one row per wave
 #pragma unroll
-  for (int o = G; o < kWave; o <<= 1)
+  for (int it = 0; it < IT; ++it)
 #pragma unroll
-    for (int it = 0; it < IT; ++it)
-#pragma unroll
-      for (int e = 0; e < VE; ++e) dwa[it][e] += __shfl_xor(dwa[it][e], o, kWave);
-  loss_acc = wave_sum(loss_acc);
-  db_acc = wave_sum(db_acc);
+    for (int e = 0; e < VE; ++e) {
+      if (G <= 16) dwa[it][e] = add_lane_xor16(dwa[it][e]);
+      if (G <= 32) dwa[it][e] = add_lane_xor32(dwa[it][e]);
+    }
+  loss_acc = group_sum<kWave>(loss_acc);
+  db_acc = group_sum<kWave>(db_acc);
   const int wv_id = threadIdx.x / kWave;
   if ((threadIdx.x & (kWave - 1)) < G) {
 #pragma unroll
@@ -698,8 +728,7 @@ __device__ __forceinline__ void gate_bwd_reduce_block(const GateReduceArgs& g, i
   float a = 0.f;
 #pragma unroll
   for (int i = 0; i < kRows; ++i) a += v[i];
-  a += __shfl_xor(a, 16, kWave);
-  a += __shfl_xor(a, 32, kWave);
+  a = add_lane_xor32(add_lane_xor16(a));
   if ((threadIdx.x & 63) < 16) red[threadIdx.x >> 6][cl] = a;
   __syncthreads();
   if (threadIdx.x < 16 && c < C + 2) {
