@@ -1,7 +1,11 @@
 // The main loop shared by the projection GEMMs (bf16 MFMA, fp32 accumulation): operand tiles go from
 // memory straight to LDS (global_load_lds, 16 bytes a lane) through a ring of STAGES buffers, so the
 // loads of the next tiles are in flight without a register, a store or a wait for each other; the only
-// waits are one counted vmcnt and one barrier per 64-deep contraction step.
+// waits are one counted vmcnt and one barrier per 64-deep contraction step.  The barrier stands before the last
+// products of the step before it, whose operands are in registers by then: they cover the first LDS reads of the
+// step, and all STAGES buffers can be filled before the first (with the barrier after them and one load after the
+// other behind it a step of 256 x 256 took 3900 cycles, 830 of them at the barrier, 1600 for 8 loads and 1250 for
+// the products, 64 of 32 cycles on a SIMD; now 3170).
 //
 // A direct load puts a wave's 64 pieces of 16 bytes next to each other, so rows cannot be padded;
 // instead the pieces of a row are permuted on the way in (each lane chooses which piece it fetches) and
@@ -30,15 +34,32 @@ __device__ __forceinline__ void load_to_lds(const __bf16* src, uint32_t dst) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(src) : "memory", "m0");
 }
 template <int N>
-__device__ __forceinline__ void wait_vmem() {      // at most N vector memory operations still in flight
+__device__ __forceinline__ void wait_memory() {    // at most N vector memory operations still in flight, and no LDS read
   static_assert(N >= 0 && N < 64, "vmcnt has six bits");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0xF70);
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x070);
 }
 
-// Operand with the contraction along its rows: fragment of rows r0 .. r0+31, contraction 16 kk .. + 15.
-__device__ __forceinline__ bf16x8 rows_frag(const __bf16* tile, int r0, int kk, int l32, int hh) {
-  const int r = r0 + l32;
-  return *reinterpret_cast<const bf16x8*>(tile + r * kGaK + (((2 * kk + hh) ^ (r & 7)) << 3));
+// The matrix instruction of a tile: EDGE x EDGE products of DEPTH contraction elements.  Lane l holds row (or
+// column) l % EDGE and elements 8 (l / EDGE) .. + 7 of an operand; of a product, column l % EDGE and, in group g,
+// rows row(g, l) .. + 3.
+struct Mfma32 {
+  static constexpr int kEdge = 32, kDepth = 16, kGroups = 4;
+  typedef floatx16 Acc;
+  __device__ static __forceinline__ Acc mul(bf16x8 a, bf16x8 b, Acc c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
+  __device__ static __forceinline__ int row(int g, int lane) { return 8 * g + 4 * (lane >> 5); }
+};
+struct Mfma16 {
+  static constexpr int kEdge = 16, kDepth = 32, kGroups = 1;
+  typedef floatx4 Acc;
+  __device__ static __forceinline__ Acc mul(bf16x8 a, bf16x8 b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+  __device__ static __forceinline__ int row(int, int lane) { return 4 * (lane >> 4); }
+};
+
+// Operand with the contraction along its rows: fragment of rows r0 .. + EDGE - 1, contraction DEPTH kk .. + DEPTH - 1.
+template <class MF>
+__device__ __forceinline__ bf16x8 rows_frag(const __bf16* tile, int r0, int kk, int lane) {
+  const int r = r0 + lane % MF::kEdge;
+  return *reinterpret_cast<const bf16x8*>(tile + r * kGaK + (((MF::kDepth / 8 * kk + lane / MF::kEdge) ^ (r & 7)) << 3));
 }
 // Operand with the contraction down its rows (COLS columns): fragment of columns c0 .. c0+31, contraction
 // rows 16 kk .. + 15, by the transposing read: within each block of 16 lanes lane i, element e, receives
@@ -56,22 +77,45 @@ __device__ __forceinline__ bf16x8 deep_frag(const __bf16* tile, int kk, int c0, 
   return __builtin_shufflevector(l4, h4, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// Which piece of which row a thread fetches: piece `col` (elements) of tile row row0 + u * row_step for
-// u = 0 .. count - 1.
+// Deep operand in blocks of 64 columns ([columns / 64][64][64]): fragment of columns c0 .. c0+15, contraction rows
+// 32 kk .. + 31.  Piece c of row r sits at c ^ (2 (r / 2 % 2) + 4 (r / 8 % 2)): the 8 rows that 32 lanes read
+// together fall on distinct banks.
+__device__ __forceinline__ bf16x8 deep_block_frag(const __bf16* tile, int kk, int c0, int lane) {
+  const int blk = lane >> 4, s = lane & 15, row = 32 * kk + 8 * blk + (s >> 2);
+  const int piece = (((c0 & 63) >> 3) + ((s & 3) >> 1)) ^ (2 * (s >> 3) + 4 * (blk & 1));
+  const __bf16* p = tile + (c0 >> 6) * (64 * kGaK) + row * 64 + piece * 8 + 4 * (s & 1);
+  typedef shortx4_lds __attribute__((address_space(3))) * lds_ptr;
+  const shortx4_lds lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p));
+  const shortx4_lds hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 4 * 64));
+  const bf16x4 l4 = __builtin_bit_cast(bf16x4, lo), h4 = __builtin_bit_cast(bf16x4, hi);
+  return __builtin_shufflevector(l4, h4, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// Which piece a thread fetches: piece `col` (elements) of tile row `row` for u = 0 .. count - 1.
 template <int ROWS, int THREADS>
 struct RowsPieces {
   static constexpr int kCount = ROWS * 8 / THREADS, kRowStep = THREADS / 8;
   static_assert(kRowStep % 8 == 0, "a thread keeps its permuted column");
-  __device__ static __forceinline__ int row0(int tid) { return tid >> 3; }
-  __device__ static __forceinline__ int col(int tid) { return ((tid & 7) ^ ((tid >> 3) & 7)) * 8; }
+  __device__ static __forceinline__ int row(int tid, int u) { return (tid >> 3) + u * kRowStep; }
+  __device__ static __forceinline__ int col(int tid, int) { return ((tid & 7) ^ ((tid >> 3) & 7)) * 8; }
 };
 template <int COLS, int THREADS>
 struct DeepPieces {
   static constexpr int kPerRow = COLS / 8, kCount = kGaK * kPerRow / THREADS, kRowStep = THREADS / kPerRow;
   static_assert(kRowStep % 4 == 0, "a thread keeps its permuted column");
-  __device__ static __forceinline__ int row0(int tid) { return tid / kPerRow; }
-  __device__ static __forceinline__ int col(int tid) {
+  __device__ static __forceinline__ int row(int tid, int u) { return tid / kPerRow + u * kRowStep; }
+  __device__ static __forceinline__ int col(int tid, int) {
     return ((tid % kPerRow) ^ (4 * ((tid / kPerRow) & 3))) * 8;
+  }
+};
+template <int COLS, int THREADS>
+struct DeepBlocks {                  // one block of 64 columns a step of u: a thread keeps its row
+  static constexpr int kCount = COLS / 64;
+  static_assert(THREADS == kGaK * 8, "a piece a thread and block");
+  __device__ static __forceinline__ int row(int tid, int) { return tid >> 3; }
+  __device__ static __forceinline__ int col(int tid, int u) {
+    const int r = tid >> 3;
+    return u * 64 + ((tid & 7) ^ (2 * (r >> 1 & 1) + 4 * (r >> 3 & 1))) * 8;
   }
 };
 
@@ -79,64 +123,98 @@ struct DeepPieces {
 // are B's index and whose columns are A's.  The wave's block is TM * 32 of A by TN * 32 of B.
 // next_a(u, t) / next_b(u, t): address of the thread's u-th piece of step t (called for t = 0, 1, ... in
 // order, so they may step a pointer).  frag_a(tile, i, kk), frag_b(tile, j, kk): fragments;
-// beside(af): called with the A fragments of every 16 contraction elements.  All threads call it.  On
+// beside(af): called with the A fragments of every 16 contraction elements; last(): before the last barrier.  All threads
+// call it.  On
 // return nothing is in flight and every wave is past its last read of the buffers.
 struct Nothing {
   template <class T> __device__ __forceinline__ void operator()(const T&) const {}
 };
-template <int A_ELEMS, int B_ELEMS, int NA, int NB, int STAGES, int THREADS, int TM, int TN, class FA, class FB, class RA, class RB,
-          class BS = Nothing>
+template <class MF, int A_ELEMS, int B_ELEMS, int NA, int NB, int STAGES, int THREADS, int TM, int TN, class FA, class FB, class RA,
+          class RB, class LS, class BS = Nothing>
 __device__ __forceinline__ void gemm_async_loop(__bf16* lds, int nk, FA&& next_a, FB&& next_b, RA&& frag_a, RB&& frag_b,
-                                                floatx16 (&acc)[TM][TN], BS&& beside = BS{}) {
-  constexpr int STAGE = A_ELEMS + B_ELEMS, KK = kGaK / 16;
+                                                typename MF::Acc (&acc)[TM][TN], LS&& last, BS&& beside = BS{}) {
+  constexpr int STAGE = A_ELEMS + B_ELEMS, KK = kGaK / MF::kDepth;
+  // Products between two loads: with two waves a SIMD in one workgroup the loads are dealt among the products, each
+  // occupies the wave until the unit's address path takes it (16 cycles a load of 1 KB and wave); with one wave a
+  // SIMD, or two of workgroups that are not in step, they go first (dealt out: 2304 -> 768, 1568 rows, 26 -> 32 us).
+  constexpr int GAP = THREADS == 256 ? 0 : STAGES == 2 ? 2 : KK * TM * TN / (NA + NB);
+  constexpr int GAP1 = GAP > 0 ? GAP : 1;
+  static_assert((NA + NB - 1) * GAP < KK * TM * TN, "every load of a step has its place");
   const uint32_t wave_dst = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds +
                             __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 1024;
-  auto issue = [&](int t, int stage) {
-    const uint32_t a = wave_dst + stage * (STAGE * 2), b = a + A_ELEMS * 2;
-#pragma unroll
-    for (int u = 0; u < NA; ++u) load_to_lds(next_a(u, t), a + u * (THREADS * 16));
-#pragma unroll
-    for (int u = 0; u < NB; ++u) load_to_lds(next_b(u, t), b + u * (THREADS * 16));
+  auto issue = [&](int q, int t, int stage) {       // load q of step t
+    const uint32_t a = wave_dst + stage * (STAGE * 2);
+    if (q < NA) load_to_lds(next_a(q, t), a + q * (THREADS * 16));
+    else load_to_lds(next_b(q - NA, t), a + A_ELEMS * 2 + (q - NA) * (THREADS * 16));
   };
 #pragma unroll
-  for (int s = 0; s < STAGES - 1; ++s)
-    if (s < nk) issue(s, s);
+  for (int s = 0; s < STAGES; ++s)
+    if (s < nk) {
+#pragma unroll
+      for (int q = 0; q < NA + NB; ++q) issue(q, s, s);
+    }
+  bf16x8 af[2][TM], bfr[2][TN];
   int stage = 0;
   for (int t = 0; t < nk; ++t) {
-    // this wave's pieces of step t have arrived (near the end fewer younger steps are in flight)
-    if (STAGES == 2 || t + STAGES - 2 >= nk) wait_vmem<0>();
-    else wait_vmem<(STAGES - 2) * (NA + NB)>();
-    __builtin_amdgcn_s_barrier();               // and everybody's; and step t - 1 has been read by all
+    // this wave's pieces of step t have arrived (near the end fewer younger steps are in flight), and its
+    // reads of step t - 1
+    if (t == 0 && STAGES <= nk) wait_memory<(STAGES - 1) * (NA + NB)>();
+    else if (STAGES == 2 || t == 0 || t + STAGES - 2 >= nk) wait_memory<0>();
+    else wait_memory<(STAGES - 2) * (NA + NB)>();
+    __builtin_amdgcn_s_barrier();               // and everybody's
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
     const __bf16* a = lds + stage * STAGE;
     const __bf16* b = a + A_ELEMS;
-    // the fragments of 16 contraction elements are read while the MFMAs of the 16 before run; left to
-    // itself the compiler puts every read right before its use and the two never overlap
-    bf16x8 af[2][TM], bfr[2][TN];
     auto read = [&](int kk) {
 #pragma unroll
       for (int i = 0; i < TM; ++i) af[kk & 1][i] = frag_a(a, i, kk);
 #pragma unroll
       for (int j = 0; j < TN; ++j) bfr[kk & 1][j] = frag_b(b, j, kk);
     };
-    read(0);
-    __builtin_amdgcn_sched_barrier(0);
-    if (t + STAGES - 1 < nk) issue(t + STAGES - 1, stage == 0 ? STAGES - 1 : stage - 1);
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      if (kk + 1 < KK) read(kk + 1);
-      __builtin_amdgcn_sched_barrier(0);
+    const int freed = stage == 0 ? STAGES - 1 : stage - 1;        // the buffer of step t - 1
+    const bool more = t > 0 && t + STAGES - 1 < nk;
+    auto multiply = [&](int kk, int group) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[kk & 1][j], af[kk & 1][i], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < TN; ++j) {
+          acc[i][j] = MF::mul(bfr[kk & 1][j], af[kk & 1][i], acc[i][j]);
+          const int n = (group * TM + i) * TN + j;
+          if (GAP > 0 && n % GAP1 == 0 && n / GAP1 < NA + NB) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (more) issue(n / GAP1, t + STAGES - 1, freed);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
       beside(af[kk & 1]);
       __builtin_amdgcn_sched_barrier(0);
+    };
+    read(0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (GAP == 0 && more) {
+#pragma unroll
+      for (int q = 0; q < NA + NB; ++q) issue(q, t + STAGES - 1, freed);
+    }
+    if (t > 0) multiply(KK - 1, 0);
+#pragma unroll
+    for (int kk = 0; kk + 1 < KK; ++kk) {
+      read(kk + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(kk, kk + 1);
     }
     stage = stage + 1 == STAGES ? 0 : stage + 1;
   }
-  wait_vmem<0>();
+  last();
   __syncthreads();
+  if (nk > 0) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        acc[i][j] = MF::mul(bfr[1][j], af[1][i], acc[i][j]);
+    beside(af[1]);
+  }
 }
 
 }  // namespace spa

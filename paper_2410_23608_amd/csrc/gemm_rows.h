@@ -12,53 +12,62 @@ namespace spa {
 // Workgroup tile BM x BN, WGM x WGN waves, each wave (BM / WGM) x (BN / WGN) of the output.
 // kDeep = false: out = A W^T, W [ncols][kc] (forward); kDeep = true: out = A W, W [kc][ncols] (input side
 // of the backward).  Either way the contraction has kc elements and runs along the rows of A.
-template <bool kScale, bool kDeep, int BM, int BN, int WGM, int WGN, int STAGES>
+template <class MF, bool kScale, bool kDeep, bool LOOP, int BM, int BN, int WGM, int WGN, int STAGES>
 __device__ __forceinline__ void gemm_rows_block(const GemmArgs& p, unsigned char* gemm_smem, unsigned block, unsigned blocks) {
-  constexpr int THREADS = 64 * WGM * WGN, TM = BM / WGM / 32, TN = BN / WGN / 32;
+  constexpr int E = MF::kEdge, THREADS = 64 * WGM * WGN, TM = BM / WGM / E, TN = BN / WGN / E;
+  static_assert(BM == WGM * TM * E && BN == WGN * TN * E, "whole matrix tiles");
   using PA = RowsPieces<BM, THREADS>;
-  using PB = typename std::conditional<kDeep, DeepPieces<BN, THREADS>, RowsPieces<BN, THREADS>>::type;
+  using PB = typename std::conditional<!kDeep, RowsPieces<BN, THREADS>,
+                                      typename std::conditional<E == 16, DeepBlocks<BN, THREADS>, DeepPieces<BN, THREADS>>::type>::type;
   __bf16* lds = reinterpret_cast<__bf16*>(gemm_smem);
   __shared__ float bias_s[BN];     // bias of the tile's output columns (0 past the edge or without bias)
   __shared__ int o_row[BM];        // output row of every tile row
 
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
   // Tile order.  Workgroup ids go to the 8 XCDs round-robin (id % 8) and each XCD has its own
   // L2.  The LIVE tiles (the row count is only known here, on the device) are numbered m-major
   // and cut into 8 equal contiguous ranges, one per XCD: the workgroups that share a block of A
   // rows run on one XCD, and every XCD gets the same number of tiles.
   const int M = p.total != nullptr ? min(p.total[0], p.m_cap) : p.m_cap;
-  const int live_tiles = ((M + BM - 1) / BM) * p.n_tiles, per_xcd = (live_tiles + 7) >> 3;
-  const int xcd = block & 7, jx = block >> 3, tile_id = xcd * per_xcd + jx;
-  if (jx < per_xcd && tile_id < live_tiles) {
-    const int mt = tile_id / p.n_tiles, nt = tile_id - mt * p.n_tiles;
+  const int n_tiles = (p.ncols + BN - 1) / BN, live_tiles = ((M + BM - 1) / BM) * n_tiles, per_xcd = (live_tiles + 7) >> 3;
+  // A workgroup takes the tiles jx, jx + blocks / 8, ... of its XCD's range.
+  const int xcd = block & 7;
+  for (int jx = block >> 3; jx < per_xcd && xcd * per_xcd + jx < live_tiles; jx += blocks >> 3) {
+    const int tid = LOOP ? fresh_thread_id() : threadIdx.x, lane = tid & 63, wv = tid >> 6, tile_id = xcd * per_xcd + jx;
+    const int mt = tile_id / n_tiles, nt = tile_id - mt * n_tiles;
     const int m0 = mt * BM, n0 = nt * BN;
-    const int wm = (wv / WGN) * TM * 32, wn = (wv % WGN) * TN * 32;
+    const int wm = (wv / WGN) * TM * E, wn = (wv % WGN) * TN * E;
 
     // rows past the end fetch the last valid row and columns past the edge a valid column: they only
     // reach outputs that are never stored
     const __bf16* ap[PA::kCount];
     const __bf16* bp[PB::kCount];
-    const int a_col = PA::col(tid), b_col = PB::col(tid);
+    const int a_col = PA::col(tid, 0);
+    int a_row[PA::kCount];
 #pragma unroll
-    for (int u = 0; u < PA::kCount; ++u) {
-      const int r = min(m0 + PA::row0(tid) + u * PA::kRowStep, M - 1);
-      ap[u] = p.a + (p.a_idx != nullptr ? (long)p.a_idx[r] : (long)r) * p.lda + a_col;
+    for (int u = 0; u < PA::kCount; ++u) a_row[u] = min(m0 + PA::row(tid, u), M - 1);
+    if (p.a_idx != nullptr) {
+#pragma unroll
+      for (int u = 0; u < PA::kCount; ++u) a_row[u] = p.a_idx[a_row[u]];
     }
+    // bias and output row of the thread's column and row; they go to the tables when the products are done
+    static_assert(BM <= THREADS && BN <= THREADS, "one of each a thread");
+    __bf16 bias_v = static_cast<__bf16>(0.f);
+    int o_v = m0 + tid;
+    if (p.bias != nullptr && tid < BN && n0 + tid < p.ncols) bias_v = p.bias[n0 + tid];
+    if (p.o_idx != nullptr && tid < BM && m0 + tid < M) o_v = p.o_idx[m0 + tid];
+#pragma unroll
+    for (int u = 0; u < PA::kCount; ++u) ap[u] = p.a + (long)a_row[u] * p.lda + a_col;
     float row_scale[TM];
     if (kScale) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i) row_scale[i] = p.scores[p.a_idx[min(m0 + wm + i * 32 + l32, M - 1)]];
+      for (int i = 0; i < TM; ++i) row_scale[i] = p.scores[p.a_idx[min(m0 + wm + i * E + lane % E, M - 1)]];
     }
 #pragma unroll
     for (int u = 0; u < PB::kCount; ++u) {
-      const int r = PB::row0(tid) + u * PB::kRowStep;
+      const int r = PB::row(tid, u), b_col = PB::col(tid, u);
       bp[u] = kDeep ? p.w + (long)r * p.ncols + (n0 + b_col < p.ncols ? n0 + b_col : n0)
                     : p.w + (long)min(n0 + r, p.ncols - 1) * p.kc + b_col;
     }
-    for (int t = tid; t < BN; t += THREADS)
-      bias_s[t] = p.bias != nullptr && n0 + t < p.ncols ? static_cast<float>(p.bias[n0 + t]) : 0.f;
-    for (int t = tid; t < BM; t += THREADS) o_row[t] = p.o_idx != nullptr && m0 + t < M ? p.o_idx[m0 + t] : m0 + t;
-
     const int nk = (p.kc + kGaK - 1) / kGaK, k_tail = p.kc % kGaK;
     const __bf16* zeros = reinterpret_cast<const __bf16*>(gemm_zeros);
     const long b_step = kDeep ? (long)kGaK * p.ncols : kGaK;
@@ -72,30 +81,35 @@ __device__ __forceinline__ void gemm_rows_block(const GemmArgs& p, unsigned char
     auto next_b = [&](int u, int t) {
       const __bf16* g = bp[u];
       bp[u] += b_step;
-      if (k_tail != 0 && t == nk - 1 && (kDeep ? PB::row0(tid) + u * PB::kRowStep : b_col) >= k_tail) g = zeros;
+      if (k_tail != 0 && t == nk - 1 && (kDeep ? PB::row(tid, u) : PB::col(tid, u)) >= k_tail) g = zeros;
       return g;
     };
-    auto frag_a = [&](const __bf16* tile, int i, int kk) { return rows_frag(tile, wm + i * 32, kk, l32, hh); };
+    auto frag_a = [&](const __bf16* tile, int i, int kk) { return rows_frag<MF>(tile, wm + i * E, kk, lane); };
     auto frag_b = [&](const __bf16* tile, int j, int kk) {
-      if constexpr (kDeep) return deep_frag<BN>(tile, kk, wn + j * 32, lane);
-      else return rows_frag(tile, wn + j * 32, kk, l32, hh);
+      if constexpr (kDeep && E == 16) return deep_block_frag(tile, kk, wn + j * E, lane);
+      else if constexpr (kDeep) return deep_frag<BN>(tile, kk, wn + j * E, lane);
+      else return rows_frag<MF>(tile, wn + j * E, kk, lane);
     };
-    floatx16 acc[TM][TN];
+    auto tables = [&] {
+      if (tid < BN) bias_s[tid] = static_cast<float>(bias_v);
+      if (tid < BM) o_row[tid] = o_v;
+    };
+    typename MF::Acc acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    gemm_async_loop<BM * kGaK, BN * kGaK, PA::kCount, PB::kCount, STAGES, THREADS, TM, TN>(lds, nk, next_a, next_b, frag_a,
-                                                                                           frag_b, acc);
+        for (int r = 0; r < 4 * MF::kGroups; ++r) acc[i][j][r] = 0.f;
+    gemm_async_loop<MF, BM * kGaK, BN * kGaK, PA::kCount, PB::kCount, STAGES, THREADS, TM, TN>(lds, nk, next_a, next_b, frag_a,
+                                                                                               frag_b, acc, tables);
 
-    // epilogue: scale, bias, bf16; 32 rows of the wave at a time are parked in its own part of LDS (LDS
+    // epilogue: scale, bias, bf16; the EDGE rows of a row of matrix tiles at a time are parked in its own part of LDS (LDS
     // operations of a wave complete in order) and leave as whole 16-byte pieces.  The pieces of the residual are
     // fetched together, pieces past the edge from a valid place (one at a time where they are added, each waits
     // for memory: the output projection of 64 x 196 tokens of 384 columns 11.4 -> 9.8 us)
-    constexpr int NC = TN * 32, ORS = NC + 8, PIECES = NC / 8, PER_LANE = 32 * PIECES / 64;
-    static_assert(WGM * WGN * 2 * 32 * ORS <= STAGES * (BM + BN) * kGaK, "output staging fits in the operand buffers");
+    constexpr int NC = TN * E, ORS = NC + 8, PIECES = NC / 8, PER_LANE = E * PIECES / 64;
+    static_assert(E * PIECES % 64 == 0 && WGM * WGN * 2 * E * ORS <= STAGES * (BM + BN) * kGaK, "output staging fits in the operand buffers");
     auto epilogue = [&](auto with_residual) {
       constexpr bool kResidual = decltype(with_residual)::value;
       bf16x8 res[kResidual ? TM : 1][kResidual ? PER_LANE : 1];
@@ -104,27 +118,27 @@ __device__ __forceinline__ void gemm_rows_block(const GemmArgs& p, unsigned char
         for (int i = 0; i < TM; ++i)
 #pragma unroll
           for (int u = 0; u < PER_LANE; ++u) {
-            const int c = lane + 64 * u, row = min(wm + i * 32 + c / PIECES, M - 1 - m0), n = n0 + wn + c % PIECES * 8;
+            const int c = lane + 64 * u, row = min(wm + i * E + c / PIECES, M - 1 - m0), n = n0 + wn + c % PIECES * 8;
             res[i][u] = *reinterpret_cast<const bf16x8*>(p.residual + (long)o_row[row] * p.ldo + (n < p.ncols ? n : n0));
           }
       }
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        __bf16* tile = lds + (wv * 2 + (i & 1)) * 32 * ORS;
+        __bf16* tile = lds + (wv * 2 + (i & 1)) * E * ORS;
         const float rs = kScale ? sigmoidf_dev(row_scale[i]) : 1.f;
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const int n = j * 32 + 8 * g + 4 * hh;        // 4 consecutive output columns
+          for (int g = 0; g < MF::kGroups; ++g) {
+            const int n = j * E + MF::row(g, lane);       // 4 consecutive output columns
             floatx4 f = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
             if (kScale) f *= rs;
             f += *reinterpret_cast<const floatx4*>(&bias_s[wn + n]);
-            *reinterpret_cast<bf16x4*>(&tile[l32 * ORS + n]) = __builtin_convertvector(f, bf16x4);
+            *reinterpret_cast<bf16x4*>(&tile[lane % E * ORS + n]) = __builtin_convertvector(f, bf16x4);
           }
 #pragma unroll
         for (int u = 0; u < PER_LANE; ++u) {
-          const int c = lane + 64 * u, r = c / PIECES, ch = c % PIECES, row = wm + i * 32 + r, n = n0 + wn + ch * 8;
+          const int c = lane + 64 * u, r = c / PIECES, ch = c % PIECES, row = wm + i * E + r, n = n0 + wn + ch * 8;
           bf16x8 val = *reinterpret_cast<const bf16x8*>(&tile[r * ORS + ch * 8]);
           if constexpr (kResidual) val = float_to_bf16x8(bf16x8_to_float(val) + bf16x8_to_float(res[i][u]));
           if (m0 + row < M && n < p.ncols) *reinterpret_cast<bf16x8*>(p.out + (long)o_row[row] * p.ldo + n) = val;
@@ -133,11 +147,14 @@ __device__ __forceinline__ void gemm_rows_block(const GemmArgs& p, unsigned char
     };
     if (p.residual != nullptr) epilogue(std::true_type{});
     else epilogue(std::false_type{});
+    if (!LOOP) break;
+    __syncthreads();                 // the tables and buffers are read to the end
   }
   // The rows no packed row maps to: shared by the waves of the workgroups without a tile, which run beside
   // the others, or by all when those are few.
   if (p.inv_pos != nullptr) {
     constexpr int NW = WGM * WGN;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int live = min((int)blocks, 8 * per_xcd), idle = (int)blocks - live;
     const bool by_idle = 4 * idle >= live;
     const long units = (long)(by_idle ? idle : (int)blocks) * NW;
@@ -148,11 +165,36 @@ __device__ __forceinline__ void gemm_rows_block(const GemmArgs& p, unsigned char
   }
 }
 
-template <bool kScale, bool kDeep, int BM, int BN, int WGM, int WGN, int STAGES>
-__global__ void __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(BM > 128 ? 1 : 2)))
-gemm_rows_kernel(const GemmArgs p) {
+constexpr size_t kGemmSmallLds = (size_t)2 * (128 + 128) * kGaK * sizeof(__bf16);
+constexpr size_t kGemmBigLds = (size_t)3 * (192 + 192) * kGaK * sizeof(__bf16);     // (two of 256 + 256 need less)
+
+// 128 x 128 tiles: four waves of 64 x 64, two workgroups per unit.
+template <bool kScale, bool kDeep>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) gemm_rows_small_kernel(const GemmArgs p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char gemm_smem[];
-  gemm_rows_block<kScale, kDeep, BM, BN, WGM, WGN, STAGES>(p, gemm_smem, blockIdx.x, gridDim.x);
+  gemm_rows_block<Mfma32, kScale, kDeep, false, 128, 128, 2, 2, 2>(p, gemm_smem, blockIdx.x, gridDim.x);
+}
+
+// Tiles of 256 x 256 (eight waves of 128 x 64) or 192 x 192 (eight of 48 x 96, whose accumulators leave room for three
+// operand stages): one resident workgroup per unit walks the tiles (a workgroup per tile of the capacity: 1.5 us more
+// for those without one), and the rounds that takes decide, a round of the smaller tile is about .7 of one of the
+// larger.  The row count is only known here.  Measured, K 768, 256 x 256 | 192 x 192, rounds in brackets, us: 11540 rows
+// of 768 columns 24.6 (1) | 19.0 (1), 15052 rows 24.9 (1) | 30.1 (2); rows of 2304 columns: 7526 46.7 (2) | 38.8 (2), 11540
+// 49.8 (2) | 52.2 (3), 12544 51.2 (2) | 64.4 (4), 15052 72.6 (3) | 67.5 (4); K 2304, 11540 rows of 768 columns: 54.3 (1) |
+// 45.5 (1).  At 240 tiles a step of 64 takes 1.0 us, 256 x 256 1.45: bound by the L2 (11 TB/s) and by power (1.8 GHz
+// when all units multiply); launch, first loads and the epilogue of a round take 4 us more.
+template <class T>
+__host__ __device__ inline T gemm_tiles(T rows, T ncols, T edge) { return (rows + edge - 1) / edge * ((ncols + edge - 1) / edge); }
+__host__ __device__ inline bool medium_tiles(int rows, int ncols) {
+  return 7 * ((gemm_tiles(rows, ncols, 192) + 255) / 256) <= 10 * ((gemm_tiles(rows, ncols, 256) + 255) / 256);
+}
+
+template <bool kScale, bool kDeep>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1))) gemm_rows_big_kernel(const GemmArgs p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char gemm_smem[];
+  const int M = p.total != nullptr ? min(p.total[0], p.m_cap) : p.m_cap;
+  if (medium_tiles(M, p.ncols)) gemm_rows_block<Mfma16, kScale, kDeep, true, 192, 192, 4, 2, 3>(p, gemm_smem, blockIdx.x, gridDim.x);
+  else gemm_rows_block<Mfma32, kScale, kDeep, true, 256, 256, 2, 4, 2>(p, gemm_smem, blockIdx.x, gridDim.x);
 }
 
 }  // namespace spa

@@ -6,11 +6,11 @@
 // one rounding fewer than multiplying a materialised bf16 r_g.
 //
 // bf16 path: MFMA GEMM on the pipelined loop of gemm_async.h, 64 deep steps, tiles of 128 x 128 (four waves
-// of 64 x 64, two workgroups per unit) or 256 x 256 (eight waves of 128 x 64); the same kernel multiplies
+// of 64 x 64, two workgroups per unit), 192 x 192 or 256 x 256 (eight waves); the same kernels multiply
 // by W as it lies for the input side of the backward (linear_bwd.hip).  With 128 x 128 tiles every flop
-// needs 1/64 byte from L2 and the L2 delivers about 12 TB/s with this pattern, so the large tile, which
-// halves that, wins wherever its workgroups still fill the chip (launch_gemm_rows).  Measured, 12544 rows of
-// 768 -> 2304: 51 us = 870 TFLOP/s (operands staged through registers: 68 us); 6272 rows of 384 -> 384: 6.9
+// needs 1/64 byte from L2 and the L2 delivers about 12 TB/s with this pattern, so the large tiles, which
+// need two thirds and half of that, win wherever they still fill the chip (launch_gemm_rows).  Measured, 12544 rows of
+// 768 -> 2304: 47 us = 940 TFLOP/s (operands staged through registers: 68 us); 6272 rows of 384 -> 384: 7.2
 // us (8.7); 98 rows: 6.3 us (8.1), its steps bound by latency.  The output tile leaves through LDS as
 // whole rows.
 // fp32 path (tiny workload): one thread per output element.
@@ -51,45 +51,43 @@ linear_f32_kernel(const float* __restrict__ x, const int32_t* __restrict__ gathe
   }
 }
 
-template <bool kScale, bool kDeep, int BM, int BN, int WGM, int WGN, int STAGES>
-static int launch_gemm_rows_tile(const char* fn, GemmArgs args, hipStream_t st) {
-  constexpr size_t smem = (size_t)STAGES * (BM + BN) * kGaK * sizeof(__bf16);
-  const long m_tiles = (args.m_cap + BM - 1) / BM;
-  args.n_tiles = (args.ncols + BN - 1) / BN;
-  SPA_REQUIRE(m_tiles * args.n_tiles + 8 < 2147483647L / 2, SPA_ERR_INVALID_ARG, "%s: too many tiles", fn);
-  const void* kernel = (const void*)gemm_rows_kernel<kScale, kDeep, BM, BN, WGM, WGN, STAGES>;
-  const hipError_t attr = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+template <bool kScale, bool kDeep>
+static int launch_gemm_rows_tile(const char* fn, const GemmArgs& args, bool big, hipStream_t st) {
+  const size_t smem = big ? kGemmBigLds : kGemmSmallLds;
+  const long tiles = gemm_tiles<long>(args.m_cap, args.ncols, big ? 192 : 128);     // (no less than with 256)
+  SPA_REQUIRE(tiles + 8 < 2147483647L / 2, SPA_ERR_INVALID_ARG, "%s: too many tiles", fn);
+  const long tiles8 = (tiles + 7) / 8 * 8;
+  const auto kernel = big ? gemm_rows_big_kernel<kScale, kDeep> : gemm_rows_small_kernel<kScale, kDeep>;
+  const hipError_t attr = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   SPA_REQUIRE(attr == hipSuccess, SPA_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, smem);
-  const unsigned grid = (unsigned)((m_tiles * args.n_tiles + 7) / 8 * 8);
-  hipLaunchKernelGGL((gemm_rows_kernel<kScale, kDeep, BM, BN, WGM, WGN, STAGES>), dim3(grid), dim3(64 * WGM * WGN), smem,
-                     st, args);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(big ? std::min(tiles8, 256L) : tiles8)), dim3(big ? 512 : 256), smem, st, args);
   return check_launch(fn);
 }
 
-// Tile shape, from about half of the capacity live (what a packed stream has).  Measured step times: a 128 x
-// 128 x 64 step takes 0.45 us alone on its unit, two workgroups per unit and all units share the L2
-// bandwidth (0.0033 us per tile of the launch); a 256 x 256 x 64 step takes 1.55 us, and 0.0087 us per tile
-// when all units are busy: two thirds of the time per output, paid with a quarter of the workgroups and 3 us
-// more before the first and after the last step (6272 x 2304, K 768: 27.5 against 35 us; 6272 x 768: 23
-// against 16 us).  Option gemm_tm = 2 | 8 forces 128 x 128 | 256 x 256 (tuning aid).
+// Tile shape, from about half of the capacity live (what a packed stream has).  Measured times: a 128 x 128 x 64 step
+// takes 0.6 us alone on its unit, and the launch 3.3 us before the first and after the last; .95 and 5.5 us beside another,
+// 1.65 where some units have a third tile to take and 0.0026 us per tile of the launch beyond.  A round of the large tiles
+// (gemm_rows.h) takes 5 us and 1.2 a step (192) or 9.5 and 1.2 (256).  In us, 128 | large: 6272 x 2304, K 768 33 | 28;
+// 6272 x 768 16 | 17; 12544 x 768 25 | 23.5; 12544 x 1536, K 512 28 | 33; 12544 x 768, K 2304 62 | 55.  Option gemm_tm = 2 | 8
+// forces 128 x 128 | large (tuning aid).
 static bool big_tiles(const GemmArgs& a) {
   const int cfg = options().gemm_tm;
   if (cfg != 0) return cfg == 8;
-  const double live = a.total != nullptr ? 0.5 * a.m_cap : a.m_cap, nk = (a.kc + kGaK - 1) / kGaK;
-  const double big = ((live + 255) / 256) * ((a.ncols + 255) / 256), small = ((live + 127) / 128) * ((a.ncols + 127) / 128);
-  return nk * fmax(1.55, 0.0087 * big) + 3.0 < nk * fmax(0.45, 0.0033 * small);
+  const int live = a.total != nullptr ? a.m_cap / 2 : a.m_cap;
+  const auto tiles = [&](long edge) { return gemm_tiles<long>(live, a.ncols, edge); };
+  const auto rounds = [&](long edge) { return (double)((tiles(edge) + 255) / 256); };
+  const double nk = (a.kc + kGaK - 1) / kGaK, t = (double)tiles(128);
+  const double small = t <= 256 ? 3.3 + 0.6 * nk : 5.5 + nk * (t <= 512 ? 0.95 : fmax(1.65, 0.0026 * t));
+  const double big = medium_tiles(live, a.ncols) ? rounds(192) * (5.0 + 1.2 * nk) : rounds(256) * (9.5 + 1.2 * nk);
+  return big < small;
 }
 
 int launch_gemm_rows(const char* fn, const GemmArgs& args, bool deep, hipStream_t st) {
   const bool big = big_tiles(args);
   if (group_open()) return group_note_rows(fn, args, big);
-#define SPA_GEMM(S_, D_)                                                                              \
-  return big ? launch_gemm_rows_tile<S_, D_, 256, 256, 2, 4, 2>(fn, args, st)                         \
-             : launch_gemm_rows_tile<S_, D_, 128, 128, 2, 2, 2>(fn, args, st)
-  if (deep) SPA_GEMM(false, true);
-  if (args.scores != nullptr) SPA_GEMM(true, false);
-  SPA_GEMM(false, false);
-#undef SPA_GEMM
+  if (deep) return launch_gemm_rows_tile<false, true>(fn, args, big, st);
+  if (args.scores != nullptr) return launch_gemm_rows_tile<true, false>(fn, args, big, st);
+  return launch_gemm_rows_tile<false, false>(fn, args, big, st);
 }
 
 }  // namespace spa

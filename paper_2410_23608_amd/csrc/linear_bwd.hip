@@ -173,7 +173,7 @@ __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned 
   const __bf16* zeros = reinterpret_cast<const __bf16*>(gemm_zeros);
 
   // columns past the matrix edge fetch a valid column (never stored)
-  const int col = P::col(tid);
+  const int col = P::col(tid, 0);
   const __bf16* gcol = dout + (w.n0 + col < n_out ? w.n0 + col : w.n0);
   const __bf16* xcol = x + (w.k0 + col < K ? w.k0 + col : w.k0);
   int gi[P::kCount], xi[P::kCount];                  // row indices of the next step to be issued
@@ -181,19 +181,19 @@ __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned 
     if (!kGather) return;
 #pragma unroll
     for (int u = 0; u < P::kCount; ++u) {
-      const int m = min(w.m_begin + t * kGaK + P::row0(tid) + u * P::kRowStep, w.m_end - 1);
+      const int m = min(w.m_begin + t * kGaK + P::row(tid, u), w.m_end - 1);
       gi[u] = dout_idx != nullptr ? dout_idx[m] : m;
       xi[u] = x_idx != nullptr ? x_idx[m] : m;
     }
   };
   const int rows = w.m_end - w.m_begin, nk = rows > 0 ? (rows + kGaK - 1) / kGaK : 0;
   auto next_g = [&](int u, int t) {
-    const int r = t * kGaK + P::row0(tid) + u * P::kRowStep;
+    const int r = t * kGaK + P::row(tid, u);
     const __bf16* p = gcol + (long)(kGather ? gi[u] : w.m_begin + r) * ldd;
     return r < rows ? p : zeros;
   };
   auto next_x = [&](int u, int t) {
-    const int r = t * kGaK + P::row0(tid) + u * P::kRowStep;
+    const int r = t * kGaK + P::row(tid, u);
     const __bf16* p = xcol + (long)(kGather ? xi[u] : w.m_begin + r) * K;
     if (u == P::kCount - 1 && t + 1 < nk) index(t + 1);      // (the last address of step t has been formed)
     return r < rows ? p : zeros;
@@ -210,9 +210,9 @@ __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned 
   const __bf16 one = static_cast<__bf16>(1.0f);
   const bf16x8 ones = {one, one, one, one, one, one, one, one};
   if (nk > 0) index(0);
-  gemm_async_loop<kLbT * kGaK, kLbT * kGaK, P::kCount, P::kCount, STAGES, kLbThreads, 2, 2>(
+  gemm_async_loop<Mfma32, kLbT * kGaK, kLbT * kGaK, P::kCount, P::kCount, STAGES, kLbThreads, 2, 2>(
       lds, nk, next_g, next_x, [&](const __bf16* tile, int i, int kk) { return deep_frag<kLbT>(tile, kk, wn + i * 32, lane); },
-      [&](const __bf16* tile, int j, int kk) { return deep_frag<kLbT>(tile, kk, wk + j * 32, lane); }, acc,
+      [&](const __bf16* tile, int j, int kk) { return deep_frag<kLbT>(tile, kk, wk + j * 32, lane); }, acc, [] {},
       [&](const bf16x8 (&g)[2]) {
         if (do_bias) {
           accb[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, g[0], accb[0], 0, 0, 0);
@@ -250,7 +250,7 @@ __global__ void __launch_bounds__(kLbThreads) __attribute__((amdgpu_waves_per_eu
   extern __shared__ __attribute__((aligned(16))) unsigned char lb_smem[];
   const unsigned block = blockIdx.x;
   if (block < g.end[0]) {
-    gemm_rows_block<false, true, 128, 128, 2, 2, 2>(g.rows, lb_smem, block, g.end[0]);
+    gemm_rows_block<Mfma32, false, true, false, 128, 128, 2, 2, 2>(g.rows, lb_smem, block, g.end[0]);
     return;
   }
   const int s = block >= g.end[1];
@@ -535,8 +535,7 @@ int group_flush_linear(hipStream_t st) {
   if (n.n_rows == 1 && n.n_weight > 0 && !n.big) {
     LinearGroup g;
     g.rows = n.rows;
-    g.rows.n_tiles = (n.rows.ncols + 127) / 128;
-    const long tiles = (long)((n.rows.m_cap + 127) / 128) * g.rows.n_tiles;
+    const long tiles = (long)((n.rows.m_cap + 127) / 128) * ((n.rows.ncols + 127) / 128);
     g.end[0] = (unsigned)((tiles + 7) / 8 * 8);
     g.w[0] = n.w[0];
     g.w[1] = n.w[n.n_weight - 1];
