@@ -143,8 +143,9 @@ __device__ __forceinline__ void store_weight_block(const floatx16 (&acc)[2][2], 
 // more MFMA per 16 rows against a vector of ones, in the workgroups of the first k tile).  Both operands
 // have the contraction (the tokens) down their rows and come through the ring of gemm_async.h, rows of
 // zeros past the chunk's end.  kGather: rows of g / x are named by index arrays (null: in order), read one
-// step ahead of the loads that use them.  12544 rows, 2304 x 768, with the
-// reduction: gathered 97 -> 80 us, in order 68 us; 98 rows of 384 x 1152: 9.8 -> 6.2 us.
+// step ahead of the loads that use them, with one test for all rows of a thread (a test a row: 3072 x 1024, 12544 rows, 139 ->
+// 125 us).  12544 rows, 2304 x 768, with the reduction: gathered 97 -> 71 us, in order 66 us; 98 rows of 384 x 1152: 9.8 ->
+// 6.2 us.
 struct WeightArgs {
   const __bf16* dout;
   const int32_t* dout_idx;
@@ -180,10 +181,14 @@ __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned 
   auto index = [&](int t) {
     if (!kGather) return;
 #pragma unroll
-    for (int u = 0; u < P::kCount; ++u) {
-      const int m = min(w.m_begin + t * kGaK + P::row(tid, u), w.m_end - 1);
-      gi[u] = dout_idx != nullptr ? dout_idx[m] : m;
-      xi[u] = x_idx != nullptr ? x_idx[m] : m;
+    for (int u = 0; u < P::kCount; ++u) gi[u] = xi[u] = min(w.m_begin + t * kGaK + P::row(tid, u), w.m_end - 1);
+    if (dout_idx != nullptr) {
+#pragma unroll
+      for (int u = 0; u < P::kCount; ++u) gi[u] = dout_idx[gi[u]];
+    }
+    if (x_idx != nullptr) {
+#pragma unroll
+      for (int u = 0; u < P::kCount; ++u) xi[u] = x_idx[xi[u]];
     }
   };
   const int rows = w.m_end - w.m_begin, nk = rows > 0 ? (rows + kGaK - 1) / kGaK : 0;
