@@ -684,6 +684,7 @@ wave_attention(WaveLds<DH, STEP>* lds, int part, const Segment seg, int h, int q
   constexpr int RS = DH + 8, KK = DH / 16, CPR = DH / 8;
   constexpr int NSB = STEP / 32;                 // 32-key sub-tiles per step (one softmax update)
   constexpr int LPL = STEP * CPR / 64;           // 16-byte loads per lane per tensor per step
+  if (SPLIT == 1) part = 0;                      // (known here: the loop and the tiles of the one-wave form depend on it)
   __bf16 *Ks = lds[part].Ks, *Vs = lds[part].Vs;
   const long C = (long)H * DH;
   const int lane = threadIdx.x & 63, l32 = lane & 31, hh = lane >> 5;
