@@ -2,10 +2,11 @@
 // All kernels move feature rows with 16-byte accesses and are bandwidth-bound.
 //
 // spa_pack is ONE launch with no scratch memory and no inter-workgroup dependency: a
-// workgroup owns one tile of <= 256 consecutive tokens of one image, counts the selected
+// workgroup owns one tile of up to 256 consecutive tokens of one image (1024 where only the index is wanted), counts the selected
 // tokens that precede its tile (from the per-image counts when the caller has them, else
 // from the mask bytes themselves — B*N bytes that sit in L2), ranks its own tokens with
 // wave ballots, and copies its survivors' rows to their final place.
+#include <algorithm>
 #include <cstdlib>
 
 #include "group.h"
@@ -22,40 +23,28 @@ __device__ __forceinline__ int nonzero_bytes(uint32_t w) {
   return __popc(t);
 }
 
-// Sum over the workgroup; every thread gets the result.  red: kPackWaves ints of LDS.
-__device__ __forceinline__ int block_sum(int v, int* red) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  __syncthreads();
-  if (lane_id() == 0) red[threadIdx.x / kWave] = v;
-  __syncthreads();
-  int s = 0;
-#pragma unroll
-  for (int i = 0; i < kPackWaves; ++i) s += red[i];
-  return s;
-}
-
 // Non-zero bytes of m[0 .. n), counted cooperatively by the workgroup (partial per thread).
+template <int THREADS>
 __device__ __forceinline__ int count_bytes_partial(const uint8_t* m, long n) {
   int cnt = 0;
   const uintptr_t a = reinterpret_cast<uintptr_t>(m);
   long head = (16 - (a & 15)) & 15;
   if (head > n) head = n;
-  for (long i = threadIdx.x; i < head; i += kPackThreads) cnt += m[i] != 0;
+  for (long i = threadIdx.x; i < head; i += THREADS) cnt += m[i] != 0;
   const long nvec = (n - head) / 16;
   const uintx4* mv = reinterpret_cast<const uintx4*>(m + head);
   // eight loads in flight (134400 mask bytes: the launch 11.8 -> 7.9 us)
   constexpr int U = 8;
-  for (long i = threadIdx.x; i < nvec; i += U * kPackThreads) {
+  for (long i = threadIdx.x; i < nvec; i += U * THREADS) {
     uintx4 v[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = mv[min(i + u * kPackThreads, nvec - 1)];
+    for (int u = 0; u < U; ++u) v[u] = mv[min(i + u * THREADS, nvec - 1)];
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (i + u * kPackThreads < nvec)
+      if (i + u * THREADS < nvec)
         cnt += nonzero_bytes(v[u][0]) + nonzero_bytes(v[u][1]) + nonzero_bytes(v[u][2]) + nonzero_bytes(v[u][3]);
   }
-  for (long i = head + nvec * 16 + threadIdx.x; i < n; i += kPackThreads) cnt += m[i] != 0;
+  for (long i = head + nvec * 16 + threadIdx.x; i < n; i += THREADS) cnt += m[i] != 0;
   return cnt;
 }
 
@@ -137,13 +126,13 @@ struct PackArgs {
   int C2;
   T* packed2;
 };
-template <typename T, bool kScale, bool kShift, bool kPair>
+template <typename T, bool kScale, bool kShift, bool kPair, bool kIndex = false, int THREADS = kPackThreads>
 __device__ __forceinline__ void pack_block(const PackArgs<T>& a, int block) {
-  constexpr int VE = 16 / sizeof(T);
-  __shared__ int red[kPackWaves];
-  __shared__ int wave_cnt[kPackWaves];
-  __shared__ int sel_src[kPackThreads];
-  __shared__ float sel_scale[kPackThreads];
+  static_assert(kIndex || THREADS == kPackThreads, "rows are copied by 256 threads");
+  constexpr int VE = 16 / sizeof(T), WAVES = THREADS / kWave;
+  __shared__ int before_w[WAVES], wave_cnt[WAVES];
+  __shared__ int sel_src[kIndex ? 1 : kPackThreads];
+  __shared__ float sel_scale[kIndex ? 1 : kPackThreads];
   const T *x = a.x, *x2 = a.x2;
   const uint8_t* mask = a.mask;
   const int32_t* counts = a.counts;
@@ -160,43 +149,47 @@ __device__ __forceinline__ void pack_block(const PackArgs<T>& a, int block) {
   const int tile_n = min(tile, N - tile_start);
   const long img0 = (long)b * N;
 
-  // 1. selected tokens before this tile
-  int part = 0;
-  if (counts != nullptr) {
-    for (int i = threadIdx.x; i < b; i += kPackThreads) part += counts[i];
-    if (!kShift) part += count_bytes_partial(mask + img0, tile_start);
-  } else {
-    part = count_bytes_partial(mask, kShift ? img0 : img0 + tile_start);
-  }
-  if (kShift)   // the tile's predecessors inside the image are not contiguous in memory
-    for (int p = threadIdx.x; p < tile_start; p += kPackThreads) part += mask[img0 + shift.orig(p)] != 0;
-  const int base = block_sum(part, red);
-
-  // 2. rank of each token of the tile among the tile's survivors
-  const int tid = threadIdx.x;
+  // 1. the tile's own mask bytes, fetched with the first of the others, and selected tokens before this tile
+  const int tid = threadIdx.x, wv = tid / kWave;
   const bool in_tile = tid < tile_n;
   const int src = in_tile ? (kShift ? shift.orig(tile_start + tid) : tile_start + tid) : 0;   // position in the image
-  const bool flag = in_tile && mask[img0 + src] != 0;
+  const uint8_t own = mask[img0 + src];
+  int part = 0;
+  if (counts != nullptr) {
+    for (int i = tid; i < b; i += THREADS) part += counts[i];
+    if (!kShift) part += count_bytes_partial<THREADS>(mask + img0, tile_start);
+  } else {
+    part = count_bytes_partial<THREADS>(mask, kShift ? img0 : img0 + tile_start);
+  }
+  if (kShift)   // the tile's predecessors inside the image are not contiguous in memory
+    for (int p = tid; p < tile_start; p += THREADS) part += mask[img0 + shift.orig(p)] != 0;
+  part = wave_sum(part);
+
+  // 2. rank of each token of the tile among the tile's survivors
+  const bool flag = in_tile && own != 0;
   const uint64_t bal = __ballot(flag);
-  const int wv = tid / kWave;
-  if (lane_id() == 0) wave_cnt[wv] = __popcll(bal);
+  if (lane_id() == 0) {
+    before_w[wv] = part;
+    wave_cnt[wv] = __popcll(bal);
+  }
   __syncthreads();
-  int wave_off = 0, nsel = 0;
+  int base = 0, wave_off = 0, nsel = 0;
 #pragma unroll
-  for (int i = 0; i < kPackWaves; ++i) {
+  for (int i = 0; i < WAVES; ++i) {
     const int c = wave_cnt[i];
     if (i < wv) wave_off += c;
     nsel += c;
+    base += before_w[i];
   }
   const int local_rank = wave_off + rank_in_ballot(bal);
   if (in_tile && inv_pos != nullptr) inv_pos[img0 + src] = flag ? base + local_rank : -1;
   if (flag) {
     if (gather_idx != nullptr) gather_idx[base + local_rank] = (int32_t)(img0 + src);
-    sel_src[local_rank] = src;
-    if (kScale) sel_scale[local_rank] = sigmoidf_dev(gate_scores[img0 + src]);
+    if (!kIndex) sel_src[local_rank] = src;
+    if (!kIndex && kScale) sel_scale[local_rank] = sigmoidf_dev(gate_scores[img0 + src]);
   }
   if (t == 0 && tid == 0 && cu_seqlens != nullptr) cu_seqlens[b] = base;
-  __syncthreads();
+  if (!kIndex) __syncthreads();
 
   const int chunks = C / VE;
   // 3. the last tile knows T: publish it and zero the tail of the last container
@@ -206,7 +199,7 @@ __device__ __forceinline__ void pack_block(const PackArgs<T>& a, int block) {
       if (cu_seqlens != nullptr) cu_seqlens[B] = T_sel;
       if (total != nullptr) total[0] = T_sel;
     }
-    if (container_len > 0 && packed != nullptr) {
+    if (!kIndex && container_len > 0 && packed != nullptr) {
       const long t_pad = ((long)T_sel + container_len - 1) / container_len * container_len;
       const long nz = (t_pad - T_sel) * chunks;
       uintx4* dst = reinterpret_cast<uintx4*>(packed + (long)T_sel * C);
@@ -219,7 +212,7 @@ __device__ __forceinline__ void pack_block(const PackArgs<T>& a, int block) {
   //    of a second tensor x2 (width C2) of the same tokens, multiplied by Sigmoid(s) when scores
   //    are given, go to packed2, in the same launch (one copy after the other: one list of chunks
   //    over both tensors, with all loads in flight together, measured slower, 13.6 against 12.3 us).
-  if (packed != nullptr)
+  if (!kIndex && packed != nullptr)
     copy_selected_rows<T, kScale && !kPair>(x + img0 * (long)C, packed + (long)base * C, C, nsel, sel_src, sel_scale, tid);
   if (kPair)
     copy_selected_rows<T, kScale>(x2 + img0 * (long)C2, packed2 + (long)base * C2, C2, nsel, sel_src, sel_scale, tid);
@@ -229,14 +222,29 @@ template <typename T, bool kScale, bool kShift, bool kPair>
 __global__ void __launch_bounds__(kPackThreads) pack_kernel(const PackArgs<T> a) {
   pack_block<T, kScale, kShift, kPair>(a, blockIdx.x);
 }
+// The index alone: nothing to copy, so few large tiles, a token a thread, each of which counts the bytes before it: 256
+// threads up to 64 K tokens (sixteen pieces a thread), else 1024.  us, tiles of 16 / 32 / 64 / 128 / 256 tokens by 256 threads: 64 x
+// 196 tokens 3.8 / 3.4 / 3.1 / 3.1 / 3.1, 8 x 4200 6.7 / 4.7 / 4.0 / 3.7 / 3.5; 256 | 1024 threads: 8 x 4200 3.6 | 4.0, 16 x 4200 4.6 |
+// 4.6, 32 x 4200 6.7 | 4.5; four calls of 16 x 3136 tokens and their halvings in one launch 4.6 | 5.0, of 32 6.1 | 5.0.
+static int index_threads(long tokens) { return tokens <= 65536 ? 256 : 1024; }
+static int index_tile(int threads) { return options().pack_tile != 0 ? options().pack_tile : threads; }
+template <bool kShift, int THREADS>
+__global__ void __launch_bounds__(THREADS) pack_index_kernel(const PackArgs<__bf16> a) {
+  pack_block<__bf16, false, kShift, false, true, THREADS>(a, blockIdx.x);
+}
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS) pack_index_group_kernel(const Members<PackArgs<__bf16>> m) {
+  const MemberBlock mb = member_of(m, blockIdx.x);
+  pack_block<__bf16, false, false, false, true, THREADS>(m.a[mb.s], mb.block);
+}
 // Several calls in one launch (launch groups)
 template <bool kScale, bool kPair>
 __global__ void __launch_bounds__(kPackThreads) pack_group_kernel(const Members<PackArgs<__bf16>> m) {
   const MemberBlock mb = member_of(m, blockIdx.x);
   pack_block<__bf16, kScale, false, kPair>(m.a[mb.s], mb.block);
 }
-static thread_local Noted<PackArgs<__bf16>> g_noted[2];       // rows or index alone, pairs with a gated second row
-void group_forget_pack() { g_noted[0].n = g_noted[1].n = 0; }
+static thread_local Noted<PackArgs<__bf16>> g_noted[3];       // rows, pairs with a gated second row, index alone
+void group_forget_pack() { g_noted[0].n = g_noted[1].n = g_noted[2].n = 0; }
 int group_flush_pack(hipStream_t st) {
   Members<PackArgs<__bf16>> m;
   if (g_noted[0].n > 0) {
@@ -246,6 +254,21 @@ int group_flush_pack(hipStream_t st) {
   if (g_noted[1].n > 0) {
     const unsigned blocks = g_noted[1].members(m);
     hipLaunchKernelGGL((pack_group_kernel<true, true>), dim3(blocks), dim3(kPackThreads), 0, st, m);
+  }
+  if (g_noted[2].n > 0) {
+    auto& g = g_noted[2];
+    long most = 0;
+    for (int i = 0; i < g.n; ++i) most = std::max(most, (long)g.a[i].B * g.a[i].N);
+    const int threads = index_threads(most);
+    for (int i = 0; i < g.n; ++i) {
+      PackArgs<__bf16>& a = g.a[i];
+      a.tile = index_tile(threads);
+      a.tiles_per_image = (a.N + a.tile - 1) / a.tile;
+      g.blocks[i] = (unsigned)((long)a.B * a.tiles_per_image);
+    }
+    const unsigned blocks = g.members(m);
+    const auto kernel = threads == 1024 ? pack_index_group_kernel<1024> : pack_index_group_kernel<256>;
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), 0, st, m);
   }
   return check_launch("spa_group_end");
 }
@@ -311,7 +334,7 @@ template <bool kShift>
 __global__ void __launch_bounds__(kPackThreads) pack_containers_kernel(const PackArgs<__bf16> a, const SegmentArgs s) {
   static_assert(kSegImages == 4 * kPackThreads, "four images per thread below");
   if (blockIdx.x != 0) {
-    pack_block<__bf16, false, kShift, false>(a, blockIdx.x - 1);
+    pack_block<__bf16, false, kShift, false, true>(a, blockIdx.x - 1);
     return;
   }
   __shared__ int cu[kSegImages + 1];
@@ -525,10 +548,12 @@ static int pack_common(const char* fn, const void* x, const uint8_t* mask, const
   if (int rc = check_rows(fn, B, N, C, dtype)) return rc;
   SPA_REQUIRE(container_len >= 0, SPA_ERR_INVALID_ARG, "%s: container_len must be >= 0", fn);
   SPA_REQUIRE(aligned16(x) && aligned16(packed), SPA_ERR_INVALID_ARG, "%s: x / packed not 16-byte aligned", fn);
-  const int tile = pick_tile(B, N, counts != nullptr);
+  const bool index = packed == nullptr;
+  const int threads = index ? index_threads((long)B * N) : kPackThreads;
+  const int tile = index ? index_tile(threads) : pick_tile(B, N, counts != nullptr);
   const int tpi = (N + tile - 1) / tile;
   SPA_REQUIRE((long)B * tpi < 2147483647L, SPA_ERR_INVALID_ARG, "%s: too many tiles", fn);
-  const dim3 grid((unsigned)((long)B * tpi)), block(kPackThreads);
+  const dim3 grid((unsigned)((long)B * tpi)), block(threads);
   hipStream_t st = as_stream(stream);
 #define SPA_PACK_ARGS(T)                                                                                       \
   PackArgs<T> {                                                                                                \
@@ -538,7 +563,15 @@ static int pack_common(const char* fn, const void* x, const uint8_t* mask, const
   if (group_open()) {
     SPA_REQUIRE(dtype == SPA_BF16 && !shifted && gate_scores == nullptr, SPA_ERR_UNSUPPORTED,
                 "%s: this form cannot be part of a group", fn);
-    return g_noted[0].add(fn, SPA_PACK_ARGS(__bf16), grid.x);
+    return g_noted[index ? 2 : 0].add(fn, SPA_PACK_ARGS(__bf16), grid.x);
+  }
+  if (index) {
+    const PackArgs<__bf16> args = {nullptr, mask, counts, nullptr, B, N, C, tile, tpi, 0, shift, nullptr,
+                                   cu_seqlens, gather_idx, inv_pos, total, nullptr, 0, nullptr};
+    const auto kernel = threads == 1024 ? shifted ? pack_index_kernel<true, 1024> : pack_index_kernel<false, 1024>
+                                        : shifted ? pack_index_kernel<true, 256> : pack_index_kernel<false, 256>;
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, args);
+    return check_launch(fn);
   }
 #define SPA_PACK_LAUNCH(T, S, SH) hipLaunchKernelGGL((pack_kernel<T, S, SH, false>), grid, block, 0, st, SPA_PACK_ARGS(T))
 #define SPA_PACK_SCALE(T, SH)                                                                            \

@@ -1,0 +1,62 @@
+"""The packing index alone (no rows copied): tiles of 256 and of 1024 tokens, on both sides of the line between them and at the
+edges of a tile, of an image and of a 16-byte piece; ordinary, shifted, with the caller's counts and in a launch group, against
+the order of the mask's set bytes.  Exact."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(mask, order, cu, gi, inv, tot):
+    """order: position in the image of the p-th token in packing order."""
+    B, N = mask.shape
+    kept = mask[:, order].bool()
+    rows = (torch.arange(B, device="cuda")[:, None] * N + order[None, :])[kept].int()
+    n = rows.numel()
+    assert tot.item() == n
+    assert torch.equal(gi[:n], rows)
+    assert torch.equal(cu, torch.cat([torch.zeros(1, dtype=torch.int32, device="cuda"), kept.sum(1).cumsum(0).int()]))
+    ref = torch.full((B * N,), -1, dtype=torch.int32, device="cuda")
+    ref[rows.long()] = torch.arange(n, dtype=torch.int32, device="cuda")
+    assert torch.equal(inv, ref)
+
+
+def _buffers(B, N):
+    z = lambda n: torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    return z(B + 1), z(B * N), z(B * N), z(1)
+
+
+@pytest.mark.parametrize("B,h,w", [(1, 1, 1), (3, 1, 17), (2, 16, 16), (3, 1, 257), (5, 32, 32), (16, 64, 64), (17, 25, 241),
+                                   (70, 1, 1025), (33, 50, 84)])
+@pytest.mark.parametrize("form", ["plain", "counts", "shifted"])
+def test_index_alone(B, h, w, form):
+    from paper_2410_23608_amd import spa
+    N = h * w
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B * N)
+    for keep in (0.0, 0.4, 1.0):
+        mask = (torch.rand(B, N, generator=g, device="cuda") < keep).to(torch.uint8) * 3        # (any non-zero byte counts)
+        cu, gi, inv, tot = _buffers(B, N)
+        order = torch.arange(N, device="cuda")
+        if form == "shifted":
+            sh, sw = (h + 1) // 2, w // 3
+            order = order.view(h, w).roll((-sh, -sw), (0, 1)).reshape(-1)
+            spa.spa_pack_shifted(None, mask, None, None, h, w, sh, sw, 0, None, cu, gi, inv, tot)
+        else:
+            counts = (mask != 0).sum(1).int() if form == "counts" else None
+            spa.spa_pack(None, mask, counts, None, 0, None, cu, gi, inv, tot)
+        torch.cuda.synchronize()
+        _check(mask, order, cu, gi, inv, tot)
+
+
+@pytest.mark.parametrize("shapes", [[(2, 49), (3, 300)], [(16, 3136), (16, 784), (16, 49)], [(40, 1700), (1, 1), (2, 1030)]])
+def test_index_alone_in_a_group(shapes):
+    from paper_2410_23608_amd import spa
+    g = torch.Generator(device="cuda")
+    g.manual_seed(len(shapes))
+    masks = [(torch.rand(B, N, generator=g, device="cuda") < 0.5).to(torch.uint8) for B, N in shapes]
+    outs = [_buffers(B, N) for B, N in shapes]
+    spa.group(*[spa.spa_pack(None, m, None, None, 0, None, *o, prepare=True) for m, o in zip(masks, outs)])()
+    torch.cuda.synchronize()
+    for m, o in zip(masks, outs):
+        _check(m, torch.arange(m.shape[1], device="cuda"), *o)
