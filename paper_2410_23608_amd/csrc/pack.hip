@@ -501,12 +501,17 @@ static int rows_per_block(long chunks) {
   return (int)(r < 1 ? 1 : r);
 }
 
-static int pick_tile(int B, int N, bool have_counts) {
-  // Small tiles give more workgroups (bandwidth), but without per-image counts every
-  // workgroup re-reads the mask prefix, so keep tiles larger when B*N is large.
-  const long want = (!have_counts && (long)B * N > 16384) ? 512 : 1024;
-  int tile = 256;
-  while (tile > 16 && (long)B * ((N + tile - 1) / tile) < want) tile >>= 1;
+// Tokens of a tile where rows of row_bytes are copied (0: none).  Small tiles spread the copy, so 16 while their workgroups
+// are resident together (1024), and beyond that as long as a tile's rows have 40 KB; but without per-image counts every
+// workgroup reads the mask before its tile, so no more workgroups than that keeps below what is copied.  us, tiles of 16 / 32 / 64:
+// rows of 1536 bytes, 128 x 196 tokens 10.1 / 8.6 / 10.1, 64 x 196 6.3 / 6.6 / 8.0; of 768 bytes, 128 x 196 8.5 / 6.5 / 7.0; of 2688 bytes,
+// 92 x 391 17.7 / 18.3 / 20.1, 16 x 4200 37.2 / 38.5 / 40.6.
+static int pick_tile(int B, int N, long row_bytes, bool have_counts) {
+  const auto tiles = [&](int tile) { return (long)B * ((N + tile - 1) / tile); };
+  int tile = 16;
+  while (tile < 256 && ((tiles(tile) > 1024 && tile * row_bytes < 40960) ||
+                        (!have_counts && tiles(tile) > std::max(1024L, 2 * row_bytes))))
+    tile *= 2;
   if (options().pack_tile != 0) tile = options().pack_tile;       // option pack_tile
   return tile;
 }
@@ -550,7 +555,7 @@ static int pack_common(const char* fn, const void* x, const uint8_t* mask, const
   SPA_REQUIRE(aligned16(x) && aligned16(packed), SPA_ERR_INVALID_ARG, "%s: x / packed not 16-byte aligned", fn);
   const bool index = packed == nullptr;
   const int threads = index ? index_threads((long)B * N) : kPackThreads;
-  const int tile = index ? index_tile(threads) : pick_tile(B, N, counts != nullptr);
+  const int tile = index ? index_tile(threads) : pick_tile(B, N, (long)C * elem_size(dtype), counts != nullptr);
   const int tpi = (N + tile - 1) / tile;
   SPA_REQUIRE((long)B * tpi < 2147483647L, SPA_ERR_INVALID_ARG, "%s: too many tiles", fn);
   const dim3 grid((unsigned)((long)B * tpi)), block(threads);
@@ -607,7 +612,7 @@ extern "C" int spa_pack_pair(const void* x, int C, const void* x2, int C2, const
   if (int rc = check_rows(fn, B, N, C2, dtype)) return rc;
   SPA_REQUIRE(aligned16(x) && aligned16(packed) && aligned16(x2) && aligned16(packed2), SPA_ERR_INVALID_ARG,
               "%s: buffers not 16-byte aligned", fn);
-  const int tile = pick_tile(B, N, counts != nullptr);
+  const int tile = pick_tile(B, N, ((long)C + C2) * elem_size(dtype), counts != nullptr);
   const int tpi = (N + tile - 1) / tile;
   SPA_REQUIRE((long)B * tpi < 2147483647L, SPA_ERR_INVALID_ARG, "%s: too many tiles", fn);
   const dim3 grid((unsigned)((long)B * tpi)), block(kPackThreads);
@@ -689,7 +694,7 @@ extern "C" int spa_pack_containers(const uint8_t* mask, int B, int grid_h, int g
       return rc;
     return spa_container_segments(cu_seqlens, B, container_len, (int64_t)B * N, seg_cap, seg_cu_seqlens, n_segments, stream);
   }
-  const int tile = pick_tile(B, N, false), tpi = (N + tile - 1) / tile;
+  const int tile = pick_tile(B, N, 0, false), tpi = (N + tile - 1) / tile;
   SPA_REQUIRE((long)B * tpi + 1 < 2147483647L, SPA_ERR_INVALID_ARG, "%s: too many tiles", fn);
   const PackArgs<__bf16> a = {nullptr, mask, nullptr, nullptr, B, N, 8, tile, tpi, 0, Shift{grid_h, grid_w, sh, sw}, nullptr,
                               cu_seqlens, gather_idx, inv_pos, total, nullptr, 0, nullptr};
