@@ -478,8 +478,7 @@ __device__ __forceinline__ void bwd_dvec_block(const BwdArgs& p, unsigned block,
 #pragma unroll
       for (int e = 0; e < 8; ++e) d = fmaf(of[e], gf[e], d);
     }
-#pragma unroll
-    for (int o = 1; o < CPR; o <<= 1) d += __shfl_xor(d, o, kWave);
+    d = adjacent_sum<CPR>(d);
     if (i < total && c == 0) p.dvec[h * p.lse_stride + row] = d;
   }
 }
@@ -612,8 +611,7 @@ attn_bwd_short_bf16_kernel(const BwdArgs p) {
         float d = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) d = fmaf(of[e], gf[e], d);
-#pragma unroll
-        for (int o = 1; o < CPR; o <<= 1) d += __shfl_xor(d, o, kWave);     // the CPR chunks of a row: adjacent lanes
+        d = adjacent_sum<CPR>(d);                                           // the CPR chunks of a row: adjacent lanes
         if (c == 0) {
           Ds[r] = d;
           lse2s[r] = lreg[t];

@@ -284,12 +284,7 @@ __device__ __forceinline__ LiveOrder live_order(int xcd, int H, int B, const int
   const int rank_l = ok ? pair / H : 0;
   const int len_l = __builtin_amdgcn_ds_bpermute(rank_l << 2, o.len);
   o.nb = ok ? (len_l + rows - 1) / rows : 0;
-  o.incl = o.nb;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int up = __shfl_up(o.incl, d, 64);
-    if (lane >= d) o.incl += up;
-  }
+  o.incl = wave_scan(o.nb);
   return o;
 }
 // kPasses == 2: the numbers after an XCD's last live block go through the same blocks once more.

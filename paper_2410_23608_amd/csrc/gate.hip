@@ -50,10 +50,6 @@ __device__ __forceinline__ void widen(bf16x8 v, float (&f)[8]) {
 // vector ALU: the two halves and the two 16-lane rows of a half by the lane swaps, ^ 8 as a rotation of the row by 8, ^ 4 as
 // one by 4 once both halves of a row hold the same (groups of 8: as two shifts), ^ 2 and ^ 1 inside a quad.  An
 // exchange through LDS takes 85 cycles, one of these 8 to 16, and the dot products wait for each of them.
-template <int CTRL, int BANKS = 0xF>
-__device__ __forceinline__ float dpp_move(float v, float other = 0.f) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, other), __builtin_bit_cast(int, v), CTRL, 0xF, BANKS, false));
-}
 __device__ __forceinline__ float add_lane_xor32(float v) {
   const unsigned u = __builtin_bit_cast(unsigned, v);
   const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
@@ -68,14 +64,14 @@ __device__ __forceinline__ float add_lane_xor16(float v) {
 }
 template <int G>
 __device__ __forceinline__ float group_sum(float v) {
-  constexpr int kRor = 0x120, kShl = 0x100, kShr = 0x110;
+  constexpr int kRor = 0x120;
   if (G > 32) v = add_lane_xor32(v);
   if (G > 16) v = add_lane_xor16(v);
   if (G > 8) v += dpp_move<kRor + 8>(v);
   if (G > 8) v += dpp_move<kRor + 4>(v);
-  else v += dpp_move<kShr + 4, 0xA>(v, dpp_move<kShl + 4, 0x5>(v));
-  v += dpp_move<0x4E>(v);                                  // quad_perm [2, 3, 0, 1]
-  return v + dpp_move<0xB1>(v);                            // quad_perm [1, 0, 3, 2]
+  else v += lane_xor<4>(v);
+  v += lane_xor<2>(v);
+  return v + lane_xor<1>(v);
 }
 
 // Lanes per token: by the row's 16-byte chunks (the same for every launch of the gate)
@@ -168,12 +164,7 @@ __device__ __forceinline__ void build_pack_index(const uint8_t* mask, int ntok, 
       if (t_super + r * kPerRound >= ntok) break;      // uniform
       const int cnt = nonzero_bytes_u32(m[r][0]) + nonzero_bytes_u32(m[r][1]) + nonzero_bytes_u32(m[r][2]) +
                       nonzero_bytes_u32(m[r][3]);
-      int inc = cnt;                                   // inclusive scan over the wave
-#pragma unroll
-      for (int o = 1; o < kWave; o <<= 1) {
-        const int up = __shfl_up(inc, o, kWave);
-        if (lane >= o) inc += up;
-      }
+      const int inc = wave_scan(cnt);
       if (lane == kWave - 1) s_wave[r & 1][wv] = inc;
       __syncthreads();                                 // one barrier per round: the wave totals alternate between two rows
       int run = carry + inc - cnt, total = 0;          // selected tokens before this thread's first token
@@ -476,8 +467,7 @@ count_selected_kernel(const uint8_t* __restrict__ mask, int N, int32_t* __restri
   const uint8_t* m = mask + (long)blockIdx.x * N;
   int c = 0;
   for (int i = threadIdx.x; i < N; i += 256) c += m[i] != 0;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, kWave);
+  c = wave_sum(c);
   if (lane_id() == 0) red[threadIdx.x / kWave] = c;
   __syncthreads();
   if (threadIdx.x == 0) counts[blockIdx.x] = red[0] + red[1] + red[2] + red[3];

@@ -282,7 +282,7 @@ struct SegmentArgs {
 __device__ __forceinline__ void segments_block(const int32_t* cu_seqlens, int B, const SegmentArgs& s) {
   const int L = s.L, seg_cap = s.cap;
   int32_t *seg_cu = s.seg_cu, *n_segments = s.n_segments;
-  __shared__ int wave_sum[4];
+  __shared__ int wave_total[4];
   __shared__ int carry_s;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   if (tid == 0) carry_s = 0;
@@ -297,16 +297,11 @@ __device__ __forceinline__ void segments_block(const int32_t* cu_seqlens, int B,
       if (end > start) cnt = (end + L - 1) / L - start / L;   // the image's start, then every multiple of L inside it
     }
     // exclusive scan of cnt over the 256 images of this round
-    int inc = cnt;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int up = __shfl_up(inc, o, 64);
-      if (lane >= o) inc += up;
-    }
-    if (lane == 63) wave_sum[wv] = inc;
+    const int inc = wave_scan(cnt);
+    if (lane == 63) wave_total[wv] = inc;
     __syncthreads();
     int off = carry_s;
-    for (int i = 0; i < wv; ++i) off += wave_sum[i];
+    for (int i = 0; i < wv; ++i) off += wave_total[i];
     const int first = off + inc - cnt;
     for (int i = 0; i < cnt; ++i) {
       const int pos = i == 0 ? start : (start / L + i) * L;
@@ -387,12 +382,7 @@ __global__ void __launch_bounds__(kPackThreads) pack_containers_kernel(const Pac
   int own[4], sum = 0;
 #pragma unroll
   for (int e = 0; e < 4; ++e) own[e] = sum += 4 * tid + e < B ? cu[4 * tid + e + 1] : 0;
-  int inc = sum;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int up = __shfl_up(inc, o, kWave);
-    if (lane_id() >= o) inc += up;
-  }
+  const int inc = wave_scan(sum);
   if (lane_id() == kWave - 1) sums[tid / kWave] = inc;
   __syncthreads();
   int off = inc - sum;

@@ -70,6 +70,35 @@ __device__ __forceinline__ int wave_sum(int v) {
   return add_dpp<0xB1>(add_dpp<0x4E>(add_dpp<0x124>(add_dpp<0x128>((int)(d + e)))));
 }
 
+// Inclusive sums over the wave: shifts by 1, 2, 4 and 8 in a row of 16, then the last lane of every other row and of the
+// first half to the rows after them.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int add_dpp_rows(int v) { return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false); }
+__device__ __forceinline__ int wave_scan(int v) {
+  v = add_dpp_rows<0x118, 0xF>(add_dpp_rows<0x114, 0xF>(add_dpp_rows<0x112, 0xF>(add_dpp_rows<0x111, 0xF>(v))));
+  return add_dpp_rows<0x143, 0xC>(add_dpp_rows<0x142, 0xA>(v));
+}
+// The value of another lane, without LDS: lane ^ 1, ^ 2 inside a quad, ^ 4 as two shifts.
+template <int CTRL, int BANKS = 0xF>
+__device__ __forceinline__ float dpp_move(float v, float other = 0.f) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, other), __builtin_bit_cast(int, v), CTRL, 0xF, BANKS, false));
+}
+template <int MASK>
+__device__ __forceinline__ float lane_xor(float v) {
+  static_assert(MASK == 1 || MASK == 2 || MASK == 4, "inside a row of 16");
+  if (MASK == 1) return dpp_move<0xB1>(v);
+  if (MASK == 2) return dpp_move<0x4E>(v);
+  return dpp_move<0x114, 0xA>(v, dpp_move<0x104, 0x5>(v));
+}
+// Sum over G = 4 or 8 adjacent lanes, in every one of them
+template <int G>
+__device__ __forceinline__ float adjacent_sum(float v) {
+  static_assert(G == 4 || G == 8, "a quad or two");
+  v += lane_xor<1>(v);
+  v += lane_xor<2>(v);
+  return G == 8 ? v + lane_xor<4>(v) : v;
+}
+
 // 8 bf16 (one 16-byte chunk) <-> 8 floats
 __device__ __forceinline__ floatx8 bf16x8_to_float(bf16x8 v) { return __builtin_convertvector(v, floatx8); }
 __device__ __forceinline__ bf16x8 float_to_bf16x8(floatx8 v) { return __builtin_convertvector(v, bf16x8); }
