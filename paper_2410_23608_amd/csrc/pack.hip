@@ -378,6 +378,37 @@ __global__ void __launch_bounds__(kPackThreads) pack_containers_kernel(const Pac
         atomicAdd(&cu[img[u] + 1], nonzero_bytes(v[u][0]) + nonzero_bytes(v[u][1]) + nonzero_bytes(v[u][2]) + nonzero_bytes(v[u][3]));
   }
   __syncthreads();
+  // Up to 256 images, one a thread: its tokens and its segments by two sums over the workgroup, in registers (through
+  // cu as below, five barriers and a dozen trips to LDS more: 256 x 196 tokens 6.7 us, here 6.2; 8 x 4200 10.2, 9.7)
+  if (B <= kPackThreads) {
+    __shared__ int sums2[kPackWaves];
+    const int n_b = tid < B ? cu[tid + 1] : 0, wv = tid / kWave;
+    int end = wave_scan(n_b);
+    if (lane_id() == kWave - 1) sums[wv] = end;
+    __syncthreads();
+    int T = 0;
+#pragma unroll
+    for (int i = 0; i < kPackWaves; ++i) {
+      if (i < wv) end += sums[i];
+      T += sums[i];
+    }
+    const int start = end - n_b, q = start / s.L, cnt = n_b > 0 ? (end + s.L - 1) / s.L - q : 0;
+    int first = wave_scan(cnt);
+    if (lane_id() == kWave - 1) sums2[wv] = first;
+    __syncthreads();
+    int n = 0;
+    first -= cnt;
+#pragma unroll
+    for (int i = 0; i < kPackWaves; ++i) {
+      if (i < wv) first += sums2[i];
+      n += sums2[i];
+    }
+    for (int i = 0; i < cnt; ++i)
+      if (first + i <= s.cap) s.seg_cu[first + i] = i == 0 ? start : (q + i) * s.L;
+    for (int i = n + tid; i <= s.cap; i += kPackThreads) s.seg_cu[i] = T;
+    if (tid == 0) s.n_segments[0] = n;
+    return;
+  }
   // cu[b + 1] = tokens of the images up to b: four images per thread, then over the threads
   int own[4], sum = 0;
 #pragma unroll

@@ -60,3 +60,27 @@ def test_index_alone_in_a_group(shapes):
     torch.cuda.synchronize()
     for m, o in zip(masks, outs):
         _check(m, torch.arange(m.shape[1], device="cuda"), *o)
+
+
+@pytest.mark.parametrize("B", [1, 63, 64, 65, 255, 256, 257])
+@pytest.mark.parametrize("L", [1, 7, 64])
+def test_segment_list_on_both_sides_of_a_thread_an_image(B, L):
+    from paper_2410_23608_amd import spa
+    h, w, N = 3, 7, 21
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B + L)
+    mask = (torch.rand(B, N, generator=g, device="cuda") < 0.5).to(torch.uint8)
+    mask[B // 2] = 0                                       # (an image without tokens has no segment)
+    cap = B + B * N // L
+    cu, gi, inv, tot = _buffers(B, N)
+    seg, n = torch.full((cap + 1,), -7, dtype=torch.int32, device="cuda"), torch.full((1,), -7, dtype=torch.int32, device="cuda")
+    spa.spa_pack_containers(mask, h, w, 0, 0, L, cu, gi, inv, tot, seg, n)
+    torch.cuda.synchronize()
+    _check(mask, torch.arange(N, device="cuda"), cu, gi, inv, tot)
+    ends = cu.tolist()
+    ref = []
+    for b in range(B):
+        if ends[b + 1] > ends[b]:
+            ref += [ends[b]] + [p for p in range(ends[b] + 1, ends[b + 1]) if p % L == 0]
+    assert n.item() == len(ref)
+    assert seg.tolist() == ref + [ends[B]] * (cap + 1 - len(ref))
