@@ -29,20 +29,20 @@ PRE = "cd /tmp && export TMPDIR=/tmp && "
 CHAINS = {
     "forward_fused": [("gate_select_kernel", "gate_select_index"), ("attn_fwd", "gathered_attention_unpack")],
     "forward_selected": [("gate_select_kernel", "gate_select"), ("attn_fwd", "selected_attention_unpack")],
-    "forward_gathered": [("gate_select_kernel", "gate_select"), ("pack_kernel", "pack_indices"),
+    "forward_gathered": [("gate_select_kernel", "gate_select"), ("pack_index_kernel", "pack_indices"),
                          ("attn_fwd", "gathered_attention_unpack")],
     "forward_packed": [("gate_select_kernel", "gate_select"), ("pack_kernel", "pack"),
                        ("attn_fwd", "packed_attention_unpack")],
-    "train": [("gate_select_kernel", "gate_select"), ("pack_kernel", "pack_indices"), ("attn_fwd", "gated_attention_unpack"),
+    "train": [("gate_select_kernel", "gate_select"), ("pack_index_kernel", "pack_indices"), ("attn_fwd", "gated_attention_unpack"),
               ("attn_bwd", "gated_attention_bwd_tokens"), ("gate_bwd", "gate_bwd")],
 }
-CHAINS["hierarchy"] = [("gate_pyramid_kernel", "gate_select"), ("pack_group_kernel", "pack_indices"),
+CHAINS["hierarchy"] = [("gate_pyramid_kernel", "gate_select"), ("pack_index_group_kernel", "pack_indices"),
                        ("attn_fwd_bf16_group_kernel<1>", "gathered_attention_unpack"),      # the forward-only chain
                        ("attn_fwd_bf16_group_kernel<2>", "gated_attention_unpack"),
                        ("attn_bwd_dvec_group", "gated_attention_bwd_tokens"), ("attn_bwd_group", "gated_attention_bwd_tokens"),
                        ("gate_bwd_group", "gate_bwd"), ("gate_bwd_reduce_group", "gate_bwd")]
 # a whole bench.py run (every configuration and the extras): calls named by kind only
-CHAINS["all"] = [("gate_select_kernel", "gate"), ("count_selected", "gate"), ("pack_kernel", "pack"), ("unpack_kernel", "unpack"),
+CHAINS["all"] = [("gate_select_kernel", "gate"), ("count_selected", "gate"), ("unpack_kernel", "unpack"), ("pack_", "pack"),
                  ("gather_rows", "unpack / pack backward"), ("attn_fwd", "attention forward"), ("attn_bwd", "attention backward"),
                  ("gate_bwd", "gate backward"), ("linear_bwd", "projection backward"), ("linear", "projection"),
                  ("container_segments", "container segments"), ("maxpool", "max-pool"), ("ceiling", "yardstick")]
