@@ -826,6 +826,7 @@ struct MaskLds {
 // Unit j of XCD xcd (N <= 256 tokens per image, mask and fill of y: a.sc), wave `part` of it
 template <int DH, int STEP, int SPLIT>
 __device__ __forceinline__ void mask_unit(MaskLds<DH, STEP, SPLIT>& lds, const FwdArgs& a, int xcd, int j, int part) {
+  if (SPLIT == 1) part = 0;
   const TileId tile_id = xcd_tile_at(xcd, j, a.nqb, a.H, a.B);
   if (!tile_id.valid) {
     if (SPLIT > 1) __syncthreads();
@@ -940,6 +941,7 @@ static unsigned lpt64_grid(int B, int H, int nqb) {
 // batch has ~2800 live waves for 1024 SIMDs and then runs in one round instead of two.
 template <int DH, int STEP, int GATHER, int SPLIT>
 __device__ __forceinline__ void lpt64_unit(WaveLds<DH, STEP>* lds, const FwdArgs& a, int x, int j, int units, int part) {
+  if (SPLIT == 1) part = 0;
   const int unit = j & 31, m = j >> 5;
   const LptBlock blk = lpt64_block<32>(a.cu, a.key_lens, a.n_pad, a.B, a.H, a.nqb, x, m * 32 + ((m & 1) ? 31 - unit : unit));
   if (blk.live)
