@@ -595,8 +595,7 @@ __device__ __forceinline__ void tiled_block(TiledShared<DH>& sh, const FwdArgs& 
       if (round > 0) __syncthreads();                       // the parked rows are written
       // More live blocks than workgroups: the longer segments, which began the launch, also end it, so they go first where a
       // SIMD's waves compete (32 x 4200 tokens, 5-40 %, 8 heads of 32: 63.2 -> 61.0 us, 48 images 115 -> 106; 8 images, two
-      // workgroups a unit: 23.0 -> 23.5,
-      // so not there).
+      // workgroups a unit: 23.0 -> 23.5, so not there).
       if (__builtin_amdgcn_readlane(o.incl, 63) > G) {
         if (4 * lt.len > 3 * lt.longest) __builtin_amdgcn_s_setprio(3);
         else if (2 * lt.len > lt.longest) __builtin_amdgcn_s_setprio(2);
