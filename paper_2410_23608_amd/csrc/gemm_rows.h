@@ -181,8 +181,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) g
 // larger.  The row count is only known here.  Measured, K 768, 256 x 256 | 192 x 192, rounds in brackets, us: 11540 rows
 // of 768 columns 24.6 (1) | 19.0 (1), 15052 rows 24.9 (1) | 30.1 (2); rows of 2304 columns: 7526 46.7 (2) | 38.8 (2), 11540
 // 49.8 (2) | 52.2 (3), 12544 51.2 (2) | 64.4 (4), 15052 72.6 (3) | 67.5 (4); K 2304, 11540 rows of 768 columns: 54.3 (1) |
-// 45.5 (1).  At 240 tiles a step of 64 takes 1.0 us, 256 x 256 1.45: bound by the L2 (11 TB/s) and by power (1.8 GHz
-// when all units multiply); launch, first loads and the epilogue of a round take 4 us more.
+// 45.5 (1).  At 240 tiles a step of 64 takes 1.0 us, 256 x 256 1.45: bound by the L2 (11 TB/s), 47 and 65 % of
+// the products' own cycles at 2.0 to 2.3 GHz; launch, first loads and the epilogue of a round take 4 us more.
 template <class T>
 __host__ __device__ inline T gemm_tiles(T rows, T ncols, T edge) { return (rows + edge - 1) / edge * ((ncols + edge - 1) / edge); }
 __host__ __device__ inline bool medium_tiles(int rows, int ncols) {

@@ -68,9 +68,9 @@ static int launch_gemm_rows_tile(const char* fn, const GemmArgs& args, bool big,
 // takes 0.6 us alone on its unit, and the launch 3.3 us before the first and after the last; .95 and 5.5 us beside another,
 // 1.65 where some units have a third tile to take and 0.0026 us per tile of the launch beyond.  A round of the large tiles
 // (gemm_rows.h) takes 5 us and 1.2 a step (192) or 9.5 and 1.2 (256).  In us, 128 | large: 6272 x 2304, K 768 33 | 28;
-// 6272 x 768 16 | 17; 12544 x 768 25 | 23.5; 12544 x 1536, K 512 28 | 33; 12544 x 768, K 2304 62 | 55.  Large where they tie: small
-// tiles fetch more bytes a product and the launches beside and after them then run at a lower clock (9408 x 2304, K 768, 43.4 |
-// 45 on their own, the training step around it 300 | 293).  Option gemm_tm = 2 | 8 forces 128 x 128 | large (tuning aid).
+// 6272 x 768 16 | 17; 12544 x 768 25 | 23.5; 12544 x 1536, K 512 28 | 33; 12544 x 768, K 2304 62 | 55.  Large where they tie: the
+// same launch loses in a step what it wins alone (9408 x 2304, K 768, 43.4 | 45 called again and again, the training step around
+// it 300 | 293).  Option gemm_tm = 2 | 8 forces 128 x 128 | large (tuning aid).
 static bool big_tiles(const GemmArgs& a) {
   const int cfg = options().gemm_tm;
   if (cfg != 0) return cfg == 8;
