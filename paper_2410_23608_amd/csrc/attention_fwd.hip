@@ -16,6 +16,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <limits>
 #include <type_traits>
 
 #include "attn_tiles.h"
@@ -165,6 +166,9 @@ __device__ __forceinline__ void scatter_fill_rows(const Scatter& sc, long r0, lo
 }
 
 // ------------------------------------------------------------------------- bf16 / MFMA
+// The running maximum before any score: the lowest finite number, so that keys whose scores are all -inf (products that
+// overflow; a wave of a split unit may see no others) weigh exp(-inf - m) = 0 instead of exp(-inf + inf) = NaN.
+constexpr float kNoScore = -std::numeric_limits<float>::max();
 // Per-wave state of the softmax: O^T accumulators (rows = head dim, cols = this wave's 32
 // queries), running maximum m of the scores (log2 domain, scale folded in; see fwd_exp) and running
 // sum l (the two halves of the wave keep partial sums that are added at the end).
@@ -177,7 +181,7 @@ struct FwdAcc {
     for (int d = 0; d < DH / 32; ++d)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[d][r] = 0.f;
-    m = -INFINITY;
+    m = kNoScore;
     l = 0.f;
   }
 };
@@ -1171,7 +1175,7 @@ attn_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
     for (int d = 0; d < DB; ++d)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[d][r] = 0.f;
-    float m = -INFINITY, l = 0.f;
+    float m = kNoScore, l = 0.f;
     if (first < seg.nk) {
       fetch(row, kf, vf);
       row = key_row(first + 32 * SPLIT);

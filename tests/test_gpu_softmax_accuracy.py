@@ -193,6 +193,38 @@ def test_infinities_and_nan_stay_where_they_belong(form, Dh, N):
             assert torch.isnan(y[r, c]).all() if math.isnan(val) else (y[r, c] == val).all(), (c, val)
 
 
+@pytest.mark.parametrize("steps", [(0,), (1,), (2,), (3,), (0, 1), (0, 1, 2, 3)])
+@pytest.mark.parametrize("form,Dh,N", _forms(FORMS, [(32, 256), (64, 196), (64, 300), (32, 700)]))
+def test_scores_of_minus_infinity_weigh_nothing(form, Dh, N, steps):
+    """Products that overflow to -inf on whole steps of 32 keys, from the first one on or in between: those keys weigh 0
+    and the other rows are what they are without them.  Of an image all of whose scores are -inf y is NaN, lse -inf."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + Dh)
+    H, lens = 2, [N, N - 3, 161, 40]
+    C, T = H * Dh, sum(lens)
+    q, k, v = (torch.randn(T, H, Dh, generator=g, device="cuda") for _ in range(3))
+    q[..., 0], k[..., 0] = 2.0 ** 120, 0.0
+    starts = [sum(lens[:b]) for b in range(len(lens))]
+    for s0 in starts[:3]:
+        for j in steps:
+            k[s0 + 32 * j:s0 + 32 * (j + 1), :, 0] = -2.0 ** 120
+    k[starts[3]:, :, 0] = -2.0 ** 120
+    q, k, v = (t.reshape(T, C).bfloat16() for t in (q, k, v))
+    y, _, lse, _ = _forward(form, q, k, v, lens, N, H, Dh)
+    for s0, n in zip(starts[:3], lens[:3]):
+        r = slice(s0, s0 + n)
+        Q, K, V = (t[r].double().view(n, H, Dh).transpose(0, 1).contiguous() for t in (q, k, v))
+        S = Q @ K.transpose(1, 2).contiguous() / math.sqrt(Dh)
+        want = (torch.softmax(S, -1) @ V).transpose(0, 1).reshape(n, C)
+        # probabilities and results rounded to bf16: 2^-9 each of the largest |v|
+        assert torch.isfinite(y[r]).all() and (y[r].double() - want).abs().max() <= 2 ** -7 * float(V.abs().max())
+        if lse is not None:
+            assert (lse[:, r] - torch.logsumexp(S, -1)).abs().max() <= 1e-4      # sums of up to 700 terms in fp32
+    assert torch.isnan(y[starts[3]:]).all()
+    if lse is not None:
+        assert (lse[:, starts[3]:] == -float("inf")).all()
+
+
 @pytest.mark.parametrize("gated", [False, True])
 @pytest.mark.parametrize("Dh,N", [(32, 300), (64, 290)])
 def test_an_infinite_gradient_reaches_dv_as_itself(Dh, N, gated):

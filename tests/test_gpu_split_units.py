@@ -63,3 +63,26 @@ def test_units_of_several_waves(form, dtype, H, Dh, N):
     if form != "selected":
         assert (out[:T].cpu().double() - got[rows]).abs().max() == 0
         assert (lse[:, :T].cpu().double() - ref_lse).abs().max() <= 1e-5
+
+
+@pytest.mark.parametrize("steps", [(0,), (1,), (2,), (3,), (0, 1, 2, 3)])
+@pytest.mark.parametrize("H,Dh,N", [(2, 32, 196), (1, 64, 193), (300, 32, 196), (1, 32, 64)])
+def test_fp32_scores_of_minus_infinity_weigh_nothing(H, Dh, N, steps):
+    """Products that overflow to -inf on whole steps of 32 keys (the first four steps are the first of a wave each where
+    four share a unit; 300 heads and 64 tokens: one wave a unit): those keys weigh 0."""
+    from paper_2410_23608_amd import spa
+    g = torch.Generator().manual_seed(N + Dh)
+    C = H * Dh
+    q, k, v = (torch.randn(N, H, Dh, generator=g) for _ in range(3))
+    q[..., 0], k[..., 0] = 2.0 ** 120, 0.0
+    steps = [j for j in steps if 32 * (j + 1) < N]
+    for j in steps:
+        k[32 * j:32 * (j + 1), :, 0] = -2.0 ** 120
+    q, k, v = (t.reshape(N, C) for t in (q, k, v))
+    ref, ref_lse = _reference(q.double(), k.double(), v.double(), [N], H, Dh)
+    cu = torch.tensor([0, N], dtype=torch.int32, device="cuda")
+    out, lse = torch.full((N, C), float("nan"), device="cuda"), torch.zeros(H, N, device="cuda")
+    spa.spa_packed_attention(q.cuda(), k.cuda(), v.cuda(), cu, 1, N, H, Dh, out, lse)
+    torch.cuda.synchronize()
+    # sums of up to 196 products of rounding 2^-24 on each, values up to 6
+    assert (out.cpu().double() - ref).abs().max() <= 1e-5 and (lse.cpu().double() - ref_lse).abs().max() <= 1e-5
