@@ -4,6 +4,7 @@
 #include <type_traits>
 
 #include "gemm_async.h"
+#include "gemm_shape.h"
 #include "linear.h"
 #include "spa_common.h"
 
@@ -183,12 +184,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) g
 // 49.8 (2) | 52.2 (3), 12544 51.2 (2) | 64.4 (4), 15052 72.6 (3) | 67.5 (4); K 2304, 11540 rows of 768 columns: 54.3 (1) |
 // 45.5 (1).  At 240 tiles a step of 64 takes 1.0 us, 256 x 256 1.45: bound by the L2 (11 TB/s), 47 and 65 % of
 // the products' own cycles at 2.0 to 2.3 GHz; launch, first loads and the epilogue of a round take 4 us more.
-template <class T>
-__host__ __device__ inline T gemm_tiles(T rows, T ncols, T edge) { return (rows + edge - 1) / edge * ((ncols + edge - 1) / edge); }
-__host__ __device__ inline bool medium_tiles(int rows, int ncols) {
-  return 7 * ((gemm_tiles(rows, ncols, 192) + 255) / 256) <= 10 * ((gemm_tiles(rows, ncols, 256) + 255) / 256);
-}
-
 template <bool kScale, bool kDeep>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1))) gemm_rows_big_kernel(const GemmArgs p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char gemm_smem[];

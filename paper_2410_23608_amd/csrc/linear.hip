@@ -64,23 +64,9 @@ static int launch_gemm_rows_tile(const char* fn, const GemmArgs& args, bool big,
   return check_launch(fn);
 }
 
-// Tile shape, from about half of the capacity live (what a packed stream has).  Measured times: a 128 x 128 x 64 step
-// takes 0.6 us alone on its unit, and the launch 3.3 us before the first and after the last; .95 and 5.5 us beside another,
-// 1.65 where some units have a third tile to take and 0.0026 us per tile of the launch beyond.  A round of the large tiles
-// (gemm_rows.h) takes 5 us and 1.2 a step (192) or 9.5 and 1.2 (256).  In us, 128 | large: 6272 x 2304, K 768 33 | 28;
-// 6272 x 768 16 | 17; 12544 x 768 25 | 23.5; 12544 x 1536, K 512 28 | 33; 12544 x 768, K 2304 62 | 55.  Large where they tie: the
-// same launch loses in a step what it wins alone (9408 x 2304, K 768, 43.4 | 45 called again and again, the training step around
-// it 300 | 293).  Option gemm_tm = 2 | 8 forces 128 x 128 | large (tuning aid).
 static bool big_tiles(const GemmArgs& a) {
-  const int cfg = options().gemm_tm;
-  if (cfg != 0) return cfg == 8;
-  const int live = a.total != nullptr ? a.m_cap / 2 : a.m_cap;
-  const auto tiles = [&](long edge) { return gemm_tiles<long>(live, a.ncols, edge); };
-  const auto rounds = [&](long edge) { return (double)((tiles(edge) + 255) / 256); };
-  const double nk = (a.kc + kGaK - 1) / kGaK, t = (double)tiles(128);
-  const double small = t <= 256 ? 3.3 + 0.6 * nk : 5.5 + nk * (t <= 512 ? 0.95 : fmax(1.65, 0.0026 * t));
-  const double big = medium_tiles(live, a.ncols) ? rounds(192) * (5.0 + 1.2 * nk) : rounds(256) * (9.5 + 1.2 * nk);
-  return big < 1.03 * small;
+  const int cfg = options().gemm_tm;      // 2 | 8 forces 128 x 128 | large (tuning aid)
+  return cfg != 0 ? cfg == 8 : large_tiles(a.m_cap, a.total != nullptr, a.ncols, a.kc);
 }
 
 int launch_gemm_rows(const char* fn, const GemmArgs& args, bool deep, hipStream_t st) {
