@@ -188,8 +188,10 @@ template <bool kScale, bool kDeep>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1))) gemm_rows_big_kernel(const GemmArgs p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char gemm_smem[];
   const int M = p.total != nullptr ? min(p.total[0], p.m_cap) : p.m_cap;
-  if (medium_tiles(M, p.ncols)) gemm_rows_block<Mfma16, kScale, kDeep, true, 192, 192, 4, 2, 3>(p, gemm_smem, blockIdx.x, gridDim.x);
-  else gemm_rows_block<Mfma32, kScale, kDeep, true, 256, 256, 2, 4, 2>(p, gemm_smem, blockIdx.x, gridDim.x);
+  if (p.large_edge != 0 ? p.large_edge == 192 : medium_tiles(M, p.ncols))
+    gemm_rows_block<Mfma16, kScale, kDeep, true, 192, 192, 4, 2, 3>(p, gemm_smem, blockIdx.x, gridDim.x);
+  else
+    gemm_rows_block<Mfma32, kScale, kDeep, true, 256, 256, 2, 4, 2>(p, gemm_smem, blockIdx.x, gridDim.x);
 }
 
 }  // namespace spa

@@ -20,11 +20,12 @@ struct GemmArgs {
   const __bf16* residual;
   const int32_t* inv_pos;        // given: the rows i < zrows of out with inv_pos[i] < 0 are zeroed (copied from residual)
   long zrows;
+  int large_edge;                // edge of the large tiles: 192 | 256, 0: by the live rows (medium_tiles)
 };
 
 // deep = false: out = A W^T (W [ncols][kc]); true: out = A W (W [kc][ncols]).
 int launch_gemm_rows(const char* fn, const GemmArgs& args, bool deep, hipStream_t st);
-// Inside a launch group (linear_bwd.hip): the row GEMM of a backward input side is noted; big: with 256 x 256 tiles.
+// Inside a launch group (linear_bwd.hip): the row GEMM of a backward input side is noted; big: with large tiles.
 int group_note_rows(const char* fn, const GemmArgs& args, bool big);
 
 }  // namespace spa

@@ -64,13 +64,13 @@ static int launch_gemm_rows_tile(const char* fn, const GemmArgs& args, bool big,
   return check_launch(fn);
 }
 
-static bool big_tiles(const GemmArgs& a) {
-  const int cfg = options().gemm_tm;      // 2 | 8 forces 128 x 128 | large (tuning aid)
-  return cfg != 0 ? cfg == 8 : large_tiles(a.m_cap, a.total != nullptr, a.ncols, a.kc);
-}
-
-int launch_gemm_rows(const char* fn, const GemmArgs& args, bool deep, hipStream_t st) {
-  const bool big = big_tiles(args);
+// Option gemm_tm (tuning aid) forces a shape: 2 | 6 | 8 for 128 x 128 | 192 x 192 | 256 x 256, 14 for either large one by
+// the live rows.
+int launch_gemm_rows(const char* fn, const GemmArgs& a, bool deep, hipStream_t st) {
+  const int cfg = options().gemm_tm;
+  const bool big = cfg != 0 ? cfg >= 6 : large_tiles(a.m_cap, a.total != nullptr, a.ncols, a.kc);
+  GemmArgs args = a;
+  args.large_edge = cfg == 6 ? 192 : cfg == 8 ? 256 : 0;
   if (group_open()) return group_note_rows(fn, args, big);
   if (deep) return launch_gemm_rows_tile<false, true>(fn, args, big, st);
   if (args.scores != nullptr) return launch_gemm_rows_tile<true, false>(fn, args, big, st);

@@ -1,5 +1,5 @@
-"""The projection GEMMs with the tile shapes that the row count decides on the device: 192 x 192 (fewer rounds of
-the units, or one each) and 256 x 256, one and several tiles per resident workgroup, rows, columns and contraction on
+"""The projection GEMMs with large tiles, 192 x 192, 256 x 256 and the shape that the row count decides on the device
+(192 x 192 with fewer rounds of the units, or one each), one and several tiles per resident workgroup, rows, columns and contraction on
 and next to the tile edges; against products in fp64.
 
 Bound: both sides take the same bf16 operands; the products are summed in fp32 (K terms, error below K 2^-24 sum |a b|)
@@ -17,7 +17,8 @@ SHAPES = [(500, 384, 64, 192), (500, 193, 136, 328), (400, 191, 8, 200), (4300, 
 
 @pytest.mark.parametrize("cap,T,K,N", SHAPES)
 @pytest.mark.parametrize("ordered", [False, True])
-def test_row_gemms_of_every_tile_shape(cap, T, K, N, ordered):
+@pytest.mark.parametrize("tile", ["14", "6", "8"])
+def test_row_gemms_of_every_tile_shape(cap, T, K, N, ordered, tile):
     from paper_2410_23608_amd import spa
     g = torch.Generator(device="cuda")
     g.manual_seed(cap + T)
@@ -32,7 +33,7 @@ def test_row_gemms_of_every_tile_shape(cap, T, K, N, ordered):
     s = torch.randn(cap, generator=g, device="cuda")
     tot = torch.tensor([T], dtype=torch.int32, device="cuda")
     rows = torch.arange(T, device="cuda") if ordered else idx
-    spa.spa_set_option("gemm_tm", "8")
+    spa.spa_set_option("gemm_tm", tile)
     try:
         out = torch.full((cap, N), float("nan"), device="cuda", dtype=torch.bfloat16)
         spa.spa_linear_packed(x, None if ordered else gi, None if ordered else s, tot, W, b, out)
@@ -60,3 +61,28 @@ def test_row_gemms_of_every_tile_shape(cap, T, K, N, ordered):
     assert torch.equal(y[inv < 0], res[inv < 0])
     check(dx[idx], d[rows], Wd, torch.zeros(T, N, device="cuda"))
     assert (dx[inv < 0] == 0).all()
+
+
+@pytest.mark.parametrize("T,K,N", [(1001, 1032, 1544), (4225, 264, 2312), (130, 2304, 768)])
+def test_every_shape_gives_the_same_bits(T, K, N):
+    """A product sums in the same order whatever the tile (both matrix instructions add their elements in the same
+    order): which shape the row count or the capacity chooses does not show in the results."""
+    from paper_2410_23608_amd import spa
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
+    x, W, Wd, b, tot = rnd(T, K), rnd(N, K), rnd(K, N), rnd(N), torch.tensor([T], dtype=torch.int32, device="cuda")
+    s, idx = torch.randn(T, generator=g, device="cuda"), torch.randperm(T, generator=g, device="cuda").int()
+    got = []
+    for tile in ("2", "6", "8", "14"):
+        spa.spa_set_option("gemm_tm", tile)
+        try:
+            out = [torch.empty(T, N, device="cuda", dtype=torch.bfloat16) for _ in range(2)]
+            spa.spa_linear_packed(x, idx, s, tot, W, b, out[0])
+            spa.spa_linear_packed_bwd_input(x, idx, tot, Wd, T, None, None, out[1])
+        finally:
+            spa.spa_set_option("gemm_tm")
+        got.append(out)
+    torch.cuda.synchronize()
+    for other in got[1:]:
+        assert torch.equal(got[0][0], other[0]) and torch.equal(got[0][1], other[1])

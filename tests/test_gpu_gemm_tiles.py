@@ -1,5 +1,5 @@
 """The pipelined projection GEMMs at the edges of their tiles: row counts, widths and contraction
-lengths on and next to 64 / 128 / 256, one and no live row, both tile shapes, one and several token
+lengths on and next to 64 / 128 / 256, one and no live row, every tile shape, one and several token
 chunks of the weight side, and the output projection with the scatter and the copy of the other rows;
 against products in fp32."""
 import pytest
@@ -20,7 +20,7 @@ def _close(got, ref, tol):
     assert err <= tol * max(1.0, ref.abs().max().item() if ref.numel() else 1.0), err
 
 
-@pytest.mark.parametrize("tile", ["2", "8"])
+@pytest.mark.parametrize("tile", ["2", "6", "8"])
 @pytest.mark.parametrize("cap,T,K,N", [(40, 0, 64, 64), (40, 1, 8, 8), (300, 127, 64, 128), (300, 129, 72, 136),
                                        (700, 257, 200, 264), (600, 511, 64, 520), (2000, 1025, 328, 248)])
 def test_row_gemms_at_tile_edges(spa, tile, cap, T, K, N):
