@@ -184,11 +184,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) g
 // 49.8 (2) | 52.2 (3), 12544 51.2 (2) | 64.4 (4), 15052 72.6 (3) | 67.5 (4); K 2304, 11540 rows of 768 columns: 54.3 (1) |
 // 45.5 (1).  At 240 tiles a step of 64 takes 1.0 us, 256 x 256 1.45: bound by the L2 (11 TB/s), 47 and 65 % of
 // the products' own cycles at 2.0 to 2.3 GHz; launch, first loads and the epilogue of a round take 4 us more.
-template <bool kScale, bool kDeep>
+// EDGE: 192 | 256, or 0 for the one that the live rows decide.
+template <bool kScale, bool kDeep, int EDGE>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1))) gemm_rows_big_kernel(const GemmArgs p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char gemm_smem[];
   const int M = p.total != nullptr ? min(p.total[0], p.m_cap) : p.m_cap;
-  if (p.large_edge != 0 ? p.large_edge == 192 : medium_tiles(M, p.ncols))
+  if (EDGE != 0 ? EDGE == 192 : medium_tiles(M, p.ncols))
     gemm_rows_block<Mfma16, kScale, kDeep, true, 192, 192, 4, 2, 3>(p, gemm_smem, blockIdx.x, gridDim.x);
   else
     gemm_rows_block<Mfma32, kScale, kDeep, true, 256, 256, 2, 4, 2>(p, gemm_smem, blockIdx.x, gridDim.x);

@@ -20,7 +20,6 @@ struct GemmArgs {
   const __bf16* residual;
   const int32_t* inv_pos;        // given: the rows i < zrows of out with inv_pos[i] < 0 are zeroed (copied from residual)
   long zrows;
-  int large_edge;                // edge of the large tiles: 192 | 256, 0: by the live rows (medium_tiles)
 };
 
 // deep = false: out = A W^T (W [ncols][kc]); true: out = A W (W [kc][ncols]).

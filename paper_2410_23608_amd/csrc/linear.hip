@@ -57,7 +57,11 @@ static int launch_gemm_rows_tile(const char* fn, const GemmArgs& args, bool big,
   const long tiles = gemm_tiles<long>(args.m_cap, args.ncols, big ? 192 : 128);     // (no less than with 256)
   SPA_REQUIRE(tiles + 8 < 2147483647L / 2, SPA_ERR_INVALID_ARG, "%s: too many tiles", fn);
   const long tiles8 = (tiles + 7) / 8 * 8;
-  const auto kernel = big ? gemm_rows_big_kernel<kScale, kDeep> : gemm_rows_small_kernel<kScale, kDeep>;
+  const int cfg = options().gemm_tm;
+  const auto large = cfg == 6   ? gemm_rows_big_kernel<kScale, kDeep, 192>
+                     : cfg == 8 ? gemm_rows_big_kernel<kScale, kDeep, 256>
+                                : gemm_rows_big_kernel<kScale, kDeep, 0>;
+  const auto kernel = big ? large : gemm_rows_small_kernel<kScale, kDeep>;
   const hipError_t attr = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   SPA_REQUIRE(attr == hipSuccess, SPA_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, smem);
   hipLaunchKernelGGL(kernel, dim3((unsigned)(big ? std::min(tiles8, 256L) : tiles8)), dim3(big ? 512 : 256), smem, st, args);
@@ -66,11 +70,9 @@ static int launch_gemm_rows_tile(const char* fn, const GemmArgs& args, bool big,
 
 // Option gemm_tm (tuning aid) forces a shape: 2 | 6 | 8 for 128 x 128 | 192 x 192 | 256 x 256, 14 for either large one by
 // the live rows.
-int launch_gemm_rows(const char* fn, const GemmArgs& a, bool deep, hipStream_t st) {
+int launch_gemm_rows(const char* fn, const GemmArgs& args, bool deep, hipStream_t st) {
   const int cfg = options().gemm_tm;
-  const bool big = cfg != 0 ? cfg >= 6 : large_tiles(a.m_cap, a.total != nullptr, a.ncols, a.kc);
-  GemmArgs args = a;
-  args.large_edge = cfg == 6 ? 192 : cfg == 8 ? 256 : 0;
+  const bool big = cfg != 0 ? cfg >= 6 : large_tiles(args.m_cap, args.total != nullptr, args.ncols, args.kc);
   if (group_open()) return group_note_rows(fn, args, big);
   if (deep) return launch_gemm_rows_tile<false, true>(fn, args, big, st);
   if (args.scores != nullptr) return launch_gemm_rows_tile<true, false>(fn, args, big, st);
