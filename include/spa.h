@@ -285,6 +285,12 @@ int spa_pack_containers(const uint8_t* mask, int B, int grid_h, int grid_w, int 
  *      softmax_scale (host float; 0 means 1/sqrt(Dh)).
  * out: out [>= T, H*Dh] dtype, contiguous rows; lse [H, B*max_seqlen] fp32 or NULL
  *      (entry (h, j) for packed row j).  Rows >= T are not written.
+ * The bits of a result, of this call and of every other form of the forward attention below, are the same in every run and
+ * for all operand forms (packed, gathered, from the mask).  The order in which a row's keys are added is one of, bf16:
+ * max_seqlen > 256 | 97 <= max_seqlen <= 256 and 8 ceil(H B / 8) ceil(max_seqlen / 32) <= 1536 (Dh 64; Dh 32: 1024) | the
+ * rest; fp32: max_seqlen > 96 and that product <= 768 | the rest.  Two calls on the same side of these lines give an image
+ * the same bits whatever else is in the batch; across them results differ by rounding.
+ * Keys with a score of -inf weigh nothing; a row all of whose scores are -inf is NaN and its lse -inf.
  */
 int spa_packed_attention(const void* q, const void* k, const void* v, int64_t q_row_stride,
                          int64_t k_row_stride, int64_t v_row_stride, const int32_t* cu_seqlens, int B, int max_seqlen, int H, int Dh,

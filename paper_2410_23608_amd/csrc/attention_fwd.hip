@@ -794,7 +794,8 @@ wave_attention(WaveLds<DH, STEP>* lds, int part, const Segment seg, int h, int q
 // 1 / 2 / 4 waves: 8 images (336 units) 11.2 / 9.3 / 9.7, 16 images 12.0 / 10.0 / 10.5, 32 images (1344) 13.0 / 11.8 / 14.3,
 // 64 images 15.9 / 16.5 / 20.5; 32 x 256 tokens, 6 heads of 64 (1536) 15.9 / 14.1.  Head dim 32, 6 heads: 18 x 256 tokens (864)
 // 11.6 / 10.9, 32 x 256 (1536) 12.7 / 12.5, and beside other calls of a launch group, training, 100.0 / 101.4.
-// Segments of up to 3 steps are not worth a merge.
+// Segments of up to 3 steps are not worth a merge.  Two waves add a row's keys in another order than one, so an image's bits are
+// the same in any two calls on one side of this line, and differ by rounding across it.
 static int unit_waves(int Dh, int nqb, long units) { return nqb >= 4 && units <= (Dh == 64 ? 1536 : 1024) ? 2 : 1; }
 
 template <int SPLIT, int DH, int STEP, int GATHER>
@@ -1097,7 +1098,8 @@ attn_fwd_bf16_whole_kernel(const __bf16* __restrict__ q, const __bf16* __restric
 // row, S^T = K Q^T leaves 16 keys of one query in a lane, and these probabilities are the B operand of
 // O^T += V^T P^T, register r against V row acc_row(r, hh), of which the 32 lanes of a half read 128
 // consecutive bytes.  The rows of the next 32 keys are in flight during the math.  Bound by latency at
-// the sizes it is used at (2 x 196 tokens: 5 us; eight lanes per query with K / V tiles in LDS: 12.5 us).
+// the sizes it is used at (2 x 196 tokens, 60 selected each: 5.6 us; its predecessor, eight lanes per query with K / V tiles
+// in LDS, took 12.5).
 template <int DH, int SPLIT>
 __global__ void __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2)))
 attn_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
@@ -1292,8 +1294,9 @@ attn_fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
 }
 
 // ------------------------------------------------------------------------------- host
-// fp32: four waves a unit where the units leave the chip idle and there are keys to split (2 x 196 tokens, 2 heads of 32: the
-// launch 8.3 -> 4.9 us)
+// fp32: four waves a unit where the units leave the chip idle and there are keys to split (2 x 196 tokens, 2 heads of 32,
+// called again and again: 60 selected an image 6.9 -> 5.6 us, all 16.9 -> 7.6; the sums of an image then go by another order
+// than in a larger batch)
 template <class... Args>
 static void launch_f32(int Dh, int B, int H, int nqb, hipStream_t st, Args... args) {
   const dim3 grid(xcd_grid(nqb, H, B));

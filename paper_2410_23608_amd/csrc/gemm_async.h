@@ -3,16 +3,19 @@
 // loads of the next tiles are in flight without a register, a store or a wait for each other; the only
 // waits are one counted vmcnt and one barrier per 64-deep contraction step.  The barrier stands before the last
 // products of the step before it, whose operands are in registers by then: they cover the first LDS reads of the
-// step, and all STAGES buffers can be filled before the first (with the barrier after them and one load after the
-// other behind it a step of 256 x 256 took 3900 cycles, 830 of them at the barrier, 1600 for 8 loads and 1250 for
-// the products, 64 of 32 cycles on a SIMD; now 3170).
+// step, and all STAGES buffers can be filled before the first.  Stamps of one wave, 256 x 256, with the barrier after
+// them and one load after the other behind it: 3900 cycles a step, 830 at the barrier, 1600 for its 8 loads, 1250 for its
+// 32 products beside those of the SIMD's other wave; now 3170.  The two waves' 64 products take 2048.
 //
 // A direct load puts a wave's 64 pieces of 16 bytes next to each other, so rows cannot be padded;
 // instead the pieces of a row are permuted on the way in (each lane chooses which piece it fetches) and
 // un-permuted in the fragment reads:
 //   rows operand ([rows][64], contraction along the row):  piece c of row r sits at c ^ (r & 7)
 //   deep operand ([64][cols], contraction down the rows):  piece c of row r sits at c ^ 4 (r & 3)
-// which spreads the 16-byte reads of 8 rows, and the transposing reads of 4 rows, over all banks.
+// which spreads the 16-byte reads of 8 rows, and the transposing reads of 4 rows, over all banks.  The 32-row fragments
+// of rows operands read 16 rows at a time, of which rows r and r + 8 meet: by the counters half of the LDS cycles of 256 x 256
+// and 128 x 128 forward tiles are conflicts (192 x 192 a quarter, input sides 19 %, weight sides 2 to 6 %).  Pieces at
+// c ^ (r / 2 & 7) instead, measured with an earlier loop, changed no time: the LDS is busy a third of the launch.
 #pragma once
 
 #include "attn_tiles.h"

@@ -108,7 +108,8 @@ __device__ __forceinline__ void gemm_rows_block(const GemmArgs& p, unsigned char
     // epilogue: scale, bias, bf16; the EDGE rows of a row of matrix tiles at a time are parked in its own part of LDS (LDS
     // operations of a wave complete in order) and leave as whole 16-byte pieces.  The pieces of the residual are
     // fetched together, pieces past the edge from a valid place (one at a time where they are added, each waits
-    // for memory: the output projection of 64 x 196 tokens of 384 columns 11.4 -> 9.8 us)
+    // for memory: the output projection of 64 x 196 tokens of 384 columns 11.4 -> 9.8 us).  With 256 x 256 tiles they are 64
+    // registers beside 128 accumulators: nine or ten registers spill here, and a reload waits for the stores before it.
     constexpr int NC = TN * E, ORS = NC + 8, PIECES = NC / 8, PER_LANE = E * PIECES / 64;
     static_assert(E * PIECES % 64 == 0 && WGM * WGN * 2 * E * ORS <= STAGES * (BM + BN) * kGaK, "output staging fits in the operand buffers");
     auto epilogue = [&](auto with_residual) {
@@ -179,11 +180,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) g
 // Tiles of 256 x 256 (eight waves of 128 x 64) or 192 x 192 (eight of 48 x 96, whose accumulators leave room for three
 // operand stages): one resident workgroup per unit walks the tiles (a workgroup per tile of the capacity: 1.5 us more
 // for those without one), and the rounds that takes decide, a round of the smaller tile is about .7 of one of the
-// larger.  The row count is only known here.  Measured, K 768, 256 x 256 | 192 x 192, rounds in brackets, us: 11540 rows
-// of 768 columns 24.6 (1) | 19.0 (1), 15052 rows 24.9 (1) | 30.1 (2); rows of 2304 columns: 7526 46.7 (2) | 38.8 (2), 11540
-// 49.8 (2) | 52.2 (3), 12544 51.2 (2) | 64.4 (4), 15052 72.6 (3) | 67.5 (4); K 2304, 11540 rows of 768 columns: 54.3 (1) |
-// 45.5 (1).  At 240 tiles a step of 64 takes 1.0 us, 256 x 256 1.45: bound by the L2 (11 TB/s), 47 and 65 % of
-// the products' own cycles at 2.0 to 2.3 GHz; launch, first loads and the epilogue of a round take 4 us more.
+// larger.  The row count is only known here.  Measured, called again and again, K 768, 256 x 256 | 192 x 192, rounds in
+// brackets, us: 11540 rows of 768 columns 22.6 (1) | 17.8 (1), 15052 rows 23.7 (1) | 29.1 (2); rows of 2304 columns: 7526
+// 43.7 (2) | 32.0 (2), 11540 46.5 (2) | 48.0 (3), 12544 49.3 (2) | 60.9 (4), 15052 69.1 (3) | 62.5 (4); K 2304, 11540 rows of 768
+// columns: 52.0 (1) | 41.7 (1).  At 240 tiles a step of 64 takes 1.0 us, 256 x 256 1.45, of which the products' own cycles are 47
+// and 65 % at 2.0 to 2.3 GHz; launch, first loads and the epilogue of a round take 4 us more.  No unit is busy for much more than
+// a third of a launch (matrix pipe 32 %, LDS 29 %, address units 31 % of QKV's with 256 x 256; the L2 delivers 11 TB/s in the
+// loop, 6.5 over the launch): what binds is the order within a step, wait, barrier, loads, products, with one workgroup a unit
+// to fill the gaps.
 // EDGE: 192 | 256, or 0 for the one that the live rows decide.
 template <bool kScale, bool kDeep, int EDGE>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1))) gemm_rows_big_kernel(const GemmArgs p) {

@@ -8,11 +8,10 @@
 // bf16 path: MFMA GEMM on the pipelined loop of gemm_async.h, 64 deep steps, tiles of 128 x 128 (four waves
 // of 64 x 64, two workgroups per unit), 192 x 192 or 256 x 256 (eight waves); the same kernels multiply
 // by W as it lies for the input side of the backward (linear_bwd.hip).  With 128 x 128 tiles every flop
-// needs 1/64 byte from L2 and the L2 delivers about 12 TB/s with this pattern, so the large tiles, which
-// need two thirds and half of that, win wherever they still fill the chip (launch_gemm_rows).  Measured, 12544 rows of
-// 768 -> 2304: 47 us = 940 TFLOP/s (operands staged through registers: 68 us); 6272 rows of 384 -> 384: 7.2
-// us (8.7); 98 rows: 6.3 us (8.1), its steps bound by latency.  The output tile leaves through LDS as
-// whole rows.
+// needs 1/64 byte from L2; the large tiles need two thirds and half of that and win wherever they still fill the chip
+// (gemm_shape.h; what bounds them: gemm_rows.h).  Measured, called again and again: 12544 rows of 768 -> 2304 47 to 49 us =
+// 905 to 940 TFLOP/s (operands staged through registers: 68 us); 6272 rows of 384 -> 384: 7 us (8.7); 98 rows: 6.1 us (8.1),
+// its steps bound by latency.  The output tile leaves through LDS as whole rows.
 // fp32 path (tiny workload): one thread per output element.
 #include <algorithm>
 #include <cmath>

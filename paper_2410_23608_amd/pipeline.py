@@ -385,11 +385,13 @@ class BlockTrainPass(_Pass):
     overlap_weight_grads (default): nothing downstream in the step reads dW / dbias, so the two weight-side GEMMs run
     beside other work.  In bf16 with B N C^2 <= 6e9 they share one launch with the input side of the QKV projection
     (a launch group), and their partial sums one more: these GEMMs leave units idle there and every dependent launch
-    costs 4 us, most of it before its first product.  Above that line each of them fills the chip, and they are enqueued on a second HIP stream
-    (default priority) beside the attention backward, the input-side GEMM and the gate backward; events order them
-    after their inputs and the step's last stage joins the streams.  Measured, us a step, one launch / second stream /
-    in order: 32 x 196 x 384 93 / 110 / 115, 128 x 196 x 384 178 / 184 / 200, 32 x 196 x 768 148 / 190 / 168 and
-    64 x 196 x 768 (7.4e9) 222 / 218 / 241, 128 x 196 x 768 421 / 401 / 422."""
+    costs 4 us, most of it before its first product.  Above that line each of them fills the chip, and they are enqueued
+    on a second HIP stream (default priority) beside the attention backward, the input-side GEMM and the gate backward;
+    events order them after their inputs and the step's last stage joins the streams.  Measured, us a step, one launch /
+    second stream / in order: 32 x 196 x 384 90 / 105-118 / 111, 128 x 196 x 384 173 / 177 / 194, 32 x 196 x 768
+    153 / 159 / 172, 48 images of it 187 / 201 / 203, 56 (6.5e9) 206 / 210 / 230, 64 (7.4e9) 225 / 222 / 248, 80
+    268 / 270 / 286, 96 309 / 302 / 322, 128 406 / 394 / 410.  A second stream that the runtime put on the caller's own
+    hardware queue (it deals streams to four) loses what it should win: 64 images 271, 128 434."""
 
     def __init__(self, B: int, N: int, C: int, H: int, dtype: str, tau: float = 0.5, bias: float = 0.0,
                  loss_scale: Optional[float] = None, overlap_weight_grads: bool = True):

@@ -86,3 +86,35 @@ def test_fp32_scores_of_minus_infinity_weigh_nothing(H, Dh, N, steps):
     torch.cuda.synchronize()
     # sums of up to 196 products of rounding 2^-24 on each, values up to 6
     assert (out.cpu().double() - ref).abs().max() <= 1e-5 and (lse.cpu().double() - ref_lse).abs().max() <= 1e-5
+
+
+@pytest.mark.parametrize("dtype,H,Dh,N,same,other", [("bf16", 6, 64, 196, (1, 8, 36), (37, 64)), ("bf16", 4, 32, 97, (1, 64), (65, 80)),
+                                                     ("f32", 2, 32, 196, (1, 52), (53, 64)), ("bf16", 6, 64, 96, (1, 36, 64), ()),
+                                                     ("bf16", 8, 32, 300, (1, 30), ())])
+def test_what_the_bits_of_an_image_depend_on(dtype, H, Dh, N, same, other):
+    """The first image alone and with others behind it: the same bits in all batches on one side of the line of units
+    (8 ceil(H B / 8) ceil(N / 32) at most 1536, 1024 or 768), the same bits on the other side, rounding between them."""
+    from paper_2410_23608_amd import spa
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + Dh)
+    C, td, most = H * Dh, torch.bfloat16 if dtype == "bf16" else torch.float32, max(same + other)
+    q, k, v = (torch.randn(most * N, C, generator=g, device="cuda").to(td) for _ in range(3))
+    lens = [N - 3] + [(7 * b) % (N + 1) for b in range(1, most)]
+    line = {("bf16", 64): 1536, ("bf16", 32): 1024, ("f32", 32): 768}[dtype, Dh]
+    units = lambda B: (H * B + 7) // 8 * 8 * ((N + 31) // 32)
+    assert not 96 < N <= 256 or units(max(same)) <= line < units(min(other))
+    got = []
+    for B in same + other:
+        cu = torch.tensor([0] + lens[:B], dtype=torch.int32).cumsum(0).int().cuda()
+        out, lse = torch.zeros(B * N, C, dtype=td, device="cuda"), torch.zeros(H, B * N, device="cuda")
+        spa.spa_packed_attention(q[:B * N], k[:B * N], v[:B * N], cu, B, N, H, Dh, out, lse)
+        got.append((out[:N - 3], lse[:, :N - 3].contiguous()))
+    torch.cuda.synchronize()
+    for group in (got[:len(same)], got[len(same):]):
+        for out, lse in group[1:]:
+            assert torch.equal(out, group[0][0]) and torch.equal(lse, group[0][1])
+    for out, lse in got[len(same):]:
+        # bf16: probabilities of a wave rounded against its own maximum, 2^-9 of |v| up to 4.5 on either side; fp32: sums of
+        # up to 196 terms in another order
+        assert (out.double() - got[0][0].double()).abs().max() <= (2e-2 if dtype == "bf16" else 2e-6)
+        assert (lse - got[0][1]).abs().max() <= 2e-6
