@@ -3,19 +3,22 @@
 // loads of the next tiles are in flight without a register, a store or a wait for each other; the only
 // waits are one counted vmcnt and one barrier per 64-deep contraction step.  The barrier stands before the last
 // products of the step before it, whose operands are in registers by then: they cover the first LDS reads of the
-// step, and all STAGES buffers can be filled before the first.  Stamps of one wave, 256 x 256, with the barrier after
-// them and one load after the other behind it: 3900 cycles a step, 830 at the barrier, 1600 for its 8 loads, 1250 for its
-// 32 products beside those of the SIMD's other wave; now 3170.  The two waves' 64 products take 2048.
+// step, and all STAGES buffers can be filled before the first.
+//
+// What bounds it: 256 x 256, called again and again on all units, a step takes 1.65 us with random operands and 1.14 with
+// zeros (the products alone .93 with either, the loads alone .86, the reads alone .7 | .42 for rows | deep operands): the
+// clock falls with the power that the operands' bits cost, and at 1.65 us the products run at 1.3 PFLOP/s.  A wave
+// issues an LDS read in 15 to 17 cycles, a matrix instruction takes 32: a wave's reads stand between its products, not in
+// front of them (rows of 768 -> 2304, 12544 of them, 49.6 -> 46.5 us with that and the pieces' order below).
 //
 // A direct load puts a wave's 64 pieces of 16 bytes next to each other, so rows cannot be padded;
 // instead the pieces of a row are permuted on the way in (each lane chooses which piece it fetches) and
 // un-permuted in the fragment reads:
-//   rows operand ([rows][64], contraction along the row):  piece c of row r sits at c ^ (r & 7)
+//   rows operand ([rows][64], contraction along the row):  piece c of row r sits at c ^ MF::turn(r)
 //   deep operand ([64][cols], contraction down the rows):  piece c of row r sits at c ^ 4 (r & 3)
-// which spreads the 16-byte reads of 8 rows, and the transposing reads of 4 rows, over all banks.  The 32-row fragments
-// of rows operands read 16 rows at a time, of which rows r and r + 8 meet: by the counters half of the LDS cycles of 256 x 256
-// and 128 x 128 forward tiles are conflicts (192 x 192 a quarter, input sides 19 %, weight sides 2 to 6 %).  Pieces at
-// c ^ (r / 2 & 7) instead, measured with an earlier loop, changed no time: the LDS is busy a third of the launch.
+// which spreads the 16-byte reads of the rows that are read together, and the transposing reads of 4 rows, over all
+// banks: 4.2 cycles for a 16-byte read and 2.2 for a transposing one with eight waves reading (r & 7 for the 32-row
+// fragments, of whose rows r and r + 8 meet: 8.0; 256 x 256 tiles 3 % slower).
 #pragma once
 
 #include "attn_tiles.h"
@@ -50,19 +53,21 @@ struct Mfma32 {
   typedef floatx16 Acc;
   __device__ static __forceinline__ Acc mul(bf16x8 a, bf16x8 b, Acc c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
   __device__ static __forceinline__ int row(int g, int lane) { return 8 * g + 4 * (lane >> 5); }
+  __device__ static __forceinline__ int turn(int r) { return r >> 1 & 7; }     // of a rows operand's pieces
 };
 struct Mfma16 {
   static constexpr int kEdge = 16, kDepth = 32, kGroups = 1;
   typedef floatx4 Acc;
   __device__ static __forceinline__ Acc mul(bf16x8 a, bf16x8 b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
   __device__ static __forceinline__ int row(int, int lane) { return 4 * (lane >> 4); }
+  __device__ static __forceinline__ int turn(int r) { return r & 7; }
 };
 
 // Operand with the contraction along its rows: fragment of rows r0 .. + EDGE - 1, contraction DEPTH kk .. + DEPTH - 1.
 template <class MF>
 __device__ __forceinline__ bf16x8 rows_frag(const __bf16* tile, int r0, int kk, int lane) {
   const int r = r0 + lane % MF::kEdge;
-  return *reinterpret_cast<const bf16x8*>(tile + r * kGaK + (((MF::kDepth / 8 * kk + lane / MF::kEdge) ^ (r & 7)) << 3));
+  return *reinterpret_cast<const bf16x8*>(tile + r * kGaK + (((MF::kDepth / 8 * kk + lane / MF::kEdge) ^ MF::turn(r)) << 3));
 }
 // Operand with the contraction down its rows (COLS columns): fragment of columns c0 .. c0+31, contraction
 // rows 16 kk .. + 15, by the transposing read: within each block of 16 lanes lane i, element e, receives
@@ -95,16 +100,16 @@ __device__ __forceinline__ bf16x8 deep_block_frag(const __bf16* tile, int kk, in
 }
 
 // Which piece a thread fetches: piece `col` (elements) of tile row `row` for u = 0 .. count - 1.
-template <int ROWS, int THREADS>
+template <class MF, int ROWS, int THREADS>
 struct RowsPieces {
   static constexpr int kCount = ROWS * 8 / THREADS, kRowStep = THREADS / 8;
-  static_assert(kRowStep % 8 == 0, "a thread keeps its permuted column");
+  static_assert(kRowStep % 16 == 0, "a thread keeps its permuted column");
   __device__ static __forceinline__ int row(int tid, int u) { return (tid >> 3) + u * kRowStep; }
-  __device__ static __forceinline__ int col(int tid, int) { return ((tid & 7) ^ ((tid >> 3) & 7)) * 8; }
+  __device__ static __forceinline__ int col(int tid, int) { return ((tid & 7) ^ MF::turn(tid >> 3)) * 8; }
 };
-template <int COLS, int THREADS>
+template <int COLS, int THREADS, int DEPTH = kGaK>
 struct DeepPieces {
-  static constexpr int kPerRow = COLS / 8, kCount = kGaK * kPerRow / THREADS, kRowStep = THREADS / kPerRow;
+  static constexpr int kPerRow = COLS / 8, kCount = DEPTH * kPerRow / THREADS, kRowStep = THREADS / kPerRow;
   static_assert(kRowStep % 4 == 0, "a thread keeps its permuted column");
   __device__ static __forceinline__ int row(int tid, int u) { return tid / kPerRow + u * kRowStep; }
   __device__ static __forceinline__ int col(int tid, int) {
@@ -122,8 +127,8 @@ struct DeepBlocks {                  // one block of 64 columns a step of u: a t
   }
 };
 
-// acc[i][j] += sum over nk contraction steps of (B fragment j) x (A fragment i): MFMA tiles whose rows
-// are B's index and whose columns are A's.  The wave's block is TM * 32 of A by TN * 32 of B.
+// acc[i][j] += sum over nk contraction steps of DEPTH of (B fragment j) x (A fragment i): MFMA tiles whose
+// rows are B's index and whose columns are A's.  The wave's block is TM * 32 of A by TN * 32 of B.
 // next_a(u, t) / next_b(u, t): address of the thread's u-th piece of step t (called for t = 0, 1, ... in
 // order, so they may step a pointer).  frag_a(tile, i, kk), frag_b(tile, j, kk): fragments;
 // beside(af): called with the A fragments of every 16 contraction elements; last(): before the last barrier.  All threads
@@ -132,17 +137,19 @@ struct DeepBlocks {                  // one block of 64 columns a step of u: a t
 struct Nothing {
   template <class T> __device__ __forceinline__ void operator()(const T&) const {}
 };
-template <class MF, int A_ELEMS, int B_ELEMS, int NA, int NB, int STAGES, int THREADS, int TM, int TN, class FA, class FB, class RA,
-          class RB, class LS, class BS = Nothing>
+template <class MF, int A_ELEMS, int B_ELEMS, int NA, int NB, int STAGES, int THREADS, int TM, int TN, int DEPTH = kGaK, class FA,
+          class FB, class RA, class RB, class LS, class BS = Nothing>
 __device__ __forceinline__ void gemm_async_loop(__bf16* lds, int nk, FA&& next_a, FB&& next_b, RA&& frag_a, RB&& frag_b,
                                                 typename MF::Acc (&acc)[TM][TN], LS&& last, BS&& beside = BS{}) {
-  constexpr int STAGE = A_ELEMS + B_ELEMS, KK = kGaK / MF::kDepth;
-  // Products between two loads: with two waves a SIMD in one workgroup the loads are dealt among the products, each
-  // occupies the wave until the unit's address path takes it (16 cycles a load of 1 KB and wave); with one wave a
-  // SIMD, or two of workgroups that are not in step, they go first (dealt out: 2304 -> 768, 1568 rows, 26 -> 32 us).
-  constexpr int GAP = THREADS == 256 ? 0 : STAGES == 2 ? 2 : KK * TM * TN / (NA + NB);
-  constexpr int GAP1 = GAP > 0 ? GAP : 1;
-  static_assert((NA + NB - 1) * GAP < KK * TM * TN, "every load of a step has its place");
+  constexpr int STAGE = A_ELEMS + B_ELEMS, KK = DEPTH / MF::kDepth, LOADS = NA + NB;
+  static_assert(KK % 2 == 0, "the fragments of neighbouring groups take turns");
+  // Place of a group's fragment reads and loads among its products: RP fragments after each product from the first on,
+  // then a load after each.  With one wave a SIMD, or two of workgroups that are not in step, the loads of a step go
+  // first (dealt out: 2304 -> 768, 1568 rows, 26 -> 32 us).
+  constexpr int P = TM * TN, R = TM + TN, RP = (2 * R + P - 1) / P, READS = (R + RP - 1) / RP;
+  constexpr bool kLoadsFirst = THREADS == 256;
+  constexpr int PER_GROUP = P - READS;
+  static_assert(READS < P && (kLoadsFirst || LOADS <= KK * PER_GROUP), "every read and every load has its place");
   const uint32_t wave_dst = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds +
                             __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 1024;
   auto issue = [&](int q, int t, int stage) {       // load q of step t
@@ -154,59 +161,73 @@ __device__ __forceinline__ void gemm_async_loop(__bf16* lds, int nk, FA&& next_a
   for (int s = 0; s < STAGES; ++s)
     if (s < nk) {
 #pragma unroll
-      for (int q = 0; q < NA + NB; ++q) issue(q, s, s);
+      for (int q = 0; q < LOADS; ++q) issue(q, s, s);
     }
   bf16x8 af[2][TM], bfr[2][TN];
-  int stage = 0;
-  for (int t = 0; t < nk; ++t) {
-    // this wave's pieces of step t have arrived (near the end fewer younger steps are in flight), and its
-    // reads of step t - 1
-    if (t == 0 && STAGES <= nk) wait_memory<(STAGES - 1) * (NA + NB)>();
-    else if (STAGES == 2 || t == 0 || t + STAGES - 2 >= nk) wait_memory<0>();
-    else wait_memory<(STAGES - 2) * (NA + NB)>();
-    __builtin_amdgcn_s_barrier();               // and everybody's
+  const __bf16 *a = lds, *b = lds + A_ELEMS;
+  auto read = [&](int kk, int r) {                   // fragment r of group kk: a and b in turn while both last
+    const int both = 2 * (TM < TN ? TM : TN);
+    const bool is_a = r < both ? r % 2 == 0 : TM > TN;
+    const int i = r < both ? r / 2 : r - both / 2;
+    if (is_a) af[kk & 1][i] = frag_a(a, i, kk);
+    else bfr[kk & 1][i] = frag_b(b, i, kk);
+  };
+  // the products of group kk beside the reads of group `next` and the loads of step t from number `from` on
+  auto group = [&](int kk, int next, bool loads, int from, int t, int into) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int n = i * TN + j;
+        acc[i][j] = MF::mul(bfr[kk & 1][j], af[kk & 1][i], acc[i][j]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (n < READS) {
+#pragma unroll
+          for (int r = n * RP; r < (n + 1) * RP && r < R; ++r) read(next, r);
+        } else if (!kLoadsFirst && from + n - READS < LOADS) {
+          if (loads) issue(from + n - READS, t, into);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    beside(af[kk & 1]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if (nk > 0) {
+    if (STAGES <= nk) wait_memory<(STAGES - 1) * LOADS>();
+    else wait_memory<0>();
+    __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    const __bf16* a = lds + stage * STAGE;
-    const __bf16* b = a + A_ELEMS;
-    auto read = [&](int kk) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i) af[kk & 1][i] = frag_a(a, i, kk);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) bfr[kk & 1][j] = frag_b(b, j, kk);
-    };
-    const int freed = stage == 0 ? STAGES - 1 : stage - 1;        // the buffer of step t - 1
-    const bool more = t > 0 && t + STAGES - 1 < nk;
-    auto multiply = [&](int kk, int group) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          acc[i][j] = MF::mul(bfr[kk & 1][j], af[kk & 1][i], acc[i][j]);
-          const int n = (group * TM + i) * TN + j;
-          if (GAP > 0 && n % GAP1 == 0 && n / GAP1 < NA + NB) {
-            __builtin_amdgcn_sched_barrier(0);
-            if (more) issue(n / GAP1, t + STAGES - 1, freed);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-      beside(af[kk & 1]);
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    read(0);
+    for (int r = 0; r < R; ++r) read(0, r);
     __builtin_amdgcn_sched_barrier(0);
-    if (GAP == 0 && more) {
+  }
+  int stage = 0, freed = 0;                          // buffers of this step and the one before it
+  bool more = false;                                 // loads of step t + STAGES - 1 are under way
+  for (int t = 0; t + 1 < nk; ++t) {
 #pragma unroll
-      for (int q = 0; q < NA + NB; ++q) issue(q, t + STAGES - 1, freed);
-    }
-    if (t > 0) multiply(KK - 1, 0);
-#pragma unroll
-    for (int kk = 0; kk + 1 < KK; ++kk) {
-      read(kk + 1);
-      __builtin_amdgcn_sched_barrier(0);
-      multiply(kk, kk + 1);
-    }
+    for (int kk = 0; kk + 1 < KK; ++kk) group(kk, kk + 1, more, (kk + 1) * PER_GROUP, t + STAGES - 1, freed);
+    // this wave's pieces of step t + 1 have arrived (near the end fewer younger steps are in flight), and its
+    // reads of step t
+    if (STAGES == 2 || t + STAGES - 1 >= nk) wait_memory<0>();
+    else wait_memory<(STAGES - 2) * LOADS>();
+    __builtin_amdgcn_s_barrier();                   // and everybody's
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    freed = stage;
     stage = stage + 1 == STAGES ? 0 : stage + 1;
+    a = lds + stage * STAGE;
+    b = a + A_ELEMS;
+    more = t + STAGES < nk;
+    if (kLoadsFirst && more) {
+#pragma unroll
+      for (int q = 0; q < LOADS; ++q) issue(q, t + STAGES, freed);
+    }
+    group(KK - 1, 0, more, 0, t + STAGES, freed);
+  }
+  if (nk > 0) {
+#pragma unroll
+    for (int kk = 0; kk + 1 < KK; ++kk) group(kk, kk + 1, false, 0, 0, 0);
   }
   last();
   __syncthreads();

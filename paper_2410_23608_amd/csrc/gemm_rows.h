@@ -17,8 +17,8 @@ template <class MF, bool kScale, bool kDeep, bool LOOP, int BM, int BN, int WGM,
 __device__ __forceinline__ void gemm_rows_block(const GemmArgs& p, unsigned char* gemm_smem, unsigned block, unsigned blocks) {
   constexpr int E = MF::kEdge, THREADS = 64 * WGM * WGN, TM = BM / WGM / E, TN = BN / WGN / E;
   static_assert(BM == WGM * TM * E && BN == WGN * TN * E, "whole matrix tiles");
-  using PA = RowsPieces<BM, THREADS>;
-  using PB = typename std::conditional<!kDeep, RowsPieces<BN, THREADS>,
+  using PA = RowsPieces<MF, BM, THREADS>;
+  using PB = typename std::conditional<!kDeep, RowsPieces<MF, BN, THREADS>,
                                       typename std::conditional<E == 16, DeepBlocks<BN, THREADS>, DeepPieces<BN, THREADS>>::type>::type;
   __bf16* lds = reinterpret_cast<__bf16*>(gemm_smem);
   __shared__ float bias_s[BN];     // bias of the tile's output columns (0 past the edge or without bias)
@@ -33,7 +33,8 @@ __device__ __forceinline__ void gemm_rows_block(const GemmArgs& p, unsigned char
   // A workgroup takes the tiles jx, jx + blocks / 8, ... of its XCD's range.
   const int xcd = block & 7;
   for (int jx = block >> 3; jx < per_xcd && xcd * per_xcd + jx < live_tiles; jx += blocks >> 3) {
-    const int tid = LOOP ? fresh_thread_id() : threadIdx.x, lane = tid & 63, wv = tid >> 6, tile_id = xcd * per_xcd + jx;
+    const int tid = LOOP ? fresh_thread_id() : threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), tile_id = xcd * per_xcd + jx;
     const int mt = tile_id / n_tiles, nt = tile_id - mt * n_tiles;
     const int m0 = mt * BM, n0 = nt * BN;
     const int wm = (wv / WGN) * TM * E, wn = (wv % WGN) * TN * E;
@@ -114,20 +115,22 @@ __device__ __forceinline__ void gemm_rows_block(const GemmArgs& p, unsigned char
     static_assert(E * PIECES % 64 == 0 && WGM * WGN * 2 * E * ORS <= STAGES * (BM + BN) * kGaK, "output staging fits in the operand buffers");
     auto epilogue = [&](auto with_residual) {
       constexpr bool kResidual = decltype(with_residual)::value;
-      bf16x8 res[kResidual ? TM : 1][kResidual ? PER_LANE : 1];
-      if constexpr (kResidual) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
+      bf16x8 res[2][kResidual ? PER_LANE : 1];
+      auto fetch = [&](int i) {
+        if constexpr (kResidual) {
 #pragma unroll
           for (int u = 0; u < PER_LANE; ++u) {
             const int c = lane + 64 * u, row = min(wm + i * E + c / PIECES, M - 1 - m0), n = n0 + wn + c % PIECES * 8;
-            res[i][u] = *reinterpret_cast<const bf16x8*>(p.residual + (long)o_row[row] * p.ldo + (n < p.ncols ? n : n0));
+            res[i & 1][u] = *reinterpret_cast<const bf16x8*>(p.residual + (long)o_row[row] * p.ldo + (n < p.ncols ? n : n0));
           }
-      }
+        }
+      };
+      fetch(0);
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         __bf16* tile = lds + (wv * 2 + (i & 1)) * E * ORS;
         const float rs = kScale ? sigmoidf_dev(row_scale[i]) : 1.f;
+        if (i + 1 < TM) fetch(i + 1);
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -138,13 +141,15 @@ __device__ __forceinline__ void gemm_rows_block(const GemmArgs& p, unsigned char
             f += *reinterpret_cast<const floatx4*>(&bias_s[wn + n]);
             *reinterpret_cast<bf16x4*>(&tile[lane % E * ORS + n]) = __builtin_convertvector(f, bf16x4);
           }
+        if (kResidual) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < PER_LANE; ++u) {
           const int c = lane + 64 * u, r = c / PIECES, ch = c % PIECES, row = wm + i * E + r, n = n0 + wn + ch * 8;
           bf16x8 val = *reinterpret_cast<const bf16x8*>(&tile[r * ORS + ch * 8]);
-          if constexpr (kResidual) val = float_to_bf16x8(bf16x8_to_float(val) + bf16x8_to_float(res[i][u]));
+          if constexpr (kResidual) val = float_to_bf16x8(bf16x8_to_float(val) + bf16x8_to_float(res[i & 1][u]));
           if (m0 + row < M && n < p.ncols) *reinterpret_cast<bf16x8*>(p.out + (long)o_row[row] * p.ldo + n) = val;
         }
+        if (kResidual) __builtin_amdgcn_sched_barrier(0);
       }
     };
     if (p.residual != nullptr) epilogue(std::true_type{});

@@ -20,6 +20,7 @@
 // stages them through registers (linear_bwd_weight_bf16_kernel).
 // fp32 (tiny workload): one thread per output element.
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 
 #include "attn_tiles.h"
@@ -99,7 +100,7 @@ struct WeightItem {
   int split, n0, k0, m_begin, m_end;
   bool valid;
 };
-__device__ __forceinline__ WeightItem weight_item(int M, int splits, int n_tiles, int k_tiles, int live_min, unsigned block) {
+__device__ __forceinline__ WeightItem weight_item(int M, int splits, int n_tiles, int k_tiles, int live_min, int edge, unsigned block) {
   const TokenSplit ts = token_split(M, splits);
   const int tiles = n_tiles * k_tiles, items = max(ts.live, live_min) * tiles, per_xcd = (items + 7) >> 3;
   const int xcd = block & 7, jx = block >> 3, item = xcd * per_xcd + jx;
@@ -107,45 +108,43 @@ __device__ __forceinline__ WeightItem weight_item(int M, int splits, int n_tiles
   w.valid = jx < per_xcd && item < items;
   w.split = item / tiles;
   const int tile_id = item - w.split * tiles, nt = tile_id / k_tiles;
-  w.n0 = nt * kLbT;
-  w.k0 = (tile_id - nt * k_tiles) * kLbT;
+  w.n0 = nt * edge;
+  w.k0 = (tile_id - nt * k_tiles) * edge;
   w.m_begin = w.split * ts.chunk;
   w.m_end = min(M, w.m_begin + ts.chunk);
   return w;
 }
 
-// The wave's 64 (n) x 64 (k) block leaves as 16-byte pieces of 256-byte row segments, 32 n at a time
-// through its own part of LDS; acc[i][j]: n block i, rows of the tile = k block j.
-__device__ __forceinline__ void store_weight_block(const floatx16 (&acc)[2][2], float* lds_of_wave, float* dst, int n_first,
-                                                   int k_first, int n_out, int K, int lane) {
+// 32 (n) x 64 (k) products of a wave leave as 16-byte pieces of 256-byte row segments through its own part of LDS (LDS
+// operations of a wave complete in order); acc[j]: rows of the tile = k block j.
+__device__ __forceinline__ void store_weight_block(const floatx16 (&acc)[2], float* tile, float* dst, int n_first, int k_first,
+                                                   int n_out, int K, int lane) {
   constexpr int ORS = 64 + 4;
   const int l32 = lane & 31, hh = lane >> 5;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    float* tile = lds_of_wave;                         // (LDS operations of a wave complete in order)
+  for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const floatx4 f = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-        *reinterpret_cast<floatx4*>(&tile[l32 * ORS + j * 32 + 8 * g + 4 * hh]) = f;
-      }
-#pragma unroll
-    for (int c = lane; c < 32 * 16; c += 64) {
-      const int r = c >> 4, ch = c & 15, n = n_first + i * 32 + r, k = k_first + ch * 4;
-      if (n < n_out && k < K)
-        *reinterpret_cast<floatx4*>(dst + (long)n * K + k) = *reinterpret_cast<const floatx4*>(&tile[r * ORS + ch * 4]);
+    for (int g = 0; g < 4; ++g) {
+      const floatx4 f = {acc[j][4 * g], acc[j][4 * g + 1], acc[j][4 * g + 2], acc[j][4 * g + 3]};
+      *reinterpret_cast<floatx4*>(&tile[l32 * ORS + j * 32 + 8 * g + 4 * hh]) = f;
     }
+#pragma unroll
+  for (int c = lane; c < 32 * 16; c += 64) {
+    const int r = c >> 4, ch = c & 15, n = n_first + r, k = k_first + ch * 4;
+    if (n < n_out && k < K)
+      *reinterpret_cast<floatx4*>(dst + (long)n * K + k) = *reinterpret_cast<const floatx4*>(&tile[r * ORS + ch * 4]);
   }
 }
 
-// part_w[split][n][k] = sum over the chunk's rows j of g_j[n] x_j[k]; part_b[split][n] = sum g_j[n] (one
-// more MFMA per 16 rows against a vector of ones, in the workgroups of the first k tile).  Both operands
-// have the contraction (the tokens) down their rows and come through the ring of gemm_async.h, rows of
-// zeros past the chunk's end.  kGather: rows of g / x are named by index arrays (null: in order), read one
-// step ahead of the loads that use them, with one test for all rows of a thread (a test a row: 3072 x 1024, 12544 rows, 139 ->
-// 125 us).  12544 rows, 2304 x 768, with the reduction: gathered 97 -> 71 us, in order 66 us; 98 rows of 384 x 1152: 9.8 ->
-// 6.2 us.
+// part_w[split][n][k] = sum over the chunk's rows j of g_j[n] x_j[k]; part_b[split][n] = sum g_j[n] (from the fragments, in the
+// workgroups of the first k tile).  Both operands have the contraction (the tokens) down their rows and come through the
+// ring of gemm_async.h, rows of zeros past the chunk's end.  GI / XI: rows of g / x are named by an index array, read one
+// step ahead of the loads that use it, without a branch (each branch made the compiler copy indices in flight, i.e. wait
+// for them).  Tiles of 128 x 128 (four waves of 64 x 64, two workgroups a unit) or, EDGE 256, 256 x 256 (eight of 128 x 64).
+// Addresses that step a pointer instead of a product and a select a load, and sums of the columns by vector additions,
+// took a step of 128 x 128 tiles beside another workgroup from 1.35 to 1.06 us and one of 256 x 256 from 2.0 to 1.7.
+// Measured with the sums, called again and again, 128 | 256, us: 12544 rows, 2304 x 768 62 (72 before) | 58, 3072 x 1024
+// 107 (132) | 86, 1536 x 512 35 | 38; gathered, 768 x 768 31.8 (36) | 37; 6272 rows, 2304 x 768 38.7 | 42.
 struct WeightArgs {
   const __bf16* dout;
   const int32_t* dout_idx;
@@ -155,91 +154,119 @@ struct WeightArgs {
   int m_cap, K, n_out, splits, n_tiles, k_tiles;
   float *part_w, *part_b;
 };
-template <bool kGather>
+template <int EDGE, bool GI, bool XI>
 __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned char* lb_smem, unsigned block) {
-  constexpr int STAGES = 2;
-  using P = DeepPieces<kLbT, kLbThreads>;
+  constexpr int STAGES = 2, DEPTH = 64;
+  constexpr int THREADS = EDGE == 256 ? 512 : 256, WK = EDGE / 64, TM = EDGE == 256 ? 4 : 2;
+  static_assert(WK == TM, "one column block of g for the sums of a wave");
+  using P = DeepPieces<EDGE, THREADS, DEPTH>;
   __bf16* lds = reinterpret_cast<__bf16*>(lb_smem);
-  const __bf16 *dout = a.dout, *x = a.x;
-  const int32_t *dout_idx = a.dout_idx, *x_idx = a.x_idx, *total = a.total;
   const long ldd = a.ldd;
-  const int m_cap = a.m_cap, K = a.K, n_out = a.n_out;
-  float *part_w = a.part_w, *part_b = a.part_b;
-  const int M = total != nullptr ? min(total[0], m_cap) : m_cap;
-  const WeightItem w = weight_item(M, a.splits, a.n_tiles, a.k_tiles, 1, block);
+  const int K = a.K, n_out = a.n_out;
+  const int M = a.total != nullptr ? min(a.total[0], a.m_cap) : a.m_cap;
+  const WeightItem w = weight_item(M, a.splits, a.n_tiles, a.k_tiles, 1, EDGE, block);
   if (!w.valid) return;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
-  const int wn = (wv >> 1) * 64, wk = (wv & 1) * 64;
-  const bool do_bias = part_b != nullptr && w.k0 == 0 && wk == 0;
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), wkb = wv % WK, wn = wv / WK * 32 * TM, wk = wkb * 64;
   const __bf16* zeros = reinterpret_cast<const __bf16*>(gemm_zeros);
 
   // columns past the matrix edge fetch a valid column (never stored)
-  const int col = P::col(tid, 0);
-  const __bf16* gcol = dout + (w.n0 + col < n_out ? w.n0 + col : w.n0);
-  const __bf16* xcol = x + (w.k0 + col < K ? w.k0 + col : w.k0);
-  int gi[P::kCount], xi[P::kCount];                  // row indices of the next step to be issued
+  const int col = P::col(tid, 0), row = P::row(tid, 0);
+  const __bf16* gcol = a.dout + (w.n0 + col < n_out ? w.n0 + col : w.n0);
+  const __bf16* xcol = a.x + (w.k0 + col < K ? w.k0 + col : w.k0);
+  const int rows = w.m_end - w.m_begin, nk = rows > 0 ? (rows + DEPTH - 1) / DEPTH : 0;
+  // Named rows: their indices, those of the step to be issued next (past the end the last row's).  Rows in order: a
+  // pointer to the thread's first.
+  int gi[P::kCount], xi[P::kCount];
   auto index = [&](int t) {
-    if (!kGather) return;
 #pragma unroll
-    for (int u = 0; u < P::kCount; ++u) gi[u] = xi[u] = min(w.m_begin + t * kGaK + P::row(tid, u), w.m_end - 1);
-    if (dout_idx != nullptr) {
-#pragma unroll
-      for (int u = 0; u < P::kCount; ++u) gi[u] = dout_idx[gi[u]];
-    }
-    if (x_idx != nullptr) {
-#pragma unroll
-      for (int u = 0; u < P::kCount; ++u) xi[u] = x_idx[xi[u]];
+    for (int u = 0; u < P::kCount; ++u) {
+      const int at = min(w.m_begin + t * DEPTH + P::row(tid, u), w.m_end - 1);
+      if (GI) gi[u] = a.dout_idx[at];
+      if (XI) xi[u] = a.x_idx[at];
     }
   };
-  const int rows = w.m_end - w.m_begin, nk = rows > 0 ? (rows + kGaK - 1) / kGaK : 0;
+  const __bf16* gp = gcol + (GI ? 0 : (long)(w.m_begin + row) * ldd);
+  const __bf16* xp = xcol + (XI ? 0 : (long)(w.m_begin + row) * K);
+  // the last step may be partial: rows past the end are zero in both operands
+  const int tail = rows % DEPTH, partial = tail != 0 ? nk - 1 : -1;
+  auto past = [&](int u, int t, const __bf16* p) {
+    if (t == partial) {
+      asm volatile("" : "+v"(p));                    // (a branch: selects in every step cost more than it)
+      p = P::row(tid, u) >= tail ? zeros : p;
+    }
+    return p;
+  };
   auto next_g = [&](int u, int t) {
-    const int r = t * kGaK + P::row(tid, u);
-    const __bf16* p = gcol + (long)(kGather ? gi[u] : w.m_begin + r) * ldd;
-    return r < rows ? p : zeros;
+    const __bf16* p = GI ? gcol + (size_t)(uint32_t)gi[u] * (size_t)ldd : gp;
+    if (!GI) gp += (long)P::kRowStep * ldd;          // (a step's pieces are as far apart as the steps')
+    return past(u, t, p);
   };
   auto next_x = [&](int u, int t) {
-    const int r = t * kGaK + P::row(tid, u);
-    const __bf16* p = xcol + (long)(kGather ? xi[u] : w.m_begin + r) * K;
-    if (u == P::kCount - 1 && t + 1 < nk) index(t + 1);      // (the last address of step t has been formed)
-    return r < rows ? p : zeros;
+    const __bf16* p = XI ? xcol + (size_t)(uint32_t)xi[u] * K : xp;
+    if (!XI) xp += (long)P::kRowStep * K;
+    if ((GI || XI) && u == P::kCount - 1) index(t + 1);      // (the last address of step t has been formed)
+    return past(u, t, p);
   };
-  floatx16 acc[2][2], accb[2];
+  static_assert(P::kCount * P::kRowStep == DEPTH, "pieces a constant distance apart");
+  floatx16 acc[TM][2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      accb[i][r] = 0.f;
       acc[i][0][r] = 0.f;
       acc[i][1][r] = 0.f;
     }
-  const __bf16 one = static_cast<__bf16>(1.0f);
-  const bf16x8 ones = {one, one, one, one, one, one, one, one};
-  if (nk > 0) index(0);
-  gemm_async_loop<Mfma32, kLbT * kGaK, kLbT * kGaK, P::kCount, P::kCount, STAGES, kLbThreads, 2, 2>(
-      lds, nk, next_g, next_x, [&](const __bf16* tile, int i, int kk) { return deep_frag<kLbT>(tile, kk, wn + i * 32, lane); },
-      [&](const __bf16* tile, int j, int kk) { return deep_frag<kLbT>(tile, kk, wk + j * 32, lane); }, acc, [] {},
-      [&](const bf16x8 (&g)[2]) {
+  // Column block i of the wave's is number (i + wkb) % TM of g's, so that the TM waves that hold the same blocks have each
+  // another one as block 0, whose column sums it forms: of every 16 contraction elements a lane holds 8 of column l32.
+  auto g_block = [&](int i) { return wn + (i + wkb) % TM * 32; };
+  const bool do_bias = a.part_b != nullptr && w.k0 == 0;
+  float colsum = 0.f;
+  if ((GI || XI) && nk > 0) index(0);
+  gemm_async_loop<Mfma32, EDGE * DEPTH, EDGE * DEPTH, P::kCount, P::kCount, STAGES, THREADS, TM, 2, DEPTH>(
+      lds, nk, next_g, next_x, [&](const __bf16* tile, int i, int kk) { return deep_frag<EDGE>(tile, kk, g_block(i), lane); },
+      [&](const __bf16* tile, int j, int kk) { return deep_frag<EDGE>(tile, kk, wk + j * 32, lane); }, acc, [] {},
+      [&](const bf16x8 (&g)[TM]) {
         if (do_bias) {
-          accb[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, g[0], accb[0], 0, 0, 0);
-          accb[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, g[1], accb[1], 0, 0, 0);
+          const floatx8 f = bf16x8_to_float(g[0]);
+          colsum += ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
         }
       });
-  static_assert((size_t)4 * 32 * 68 * sizeof(float) <= kLbGemmLds, "output staging fits in the operand stages");
-  store_weight_block(acc, reinterpret_cast<float*>(lb_smem) + wv * 32 * 68, part_w + (long)w.split * n_out * K, w.n0 + wn,
-                     w.k0 + wk, n_out, K, lane);
-  if (do_bias && hh == 0) {
+  static_assert(THREADS / 64 * 32 * 68 * sizeof(float) <= STAGES * 2 * EDGE * DEPTH * sizeof(__bf16), "output staging fits in the operand stages");
+  float* dst = a.part_w + (long)w.split * n_out * K;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int n = w.n0 + wn + i * 32 + l32;
-      if (n < n_out) part_b[(long)w.split * n_out + n] = accb[i][0];   // every row of the tile holds the column sums
-    }
+  for (int i = 0; i < TM; ++i)
+    store_weight_block(acc[i], reinterpret_cast<float*>(lb_smem) + wv * 32 * 68, dst, w.n0 + g_block(i), w.k0 + wk, n_out, K, lane);
+  if (do_bias) {
+    const float s = sum_across_halves(colsum);
+    const int n = w.n0 + g_block(0) + l32;
+    if (hh == 0 && n < n_out) a.part_b[(long)w.split * n_out + n] = s;
   }
 }
+template <int EDGE>
+__device__ __forceinline__ void weight_gemm_any(const WeightArgs& a, unsigned char* lb_smem, unsigned block) {
+  const bool gi = a.dout_idx != nullptr, xi = a.x_idx != nullptr;
+  if (!gi && !xi) weight_gemm_block<EDGE, false, false>(a, lb_smem, block);
+  else if (!xi) weight_gemm_block<EDGE, true, false>(a, lb_smem, block);
+  else if (!gi) weight_gemm_block<EDGE, false, true>(a, lb_smem, block);
+  else weight_gemm_block<EDGE, true, true>(a, lb_smem, block);
+}
 
-template <bool kGather>
+constexpr size_t kLbBigLds = (size_t)2 * 2 * kLbK * 256 * sizeof(__bf16);
+template <bool GI, bool XI>
 __global__ void __launch_bounds__(kLbThreads) __attribute__((amdgpu_waves_per_eu(2))) weight_gemm_kernel(const WeightArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lb_smem[];
-  weight_gemm_block<kGather>(a, lb_smem, blockIdx.x);
+  weight_gemm_block<kLbT, GI, XI>(a, lb_smem, blockIdx.x);
+}
+// Tiles of 256 x 256, eight waves, one workgroup a unit; up to two weight sides in a launch, workgroups [0, end) of the first.
+struct WeightPair {
+  WeightArgs w[2];
+  unsigned end;
+};
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1))) weight_gemm_big_kernel(const WeightPair p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lb_smem[];
+  const int s = blockIdx.x >= p.end;
+  weight_gemm_any<256>(p.w[s], lb_smem, blockIdx.x - (s ? p.end : 0u));
 }
 
 // A launch group of the projections' backward: an input side with 128 x 128 tiles and up to two weight sides in one
@@ -260,8 +287,7 @@ __global__ void __launch_bounds__(kLbThreads) __attribute__((amdgpu_waves_per_eu
   }
   const int s = block >= g.end[1];
   const WeightArgs& a = g.w[s];
-  if (a.dout_idx != nullptr || a.x_idx != nullptr) weight_gemm_block<true>(a, lb_smem, block - g.end[s]);
-  else weight_gemm_block<false>(a, lb_smem, block - g.end[s]);
+  weight_gemm_any<kLbT>(a, lb_smem, block - g.end[s]);
 }
 
 // part_w[split][n][k] = sum over the chunk's rows j of g_j[n] r_j[k]; part_b[split][n] = sum g_j[n]
@@ -510,24 +536,105 @@ static int reserve_lds(const char* fn, const void* kernel, size_t bytes) {
   const hipError_t attr = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   return attr == hipSuccess ? SPA_OK : fail(SPA_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, bytes);
 }
-static int launch_weight(const char* fn, const WeightArgs& a, unsigned grid, hipStream_t st) {
-  const bool gather = a.dout_idx != nullptr || a.x_idx != nullptr;
-  if (int rc = reserve_lds(fn, gather ? (const void*)weight_gemm_kernel<true> : (const void*)weight_gemm_kernel<false>, kLbGemmLds))
-    return rc;
-  if (gather) hipLaunchKernelGGL((weight_gemm_kernel<true>), dim3(grid), dim3(kLbThreads), kLbGemmLds, st, a);
-  else hipLaunchKernelGGL((weight_gemm_kernel<false>), dim3(grid), dim3(kLbThreads), kLbGemmLds, st, a);
+// How a weight side is cut: tiles of `edge`, `splits` chunks of tokens.  The number of chunks decides the bits of the
+// result, the edge does not.
+struct WeightShape {
+  int edge, splits;
+  long tiles(int n_out, int K) const { return gemm_tiles<long>(n_out, K, edge); }
+};
+// A noted or called weight side: the kernel's arguments but for the shape, the sum of its chunks, where the result goes.
+struct WeightCall {
+  WeightArgs a;
+  WeightReduceArgs r;            // r.part_w, r.part_b: the workspace
+  int max_splits;                // that fit in the workspace
+  unsigned set(WeightShape s) {  // its workgroups
+    a.splits = r.splits = s.splits;
+    a.n_tiles = (a.n_out + s.edge - 1) / s.edge;
+    a.k_tiles = (a.K + s.edge - 1) / s.edge;
+    // one chunk: the tiles are the result; more: partial tiles that the second kernel adds
+    r.part_b = r.part_w + (size_t)s.splits * a.n_out * a.K;
+    a.part_w = s.splits == 1 ? r.dW : const_cast<float*>(r.part_w);
+    a.part_b = s.splits == 1 ? r.dbias : const_cast<float*>(r.part_b);
+    return (unsigned)(((long)s.splits * a.n_tiles * a.k_tiles + 7) / 8 * 8);
+  }
+  unsigned reduce_blocks() const { return (unsigned)std::min<long>((r.nk / 4 + a.n_out + 255) / 256, 4096); }
+};
+
+static int launch_weight_big(const char* fn, const WeightPair& p, unsigned blocks, hipStream_t st) {
+  if (int rc = reserve_lds(fn, (const void*)weight_gemm_big_kernel, kLbBigLds)) return rc;
+  hipLaunchKernelGGL(weight_gemm_big_kernel, dim3(blocks), dim3(512), kLbBigLds, st, p);
   return check_launch(fn);
+}
+static int launch_weight(const char* fn, WeightCall& c, WeightShape shape, hipStream_t st) {
+  const unsigned grid = c.set(shape);
+  if (shape.edge == 256) return launch_weight_big(fn, {{c.a, c.a}, grid}, grid, st);
+  const bool gi = c.a.dout_idx != nullptr, xi = c.a.x_idx != nullptr;
+  const auto kernel = gi ? (xi ? weight_gemm_kernel<true, true> : weight_gemm_kernel<true, false>)
+                         : (xi ? weight_gemm_kernel<false, true> : weight_gemm_kernel<false, false>);
+  if (int rc = reserve_lds(fn, (const void*)kernel, kLbGemmLds)) return rc;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kLbThreads), kLbGemmLds, st, c.a);
+  return check_launch(fn);
+}
+
+// Number of token chunks with 128 x 128 tiles: (chunk, tile) workgroups for two per compute unit (what
+// is resident at a time), at most 16 chunks (every chunk's partial tiles are written and read once), chunks
+// of at least 256 rows at full capacity, and one chunk (no partial tiles, no second launch) up to 2048
+// rows: at half of them live its 16 steps take as long as 3 steps and the second launch.  The option
+// gemm_splits overrides it (tuning aid).
+static int weight_splits(int M_cap, int K, int N_out) {
+  const int env = options().gemm_splits;
+  if (env > 0) return env;
+  const long tiles = gemm_tiles<long>(N_out, K, kLbT);
+  if (M_cap <= 2048) return 1;
+  const long by_rows = std::max(M_cap / 256, 1);
+  return (int)std::clamp(std::min(512 / tiles, by_rows), 1L, 16L);
+}
+// With 256 x 256 tiles: a workgroup a unit, chunks of at least 512 rows at full capacity.
+static int weight_splits_big(int M_cap, long tiles) {
+  const int env = options().gemm_splits;
+  if (env > 0) return env;
+  const long by_rows = std::max(M_cap / 512, 1);
+  return (int)std::clamp(std::min(256 / tiles, by_rows), 1L, 16L);
+}
+// The shape of a call of its own, by what was measured (above weight_gemm_block; half of the capacity live): a step takes
+// 1.1 us in a round of two 128 x 128 workgroups a unit and 1.8 in one of 256 x 256 tiles, launch, first loads and last stores 6
+// and 9 us, and the sums 0.15 us a MB of partial tiles.  Option gemm_tm (tuning aid): 2 | 8 forces 128 x 128 | 256 x 256.
+static WeightShape weight_shape(int M_cap, int K, int N_out) {
+  const int cfg = options().gemm_tm;
+  const WeightShape small = {kLbT, weight_splits(M_cap, K, N_out)};
+  const WeightShape big = {256, weight_splits_big(M_cap, gemm_tiles<long>(N_out, K, 256))};
+  if (cfg == 2 || cfg == 8) return cfg == 8 ? big : small;
+  const double mb = 4e-6 * N_out * K;
+  const auto steps = [&](int splits) { return (double)((std::max(M_cap / 2, 1) / splits + 63) / 64); };
+  const double t_small = 6 + 1.1 * steps(small.splits) * std::ceil(small.splits * small.tiles(N_out, K) / 512.) + 0.15 * mb * small.splits;
+  const double t_big = 9 + 1.8 * steps(big.splits) * std::ceil(big.splits * big.tiles(N_out, K) / 256.) + 0.15 * mb * big.splits;
+  return t_big < 0.97 * t_small ? big : small;
+}
+static int weight_max_splits(int M_cap, int K, int N_out) {      // (rows with a gate scale take the small tiles)
+  return std::max(weight_splits(M_cap, K, N_out), weight_shape(M_cap, K, N_out).splits);
+}
+
+// Two weight sides of one group in one launch with 256 x 256 tiles: chunks of each, 0 for not.  Together they fill the chip
+// with fewer chunks than each alone: 12544 rows, 768 x 768 gathered and 2304 x 768 in seven chunks, with their sums 84.7 us
+// (two launches of 128 x 128 tiles and one for the sums 93, before 106); 512 columns 46 (55), 6272 rows of 768 columns 53 (60);
+// 1024 columns 149 (150).  From 2.4e10 multiplications at full capacity on: below, BlockTrainPass has them in one launch with
+// the input side, and its results are the same bits whether or not it may run them beside other work.
+static int weight_pair_splits(const WeightCall (&w)[2]) {
+  const int cfg = options().gemm_tm;
+  if (cfg == 2) return 0;
+  const long tiles = gemm_tiles<long>(w[0].a.n_out, w[0].a.K, 256) + gemm_tiles<long>(w[1].a.n_out, w[1].a.K, 256);
+  const double work = (double)w[0].a.m_cap * w[0].a.n_out * w[0].a.K + (double)w[1].a.m_cap * w[1].a.n_out * w[1].a.K;
+  if (cfg != 8 && (work <= 2.4e10 || tiles > 256)) return 0;
+  return std::min({weight_splits_big(std::max(w[0].a.m_cap, w[1].a.m_cap), tiles), w[0].max_splits, w[1].max_splits});
 }
 
 static thread_local struct {
   int n_rows, n_weight;
   bool big;
   GemmArgs rows;
-  WeightArgs w[2];
-  unsigned wgrid[2];
-  Noted<WeightReduceArgs> reduce;
+  WeightCall w[2];
 } g_noted;
-void group_forget_linear() { g_noted.n_rows = g_noted.n_weight = g_noted.reduce.n = 0; }
+void group_forget_linear() { g_noted.n_rows = g_noted.n_weight = 0; }
 int group_note_rows(const char* fn, const GemmArgs& args, bool big) {
   SPA_REQUIRE(g_noted.n_rows == 0, SPA_ERR_UNSUPPORTED, "%s: one input side in a group", fn);
   g_noted.rows = args;
@@ -537,46 +644,50 @@ int group_note_rows(const char* fn, const GemmArgs& args, bool big) {
 }
 int group_flush_linear(hipStream_t st) {
   auto& n = g_noted;
+  const char* fn = "spa_group_end";
+  const auto small = [&](const WeightCall& c) { return WeightShape{kLbT, weight_splits(c.a.m_cap, c.a.K, c.a.n_out)}; };
   if (n.n_rows == 1 && n.n_weight > 0 && !n.big) {
     LinearGroup g;
     g.rows = n.rows;
     const long tiles = (long)((n.rows.m_cap + 127) / 128) * ((n.rows.ncols + 127) / 128);
     g.end[0] = (unsigned)((tiles + 7) / 8 * 8);
-    g.w[0] = n.w[0];
-    g.w[1] = n.w[n.n_weight - 1];
-    g.end[1] = g.end[0] + n.wgrid[0];
-    const unsigned blocks = g.end[1] + (n.n_weight == 2 ? n.wgrid[1] : 0);
-    if (int rc = reserve_lds("spa_group_end", (const void*)linear_bwd_group_kernel, kLbGemmLds)) return rc;
+    unsigned blocks = g.end[0];
+    for (int i = 0; i < n.n_weight; ++i) {
+      blocks += n.w[i].set(small(n.w[i]));
+      if (i == 0) g.end[1] = blocks;
+      g.w[i] = n.w[i].a;
+    }
+    if (n.n_weight == 1) g.w[1] = g.w[0];
+    if (int rc = reserve_lds(fn, (const void*)linear_bwd_group_kernel, kLbGemmLds)) return rc;
     hipLaunchKernelGGL(linear_bwd_group_kernel, dim3(blocks), dim3(kLbThreads), kLbGemmLds, st, g);
   } else {
     if (n.n_rows == 1)
-      if (int rc = launch_gemm_rows("spa_group_end", n.rows, true, st)) return rc;
-    for (int i = 0; i < n.n_weight; ++i)
-      if (int rc = launch_weight("spa_group_end", n.w[i], n.wgrid[i], st)) return rc;
+      if (int rc = launch_gemm_rows(fn, n.rows, true, st)) return rc;
+    const int together = n.n_weight == 2 ? weight_pair_splits(n.w) : 0;
+    if (together > 0) {
+      WeightPair p;
+      unsigned blocks = 0;
+      for (int i = 0; i < 2; ++i) {
+        blocks += n.w[i].set({256, together});
+        if (i == 0) p.end = blocks;
+        p.w[i] = n.w[i].a;
+      }
+      if (int rc = launch_weight_big(fn, p, blocks, st)) return rc;
+    } else {
+      for (int i = 0; i < n.n_weight; ++i)
+        if (int rc = launch_weight(fn, n.w[i], small(n.w[i]), st)) return rc;
+    }
   }
-  if (n.reduce.n > 0) {
+  Noted<WeightReduceArgs> reduce;
+  for (int i = 0; i < n.n_weight; ++i)
+    if (n.w[i].r.splits > 1)
+      if (int rc = reduce.add(fn, n.w[i].r, n.w[i].reduce_blocks())) return rc;
+  if (reduce.n > 0) {
     Members<WeightReduceArgs> m;
-    const unsigned blocks = n.reduce.members(m);
+    const unsigned blocks = reduce.members(m);
     hipLaunchKernelGGL(linear_bwd_weight_reduce_group_kernel, dim3(blocks), dim3(256), 0, st, m);
   }
-  return check_launch("spa_group_end");
-}
-
-// Number of token chunks of the weight-side kernel: (chunk, tile) workgroups for two per compute unit (what
-// is resident at a time), at most 16 chunks (every chunk's partial tiles are written and read once), chunks
-// of at least 256 rows at full capacity, and one chunk (no partial tiles, no second launch) up to 2048
-// rows: at half of them live its 16 steps take as long as 3 steps and the second launch.  The option
-// gemm_splits overrides it (tuning aid).
-static int weight_splits(int M_cap, int K, int N_out) {
-  const int env = options().gemm_splits;
-  if (env > 0) return env;
-  const long tiles = (long)((N_out + kLbT - 1) / kLbT) * ((K + kLbT - 1) / kLbT);
-  if (M_cap <= 2048) return 1;
-  long s = 512 / tiles;
-  const long by_rows = M_cap / 256 > 0 ? M_cap / 256 : 1;
-  if (s > by_rows) s = by_rows;
-  if (s > 16) s = 16;
-  return (int)(s < 1 ? 1 : s);
+  return check_launch(fn);
 }
 
 }  // namespace spa
@@ -631,7 +742,7 @@ extern "C" int spa_linear_packed_bwd_input(const void* dout, const int32_t* dout
 extern "C" size_t spa_linear_bwd_weight_workspace_bytes(int M_cap, int K, int N_out, int dtype) {
   if (dtype != SPA_BF16 || M_cap < 1 || K < 1 || N_out < 1) return 0;
   const size_t per_split = ((size_t)N_out * K + N_out) * sizeof(float);
-  return ((size_t)weight_splits(M_cap, K, N_out) * per_split + 255) & ~(size_t)255;
+  return ((size_t)weight_max_splits(M_cap, K, N_out) * per_split + 255) & ~(size_t)255;
 }
 
 extern "C" int spa_linear_packed_bwd_weight(const void* dout, const int32_t* dout_idx, int64_t dout_row_stride,
@@ -663,41 +774,39 @@ extern "C" int spa_linear_packed_bwd_weight(const void* dout, const int32_t* dou
               "%s: workspace of %zu bytes needed, %zu given", fn, need, workspace_bytes);
   SPA_REQUIRE((reinterpret_cast<uintptr_t>(workspace) & 255u) == 0, SPA_ERR_INVALID_ARG,
               "%s: workspace not 256-byte aligned", fn);
-  const int splits = weight_splits(M_cap, K, N_out);
-  const int n_tiles = (N_out + kLbT - 1) / kLbT, k_tiles = (K + kLbT - 1) / kLbT;
-  const long items = (long)splits * n_tiles * k_tiles;
-  SPA_REQUIRE(items + 8 < 2147483647L / 2, SPA_ERR_INVALID_ARG, "%s: too many tiles", fn);
-  const unsigned grid = (unsigned)(((items + 7) / 8) * 8);
-  float* part_w = static_cast<float*>(workspace);
-  float* part_b = part_w + (size_t)splits * N_out * K;
-  const WeightReduceArgs rargs = {part_w, part_b, total, M_cap, splits, (long)N_out * K, N_out, dW, dbias};
-  const unsigned rblocks = (unsigned)std::min<long>(((long)N_out * K / 4 + N_out + 255) / 256, 4096);
+  const WeightShape shape = gate_scores != nullptr ? WeightShape{kLbT, weight_splits(M_cap, K, N_out)} : weight_shape(M_cap, K, N_out);
+  SPA_REQUIRE(shape.splits * shape.tiles(N_out, K) + 8 < 2147483647L / 2, SPA_ERR_INVALID_ARG, "%s: too many tiles", fn);
   SPA_REQUIRE(!(group_open() && gate_scores != nullptr), SPA_ERR_UNSUPPORTED, "%s: gated rows cannot be part of a group", fn);
+  WeightCall c = {};
+  c.a.dout = (const __bf16*)dout;
+  c.a.dout_idx = dout_idx;
+  c.a.ldd = dout_row_stride;
+  c.a.x = (const __bf16*)x;
+  c.a.x_idx = x_idx;
+  c.a.total = total;
+  c.a.m_cap = M_cap;
+  c.a.K = K;
+  c.a.n_out = N_out;
+  c.r = {static_cast<const float*>(workspace), nullptr, total, M_cap, 0, (long)N_out * K, N_out, dW, dbias};
+  c.max_splits = weight_max_splits(M_cap, K, N_out);
+  if (group_open()) {
+    SPA_REQUIRE(g_noted.n_weight < 2, SPA_ERR_UNSUPPORTED, "%s: two weight sides in a group", fn);
+    g_noted.w[g_noted.n_weight++] = c;
+    return SPA_OK;
+  }
   if (gate_scores != nullptr) {
-    const hipError_t attr = hipFuncSetAttribute((const void*)linear_bwd_weight_bf16_kernel,
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLbWeightLds);
-    SPA_REQUIRE(attr == hipSuccess, SPA_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, kLbWeightLds);
-    hipLaunchKernelGGL(linear_bwd_weight_bf16_kernel, dim3(grid), dim3(kLbThreads), kLbWeightLds, st, (const __bf16*)dout,
-                       dout_idx, (long)dout_row_stride, (const __bf16*)x, x_idx, gate_scores, total, M_cap, K, N_out, splits,
-                       n_tiles, k_tiles, part_w, part_b);
+    const unsigned grid = c.set(shape);
+    if (int rc = reserve_lds(fn, (const void*)linear_bwd_weight_bf16_kernel, kLbWeightLds)) return rc;
+    hipLaunchKernelGGL(linear_bwd_weight_bf16_kernel, dim3(grid), dim3(kLbThreads), kLbWeightLds, st, c.a.dout, dout_idx, c.a.ldd,
+                       c.a.x, x_idx, gate_scores, total, M_cap, K, N_out, shape.splits, c.a.n_tiles, c.a.k_tiles,
+                       const_cast<float*>(c.r.part_w), const_cast<float*>(c.r.part_b));
   } else {
-    // one chunk: the tiles are the result; more: partial tiles that the second kernel adds
-    float* pw = splits == 1 ? dW : part_w;
-    float* pb = splits == 1 ? dbias : part_b;
-    const WeightArgs wargs = {(const __bf16*)dout, dout_idx, (long)dout_row_stride, (const __bf16*)x, x_idx, total, M_cap, K,
-                              N_out, splits, n_tiles, k_tiles, pw, pb};
-    if (group_open()) {
-      SPA_REQUIRE(g_noted.n_weight < 2, SPA_ERR_UNSUPPORTED, "%s: two weight sides in a group", fn);
-      g_noted.w[g_noted.n_weight] = wargs;
-      g_noted.wgrid[g_noted.n_weight++] = grid;
-      return splits == 1 ? SPA_OK : g_noted.reduce.add(fn, rargs, rblocks);
-    }
-    if (int rc = launch_weight(fn, wargs, grid, st)) return rc;
-    if (splits == 1) return SPA_OK;
+    if (int rc = launch_weight(fn, c, shape, st)) return rc;
+    if (shape.splits == 1) return SPA_OK;
   }
   const int rc = check_launch(fn);
   if (rc != SPA_OK) return rc;
-  hipLaunchKernelGGL(linear_bwd_weight_reduce_kernel, dim3(rblocks), dim3(256), 0, st, rargs);
+  hipLaunchKernelGGL(linear_bwd_weight_reduce_kernel, dim3(c.reduce_blocks()), dim3(256), 0, st, c.r);
   return check_launch(fn);
 }
 

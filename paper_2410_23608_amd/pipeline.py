@@ -441,18 +441,19 @@ class BlockTrainPass(_Pass):
                     spa.spa_linear_packed_bwd_weight(dp, None, self.packed_rg, None, None, self.total, cap,
                                                      self.dW_qkv, self.db_qkv, self.ws_qkv, prepare=True))
 
-        if self.overlap:
-            with torch.cuda.stream(self.side):             # the prepared calls keep the stream they were made on
-                w_o, w_qkv = weight_side()
-            events = [spa.Event() for _ in range(3)]
-
-            def on_side(ev, call):      # inputs of the GEMM are complete on the main stream
-                return spa.chain(ev.record(main), ev.wait(self.side), call)
-
-            join = spa.chain(events[2].record(self.side), events[2].wait(main))
-            w_o, w_qkv = on_side(events[0], w_o), on_side(events[1], w_qkv)
-        else:
+        with torch.cuda.stream(self.side if self.overlap else main):       # prepared calls keep the stream they were made on
             w_o, w_qkv = weight_side()
+            if not self.grouped and p.dtype == torch.bfloat16:
+                weights = [("projections_bwd_weight", spa.group(w_o, w_qkv))]
+            else:
+                weights = [("out_projection_bwd_weight", w_o), ("qkv_projection_bwd_weight", w_qkv)]
+        join = []
+        if self.overlap:                               # (the inputs of both are complete on the main stream)
+            start, done = spa.Event(), spa.Event()
+            calls = [fn for _, fn in weights]
+            weights = [("projections_bwd_weight", spa.chain(start.record(main), start.wait(self.side), *calls,
+                                                            done.record(self.side)))]
+            join = [("join_streams", done.wait(main))]
         forward = [
             ("gate_select", spa.spa_gate_select(x, w, self.bias, None, self.tau, self.scores, self.mask, None,
                                                 prepare=True)),
@@ -476,10 +477,8 @@ class BlockTrainPass(_Pass):
         if self.grouped:
             return forward + [("out_projection_bwd_input", in_o), ("packed_attention_bwd", attention_bwd),
                               ("projections_bwd", spa.group(in_qkv, w_o, w_qkv)), gate_bwd]
-        return forward + [
-            ("out_projection_bwd_weight", w_o), ("out_projection_bwd_input", in_o), ("packed_attention_bwd", attention_bwd),
-            ("qkv_projection_bwd_weight", w_qkv), ("qkv_projection_bwd_input", in_qkv), gate_bwd,
-        ] + ([("join_streams", join)] if self.overlap else [])
+        return forward + [("out_projection_bwd_input", in_o), ("packed_attention_bwd", attention_bwd), *weights,
+                          ("qkv_projection_bwd_input", in_qkv), gate_bwd, *join]
 
     def run(self, x, w, W_qkv, b_qkv, W_o, b_o, labels, dy):
         self._issue(x, w, W_qkv, b_qkv, W_o, b_o, labels, dy)
