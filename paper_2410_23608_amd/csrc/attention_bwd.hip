@@ -530,14 +530,18 @@ int group_flush_attention_bwd(hipStream_t st) {
 // segment's tokens 32j .. 32j+31, first as keys, then as queries.
 //   keys:    Q and dO of the segment in LDS; S = Q_t K_j^T (a lane holds 16 queries of ONE key), then
 //            dV_j^T += dO_t^T P and, with dP = dO_t V_j^T, dK_j^T += Q_t^T dS over the query tiles t;
-//   queries: K and V of the segment in the same LDS; S^T = K_t Q_j^T, dP^T = V_t dO_j^T (16 keys of one
-//            query in a lane), dQ_j^T += K_t^T dS^T over the key tiles t.
+//   queries: K and V of the segment, from the registers of the waves that own them, in the same LDS;
+//            S^T = K_t Q_j^T, dP^T = V_t dO_j^T (16 keys of one query in a lane), dQ_j^T += K_t^T dS^T over
+//            the key tiles t.
 // S (and at head dim 64 P, see kOnePass) is computed again instead of exchanged: no dS tiles, no dQ
 // accumulators in LDS, no barrier inside either half, so the waves of a workgroup drift apart, and with
 // 65 instead of 141 KB at 196 tokens and at most 128 registers two workgroups share a unit: one loads
 // while the other multiplies.  No atomics, every sum in a fixed order: run-to-run bit-stable.
 // Measured on the ViT-B-shaped batch (64 x 196 tokens, 12 heads of 64): 44.8 -> 37.3 us; 128 images, their order by
-// ballots instead of a ranking in LDS in every workgroup: 82 -> 72.
+// ballots instead of a ranking in LDS in every workgroup: 82 -> 72.  Bound by its memory phases: without any walk it takes 26 of
+// 36 us (77 MB of rows, 29 MB of zeros), so the K and V rows are not fetched a second time: 40.0 -> 36.2 us (q, k, v
+// at token positions), 128 images with packed rows 61 -> 51.6.  Two short segments in one workgroup, so that all its waves
+// have tokens: 38.1 | 38.0 us with | without, 128 images 52.7 | 52.1 - fewer workgroups overlap their phases less.
 // Operand rows: packed (row0 + j), or GATED: q, k, v at token positions (row gather_idx[j]), the v row
 // multiplied by Sigmoid(score) and rounded to bf16 (r_g = Sigmoid(s) . r, as a packed r_g holds it).
 // Dynamic LDS, rows = 32 * nw:  A [rows][DH+8] (Q, then K) | B [rows][DH+8] (dO, then V) |
@@ -702,8 +706,8 @@ attn_bwd_short_bf16_kernel(const BwdArgs p) {
       store_rows<DH>(dka, p.scale, p.dk + my_row * p.dks + h * DH, t_ok, hh);
     }
 
-    // ---- as queries: Q_j, dO_j from LDS to registers, then K and V rows take their place
-    bf16x8 qf[KK], gf[KK], kreg[PER], vreg[PER];
+    // ---- as queries: Q_j, dO_j from LDS to registers, then every wave's K and V rows, which it holds, take their place
+    bf16x8 qf[KK], gf[KK];
     float D = 0.f, lse2 = INFINITY;                  // (queries past the segment: probability 0)
     if (live) {
 #pragma unroll
@@ -714,24 +718,13 @@ attn_bwd_short_bf16_kernel(const BwdArgs p) {
       D = Ds[ti];
       lse2 = lse2s[ti];
     }
-#pragma unroll
-    for (int t = 0; t < PER; ++t) {
-      const int i = tid + t * threads, r = i / CPR, c = i % CPR;
-      kreg[t] = zero_bf16x8();
-      vreg[t] = zero_bf16x8();
-      if (r < n) {
-        const long src = src_row(r);
-        kreg[t] = *reinterpret_cast<const bf16x8*>(p.k + src * p.ks + h * DH + c * 8);
-        vreg[t] = *reinterpret_cast<const bf16x8*>(p.v + src * p.vs + h * DH + c * 8);
-        if (GATED) vreg[t] = scale_row(vreg[t], sigmoidf_dev(p.v_scores[src]));
-      }
-    }
     __syncthreads();                                 // every wave is done with Q and dO
+    if (live) {
 #pragma unroll
-    for (int t = 0; t < PER; ++t) {
-      const int i = tid + t * threads, r = i / CPR, c = i % CPR;
-      *reinterpret_cast<bf16x8*>(&As[r * RS + c * 8]) = kreg[t];
-      *reinterpret_cast<bf16x8*>(&Bs[r * RS + c * 8]) = vreg[t];
+      for (int kk = 0; kk < KK; ++kk) {
+        *reinterpret_cast<bf16x8*>(&As[ti * RS + kk * 16 + hh * 8]) = kf[kk];
+        *reinterpret_cast<bf16x8*>(&Bs[ti * RS + kk * 16 + hh * 8]) = vf[kk];
+      }
     }
     __syncthreads();
     if (live) {
