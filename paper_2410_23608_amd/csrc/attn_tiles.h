@@ -493,16 +493,16 @@ struct PairStage {
   const int tid;                 // this thread's number
   bf16x8 v[2][CPT];
   int idx[CPT];
-  const __bf16* base[2];         // this thread's columns of row 0 (indexed) or of the segment's first row
-  int stride[2];
+  const char* base[2];           // this thread's columns of row 0 (indexed) or of the segment's first row
+  uint32_t stride[2];            // bytes: an address is one 32 x 32 + 64 bit multiply-add
   const int32_t* gi;
   int last;                      // the segment's last row
   int from;                      // first row of the tile in flight
   __device__ __forceinline__ explicit PairStage(int tid_) : tid(tid_) {}
   __device__ __forceinline__ int row(int t) const { return tid / CPR + t * RPP; }
   __device__ __forceinline__ void source(int o, const __bf16* p, long row_stride, long row0) {
-    base[o] = p + tid % CPR * 8 + ((o ? IDX1 : IDX0) ? 0 : row0 * row_stride);
-    stride[o] = (int)row_stride;
+    base[o] = reinterpret_cast<const char*>(p + tid % CPR * 8 + ((o ? IDX1 : IDX0) ? 0 : row0 * row_stride));
+    stride[o] = (uint32_t)row_stride * (uint32_t)sizeof(__bf16);
   }
   __device__ __forceinline__ void index(int t0) {
     if (IDX0 || IDX1) {
@@ -515,8 +515,8 @@ struct PairStage {
 #pragma unroll
     for (int t = 0; t < CPT; ++t) {
       const int r = min(t0 + row(t), last);
-      v[0][t] = *reinterpret_cast<const bf16x8*>(base[0] + (long)(IDX0 ? idx[t] : r) * stride[0]);
-      v[1][t] = *reinterpret_cast<const bf16x8*>(base[1] + (long)(IDX1 ? idx[t] : r) * stride[1]);
+      v[0][t] = *reinterpret_cast<const bf16x8*>(base[0] + (uint64_t)(uint32_t)(IDX0 ? idx[t] : r) * stride[0]);
+      v[1][t] = *reinterpret_cast<const bf16x8*>(base[1] + (uint64_t)(uint32_t)(IDX1 ? idx[t] : r) * stride[1]);
     }
   }
   __device__ __forceinline__ void clear_past() {
