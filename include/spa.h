@@ -365,6 +365,28 @@ int spa_gated_attention_unpack(const void* q, const void* k, const void* x, int6
                                void* out, float* lse, void* y, void* stream);
 
 /*
+ * A training step whose dy is there before the forward pass: spa_gated_attention_unpack that also leaves D_i = <dy_i, out_i>
+ * in the workspace of the backward (>= spa_attention_bwd_workspace_bytes), and spa_gated_attention_bwd_tokens_spread that
+ * takes it from there (max_seqlen > 256 or in a launch group; below, it may form D itself) instead of with a launch of its
+ * own.  The two calls of a step get the same dy, y, out, B, N = max_seqlen and workspace, and nothing writes dy, out or the
+ * workspace between them.  Where dy shares memory with y or out, both form D as the other entry points do.  The same bits.
+ */
+int spa_gated_attention_unpack_dvec(const void* q, const void* k, const void* x, int64_t q_row_stride,
+                                    int64_t k_row_stride, int64_t x_row_stride, const float* scores,
+                                    const int32_t* cu_seqlens, const int32_t* gather_idx, const int32_t* inv_pos,
+                                    const void* base, int B, int N, int H, int Dh, int dtype, float softmax_scale,
+                                    void* out, float* lse, void* y, const void* dy, void* workspace, size_t workspace_bytes,
+                                    void* stream);
+int spa_gated_attention_bwd_tokens_dvec(const void* q, const void* k, const void* x, int64_t q_row_stride,
+                                        int64_t k_row_stride, int64_t x_row_stride, const float* scores,
+                                        const void* out, const void* dy, const float* lse, const int32_t* cu_seqlens,
+                                        int B, int max_seqlen, int H, int Dh, int dtype, float softmax_scale,
+                                        const int32_t* gather_idx, const int32_t* inv_pos, int64_t rows, void* dq,
+                                        void* dk, void* d_rg, int64_t dq_row_stride, int64_t dk_row_stride,
+                                        int64_t d_rg_row_stride, void* workspace, size_t workspace_bytes, const void* y,
+                                        void* stream);
+
+/*
  * Packing order, attention and scatter in ONE call, for images of at most 256 tokens (Section 3.2:
  * the positive tokens, in token order, attend to each other inside their image; the negative tokens
  * go on directly): spa_gathered_attention_unpack without a packing index.  Every wave derives its

@@ -4,7 +4,7 @@
 // No atomics anywhere; results are run-to-run bit-stable.
 // Segments of up to 256 tokens (bf16): one kernel, a workgroup per (image, head); see
 // attn_bwd_short_bf16_kernel.
-// Longer segments (bf16): two roles in one launch, after a small kernel that writes D_i:
+// Longer segments (bf16): two roles in one launch, after a small kernel that writes D_i (or the forward pass has):
 //   dq role   : a wave owns 32 queries and walks the segment's keys.  Like the forward it
 //               works on transposed tiles (S^T = K Q^T, dP^T = V dO^T) so lse_i and D_i are
 //               one scalar per lane and dS^T is already the B operand of dQ^T += K^T dS^T.
@@ -458,7 +458,10 @@ attn_bwd_resident_bf16_kernel(const BwdArgs p) {
 }
 
 // D[h][j] = <dO_j, O_j> over head h's columns, for the packed rows j < cu[B]: DH / 8 adjacent
-// lanes share a (row, head).
+// lanes share a (row, head).  A launch of 4 to 6 us for a few MB; where dO is known before the forward pass, that pass forms
+// D with the same sums from the rows it holds (fwd_flush), and this launch falls away.  us a training step: 32 x 400 tokens, 6
+// heads of 64, 64.6 -> 61.6, 12 x 720, 8 heads of 32, 45.0 -> 42.1, 8 x 1024, 12 heads of 64, 94.3 -> 91.1; four stages of 16 x 3136
+// tokens as launch groups 136.8 -> 133.7, of one image 62.9 -> 60.3.
 template <int DH>
 __device__ __forceinline__ void bwd_dvec_block(const BwdArgs& p, unsigned block, unsigned blocks) {
   constexpr int CPR = DH / 8;
@@ -509,8 +512,10 @@ static void flush_mode(hipStream_t st) {
   constexpr int g = MODE == kGated;
   if (g_noted[g].n == 0) return;
   Members<BwdArgs> m;
-  const unsigned dblocks = g_noted_dvec[g].members(m);
-  hipLaunchKernelGGL(attn_bwd_dvec_group_kernel, dim3(dblocks), dim3(256), 0, st, m);
+  if (g_noted_dvec[g].n > 0) {
+    const unsigned dblocks = g_noted_dvec[g].members(m);
+    hipLaunchKernelGGL(attn_bwd_dvec_group_kernel, dim3(dblocks), dim3(256), 0, st, m);
+  }
   bool resident = true;
   for (int i = 0; i < g_noted[g].n; ++i) resident = resident && live_tiles_apply(g_noted[g].a[i].H, g_noted[g].a[i].B);
   for (int i = 0; resident && i < g_noted[g].n; ++i)
@@ -927,7 +932,7 @@ static int attention_bwd_common(const char* fn, const void* q, const void* k, co
                                 int dtype, float softmax_scale, void* dq, void* dk, void* dv,
                                 int64_t dq_row_stride, int64_t dk_row_stride, int64_t dv_row_stride,
                                 void* workspace, size_t workspace_bytes, TokenIO tok, void* stream,
-                                bool spread, const float* v_scores = nullptr) {
+                                bool spread, const float* v_scores = nullptr, bool have_d = false) {
   const bool at_tokens = tok.gather_idx != nullptr;
   SPA_REQUIRE(q && k && v && out && dout && lse && cu_seqlens && dq && dk && dv, SPA_ERR_INVALID_ARG,
               "%s: null pointer", fn);
@@ -1005,7 +1010,8 @@ static int attention_bwd_common(const char* fn, const void* q, const void* k, co
     const unsigned all = 2 * xcd_grid(nblk, H, B), grid = resident && !group_open() ? std::min(all, (unsigned)bwd_long_slots(Dh)) : all;
     const unsigned dgrid = (unsigned)std::min<long>(((long)B * max_seqlen * H * (Dh / 8) + 255) / 256, 4096L);
     if (group_open()) {
-      if (int rc = g_noted_dvec[v_scores != nullptr].add(fn, args, dgrid)) return rc;
+      if (!have_d)
+        if (int rc = g_noted_dvec[v_scores != nullptr].add(fn, args, dgrid)) return rc;
       return g_noted[v_scores != nullptr].add(fn, args, grid);
     }
 #define SPA_BWD_MODE(KERNEL, D)                                                                                 \
@@ -1016,7 +1022,7 @@ static int attention_bwd_common(const char* fn, const void* q, const void* k, co
   } while (0)
 #define SPA_BWD_LONG(D)                                                                                         \
   do {                                                                                                          \
-    hipLaunchKernelGGL((attn_bwd_dvec_kernel<D>), dim3(dgrid), dim3(256), 0, st, args);                         \
+    if (!have_d) hipLaunchKernelGGL((attn_bwd_dvec_kernel<D>), dim3(dgrid), dim3(256), 0, st, args);            \
     if (resident) SPA_BWD_MODE(attn_bwd_resident_bf16_kernel, D);                                               \
     else SPA_BWD_MODE(attn_bwd_long_bf16_kernel, D);                                                            \
   } while (0)
@@ -1102,4 +1108,22 @@ extern "C" int spa_gated_attention_bwd_tokens_spread(const void* q, const void* 
                               max_seqlen, H, Dh, dtype, softmax_scale, dq, dk, d_rg, dq_row_stride, dk_row_stride,
                               d_rg_row_stride, workspace, workspace_bytes, TokenIO{gather_idx, inv_pos, (long)rows},
                               stream, true, scores);
+}
+
+extern "C" int spa_gated_attention_bwd_tokens_dvec(const void* q, const void* k, const void* x, int64_t q_row_stride,
+                                                   int64_t k_row_stride, int64_t x_row_stride, const float* scores,
+                                                   const void* out, const void* dy, const float* lse, const int32_t* cu_seqlens,
+                                                   int B, int max_seqlen, int H, int Dh, int dtype, float softmax_scale,
+                                                   const int32_t* gather_idx, const int32_t* inv_pos, int64_t rows, void* dq,
+                                                   void* dk, void* d_rg, int64_t dq_row_stride, int64_t dk_row_stride,
+                                                   int64_t d_rg_row_stride, void* workspace, size_t workspace_bytes,
+                                                   const void* y, void* stream) {
+  const char* fn = "spa_gated_attention_bwd_tokens_dvec";
+  SPA_REQUIRE(scores && gather_idx && inv_pos && y, SPA_ERR_INVALID_ARG, "%s: null pointer", fn);
+  SPA_REQUIRE(rows >= 1 && rows < 2147483647L, SPA_ERR_INVALID_ARG, "%s: rows must be in [1, 2^31)", fn);
+  SPA_REQUIRE(dtype == SPA_BF16, SPA_ERR_UNSUPPORTED, "%s: bf16 only (use spa_pack_pair + spa_packed_attention_bwd_tokens)", fn);
+  return attention_bwd_common(fn, q, k, x, q_row_stride, k_row_stride, x_row_stride, out, dy, lse, cu_seqlens, B,
+                              max_seqlen, H, Dh, dtype, softmax_scale, dq, dk, d_rg, dq_row_stride, dk_row_stride,
+                              d_rg_row_stride, workspace, workspace_bytes, TokenIO{gather_idx, inv_pos, (long)rows},
+                              stream, true, scores, d_from_forward(dy, y, out, (size_t)B * max_seqlen * H * Dh * 2));
 }

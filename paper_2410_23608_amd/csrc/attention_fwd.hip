@@ -44,6 +44,8 @@ struct Scatter {
                                //    builds the index and no row is copied before the attention
   const uint8_t* mask;         // [B*N] or nullptr: when given, a token bypasses attention iff its mask byte is 0
                                //    (used in place of inv_pos by the form that is given no packing index)
+  const __bf16* dy = nullptr;  // kFwdGatedD: the gradient of y, where it is there already, and
+  float* dvec = nullptr;       //    D_i = <dy_i, out_i> of every (head, packed row), laid out as lse, for the backward
 };
 __device__ __forceinline__ bool bypasses(const Scatter& sc, long row) {
   return sc.mask != nullptr ? sc.mask[row] == 0 : sc.inv_pos[row] < 0;
@@ -71,7 +73,9 @@ struct FwdArgs {
 // absent and the row addresses stay affine in the loop counters (pointer increments), with gathered
 // rows every row address is a multiply on a loaded index.  kFwdGated: gathered, and a v row is multiplied by
 // Sigmoid(score of its token) and rounded to bf16 on its way to LDS, as a packed r_g holds it.
-constexpr int kFwdPacked = 0, kFwdGathered = 1, kFwdGated = 2;
+// kFwdGatedD: and D of the backward (Scatter::dvec).
+constexpr int kFwdPacked = 0, kFwdGathered = 1, kFwdGated = 2, kFwdGatedD = 3, kFwdForms = 4;
+constexpr bool is_gated(int gather) { return gather >= kFwdGated; }
 template <int GATHER>
 __device__ __forceinline__ const int32_t* gather_base(const Scatter& sc, long row0) {
   return GATHER ? sc.gather_idx + row0 : nullptr;
@@ -355,10 +359,32 @@ __device__ __forceinline__ void fwd_park(FwdAcc<DH>& acc, bool q_ok, bool have_k
 // Output stage, phase 2 (after a barrier): the wave copies its parked tile to global memory,
 // consecutive lanes writing consecutive 16-byte chunks of a row.  nrows = valid rows (<= 32);
 // prow0 = packed row of the tile's first row, y_row = row of y of lane % 32's row.  out may be null when only y is wanted.
-template <int DH, int RS>
+// D (dvec): also the products of the rows with those of sc.dy, to dvec[packed row].
+template <int DH, int RS, bool D = false>
 __device__ __forceinline__ void fwd_flush(const __bf16* tile, __bf16* out, const Scatter& sc, int y_row, long prow0, int h,
-                                          long C, int nrows, int lane) {
+                                          long C, int nrows, int lane, float* dvec = nullptr) {
   constexpr int CPR = DH / 8;
+  if constexpr (D) {
+    constexpr int PASSES = 32 * CPR / 64;
+    bf16x8 g[PASSES];
+#pragma unroll
+    for (int t = 0; t < PASSES; ++t) {
+      const int i = lane + 64 * t, r = i / CPR, token = __builtin_amdgcn_ds_bpermute(r << 2, y_row);
+      g[t] = zero_bf16x8();
+      if (r < nrows) g[t] = *reinterpret_cast<const bf16x8*>(sc.dy + (long)token * C + h * DH + i % CPR * 8);
+    }
+#pragma unroll
+    for (int t = 0; t < PASSES; ++t) {
+      const int i = lane + 64 * t, r = i / CPR;
+      const floatx8 of = bf16x8_to_float(*reinterpret_cast<const bf16x8*>(&tile[r * RS + i % CPR * 8]));
+      const floatx8 gf = bf16x8_to_float(g[t]);
+      float d = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) d = fmaf(of[e], gf[e], d);
+      d = adjacent_sum<CPR>(d);
+      if (r < nrows && i % CPR == 0) dvec[prow0 + r] = d;
+    }
+  }
 #pragma unroll
   for (int i = lane; i < 32 * CPR; i += 64) {
     const int r = i / CPR, c = i % CPR, token = __builtin_amdgcn_ds_bpermute(r << 2, y_row);
@@ -539,14 +565,14 @@ tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, c
   float gate[decltype(stage)::CPT] = {};
   auto load_tile = [&](int kt) {                                // (then the index of the one after it)
     stage.load(kt);
-    if (GATHER == kFwdGated) {
+    if (is_gated(GATHER)) {
 #pragma unroll
       for (int t = 0; t < decltype(stage)::CPT; ++t) gate[t] = v_scores[stage.idx[t]];
     }
     stage.index(kt + BN);
   };
   auto store_tile = [&](int buf, auto clear) {
-    if (GATHER == kFwdGated) stage.template store_gated<clear>(Ks[buf], Vs[buf], gate);
+    if (is_gated(GATHER)) stage.template store_gated<clear>(Ks[buf], Vs[buf], gate);
     else stage.template store<clear>(Ks[buf], Vs[buf]);
   };
   stage.index(0);
@@ -577,7 +603,8 @@ tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, c
     fwd_park<DH, RS>(acc, q_ok, seg.nk > 0, parked, lse != nullptr ? lse + h * lse_stride + seg.row0 + qi : nullptr,
                      l32, hh);
     __builtin_amdgcn_wave_barrier();
-    fwd_flush<DH, RS>(parked, out, sc, y_row, seg.row0 + q0 + wv * 32, h, C, min(32, seg.nq - q0 - wv * 32), lane);
+    fwd_flush<DH, RS, GATHER == kFwdGatedD>(parked, out, sc, y_row, seg.row0 + q0 + wv * 32, h, C, min(32, seg.nq - q0 - wv * 32),
+                                           lane, sc.dvec + h * lse_stride);
   }
 }
 
@@ -789,7 +816,7 @@ wave_attention(WaveLds<DH, STEP>* lds, int part, const Segment seg, int h, int q
         }
         if (!KREGS) kreg[t] = *reinterpret_cast<const bf16x8*>(kp);
         vreg[t] = *reinterpret_cast<const bf16x8*>(vp);
-        if (GATHER == kFwdGated) gate[t] = v_scores[tok_rows[t]];
+        if (is_gated(GATHER)) gate[t] = v_scores[tok_rows[t]];
       }
     }
   };
@@ -799,7 +826,7 @@ wave_attention(WaveLds<DH, STEP>* lds, int part, const Segment seg, int h, int q
       const int i = lane + 64 * t, r = i / CPR, c = i % CPR;
       if (!KREGS) *reinterpret_cast<bf16x8*>(&Ks[r * RS + c * 8]) = kreg[t];
       *reinterpret_cast<bf16x8*>(&Vs[r * RS + c * 8]) =
-          GATHER == kFwdGated ? scale_row(vreg[t], sigmoidf_dev(gate[t])) : vreg[t];
+          is_gated(GATHER) ? scale_row(vreg[t], sigmoidf_dev(gate[t])) : vreg[t];
     }
   };
 
@@ -852,7 +879,8 @@ wave_attention(WaveLds<DH, STEP>* lds, int part, const Segment seg, int h, int q
   // output: park the 32 x DH tile in the (now free) K tile, then write whole rows
   fwd_park<DH, RS>(acc, q_ok, seg.nk > 0, Ks, lse != nullptr ? lse + h * lse_stride + seg.row0 + qi : nullptr, l32,
                    hh);
-  fwd_flush<DH, RS>(Ks, out, sc, y_row, seg.row0 + q0, h, C, min(32, seg.nq - q0), lane);
+  fwd_flush<DH, RS, GATHER == kFwdGatedD>(Ks, out, sc, y_row, seg.row0 + q0, h, C, min(32, seg.nq - q0), lane,
+                                         sc.dvec + h * lse_stride);
 }
 
 // Waves a unit.  One wave a unit lives 2 us + 0.8 us for every 32 keys + 1.5 us; where the units do not fill the chip (half
@@ -1075,8 +1103,8 @@ attn_fwd_bf16_group_kernel(const Members<FwdArgs> m) {
   }
 }
 
-static thread_local Noted<FwdArgs> g_noted[3];       // by form
-void group_forget_attention() { g_noted[0].n = g_noted[1].n = g_noted[2].n = 0; }
+static thread_local Noted<FwdArgs> g_noted[kFwdForms];       // by form
+void group_forget_attention() { for (auto& g : g_noted) g.n = 0; }
 template <int FORM>
 static void flush_form(hipStream_t st) {
   if (g_noted[FORM].n == 0) return;
@@ -1088,6 +1116,7 @@ int group_flush_attention(hipStream_t st) {
   flush_form<kFwdPacked>(st);
   flush_form<kFwdGathered>(st);
   flush_form<kFwdGated>(st);
+  flush_form<kFwdGatedD>(st);
   return check_launch("spa_group_end");
 }
 // workgroups of four waves for so many units (8 XCDs)
@@ -1413,7 +1442,7 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
     const float scale_log2 = scale * 1.4426950408889634f;
     FwdArgs args = {(const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_stride, (long)k_stride, (long)v_stride, v_scores,
                     cu, key_lens, n_max, H, scale_log2, (__bf16*)out, lse, lse_stride, sc, B, 0, 0, 1};
-    const int form = v_scores != nullptr ? kFwdGated : sc.gathered ? kFwdGathered : kFwdPacked;
+    const int form = v_scores != nullptr ? (sc.dvec != nullptr ? kFwdGatedD : kFwdGated) : sc.gathered ? kFwdGathered : kFwdPacked;
     const auto live = [&] { return key_lens == nullptr && live_tiles_apply(H, B); };
     // the tiled kernel's workgroups: resident together 3 waves per SIMD at head dim 32, 2 at 64
     const auto tiled_grid = [&] {
@@ -1442,7 +1471,8 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
   } while (0)
 #define SPA_LAUNCH_FORM(KERNEL, GRID, BLOCK, ARGS, ...)                                                       \
   do {                                                                                                        \
-    if (form == kFwdGated) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFwdGated>), GRID, BLOCK, 0, st, ARGS);    \
+    if (form == kFwdGatedD) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFwdGatedD>), GRID, BLOCK, 0, st, ARGS);  \
+    else if (form == kFwdGated) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, kFwdGated>), GRID, BLOCK, 0, st, ARGS); \
     else SPA_LAUNCH(KERNEL, GRID, BLOCK, ARGS, __VA_ARGS__);                                                  \
   } while (0)
 #define SPA_ARGS                                                                                              \
@@ -1454,7 +1484,7 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
     const bool tiled = opt.fwd_tiled;
     const bool use_whole = opt.fwd_whole;
     const int wave_max = opt.fwd_wave_max;
-    if (!tiled && n_max <= wave_max && (!use_whole || form == kFwdGated)) {
+    if (!tiled && n_max <= wave_max && (!use_whole || is_gated(form))) {
       // short segments: one wave per (image, head, 32 queries)
       const int nqb = (n_max + 31) / 32;
       const dim3 grid(xcd_grid(nqb, H, B));
@@ -1479,7 +1509,7 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
         else SPA_WAVE(attn_fwd_bf16_wave_kernel, grid, 64);
       }
 #undef SPA_WAVE
-    } else if (!tiled && n_max <= 256 && form != kFwdGated) {
+    } else if (!tiled && n_max <= 256 && !is_gated(form)) {
       // short segments: one workgroup per (image, head), whole segment in LDS
       const dim3 grid(H, B);
 #define SPA_WHOLE(D)                                                                                          \
@@ -1569,18 +1599,45 @@ extern "C" int spa_gathered_attention_unpack(const void* q, const void* k, const
                           dtype, softmax_scale, out, lse, sc, stream);
 }
 
+static int gated_attention_unpack(const char* fn, const void* q, const void* k, const void* x, int64_t q_row_stride,
+                                  int64_t k_row_stride, int64_t x_row_stride, const float* scores, const int32_t* cu_seqlens,
+                                  const int32_t* gather_idx, const int32_t* inv_pos, const void* base, int B, int N, int H,
+                                  int Dh, int dtype, float softmax_scale, void* out, float* lse, void* y, const void* dy,
+                                  float* dvec, void* stream) {
+  SPA_REQUIRE(scores && cu_seqlens && gather_idx && inv_pos && y, SPA_ERR_INVALID_ARG, "%s: null pointer", fn);
+  SPA_REQUIRE(aligned16(y) && aligned16(base) && aligned16(dy), SPA_ERR_INVALID_ARG, "%s: y / base / dy not 16-byte aligned", fn);
+  SPA_REQUIRE(dtype == SPA_BF16, SPA_ERR_UNSUPPORTED, "%s: bf16 only (use spa_pack_pair + spa_packed_attention_unpack)", fn);
+  Scatter sc = {gather_idx, inv_pos, base, y, N, 0, 1, nullptr};
+  if (dy != nullptr && d_from_forward(dy, y, out, (size_t)B * N * H * Dh * 2)) {
+    sc.dy = static_cast<const __bf16*>(dy);
+    sc.dvec = dvec;
+  }
+  return attention_common(fn, q, k, x, q_row_stride, k_row_stride, x_row_stride, cu_seqlens, nullptr, B, N, H, Dh, dtype,
+                          softmax_scale, out, lse, sc, stream, scores);
+}
+
 extern "C" int spa_gated_attention_unpack(const void* q, const void* k, const void* x, int64_t q_row_stride,
                                           int64_t k_row_stride, int64_t x_row_stride, const float* scores,
                                           const int32_t* cu_seqlens, const int32_t* gather_idx, const int32_t* inv_pos,
                                           const void* base, int B, int N, int H, int Dh, int dtype, float softmax_scale,
                                           void* out, float* lse, void* y, void* stream) {
-  const char* fn = "spa_gated_attention_unpack";
-  SPA_REQUIRE(scores && cu_seqlens && gather_idx && inv_pos && y, SPA_ERR_INVALID_ARG, "%s: null pointer", fn);
-  SPA_REQUIRE(aligned16(y) && aligned16(base), SPA_ERR_INVALID_ARG, "%s: y / base not 16-byte aligned", fn);
-  SPA_REQUIRE(dtype == SPA_BF16, SPA_ERR_UNSUPPORTED, "%s: bf16 only (use spa_pack_pair + spa_packed_attention_unpack)", fn);
-  const Scatter sc = {gather_idx, inv_pos, base, y, N, 0, 1, nullptr};
-  return attention_common(fn, q, k, x, q_row_stride, k_row_stride, x_row_stride, cu_seqlens, nullptr, B, N, H, Dh, dtype,
-                          softmax_scale, out, lse, sc, stream, scores);
+  return gated_attention_unpack("spa_gated_attention_unpack", q, k, x, q_row_stride, k_row_stride, x_row_stride, scores,
+                                cu_seqlens, gather_idx, inv_pos, base, B, N, H, Dh, dtype, softmax_scale, out, lse, y, nullptr,
+                                nullptr, stream);
+}
+
+extern "C" int spa_gated_attention_unpack_dvec(const void* q, const void* k, const void* x, int64_t q_row_stride,
+                                               int64_t k_row_stride, int64_t x_row_stride, const float* scores,
+                                               const int32_t* cu_seqlens, const int32_t* gather_idx, const int32_t* inv_pos,
+                                               const void* base, int B, int N, int H, int Dh, int dtype, float softmax_scale,
+                                               void* out, float* lse, void* y, const void* dy, void* workspace,
+                                               size_t workspace_bytes, void* stream) {
+  const char* fn = "spa_gated_attention_unpack_dvec";
+  SPA_REQUIRE(dy && out && lse, SPA_ERR_INVALID_ARG, "%s: null pointer", fn);
+  SPA_REQUIRE(workspace != nullptr && workspace_bytes >= spa_attention_bwd_workspace_bytes(B, N, H, Dh, dtype), SPA_ERR_WORKSPACE,
+              "%s: the workspace of the backward is needed, %zu bytes given", fn, workspace_bytes);
+  return gated_attention_unpack(fn, q, k, x, q_row_stride, k_row_stride, x_row_stride, scores, cu_seqlens, gather_idx, inv_pos,
+                                base, B, N, H, Dh, dtype, softmax_scale, out, lse, y, dy, static_cast<float*>(workspace), stream);
 }
 
 extern "C" int spa_selected_attention_unpack(const void* q, const void* k, const void* v, int64_t q_row_stride,

@@ -67,7 +67,8 @@ const Entry kEntries[] = {
     ENTRY(spa_gate_bwd_straight_through), ENTRY(spa_maxpool2x2), ENTRY(spa_pack), ENTRY(spa_pack_pair),
     ENTRY(spa_pack_shifted), ENTRY(spa_container_segments), ENTRY(spa_packed_attention), ENTRY(spa_packed_attention_running_max),
     ENTRY(spa_packed_attention_unpack), ENTRY(spa_gathered_attention_unpack), ENTRY(spa_selected_attention_unpack),
-    ENTRY(spa_gated_attention_unpack), ENTRY(spa_gated_attention_bwd_tokens), ENTRY(spa_segment_attention_unpack),
+    ENTRY(spa_gated_attention_unpack), ENTRY(spa_gated_attention_bwd_tokens),
+    ENTRY(spa_gated_attention_unpack_dvec), ENTRY(spa_gated_attention_bwd_tokens_dvec), ENTRY(spa_segment_attention_unpack),
     ENTRY(spa_pack_containers), ENTRY(spa_packed_attention_bwd_spread), ENTRY(spa_gated_attention_bwd_tokens_spread),
     ENTRY(spa_gathered_segment_attention_unpack), ENTRY(spa_ceiling_copy), ENTRY(spa_linear_packed),
     ENTRY(spa_linear_packed_scatter), ENTRY(spa_linear_packed_unpack), ENTRY(spa_linear_packed_bwd_input), ENTRY(spa_linear_packed_bwd_weight),

@@ -25,6 +25,15 @@ const Options& options();
 
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+// D of the attention backward from the forward's launch: not where dy shares memory with what that launch writes (dy = y is
+// the gradient of |y|^2 / 2), as it would be read too early.  bytes: of each.
+inline bool d_from_forward(const void* dy, const void* y, const void* out, size_t bytes) {
+  const auto apart = [&](const void* w) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(dy), b = reinterpret_cast<uintptr_t>(w);
+    return a + bytes <= b || b + bytes <= a;
+  };
+  return apart(y) && apart(out);
+}
 inline int elem_size(int dtype) { return dtype == SPA_BF16 ? 2 : 4; }
 
 extern thread_local bool g_group_open;             // a launch group is open on this thread (group.h)

@@ -231,7 +231,12 @@ class TrainPass(_Pass):
         s_fine [B, 4N] f32 with grid = (grid_h, grid_w): the score map of the 2x finer stage of a
         hierarchy; it is max-pooled inside the gate kernel and the pooled map is the s_up of the
         gate backward (no gradient to this stage's gate where the up-scale score won)."""
-        st = self._stages(x, w, qk, labels, dy)
+        return self._all_stages(False, x, w, qk, labels, dy, noise, temperature, s_fine, grid)
+
+    def _all_stages(self, whole, x, w, qk, labels, dy, noise=None, temperature=1.0, s_fine=None, grid=None):
+        # whole: the stages run one after the other on this dy (a caller of single stages may fill it after the forward
+        # pass), so the forward's launch forms the D of the backward
+        st = self._stages(x, w, qk, labels, dy, whole)
         if s_fine is not None:
             if noise is not None:
                 raise ValueError("s_fine and noise together are not wired up")
@@ -253,10 +258,14 @@ class TrainPass(_Pass):
             self.loss, self.dx, self.dw, self.db, self.ws_gate, prepare=True))
         return st
 
-    def _stages(self, x, w, qk, labels, dy) -> List[Tuple[str, Callable[[], None]]]:
+    def _steps(self, x, w, qk, labels, dy):
+        return self._all_stages(self.N > 256, x, w, qk, labels, dy)        # (shorter ones form D where they use it)
+
+    def _stages(self, x, w, qk, labels, dy, whole=False) -> List[Tuple[str, Callable[[], None]]]:
         C = self.C
         B, N, H, Dh = self.B, self.N, self.H, self.Dh
         if self.gated:
+            given = dict(dy=dy, workspace=self.ws_attn) if whole else {}
             t, xt, dqk_tok = qk.view(B * N, 2 * C), x.view(B * N, C), self.dqk.view(B * N, 2 * C)
             return [
                 ("gate_select", spa.spa_gate_select(x, w, self.bias, None, self.tau, self.scores, self.mask, None, prepare=True)),
@@ -264,11 +273,11 @@ class TrainPass(_Pass):
                                               self.inv_pos, self.total, prepare=True)),
                 ("gated_attention_unpack", spa.spa_gated_attention_unpack(
                     t[:, :C], t[:, C:], xt, self.scores, self.cu_seqlens, self.gather_idx, self.inv_pos, None, H, Dh,
-                    self.y, self.out, self.lse, prepare=True)),
+                    self.y, self.out, self.lse, prepare=True, **given)),
                 ("gated_attention_bwd_tokens", spa.spa_gated_attention_bwd_tokens(
                     t[:, :C], t[:, C:], xt, self.scores, self.out, dy, self.lse, self.cu_seqlens, B, N, H, Dh,
                     self.gather_idx, self.inv_pos, dqk_tok[:, :C], dqk_tok[:, C:], self.d_rg.view(B * N, C), self.ws_attn,
-                    prepare=True, spread=True)),
+                    prepare=True, spread=True, y=self.y if whole else None)),
                 ("gate_bwd", spa.spa_gate_bwd(x, w, self.bias, self.scores, None, labels, self.d_rg, True,
                                               self.loss_scale, self.loss, self.dx, self.dw, self.db, self.ws_gate,
                                               prepare=True)),
@@ -645,7 +654,7 @@ class HierarchyPass(_Pass):
 class HierarchyTrainPass(_Pass):
     """Forward + backward of every stage of a hierarchy (TrainPass per stage); from the second
     stage on the gate takes the finer stage's score map (pooled in the gate kernel).  The same step of all
-    stages is one launch group where _groupable says so (seven launches per chain); else all forwards run
+    stages is one launch group where _groupable says so (seven launches per chain, in run() six); else all forwards run
     first (a stage's gate needs the finer stage's scores), then all backwards.
     The score map handed down is treated as a constant by the coarser stage's backward.
 
@@ -665,13 +674,17 @@ class HierarchyTrainPass(_Pass):
                        for (B, gh, gw, C, H, dtype, tau, bias) in self.cfg]
 
     def stages(self, xs, ws, qks, labels, dys) -> List[Tuple[str, Callable[[], None]]]:
+        return self._all_stages(False, xs, ws, qks, labels, dys)
+
+    def _all_stages(self, whole, xs, ws, qks, labels, dys):
+        grouped = not self.concurrent and _groupable(self.cfg) and all(tp.gated for tp in self.passes)
         chains = []
         for i, (tp, cfg) in enumerate(zip(self.passes, self.cfg)):
             with torch.cuda.stream(self.streams[self.stream_of[i]] if self.concurrent else torch.cuda.current_stream()):
-                st = tp.stages(xs[i], ws[i], qks[i], labels[i], dys[i],
-                               s_fine=self.passes[i - 1].scores if i > 0 else None, grid=(cfg[1], cfg[2]))
+                st = tp._all_stages(whole and (grouped or tp.N > 256), xs[i], ws[i], qks[i], labels[i], dys[i],
+                                    s_fine=self.passes[i - 1].scores if i > 0 else None, grid=(cfg[1], cfg[2]))
             chains.append(st)
-        if not self.concurrent and _groupable(self.cfg) and all(tp.gated for tp in self.passes):
+        if grouped:
             # gate, pack, attention + scatter, attention backward, gate backward
             return [(name, spa.group(*(st[j][1] for st in chains))) for j, (name, _) in enumerate(chains[0])]
         chains = [[(f"s{i + 1}.{n}", f) for n, f in st] for i, st in enumerate(chains)]
@@ -682,7 +695,7 @@ class HierarchyTrainPass(_Pass):
 
     def _steps(self, *t):
         n = len(self.cfg)
-        return self.stages(*(t[i * n:(i + 1) * n] for i in range(5)))
+        return self._all_stages(not self.concurrent, *(t[i * n:(i + 1) * n] for i in range(5)))
 
     def run(self, xs, ws, qks, labels, dys):
         n = len(self.cfg)

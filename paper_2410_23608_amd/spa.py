@@ -67,6 +67,8 @@ _SIGNATURES = {
                                               c_int, c_int, c_float, _P, _P, _P, _P]),
     "spa_gated_attention_unpack": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, _P, _P, _P, _P, c_int, c_int, c_int,
                                            c_int, c_int, c_float, _P, _P, _P, _P]),
+    "spa_gated_attention_unpack_dvec": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, _P, _P, _P, _P, c_int, c_int, c_int,
+                                                c_int, c_int, c_float, _P, _P, _P, _P, _P, c_size_t, _P]),
     "spa_selected_attention_unpack": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, _P, c_int, c_int, c_int, c_int,
                                               c_int, c_float, _P, _P]),
     "spa_segment_attention_unpack": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, c_int, c_int, _P, _P, _P, c_int64,
@@ -102,6 +104,9 @@ _SIGNATURES = {
     "spa_gated_attention_bwd_tokens_spread": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, _P, _P, _P, _P, c_int, c_int,
                                                       c_int, c_int, c_int, c_float, _P, _P, c_int64, _P, _P, _P, c_int64,
                                                       c_int64, c_int64, _P, c_size_t, _P]),
+    "spa_gated_attention_bwd_tokens_dvec": (c_int, [_P, _P, _P, c_int64, c_int64, c_int64, _P, _P, _P, _P, _P, c_int, c_int,
+                                                    c_int, c_int, c_int, c_float, _P, _P, c_int64, _P, _P, _P, c_int64,
+                                                    c_int64, c_int64, _P, c_size_t, _P, _P]),
     "spa_gate_bwd_workspace_bytes": (c_size_t, [c_int, c_int, c_int, c_int]),
     "spa_gate_bwd": (c_int, [_P, _P, c_float, _P, _P, _P, _P, c_int, c_float, c_int, c_int, c_int, c_int,
                              _P, _P, _P, _P, _P, c_size_t, _P]),
@@ -615,20 +620,27 @@ def spa_gathered_attention_unpack(q, k, v, cu_seqlens, gather_idx, inv_pos, base
 
 
 def spa_gated_attention_unpack(q, k, x, scores, cu_seqlens, gather_idx, inv_pos, base, H, Dh, y, out=None, lse=None,
-                               softmax_scale=0.0, prepare=False):
-    """spa_gathered_attention_unpack with v = Sigmoid(scores) * x (scores [B,N] f32)."""
-    fn = "spa_gated_attention_unpack"
+                               softmax_scale=0.0, prepare=False, dy=None, workspace=None):
+    """spa_gathered_attention_unpack with v = Sigmoid(scores) * x (scores [B,N] f32).
+    dy, workspace: leaves D of the backward there (spa_gated_attention_unpack_dvec)."""
+    fn = "spa_gated_attention_unpack" if dy is None else "spa_gated_attention_unpack_dvec"
     B, N, C = y.shape
     _, code = _scatter_checks(fn, q, k, x, cu_seqlens, B, N, gather_idx, inv_pos, base, H, Dh, y, out, lse)
     _typed(fn, torch.float32, scores=scores)
     _rows(fn, C, q=(q, B * N), k=(k, B * N), x=(x, B * N))
     _holds(fn, scores=(scores, B * N))
-    _keep = (q, k, x, scores, cu_seqlens, gather_idx, inv_pos, base, y, out, lse,)
+    tail = ()
+    if dy is not None:
+        _features(fn, dy=dy, y=y)
+        _holds(fn, dy=(dy, B * N * C))
+        _contig(dy, workspace)
+        tail = (_ptr(dy), _ptr(workspace), 0 if workspace is None else workspace.numel() * workspace.element_size())
+    _keep = (q, k, x, scores, cu_seqlens, gather_idx, inv_pos, base, y, out, lse, dy, workspace,)
     _contig(scores, cu_seqlens, gather_idx, inv_pos, base, y, out, lse)
-    return _dispatch(lib.spa_gated_attention_unpack,
+    return _dispatch(getattr(lib, fn),
                      (_ptr(q), _ptr(k), _ptr(x), _row_stride(q), _row_stride(k), _row_stride(x), _ptr(scores),
                       _ptr(cu_seqlens), _ptr(gather_idx), _ptr(inv_pos), _ptr(base), B, N, H, Dh, code,
-                      _num(softmax_scale), _ptr(out), _ptr(lse), _ptr(y), _stream(),), _keep, prepare)
+                      _num(softmax_scale), _ptr(out), _ptr(lse), _ptr(y), *tail, _stream(),), _keep, prepare)
 
 
 def spa_selected_attention_unpack(q, k, v, mask, base, H, Dh, y, softmax_scale=0.0, prepare=False):
@@ -888,11 +900,12 @@ def spa_packed_attention_bwd_tokens(q, k, v, out, dy, lse, cu_seqlens, B, max_se
 
 
 def spa_gated_attention_bwd_tokens(q, k, x, scores, out, dy, lse, cu_seqlens, B, max_seqlen, H, Dh, gather_idx, inv_pos,
-                                   dq, dk, d_rg, workspace=None, softmax_scale=0.0, prepare=False, spread=False):
+                                   dq, dk, d_rg, workspace=None, softmax_scale=0.0, prepare=False, spread=False, y=None):
     """The backward of spa_gated_attention_unpack, everything but out and lse at token positions
     (workspace: only for max_seqlen > 256, and in a launch group).  spread: may take the long-segment kernel, given the
-    workspace, where few (image, head) pairs idle the chip (spa_gated_attention_bwd_tokens_spread)."""
-    fn = "spa_gated_attention_bwd_tokens_spread" if spread else "spa_gated_attention_bwd_tokens"
+    workspace, where few (image, head) pairs idle the chip (spa_gated_attention_bwd_tokens_spread).  y (with spread): of the
+    forward call that was given dy and the workspace, D is there (spa_gated_attention_bwd_tokens_dvec)."""
+    fn = "spa_gated_attention_bwd_tokens" + ("_dvec" if y is not None else "_spread" if spread else "")
     C = H * Dh
     rows = dy.numel() // dy.shape[-1]
     code = _features(fn, q=q, k=k, x=x, out=out, dy=dy, dq=dq, dk=dk, d_rg=d_rg)
@@ -903,14 +916,17 @@ def spa_gated_attention_bwd_tokens(q, k, x, scores, out, dy, lse, cu_seqlens, B,
     _rows(fn, C, q=(q, rows), k=(k, rows), x=(x, rows), out=(out, 1), dq=(dq, rows), dk=(dk, rows), d_rg=(d_rg, rows))
     _holds(fn, cu_seqlens=(cu_seqlens, B + 1), lse=(lse, H * B * max_seqlen), gather_idx=(gather_idx, rows),
            inv_pos=(inv_pos, rows), scores=(scores, rows))
-    _keep = (q, k, x, scores, dq, dk, d_rg, out, dy, lse, cu_seqlens, gather_idx, inv_pos, workspace,)
+    if y is not None:
+        _holds(fn, y=(y, rows * C))
+    _keep = (q, k, x, scores, dq, dk, d_rg, out, dy, lse, cu_seqlens, gather_idx, inv_pos, workspace, y,)
     _contig(scores, out, dy, lse, cu_seqlens, gather_idx, inv_pos, workspace)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     return _dispatch(getattr(lib, fn),
                      (_ptr(q), _ptr(k), _ptr(x), _row_stride(q), _row_stride(k), _row_stride(x), _ptr(scores), _ptr(out),
                       _ptr(dy), _ptr(lse), _ptr(cu_seqlens), B, max_seqlen, H, Dh, code, _num(softmax_scale),
                       _ptr(gather_idx), _ptr(inv_pos), rows, _ptr(dq), _ptr(dk), _ptr(d_rg), _row_stride(dq),
-                      _row_stride(dk), _row_stride(d_rg), _ptr(workspace), ws_bytes, _stream(),), _keep, prepare)
+                      _row_stride(dk), _row_stride(d_rg), _ptr(workspace), ws_bytes, *(() if y is None else (_ptr(y),)),
+                      _stream(),), _keep, prepare)
 
 
 def spa_gate_bwd_workspace_bytes(B, N, C, dtype) -> int:
