@@ -86,17 +86,17 @@ int spa_set_option(const char* name, const char* value);
  * counts needed, no scores), spa_pack_pair (with scores), of each operand form of the attention (packed:
  * spa_packed_attention, spa_packed_attention_unpack, spa_segment_attention_unpack; gathered:
  * spa_gathered_attention_unpack, spa_gathered_segment_attention_unpack, spa_selected_attention_unpack; gated:
- * spa_gated_attention_unpack),
- * spa_packed_attention_bwd_tokens / spa_gated_attention_bwd_tokens (which need their workspace here whatever
- * max_seqlen) and spa_gate_bwd (C <= 1024), and one spa_linear_packed_bwd_input with up to two
+ * spa_gated_attention_unpack; gated with D: spa_gated_attention_unpack_dvec), of
+ * spa_packed_attention_bwd_tokens and of spa_gated_attention_bwd_tokens or its _spread and _dvec forms (which need their
+ * workspace here whatever max_seqlen) and spa_gate_bwd (C <= 1024), and one spa_linear_packed_bwd_input with up to two
  * spa_linear_packed_bwd_weight (without gate_scores; one launch unless the input side takes 256 x 256 tiles), check
  * their arguments and are noted;
  * spa_group_end launches them on its stream, step by step in that order: a call sees what calls of earlier steps
  * of the group write, and a pooled gate the scores of the gate called before it.  bf16, head dim 32; for at most 256
  * tokens per image at most 64 images, and no gathered attention.  Any other call, or one outside these limits,
  * returns SPA_ERR_UNSUPPORTED; an error of any call ends the group, nothing is launched, neither of the group nor by
- * the call itself.  Same results as the calls
- * one by one, but for the rounding of the attention backward of short segments (the long-segment kernel serves all).
+ * the call itself.  Same results as the calls one by one, but for the rounding of the attention backward of short
+ * segments (the long-segment kernel serves all).
  */
 int spa_group_begin(void);
 int spa_group_end(void* stream);
@@ -369,7 +369,8 @@ int spa_gated_attention_unpack(const void* q, const void* k, const void* x, int6
  * in the workspace of the backward (>= spa_attention_bwd_workspace_bytes), and spa_gated_attention_bwd_tokens_spread that
  * takes it from there (max_seqlen > 256 or in a launch group; below, it may form D itself) instead of with a launch of its
  * own.  The two calls of a step get the same dy, y, out, B, N = max_seqlen and workspace, and nothing writes dy, out or the
- * workspace between them.  Where dy shares memory with y or out, both form D as the other entry points do.  The same bits.
+ * workspace between them.  dy may share memory with what the forward call, or another call of its launch group, writes (y,
+ * out, lse): D is then formed in a launch of its own after them.  (The backward does not read y.)  The same bits.
  */
 int spa_gated_attention_unpack_dvec(const void* q, const void* k, const void* x, int64_t q_row_stride,
                                     int64_t k_row_stride, int64_t x_row_stride, const float* scores,

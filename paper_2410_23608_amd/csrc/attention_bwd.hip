@@ -489,6 +489,22 @@ template <int DH>
 __global__ void __launch_bounds__(256) attn_bwd_dvec_kernel(const BwdArgs p) {
   bwd_dvec_block<DH>(p, blockIdx.x, gridDim.x);
 }
+static unsigned dvec_blocks(long rows, int H, int Dh) { return (unsigned)std::min<long>((rows * H * (Dh / 8) + 255) / 256, 4096L); }
+void launch_dvec(const void* out, const void* dy, const int32_t* gather_idx, const int32_t* cu, int B, int H, int Dh, long lse_stride,
+                 float* dvec, hipStream_t st) {
+  BwdArgs args = {};
+  args.out = static_cast<const __bf16*>(out);
+  args.dout = static_cast<const __bf16*>(dy);
+  args.tok.gather_idx = gather_idx;
+  args.cu = cu;
+  args.B = B;
+  args.H = H;
+  args.lse_stride = lse_stride;
+  args.dvec = dvec;
+  const dim3 grid(dvec_blocks(lse_stride, H, Dh));
+  if (Dh == 32) hipLaunchKernelGGL((attn_bwd_dvec_kernel<32>), grid, dim3(256), 0, st, args);
+  else hipLaunchKernelGGL((attn_bwd_dvec_kernel<64>), grid, dim3(256), 0, st, args);
+}
 
 // Several calls in one launch (launch groups, head dim 32, gradients at token positions): whatever the segment
 // lengths, the long-segment form (the short one's workgroups have the size of their segments).
@@ -1008,7 +1024,7 @@ static int attention_bwd_common(const char* fn, const void* q, const void* k, co
     SPA_REQUIRE(2 * ((long)H * B + 8) * nblk < 2147483647L, SPA_ERR_INVALID_ARG, "%s: B*H*blocks must be < 2^30", fn);
     const bool resident = nblk <= 4 && live_tiles_apply(H, B);
     const unsigned all = 2 * xcd_grid(nblk, H, B), grid = resident && !group_open() ? std::min(all, (unsigned)bwd_long_slots(Dh)) : all;
-    const unsigned dgrid = (unsigned)std::min<long>(((long)B * max_seqlen * H * (Dh / 8) + 255) / 256, 4096L);
+    const unsigned dgrid = dvec_blocks((long)B * max_seqlen, H, Dh);
     if (group_open()) {
       if (!have_d)
         if (int rc = g_noted_dvec[v_scores != nullptr].add(fn, args, dgrid)) return rc;
@@ -1125,5 +1141,5 @@ extern "C" int spa_gated_attention_bwd_tokens_dvec(const void* q, const void* k,
   return attention_bwd_common(fn, q, k, x, q_row_stride, k_row_stride, x_row_stride, out, dy, lse, cu_seqlens, B,
                               max_seqlen, H, Dh, dtype, softmax_scale, dq, dk, d_rg, dq_row_stride, dk_row_stride,
                               d_rg_row_stride, workspace, workspace_bytes, TokenIO{gather_idx, inv_pos, (long)rows},
-                              stream, true, scores, d_from_forward(dy, y, out, (size_t)B * max_seqlen * H * Dh * 2));
+                              stream, true, scores, true);
 }

@@ -1103,20 +1103,44 @@ attn_fwd_bf16_group_kernel(const Members<FwdArgs> m) {
   }
 }
 
+// Where call w of the same launch writes into the dy of call d (dy = y is the gradient of |y|^2 / 2), the launch cannot form
+// the D of d: it would read dy too early, or while it is written.
+static bool dy_apart(const FwdArgs& d, const FwdArgs& w, int Dh) {
+  const size_t bytes = (size_t)d.lse_stride * d.H * Dh * sizeof(__bf16);
+  const auto apart_from = [&](const void* p, size_t n) { return p == nullptr || apart(d.sc.dy, bytes, p, n); };
+  const size_t rows = (size_t)w.lse_stride * w.H * Dh * sizeof(__bf16);
+  return apart_from(w.sc.y, rows) && apart_from(w.out, rows) && apart_from(w.lse, (size_t)w.lse_stride * w.H * sizeof(float));
+}
+static void launch_dvec_of(const FwdArgs& d, int Dh, hipStream_t st) {
+  launch_dvec(d.out, d.sc.dy, d.sc.gather_idx, d.cu, d.B, d.H, Dh, d.lse_stride, d.sc.dvec, st);
+}
+
 static thread_local Noted<FwdArgs> g_noted[kFwdForms];       // by form
 void group_forget_attention() { for (auto& g : g_noted) g.n = 0; }
 template <int FORM>
-static void flush_form(hipStream_t st) {
-  if (g_noted[FORM].n == 0) return;
+static void flush_form(Noted<FwdArgs>& noted, hipStream_t st) {
+  if (noted.n == 0) return;
   Members<FwdArgs> m;
-  const unsigned blocks = g_noted[FORM].members(m);
+  const unsigned blocks = noted.members(m);
   hipLaunchKernelGGL((attn_fwd_bf16_group_kernel<FORM>), dim3(blocks), dim3(256), 0, st, m);
 }
 int group_flush_attention(hipStream_t st) {
-  flush_form<kFwdPacked>(st);
-  flush_form<kFwdGathered>(st);
-  flush_form<kFwdGated>(st);
-  flush_form<kFwdGatedD>(st);
+  Noted<FwdArgs> with_d, after;                              // D in the launch; in one of its own after them all
+  const Noted<FwdArgs>& d = g_noted[kFwdGatedD];
+  for (int i = 0; i < d.n; ++i) {
+    bool beside = true;
+    for (const auto& g : g_noted)
+      for (int j = 0; j < g.n; ++j) beside = beside && dy_apart(d.a[i], g.a[j], 32);
+    if (int rc = (beside ? with_d : after).add("spa_group_end", d.a[i], d.blocks[i])) return rc;
+  }
+  const int late = after.n;
+  g_noted[kFwdGatedD].n = 0;
+  flush_form<kFwdPacked>(g_noted[kFwdPacked], st);
+  flush_form<kFwdGathered>(g_noted[kFwdGathered], st);
+  flush_form<kFwdGated>(g_noted[kFwdGated], st);
+  flush_form<kFwdGatedD>(with_d, st);
+  flush_form<kFwdGated>(after, st);
+  for (int i = 0; i < late; ++i) launch_dvec_of(after.a[i], 32, st);
   return check_launch("spa_group_end");
 }
 // workgroups of four waves for so many units (8 XCDs)
@@ -1442,7 +1466,8 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
     const float scale_log2 = scale * 1.4426950408889634f;
     FwdArgs args = {(const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (long)q_stride, (long)k_stride, (long)v_stride, v_scores,
                     cu, key_lens, n_max, H, scale_log2, (__bf16*)out, lse, lse_stride, sc, B, 0, 0, 1};
-    const int form = v_scores != nullptr ? (sc.dvec != nullptr ? kFwdGatedD : kFwdGated) : sc.gathered ? kFwdGathered : kFwdPacked;
+    const bool d_after = sc.dvec != nullptr && !group_open() && !dy_apart(args, args, Dh);      // D in a launch of its own
+    const int form = v_scores != nullptr ? (sc.dvec != nullptr && !d_after ? kFwdGatedD : kFwdGated) : sc.gathered ? kFwdGathered : kFwdPacked;
     const auto live = [&] { return key_lens == nullptr && live_tiles_apply(H, B); };
     // the tiled kernel's workgroups: resident together 3 waves per SIMD at head dim 32, 2 at 64
     const auto tiled_grid = [&] {
@@ -1534,6 +1559,7 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
 #undef SPA_ARGS
 #undef SPA_LAUNCH
 #undef SPA_LAUNCH_FORM
+    if (d_after) launch_dvec_of(args, Dh, st);
   }
   return check_launch(fn);
 }
@@ -1607,11 +1633,7 @@ static int gated_attention_unpack(const char* fn, const void* q, const void* k, 
   SPA_REQUIRE(scores && cu_seqlens && gather_idx && inv_pos && y, SPA_ERR_INVALID_ARG, "%s: null pointer", fn);
   SPA_REQUIRE(aligned16(y) && aligned16(base) && aligned16(dy), SPA_ERR_INVALID_ARG, "%s: y / base / dy not 16-byte aligned", fn);
   SPA_REQUIRE(dtype == SPA_BF16, SPA_ERR_UNSUPPORTED, "%s: bf16 only (use spa_pack_pair + spa_packed_attention_unpack)", fn);
-  Scatter sc = {gather_idx, inv_pos, base, y, N, 0, 1, nullptr};
-  if (dy != nullptr && d_from_forward(dy, y, out, (size_t)B * N * H * Dh * 2)) {
-    sc.dy = static_cast<const __bf16*>(dy);
-    sc.dvec = dvec;
-  }
+  const Scatter sc = {gather_idx, inv_pos, base, y, N, 0, 1, nullptr, static_cast<const __bf16*>(dy), dvec};
   return attention_common(fn, q, k, x, q_row_stride, k_row_stride, x_row_stride, cu_seqlens, nullptr, B, N, H, Dh, dtype,
                           softmax_scale, out, lse, sc, stream, scores);
 }

@@ -25,16 +25,15 @@ const Options& options();
 
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-// D of the attention backward from the forward's launch: not where dy shares memory with what that launch writes (dy = y is
-// the gradient of |y|^2 / 2), as it would be read too early.  bytes: of each.
-inline bool d_from_forward(const void* dy, const void* y, const void* out, size_t bytes) {
-  const auto apart = [&](const void* w) {
-    const uintptr_t a = reinterpret_cast<uintptr_t>(dy), b = reinterpret_cast<uintptr_t>(w);
-    return a + bytes <= b || b + bytes <= a;
-  };
-  return apart(y) && apart(out);
+inline bool apart(const void* a, size_t na, const void* b, size_t nb) {      // two ranges of memory share no byte
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x + na <= y || y + nb <= x;
 }
 inline int elem_size(int dtype) { return dtype == SPA_BF16 ? 2 : 4; }
+
+// D_i = <dy_i, out_i> of every (head, packed row) for the attention backward, dy at token positions (attention_bwd.hip)
+void launch_dvec(const void* out, const void* dy, const int32_t* gather_idx, const int32_t* cu, int B, int H, int Dh, long lse_stride,
+                 float* dvec, hipStream_t st);
 
 extern thread_local bool g_group_open;             // a launch group is open on this thread (group.h)
 inline bool group_open() { return g_group_open; }

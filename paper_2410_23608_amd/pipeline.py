@@ -681,7 +681,8 @@ class HierarchyTrainPass(_Pass):
         chains = []
         for i, (tp, cfg) in enumerate(zip(self.passes, self.cfg)):
             with torch.cuda.stream(self.streams[self.stream_of[i]] if self.concurrent else torch.cuda.current_stream()):
-                st = tp._all_stages(whole and (grouped or tp.N > 256), xs[i], ws[i], qks[i], labels[i], dys[i],
+                # (D from the forward's launch in a group alone: stage by stage, a later stage may write this one's dy)
+                st = tp._all_stages(whole and grouped, xs[i], ws[i], qks[i], labels[i], dys[i],
                                     s_fine=self.passes[i - 1].scores if i > 0 else None, grid=(cfg[1], cfg[2]))
             chains.append(st)
         if grouped:
@@ -695,7 +696,7 @@ class HierarchyTrainPass(_Pass):
 
     def _steps(self, *t):
         n = len(self.cfg)
-        return self._all_stages(not self.concurrent, *(t[i * n:(i + 1) * n] for i in range(5)))
+        return self._all_stages(True, *(t[i * n:(i + 1) * n] for i in range(5)))
 
     def run(self, xs, ws, qks, labels, dys):
         n = len(self.cfg)

@@ -904,7 +904,7 @@ def spa_gated_attention_bwd_tokens(q, k, x, scores, out, dy, lse, cu_seqlens, B,
     """The backward of spa_gated_attention_unpack, everything but out and lse at token positions
     (workspace: only for max_seqlen > 256, and in a launch group).  spread: may take the long-segment kernel, given the
     workspace, where few (image, head) pairs idle the chip (spa_gated_attention_bwd_tokens_spread).  y (with spread): of the
-    forward call that was given dy and the workspace, D is there (spa_gated_attention_bwd_tokens_dvec)."""
+    forward call that was given dy and the workspace: D is there (spa_gated_attention_bwd_tokens_dvec)."""
     fn = "spa_gated_attention_bwd_tokens" + ("_dvec" if y is not None else "_spread" if spread else "")
     C = H * Dh
     rows = dy.numel() // dy.shape[-1]

@@ -63,3 +63,38 @@ def test_hierarchy(grids, B, C):
         got.append([t for tp in p.passes for t in _outputs(tp)])
     for g in got[1:]:
         _same(got[0], g)
+
+
+@pytest.mark.parametrize("C", [32, 64])                    # launch groups; heads of 64 columns: stage by stage
+def test_hierarchy_with_dy_in_another_stages_buffers(C):
+    """dy of a stage may lie in what another stage's forward pass writes, whichever of them comes first: it is read after
+    all of them."""
+    from paper_2410_23608_amd.pipeline import HierarchyTrainPass
+    B, H = 3, 1
+    cfg = [(B, 40 >> i, 40 >> i, C << i, H << i, "bf16", 0.5, 0.0) for i in range(2)]
+    xs, ws, qks, labels, dys = [list(t) for t in zip(*(_inputs(B, c[1] * c[2], c[3], i) for i, c in enumerate(cfg)))]
+    p = HierarchyTrainPass(cfg)
+    fine, coarse = p.passes
+    in_y, in_out = (t.view(-1)[-dys[1].numel():].view(dys[1].shape) for t in (fine.y, fine.out))
+    room = torch.zeros(dys[0].numel() + 8, dtype=torch.bfloat16, device="cuda")       # the finer dy around the coarser y
+    coarse.y = room[8:8 + coarse.y.numel()].view(coarse.y.shape)
+    around = torch.zeros_like(dys[1])                                                   # the coarser dy around the finer lse
+    fine.lse = around.view(torch.float32).view(-1)[:fine.lse.numel()].view(fine.lse.shape)
+    cases = [([dys[0], in_y], fine.y), ([dys[0], in_out], fine.out), ([dys[0], around], around),
+             ([room[8:].view(dys[0].shape), dys[1]], room)]
+    for given, written in cases:
+        got = []
+        for i in range(4):                                 # stages, then runs: call by call, recorded, replayed
+            for tp in p.passes:
+                tp.ws_attn.fill_(255)
+            written.fill_(1.0)
+            if i == 0:
+                for _, call in p.stages(xs, ws, qks, labels, given):
+                    call()
+            else:
+                p.run(xs, ws, qks, labels, given)
+            torch.cuda.synchronize()
+            got.append([t for tp in p.passes for t in _outputs(tp)])
+        for g in got[1:]:
+            _same(got[0], g)
+        assert got[0][6].any() and got[0][15].any()        # d_rg of both stages
