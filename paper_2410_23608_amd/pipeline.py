@@ -39,6 +39,10 @@ class _Pass:
     def _steps(self, *inputs):
         return self.stages(*inputs)
 
+    def _own_stages(self, cls):
+        # stages() is that of cls: no subclass or program put another in its place, whose stages a run has to issue
+        return getattr(self.stages, "__func__", None) is cls._as_written
+
     def _issue(self, *inputs):
         plan = self._plan
         if plan is None or not plan(self, *inputs):
@@ -233,6 +237,8 @@ class TrainPass(_Pass):
         gate backward (no gradient to this stage's gate where the up-scale score won)."""
         return self._all_stages(False, x, w, qk, labels, dy, noise, temperature, s_fine, grid)
 
+    _as_written = stages
+
     def _all_stages(self, whole, x, w, qk, labels, dy, noise=None, temperature=1.0, s_fine=None, grid=None):
         # whole: the stages run one after the other on this dy (a caller of single stages may fill it after the forward
         # pass), so the forward's launch forms the D of the backward
@@ -258,8 +264,12 @@ class TrainPass(_Pass):
             self.loss, self.dx, self.dw, self.db, self.ws_gate, prepare=True))
         return st
 
+    def _whole(self, early_d, *inputs, **options):
+        # the stages of a step that runs as a whole, D from the forward's launch where early_d
+        return self._all_stages(early_d, *inputs, **options) if self._own_stages(TrainPass) else self.stages(*inputs, **options)
+
     def _steps(self, x, w, qk, labels, dy):
-        return self._all_stages(self.N > 256, x, w, qk, labels, dy)        # (shorter ones form D where they use it)
+        return self._whole(self.N > 256, x, w, qk, labels, dy)             # (shorter ones form D where they use it)
 
     def _stages(self, x, w, qk, labels, dy, whole=False) -> List[Tuple[str, Callable[[], None]]]:
         C = self.C
@@ -676,14 +686,16 @@ class HierarchyTrainPass(_Pass):
     def stages(self, xs, ws, qks, labels, dys) -> List[Tuple[str, Callable[[], None]]]:
         return self._all_stages(False, xs, ws, qks, labels, dys)
 
+    _as_written = stages
+
     def _all_stages(self, whole, xs, ws, qks, labels, dys):
         grouped = not self.concurrent and _groupable(self.cfg) and all(tp.gated for tp in self.passes)
         chains = []
         for i, (tp, cfg) in enumerate(zip(self.passes, self.cfg)):
             with torch.cuda.stream(self.streams[self.stream_of[i]] if self.concurrent else torch.cuda.current_stream()):
                 # (D from the forward's launch in a group alone: stage by stage, a later stage may write this one's dy)
-                st = tp._all_stages(whole and grouped, xs[i], ws[i], qks[i], labels[i], dys[i],
-                                    s_fine=self.passes[i - 1].scores if i > 0 else None, grid=(cfg[1], cfg[2]))
+                st = tp._whole(whole and grouped, xs[i], ws[i], qks[i], labels[i], dys[i],
+                               s_fine=self.passes[i - 1].scores if i > 0 else None, grid=(cfg[1], cfg[2]))
             chains.append(st)
         if grouped:
             # gate, pack, attention + scatter, attention backward, gate backward
@@ -696,7 +708,8 @@ class HierarchyTrainPass(_Pass):
 
     def _steps(self, *t):
         n = len(self.cfg)
-        return self._all_stages(True, *(t[i * n:(i + 1) * n] for i in range(5)))
+        inputs = [t[i * n:(i + 1) * n] for i in range(5)]
+        return self._all_stages(True, *inputs) if self._own_stages(HierarchyTrainPass) else self.stages(*inputs)
 
     def run(self, xs, ws, qks, labels, dys):
         n = len(self.cfg)
