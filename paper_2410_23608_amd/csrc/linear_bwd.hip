@@ -143,8 +143,11 @@ __device__ __forceinline__ void store_weight_block(const floatx16 (&acc)[2], flo
 // for them).  Tiles of 128 x 128 (four waves of 64 x 64, two workgroups a unit) or, EDGE 256, 256 x 256 (eight of 128 x 64).
 // Addresses that step a pointer instead of a product and a select a load, and sums of the columns by vector additions,
 // took a step of 128 x 128 tiles beside another workgroup from 1.35 to 1.06 us and one of 256 x 256 from 2.0 to 1.7.
-// Measured with the sums, called again and again, 128 | 256, us: 12544 rows, 2304 x 768 62 (72 before) | 58, 3072 x 1024
-// 107 (132) | 86, 1536 x 512 35 | 38; gathered, 768 x 768 31.8 (36) | 37; 6272 rows, 2304 x 768 38.7 | 42.
+// Measured with the sums, called again and again, 128 | 256, us: 12544 rows, 2304 x 768 in as many chunks as each fills the
+// chip with 62 (72 before) | 58, 3072 x 1024 107 (132) | 86, 1536 x 512 35 | 38; gathered, 768 x 768 31.8 (36) | 37; 6272 rows,
+// 2304 x 768 38.7 | 42.  In the chunks of a block's pair (weight_splits), by the rule, half of the rows live | all: 12544 rows,
+// 2304 x 768 43 | 65, 768 x 768 24 | 33, 3072 x 1024 59 | 95, 1024 x 1024 30 | 47; 25088 rows, 768 x 768 34 | 61 (with the
+// chunks of its own 33 | 49: the price of the same bits alone and in a group; the training steps run the pair).
 struct WeightArgs {
   const __bf16* dout;
   const int32_t* dout_idx;
@@ -546,7 +549,6 @@ struct WeightShape {
 struct WeightCall {
   WeightArgs a;
   WeightReduceArgs r;            // r.part_w, r.part_b: the workspace
-  int max_splits;                // that fit in the workspace
   unsigned set(WeightShape s) {  // its workgroups
     a.splits = r.splits = s.splits;
     a.n_tiles = (a.n_out + s.edge - 1) / s.edge;
@@ -576,11 +578,12 @@ static int launch_weight(const char* fn, WeightCall& c, WeightShape shape, hipSt
   return check_launch(fn);
 }
 
-// Number of token chunks with 128 x 128 tiles: (chunk, tile) workgroups for two per compute unit (what
-// is resident at a time), at most 16 chunks (every chunk's partial tiles are written and read once), chunks
-// of at least 256 rows at full capacity, and one chunk (no partial tiles, no second launch) up to 2048
-// rows: at half of them live its 16 steps take as long as 3 steps and the second launch.  The option
-// gemm_splits overrides it (tuning aid).
+// Number of token chunks.  It decides the bits of the result, so it follows from the call alone, whatever stands beside it in
+// a group and whatever the tiles; the option gemm_splits overrides it (tuning aid).
+// With 128 x 128 tiles: (chunk, tile) workgroups for two per compute unit (what is resident at a time), at most 16
+// chunks (every chunk's partial tiles are written and read once), chunks of at least 256 rows at full capacity, and
+// one chunk (no partial tiles, no second launch) up to 2048 rows: at half of them live its 16 steps take as long as 3
+// steps and the second launch.
 static int weight_splits(int M_cap, int K, int N_out) {
   const int env = options().gemm_splits;
   if (env > 0) return env;
@@ -590,42 +593,56 @@ static int weight_splits(int M_cap, int K, int N_out) {
   return (int)std::clamp(std::min(512 / tiles, by_rows), 1L, 16L);
 }
 // With 256 x 256 tiles: a workgroup a unit, chunks of at least 512 rows at full capacity.
-static int weight_splits_big(int M_cap, long tiles) {
+static int weight_splits_big(int M_cap, long tiles, long most) {
   const int env = options().gemm_splits;
   if (env > 0) return env;
   const long by_rows = std::max(M_cap / 512, 1);
-  return (int)std::clamp(std::min(256 / tiles, by_rows), 1L, 16L);
+  return (int)std::clamp(std::min(256 / tiles, by_rows), 1L, most);
 }
+// The weight sides of a block (N_out = K and 3 K) stand in one group.  Up to 2.4e10 multiplications of both they share a
+// launch of 128 x 128 tiles with the input side; beyond, the two alone have one of 256 x 256 tiles, which they fill together
+// with fewer chunks than each by itself (12544 rows, 768 columns: seven; with their sums 84.7 us, as two launches of
+// 128 x 128 tiles and one for the sums 93, before 106; 6272 rows 53 (60)).  More than ten do not pay (a step of 25088 rows, 512
+// columns, 10 | 16: 237.8 | 238.8 us; 32768 rows 279.6 | 284.8).
+constexpr double kPairWork = 2.4e10;
+static double weight_work(int M_cap, int K, int N_out) { return (double)M_cap * K * N_out; }
 // The shape of a call of its own, by what was measured (above weight_gemm_block; half of the capacity live): a step takes
 // 1.1 us in a round of two 128 x 128 workgroups a unit and 1.8 in one of 256 x 256 tiles, launch, first loads and last stores 6
 // and 9 us, and the sums 0.15 us a MB of partial tiles.  Option gemm_tm (tuning aid): 2 | 8 forces 128 x 128 | 256 x 256.
 static WeightShape weight_shape(int M_cap, int K, int N_out) {
   const int cfg = options().gemm_tm;
-  const WeightShape small = {kLbT, weight_splits(M_cap, K, N_out)};
-  const WeightShape big = {256, weight_splits_big(M_cap, gemm_tiles<long>(N_out, K, 256))};
-  if (cfg == 2 || cfg == 8) return cfg == 8 ? big : small;
+  WeightShape small = {kLbT, weight_splits(M_cap, K, N_out)};
+  WeightShape big = {256, weight_splits_big(M_cap, gemm_tiles<long>(N_out, K, 256), 16)};
+  if (N_out == K || N_out == 3 * (long)K) {
+    if (weight_work(M_cap, K, K) + 3 * weight_work(M_cap, K, K) > kPairWork)
+      small.splits = weight_splits_big(M_cap, gemm_tiles<long>(K, K, 256) + gemm_tiles<long>(3L * K, K, 256), 10);
+    big.splits = small.splits;
+  }
   const double mb = 4e-6 * N_out * K;
   const auto steps = [&](int splits) { return (double)((std::max(M_cap / 2, 1) / splits + 63) / 64); };
   const double t_small = 6 + 1.1 * steps(small.splits) * std::ceil(small.splits * small.tiles(N_out, K) / 512.) + 0.15 * mb * small.splits;
   const double t_big = 9 + 1.8 * steps(big.splits) * std::ceil(big.splits * big.tiles(N_out, K) / 256.) + 0.15 * mb * big.splits;
-  return t_big < 0.97 * t_small ? big : small;
+  WeightShape shape = t_big < 0.97 * t_small ? big : small;
+  if (cfg == 2 || cfg == 8) shape.edge = cfg == 8 ? 256 : kLbT;
+  return shape;
 }
 static int weight_max_splits(int M_cap, int K, int N_out) {      // (rows with a gate scale take the small tiles)
   return std::max(weight_splits(M_cap, K, N_out), weight_shape(M_cap, K, N_out).splits);
 }
 
-// Two weight sides of one group in one launch with 256 x 256 tiles: chunks of each, 0 for not.  Together they fill the chip
-// with fewer chunks than each alone: 12544 rows, 768 x 768 gathered and 2304 x 768 in seven chunks, with their sums 84.7 us
-// (two launches of 128 x 128 tiles and one for the sums 93, before 106); 512 columns 46 (55), 6272 rows of 768 columns 53 (60);
-// 1024 columns 149 (150).  From 2.4e10 multiplications at full capacity on: below, BlockTrainPass has them in one launch with
-// the input side, and its results are the same bits whether or not it may run them beside other work.
-static int weight_pair_splits(const WeightCall (&w)[2]) {
+// Two weight sides of a group in one launch of 256 x 256 tiles: those of a block past its line, and others that are as large
+// and fit the chip at a time.
+static bool weights_together(const WeightCall& a, const WeightCall& b) {
   const int cfg = options().gemm_tm;
-  if (cfg == 2) return 0;
-  const long tiles = gemm_tiles<long>(w[0].a.n_out, w[0].a.K, 256) + gemm_tiles<long>(w[1].a.n_out, w[1].a.K, 256);
-  const double work = (double)w[0].a.m_cap * w[0].a.n_out * w[0].a.K + (double)w[1].a.m_cap * w[1].a.n_out * w[1].a.K;
-  if (cfg != 8 && (work <= 2.4e10 || tiles > 256)) return 0;
-  return std::min({weight_splits_big(std::max(w[0].a.m_cap, w[1].a.m_cap), tiles), w[0].max_splits, w[1].max_splits});
+  if (cfg == 2 || cfg == 8) return cfg == 8;
+  long blocks = 0;
+  double work = 0;
+  for (const WeightCall* c : {&a, &b}) {
+    const WeightShape shape = weight_shape(c->a.m_cap, c->a.K, c->a.n_out);
+    blocks += shape.splits * gemm_tiles<long>(c->a.n_out, c->a.K, 256);
+    work += weight_work(c->a.m_cap, c->a.K, c->a.n_out);
+  }
+  return work > kPairWork && blocks <= 256;
 }
 
 static thread_local struct {
@@ -645,7 +662,7 @@ int group_note_rows(const char* fn, const GemmArgs& args, bool big) {
 int group_flush_linear(hipStream_t st) {
   auto& n = g_noted;
   const char* fn = "spa_group_end";
-  const auto small = [&](const WeightCall& c) { return WeightShape{kLbT, weight_splits(c.a.m_cap, c.a.K, c.a.n_out)}; };
+  const auto shape = [&](const WeightCall& c) { return weight_shape(c.a.m_cap, c.a.K, c.a.n_out); };
   if (n.n_rows == 1 && n.n_weight > 0 && !n.big) {
     LinearGroup g;
     g.rows = n.rows;
@@ -653,7 +670,7 @@ int group_flush_linear(hipStream_t st) {
     g.end[0] = (unsigned)((tiles + 7) / 8 * 8);
     unsigned blocks = g.end[0];
     for (int i = 0; i < n.n_weight; ++i) {
-      blocks += n.w[i].set(small(n.w[i]));
+      blocks += n.w[i].set({kLbT, shape(n.w[i]).splits});
       if (i == 0) g.end[1] = blocks;
       g.w[i] = n.w[i].a;
     }
@@ -663,19 +680,18 @@ int group_flush_linear(hipStream_t st) {
   } else {
     if (n.n_rows == 1)
       if (int rc = launch_gemm_rows(fn, n.rows, true, st)) return rc;
-    const int together = n.n_weight == 2 ? weight_pair_splits(n.w) : 0;
-    if (together > 0) {
+    if (n.n_weight == 2 && weights_together(n.w[0], n.w[1])) {
       WeightPair p;
       unsigned blocks = 0;
       for (int i = 0; i < 2; ++i) {
-        blocks += n.w[i].set({256, together});
+        blocks += n.w[i].set({256, shape(n.w[i]).splits});
         if (i == 0) p.end = blocks;
         p.w[i] = n.w[i].a;
       }
       if (int rc = launch_weight_big(fn, p, blocks, st)) return rc;
     } else {
       for (int i = 0; i < n.n_weight; ++i)
-        if (int rc = launch_weight(fn, n.w[i], small(n.w[i]), st)) return rc;
+        if (int rc = launch_weight(fn, n.w[i], shape(n.w[i]), st)) return rc;
     }
   }
   Noted<WeightReduceArgs> reduce;
@@ -788,7 +804,6 @@ extern "C" int spa_linear_packed_bwd_weight(const void* dout, const int32_t* dou
   c.a.K = K;
   c.a.n_out = N_out;
   c.r = {static_cast<const float*>(workspace), nullptr, total, M_cap, 0, (long)N_out * K, N_out, dW, dbias};
-  c.max_splits = weight_max_splits(M_cap, K, N_out);
   if (group_open()) {
     SPA_REQUIRE(g_noted.n_weight < 2, SPA_ERR_UNSUPPORTED, "%s: two weight sides in a group", fn);
     g_noted.w[g_noted.n_weight++] = c;
