@@ -386,7 +386,7 @@ class BlockPass(_Pass):
 
 class BlockTrainPass(_Pass):
     """Forward + backward of one SPA attention block WITH its projections (Section 3.2) and the
-    selection loss (Section 3.3), eleven calls:
+    selection loss (Section 3.3), eleven calls one by one, nine or ten with the weight sides beside other work:
 
       fwd: gate_select(x) -> pack (indices and the gated rows, which the weight side of the backward
            reads) -> QKV projection of the selected, gated tokens -> packed attention -> output
@@ -403,14 +403,16 @@ class BlockTrainPass(_Pass):
 
     overlap_weight_grads (default): nothing downstream in the step reads dW / dbias, so the two weight-side GEMMs run
     beside other work.  In bf16 with B N C^2 <= 6e9 they share one launch with the input side of the QKV projection
-    (a launch group), and their partial sums one more: these GEMMs leave units idle there and every dependent launch
-    costs 4 us, most of it before its first product.  Above that line each of them fills the chip, and they are enqueued
-    on a second HIP stream (default priority) beside the attention backward, the input-side GEMM and the gate backward;
-    events order them after their inputs and the step's last stage joins the streams.  Measured, us a step, one launch /
-    second stream / in order: 32 x 196 x 384 90 / 105-118 / 111, 128 x 196 x 384 173 / 177 / 194, 32 x 196 x 768
-    153 / 159 / 172, 48 images of it 187 / 201 / 203, 56 (6.5e9) 206 / 210 / 230, 64 (7.4e9) 225 / 222 / 248, 80
-    268 / 270 / 286, 96 309 / 302 / 322, 128 406 / 394 / 410.  A second stream that the runtime put on the caller's own
-    hardware queue (it deals streams to four) loses what it should win: 64 images 271, 128 434."""
+    (a launch group, stage projections_bwd), and their partial sums one more: these GEMMs leave units idle there and every
+    dependent launch costs 4 us, most of it before its first product.  Above that line the two fill the chip together: one
+    launch for both and one for their sums (stage projections_bwd_weight), on a second HIP stream (default priority) beside
+    the input-side GEMM and the gate backward; an event orders them after their inputs and the step's last stage
+    (join_streams) joins the streams.  In fp32 each is a stage of its own (out_projection_bwd_weight, beside the attention
+    backward, and qkv_projection_bwd_weight).  overlap_weight_grads=False: every call a launch in order, under those names.
+    Measured, us a step, one launch / second stream (two streams that the runtime dealt) / in order: 32 x 196 x 384
+    93 / 117 / 114, 128 x 196 x 384 175 / 192 / 194, 32 x 196 x 768 156 / 168-176 / 172, 48 images of it 188 / 208 / 203,
+    56 (6.5e9) 203 / 205-216 / 222, 64 (7.4e9) 219 / 219-235 / 237, 80 259 / 253-264 / 278, 96 300 / 302 / 317,
+    128 358 / 344-357 / 381."""
 
     def __init__(self, B: int, N: int, C: int, H: int, dtype: str, tau: float = 0.5, bias: float = 0.0,
                  loss_scale: Optional[float] = None, overlap_weight_grads: bool = True):
@@ -462,17 +464,7 @@ class BlockTrainPass(_Pass):
 
         with torch.cuda.stream(self.side if self.overlap else main):       # prepared calls keep the stream they were made on
             w_o, w_qkv = weight_side()
-            if not self.grouped and p.dtype == torch.bfloat16:
-                weights = [("projections_bwd_weight", spa.group(w_o, w_qkv))]
-            else:
-                weights = [("out_projection_bwd_weight", w_o), ("qkv_projection_bwd_weight", w_qkv)]
-        join = []
-        if self.overlap:                               # (the inputs of both are complete on the main stream)
-            start, done = spa.Event(), spa.Event()
-            calls = [fn for _, fn in weights]
-            weights = [("projections_bwd_weight", spa.chain(start.record(main), start.wait(self.side), *calls,
-                                                            done.record(self.side)))]
-            join = [("join_streams", done.wait(main))]
+            pair = spa.group(w_o, w_qkv) if self.overlap and p.dtype == torch.bfloat16 else None
         forward = [
             ("gate_select", spa.spa_gate_select(x, w, self.bias, None, self.tau, self.scores, self.mask, None,
                                                 prepare=True)),
@@ -496,8 +488,22 @@ class BlockTrainPass(_Pass):
         if self.grouped:
             return forward + [("out_projection_bwd_input", in_o), ("packed_attention_bwd", attention_bwd),
                               ("projections_bwd", spa.group(in_qkv, w_o, w_qkv)), gate_bwd]
-        return forward + [("out_projection_bwd_input", in_o), ("packed_attention_bwd", attention_bwd), *weights,
-                          ("qkv_projection_bwd_input", in_qkv), gate_bwd, *join]
+        join = []
+        if self.overlap:
+            start_o, start_qkv, done = (spa.Event() for _ in range(3))
+
+            def on_side(ev, call):      # inputs of the GEMM are complete on the main stream
+                return spa.chain(ev.record(main), ev.wait(self.side), call)
+
+            join = [("join_streams", spa.chain(done.record(self.side), done.wait(main)))]
+            if pair is not None:
+                return forward + [("out_projection_bwd_input", in_o), ("packed_attention_bwd", attention_bwd),
+                                  ("projections_bwd_weight", on_side(start_qkv, pair)),
+                                  ("qkv_projection_bwd_input", in_qkv), gate_bwd, *join]
+            w_o, w_qkv = on_side(start_o, w_o), on_side(start_qkv, w_qkv)
+        return forward + [
+            ("out_projection_bwd_weight", w_o), ("out_projection_bwd_input", in_o), ("packed_attention_bwd", attention_bwd),
+            ("qkv_projection_bwd_weight", w_qkv), ("qkv_projection_bwd_input", in_qkv), gate_bwd, *join]
 
     def run(self, x, w, W_qkv, b_qkv, W_o, b_o, labels, dy):
         self._issue(x, w, W_qkv, b_qkv, W_o, b_o, labels, dy)

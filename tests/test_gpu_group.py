@@ -99,6 +99,24 @@ def test_block_backward_projections_in_one_launch(mods, B, N, C, H, tm):
         assert torch.equal(getattr(got[0], name), getattr(got[1], name)), name
 
 
+@pytest.mark.parametrize("B,C,dtype,beside,names", [
+    (64, 768, "bf16", False, "owqj"), (2, 64, "bf16", False, "owqj"), (2, 64, "f32", False, "owqj"), (2, 64, "f32", True, "owqj join"),
+    (64, 768, "bf16", True, "pair join"), (2, 64, "bf16", True, "one")])
+def test_stages_of_the_block_backward(mods, B, C, dtype, beside, names):
+    """Each weight side is a stage by name but where bf16 runs them in one launch, and fp32 keeps the output projection's
+    beside the attention backward."""
+    _, pipeline = mods
+    p = pipeline.BlockTrainPass(B, 196, C, C // 32, dtype, overlap_weight_grads=beside)
+    t = lambda *s: torch.zeros(*s, device="cuda", dtype=p.y.dtype)
+    got = [n for n, _ in p.stages(t(B, 196, C), t(C), t(3 * C, C), t(3 * C), t(C, C), t(C),
+                                  torch.zeros(B, 196, dtype=torch.uint8, device="cuda"), t(B, 196, C))][5:]
+    each = ["out_projection_bwd_weight", "out_projection_bwd_input", "packed_attention_bwd", "qkv_projection_bwd_weight",
+            "qkv_projection_bwd_input", "gate_bwd"]
+    want = {"owqj": each, "one": each[1:3] + ["projections_bwd", "gate_bwd"],
+            "pair": each[1:3] + ["projections_bwd_weight"] + each[4:]}[names.split()[0]]
+    assert got == want + (["join_streams"] if "join" in names else [])
+
+
 def test_what_a_group_refuses(mods):
     spa, _ = mods
     x, w = torch.randn(1, 40, 64, device="cuda"), torch.randn(64, device="cuda")
