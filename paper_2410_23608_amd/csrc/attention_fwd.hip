@@ -190,6 +190,11 @@ struct FwdAcc {
   }
 };
 
+// When a group's fragments are read from LDS.  kReadLate: each where a product needs it.  kReadSome: K before the first score
+// product, the first of V before the softmax, the others right after it.  kReadAll: all of V before the softmax, which
+// covers the reads.
+enum FragReads { kReadLate, kReadSome, kReadAll };
+
 // Score sub-tiles of one group of GSB*32 keys: S^T = K Q^T (rows = keys, cols = queries).
 // key0 = first key of the group inside the LDS tile, rem = valid keys of the tile.
 // EARLY: all of its K fragments are read before the first product.
@@ -278,8 +283,8 @@ __device__ __forceinline__ void fwd_exp(const floatx16 (&s)[GSB], int key0, int 
 // The probabilities of a group of GSB*32 keys, then O^T += V^T P^T.  V^T at vbuf (row stride TS), the
 // group's keys at column vcol; TS == 0: V rows as they lie in memory (row stride DH + 8, the group's keys
 // from row vcol), the V^T fragments then come from the transposing LDS read.
-// EARLY: its V^T fragments are read before the softmax, which covers the reads.
-template <int DH, int TS, int GSB, bool FULL, bool EARLY = false>
+// READS: when its V^T fragments are read.
+template <int DH, int TS, int GSB, bool FULL, FragReads READS = kReadLate>
 __device__ __forceinline__ void fwd_softmax_pv(const floatx16 (&s)[GSB], const __bf16* vbuf, int vcol, int key0, int rem,
                                                FwdAcc<DH>& acc, float scale_log2, int l32, int hh) {
   constexpr int DB = DH / 32;
@@ -287,18 +292,20 @@ __device__ __forceinline__ void fwd_softmax_pv(const floatx16 (&s)[GSB], const _
     return TS == 0 ? transposed_frag_rowmajor<DH + 8>(vbuf, d, vcol + sb * 32, mf, l32 + 32 * hh)
                    : transposed_frag<TS == 0 ? 1 : TS>(vbuf, d * 32 + l32, vcol + sb * 32, mf, hh);
   };
-  bf16x8 vf[EARLY ? GSB : 1][2][DB], pb[GSB][2];
-  if constexpr (EARLY) {
+  constexpr int F = 2 * GSB, BEFORE = READS == kReadAll ? F : READS == kReadSome ? 1 : 0;    // (of each 32 columns)
+  bf16x8 vf[READS != kReadLate ? GSB : 1][2][DB], pb[GSB][2];
+  auto read = [&](int from, int to) {
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int sb = 0; sb < GSB; ++sb)
+    for (int f = 0; f < F; ++f)
 #pragma unroll
-      for (int mf = 0; mf < 2; ++mf)
-#pragma unroll
-        for (int d = 0; d < DB; ++d) vf[sb][mf][d] = v_frag(sb, mf, d);
+      for (int d = 0; d < DB; ++d)
+        if (f >= from && f < to) vf[READS != kReadLate ? f >> 1 : 0][f & 1][d] = v_frag(f >> 1, f & 1, d);
     __builtin_amdgcn_sched_barrier(0);
-  }
+  };
+  if constexpr (BEFORE > 0) read(0, BEFORE);
   fwd_exp<DH, GSB, FULL>(s, key0, rem, acc, scale_log2, pb);
+  if constexpr (READS == kReadSome) read(BEFORE, F);
 #pragma unroll
   for (int sb = 0; sb < GSB; ++sb)
     if (FULL || key0 + sb * 32 < rem) {
@@ -306,7 +313,7 @@ __device__ __forceinline__ void fwd_softmax_pv(const floatx16 (&s)[GSB], const _
       for (int mf = 0; mf < 2; ++mf)
 #pragma unroll
         for (int d = 0; d < DB; ++d) {
-          const bf16x8 a = EARLY ? vf[EARLY ? sb : 0][mf][d] : v_frag(sb, mf, d);
+          const bf16x8 a = READS != kReadLate ? vf[READS != kReadLate ? sb : 0][mf][d] : v_frag(sb, mf, d);
           acc.o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[sb][mf], acc.o[d], 0, 0, 0);
         }
     }
@@ -524,10 +531,10 @@ __device__ __forceinline__ void load_q_frags(const __bf16* qrow, bool q_ok, int 
 // double-buffered: while a tile is consumed the next one is in flight from global memory into registers
 // (PairStage), and is written to the other LDS buffer before the single barrier that ends the iteration.  K and V
 // lie in LDS as in memory, the V^T fragments come from the transposing LDS read.
-// A tile of 64 keys takes a lone wave 1430 cycles, 830 of them vector issue: EARLY, all K fragments are read before the first
+// A tile of 64 keys takes a lone wave 1430 cycles, 830 of them vector issue: kReadAll, all K fragments are read before the first
 // product and all V^T fragments before the softmax (read where they are used, each product waits for its own read: 1580).  us
 // a launch, head of 1920 tokens and 32 columns, one workgroup a unit 23.1 -> 21.3; a step of 2 x 4200 tokens, 5-40 %, 8 heads
-// of 32, 23.0 -> 21.7, 8 images 32.7 -> 31.5 (when not: where the kernel is launched).  The scores of the next tile beside the exponentials, from a
+// of 32, 23.0 -> 21.7, 8 images 32.7 -> 31.5 (which form where: where the kernel is launched).  The scores of the next tile beside the exponentials, from a
 // ring of three tiles, without a spill in the loop: 23.1 -> 25.5, 8 images 34.6 -> 39.
 template <int DH, int BN>
 struct TiledLds {
@@ -538,7 +545,7 @@ struct TiledLds {
 constexpr int kTiledBN = 64;
 
 // The workgroup's work on queries [q0, q0 + 32 NW) of head h of segment seg (q0 < seg.nq).
-template <int DH, int NW, bool EARLY, int GATHER>
+template <int DH, int NW, FragReads READS, int GATHER>
 __device__ __forceinline__ void
 tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, const __bf16* __restrict__ q,
                 const __bf16* __restrict__ k, const __bf16* __restrict__ v, long qs, long ks, long vs, int H,
@@ -591,8 +598,8 @@ tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, c
     if (!last) load_tile(kt + BN);
     if (wave_live) {
       floatx16 s[GSB];
-      fwd_scores<DH, RS, GSB, !last, EARLY>(Ks[buf], 0, seg.nk - kt, qf, s, l32, hh);
-      fwd_softmax_pv<DH, 0, GSB, !last, EARLY>(s, Vs[buf], 0, 0, seg.nk - kt, acc, scale_log2, l32, hh);
+      fwd_scores<DH, RS, GSB, !last, READS != kReadLate>(Ks[buf], 0, seg.nk - kt, qf, s, l32, hh);
+      fwd_softmax_pv<DH, 0, GSB, !last, READS>(s, Vs[buf], 0, 0, seg.nk - kt, acc, scale_log2, l32, hh);
     }
     if (!last) store_tile(buf ^ 1, std::bool_constant<decltype(at)::value == kTileBeforeLast>{});
     __syncthreads();
@@ -621,12 +628,12 @@ struct TiledShared {
   int s_cu[2 * kLptMaxB + 1];
   int s_pick;
 };
-template <int DH, int NW, bool EARLY, int GATHER>
+template <int DH, int NW, FragReads READS, int GATHER>
 __device__ __forceinline__ void tiled_block(TiledShared<DH>& sh, const FwdArgs& a, unsigned block, unsigned blocks) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, H = a.H, B = a.B;
   const Scatter& sc = a.sc;
   auto attend = [&](const Segment& seg, int h, int q0) {
-    tiled_attention<DH, NW, EARLY, GATHER>(sh.lds, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, H, a.v_scores, a.scale_log2,
+    tiled_attention<DH, NW, READS, GATHER>(sh.lds, seg, h, q0, a.q, a.k, a.v, a.qs, a.ks, a.vs, H, a.v_scores, a.scale_log2,
                                         a.out, a.lse, a.lse_stride, sc);
   };
   if ((int)block >= a.ntile) {
@@ -678,11 +685,13 @@ __device__ __forceinline__ void tiled_block(TiledShared<DH>& sh, const FwdArgs& 
   if (q0 < seg.nq) attend(seg, tile_id.h, q0);
 }
 
-template <int DH, int NW, bool EARLY, int GATHER>
-__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 2 : EARLY ? 3 : 4)))
+template <int DH, int NW, FragReads READS, int GATHER>
+__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH == 64 || READS == kReadAll ? 3 : 4)))
 attn_fwd_bf16_tiled_kernel(const FwdArgs a) {
   __shared__ TiledShared<DH> sh;
-  tiled_block<DH, NW, EARLY, GATHER>(sh, a, blockIdx.x, gridDim.x);
+  // (at head dim 64 the form that leaves D has no register for an early read: 32 x 400 tokens, 6 heads, a training step, some |
+  // late 62.8 | 61.4 us)
+  tiled_block<DH, NW, DH == 64 && GATHER == kFwdGatedD ? kReadLate : READS, GATHER>(sh, a, blockIdx.x, gridDim.x);
 }
 
 // Short segments.  A work unit is 32 queries of one (image, head); SPLIT waves share it, each taking every SPLIT-th step of
@@ -871,7 +880,7 @@ wave_attention(WaveLds<DH, STEP>* lds, int part, const Segment seg, int h, int q
     } else {
       fwd_scores<DH, RS, NSB, false>(Ks, 0, rem, qf, s, l32, hh);
     }
-    fwd_softmax_pv<DH, 0, NSB, false, KREGS>(s, Vs, 0, 0, rem, acc, scale_log2, l32, hh);
+    fwd_softmax_pv<DH, 0, NSB, false, KREGS ? kReadAll : kReadLate>(s, Vs, 0, 0, rem, acc, scale_log2, l32, hh);
   }
 
   if constexpr (SPLIT > 1)
@@ -1091,7 +1100,7 @@ attn_fwd_bf16_group_kernel(const Members<FwdArgs> m) {
   const MemberBlock mb = work_first(m, blockIdx.x);
   const FwdArgs& a = m.a[mb.s];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (a.ntile > 0) tiled_block<DH, 4, true, FORM>(sh.tiled, a, mb.block, mb.blocks);
+  if (a.ntile > 0) tiled_block<DH, 4, kReadAll, FORM>(sh.tiled, a, mb.block, mb.blocks);
   else if (a.waves == 2) {
     const int j = (mb.block >> 3) * 2 + (wv >> 1);
     if constexpr (FORM == kFwdGathered) mask_unit<DH, STEP, 2>(sh.pair[wv >> 1], a, mb.block & 7, j, wv & 1);
@@ -1550,11 +1559,13 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
       // Early reads take 165 registers at head dim 32, three workgroups a unit, which the walks fill from about 6000 blocks of
       // capacity on: the workgroups that fill rows of y then come last.  us a step late | early, 4200 tokens, 8 heads of 32,
       // 5-40 % and 30-90 % selected: 16 images (4224 blocks) 47.0 | 46.1 and 187 | 183, 24 images 64.7 | 66.6 and 287 | 282,
-      // 32 images, new tensors every step, 102 | 106.  At head dim 64 both run two a unit.
+      // 32 images, new tensors every step, 102 | 106.  At head dim 64 some of the reads are early, as three workgroups a unit
+      // have registers for: late | some | all (two a unit), 10-90 % selected, heads of 64: 23 x 391 tokens, 7 heads, 19.0 |
+      // 18.0 | 18.5, 64 x 400, 12 heads, 46.9 | 46.3 | 54.1, 64 x 1024, 12 heads, 147 | 145 | 161, 32 x 4096, 6 heads, 393 | 393 | 391.
       const bool early = xcd_grid(args.nqb, H, B) <= 5120;
-      if (Dh == 64) SPA_LAUNCH_FORM(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 64, 4, true);
-      else if (early) SPA_LAUNCH_FORM(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 32, 4, true);
-      else SPA_LAUNCH_FORM(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 32, 4, false);
+      if (Dh == 64) SPA_LAUNCH_FORM(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 64, 4, kReadSome);
+      else if (early) SPA_LAUNCH_FORM(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 32, 4, kReadAll);
+      else SPA_LAUNCH_FORM(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 32, 4, kReadLate);
     }
 #undef SPA_ARGS
 #undef SPA_LAUNCH

@@ -1,6 +1,6 @@
-"""Long segments of heads of 32 columns: up to 5120 blocks of capacity the tiles' fragments are read early, above where they
-are used.  The same bits on both sides of the line, for segments that end on and next to tile and block edges, against
-fp32; scores that overflow, in a first tile and in a last one."""
+"""Long segments: up to 5120 blocks of capacity the tiles' fragments are read early at 32 columns a head, above where they are
+used; at 64 some of them are.  The same bits on both sides of the line, for segments that end on and next to tile and
+block edges, against fp32; scores that overflow, in a first tile and in a last one."""
 import pytest
 import torch
 
@@ -8,10 +8,11 @@ pytestmark = pytest.mark.gpu
 LENS = (1, 31, 64, 65, 127, 128, 129, 192, 257, 700)
 
 
+@pytest.mark.parametrize("H,Dh,capacities", [(8, 32, (1280, 1281)), (2, 64, (768, 769))])      # 5120 and 5632 blocks
 @pytest.mark.parametrize("form", ["packed", "gathered", "gated"])
-def test_both_sides_of_the_line(form):
+def test_both_sides_of_the_line(form, H, Dh, capacities):
     from paper_2410_23608_amd import spa
-    B, H, Dh = 64, 8, 32
+    B = 64
     C = H * Dh
     g = torch.Generator(device="cuda")
     g.manual_seed(len(form))
@@ -20,7 +21,7 @@ def test_both_sides_of_the_line(form):
     cu = torch.cat([torch.zeros(1, dtype=torch.long), lens.cumsum(0)])
     T = int(cu[-1])
     got = []
-    for N in (1280, 1281):                                 # 10 and 11 blocks a segment: 5120 and 5632
+    for N in capacities:
         g.manual_seed(7)
         rows = rnd(T, 3 * C)
         rows[int(cu[3]) + 1, C:2 * C] = float("-inf")      # a key whose scores are -inf, inf or NaN: the same on both sides

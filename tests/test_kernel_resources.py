@@ -1,0 +1,46 @@
+"""Registers of the built kernels, from the notes of the code objects in libspa.so: how many workgroups of a kernel a unit
+holds is part of its design, and a spill in a loop is paid on every turn."""
+import re
+import struct
+
+import pytest
+
+from paper_2410_23608_amd import build as spa_build
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    """{demangled enough: (registers, spilled registers, scratch bytes, LDS bytes)}"""
+    msgpack = pytest.importorskip("msgpack")
+    b, out, at = open(spa_build.LIB_PATH, "rb").read(), {}, 0
+    while (at := b.find(b"\x7fELF", at)) >= 0:
+        if b[at + 4] == 2 and struct.unpack_from("<H", b, at + 18)[0] == 224:              # 64 bits, AMD GPU
+            sections, count = struct.unpack_from("<Q", b, at + 40)[0], struct.unpack_from("<H", b, at + 60)[0]
+            for o in (at + sections + 64 * i for i in range(count)):
+                if struct.unpack_from("<I", b, o + 4)[0] == 7:                               # notes
+                    p = at + struct.unpack_from("<Q", b, o + 24)[0]
+                    name, size, kind = struct.unpack_from("<III", b, p)
+                    if kind == 32:                                                           # the metadata
+                        start = p + 12 + (name + 3) // 4 * 4
+                        for k in msgpack.unpackb(b[start:start + size])["amdhsa.kernels"]:
+                            out[k[".name"]] = (k[".vgpr_count"], k[".vgpr_spill_count"], k[".private_segment_fixed_size"],
+                                               k[".group_segment_fixed_size"])
+        at += 4
+    assert len(out) > 100
+    return out
+
+
+def _waves(registers):                                                                       # of a SIMD, 512 registers a lane
+    return 512 // ((registers + 7) // 8 * 8)
+
+
+@pytest.mark.parametrize("pattern,count,waves", [
+    (r"attn_fwd_bf16_tiled_kernelILi64E", 4, 3),
+])
+def test_waves_of_a_simd(kernels, pattern, count, waves):
+    found = {n: k for n, k in kernels.items() if re.search(pattern, n)}
+    assert len(found) == count
+    for name, (registers, spilled, scratch, lds) in found.items():
+        assert _waves(registers) >= waves and spilled == scratch == 0, name
+        if "tiled" in name or "group" in name:                                               # four waves a workgroup
+            assert waves * lds <= 160 * 1024, name
