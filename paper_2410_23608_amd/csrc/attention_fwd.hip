@@ -1478,7 +1478,7 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
     const bool d_after = sc.dvec != nullptr && !group_open() && !dy_apart(args, args, Dh);      // D in a launch of its own
     const int form = v_scores != nullptr ? (sc.dvec != nullptr && !d_after ? kFwdGatedD : kFwdGated) : sc.gathered ? kFwdGathered : kFwdPacked;
     const auto live = [&] { return key_lens == nullptr && live_tiles_apply(H, B); };
-    // the tiled kernel's workgroups: resident together 3 waves per SIMD at head dim 32, 2 at 64
+    // the tiled kernel's workgroups: of those resident together three a unit walk at head dim 32, two at 64, beside the fill
     const auto tiled_grid = [&] {
       args.nqb = (n_max + 127) / 128;
       const long all = xcd_grid(args.nqb, H, B);
@@ -1556,13 +1556,16 @@ static int attention_common(const char* fn, const void* q, const void* k, const 
 #undef SPA_WHOLE
     } else {
       const dim3 grid(tiled_grid());
-      // Early reads take 165 registers at head dim 32, three workgroups a unit, which the walks fill from about 6000 blocks of
-      // capacity on: the workgroups that fill rows of y then come last.  us a step late | early, 4200 tokens, 8 heads of 32,
-      // 5-40 % and 30-90 % selected: 16 images (4224 blocks) 47.0 | 46.1 and 187 | 183, 24 images 64.7 | 66.6 and 287 | 282,
-      // 32 images, new tensors every step, 102 | 106.  At head dim 64 some of the reads are early, as three workgroups a unit
-      // have registers for: late | some | all (two a unit), 10-90 % selected, heads of 64: 23 x 391 tokens, 7 heads, 19.0 |
+      // All reads early take 165 registers at head dim 32, three workgroups a unit.  Up to as many blocks of capacity as these
+      // slots hold; beyond, the fourth workgroup works for the launch itself or for another batch in flight.  us a step with 1 |
+      // 2 | 4 streams, 8 heads of 32, late, then early: 1 x 4200 tokens, 5-40 % selected, 20.7 | 13.4 | 9.9 and 19.9 | 12.0 |
+      // 9.1, 8 x 1024, 10-90 %, (512 blocks) 20.0 | 13.1 | 10.7 and 19.6 | 12.5 | 10.2, 8 x 1600 (832) 28.6 | 19.0 | 16.3
+      // and 28.1 | 19.6 | 16.9, 16 x 1024 (1024) 23.2 | 16.2 | 14.0 and 22.9 | 17.2 | 14.8, 8 x 4200 (2112) 32.3 | 20.9 |
+      // 19.1 and 31.7 | 22.2 | 20.6, 16 x 4200 51.6 | 41.5 | 39.6 and 52.7 | 43.7 | 41.2.
+      // At head dim 64 some of the reads are early, as three workgroups a unit have registers for: late | some | all (two a
+      // unit), 10-90 % selected: 23 x 391 tokens, 7 heads, 19.0 |
       // 18.0 | 18.5, 64 x 400, 12 heads, 46.9 | 46.3 | 54.1, 64 x 1024, 12 heads, 147 | 145 | 161, 32 x 4096, 6 heads, 393 | 393 | 391.
-      const bool early = xcd_grid(args.nqb, H, B) <= 5120;
+      const bool early = xcd_grid(args.nqb, H, B) <= 768;
       if (Dh == 64) SPA_LAUNCH_FORM(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 64, 4, kReadSome);
       else if (early) SPA_LAUNCH_FORM(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 32, 4, kReadAll);
       else SPA_LAUNCH_FORM(attn_fwd_bf16_tiled_kernel, grid, dim3(256), args, 32, 4, kReadLate);

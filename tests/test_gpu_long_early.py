@@ -1,4 +1,4 @@
-"""Long segments: up to 5120 blocks of capacity the tiles' fragments are read early at 32 columns a head, above where they are
+"""Long segments: up to 768 blocks of capacity the tiles' fragments are read early at 32 columns a head, above where they are
 used; at 64 some of them are.  The same bits on both sides of the line, for segments that end on and next to tile and
 block edges, against fp32; scores that overflow, in a first tile and in a last one."""
 import pytest
@@ -8,7 +8,7 @@ pytestmark = pytest.mark.gpu
 LENS = (1, 31, 64, 65, 127, 128, 129, 192, 257, 700)
 
 
-@pytest.mark.parametrize("H,Dh,capacities", [(8, 32, (1280, 1281)), (2, 64, (768, 769))])      # 5120 and 5632 blocks
+@pytest.mark.parametrize("H,Dh,capacities", [(2, 32, (768, 769)), (8, 32, (1280, 1281)), (2, 64, (768, 769))])      # first: 768 and 896 blocks
 @pytest.mark.parametrize("form", ["packed", "gathered", "gated"])
 def test_both_sides_of_the_line(form, H, Dh, capacities):
     from paper_2410_23608_amd import spa

@@ -36,6 +36,8 @@ def _waves(registers):                                                          
 
 @pytest.mark.parametrize("pattern,count,waves", [
     (r"attn_fwd_bf16_tiled_kernelILi64E", 4, 3),
+    (r"attn_fwd_bf16_tiled_kernelILi32E.*FragReadsE0", 4, 4),                                # past 768 blocks
+    (r"attn_fwd_bf16_tiled_kernelILi32E.*FragReadsE2", 4, 3),
 ])
 def test_waves_of_a_simd(kernels, pattern, count, waves):
     found = {n: k for n, k in kernels.items() if re.search(pattern, n)}
