@@ -1087,11 +1087,14 @@ __device__ __forceinline__ MemberBlock work_first(const Members<FwdArgs>& m, uns
   return {s, work[s] + block, all[s]};
 }
 // Four waves a SIMD: the workgroups beyond the three a unit that walk the longest segments are those of the other calls (four
-// stages of 16 x 3136 tokens 40.2 us a step, with three 42.3).
+// stages of 16 x 3136 tokens 40.2 us a step, with three 42.3).  128 registers hold all of a tile's reads early but for gated
+// rows, of which they hold some: all with spills | late | some, a training step of four stages of 16 x 3136 tokens 133.2 | 131.1 |
+// 131.1, of four images 73.8 | 73.8 | 73.4, of one 60.6 | 60.9 | 60.6; forward, all | late, 4 x 3136 30.1 | 31.2.
 template <int FORM>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 attn_fwd_bf16_group_kernel(const Members<FwdArgs> m) {
   constexpr int DH = 32, STEP = 32;
+  constexpr FragReads READS = is_gated(FORM) ? kReadSome : kReadAll;
   __shared__ union {
     TiledShared<DH> tiled;
     MaskLds<DH, STEP, 1> wave[4];
@@ -1100,7 +1103,7 @@ attn_fwd_bf16_group_kernel(const Members<FwdArgs> m) {
   const MemberBlock mb = work_first(m, blockIdx.x);
   const FwdArgs& a = m.a[mb.s];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (a.ntile > 0) tiled_block<DH, 4, kReadAll, FORM>(sh.tiled, a, mb.block, mb.blocks);
+  if (a.ntile > 0) tiled_block<DH, 4, READS, FORM>(sh.tiled, a, mb.block, mb.blocks);
   else if (a.waves == 2) {
     const int j = (mb.block >> 3) * 2 + (wv >> 1);
     if constexpr (FORM == kFwdGathered) mask_unit<DH, STEP, 2>(sh.pair[wv >> 1], a, mb.block & 7, j, wv & 1);

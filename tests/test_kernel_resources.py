@@ -38,6 +38,7 @@ def _waves(registers):                                                          
     (r"attn_fwd_bf16_tiled_kernelILi64E", 4, 3),
     (r"attn_fwd_bf16_tiled_kernelILi32E.*FragReadsE0", 4, 4),                                # past 768 blocks
     (r"attn_fwd_bf16_tiled_kernelILi32E.*FragReadsE2", 4, 3),
+    (r"attn_fwd_bf16_group_kernel", 4, 4),
 ])
 def test_waves_of_a_simd(kernels, pattern, count, waves):
     found = {n: k for n, k in kernels.items() if re.search(pattern, n)}
@@ -46,3 +47,7 @@ def test_waves_of_a_simd(kernels, pattern, count, waves):
         assert _waves(registers) >= waves and spilled == scratch == 0, name
         if "tiled" in name or "group" in name:                                               # four waves a workgroup
             assert waves * lds <= 160 * 1024, name
+
+
+def test_no_kernel_spills(kernels):
+    assert [n for n, k in kernels.items() if k[1] or k[2]] == []
