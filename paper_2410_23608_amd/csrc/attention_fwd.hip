@@ -767,7 +767,9 @@ wave_attention(WaveLds<DH, STEP>* lds, int part, const Segment seg, int h, int q
   // wave's chain.  us a step, before -> now: 64 x 196 tokens, 6 heads of 64, from the mask 15.9 -> 15.3 (128 images 23.4 | 23.4),
   // containers of 49 tokens, 12 heads of 32, 18.5 -> 18.3.  Rows of whole lines are cheaper to load where all SIMDs are busy with
   // products: packed, 128 x 196 tokens, 12 heads of 64, forward and backward, 356.6 -> 360.9, gated, 64 images, 80.6 -> 81.5.
-  constexpr bool KREGS = GATHER == kFwdGathered;
+  // Steps of 64 keys have no registers for it (head dim 64: one wave a SIMD instead of two, 64 x 196 tokens, 6 heads, through
+  // the index 21.1 -> 23.9; head dim 32, 12 heads: two instead of three, 20.0 -> 21.2).
+  constexpr bool KREGS = GATHER == kFwdGathered && STEP == 32;
   if (SPLIT == 1) part = 0;                      // (known here: the loop and the tiles of the one-wave form depend on it)
   __bf16 *Ks = lds[part].Ks, *Vs = lds[part].Vs;
   const long C = (long)H * DH;
