@@ -284,7 +284,7 @@ __device__ __forceinline__ void fwd_exp(const floatx16 (&s)[GSB], int key0, int 
 // group's keys at column vcol; TS == 0: V rows as they lie in memory (row stride DH + 8, the group's keys
 // from row vcol), the V^T fragments then come from the transposing LDS read.
 // READS: when its V^T fragments are read.
-template <int DH, int TS, int GSB, bool FULL, FragReads READS = kReadLate>
+template <int DH, int TS, int GSB, bool FULL, int READS = kReadLate>
 __device__ __forceinline__ void fwd_softmax_pv(const floatx16 (&s)[GSB], const __bf16* vbuf, int vcol, int key0, int rem,
                                                FwdAcc<DH>& acc, float scale_log2, int l32, int hh) {
   constexpr int DB = DH / 32;
@@ -545,7 +545,7 @@ struct TiledLds {
 constexpr int kTiledBN = 64;
 
 // The workgroup's work on queries [q0, q0 + 32 NW) of head h of segment seg (q0 < seg.nq).
-template <int DH, int NW, FragReads READS, int GATHER>
+template <int DH, int NW, int READS, int GATHER>
 __device__ __forceinline__ void
 tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, const __bf16* __restrict__ q,
                 const __bf16* __restrict__ k, const __bf16* __restrict__ v, long qs, long ks, long vs, int H,
@@ -628,7 +628,7 @@ struct TiledShared {
   int s_cu[2 * kLptMaxB + 1];
   int s_pick;
 };
-template <int DH, int NW, FragReads READS, int GATHER>
+template <int DH, int NW, int READS, int GATHER>
 __device__ __forceinline__ void tiled_block(TiledShared<DH>& sh, const FwdArgs& a, unsigned block, unsigned blocks) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, H = a.H, B = a.B;
   const Scatter& sc = a.sc;
@@ -685,7 +685,7 @@ __device__ __forceinline__ void tiled_block(TiledShared<DH>& sh, const FwdArgs& 
   if (q0 < seg.nq) attend(seg, tile_id.h, q0);
 }
 
-template <int DH, int NW, FragReads READS, int GATHER>
+template <int DH, int NW, int READS, int GATHER>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH == 64 || READS == kReadAll ? 3 : 4)))
 attn_fwd_bf16_tiled_kernel(const FwdArgs a) {
   __shared__ TiledShared<DH> sh;
@@ -1096,7 +1096,7 @@ template <int FORM>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 attn_fwd_bf16_group_kernel(const Members<FwdArgs> m) {
   constexpr int DH = 32, STEP = 32;
-  constexpr FragReads READS = is_gated(FORM) ? kReadSome : kReadAll;
+  constexpr int READS = is_gated(FORM) ? kReadSome : kReadAll;
   __shared__ union {
     TiledShared<DH> tiled;
     MaskLds<DH, STEP, 1> wave[4];

@@ -107,10 +107,10 @@ __device__ __forceinline__ void gemm_rows_block(const GemmArgs& p, unsigned char
                                                                                                frag_b, acc, tables);
 
     // epilogue: scale, bias, bf16; the EDGE rows of a row of matrix tiles at a time are parked in its own part of LDS (LDS
-    // operations of a wave complete in order) and leave as whole 16-byte pieces.  The pieces of the residual are
-    // fetched together, pieces past the edge from a valid place (one at a time where they are added, each waits
-    // for memory: the output projection of 64 x 196 tokens of 384 columns 11.4 -> 9.8 us).  With 256 x 256 tiles they are 64
-    // registers beside 128 accumulators: nine or ten registers spill here, and a reload waits for the stores before it.
+    // operations of a wave complete in order) and leave as whole 16-byte pieces.  The pieces of the residual of the
+    // next row of tiles are fetched while this one is added and stored, pieces past the edge from a valid place (one at a
+    // time where they are added, each waits for memory: the output projection of 64 x 196 tokens of 384 columns 11.4 -> 9.8 us;
+    // all together they are 64 registers beside the 128 accumulators of 256 x 256 tiles, and spill).
     constexpr int NC = TN * E, ORS = NC + 8, PIECES = NC / 8, PER_LANE = E * PIECES / 64;
     static_assert(E * PIECES % 64 == 0 && WGM * WGN * 2 * E * ORS <= STAGES * (BM + BN) * kGaK, "output staging fits in the operand buffers");
     auto epilogue = [&](auto with_residual) {

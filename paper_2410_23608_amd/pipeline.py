@@ -608,8 +608,8 @@ def _on_streams(per_stage, streams, stream_of):
 def _groupable(cfg):
     """Stages whose calls can share launches (spa_group_begin).  The limits are those of the grouped kernels: four
     calls a launch; bf16; heads of 32, the one head dim their attention is built for (two of them in one kernel would
-    hold the registers and the LDS of the wider: at head dim 64 the tiled form runs two wavefronts per SIMD, at 32
-    three); 1024 columns (the gate backward holds a row in registers); 64 images (one per lane where the one-wave
+    hold the registers and the LDS of the wider: at head dim 64 the tiled form runs three wavefronts per SIMD, in a group
+    at 32 four); 1024 columns (the gate backward holds a row in registers); 64 images (one per lane where the one-wave
     attention numbers its blocks)."""
     return 2 <= len(cfg) <= 4 and all(c[5] == "bf16" and c[3] == 32 * c[4] and c[3] <= 1024 and c[0] <= 64 for c in cfg)
 

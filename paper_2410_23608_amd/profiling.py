@@ -39,6 +39,7 @@ CHAINS = {
 CHAINS["hierarchy"] = [("gate_pyramid_kernel", "gate_select"), ("pack_index_group_kernel", "pack_indices"),
                        ("attn_fwd_bf16_group_kernel<1>", "gathered_attention_unpack"),      # the forward-only chain
                        ("attn_fwd_bf16_group_kernel<2>", "gated_attention_unpack"),
+                       ("attn_fwd_bf16_group_kernel<3>", "gated_attention_unpack"),
                        ("attn_bwd_dvec_group", "gated_attention_bwd_tokens"), ("attn_bwd_group", "gated_attention_bwd_tokens"),
                        ("gate_bwd_group", "gate_bwd"), ("gate_bwd_reduce_group", "gate_bwd")]
 # a whole bench.py run (every configuration and the extras): calls named by kind only

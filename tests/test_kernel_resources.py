@@ -36,8 +36,8 @@ def _waves(registers):                                                          
 
 @pytest.mark.parametrize("pattern,count,waves", [
     (r"attn_fwd_bf16_tiled_kernelILi64E", 4, 3),
-    (r"attn_fwd_bf16_tiled_kernelILi32E.*FragReadsE0", 4, 4),                                # past 768 blocks
-    (r"attn_fwd_bf16_tiled_kernelILi32E.*FragReadsE2", 4, 3),
+    (r"attn_fwd_bf16_tiled_kernelILi32ELi4ELi0E", 4, 4),                                # past 768 blocks
+    (r"attn_fwd_bf16_tiled_kernelILi32ELi4ELi2E", 4, 3),
     (r"attn_fwd_bf16_group_kernel", 4, 4),
     (r"attn_fwd_bf16_wave_kernelILi1ELi32ELi64ELi[01]E", 2, 3),                              # 64-key steps, in order and gathered
     (r"attn_fwd_bf16_wave_kernelILi1ELi64ELi64ELi[01]E", 2, 2),
