@@ -516,7 +516,7 @@ class ContainerForwardPass(_Pass):
     own image inside its own container; shift = (sh, sw) packs the cyclically shifted map.
 
       gate_select(x) -> packing index and segment list -> attention on the image x container segments, which
-      fetches the rows through the index, + scatter back: three launches (64 x 196 x 384, L = 49: 18.1 us; with
+      fetches the rows through the index, + scatter back: three launches (64 x 196 x 384, L = 49: 17.1 us; with
       packed rows and the list in a launch of its own 23.4; fused_unpack=False: pack_shifted(qkv) and
       container_segments, attention and scatter as separate launches).  No host sync."""
 
