@@ -244,12 +244,15 @@ __device__ __forceinline__ void fwd_scores(const __bf16* kbuf, int key0, int rem
 template <int DH, int GSB, bool FULL>
 __device__ __forceinline__ void fwd_exp(const floatx16 (&s)[GSB], int key0, int rem, FwdAcc<DH>& acc, float scale_log2,
                                         bf16x8 (&pb)[GSB][2]) {
+  // (maximum, not fmaxf: a NaN stays one, so that no operand is canonicalised first, 6 instructions fewer of 145 a tile of 64
+  // keys; us a step, 32 x 4200 tokens, 5-40 %, 8 heads of 32, 85.0 -> 84.4, 8 images 32.2 -> 31.7, 64 x 196 tokens, 6 heads
+  // of 64, 15.2 -> 15.1.  A row with a NaN among its scores is NaN either way.)
   float mx = s[0][0];
 #pragma unroll
   for (int sb = 0; sb < GSB; ++sb)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sb][r]);
-  const float m_new = fmaxf(acc.m, max_across_halves(mx) * scale_log2);
+    for (int r = 0; r < 16; ++r) mx = __builtin_elementwise_maximum(mx, s[sb][r]);
+  const float m_new = __builtin_elementwise_maximum(acc.m, max_across_halves(mx) * scale_log2);
   if (__ballot(m_new != acc.m) != 0) {                 // some query's running max moved: rescale
     const float alpha = __builtin_amdgcn_exp2f(acc.m - m_new);
     acc.l *= alpha;

@@ -102,7 +102,7 @@ __device__ __forceinline__ void swap_halves(float v, float& lo, float& hi) {
 __device__ __forceinline__ float max_across_halves(float v) {
   float lo, hi;
   swap_halves(v, lo, hi);
-  return fmaxf(lo, hi);
+  return __builtin_elementwise_maximum(lo, hi);
 }
 __device__ __forceinline__ float sum_across_halves(float v) {
   float lo, hi;
