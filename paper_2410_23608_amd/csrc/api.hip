@@ -49,9 +49,9 @@ static bool parse_option(Options& o, const char* name, const char* value) {
   } else if (!std::strcmp(name, "attn_bwd_short")) {   // "" | "tiled"
     o.bwd_tiled = v[0] == 't';
   } else if (!std::strcmp(name, "attn_bwd_long")) {    // (one form: any value is taken)
-  } else if (!std::strcmp(name, "gemm_tm")) {          // 0 | 2 | 4 | 6 | 8 | 14
+  } else if (!std::strcmp(name, "gemm_tm")) {          // 0 | 2 | 4 | 6 | 8 | 10 | 14
     const int n = std::atoi(v);
-    if (!(n == 0 || n == 2 || n == 4 || n == 6 || n == 8 || n == 14)) return false;
+    if (!(n == 0 || n == 2 || n == 4 || n == 6 || n == 8 || n == 10 || n == 14)) return false;
     o.gemm_tm = n;
   } else if (!std::strcmp(name, "gemm_splits")) {      // 0 (automatic) .. 16
     const int n = std::atoi(v);

@@ -58,10 +58,10 @@ __device__ __forceinline__ bf16x8 transposed_frag_rowmajor(const __bf16* rows, i
 
 // One wave zeroes columns [0, C) of the unselected rows among rows [r0, r1), or copies them from `from`
 // (same layout) when that is given: the lanes test 64 rows at a time, then the wave writes the rows that
-// need it, a lane per 16-byte chunk, four rows of loads in flight.
+// need it, a lane per 16-byte chunk, U rows of loads in flight.
+template <int U = 4, int PASSES = 1>
 __device__ __forceinline__ void zero_unselected_rows(__bf16* dst, long row_stride, int C, const int32_t* inv_pos, long r0,
                                                      long r1, int lane, const __bf16* from = nullptr) {
-  constexpr int U = 4;
   for (long rb = r0; rb < r1; rb += kWave) {
     const long row = rb + lane;
     uint64_t todo = __ballot(row < r1 && inv_pos[row] < 0);
@@ -72,12 +72,22 @@ __device__ __forceinline__ void zero_unselected_rows(__bf16* dst, long row_strid
         off[u] = todo != 0 ? (rb + __ffsll((unsigned long long)todo) - 1) * row_stride : off[u > 0 ? u - 1 : 0];
         todo &= todo - 1;
       }
-      for (int c = lane; c < C / 8; c += kWave) {
-        bf16x8 v[U];
+      // (rows of a copy in up to PASSES pieces a lane at a time: a wave waits for its stores with its next loads)
+      for (int c = lane; c < C / 8; c += PASSES * kWave) {
+        bf16x8 v[PASSES][U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = from != nullptr ? *reinterpret_cast<const bf16x8*>(from + off[u] + c * 8) : zero_bf16x8();
+        for (int q = 0; q < PASSES; ++q)
+          if (q == 0 || c + q * kWave < C / 8) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) *reinterpret_cast<bf16x8*>(dst + off[u] + c * 8) = v[u];
+            for (int u = 0; u < U; ++u)
+              v[q][u] = from != nullptr ? *reinterpret_cast<const bf16x8*>(from + off[u] + (c + q * kWave) * 8) : zero_bf16x8();
+          }
+#pragma unroll
+        for (int q = 0; q < PASSES; ++q)
+          if (q == 0 || c + q * kWave < C / 8) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) *reinterpret_cast<bf16x8*>(dst + off[u] + (c + q * kWave) * 8) = v[q][u];
+          }
       }
     }
   }

@@ -1,9 +1,9 @@
 // The main loop shared by the projection GEMMs (bf16 MFMA, fp32 accumulation): operand tiles go from
-// memory straight to LDS (global_load_lds, 16 bytes a lane) through a ring of STAGES buffers, so the
+// memory straight to LDS (global_load_lds, 16 bytes a lane) through a ring of two or three buffers, so the
 // loads of the next tiles are in flight without a register, a store or a wait for each other; the only
 // waits are one counted vmcnt and one barrier per 64-deep contraction step.  The barrier stands before the last
 // products of the step before it, whose operands are in registers by then: they cover the first LDS reads of the
-// step, and all STAGES buffers can be filled before the first.
+// step, and all buffers can be filled before the first.
 //
 // What bounds it: 256 x 256, called again and again on all units, a step takes 1.65 us with random operands and 1.14 with
 // zeros (the products alone .93 with either, the loads alone .86, the reads alone .7 | .42 for rows | deep operands): the
@@ -132,17 +132,18 @@ struct DeepBlocks {                  // one block of 64 columns a step of u: a t
 // next_a(u, t) / next_b(u, t): address of the thread's u-th piece of step t (called for t = 0, 1, ... in
 // order, so they may step a pointer).  frag_a(tile, i, kk), frag_b(tile, j, kk): fragments;
 // beside(af): called with the A fragments of every 16 contraction elements; last(): before the last barrier.  All threads
-// call it.  On
-// return nothing is in flight and every wave is past its last read of the buffers.
+// call it.  On return nothing is in flight and every wave is past its last read of the buffers.  SA, SB: steps of A and B in LDS; A may have
+// one more (rows that nobody has fetched yet take longer to come than the other operand, which all units share).
 struct Nothing {
   template <class T> __device__ __forceinline__ void operator()(const T&) const {}
 };
-template <class MF, int A_ELEMS, int B_ELEMS, int NA, int NB, int STAGES, int THREADS, int TM, int TN, int DEPTH = kGaK, class FA,
+template <class MF, int A_ELEMS, int B_ELEMS, int NA, int NB, int SA, int SB, int THREADS, int TM, int TN, int DEPTH = kGaK, class FA,
           class FB, class RA, class RB, class LS, class BS = Nothing>
 __device__ __forceinline__ void gemm_async_loop(__bf16* lds, int nk, FA&& next_a, FB&& next_b, RA&& frag_a, RB&& frag_b,
                                                 typename MF::Acc (&acc)[TM][TN], LS&& last, BS&& beside = BS{}) {
-  constexpr int STAGE = A_ELEMS + B_ELEMS, KK = DEPTH / MF::kDepth, LOADS = NA + NB;
+  constexpr int KK = DEPTH / MF::kDepth, LOADS = NA + NB;
   static_assert(KK % 2 == 0, "the fragments of neighbouring groups take turns");
+  static_assert(SB >= 2 && (SA == SB || SA == SB + 1), "waits by whole groups of loads");
   // Place of a group's fragment reads and loads among its products: RP fragments after each product from the first on,
   // then a load after each.  With one wave a SIMD, or two of workgroups that are not in step, the loads of a step go
   // first (dealt out: 2304 -> 768, 1568 rows, 26 -> 32 us).
@@ -150,21 +151,28 @@ __device__ __forceinline__ void gemm_async_loop(__bf16* lds, int nk, FA&& next_a
   constexpr bool kLoadsFirst = THREADS == 256;
   constexpr int PER_GROUP = P - READS;
   static_assert(READS < P && (kLoadsFirst || LOADS <= KK * PER_GROUP), "every read and every load has its place");
-  const uint32_t wave_dst = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds +
-                            __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 1024;
-  auto issue = [&](int q, int t, int stage) {       // load q of step t
-    const uint32_t a = wave_dst + stage * (STAGE * 2);
-    if (q < NA) load_to_lds(next_a(q, t), a + q * (THREADS * 16));
-    else load_to_lds(next_b(q - NA, t), a + A_ELEMS * 2 + (q - NA) * (THREADS * 16));
-  };
+  // one ring of A and B together, or one of A and one of B behind it
+  constexpr bool kOneRing = SA == SB;
+  constexpr int A_STEP = kOneRing ? A_ELEMS + B_ELEMS : A_ELEMS, B_STEP = kOneRing ? A_STEP : B_ELEMS;
+  static_assert(kOneRing || !kLoadsFirst, "one ring where the loads go first");
+  constexpr int B_FIRST = kOneRing ? A_ELEMS : SA * A_ELEMS;
+  const uint32_t dst_a = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds +
+                         __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 1024;
+  // load q of step t, A's before B's in one ring; in two B's first, they are waited for first
+  auto issue_a = [&](int q, int t, int buf) { load_to_lds(next_a(q, t), dst_a + buf * (A_STEP * 2) + q * (THREADS * 16)); };
+  auto issue_b = [&](int q, int t, int buf) { load_to_lds(next_b(q, t), dst_a + B_FIRST * 2 + buf * (B_STEP * 2) + q * (THREADS * 16)); };
 #pragma unroll
-  for (int s = 0; s < STAGES; ++s)
+  for (int s = 0; s < SA; ++s)
     if (s < nk) {
 #pragma unroll
-      for (int q = 0; q < LOADS; ++q) issue(q, s, s);
+      for (int q = 0; q < (kOneRing ? NA : 0); ++q) issue_a(q, s, s);
+#pragma unroll
+      for (int q = 0; q < (s < SB ? NB : 0); ++q) issue_b(q, s, s);
+#pragma unroll
+      for (int q = 0; q < (kOneRing ? 0 : NA); ++q) issue_a(q, s, s);
     }
   bf16x8 af[2][TM], bfr[2][TN];
-  const __bf16 *a = lds, *b = lds + A_ELEMS;
+  const __bf16 *a = lds, *b = lds + B_FIRST;
   auto read = [&](int kk, int r) {                   // fragment r of group kk: a and b in turn while both last
     const int both = 2 * (TM < TN ? TM : TN);
     const bool is_a = r < both ? r % 2 == 0 : TM > TN;
@@ -172,8 +180,19 @@ __device__ __forceinline__ void gemm_async_loop(__bf16* lds, int nk, FA&& next_a
     if (is_a) af[kk & 1][i] = frag_a(a, i, kk);
     else bfr[kk & 1][i] = frag_b(b, i, kk);
   };
-  // the products of group kk beside the reads of group `next` and the loads of step t from number `from` on
-  auto group = [&](int kk, int next, bool loads, int from, int t, int into) {
+  int buf_a = 0, buf_b = 0, freed_a = 0, freed_b = 0;      // buffers of this step and of the one before it
+  bool more_a = false, more_b = false;                     // the loads that fill the freed buffers exist
+  auto issue = [&](int q, int t) {                         // load q of those that follow step t: A of step t + SA, B of step t + SB
+    if constexpr (kOneRing) {
+      if (more_a) q < NA ? issue_a(q, t + SA, freed_a) : issue_b(q - NA, t + SB, freed_a);
+    } else if (q < NB) {
+      if (more_b) issue_b(q, t + SB, freed_b);
+    } else if (more_a) {
+      issue_a(q - NB, t + SA, freed_a);
+    }
+  };
+  // the products of group kk beside the reads of group `next` and the loads that follow step t from number `from` on
+  auto group = [&](int kk, int next, bool loads, int from, int t) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -185,7 +204,7 @@ __device__ __forceinline__ void gemm_async_loop(__bf16* lds, int nk, FA&& next_a
 #pragma unroll
           for (int r = n * RP; r < (n + 1) * RP && r < R; ++r) read(next, r);
         } else if (!kLoadsFirst && from + n - READS < LOADS) {
-          if (loads) issue(from + n - READS, t, into);
+          if (loads) issue(from + n - READS, t);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -193,7 +212,7 @@ __device__ __forceinline__ void gemm_async_loop(__bf16* lds, int nk, FA&& next_a
     __builtin_amdgcn_sched_barrier(0);
   };
   if (nk > 0) {
-    if (STAGES <= nk) wait_memory<(STAGES - 1) * LOADS>();
+    if (SA <= nk) wait_memory<(SB - 1) * LOADS + (SA - SB) * NA>();
     else wait_memory<0>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -202,32 +221,33 @@ __device__ __forceinline__ void gemm_async_loop(__bf16* lds, int nk, FA&& next_a
     for (int r = 0; r < R; ++r) read(0, r);
     __builtin_amdgcn_sched_barrier(0);
   }
-  int stage = 0, freed = 0;                          // buffers of this step and the one before it
-  bool more = false;                                 // loads of step t + STAGES - 1 are under way
   for (int t = 0; t + 1 < nk; ++t) {
 #pragma unroll
-    for (int kk = 0; kk + 1 < KK; ++kk) group(kk, kk + 1, more, (kk + 1) * PER_GROUP, t + STAGES - 1, freed);
-    // this wave's pieces of step t + 1 have arrived (near the end fewer younger steps are in flight), and its
+    for (int kk = 0; kk + 1 < KK; ++kk) group(kk, kk + 1, true, (kk + 1) * PER_GROUP, t - 1);
+    // this wave's pieces of step t + 1 have arrived (near the end fewer younger ones are in flight), and its
     // reads of step t
-    if (STAGES == 2 || t + STAGES - 1 >= nk) wait_memory<0>();
-    else wait_memory<(STAGES - 2) * LOADS>();
+    if (t + SA - 1 >= nk) wait_memory<0>();
+    else wait_memory<(SB - 2) * LOADS + (SA - SB) * NA>();
     __builtin_amdgcn_s_barrier();                   // and everybody's
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    freed = stage;
-    stage = stage + 1 == STAGES ? 0 : stage + 1;
-    a = lds + stage * STAGE;
-    b = a + A_ELEMS;
-    more = t + STAGES < nk;
-    if (kLoadsFirst && more) {
+    freed_a = buf_a;
+    freed_b = buf_b;
+    buf_a = buf_a + 1 == SA ? 0 : buf_a + 1;
+    buf_b = buf_b + 1 == SB ? 0 : buf_b + 1;
+    a = lds + buf_a * A_STEP;
+    b = kOneRing ? a + B_FIRST : lds + B_FIRST + buf_b * B_STEP;
+    more_a = t + SA < nk;
+    more_b = t + SB < nk;
+    if (kLoadsFirst && more_a) {
 #pragma unroll
-      for (int q = 0; q < LOADS; ++q) issue(q, t + STAGES, freed);
+      for (int q = 0; q < LOADS; ++q) issue(q, t);
     }
-    group(KK - 1, 0, more, 0, t + STAGES, freed);
+    group(KK - 1, 0, true, 0, t);
   }
   if (nk > 0) {
 #pragma unroll
-    for (int kk = 0; kk + 1 < KK; ++kk) group(kk, kk + 1, false, 0, 0, 0);
+    for (int kk = 0; kk + 1 < KK; ++kk) group(kk, kk + 1, false, 0, 0);
   }
   last();
   __syncthreads();

@@ -1,6 +1,7 @@
 // Arguments of the row GEMM shared by the projections and the input side of their backward (linear.hip).
 #pragma once
 
+#include "gemm_shape.h"
 #include "spa_common.h"
 
 namespace spa {
@@ -20,6 +21,7 @@ struct GemmArgs {
   const __bf16* residual;
   const int32_t* inv_pos;        // given: the rows i < zrows of out with inv_pos[i] < 0 are zeroed (copied from residual)
   long zrows;
+  LargeRule rule;                // of the large tiles (set by the launch)
 };
 
 // deep = false: out = A W^T (W [ncols][kc]); true: out = A W (W [kc][ncols]).

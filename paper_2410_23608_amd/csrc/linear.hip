@@ -6,7 +6,7 @@
 // one rounding fewer than multiplying a materialised bf16 r_g.
 //
 // bf16 path: MFMA GEMM on the pipelined loop of gemm_async.h, 64 deep steps, tiles of 128 x 128 (four waves
-// of 64 x 64, two workgroups per unit), 192 x 192 or 256 x 256 (eight waves); the same kernels multiply
+// of 64 x 64, two workgroups per unit), 192 x 192, 256 x 192 or 256 x 256 (eight waves); the same kernels multiply
 // by W as it lies for the input side of the backward (linear_bwd.hip).  With 128 x 128 tiles every flop
 // needs 1/64 byte from L2; the large tiles need two thirds and half of that and win wherever they still fill the chip
 // (gemm_shape.h; what bounds them: gemm_rows.h).  Measured, called again and again: 12544 rows of 768 -> 2304 47 to 49 us =
@@ -51,15 +51,17 @@ linear_f32_kernel(const float* __restrict__ x, const int32_t* __restrict__ gathe
 }
 
 template <bool kScale, bool kDeep>
-static int launch_gemm_rows_tile(const char* fn, const GemmArgs& args, bool big, hipStream_t st) {
+static int launch_gemm_rows_tile(const char* fn, GemmArgs args, bool big, hipStream_t st) {
+  args.rule = large_rule(args.ncols, args.kc, args.residual != nullptr);
   const size_t smem = big ? kGemmBigLds : kGemmSmallLds;
   const long tiles = gemm_tiles<long>(args.m_cap, args.ncols, big ? 192 : 128);     // (no less than with 256)
   SPA_REQUIRE(tiles + 8 < 2147483647L / 2, SPA_ERR_INVALID_ARG, "%s: too many tiles", fn);
   const long tiles8 = (tiles + 7) / 8 * 8;
   const int cfg = options().gemm_tm;
-  const auto large = cfg == 6   ? gemm_rows_big_kernel<kScale, kDeep, 192>
-                     : cfg == 8 ? gemm_rows_big_kernel<kScale, kDeep, 256>
-                                : gemm_rows_big_kernel<kScale, kDeep, 0>;
+  const auto large = cfg == 6    ? gemm_rows_big_kernel<kScale, kDeep, Large::k192>
+                     : cfg == 8  ? gemm_rows_big_kernel<kScale, kDeep, Large::k256>
+                     : cfg == 10 ? gemm_rows_big_kernel<kScale, kDeep, Large::k256x192>
+                                 : gemm_rows_big_kernel<kScale, kDeep, Large::kByRows>;
   const auto kernel = big ? large : gemm_rows_small_kernel<kScale, kDeep>;
   const hipError_t attr = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   SPA_REQUIRE(attr == hipSuccess, SPA_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, smem);
@@ -67,8 +69,8 @@ static int launch_gemm_rows_tile(const char* fn, const GemmArgs& args, bool big,
   return check_launch(fn);
 }
 
-// Option gemm_tm (tuning aid) forces a shape: 2 | 6 | 8 for 128 x 128 | 192 x 192 | 256 x 256, 14 for either large one by
-// the live rows.
+// Option gemm_tm (tuning aid) forces a shape: 2 | 6 | 8 | 10 for 128 x 128 | 192 x 192 | 256 x 256 | 256 x 192, 14 for the
+// large ones by the live rows.
 int launch_gemm_rows(const char* fn, const GemmArgs& args, bool deep, hipStream_t st) {
   const int cfg = options().gemm_tm;
   const bool big = cfg != 0 ? cfg >= 6 : large_tiles(args.m_cap, args.total != nullptr, args.ncols, args.kc);

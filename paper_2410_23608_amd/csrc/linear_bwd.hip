@@ -226,7 +226,7 @@ __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned 
   const bool do_bias = a.part_b != nullptr && w.k0 == 0;
   float colsum = 0.f;
   if ((GI || XI) && nk > 0) index(0);
-  gemm_async_loop<Mfma32, EDGE * DEPTH, EDGE * DEPTH, P::kCount, P::kCount, STAGES, THREADS, TM, 2, DEPTH>(
+  gemm_async_loop<Mfma32, EDGE * DEPTH, EDGE * DEPTH, P::kCount, P::kCount, STAGES, STAGES, THREADS, TM, 2, DEPTH>(
       lds, nk, next_g, next_x, [&](const __bf16* tile, int i, int kk) { return deep_frag<EDGE>(tile, kk, g_block(i), lane); },
       [&](const __bf16* tile, int j, int kk) { return deep_frag<EDGE>(tile, kk, wk + j * 32, lane); }, acc, [] {},
       [&](const bf16x8 (&g)[TM]) {
@@ -285,7 +285,7 @@ __global__ void __launch_bounds__(kLbThreads) __attribute__((amdgpu_waves_per_eu
   extern __shared__ __attribute__((aligned(16))) unsigned char lb_smem[];
   const unsigned block = blockIdx.x;
   if (block < g.end[0]) {
-    gemm_rows_block<Mfma32, false, true, false, 128, 128, 2, 2, 2>(g.rows, lb_smem, block, g.end[0]);
+    gemm_rows_small<false, true>(g.rows, lb_smem, block, g.end[0]);
     return;
   }
   const int s = block >= g.end[1];
