@@ -572,6 +572,16 @@ __host__ __device__ constexpr size_t bwd_short_lds_bytes(int nw) {
   return (size_t)nw * (2 * 32 * (DH + 8) * 2 + 2 * 32 * 4);
 }
 
+// Heaviest image first, but the second workgroup of every unit takes the lightest images: the first 512 workgroups start together, and
+// with images of like length they all load, then all multiply, then all store.  Where two workgroups share a unit (six waves or more)
+// and from 832 (image, head) pairs on; us a training step, by weight alone | so, heads of 64: 64 x 196 tokens, 12 heads (768 pairs) 82.1 | 82.3, 72 images 98.2 | 97.7,
+// 80 106.4 | 103.9, 128 154.4 | 152.7, 64 of 16 heads 105.8 | 102.1, 110 x 169, 12 heads 127.7 | 124.1; 48 x 196 (576 pairs) 68.5 |
+// 73.8; 96 x 100, where four share a unit, 75.6 | 77.1; heads of 32, 100 x 196 85.9 | 86.3.
+__device__ __forceinline__ int staggered_place(int rank, int B, int H) {
+  const int first = 256 / H;                         // images of the first workgroup of every unit
+  return rank < first ? rank : rank < 2 * first ? B - 1 - (rank - first) : rank - first;
+}
+
 template <int DH, bool GATED>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
 attn_bwd_short_bf16_kernel(const BwdArgs p) {
@@ -588,12 +598,13 @@ attn_bwd_short_bf16_kernel(const BwdArgs p) {
   const int H = p.H, B = p.B, h = blockIdx.x % H, rank = blockIdx.x / H;
   const int32_t* cu = p.cu;
   const bool at_tokens = p.tok.gather_idx != nullptr;
-  // heaviest image first (work per segment grows like n^2)
+  // by weight (work per segment grows like n^2)
   int img = rank, start = 0, len = 0;
   if (B > 1 && B <= 8 * kWave) {                     // every wave ranks on its own: no LDS, no barrier
-    const RankedSegment rs = B <= kWave       ? ranked_segment_wave<1>(rank, B, cu, nw)
-                             : B <= 2 * kWave ? ranked_segment_wave<2>(rank, B, cu, nw)
-                                              : ranked_segment_wave<8>(rank, B, cu, nw);
+    const int place = DH == 64 && nw >= 6 && (long)B * H >= 832 ? staggered_place(rank, B, H) : rank;
+    const RankedSegment rs = B <= kWave       ? ranked_segment_wave<1>(place, B, cu, nw)
+                             : B <= 2 * kWave ? ranked_segment_wave<2>(place, B, cu, nw)
+                                              : ranked_segment_wave<8>(place, B, cu, nw);
     img = rs.img;
     start = rs.row0;
     len = rs.len;
