@@ -21,6 +21,8 @@
 // fragments, of whose rows r and r + 8 meet: 8.0; 256 x 256 tiles 3 % slower).
 #pragma once
 
+#include <type_traits>
+
 #include "attn_tiles.h"
 #include "spa_common.h"
 
@@ -129,8 +131,8 @@ struct DeepBlocks {                  // one block of 64 columns a step of u: a t
 
 // acc[i][j] += sum over nk contraction steps of DEPTH of (B fragment j) x (A fragment i): MFMA tiles whose
 // rows are B's index and whose columns are A's.  The wave's block is TM * 32 of A by TN * 32 of B.
-// next_a(u, t) / next_b(u, t): address of the thread's u-th piece of step t (called for t = 0, 1, ... in
-// order, so they may step a pointer).  frag_a(tile, i, kk), frag_b(tile, j, kk): fragments;
+// next_a(u, t, inside) / next_b(u, t, inside): address of the thread's u-th piece of step t (called for t = 0, 1, ... in
+// order, so they may step a pointer; inside: t + 1 < nk).  frag_a(tile, i, kk), frag_b(tile, j, kk): fragments;
 // beside(af): called with the A fragments of every 16 contraction elements; last(): before the last barrier.  All threads
 // call it.  On return nothing is in flight and every wave is past its last read of the buffers.  SA, SB: steps of A and B in LDS; A may have
 // one more (rows that nobody has fetched yet take longer to come than the other operand, which all units share).
@@ -159,17 +161,19 @@ __device__ __forceinline__ void gemm_async_loop(__bf16* lds, int nk, FA&& next_a
   const uint32_t dst_a = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds +
                          __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 1024;
   // load q of step t, A's before B's in one ring; in two B's first, they are waited for first
-  auto issue_a = [&](int q, int t, int buf) { load_to_lds(next_a(q, t), dst_a + buf * (A_STEP * 2) + q * (THREADS * 16)); };
-  auto issue_b = [&](int q, int t, int buf) { load_to_lds(next_b(q, t), dst_a + B_FIRST * 2 + buf * (B_STEP * 2) + q * (THREADS * 16)); };
+  auto issue_a = [&](int q, int t, int buf, auto inside) { load_to_lds(next_a(q, t, inside), dst_a + buf * (A_STEP * 2) + q * (THREADS * 16)); };
+  auto issue_b = [&](int q, int t, int buf, auto inside) {
+    load_to_lds(next_b(q, t, inside), dst_a + B_FIRST * 2 + buf * (B_STEP * 2) + q * (THREADS * 16));
+  };
 #pragma unroll
   for (int s = 0; s < SA; ++s)
     if (s < nk) {
 #pragma unroll
-      for (int q = 0; q < (kOneRing ? NA : 0); ++q) issue_a(q, s, s);
+      for (int q = 0; q < (kOneRing ? NA : 0); ++q) issue_a(q, s, s, std::false_type{});
 #pragma unroll
-      for (int q = 0; q < (s < SB ? NB : 0); ++q) issue_b(q, s, s);
+      for (int q = 0; q < (s < SB ? NB : 0); ++q) issue_b(q, s, s, std::false_type{});
 #pragma unroll
-      for (int q = 0; q < (kOneRing ? 0 : NA); ++q) issue_a(q, s, s);
+      for (int q = 0; q < (kOneRing ? 0 : NA); ++q) issue_a(q, s, s, std::false_type{});
     }
   bf16x8 af[2][TM], bfr[2][TN];
   const __bf16 *a = lds, *b = lds + B_FIRST;
@@ -182,17 +186,19 @@ __device__ __forceinline__ void gemm_async_loop(__bf16* lds, int nk, FA&& next_a
   };
   int buf_a = 0, buf_b = 0, freed_a = 0, freed_b = 0;      // buffers of this step and of the one before it
   bool more_a = false, more_b = false;                     // the loads that fill the freed buffers exist
-  auto issue = [&](int q, int t) {                         // load q of those that follow step t: A of step t + SA, B of step t + SB
+  // load q of those that follow step t: A of step t + SA, B of step t + SB.  inside: all of them exist and none is of the last
+  // step, which may be partial: no test and no branch
+  auto issue = [&](int q, int t, auto inside) {
     if constexpr (kOneRing) {
-      if (more_a) q < NA ? issue_a(q, t + SA, freed_a) : issue_b(q - NA, t + SB, freed_a);
+      if (inside || more_a) q < NA ? issue_a(q, t + SA, freed_a, inside) : issue_b(q - NA, t + SB, freed_a, inside);
     } else if (q < NB) {
-      if (more_b) issue_b(q, t + SB, freed_b);
-    } else if (more_a) {
-      issue_a(q - NB, t + SA, freed_a);
+      if (inside || more_b) issue_b(q, t + SB, freed_b, inside);
+    } else if (inside || more_a) {
+      issue_a(q - NB, t + SA, freed_a, inside);
     }
   };
   // the products of group kk beside the reads of group `next` and the loads that follow step t from number `from` on
-  auto group = [&](int kk, int next, bool loads, int from, int t) {
+  auto group = [&](int kk, int next, bool loads, int from, int t, auto inside) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -204,12 +210,36 @@ __device__ __forceinline__ void gemm_async_loop(__bf16* lds, int nk, FA&& next_a
 #pragma unroll
           for (int r = n * RP; r < (n + 1) * RP && r < R; ++r) read(next, r);
         } else if (!kLoadsFirst && from + n - READS < LOADS) {
-          if (loads) issue(from + n - READS, t);
+          if (loads) issue(from + n - READS, t, inside);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     beside(af[kk & 1]);
     __builtin_amdgcn_sched_barrier(0);
+  };
+  auto step = [&](int t, auto inside) {
+#pragma unroll
+    for (int kk = 0; kk + 1 < KK; ++kk) group(kk, kk + 1, true, (kk + 1) * PER_GROUP, t - 1, inside);
+    // this wave's pieces of step t + 1 have arrived (near the end fewer younger ones are in flight), and its
+    // reads of step t
+    if (SA > 2 && !inside && t + SA - 1 >= nk) wait_memory<0>();
+    else wait_memory<(SB - 2) * LOADS + (SA - SB) * NA>();
+    __builtin_amdgcn_s_barrier();                   // and everybody's
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    freed_a = buf_a;
+    freed_b = buf_b;
+    buf_a = buf_a + 1 == SA ? 0 : buf_a + 1;
+    buf_b = buf_b + 1 == SB ? 0 : buf_b + 1;
+    a = lds + buf_a * A_STEP;
+    b = kOneRing ? a + B_FIRST : lds + B_FIRST + buf_b * B_STEP;
+    more_a = inside || t + SA < nk;
+    more_b = inside || t + SB < nk;
+    if (kLoadsFirst && more_a) {
+#pragma unroll
+      for (int q = 0; q < LOADS; ++q) issue(q, t, inside);
+    }
+    group(KK - 1, 0, true, 0, t, inside);
   };
   if (nk > 0) {
     if (SA <= nk) wait_memory<(SB - 1) * LOADS + (SA - SB) * NA>();
@@ -221,33 +251,13 @@ __device__ __forceinline__ void gemm_async_loop(__bf16* lds, int nk, FA&& next_a
     for (int r = 0; r < R; ++r) read(0, r);
     __builtin_amdgcn_sched_barrier(0);
   }
-  for (int t = 0; t + 1 < nk; ++t) {
-#pragma unroll
-    for (int kk = 0; kk + 1 < KK; ++kk) group(kk, kk + 1, true, (kk + 1) * PER_GROUP, t - 1);
-    // this wave's pieces of step t + 1 have arrived (near the end fewer younger ones are in flight), and its
-    // reads of step t
-    if (t + SA - 1 >= nk) wait_memory<0>();
-    else wait_memory<(SB - 2) * LOADS + (SA - SB) * NA>();
-    __builtin_amdgcn_s_barrier();                   // and everybody's
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-    freed_a = buf_a;
-    freed_b = buf_b;
-    buf_a = buf_a + 1 == SA ? 0 : buf_a + 1;
-    buf_b = buf_b + 1 == SB ? 0 : buf_b + 1;
-    a = lds + buf_a * A_STEP;
-    b = kOneRing ? a + B_FIRST : lds + B_FIRST + buf_b * B_STEP;
-    more_a = t + SA < nk;
-    more_b = t + SB < nk;
-    if (kLoadsFirst && more_a) {
-#pragma unroll
-      for (int q = 0; q < LOADS; ++q) issue(q, t);
-    }
-    group(KK - 1, 0, true, 0, t);
-  }
+  int t = 0;
+  if (nk > 1) step(t++, std::false_type{});
+  for (; t + SA + 1 < nk; ++t) step(t, std::true_type{});
+  for (; t + 1 < nk; ++t) step(t, std::false_type{});
   if (nk > 0) {
 #pragma unroll
-    for (int kk = 0; kk + 1 < KK; ++kk) group(kk, kk + 1, false, 0, 0);
+    for (int kk = 0; kk + 1 < KK; ++kk) group(kk, kk + 1, false, 0, 0, std::false_type{});
   }
   last();
   __syncthreads();

@@ -78,16 +78,16 @@ __device__ __forceinline__ int gemm_rows_tiles(const GemmArgs& p, unsigned char*
     const __bf16* zeros = reinterpret_cast<const __bf16*>(gemm_zeros);
     const long b_step = kDeep ? (long)kGaK * p.ncols : kGaK;
     // the last step may be partial: pieces past the contraction are zero in both operands
-    auto next_a = [&](int u, int t) {
+    auto next_a = [&](int u, int t, auto inside) {
       const __bf16* g = ap[u];
       ap[u] += kGaK;
-      if (k_tail != 0 && t == nk - 1 && a_col >= k_tail) g = zeros;
+      if (!inside && k_tail != 0 && t == nk - 1 && a_col >= k_tail) g = zeros;
       return g;
     };
-    auto next_b = [&](int u, int t) {
+    auto next_b = [&](int u, int t, auto inside) {
       const __bf16* g = bp[u];
       bp[u] += b_step;
-      if (k_tail != 0 && t == nk - 1 && (kDeep ? PB::row(tid, u) : PB::col(tid, u)) >= k_tail) g = zeros;
+      if (!inside && k_tail != 0 && t == nk - 1 && (kDeep ? PB::row(tid, u) : PB::col(tid, u)) >= k_tail) g = zeros;
       return g;
     };
     auto frag_a = [&](const __bf16* tile, int i, int kk) { return rows_frag<MF>(tile, wm + i * E, kk, lane); };

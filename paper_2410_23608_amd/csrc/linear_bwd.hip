@@ -193,23 +193,23 @@ __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned 
   const __bf16* xp = xcol + (XI ? 0 : (long)(w.m_begin + row) * K);
   // the last step may be partial: rows past the end are zero in both operands
   const int tail = rows % DEPTH, partial = tail != 0 ? nk - 1 : -1;
-  auto past = [&](int u, int t, const __bf16* p) {
-    if (t == partial) {
+  auto past = [&](int u, int t, const __bf16* p, auto inside) {
+    if (!inside && t == partial) {
       asm volatile("" : "+v"(p));                    // (a branch: selects in every step cost more than it)
       p = P::row(tid, u) >= tail ? zeros : p;
     }
     return p;
   };
-  auto next_g = [&](int u, int t) {
+  auto next_g = [&](int u, int t, auto inside) {
     const __bf16* p = GI ? gcol + (size_t)(uint32_t)gi[u] * (size_t)ldd : gp;
     if (!GI) gp += (long)P::kRowStep * ldd;          // (a step's pieces are as far apart as the steps')
-    return past(u, t, p);
+    return past(u, t, p, inside);
   };
-  auto next_x = [&](int u, int t) {
+  auto next_x = [&](int u, int t, auto inside) {
     const __bf16* p = XI ? xcol + (size_t)(uint32_t)xi[u] * K : xp;
     if (!XI) xp += (long)P::kRowStep * K;
     if ((GI || XI) && u == P::kCount - 1) index(t + 1);      // (the last address of step t has been formed)
-    return past(u, t, p);
+    return past(u, t, p, inside);
   };
   static_assert(P::kCount * P::kRowStep == DEPTH, "pieces a constant distance apart");
   floatx16 acc[TM][2];
