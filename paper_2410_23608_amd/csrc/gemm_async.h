@@ -1,5 +1,5 @@
 // The main loop shared by the projection GEMMs (bf16 MFMA, fp32 accumulation): operand tiles go from
-// memory straight to LDS (global_load_lds, 16 bytes a lane) through a ring of two or three buffers, so the
+// memory straight to LDS (global_load_lds, 16 bytes a lane) through a ring of two to four buffers, so the
 // loads of the next tiles are in flight without a register, a store or a wait for each other; the only
 // waits are one counted vmcnt and one barrier per 64-deep contraction step.  The barrier stands before the last
 // products of the step before it, whose operands are in registers by then: they cover the first LDS reads of the
@@ -147,8 +147,8 @@ __device__ __forceinline__ void gemm_async_loop(__bf16* lds, int nk, FA&& next_a
   static_assert(KK % 2 == 0, "the fragments of neighbouring groups take turns");
   static_assert(SB >= 2 && (SA == SB || SA == SB + 1), "waits by whole groups of loads");
   // Place of a group's fragment reads and loads among its products: RP fragments after each product from the first on,
-  // then a load after each.  With one wave a SIMD, or two of workgroups that are not in step, the loads of a step go
-  // first (dealt out: 2304 -> 768, 1568 rows, 26 -> 32 us).
+  // then a load after each.  With two buffers and one wave a SIMD, or two of workgroups that are not in step, the loads of a
+  // step go first (dealt out: 2304 -> 768, 1568 rows, 26 -> 32 us).
   constexpr int P = TM * TN, R = TM + TN, RP = (2 * R + P - 1) / P, READS = (R + RP - 1) / RP;
   constexpr bool kLoadsFirst = THREADS == 256;
   constexpr int PER_GROUP = P - READS;

@@ -78,4 +78,12 @@ inline bool large_tiles(int m_cap, bool counted, int ncols, int kc) {      // co
   return big < 1.03 * small;
 }
 
+// 128 x 128 tiles one a unit (gemm_rows_ring_kernel) or two a unit.  One where three quarters of the capacity are no more tiles than
+// units: a second round of single tiles costs more than neighbours that cover each other's waits.  us, one | two a unit: 1152 -> 384, 294
+// tiles of capacity, 6272 rows (147 tiles) 10.9 | 13.9, 11289 rows (267) 21.5 | 19.2; 2304 -> 768 of the same capacity, 3136 rows 17.4 | 25.0;
+// 441 tiles of 384 -> 1152 12.0 | 10.9, 294 of 768 -> 768 16.2 | 14.8.
+inline bool ring_tiles(int m_cap, bool counted, int ncols) {
+  return gemm_tiles<long>(counted ? m_cap - m_cap / 4 : m_cap, ncols, 128) <= 256;
+}
+
 }  // namespace spa
