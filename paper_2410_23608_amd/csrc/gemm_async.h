@@ -133,16 +133,18 @@ struct DeepBlocks {                  // one block of 64 columns a step of u: a t
 // rows are B's index and whose columns are A's.  The wave's block is TM * 32 of A by TN * 32 of B.
 // next_a(u, t, inside) / next_b(u, t, inside): address of the thread's u-th piece of step t (called for t = 0, 1, ... in
 // order, so they may step a pointer; inside: t + 1 < nk).  frag_a(tile, i, kk), frag_b(tile, j, kk): fragments;
-// beside(af): called with the A fragments of every 16 contraction elements; last(): before the last barrier.  All threads
+// beside(af): called with the A fragments of every 16 contraction elements; stepped(t): when acc holds steps 0 .. t, of all but the
+// last; last(): before the last barrier.  All threads
 // call it.  On return nothing is in flight and every wave is past its last read of the buffers.  SA, SB: steps of A and B in LDS; A may have
 // one more (rows that nobody has fetched yet take longer to come than the other operand, which all units share).
 struct Nothing {
   template <class T> __device__ __forceinline__ void operator()(const T&) const {}
 };
 template <class MF, int A_ELEMS, int B_ELEMS, int NA, int NB, int SA, int SB, int THREADS, int TM, int TN, int DEPTH = kGaK, class FA,
-          class FB, class RA, class RB, class LS, class BS = Nothing>
+          class FB, class RA, class RB, class LS, class BS = Nothing, class ST = Nothing>
 __device__ __forceinline__ void gemm_async_loop(__bf16* lds, int nk, FA&& next_a, FB&& next_b, RA&& frag_a, RB&& frag_b,
-                                                typename MF::Acc (&acc)[TM][TN], LS&& last, BS&& beside = BS{}) {
+                                                typename MF::Acc (&acc)[TM][TN], LS&& last, BS&& beside = BS{},
+                                                ST&& stepped = ST{}) {
   constexpr int KK = DEPTH / MF::kDepth, LOADS = NA + NB;
   static_assert(KK % 2 == 0, "the fragments of neighbouring groups take turns");
   static_assert(SB >= 2 && (SA == SB || SA == SB + 1), "waits by whole groups of loads");
@@ -240,6 +242,7 @@ __device__ __forceinline__ void gemm_async_loop(__bf16* lds, int nk, FA&& next_a
       for (int q = 0; q < LOADS; ++q) issue(q, t, inside);
     }
     group(KK - 1, 0, true, 0, t, inside);
+    stepped(t);
   };
   if (nk > 0) {
     if (SA <= nk) wait_memory<(SB - 1) * LOADS + (SA - SB) * NA>();

@@ -156,8 +156,13 @@ struct WeightArgs {
   const __bf16* x;
   const int32_t *x_idx, *total;
   int m_cap, K, n_out, splits, n_tiles, k_tiles;
+  bool fold;                     // the sums of every kFoldSteps steps are added up apart (128 x 128 tiles)
   float *part_w, *part_b;
 };
+// Few chunks are long chains of products into one sum; of a block's sides in one launch the sums of every 256 rows are added up apart.
+// Relative error of dW (2-norm, to 64 bits), 2548 rows of 1024 columns in one chunk 3.05e-7 without, 1.06e-7 so (in four chunks without
+// 1.12e-7), 9800 of 512 in seven 2.26e-7, 1.11e-7 (in ten and sixteen 1.60e-7).  1 us of a step of 103 to 150.
+constexpr int kFoldSteps = 4;
 constexpr size_t weight_lds(int edge, int threads) {        // two steps of both operands, or the staging of the output
   return std::max((size_t)2 * 2 * kLbK * edge * sizeof(__bf16), (size_t)threads / 64 * 32 * 68 * sizeof(float));
 }
@@ -230,6 +235,26 @@ __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned 
   const bool do_bias = a.part_b != nullptr && w.k0 == 0 && (TM > 1 || wkb == 0);
   float colsum = 0.f;
   if ((GI || XI) && nk > 0) index(0);
+  constexpr bool kFold = EDGE == kLbT;                      // (256 x 256 tiles have no registers for a second sum)
+  floatx16 sum[kFold ? TM : 1][2];
+#pragma unroll
+  for (int i = 0; i < (kFold ? TM : 0); ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      sum[i][0][r] = 0.f;
+      sum[i][1][r] = 0.f;
+    }
+  auto fold = [&] {
+#pragma unroll
+    for (int i = 0; i < (kFold ? TM : 0); ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          sum[i][j][r] += acc[i][j][r];
+          acc[i][j][r] = 0.f;
+        }
+  };
   gemm_async_loop<Mfma32, EDGE * DEPTH, EDGE * DEPTH, P::kCount, P::kCount, STAGES, STAGES, THREADS, TM, 2, DEPTH>(
       lds, nk, next_g, next_x, [&](const __bf16* tile, int i, int kk) { return deep_frag<EDGE>(tile, kk, g_block(i), lane); },
       [&](const __bf16* tile, int j, int kk) { return deep_frag<EDGE>(tile, kk, wk + j * 32, lane); }, acc, [] {},
@@ -238,12 +263,16 @@ __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned 
           const floatx8 f = bf16x8_to_float(g[0]);
           colsum += ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
         }
+      },
+      [&](int t) {
+        if (kFold && a.fold && (t + 1) % kFoldSteps == 0) fold();
       });
+  fold();
   static_assert(THREADS / 64 * 32 * 68 * sizeof(float) <= weight_lds(EDGE, THREADS), "output staging fits in the operand stages");
   float* dst = a.part_w + (long)w.split * n_out * K;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
-    store_weight_block(acc[i], reinterpret_cast<float*>(lb_smem) + wv * 32 * 68, dst, w.n0 + g_block(i), w.k0 + wk, n_out, K, lane);
+    store_weight_block(kFold ? sum[kFold ? i : 0] : acc[i], reinterpret_cast<float*>(lb_smem) + wv * 32 * 68, dst, w.n0 + g_block(i), w.k0 + wk, n_out, K, lane);
   if (do_bias) {
     const float s = sum_across_halves(colsum);
     const int n = w.n0 + g_block(0) + l32;
@@ -552,6 +581,7 @@ static int reserve_lds(const char* fn, const void* kernel, size_t bytes) {
 // result, the edge does not.
 struct WeightShape {
   int edge, splits;
+  bool fold = false;
   long tiles(int n_out, int K) const { return gemm_tiles<long>(n_out, K, edge); }
 };
 // A noted or called weight side: the kernel's arguments but for the shape, the sum of its chunks, where the result goes.
@@ -560,6 +590,7 @@ struct WeightCall {
   WeightReduceArgs r;            // r.part_w, r.part_b: the workspace
   unsigned set(WeightShape s) {  // its workgroups
     a.splits = r.splits = s.splits;
+    a.fold = s.fold;
     a.n_tiles = (a.n_out + s.edge - 1) / s.edge;
     a.k_tiles = (a.K + s.edge - 1) / s.edge;
     // one chunk: the tiles are the result; more: partial tiles that the second kernel adds
@@ -610,11 +641,31 @@ static int weight_splits_big(int M_cap, long tiles, long most) {
 }
 // The weight sides of a block (N_out = K and 3 K) stand in one group.  Up to 2.4e10 multiplications of both they share a
 // launch of 128 x 128 tiles with the input side; beyond, the two alone have one of 256 x 256 tiles, which they fill together
-// with fewer chunks than each by itself (12544 rows, 768 columns: seven; with their sums 84.7 us, as two launches of
-// 128 x 128 tiles and one for the sums 93, before 106; 6272 rows 53 (60)).  More than ten do not pay (a step of 25088 rows, 512
+// with fewer chunks than each by itself (12544 live rows, 768 columns: seven; with their sums 84.7 us, as two launches of
+// 128 x 128 tiles and one for the sums 93).  More than ten do not pay (a step of 25088 rows, 512
 // columns, 10 | 16: 237.8 | 238.8 us; 32768 rows 279.6 | 284.8).
 constexpr double kPairWork = 2.4e10;
 static double weight_work(int M_cap, int K, int N_out) { return (double)M_cap * K * N_out; }
+// Their chunks: a chunk more shortens the walk over the rows and writes and reads a partial result more, which come out even where
+// the number is as sqrt(rows) / columns; the factors are those of the best steps measured, with 1 to 16 chunks.  In the one launch, two
+// thirds of that where the workgroups, with the input side at half of the rows live, are then two a unit and no more.  us a training step of
+// a block, with as many as fill the chip | so: 3136 rows of 1024 columns of capacity 136 | 122 (1 chunk), 5096 165 | 150 (1), 3136 of 768
+// 111 | 103 (1), 6272 140 | 132 (2), 9408 167 | 164 (2; 3 169), 4704 of 512 96 | 92.4 (3), 9800 124.5 | 117 (5), 19600 184.5 | 177 (7), 12544
+// of 384 113 | 109.4 (7); past the line 12544 of 768 212 | 200 (5), 18816 275 | 270.5 (6), 7840 of 1024 207.5 | 205 (3), 25088 of 768 the same
+// 7.  Alone, us, 768 x 768: 3136 rows 23 -> 20, 6272 24 -> 24.6, 9408 24 -> 32; 3 x that 24 -> 18, 25 -> 24, 31 -> 31.
+static bool in_one_launch(int M_cap, int C) { return 4 * weight_work(M_cap, C, C) <= kPairWork; }
+static int block_splits(int M_cap, int C, int fill) {
+  if (options().gemm_splits > 0) return fill;
+  if (in_one_launch(M_cap, C)) {
+    const long tiles = gemm_tiles<long>(C, C, kLbT) + gemm_tiles<long>(3L * C, C, kLbT);
+    const long beside = (512 - gemm_tiles<long>(std::max(M_cap / 2, 1), C, kLbT)) / tiles;
+    long best = (long)(std::sqrt(700. * M_cap) / C);
+    if (beside < best && 3 * beside >= 2 * best) best = beside;
+    return (int)std::clamp(best, 1L, (long)fill);
+  }
+  const int most = weight_splits_big(M_cap, gemm_tiles<long>(C, C, 256) + gemm_tiles<long>(3L * C, C, 256), 10);
+  return (int)std::clamp(std::sqrt(1200. * M_cap) / C + 0.5, 1., (double)most);
+}
 // The shape of a call of its own, by what was measured (above weight_gemm_block; half of the capacity live): a step takes
 // 1.1 us in a round of two 128 x 128 workgroups a unit and 1.8 in one of 256 x 256 tiles, launch, first loads and last stores 6
 // and 9 us, and the sums 0.15 us a MB of partial tiles.  Option gemm_tm (tuning aid): 2 | 8 forces 128 x 128 | 256 x 256.
@@ -623,10 +674,10 @@ static WeightShape weight_shape(int M_cap, int K, int N_out) {
   WeightShape small = {kLbT, weight_splits(M_cap, K, N_out)};
   WeightShape big = {256, weight_splits_big(M_cap, gemm_tiles<long>(N_out, K, 256), 16)};
   if (N_out == K || N_out == 3 * (long)K) {
-    if (weight_work(M_cap, K, K) + 3 * weight_work(M_cap, K, K) > kPairWork)
-      small.splits = weight_splits_big(M_cap, gemm_tiles<long>(K, K, 256) + gemm_tiles<long>(3L * K, K, 256), 10);
-    big.splits = small.splits;
+    small.fold = in_one_launch(M_cap, K) && cfg != 2 && cfg != 8 && options().gemm_splits == 0;
+    big.splits = small.splits = block_splits(M_cap, K, small.splits);
   }
+  if (small.fold) return small;
   const double mb = 4e-6 * N_out * K;
   const auto steps = [&](int splits) { return (double)((std::max(M_cap / 2, 1) / splits + 63) / 64); };
   const double t_small = 6 + 1.1 * steps(small.splits) * std::ceil(small.splits * small.tiles(N_out, K) / 512.) + 0.15 * mb * small.splits;
@@ -648,6 +699,7 @@ static bool weights_together(const WeightCall& a, const WeightCall& b) {
   double work = 0;
   for (const WeightCall* c : {&a, &b}) {
     const WeightShape shape = weight_shape(c->a.m_cap, c->a.K, c->a.n_out);
+    if (shape.fold) return false;
     blocks += shape.splits * gemm_tiles<long>(c->a.n_out, c->a.K, 256);
     work += weight_work(c->a.m_cap, c->a.K, c->a.n_out);
   }
@@ -679,7 +731,8 @@ int group_flush_linear(hipStream_t st) {
     g.end[0] = (unsigned)((tiles + 7) / 8 * 8);
     unsigned blocks = g.end[0];
     for (int i = 0; i < n.n_weight; ++i) {
-      blocks += n.w[i].set({kLbT, shape(n.w[i]).splits});
+      const WeightShape own = shape(n.w[i]);
+      blocks += n.w[i].set({kLbT, own.splits, own.fold});
       if (i == 0) g.end[1] = blocks;
       g.w[i] = n.w[i].a;
     }
