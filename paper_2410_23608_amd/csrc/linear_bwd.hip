@@ -639,12 +639,12 @@ static int weight_splits_big(int M_cap, long tiles, long most) {
   const long by_rows = std::max(M_cap / 512, 1);
   return (int)std::clamp(std::min(256 / tiles, by_rows), 1L, most);
 }
-// The weight sides of a block (N_out = K and 3 K) stand in one group.  Up to 2.4e10 multiplications of both they share a
-// launch of 128 x 128 tiles with the input side; beyond, the two alone have one of 256 x 256 tiles, which they fill together
+// The weight sides of a block (N_out = K and 3 K) stand in one group.  Up to 2.92e10 multiplications of both (2.4e10 of more than 24000 rows,
+// whose input side takes large tiles) they share a launch of 128 x 128 tiles with the input side; beyond, the two alone have one of 256 x 256 tiles, which they fill together
 // with fewer chunks than each by itself (12544 live rows, 768 columns: seven; with their sums 84.7 us, as two launches of
 // 128 x 128 tiles and one for the sums 93).  More than ten do not pay (a step of 25088 rows, 512
 // columns, 10 | 16: 237.8 | 238.8 us; 32768 rows 279.6 | 284.8).
-constexpr double kPairWork = 2.4e10;
+constexpr double pair_work(int M_cap) { return M_cap <= 24000 ? 2.92e10 : 2.4e10; }
 static double weight_work(int M_cap, int K, int N_out) { return (double)M_cap * K * N_out; }
 // Their chunks: a chunk more shortens the walk over the rows and writes and reads a partial result more, which come out even where
 // the number is as sqrt(rows) / columns; the factors are those of the best steps measured, with 1 to 16 chunks.  In the one launch, two
@@ -653,7 +653,7 @@ static double weight_work(int M_cap, int K, int N_out) { return (double)M_cap * 
 // 111 | 103 (1), 6272 140 | 132 (2), 9408 167 | 164 (2; 3 169), 4704 of 512 96 | 92.4 (3), 9800 124.5 | 117 (5), 19600 184.5 | 177 (7), 12544
 // of 384 113 | 109.4 (7); past the line 12544 of 768 212 | 200 (5), 18816 275 | 270.5 (6), 7840 of 1024 207.5 | 205 (3), 25088 of 768 the same
 // 7.  Alone, us, 768 x 768: 3136 rows 23 -> 20, 6272 24 -> 24.6, 9408 24 -> 32; 3 x that 24 -> 18, 25 -> 24, 31 -> 31.
-static bool in_one_launch(int M_cap, int C) { return 4 * weight_work(M_cap, C, C) <= kPairWork; }
+static bool in_one_launch(int M_cap, int C) { return 4 * weight_work(M_cap, C, C) <= pair_work(M_cap); }
 static int block_splits(int M_cap, int C, int fill) {
   if (options().gemm_splits > 0) return fill;
   if (in_one_launch(M_cap, C)) {
@@ -703,7 +703,7 @@ static bool weights_together(const WeightCall& a, const WeightCall& b) {
     blocks += shape.splits * gemm_tiles<long>(c->a.n_out, c->a.K, 256);
     work += weight_work(c->a.m_cap, c->a.K, c->a.n_out);
   }
-  return work > kPairWork && blocks <= 256;
+  return work > pair_work(std::max(a.a.m_cap, b.a.m_cap)) && blocks <= 256;
 }
 
 static thread_local struct {
