@@ -159,7 +159,8 @@ struct WeightArgs {
   bool fold;                     // the sums of every kFoldSteps steps are added up apart (128 x 128 tiles)
   float *part_w, *part_b;
 };
-// Few chunks are long chains of products into one sum; of a block's sides in one launch the sums of every 256 rows are added up apart.
+// Few chunks are long chains of products into one sum; of a block's sides in one launch, where they have fewer than fill
+// the chip, the sums of every 256 rows are added up apart.
 // Relative error of dW (2-norm, to 64 bits), 2548 rows of 1024 columns in one chunk 3.05e-7 without, 1.06e-7 so (in four chunks without
 // 1.12e-7), 9800 of 512 in seven 2.26e-7, 1.11e-7 (in ten and sixteen 1.60e-7).  1 us of a step of 103 to 150.
 constexpr int kFoldSteps = 4;
@@ -674,8 +675,9 @@ static WeightShape weight_shape(int M_cap, int K, int N_out) {
   WeightShape small = {kLbT, weight_splits(M_cap, K, N_out)};
   WeightShape big = {256, weight_splits_big(M_cap, gemm_tiles<long>(N_out, K, 256), 16)};
   if (N_out == K || N_out == 3 * (long)K) {
-    small.fold = in_one_launch(M_cap, K) && cfg != 2 && cfg != 8 && options().gemm_splits == 0;
-    big.splits = small.splits = block_splits(M_cap, K, small.splits);
+    const int fill = small.splits;
+    big.splits = small.splits = block_splits(M_cap, K, fill);
+    small.fold = small.splits < fill && in_one_launch(M_cap, K) && cfg != 2 && cfg != 8;
   }
   if (small.fold) return small;
   const double mb = 4e-6 * N_out * K;
