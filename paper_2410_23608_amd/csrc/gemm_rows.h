@@ -24,13 +24,8 @@ __device__ __forceinline__ int gemm_rows_tiles(const GemmArgs& p, unsigned char*
                                       typename std::conditional<E == 16, DeepBlocks<BN, THREADS>, DeepPieces<BN, THREADS>>::type>::type;
   __bf16* lds = reinterpret_cast<__bf16*>(gemm_smem);
   constexpr int NC = TN * E, ORS = NC + 8, PIECES = NC / 8, PER_LANE = E * PIECES / 64, STAGING = WGM * WGN * 2 * E * ORS;
-  // Tables of a tile's bias and output rows.  Two workgroups with three steps of A fill the LDS of a unit: theirs stand behind the
-  // staging, written when the buffers are free.
-  constexpr bool kTablesLate = !LOOP && SA > SB;
-  __shared__ float bias_own[kTablesLate ? 1 : BN];
-  __shared__ int rows_own[kTablesLate ? 1 : BM];
-  float* bias_s = kTablesLate ? reinterpret_cast<float*>(lds + STAGING) : bias_own;
-  int* o_row = kTablesLate ? reinterpret_cast<int*>(lds + STAGING) + BN : rows_own;
+  __shared__ float bias_s[BN];
+  __shared__ int o_row[BM];
   static_assert(E * PIECES % 64 == 0 && STAGING % 8 == 0 && STAGING + 2 * (BM + BN) <= (SA * BM + SB * BN) * kGaK,
                 "output staging and tables fit in the operand buffers");
 
@@ -113,13 +108,7 @@ __device__ __forceinline__ int gemm_rows_tiles(const GemmArgs& p, unsigned char*
 #pragma unroll
         for (int r = 0; r < 4 * MF::kGroups; ++r) acc[i][j][r] = 0.f;
     gemm_async_loop<MF, BM * kGaK, BN * kGaK, PA::kCount, PB::kCount, SA, SB, THREADS, TM, TN>(lds, nk, next_a, next_b, frag_a,
-                                                                                               frag_b, acc, [&] {
-      if (!kTablesLate) tables();
-    });
-    if (kTablesLate) {
-      tables();
-      __syncthreads();
-    }
+                                                                                               frag_b, acc, tables);
 
     // epilogue: scale, bias, bf16; the EDGE rows of a row of matrix tiles at a time are parked in its own part of LDS (LDS
     // operations of a wave complete in order) and leave as whole 16-byte pieces.  The pieces of the residual of the
@@ -189,10 +178,10 @@ __device__ __forceinline__ void gemm_unmapped_rows(const GemmArgs& p, int M, uns
 __device__ __forceinline__ int gemm_live_rows(const GemmArgs& p) { return p.total != nullptr ? min(p.total[0], p.m_cap) : p.m_cap; }
 // 128 x 128 tiles, a workgroup each.  The rows no packed row maps to: shared by the waves of the workgroups without a tile, or by all
 // when those are few.
-template <bool kScale, bool kDeep, int SA, int SB, int THREADS>
+template <bool kScale, bool kDeep, int STEPS, int THREADS>
 __device__ __forceinline__ void gemm_rows_small(const GemmArgs& p, unsigned char* gemm_smem, unsigned block, unsigned blocks) {
   constexpr int NW = THREADS / 64;
-  const int live = gemm_rows_tiles<Mfma32, kScale, kDeep, false, 128, 128, 2, NW / 2, SA, SB>(p, gemm_smem, block, blocks, 0, gemm_live_rows(p));
+  const int live = gemm_rows_tiles<Mfma32, kScale, kDeep, false, 128, 128, 2, NW / 2, STEPS, STEPS>(p, gemm_smem, block, blocks, 0, gemm_live_rows(p));
   if (p.inv_pos == nullptr) return;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, idle = (int)blocks - live;
   const bool by_idle = 4 * idle >= live;
@@ -203,14 +192,14 @@ __device__ __forceinline__ void gemm_rows_small(const GemmArgs& p, unsigned char
   zero_unselected_rows(p.out, p.ldo, p.ncols, p.inv_pos, r0, r1, lane, p.residual);
 }
 
-constexpr size_t gemm_small_lds(int sa, int sb) { return (size_t)(sa + sb) * 128 * kGaK * sizeof(__bf16); }
+constexpr size_t kGemmSmallLds = (size_t)2 * (128 + 128) * kGaK * sizeof(__bf16), kGemmRingLds = 2 * kGemmSmallLds;
 constexpr size_t kGemmBigLds = (size_t)(3 * 192 + 3 * 192) * kGaK * sizeof(__bf16);    // (three of 192 + 192 need less)
 
 // 128 x 128 tiles: four waves of 64 x 64, two workgroups per unit.
 template <bool kScale, bool kDeep>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) gemm_rows_small_kernel(const GemmArgs p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char gemm_smem[];
-  gemm_rows_small<kScale, kDeep, 2, 2, 256>(p, gemm_smem, blockIdx.x, gridDim.x);
+  gemm_rows_small<kScale, kDeep, 2, 256>(p, gemm_smem, blockIdx.x, gridDim.x);
 }
 // 128 x 128 tiles where a unit has one: eight waves of 64 x 32 and four steps of both operands in LDS.  With four waves and two steps
 // a wave alone on its SIMD issues loads, reads and products one after the other (0.6 us a step; the products alone 0.2) and a
@@ -221,7 +210,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) g
 template <bool kScale, bool kDeep>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) gemm_rows_ring_kernel(const GemmArgs p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char gemm_smem[];
-  gemm_rows_small<kScale, kDeep, 4, 4, 512>(p, gemm_smem, blockIdx.x, gridDim.x);
+  gemm_rows_small<kScale, kDeep, 4, 512>(p, gemm_smem, blockIdx.x, gridDim.x);
 }
 
 // Tiles of 256 x 256 (eight waves of 128 x 64), 256 x 192 (eight of 64 x 96) or 192 x 192 (eight of 48 x 96); the fewer accumulators and

@@ -54,7 +54,7 @@ template <bool kScale, bool kDeep>
 static int launch_gemm_rows_tile(const char* fn, GemmArgs args, bool big, hipStream_t st) {
   args.rule = large_rule(args.ncols, args.kc, args.residual != nullptr);
   const bool ring = !big && ring_tiles(args.m_cap, args.total != nullptr, args.ncols);
-  const size_t smem = big ? kGemmBigLds : ring ? gemm_small_lds(4, 4) : gemm_small_lds(2, 2);
+  const size_t smem = big ? kGemmBigLds : ring ? kGemmRingLds : kGemmSmallLds;
   const long tiles = gemm_tiles<long>(args.m_cap, args.ncols, big ? 192 : 128);     // (no less than with 256)
   SPA_REQUIRE(tiles + 8 < 2147483647L / 2, SPA_ERR_INVALID_ARG, "%s: too many tiles", fn);
   const long tiles8 = (tiles + 7) / 8 * 8;

@@ -140,8 +140,7 @@ __device__ __forceinline__ void store_weight_block(const floatx16 (&acc)[2], flo
 // workgroups of the first k tile).  Both operands have the contraction (the tokens) down their rows and come through the
 // ring of gemm_async.h, rows of zeros past the chunk's end.  GI / XI: rows of g / x are named by an index array, read one
 // step ahead of the loads that use it, without a branch (each branch made the compiler copy indices in flight, i.e. wait
-// for them).  Tiles of 128 x 128 (four waves of 64 x 64, in a launch group eight of 32 x 64; two workgroups a unit) or, EDGE 256,
-// 256 x 256 (eight of 128 x 64).
+// for them).  Tiles of 128 x 128 (four waves of 64 x 64, two workgroups a unit) or, EDGE 256, 256 x 256 (eight of 128 x 64).
 // Addresses that step a pointer instead of a product and a select a load, and sums of the columns by vector additions,
 // took a step of 128 x 128 tiles beside another workgroup from 1.35 to 1.06 us and one of 256 x 256 from 2.0 to 1.7.
 // Measured with the sums, called again and again, 128 | 256, us: 12544 rows, 2304 x 768 in as many chunks as each fills the
@@ -164,14 +163,11 @@ struct WeightArgs {
 // Relative error of dW (2-norm, to 64 bits), 2548 rows of 1024 columns in one chunk 3.05e-7 without, 1.06e-7 so (in four chunks without
 // 1.12e-7), 9800 of 512 in seven 2.26e-7, 1.11e-7 (in ten and sixteen 1.60e-7).  1 us of a step of 103 to 150.
 constexpr int kFoldSteps = 4;
-constexpr size_t weight_lds(int edge, int threads) {        // two steps of both operands, or the staging of the output
-  return std::max((size_t)2 * 2 * kLbK * edge * sizeof(__bf16), (size_t)threads / 64 * 32 * 68 * sizeof(float));
-}
-template <int EDGE, int THREADS, bool GI, bool XI>
+template <int EDGE, bool GI, bool XI>
 __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned char* lb_smem, unsigned block) {
   constexpr int STAGES = 2, DEPTH = 64;
-  constexpr int WK = EDGE / 64, TM = EDGE * WK * 2 / (THREADS / 64) / 64;
-  static_assert(WK == TM || TM == 1, "one column block of g for the sums of a wave");
+  constexpr int THREADS = EDGE == 256 ? 512 : 256, WK = EDGE / 64, TM = EDGE == 256 ? 4 : 2;
+  static_assert(WK == TM, "one column block of g for the sums of a wave");
   using P = DeepPieces<EDGE, THREADS, DEPTH>;
   __bf16* lds = reinterpret_cast<__bf16*>(lb_smem);
   const long ldd = a.ldd;
@@ -231,9 +227,9 @@ __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned 
       acc[i][1][r] = 0.f;
     }
   // Column block i of the wave's is number (i + wkb) % TM of g's, so that the TM waves that hold the same blocks have each
-  // another one as block 0, whose column sums it forms (of one block the first wave does): of every 16 contraction elements a lane holds 8 of column l32.
+  // another one as block 0, whose column sums it forms: of every 16 contraction elements a lane holds 8 of column l32.
   auto g_block = [&](int i) { return wn + (i + wkb) % TM * 32; };
-  const bool do_bias = a.part_b != nullptr && w.k0 == 0 && (TM > 1 || wkb == 0);
+  const bool do_bias = a.part_b != nullptr && w.k0 == 0;
   float colsum = 0.f;
   if ((GI || XI) && nk > 0) index(0);
   constexpr bool kFold = EDGE == kLbT;                      // (256 x 256 tiles have no registers for a second sum)
@@ -269,7 +265,7 @@ __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned 
         if (kFold && a.fold && (t + 1) % kFoldSteps == 0) fold();
       });
   fold();
-  static_assert(THREADS / 64 * 32 * 68 * sizeof(float) <= weight_lds(EDGE, THREADS), "output staging fits in the operand stages");
+  static_assert(THREADS / 64 * 32 * 68 * sizeof(float) <= STAGES * 2 * EDGE * DEPTH * sizeof(__bf16), "output staging fits in the operand stages");
   float* dst = a.part_w + (long)w.split * n_out * K;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -280,20 +276,20 @@ __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned 
     if (hh == 0 && n < n_out) a.part_b[(long)w.split * n_out + n] = s;
   }
 }
-template <int EDGE, int THREADS>
+template <int EDGE>
 __device__ __forceinline__ void weight_gemm_any(const WeightArgs& a, unsigned char* lb_smem, unsigned block) {
   const bool gi = a.dout_idx != nullptr, xi = a.x_idx != nullptr;
-  if (!gi && !xi) weight_gemm_block<EDGE, THREADS, false, false>(a, lb_smem, block);
-  else if (!xi) weight_gemm_block<EDGE, THREADS, true, false>(a, lb_smem, block);
-  else if (!gi) weight_gemm_block<EDGE, THREADS, false, true>(a, lb_smem, block);
-  else weight_gemm_block<EDGE, THREADS, true, true>(a, lb_smem, block);
+  if (!gi && !xi) weight_gemm_block<EDGE, false, false>(a, lb_smem, block);
+  else if (!xi) weight_gemm_block<EDGE, true, false>(a, lb_smem, block);
+  else if (!gi) weight_gemm_block<EDGE, false, true>(a, lb_smem, block);
+  else weight_gemm_block<EDGE, true, true>(a, lb_smem, block);
 }
 
 constexpr size_t kLbBigLds = (size_t)2 * 2 * kLbK * 256 * sizeof(__bf16);
 template <bool GI, bool XI>
 __global__ void __launch_bounds__(kLbThreads) __attribute__((amdgpu_waves_per_eu(2))) weight_gemm_kernel(const WeightArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lb_smem[];
-  weight_gemm_block<kLbT, kLbThreads, GI, XI>(a, lb_smem, blockIdx.x);
+  weight_gemm_block<kLbT, GI, XI>(a, lb_smem, blockIdx.x);
 }
 // Tiles of 256 x 256, eight waves, one workgroup a unit; up to two weight sides in a launch, workgroups [0, end) of the first.
 struct WeightPair {
@@ -303,33 +299,32 @@ struct WeightPair {
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1))) weight_gemm_big_kernel(const WeightPair p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lb_smem[];
   const int s = blockIdx.x >= p.end;
-  weight_gemm_any<256, 512>(p.w[s], lb_smem, blockIdx.x - (s ? p.end : 0u));
+  weight_gemm_any<256>(p.w[s], lb_smem, blockIdx.x - (s ? p.end : 0u));
 }
 
 // A launch group of the projections' backward: an input side with 128 x 128 tiles and up to two weight sides in one
 // launch (and the sums of both weight sides' chunks in one more).  On their own they leave units idle (98 rows, 384
 // columns: 3 to 9 tiles) and wait for each other.  At 3136 rows of 384 columns the training step of a block takes
-// 93 us so, 115 with the GEMMs one after the other and 110 with the weight sides on a second stream.  Two workgroups a unit, each of eight
-// waves (four a SIMD between them: few tiles leave a unit one workgroup, whose waves wait for each read and load alone), the input
-// side with a third step of A.  With four waves and two steps | now, us a training step of a block: 3136 rows of 384 columns 92.1 | 90.1,
-// 800 of 1024 111.4 | 101.9, 400 of 768 93.2 | 85.9, 1568 of 768 114.9 | 110.3, 6272 of 384 112.6 | 111.4 (four waves and the third
-// step: 91.7, 104.9, 88.7, 113.4, 114.3).
-constexpr size_t kLbGroupLds = std::max(weight_lds(kLbT, 512), gemm_small_lds(3, 2));
+// 93 us so, 115 with the GEMMs one after the other and 110 with the weight sides on a second stream.  In eight waves a
+// workgroup and a third step of A it was faster while the weight sides had 16 chunks (800 rows of 1024 columns 111 -> 102); with
+// the chunks of block_splits, four | eight: 5096 rows of 1024 columns 145 | 148, 9408 of 768 159 | 161.5, 25088 of 128 92.3 | 94.3,
+// 3920 of 192 62.2 | 61.4.
+static_assert(kLbGemmLds == kGemmSmallLds, "the launch's LDS serves both");
 struct LinearGroup {
   GemmArgs rows;
   WeightArgs w[2];
   unsigned end[2];               // workgroups of the input side, and of it and the first weight side
 };
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) linear_bwd_group_kernel(const LinearGroup g) {
+__global__ void __launch_bounds__(kLbThreads) __attribute__((amdgpu_waves_per_eu(2))) linear_bwd_group_kernel(const LinearGroup g) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lb_smem[];
   const unsigned block = blockIdx.x;
   if (block < g.end[0]) {
-    gemm_rows_small<false, true, 3, 2, 512>(g.rows, lb_smem, block, g.end[0]);
+    gemm_rows_small<false, true, 2, 256>(g.rows, lb_smem, block, g.end[0]);
     return;
   }
   const int s = block >= g.end[1];
   const WeightArgs& a = g.w[s];
-  weight_gemm_any<kLbT, 512>(a, lb_smem, block - g.end[s]);
+  weight_gemm_any<kLbT>(a, lb_smem, block - g.end[s]);
 }
 
 // part_w[split][n][k] = sum over the chunk's rows j of g_j[n] r_j[k]; part_b[split][n] = sum g_j[n]
@@ -641,8 +636,8 @@ static int weight_splits_big(int M_cap, long tiles, long most) {
   return (int)std::clamp(std::min(256 / tiles, by_rows), 1L, most);
 }
 // The weight sides of a block (N_out = K and 3 K) stand in one group.  Up to 2.92e10 multiplications of both (2.4e10 of more than 24000 rows,
-// whose input side takes large tiles) they share a launch of 128 x 128 tiles with the input side; beyond, the two alone have one of 256 x 256 tiles, which they fill together
-// with fewer chunks than each by itself (12544 live rows, 768 columns: seven; with their sums 84.7 us, as two launches of
+// whose input side takes large tiles) they share a launch of 128 x 128 tiles with the input side; beyond, the two alone have one of
+// 256 x 256 tiles, which they fill together with fewer chunks than each by itself (12544 live rows, 768 columns: seven; with their sums 84.7 us, as two launches of
 // 128 x 128 tiles and one for the sums 93).  More than ten do not pay (a step of 25088 rows, 512
 // columns, 10 | 16: 237.8 | 238.8 us; 32768 rows 279.6 | 284.8).
 constexpr double pair_work(int M_cap) { return M_cap <= 24000 ? 2.92e10 : 2.4e10; }
@@ -739,8 +734,8 @@ int group_flush_linear(hipStream_t st) {
       g.w[i] = n.w[i].a;
     }
     if (n.n_weight == 1) g.w[1] = g.w[0];
-    if (int rc = reserve_lds(fn, (const void*)linear_bwd_group_kernel, kLbGroupLds)) return rc;
-    hipLaunchKernelGGL(linear_bwd_group_kernel, dim3(blocks), dim3(512), kLbGroupLds, st, g);
+    if (int rc = reserve_lds(fn, (const void*)linear_bwd_group_kernel, kLbGemmLds)) return rc;
+    hipLaunchKernelGGL(linear_bwd_group_kernel, dim3(blocks), dim3(kLbThreads), kLbGemmLds, st, g);
   } else {
     if (n.n_rows == 1)
       if (int rc = launch_gemm_rows(fn, n.rows, true, st)) return rc;
