@@ -74,7 +74,8 @@ const char* spa_last_error(void);
  *   attn_bwd_short     "tiled": the long-segment backward for segments <= 256 (other values: the default)
  *   attn_bwd_long      accepted, without effect: the long-segment backward has one form
  *   gemm_tm            2 | 6 | 8 | 10: 128x128, 192x192, 256x256, 256x192 tiles of the projections (4 = 2; the weight sides
- *                      know 2 and 8); 14: the large ones by the live rows, as the default does where it takes large tiles
+ *                      know 2 and 8; with 8 a block's have more chunks and other bits); 14: the large ones by the live rows, as
+ *                      the default does where it takes large tiles
  *   gemm_splits        1..16 token chunks of the weight-side GEMM
  *   pack_tile          16 | 32 | 64 | 128 | 256 tokens per packing workgroup
  */

@@ -29,11 +29,12 @@
 #include "group.h"
 #include "linear.h"
 #include "spa_common.h"
+#include "weight_shape.h"
 
 namespace spa {
 
 constexpr int kLbThreads = 256;
-constexpr int kLbT = 128;          // output tile edge
+constexpr int kLbT = kWeightEdge;  // output tile edge
 constexpr int kLbK = 64;           // contraction step
 constexpr int kLbRS = kLbT + 16;   // row stride (elements) of a [contraction][128] tile: 72 dwords = 8 mod 64,
                                    // the 4 rows x 32 bytes a 16-lane block reads fall on distinct banks
@@ -158,11 +159,7 @@ struct WeightArgs {
   bool fold;                     // the sums of every kFoldSteps steps are added up apart (128 x 128 tiles)
   float *part_w, *part_b;
 };
-// Few chunks are long chains of products into one sum; of a block's sides in one launch, where they have fewer than fill
-// the chip, the sums of every 256 rows are added up apart.
-// Relative error of dW (2-norm, to 64 bits), 2548 rows of 1024 columns in one chunk 3.05e-7 without, 1.06e-7 so (in four chunks without
-// 1.12e-7), 9800 of 512 in seven 2.26e-7, 1.11e-7 (in ten and sixteen 1.60e-7).  1 us of a step of 103 to 150.
-constexpr int kFoldSteps = 4;
+constexpr int kFoldSteps = 4;    // (256 rows; WeightShape)
 template <int EDGE, bool GI, bool XI>
 __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned char* lb_smem, unsigned block) {
   constexpr int STAGES = 2, DEPTH = 64;
@@ -573,13 +570,6 @@ static int reserve_lds(const char* fn, const void* kernel, size_t bytes) {
   const hipError_t attr = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   return attr == hipSuccess ? SPA_OK : fail(SPA_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, bytes);
 }
-// How a weight side is cut: tiles of `edge`, `splits` chunks of tokens.  The number of chunks decides the bits of the
-// result, the edge does not.
-struct WeightShape {
-  int edge, splits;
-  bool fold = false;
-  long tiles(int n_out, int K) const { return gemm_tiles<long>(n_out, K, edge); }
-};
 // A noted or called weight side: the kernel's arguments but for the shape, the sum of its chunks, where the result goes.
 struct WeightCall {
   WeightArgs a;
@@ -614,77 +604,13 @@ static int launch_weight(const char* fn, WeightCall& c, WeightShape shape, hipSt
   return check_launch(fn);
 }
 
-// Number of token chunks.  It decides the bits of the result, so it follows from the call alone, whatever stands beside it in
-// a group and whatever the tiles; the option gemm_splits overrides it (tuning aid).
-// With 128 x 128 tiles: (chunk, tile) workgroups for two per compute unit (what is resident at a time), at most 16
-// chunks (every chunk's partial tiles are written and read once), chunks of at least 256 rows at full capacity, and
-// one chunk (no partial tiles, no second launch) up to 2048 rows: at half of them live its 16 steps take as long as 3
-// steps and the second launch.
-static int weight_splits(int M_cap, int K, int N_out) {
-  const int env = options().gemm_splits;
-  if (env > 0) return env;
-  const long tiles = gemm_tiles<long>(N_out, K, kLbT);
-  if (M_cap <= 2048) return 1;
-  const long by_rows = std::max(M_cap / 256, 1);
-  return (int)std::clamp(std::min(512 / tiles, by_rows), 1L, 16L);
-}
-// With 256 x 256 tiles: a workgroup a unit, chunks of at least 512 rows at full capacity.
-static int weight_splits_big(int M_cap, long tiles, long most) {
-  const int env = options().gemm_splits;
-  if (env > 0) return env;
-  const long by_rows = std::max(M_cap / 512, 1);
-  return (int)std::clamp(std::min(256 / tiles, by_rows), 1L, most);
-}
-// The weight sides of a block (N_out = K and 3 K) stand in one group.  Up to 2.92e10 multiplications of both (2.4e10 of more than 24000 rows,
-// whose input side takes large tiles) they share a launch of 128 x 128 tiles with the input side; beyond, the two alone have one of
-// 256 x 256 tiles, which they fill together with fewer chunks than each by itself (12544 live rows, 768 columns: seven; with their sums 84.7 us, as two launches of
-// 128 x 128 tiles and one for the sums 93).  More than ten do not pay (a step of 25088 rows, 512
-// columns, 10 | 16: 237.8 | 238.8 us; 32768 rows 279.6 | 284.8).
-constexpr double pair_work(int M_cap) { return M_cap <= 24000 ? 2.92e10 : 2.4e10; }
-static double weight_work(int M_cap, int K, int N_out) { return (double)M_cap * K * N_out; }
-// Their chunks: a chunk more shortens the walk over the rows and writes and reads a partial result more, which come out even where
-// the number is as sqrt(rows) / columns; the factors are those of the best steps measured, with 1 to 16 chunks.  In the one launch, two
-// thirds of that where the workgroups, with the input side at half of the rows live, are then two a unit and no more.  us a training step of
-// a block, with as many as fill the chip | so: 3136 rows of 1024 columns of capacity 136 | 122 (1 chunk), 5096 165 | 150 (1), 3136 of 768
-// 111 | 103 (1), 6272 140 | 132 (2), 9408 167 | 164 (2; 3 169), 4704 of 512 96 | 92.4 (3), 9800 124.5 | 117 (5), 19600 184.5 | 177 (7), 12544
-// of 384 113 | 109.4 (7); past the line 12544 of 768 212 | 200 (5), 18816 275 | 270.5 (6), 7840 of 1024 207.5 | 205 (3), 25088 of 768 the same
-// 7.  Alone, us, 768 x 768: 3136 rows 23 -> 20, 6272 24 -> 24.6, 9408 24 -> 32; 3 x that 24 -> 18, 25 -> 24, 31 -> 31.
-static bool in_one_launch(int M_cap, int C) { return 4 * weight_work(M_cap, C, C) <= pair_work(M_cap); }
-static int block_splits(int M_cap, int C, int fill) {
-  if (options().gemm_splits > 0) return fill;
-  if (in_one_launch(M_cap, C)) {
-    const long tiles = gemm_tiles<long>(C, C, kLbT) + gemm_tiles<long>(3L * C, C, kLbT);
-    const long beside = (512 - gemm_tiles<long>(std::max(M_cap / 2, 1), C, kLbT)) / tiles;
-    long best = (long)(std::sqrt(700. * M_cap) / C);
-    if (beside < best && 3 * beside >= 2 * best) best = beside;
-    return (int)std::clamp(best, 1L, (long)fill);
-  }
-  const int most = weight_splits_big(M_cap, gemm_tiles<long>(C, C, 256) + gemm_tiles<long>(3L * C, C, 256), 10);
-  return (int)std::clamp(std::sqrt(1200. * M_cap) / C + 0.5, 1., (double)most);
-}
-// The shape of a call of its own, by what was measured (above weight_gemm_block; half of the capacity live): a step takes
-// 1.1 us in a round of two 128 x 128 workgroups a unit and 1.8 in one of 256 x 256 tiles, launch, first loads and last stores 6
-// and 9 us, and the sums 0.15 us a MB of partial tiles.  Option gemm_tm (tuning aid): 2 | 8 forces 128 x 128 | 256 x 256.
+// Options gemm_tm and gemm_splits (tuning aids): 2 | 8 forces 128 x 128 | 256 x 256 tiles, 1 to 16 the chunks.
 static WeightShape weight_shape(int M_cap, int K, int N_out) {
-  const int cfg = options().gemm_tm;
-  WeightShape small = {kLbT, weight_splits(M_cap, K, N_out)};
-  WeightShape big = {256, weight_splits_big(M_cap, gemm_tiles<long>(N_out, K, 256), 16)};
-  if (N_out == K || N_out == 3 * (long)K) {
-    const int fill = small.splits;
-    big.splits = small.splits = block_splits(M_cap, K, fill);
-    small.fold = small.splits < fill && in_one_launch(M_cap, K) && cfg != 2 && cfg != 8;
-  }
-  if (small.fold) return small;
-  const double mb = 4e-6 * N_out * K;
-  const auto steps = [&](int splits) { return (double)((std::max(M_cap / 2, 1) / splits + 63) / 64); };
-  const double t_small = 6 + 1.1 * steps(small.splits) * std::ceil(small.splits * small.tiles(N_out, K) / 512.) + 0.15 * mb * small.splits;
-  const double t_big = 9 + 1.8 * steps(big.splits) * std::ceil(big.splits * big.tiles(N_out, K) / 256.) + 0.15 * mb * big.splits;
-  WeightShape shape = t_big < 0.97 * t_small ? big : small;
-  if (cfg == 2 || cfg == 8) shape.edge = cfg == 8 ? 256 : kLbT;
-  return shape;
+  return weight_shape(M_cap, K, N_out, options().gemm_tm, options().gemm_splits);
 }
-static int weight_max_splits(int M_cap, int K, int N_out) {      // (rows with a gate scale take the small tiles)
-  return std::max(weight_splits(M_cap, K, N_out), weight_shape(M_cap, K, N_out).splits);
+static int weight_max_splits(int M_cap, int K, int N_out) {      // (whatever the tiles; rows with a gate scale take the small ones)
+  const int forced = options().gemm_splits;
+  return std::max({weight_splits(M_cap, K, N_out, forced), weight_most_splits(M_cap, K, N_out, forced), weight_shape(M_cap, K, N_out).splits});
 }
 
 // Two weight sides of a group in one launch of 256 x 256 tiles: those of a block past its line, and others that are as large
@@ -700,7 +626,7 @@ static bool weights_together(const WeightCall& a, const WeightCall& b) {
     blocks += shape.splits * gemm_tiles<long>(c->a.n_out, c->a.K, 256);
     work += weight_work(c->a.m_cap, c->a.K, c->a.n_out);
   }
-  return work > pair_work(std::max(a.a.m_cap, b.a.m_cap)) && blocks <= 256;
+  return work > kPairWork && blocks <= 256;
 }
 
 static thread_local struct {
@@ -849,7 +775,7 @@ extern "C" int spa_linear_packed_bwd_weight(const void* dout, const int32_t* dou
               "%s: workspace of %zu bytes needed, %zu given", fn, need, workspace_bytes);
   SPA_REQUIRE((reinterpret_cast<uintptr_t>(workspace) & 255u) == 0, SPA_ERR_INVALID_ARG,
               "%s: workspace not 256-byte aligned", fn);
-  const WeightShape shape = gate_scores != nullptr ? WeightShape{kLbT, weight_splits(M_cap, K, N_out)} : weight_shape(M_cap, K, N_out);
+  const WeightShape shape = gate_scores != nullptr ? WeightShape{kLbT, weight_splits(M_cap, K, N_out, options().gemm_splits)} : weight_shape(M_cap, K, N_out);
   SPA_REQUIRE(shape.splits * shape.tiles(N_out, K) + 8 < 2147483647L / 2, SPA_ERR_INVALID_ARG, "%s: too many tiles", fn);
   SPA_REQUIRE(!(group_open() && gate_scores != nullptr), SPA_ERR_UNSUPPORTED, "%s: gated rows cannot be part of a group", fn);
   WeightCall c = {};

@@ -1,0 +1,94 @@
+// How the weight side of the projections' backward (linear_bwd.hip) is cut: tile edge and chunks of tokens; no device code, so
+// that a host program can ask the rules.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+
+#include "gemm_shape.h"
+
+namespace spa {
+
+constexpr int kWeightEdge = 128;
+
+// Tiles of `edge`, `splits` chunks of tokens.  The number of chunks and `fold` decide the bits of the result, the edge does not.
+struct WeightShape {
+  int edge, splits;
+  bool fold = false;             // a chunk's sums of every 256 rows are added up apart (128 x 128 tiles)
+  long tiles(int n_out, int K) const { return gemm_tiles<long>(n_out, K, edge); }
+};
+
+// Number of token chunks.  It decides the bits of the result, so it follows from the call alone, whatever stands beside it in
+// a group; `forced` (option gemm_splits) overrides it.
+// With 128 x 128 tiles: (chunk, tile) workgroups for two per compute unit (what is resident at a time), at most 16
+// chunks (every chunk's partial tiles are written and read once), chunks of at least 256 rows at full capacity, and
+// one chunk (no partial tiles, no second launch) up to 2048 rows: at half of them live its 16 steps take as long as 3
+// steps and the second launch.
+inline int weight_splits(int M_cap, int K, int N_out, int forced) {
+  if (forced > 0) return forced;
+  const long tiles = gemm_tiles<long>(N_out, K, kWeightEdge);
+  if (M_cap <= 2048) return 1;
+  const long by_rows = std::max(M_cap / 256, 1);
+  return (int)std::clamp(std::min(512 / tiles, by_rows), 1L, 16L);
+}
+// With 256 x 256 tiles: a workgroup a unit, chunks of at least 512 rows at full capacity.
+inline int weight_splits_big(int M_cap, long tiles, long most, int forced) {
+  if (forced > 0) return forced;
+  const long by_rows = std::max(M_cap / 512, 1);
+  return (int)std::clamp(std::min(256 / tiles, by_rows), 1L, most);
+}
+// The weight sides of a block (N_out = K and 3 K) stand in one group.  Up to 2.92e10 multiplications of both (2.4e10 of more than 24000 rows)
+// they share a launch of 128 x 128 tiles with the input side; beyond, the two alone have one of
+// 256 x 256 tiles, which they fill together with fewer chunks than each by itself (12544 live rows, 768 columns: seven; with their sums 84.7 us, as two launches of
+// 128 x 128 tiles and one for the sums 93).  More than ten do not pay (a step of 25088 rows, 512
+// columns, 10 | 16: 237.8 | 238.8 us; 32768 rows 279.6 | 284.8).
+constexpr double kPairWork = 2.4e10;
+inline double weight_work(int M_cap, int K, int N_out) { return (double)M_cap * K * N_out; }
+inline bool in_one_launch(int M_cap, int C) { return 4 * weight_work(M_cap, C, C) <= (M_cap <= 24000 ? 2.92e10 : kPairWork); }
+inline bool of_a_block(int K, int N_out) { return N_out == K || N_out == 3 * (long)K; }
+// The chunks that a call would have for speed alone.  Where a block's have fewer, and in no tile that cannot add up sums apart (256 x 256
+// has no registers for a second sum), the sums are added up apart.
+inline int weight_most_splits(int M_cap, int K, int N_out, int forced) {
+  if (of_a_block(K, N_out) && 4 * weight_work(M_cap, K, K) > kPairWork)
+    return weight_splits_big(M_cap, gemm_tiles<long>(K, K, 256) + gemm_tiles<long>(3L * K, K, 256), 10, forced);
+  return weight_splits(M_cap, K, N_out, forced);
+}
+// The chunks of a block's sides in the one launch: a chunk more shortens the walk over the rows and writes and reads a partial result more, which
+// come out even where the number is as sqrt(rows) / columns; the factor is that of the best steps measured, with 1 to 16 chunks.  Two
+// thirds of that where the workgroups, with the input side at half of the rows live, are then two a unit and no more.  us a training step of
+// a block, with as many as fill the chip | so: 3136 rows of 1024 columns of capacity 136 | 122 (1 chunk), 5096 165 | 150 (1), 3136 of 768
+// 111 | 103 (1), 6272 140 | 132 (2), 9408 167 | 164 (2; 3 169), 4704 of 512 96 | 92.4 (3), 9800 124.5 | 117 (5), 19600 184.5 | 177 (7), 12544
+// of 384 113 | 109.4 (7).  Few chunks are long chains of products into one sum: relative error of dW (2-norm, to 64 bits), 2548 rows of 1024
+// columns in one chunk 3.05e-7 as one sum, 1.06e-7 as sums of 256 rows (in four chunks 1.12e-7), 9800 of 512 in seven 2.26e-7, 1.11e-7 (in ten
+// and sixteen 1.60e-7); 1 us of a step of 103 to 150.
+inline int block_splits(int M_cap, int C, int N_out) {
+  const long tiles = gemm_tiles<long>(C, C, kWeightEdge) + gemm_tiles<long>(3L * C, C, kWeightEdge);
+  const long beside = (512 - gemm_tiles<long>(std::max(M_cap / 2, 1), C, kWeightEdge)) / tiles;
+  long best = (long)(std::sqrt(700. * M_cap) / C);
+  if (beside < best && 3 * beside >= 2 * best) best = beside;
+  return (int)std::clamp(best, 1L, (long)weight_splits(M_cap, C, N_out, 0));
+}
+// The shape of a call of its own, by what was measured (half of the capacity live): a step takes
+// 1.1 us in a round of two 128 x 128 workgroups a unit and 1.8 in one of 256 x 256 tiles, launch, first loads and last stores 6
+// and 9 us, and the sums 0.15 us a MB of partial tiles.  cfg 2 | 8 forces the tiles (where they cannot add up sums apart, with the chunks that
+// need no such sums).
+inline WeightShape weight_shape(int M_cap, int K, int N_out, int cfg, int forced) {
+  WeightShape small = {kWeightEdge, weight_most_splits(M_cap, K, N_out, forced)};
+  WeightShape big = {256, weight_splits_big(M_cap, gemm_tiles<long>(N_out, K, 256), 16, forced)};
+  if (of_a_block(K, N_out)) {
+    if (forced <= 0 && cfg != 8 && in_one_launch(M_cap, K)) {
+      const int few = block_splits(M_cap, K, N_out);
+      if (few < small.splits) return {kWeightEdge, few, true};
+    }
+    big.splits = small.splits;
+  }
+  const double mb = 4e-6 * N_out * K;
+  const auto steps = [&](int splits) { return (double)((std::max(M_cap / 2, 1) / splits + 63) / 64); };
+  const double t_small = 6 + 1.1 * steps(small.splits) * std::ceil(small.splits * small.tiles(N_out, K) / 512.) + 0.15 * mb * small.splits;
+  const double t_big = 9 + 1.8 * steps(big.splits) * std::ceil(big.splits * big.tiles(N_out, K) / 256.) + 0.15 * mb * big.splits;
+  WeightShape shape = t_big < 0.97 * t_small ? big : small;
+  if (cfg == 2 || cfg == 8) shape.edge = cfg == 8 ? 256 : kWeightEdge;
+  return shape;
+}
+
+}  // namespace spa
