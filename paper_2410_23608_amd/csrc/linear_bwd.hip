@@ -41,6 +41,7 @@ constexpr int kLbRS = kLbT + 16;   // row stride (elements) of a [contraction][1
 constexpr int kLbRows = 512;       // rows of a chunk whose sources are tabled in LDS at a time (6 KB: with the
                                    // operand stages 78 KB per workgroup, two workgroups per compute unit)
 constexpr size_t kLbGemmLds = (size_t)2 * 2 * kLbK * kLbT * sizeof(__bf16);   // two operand stages
+constexpr size_t kLdsBytes = 160 * 1024;
 constexpr size_t kLbWeightLds = (size_t)2 * 2 * kLbK * kLbRS * sizeof(__bf16);
 
 // MFMA operand fragment taken DOWN the columns of a row-major tile whose rows are the
@@ -160,11 +161,12 @@ struct WeightArgs {
   float *part_w, *part_b;
 };
 constexpr int kFoldSteps = 4;    // (256 rows; WeightShape)
-template <int EDGE, bool GI, bool XI>
+// TABLE: the indices of the chunk's named rows are in LDS, behind the operand stages, before the first step (a wait for an index from
+// memory is one for every load issued before it, i.e. for all but one or two of the steps in flight).
+template <int EDGE, int THREADS, int STAGES, bool TABLE, bool GI, bool XI>
 __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned char* lb_smem, unsigned block) {
-  constexpr int STAGES = 2, DEPTH = 64;
-  constexpr int THREADS = EDGE == 256 ? 512 : 256, WK = EDGE / 64, TM = EDGE == 256 ? 4 : 2;
-  static_assert(WK == TM, "one column block of g for the sums of a wave");
+  constexpr int DEPTH = 64, WK = EDGE / 64, TM = EDGE * EDGE / (32 * THREADS);
+  static_assert(TM <= WK && THREADS / 64 * TM * 32 * 64 == EDGE * EDGE, "a wave for the sums of every column block of g");
   using P = DeepPieces<EDGE, THREADS, DEPTH>;
   __bf16* lds = reinterpret_cast<__bf16*>(lb_smem);
   const long ldd = a.ldd;
@@ -184,12 +186,22 @@ __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned 
   // Named rows: their indices, those of the step to be issued next (past the end the last row's).  Rows in order: a
   // pointer to the thread's first.
   int gi[P::kCount], xi[P::kCount];
+  constexpr bool kTable = TABLE && (GI || XI);
+  int* g_table = reinterpret_cast<int*>(lb_smem + (size_t)STAGES * 2 * EDGE * DEPTH * sizeof(__bf16));
+  int* x_table = g_table + (GI ? rows : 0);
+  if (kTable) {
+    for (int r = tid; r < rows; r += THREADS) {
+      if (GI) g_table[r] = a.dout_idx[w.m_begin + r];
+      if (XI) x_table[r] = a.x_idx[w.m_begin + r];
+    }
+    __syncthreads();
+  }
   auto index = [&](int t) {
 #pragma unroll
     for (int u = 0; u < P::kCount; ++u) {
-      const int at = min(w.m_begin + t * DEPTH + P::row(tid, u), w.m_end - 1);
-      if (GI) gi[u] = a.dout_idx[at];
-      if (XI) xi[u] = a.x_idx[at];
+      const int r = min(t * DEPTH + P::row(tid, u), rows - 1);
+      if (GI) gi[u] = kTable ? g_table[r] : a.dout_idx[w.m_begin + r];
+      if (XI) xi[u] = kTable ? x_table[r] : a.x_idx[w.m_begin + r];
     }
   };
   const __bf16* gp = gcol + (GI ? 0 : (long)(w.m_begin + row) * ldd);
@@ -223,10 +235,10 @@ __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned 
       acc[i][0][r] = 0.f;
       acc[i][1][r] = 0.f;
     }
-  // Column block i of the wave's is number (i + wkb) % TM of g's, so that the TM waves that hold the same blocks have each
-  // another one as block 0, whose column sums it forms: of every 16 contraction elements a lane holds 8 of column l32.
+  // Column block i of the wave's is number (i + wkb) % TM of g's, so that the first TM of the waves that hold the same blocks have
+  // each another one as block 0, whose column sums it forms: of every 16 contraction elements a lane holds 8 of column l32.
   auto g_block = [&](int i) { return wn + (i + wkb) % TM * 32; };
-  const bool do_bias = a.part_b != nullptr && w.k0 == 0;
+  const bool do_bias = a.part_b != nullptr && w.k0 == 0 && wkb < TM;
   float colsum = 0.f;
   if ((GI || XI) && nk > 0) index(0);
   constexpr bool kFold = EDGE == kLbT;                      // (256 x 256 tiles have no registers for a second sum)
@@ -273,20 +285,31 @@ __device__ __forceinline__ void weight_gemm_block(const WeightArgs& a, unsigned 
     if (hh == 0 && n < n_out) a.part_b[(long)w.split * n_out + n] = s;
   }
 }
-template <int EDGE>
+template <int EDGE, int THREADS>
 __device__ __forceinline__ void weight_gemm_any(const WeightArgs& a, unsigned char* lb_smem, unsigned block) {
   const bool gi = a.dout_idx != nullptr, xi = a.x_idx != nullptr;
-  if (!gi && !xi) weight_gemm_block<EDGE, false, false>(a, lb_smem, block);
-  else if (!xi) weight_gemm_block<EDGE, true, false>(a, lb_smem, block);
-  else if (!gi) weight_gemm_block<EDGE, false, true>(a, lb_smem, block);
-  else weight_gemm_block<EDGE, true, true>(a, lb_smem, block);
+  if (!gi && !xi) weight_gemm_block<EDGE, THREADS, 2, false, false, false>(a, lb_smem, block);
+  else if (!xi) weight_gemm_block<EDGE, THREADS, 2, false, true, false>(a, lb_smem, block);
+  else if (!gi) weight_gemm_block<EDGE, THREADS, 2, false, false, true>(a, lb_smem, block);
+  else weight_gemm_block<EDGE, THREADS, 2, false, true, true>(a, lb_smem, block);
 }
 
 constexpr size_t kLbBigLds = (size_t)2 * 2 * kLbK * 256 * sizeof(__bf16);
 template <bool GI, bool XI>
 __global__ void __launch_bounds__(kLbThreads) __attribute__((amdgpu_waves_per_eu(2))) weight_gemm_kernel(const WeightArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lb_smem[];
-  weight_gemm_block<kLbT, GI, XI>(a, lb_smem, blockIdx.x);
+  weight_gemm_block<kLbT, kLbThreads, 2, false, GI, XI>(a, lb_smem, blockIdx.x);
+}
+// 128 x 128 tiles in eight waves of 32 x 64 with four steps of both operands in LDS, one workgroup a unit: the few chunks of a block's
+// weight side where it is called alone, a chain of LDS reads and products at .55 us a step.  us a call with its sums, half of the rows live, two
+// workgroups of four waves a unit | so: 768 x 768, 3136 rows 23.1 | 19.8, 6272 27.5 | 24.4; 1024 x 1024, 3136 rows 23.7 | 20.6; 512 x 512, 9800 rows
+// 21.9 | 19.7; 3072 x 1024, 5096 rows 30.8 | 28.0; more tiles than units 2304 x 768, 11000 rows 38.7 | 44.9, 1536 x 512, 19600 rows 33.0 | 38.0.  Tiles
+// of 128 x 64 in four waves 4 % faster where those are no more than units, 1 to 6 % slower where they are.
+constexpr size_t kLbRingLds = 2 * kLbGemmLds;
+template <bool GI, bool XI>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) weight_gemm_ring_kernel(const WeightArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lb_smem[];
+  weight_gemm_block<kLbT, 512, 4, true, GI, XI>(a, lb_smem, blockIdx.x);
 }
 // Tiles of 256 x 256, eight waves, one workgroup a unit; up to two weight sides in a launch, workgroups [0, end) of the first.
 struct WeightPair {
@@ -296,7 +319,7 @@ struct WeightPair {
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1))) weight_gemm_big_kernel(const WeightPair p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lb_smem[];
   const int s = blockIdx.x >= p.end;
-  weight_gemm_any<256>(p.w[s], lb_smem, blockIdx.x - (s ? p.end : 0u));
+  weight_gemm_any<256, 512>(p.w[s], lb_smem, blockIdx.x - (s ? p.end : 0u));
 }
 
 // A launch group of the projections' backward: an input side with 128 x 128 tiles and up to two weight sides in one
@@ -321,7 +344,7 @@ __global__ void __launch_bounds__(kLbThreads) __attribute__((amdgpu_waves_per_eu
   }
   const int s = block >= g.end[1];
   const WeightArgs& a = g.w[s];
-  weight_gemm_any<kLbT>(a, lb_smem, block - g.end[s]);
+  weight_gemm_any<kLbT, kLbThreads>(a, lb_smem, block - g.end[s]);
 }
 
 // part_w[split][n][k] = sum over the chunk's rows j of g_j[n] r_j[k]; part_b[split][n] = sum g_j[n]
@@ -597,6 +620,14 @@ static int launch_weight(const char* fn, WeightCall& c, WeightShape shape, hipSt
   const unsigned grid = c.set(shape);
   if (shape.edge == 256) return launch_weight_big(fn, {{c.a, c.a}, grid}, grid, st);
   const bool gi = c.a.dout_idx != nullptr, xi = c.a.x_idx != nullptr;
+  const size_t named = (size_t)(gi + xi) * (((c.a.m_cap + shape.splits - 1) / shape.splits + kLbK - 1) / kLbK * kLbK) * sizeof(int);
+  if (shape.fold && grid <= 256 && kLbRingLds + named <= kLdsBytes) {
+    const auto ring = gi ? (xi ? weight_gemm_ring_kernel<true, true> : weight_gemm_ring_kernel<true, false>)
+                         : (xi ? weight_gemm_ring_kernel<false, true> : weight_gemm_ring_kernel<false, false>);
+    if (int rc = reserve_lds(fn, (const void*)ring, kLbRingLds + named)) return rc;
+    hipLaunchKernelGGL(ring, dim3(grid), dim3(512), kLbRingLds + named, st, c.a);
+    return check_launch(fn);
+  }
   const auto kernel = gi ? (xi ? weight_gemm_kernel<true, true> : weight_gemm_kernel<true, false>)
                          : (xi ? weight_gemm_kernel<false, true> : weight_gemm_kernel<false, false>);
   if (int rc = reserve_lds(fn, (const void*)kernel, kLbGemmLds)) return rc;
@@ -653,6 +684,8 @@ int group_flush_linear(hipStream_t st) {
     const long tiles = (long)((n.rows.m_cap + 127) / 128) * ((n.rows.ncols + 127) / 128);
     g.end[0] = (unsigned)((tiles + 7) / 8 * 8);
     unsigned blocks = g.end[0];
+    // long chunks first: what does not fit at a time comes last, and short
+    if (n.n_weight == 2 && shape(n.w[0]).splits > shape(n.w[1]).splits) std::swap(n.w[0], n.w[1]);
     for (int i = 0; i < n.n_weight; ++i) {
       const WeightShape own = shape(n.w[i]);
       blocks += n.w[i].set({kLbT, own.splits, own.fold});

@@ -61,11 +61,21 @@ inline int weight_most_splits(int M_cap, int K, int N_out, int forced) {
 // of 384 113 | 109.4 (7).  Few chunks are long chains of products into one sum: relative error of dW (2-norm, to 64 bits), 2548 rows of 1024
 // columns in one chunk 3.05e-7 as one sum, 1.06e-7 as sums of 256 rows (in four chunks 1.12e-7), 9800 of 512 in seven 2.26e-7, 1.11e-7 (in ten
 // and sixteen 1.60e-7); 1 us of a step of 103 to 150.
+// The narrow side is a chain of steps on few units where it is called alone, so its chunks are of about 1325 live rows at most where that
+// is a good deal fewer.  With the input side and the wide side they are then two workgroups a unit, or else many and short, behind
+// the others.  As many chunks as the wide side's | so, us, called alone (as many as fill the chip) and a step: 5096 rows of 1024 columns 29.7 | 24.2
+// (26.8) and 147.0 | 147.7, 6664 26.1 | 24.2 (24.2), 180.5 | 178.2, 7056 of 832 26.5 | 21.1 (23.0), 160.0 | 154.4, 9408 of 768 31.3 | 21.8 (23.5),
+// 160.6 | 162.4, 10976 27.0 | 22.2 (22.1), 177.1 | 179.4; not 9800 of 640 25.0 | 21.3 (24.2), 140.4 | 144.7.
 inline int block_splits(int M_cap, int C, int N_out) {
-  const long tiles = gemm_tiles<long>(C, C, kWeightEdge) + gemm_tiles<long>(3L * C, C, kWeightEdge);
-  const long beside = (512 - gemm_tiles<long>(std::max(M_cap / 2, 1), C, kWeightEdge)) / tiles;
+  const long narrow = gemm_tiles<long>(C, C, kWeightEdge), wide = gemm_tiles<long>(3L * C, C, kWeightEdge);
+  const long left = 512 - gemm_tiles<long>(std::max(M_cap / 2, 1), C, kWeightEdge), beside = left / (narrow + wide);
   long best = (long)(std::sqrt(700. * M_cap) / C);
   if (beside < best && 3 * beside >= 2 * best) best = beside;
+  if (N_out == C && M_cap > 3300 * std::max(best, 1L)) {
+    long more = (M_cap + 1325) / 2650;
+    if (more * narrow + best * wide > left) more = std::max(more, std::min(3 * best, 256 / narrow));
+    best = std::max(best, std::min(more, weight_most_splits(M_cap, C, N_out, 0) - 1L));      // (fewer: the sums stay apart)
+  }
   return (int)std::clamp(best, 1L, (long)weight_splits(M_cap, C, N_out, 0));
 }
 // The shape of a call of its own, by what was measured (half of the capacity live): a step takes
