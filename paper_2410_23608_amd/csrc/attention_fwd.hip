@@ -612,6 +612,7 @@ tiled_attention(TiledLds<DH, kTiledBN>& lds, const Segment seg, int h, int q0, c
   if (wave_live) {
     fwd_park<DH, RS>(acc, q_ok, seg.nk > 0, parked, lse != nullptr ? lse + h * lse_stride + seg.row0 + qi : nullptr,
                      l32, hh);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     fwd_flush<DH, RS, GATHER == kFwdGatedD>(parked, out, sc, y_row, seg.row0 + q0 + wv * 32, h, C, min(32, seg.nq - q0 - wv * 32),
                                            lane, sc.dvec + h * lse_stride);

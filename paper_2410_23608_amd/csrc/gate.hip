@@ -466,6 +466,7 @@ __global__ void __launch_bounds__(kGateThreads) gate_pyramid_kernel(const Pyrami
     }
     finer = mine;
     mine += n;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // (other lanes read mine: an order for the compiler, no instruction)
     __builtin_amdgcn_wave_barrier();
   }
 }

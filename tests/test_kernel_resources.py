@@ -1,5 +1,6 @@
 """Registers of the built kernels, from the notes of the code objects in libspa.so: how many workgroups of a kernel a unit
 holds is part of its design, and a spill in a loop is paid on every turn."""
+import os
 import re
 import struct
 
@@ -53,3 +54,17 @@ def test_waves_of_a_simd(kernels, pattern, count, waves):
 
 def test_no_kernel_spills(kernels):
     assert [n for n, k in kernels.items() if k[1] or k[2]] == []
+
+
+def test_lanes_that_exchange_through_lds_order_their_memory():
+    """A wave's LDS operations run in order, but __builtin_amdgcn_wave_barrier alone leaves the compiler free to move them across it:
+    a fence of the wavefront stands before each."""
+    found = 0
+    for name in sorted(os.listdir(spa_build.CSRC)):
+        with open(os.path.join(spa_build.CSRC, name)) as f:
+            lines = f.read().splitlines()
+        for before, line in zip(lines, lines[1:]):
+            if "__builtin_amdgcn_wave_barrier()" in line:
+                found += 1
+                assert '__builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront")' in before, (name, line)
+    assert found >= 3
