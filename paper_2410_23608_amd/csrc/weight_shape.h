@@ -37,14 +37,19 @@ inline int weight_splits_big(int M_cap, long tiles, long most, int forced) {
   const long by_rows = std::max(M_cap / 512, 1);
   return (int)std::clamp(std::min(256 / tiles, by_rows), 1L, most);
 }
-// The weight sides of a block (N_out = K and 3 K) stand in one group.  Up to 2.92e10 multiplications of both (2.4e10 of more than 24000 rows)
-// they share a launch of 128 x 128 tiles with the input side; beyond, the two alone have one of
-// 256 x 256 tiles, which they fill together with fewer chunks than each by itself (12544 live rows, 768 columns: seven; with their sums 84.7 us, as two launches of
-// 128 x 128 tiles and one for the sums 93).  More than ten do not pay (a step of 25088 rows, 512
-// columns, 10 | 16: 237.8 | 238.8 us; 32768 rows 279.6 | 284.8).
-constexpr double kPairWork = 2.4e10;
+// The weight sides of a block (N_out = K and 3 K) stand in one group.  Up to a line they share a launch of 128 x 128 tiles with the input
+// side; beyond, the two alone have one of 256 x 256 tiles on a second stream (or in order), which they fill together with fewer chunks than
+// each by itself (12544 live rows, 768 columns: seven; with their sums 84.7 us, as two launches of 128 x 128 tiles and one for the sums 93).  More
+// than ten do not pay (a step of 25088 rows, 512 columns, 10 | 16: 237.8 | 238.8 us; 32768 rows 279.6 | 284.8).
+constexpr double kPairWork = 2.4e10;                       // multiplications of both
 inline double weight_work(int M_cap, int K, int N_out) { return (double)M_cap * K * N_out; }
-inline bool in_one_launch(int M_cap, int C) { return 4 * weight_work(M_cap, C, C) <= (M_cap <= 24000 ? 2.92e10 : kPairWork); }
+// The line.  One launch saves the streams' events and a launch, a constant; a second stream has the gate backward, whose time goes with rows x
+// columns, beside the weight sides, so that narrow blocks of many rows pass to it earlier.  us a training step, one launch | second stream: 12152
+// rows of 768 columns (7.2e9) 192.7 | 202.4, 9016 of 896 (7.2e9) 187.8 | 196.3, 17836 of 640 (7.3e9) 215.6 | 214.3, 16464 199.1 | 202.6, 21560 of 576 (7.2e9)
+// 232.6 | 228.3, 23912 of 512 (6.3e9) 197.7 | 199.6; 25600 of 512 (6.7e9) 205.6 | 205.6, 27648 (7.2e9) 230.0 | 214.3, 27648 of 480 (6.4e9) 234.7 |
+// 223.6, 32768 of 448 (6.6e9) 227.5 | 220.0, 48640 of 384 (7.2e9) 277.4 | 277.6; 29400 of 448 (5.9e9) 219.2 | 221.7.  (Blocks of 768 columns and more would
+// gain up to 9.2e9: 13328 rows of 768 205.1 | 209.4, 15680 231.6 | 231.5, 8624 of 1024 216.5 | 226.9.)
+inline bool in_one_launch(int M_cap, int C) { return weight_work(M_cap, C, C) <= (M_cap <= 24000 ? 7.3e9 : 6e9); }
 inline bool of_a_block(int K, int N_out) { return N_out == K || N_out == 3 * (long)K; }
 // The chunks that a call would have for speed alone.  Where a block's have fewer, and in no tile that cannot add up sums apart (256 x 256
 // has no registers for a second sum), the sums are added up apart.

@@ -384,6 +384,11 @@ class BlockPass(_Pass):
         return x if self.in_place else self.y
 
 
+def _one_launch(rows: int, C: int) -> bool:
+    """Whether a block's weight sides share a launch with the input side; in_one_launch of csrc/weight_shape.h, whose chunks go with it."""
+    return float(rows) * C * C <= (7.3e9 if rows <= 24000 else 6e9)
+
+
 class BlockTrainPass(_Pass):
     """Forward + backward of one SPA attention block WITH its projections (Section 3.2) and the
     selection loss (Section 3.3), eleven calls one by one, nine or ten with the weight sides beside other work:
@@ -402,21 +407,20 @@ class BlockTrainPass(_Pass):
     is left to the caller (it is the upstream gradient, unchanged).
 
     overlap_weight_grads (default): nothing downstream in the step reads dW / dbias, so the two weight-side GEMMs run
-    beside other work.  In bf16 with B N C^2 <= 7.3e9 (B N > 24000: 6e9) they share one launch with the input side of the QKV projection
+    beside other work.  In bf16 up to a line (_one_launch) they share one launch with the input side of the QKV projection
     (a launch group, stage projections_bwd), and their partial sums one more: these GEMMs leave units idle there and every
     dependent launch costs 4 us, most of it before its first product.  Above that line the two fill the chip together: one
     launch for both and one for their sums (stage projections_bwd_weight), on a second HIP stream (default priority) beside
     the input-side GEMM and the gate backward; an event orders them after their inputs and the step's last stage
     (join_streams) joins the streams.  In fp32 each is a stage of its own (out_projection_bwd_weight, beside the attention
     backward, and qkv_projection_bwd_weight).  overlap_weight_grads=False: every call a launch in order, under those names.
-    Measured, us a step, one launch / second stream: 52 x 196 x 768 (6.0e9) 174.5 / 178, 56 179 / 183, 62 (7.2e9) 194.5 / 195, 80 257 / 246,
-    96 310 / 275; 41 x 196 x 896 (6.5e9) 180.5 / 199.5, 46 (7.2e9) 192.5 / 197; 30 x 196 x 1024 (6.2e9) 161.5 / 180.5, 64 299 / 286;
-    122 x 196 x 512 (6.3e9) 215 / 216, 100 x 256 x 512 (6.7e9) 213 / 208.  In order 16 x 196 x 768 127, 32 155, 64 225 (one launch 103,
-    134, 203)."""
+    Measured, us a step, one launch / second stream: 62 x 196 x 768 193 / 202, 46 x 196 x 896 188 / 196, 122 x 196 x 512
+    198 / 200, 108 x 256 x 512 230 / 214 (more beside the rule's other half, csrc/weight_shape.h).  In order 16 x 196 x 768 125, 48 185 (one launch
+    100, 163)."""
 
     def __init__(self, B: int, N: int, C: int, H: int, dtype: str, tau: float = 0.5, bias: float = 0.0,
                  loss_scale: Optional[float] = None, overlap_weight_grads: bool = True):
-        self.grouped = overlap_weight_grads and dtype == "bf16" and B * N * C * C <= (7.3e9 if B * N <= 24000 else 6e9)
+        self.grouped = overlap_weight_grads and dtype == "bf16" and _one_launch(B * N, C)
         self.overlap = overlap_weight_grads and not self.grouped
         self.side = torch.cuda.Stream() if self.overlap else None
         self.B, self.N, self.C, self.H, self.Dh = B, N, C, H, C // H

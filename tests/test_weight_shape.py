@@ -70,6 +70,15 @@ def test_fewer_chunks_only_with_sums_apart(shapes, tiles):
     assert (apart > 100) == (tiles != 8)
 
 
+def test_the_pass_and_the_kernels_draw_one_line(shapes):
+    """BlockTrainPass forms the launch group where the weight sides have the chunks for it."""
+    from paper_2410_23608_amd.pipeline import _one_launch
+    calls = [(m, c, c, 0, 0) for c in COLUMNS for m in ROWS + [int(w // (c * c)) + d for w in (6e9, 7.3e9) for d in (0, 1)]
+             if 0 < m < 2 ** 31]
+    got = [s[3] for s in shapes(calls)]
+    assert got == [int(_one_launch(m, c)) for m, c, *_ in calls] and {0, 1} == set(got)
+
+
 def test_forced_chunks_are_one_sum_each(shapes):
     calls = [(m, c, 3 * c, 0, s) for m in ROWS for c in COLUMNS for s in (1, 7, 16)]
     assert all(got[1:3] == (c[4], 0) for c, got in zip(calls, shapes(calls)))
