@@ -213,6 +213,13 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) g
   gemm_rows_small<kScale, kDeep, 4, 512>(p, gemm_smem, blockIdx.x, gridDim.x);
 }
 
+// The same waves with two steps in LDS, two workgroups a unit (two_rings of gemm_shape.h).
+template <bool kScale, bool kDeep>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) gemm_rows_eight_kernel(const GemmArgs p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char gemm_smem[];
+  gemm_rows_small<kScale, kDeep, 2, 512>(p, gemm_smem, blockIdx.x, gridDim.x);
+}
+
 // Tiles of 256 x 256 (eight waves of 128 x 64), 256 x 192 (eight of 64 x 96) or 192 x 192 (eight of 48 x 96); the fewer accumulators and
 // columns of the latter two leave LDS for a third step of the rows of A, or of both: a step of K 2304 waits for rows that no other
 // unit has fetched yet, and with two steps its loads have one step to come (256 x 192 with two steps of both 63.7 us, with three of

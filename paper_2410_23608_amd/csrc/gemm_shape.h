@@ -88,5 +88,12 @@ inline bool large_tiles(int m_cap, bool counted, int ncols, int kc) {      // co
 inline bool ring_tiles(int m_cap, bool counted, int ncols) {
   return gemm_tiles<long>(counted ? m_cap - m_cap / 4 : m_cap, ncols, 128) <= 256;
 }
+// Eight waves and two steps, two a unit: where one a unit might need a second round and has few steps to gain on.  us, 19110 rows of 192 -> 192
+// (300 tiles of capacity), half | nine tenths live, two a unit in four waves 5.4 | 6.9, one a unit 5.1 | 9.2, so 5.0 | 7.1; with copied rows 7.7 | 9.3, 8.1 |
+// 12.7, 7.0 | 9.4; 19600 of 256 -> 256 copied 8.2 | 11.3, 8.7 | 14.1, 7.8 | 10.9; 14000 of 320 8.3 | 11.5, 9.3 | 14.2, 8.1 | 11.3.  With more steps one a
+// unit gains more than a rare second round costs: 12544 of 384 9.0 | 12.5, 8.4 | 15.6, 8.9 | 12.1; 5000 of 1024 14.7 | 20.6, 11.7 | 22.4, 15.4 | 20.1.
+inline bool two_rings(int m_cap, bool counted, int ncols, int kc) {
+  return kc <= 320 && ring_tiles(m_cap, counted, ncols) && gemm_tiles<long>(m_cap, ncols, 128) > 256;
+}
 
 }  // namespace spa

@@ -6,7 +6,7 @@
 // one rounding fewer than multiplying a materialised bf16 r_g.
 //
 // bf16 path: MFMA GEMM on the pipelined loop of gemm_async.h, 64 deep steps, tiles of 128 x 128 (four waves
-// of 64 x 64, two workgroups per unit; eight of 64 x 32 where a unit has one tile), 192 x 192, 256 x 192 or 256 x 256
+// of 64 x 64, two workgroups per unit; eight of 64 x 32 where a unit has one tile, or about one), 192 x 192, 256 x 192 or 256 x 256
 // (eight waves); the same kernels multiply by W as it lies for the input side of the backward (linear_bwd.hip).  With 128 x 128 tiles every flop
 // needs 1/64 byte from L2; the large tiles need two thirds and half of that and win wherever they still fill the chip
 // (gemm_shape.h; what bounds them: gemm_rows.h).  Measured, called again and again: 12544 rows of 768 -> 2304 47 to 49 us =
@@ -54,7 +54,8 @@ template <bool kScale, bool kDeep>
 static int launch_gemm_rows_tile(const char* fn, GemmArgs args, bool big, hipStream_t st) {
   args.rule = large_rule(args.ncols, args.kc, args.residual != nullptr);
   const bool ring = !big && ring_tiles(args.m_cap, args.total != nullptr, args.ncols);
-  const size_t smem = big ? kGemmBigLds : ring ? kGemmRingLds : kGemmSmallLds;
+  const bool eight = !big && two_rings(args.m_cap, args.total != nullptr, args.ncols, args.kc);
+  const size_t smem = big ? kGemmBigLds : ring && !eight ? kGemmRingLds : kGemmSmallLds;
   const long tiles = gemm_tiles<long>(args.m_cap, args.ncols, big ? 192 : 128);     // (no less than with 256)
   SPA_REQUIRE(tiles + 8 < 2147483647L / 2, SPA_ERR_INVALID_ARG, "%s: too many tiles", fn);
   const long tiles8 = (tiles + 7) / 8 * 8;
@@ -63,7 +64,10 @@ static int launch_gemm_rows_tile(const char* fn, GemmArgs args, bool big, hipStr
                      : cfg == 8  ? gemm_rows_big_kernel<kScale, kDeep, Large::k256>
                      : cfg == 10 ? gemm_rows_big_kernel<kScale, kDeep, Large::k256x192>
                                  : gemm_rows_big_kernel<kScale, kDeep, Large::kByRows>;
-  const auto kernel = big ? large : ring ? gemm_rows_ring_kernel<kScale, kDeep> : gemm_rows_small_kernel<kScale, kDeep>;
+  const auto kernel = big     ? large
+                      : eight ? gemm_rows_eight_kernel<kScale, kDeep>
+                      : ring  ? gemm_rows_ring_kernel<kScale, kDeep>
+                              : gemm_rows_small_kernel<kScale, kDeep>;
   const hipError_t attr = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   SPA_REQUIRE(attr == hipSuccess, SPA_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, smem);
   hipLaunchKernelGGL(kernel, dim3((unsigned)(big ? std::min(tiles8, 256L) : tiles8)), dim3(big || ring ? 512 : 256), smem, st, args);

@@ -16,7 +16,9 @@ def _rnd(seed):
 # line on either side (43520 and 43776 rows of one tile of columns: 255 and 257 tiles by three quarters), with more live tiles than units
 @pytest.mark.parametrize("cap,T,K,N", [(1, 1, 8, 8), (300, 0, 64, 64), (130, 129, 120, 136), (400, 256, 192, 128), (200, 128, 248, 200),
                                        (257, 257, 256, 264), (500, 333, 264, 8), (129, 100, 320, 384), (1000, 1, 576, 248),
-                                       (43520, 33000, 72, 128), (43776, 33000, 72, 128)])
+                                       (43520, 33000, 72, 128), (43776, 33000, 72, 128),
+                                       # capacities of more tiles than units: eight waves two a unit up to 320 elements, one a unit beyond
+                                       (33000, 30000, 320, 120), (33000, 16000, 8, 128), (16600, 16001, 248, 200), (33000, 30000, 328, 120)])
 def test_one_tile_a_unit(cap, T, K, N):
     from paper_2410_23608_amd import spa
     rnd = _rnd(cap + T + K)
