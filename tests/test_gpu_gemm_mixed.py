@@ -5,9 +5,12 @@ import torch
 
 pytestmark = pytest.mark.gpu
 
-# cap, live rows, contraction (1 to 6 steps of 64, whole and partial), columns.  By the rule (14): a whole round of 256 x 256 and one row,
-# a part of a tile or two tiles of 256 x 192 behind it; few rows, their copy left to units with a tile and without; one row; none.
-SHAPES = [(500, 257, 8, 192), (700, 511, 64, 200), (900, 769, 136, 376), (300, 256, 264, 584), (300, 1, 328, 8), (64, 0, 64, 64),
+# cap, live rows, contraction (1 to 10 steps of 64, whole and partial), columns.  By the rule (14): one or two whole rounds of 256 x 256 and
+# one or two of 256 x 192 behind them, in all three calls (tests/test_large_plan.py asks the rule).
+SPLIT = [(11000, 10913, 584, 2304), (12300, 12193, 200, 2304), (12460, 12449, 8, 2304), (16600, 16545, 72, 2304), (23600, 23554, 136, 1544),
+         (32800, 32770, 264, 768)]
+# 192 x 192 or 256 x 192 alone: edges, few rows, their copy left to units with a tile and without; one row; none.
+SHAPES = SPLIT + [(500, 257, 8, 192), (700, 511, 64, 200), (900, 769, 136, 376), (300, 256, 264, 584), (300, 1, 328, 8), (64, 0, 64, 64),
           (4400, 4097, 72, 4096), (4400, 4351, 200, 4088), (9000, 4609, 64, 4096), (30000, 300, 64, 1024), (9000, 8300, 64, 768)]
 
 

@@ -50,10 +50,19 @@ def test_the_measured_launches(plan):
 
 
 def test_rows_are_whole_tiles_and_the_rounds_hold_them(plan):
-    calls = [(rows, n, k, more, copy) for rows in (0, 1, 255, 256, 257, 4096, 4097, 65535, 1 << 20) for n in (8, 192, 200, 768, 2304, 8192)
+    calls = [(rows, n, k, more, copy) for rows in (0, 1, 255, 256, 257, 4096, 4097, 12449, 16545, 65535, 1 << 20) for n in (8, 192, 200, 768, 2304, 8192)
              for k, more, copy in ((8, 0, 0), (768, 5000, 1), (4096, 1 << 30, 0))]
     for (rows, n, k, more, copy), (medium, wide, rounds, rest) in zip(calls, plan(calls)):
         assert 0 <= wide <= rows and (wide == rows or wide % 256 == 0), (rows, n)
         up = lambda a, b: (a + b - 1) // b
         first = up(rows, 192) * up(n, 192) if medium else up(wide, 256) * up(n, 256)
-        assert up(first, 256) <= rounds and up(up(rows - wide, 256) * up(n, 192), 256) <= (rounds if medium else rest) or medium, (rows, n)
+        assert up(first, 256) <= rounds, (rows, n)
+        assert (wide, rest) == (0, 0) if medium else up(up(rows - wide, 256) * up(n, 192), 256) <= rest, (rows, n)
+
+
+def test_the_shapes_of_the_two_shape_launch_are_two(plan):
+    from test_gpu_gemm_mixed import SPLIT
+    calls = [(T, n, k, more, copy) for cap, T, k, n in SPLIT for more, copy in ((0, 0), (cap - T, 1), (cap - T, 0))]
+    got = plan(calls)
+    assert all(not medium and 0 < wide < c[0] and rest > 0 for c, (medium, wide, _, rest) in zip(calls, got))
+    assert {g[2:] for g in got} == {(1, 1), (1, 2), (2, 1)}
