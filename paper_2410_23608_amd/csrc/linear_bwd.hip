@@ -624,7 +624,7 @@ static int launch_weight(const char* fn, WeightCall& c, WeightShape shape, hipSt
   if (shape.fold && grid <= 256 && kLbRingLds + named <= kLdsBytes) {
     const auto ring = gi ? (xi ? weight_gemm_ring_kernel<true, true> : weight_gemm_ring_kernel<true, false>)
                          : (xi ? weight_gemm_ring_kernel<false, true> : weight_gemm_ring_kernel<false, false>);
-    if (int rc = reserve_lds(fn, (const void*)ring, kLbRingLds + named)) return rc;
+    if (int rc = reserve_lds(fn, (const void*)ring, kLdsBytes)) return rc;      // (one value whatever the call, other threads launch too)
     hipLaunchKernelGGL(ring, dim3(grid), dim3(512), kLbRingLds + named, st, c.a);
     return check_launch(fn);
   }
