@@ -24,10 +24,9 @@ __device__ __forceinline__ int gemm_rows_tiles(const GemmArgs& p, unsigned char*
                                       typename std::conditional<E == 16, DeepBlocks<BN, THREADS>, DeepPieces<BN, THREADS>>::type>::type;
   __bf16* lds = reinterpret_cast<__bf16*>(gemm_smem);
   constexpr int NC = TN * E, ORS = NC + 8, PIECES = NC / 8, PER_LANE = E * PIECES / 64, STAGING = WGM * WGN * 2 * E * ORS;
-  __shared__ float bias_s[BN];
-  __shared__ int o_row[BM];
-  static_assert(E * PIECES % 64 == 0 && STAGING % 8 == 0 && STAGING + 2 * (BM + BN) <= (SA * BM + SB * BN) * kGaK,
-                "output staging and tables fit in the operand buffers");
+  __shared__ float bias_s[BN];     // bias of the tile's output columns (0 past the edge or without bias)
+  __shared__ int o_row[BM];        // output row of every tile row
+  static_assert(E * PIECES % 64 == 0 && STAGING <= (SA * BM + SB * BN) * kGaK, "output staging fits in the operand buffers");
 
   // Tile order.  Workgroup ids go to the 8 XCDs round-robin (id % 8) and each XCD has its own
   // L2.  The LIVE tiles (the row count is only known here, on the device) are numbered m-major
@@ -193,7 +192,8 @@ __device__ __forceinline__ void gemm_rows_small(const GemmArgs& p, unsigned char
 }
 
 constexpr size_t kGemmSmallLds = (size_t)2 * (128 + 128) * kGaK * sizeof(__bf16), kGemmRingLds = 2 * kGemmSmallLds;
-constexpr size_t kGemmBigLds = (size_t)(3 * 192 + 3 * 192) * kGaK * sizeof(__bf16);    // (three of 192 + 192 need less)
+// steps of A and of B in LDS: three of 192 + 192, three of 256 and two of 192, two of 256 + 256
+constexpr size_t kGemmBigLds = (size_t)std::max({3 * 192 + 3 * 192, 3 * 256 + 2 * 192, 2 * 256 + 2 * 256}) * kGaK * sizeof(__bf16);
 
 // 128 x 128 tiles: four waves of 64 x 64, two workgroups per unit.
 template <bool kScale, bool kDeep>

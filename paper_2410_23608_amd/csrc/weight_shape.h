@@ -59,11 +59,12 @@ inline int weight_most_splits(int M_cap, int K, int N_out, int forced) {
   return weight_splits(M_cap, K, N_out, forced);
 }
 // The chunks of a block's sides in the one launch: a chunk more shortens the walk over the rows and writes and reads a partial result more, which
-// come out even where the number is as sqrt(rows) / columns; the factor is that of the best steps measured, with 1 to 16 chunks.  Two
-// thirds of that where the workgroups, with the input side at half of the rows live, are then two a unit and no more.  us a training step of
+// come out even where the number is as sqrt(rows) / columns; the factor is that of the best steps measured, with 1 to 16 chunks.  us a training step of
 // a block, with as many as fill the chip | so: 3136 rows of 1024 columns of capacity 136 | 122 (1 chunk), 5096 165 | 150 (1), 3136 of 768
-// 111 | 103 (1), 6272 140 | 132 (2), 9408 167 | 164 (2; 3 169), 4704 of 512 96 | 92.4 (3), 9800 124.5 | 117 (5), 19600 184.5 | 177 (7), 12544
-// of 384 113 | 109.4 (7).  Few chunks are long chains of products into one sum: relative error of dW (2-norm, to 64 bits), 2548 rows of 1024
+// 111 | 103 (1), 6272 140 | 132 (2), 9408 167 | 164 (2), 4704 of 512 96 | 92.4 (3), 9800 124.5 | 117 (5), 19600 184.5 | 177 (7), 12544
+// of 384 113 | 109.4 (7).  Down to two thirds of that where the workgroups, with the input side at half of the rows live, are then two a unit and no
+// more, so that none starts late: 9408 rows of 768 in two | three chunks 161.6 | 169.8, 15680 of 512 in four | five | six 151.0 | 154.7 | 152.8, 11956 of
+// 448 in five, the wide side's in six 119.5 | 124.6.  Few chunks are long chains of products into one sum: relative error of dW (2-norm, to 64 bits), 2548 rows of 1024
 // columns in one chunk 3.05e-7 as one sum, 1.06e-7 as sums of 256 rows (in four chunks 1.12e-7), 9800 of 512 in seven 2.26e-7, 1.11e-7 (in ten
 // and sixteen 1.60e-7); 1 us of a step of 103 to 150.
 // The narrow side is a chain of steps on few units where it is called alone, so its chunks are of about 1325 live rows at most where that
@@ -74,10 +75,10 @@ inline int weight_most_splits(int M_cap, int K, int N_out, int forced) {
 inline int block_splits(int M_cap, int C, int N_out) {
   const long narrow = gemm_tiles<long>(C, C, kWeightEdge), wide = gemm_tiles<long>(3L * C, C, kWeightEdge);
   const long left = 512 - gemm_tiles<long>(std::max(M_cap / 2, 1), C, kWeightEdge), beside = left / (narrow + wide);
-  long best = (long)(std::sqrt(700. * M_cap) / C);
+  long best = std::max((long)(std::sqrt(700. * M_cap) / C), 1L);
   if (beside < best && 3 * beside >= 2 * best) best = beside;
-  if (N_out == C && M_cap > 3300 * std::max(best, 1L)) {
-    long more = (M_cap + 1325) / 2650;
+  if (N_out == C && M_cap > 3300 * best) {
+    long more = (M_cap + 1325L) / 2650;
     if (more * narrow + best * wide > left) more = std::max(more, std::min(3 * best, 256 / narrow));
     best = std::max(best, std::min(more, weight_most_splits(M_cap, C, N_out, 0) - 1L));      // (fewer: the sums stay apart)
   }
