@@ -229,7 +229,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) g
 // 21.5 (1), 13500 rows 30.3 (2) | 21.2 (1) | 22.0 (1); rows of 2304 columns: 7526 31.7 (2) | 36.8 (2) | 43.5 (2), 11540 47.9 (3) |
 // 55 (3) | 46 (2), 12544 61 (4) | 58 (3) | 51 (2), the first 7168 rows of them 256 x 256 and the others 256 x 192 47.4, 15052 66 (4) |
 // 63.5 (3) | 71 (3); K 2304, rows of 768 columns: 11540 47 (1) | 51 (1) | 60 (1), 12544 77 (2) | 52.8 (1) | 61 (1).  No unit is busy
-// for much more than a third of a launch (matrix pipe 32 %, LDS 29 %, address units 31 % of QKV's with 256 x 256; the L2 delivers
+// for much more than a third of a launch (matrix pipe 35 %, LDS 19 %, address units 34 % of QKV's with both shapes; the L2 delivers
 // 11 TB/s in the loop, 6.5 over the launch): what binds is the order within a step, wait, barrier, loads, products, with one
 // workgroup a unit to fill the gaps.  Four waves of 128 x 128 (a third fewer LDS reads) took 56 us for 12544 rows of 2304 columns.
 enum class Large { kByRows, k192, k256, k256x192 };        // kByRows: the plan for the live rows (gemm_shape.h)

@@ -75,6 +75,7 @@ def short(name: str) -> str:
         return m.group(1) + "<" + template_args(args if re.search(r"L[ib]n?\d+$", args) is None else args + "E") + ">"
     if (m := re.match(r"_ZN3spa\d+([a-z_0-9]+?_kernel)E", name)):       # (no template arguments)
         return m.group(1)
+    name = re.sub(r"\(spa::\w+\)", "", name)                             # (the type of an enumerator among the arguments)
     name = re.sub(r"\(.*", "", name).replace("void ", "").replace("spa::", "")
     return name.strip()
 
